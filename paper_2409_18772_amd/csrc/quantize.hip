@@ -187,8 +187,9 @@ __global__ __launch_bounds__(256) void absmax_cols_kernel(const float* __restric
 }
 
 // The row maxima of A and the column maxima of B (already cleared) in one launch: workgroups [0, nbA) take four rows of
-// A each, one per wave, the rest a 256-column slab of B.
-template <bool TINY>
+// A each, one per wave, the rest a 256-column slab of B.  TINY_A, TINY_B: the operand's own rows have fewer than four
+// elements (K or N); one of them may while the other's are long.
+template <bool TINY_A, bool TINY_B>
 __global__ __launch_bounds__(256) void absmax_pair_kernel(const float* __restrict__ A, int lda, int M, int K,
                                                           float* __restrict__ amaxA, int nbA,
                                                           const float* __restrict__ B, int ldb, int N, int rows_per_block,
@@ -196,7 +197,7 @@ __global__ __launch_bounds__(256) void absmax_pair_kernel(const float* __restric
     __shared__ float4 red[4][64];
     if ((int)blockIdx.x >= nbA) {
         const int id = blockIdx.x - nbA;
-        absmax_cols_body<TINY>(B, ldb, K, N, rows_per_block, amaxB, q, nullptr, id % col_blocks, id / col_blocks, red);
+        absmax_cols_body<TINY_B>(B, ldb, K, N, rows_per_block, amaxB, q, nullptr, id % col_blocks, id / col_blocks, red);
         return;
     }
     const int lane = threadIdx.x & 63, row = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -206,7 +207,7 @@ __global__ __launch_bounds__(256) void absmax_pair_kernel(const float* __restric
     for (int k = lane * 4; k < K; k += 8 * 256) {       // eight loads in flight; past the end the last columns again
         float4 v[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = TINY ? load4_tail(xp, 0, K) : load4u(xp + min(k + 256 * u, K - 4));
+        for (int u = 0; u < 8; ++u) v[u] = TINY_A ? load4_tail(xp, 0, K) : load4u(xp + min(k + 256 * u, K - 4));
 #pragma unroll
         for (int u = 0; u < 8; ++u)
             m = fmaxf(fmaxf(m, fabsf(v[u].x)), fmaxf(fabsf(v[u].y), fmaxf(fabsf(v[u].z), fabsf(v[u].w))));
@@ -348,12 +349,12 @@ int launch_absmax_pair(const float* A, int lda, int M, int K, float* amaxA, cons
     const ColSlabs p = N > 0 ? plan_slabs(K, N) : ColSlabs{1, 0, 1};
     const int nbA = ceil_div(M, 4);
     dim3 grid(nbA + p.col_blocks * p.slabs);
-    if (K >= 4 && (N >= 4 || N == 0))
-        hipLaunchKernelGGL(absmax_pair_kernel<false>, grid, dim3(256), 0, st, A, lda, M, K, amaxA, nbA, B, ldb, N,
-                           p.rows_per_block, reinterpret_cast<uint32_t*>(amaxB), q, p.col_blocks);
-    else
-        hipLaunchKernelGGL(absmax_pair_kernel<true>, grid, dim3(256), 0, st, A, lda, M, K, amaxA, nbA, B, ldb, N,
-                           p.rows_per_block, reinterpret_cast<uint32_t*>(amaxB), q, p.col_blocks);
+#define LRQ_ABSMAX(TA, TB)                                                                                              \
+    hipLaunchKernelGGL((absmax_pair_kernel<TA, TB>), grid, dim3(256), 0, st, A, lda, M, K, amaxA, nbA, B, ldb, N,       \
+                       p.rows_per_block, reinterpret_cast<uint32_t*>(amaxB), q, p.col_blocks)
+    if (K >= 4) { if (N >= 4) LRQ_ABSMAX(false, false); else LRQ_ABSMAX(false, true); }
+    else        { if (N >= 4) LRQ_ABSMAX(true, false); else LRQ_ABSMAX(true, true); }
+#undef LRQ_ABSMAX
     LRQ_CHECK_LAUNCH();
     if (per_tensor) {
         if (M > 0 && N > 0) hipLaunchKernelGGL(tensor_max_kernel, dim3(2), dim3(1024), 0, st, amaxA, M, amaxB, N);

@@ -199,6 +199,39 @@ def test_ragged_operands(M, N, K, r, p, q, pad, mode):
     assert np.array_equal(to_np(L.lrqmm_gemm(Aq, amA, BqT, amB, 8, fa, fb)), C)
 
 
+# Extents below one 16-byte load (four values), one operand at a time and together: N < 4 against long rows of A, K < 4
+# against wide rows of B, both, M < 4; the last shape has enough elements for the two-stream schedule.
+TINY_EXTENTS = [(100, 1, 300, 1), (70, 3, 517, 3), (100, 2, 1000, 1), (90, 200, 3, 2), (100, 100, 3, 1), (300, 2, 1, 1),
+                (5, 3, 2, 2), (2, 300, 300, 2), (3, 5, 4, 3), (4500, 3, 3000, 2)]
+
+
+@pytest.mark.parametrize("tensor", [False, True])
+@pytest.mark.parametrize("M,N,K,r", TINY_EXTENTS)
+def test_extents_below_one_load(M, N, K, r, tensor):
+    """Group maxima, codes and both factorizations where an extent is smaller than a load: against the oracle, and against
+    the separate calls, whose quantizers are kernels of their own (a wrong maximum anywhere in an operand moves C by the
+    size of its terms; at ranks this small the two differ by float32 roundings of the sketch products)."""
+    import torch
+    import paper_2409_18772_amd as L
+    A, B = wl.random_matrix("normal", M, K, seed=71), wl.random_matrix("normal", K, N, seed=72)
+    dA, dB = to_dev(A), to_dev(B)
+    sm = L.SCALE_TENSOR if tensor else L.SCALE_VECTOR
+    say("tiny extents", M, N, K, "rank", r, "tensor", tensor)
+    D = torch.empty((M, N), dtype=torch.float32, device="cuda")
+    C = to_np(L.lrqmm_matmul_ex(dA, dB, D, 8, r, 0, 1, seed=9, scale_mode=sm))
+    ref = o.lrqmm(A, B, 8, r, 0, 1, seed=9, per_tensor=tensor)
+    d = rel_fro(ref["C"], C)
+    say("gpu vs oracle", d, "tol", tol_for(ref))
+    assert d < tol_for(ref)
+    check_elementwise(C, ref, r, what=f"tiny extents {M}x{N}x{K}")
+    Aq, amA = L.lrqmm_quantize_ex(dA, L.AXIS_ROW, 8, o.FLOOR, sm)
+    BqT, amB = L.lrqmm_quantize_ex(dB, L.AXIS_COL, 8, o.FLOOR, sm)
+    assert np.array_equal(to_np(Aq), ref["Aq"]) and np.array_equal(to_np(BqT), ref["Bq"].T)
+    fa = L.lrqmm_rsvd_ex(dA, amA, L.AXIS_ROW, 8, r, 0, 1, seed=9)
+    fb = L.lrqmm_rsvd_ex(dB, amB, L.AXIS_COL, 8, r, 0, 1, seed=9)
+    assert rel_fro(to_np(L.lrqmm_gemm(Aq, amA, BqT, amB, 8, fa, fb)), C) < 2 * tol_for(ref)
+
+
 FULL = ["c2_4096_int8_r16", "c3_4096_int4_r32_outliers"]
 
 
