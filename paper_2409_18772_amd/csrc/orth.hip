@@ -61,7 +61,7 @@ __global__ __launch_bounds__(256) void reduce_gram_kernel(GramJob a, GramJob b, 
     const int n = job.n, splits = job.splits;
     const int rb = blk * job.rows_per_block;
     const int re = min(n, rb + job.rows_per_block);
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int li = lane & 15, kq = lane >> 4;
     v4d acc[PW];
 #pragma unroll
@@ -70,30 +70,51 @@ __global__ __launch_bounds__(256) void reduce_gram_kernel(GramJob a, GramJob b, 
     for (int r0 = rb; r0 < re; r0 += TR) {
         if (r0 > rb) __syncthreads();
         // The splits are summed MAX_SPLITS at a time; the loads of a batch, over all of the thread's groups, are issued
-        // before its first add (branch free: clamped row and split indices, masked afterwards).
+        // before its first add (branch free: clamped row and split indices, masked afterwards).  SG == 1: split and tile
+        // are the same for the whole workgroup, so an address is a scalar base and one 32-bit lane offset per group.
+        // 158 registers at 48 columns and 64 rows: with 174 the kernel did not start beside two workgroups of the other
+        // chain's R^T W pass (176 registers each of a SIMD's 512) and waited for one to end: 8192^3, 40 columns, 28 -> 18 us
+        // per launch on average, the call 1.57 -> 1.49 ms.
         float4 v[ITER];
 #pragma unroll
         for (int it = 0; it < ITER; ++it) v[it] = make_float4(0.f, 0.f, 0.f, 0.f);
-        const int longest = (splits + SG - 1) / SG;
-        for (int s0 = 0; s0 < longest; s0 += MAX_SPLITS) {
-            float4 p[ITER][MAX_SPLITS];
+        if constexpr (SG == 1) {
+            uint32_t off[ITER];
 #pragma unroll
             for (int it = 0; it < ITER; ++it) {
-                const int idx = min((int)threadIdx.x + 256 * it, Q * SG - 1);
-                const int e = idx % Q, sg = idx / Q;
-                const int sb = sg * splits / SG + s0, se = (sg + 1) * splits / SG;
-                const float* src = partial + (size_t)min(r0 + e / Q4, re - 1) * LP + (e % Q4) * 4;
-#pragma unroll
-                for (int sp = 0; sp < MAX_SPLITS; ++sp)
-                    p[it][sp] = *reinterpret_cast<const float4*>(src + (size_t)max(0, min(sb + sp, se - 1)) * plane);
+                const int e = min((int)threadIdx.x + 256 * it, Q - 1);
+                off[it] = (uint32_t)(min(e / Q4, re - 1 - r0) * LP + (e % Q4) * 4);
             }
+            for (int s0 = 0; s0 < splits; s0 += MAX_SPLITS) {
+                float4 p[MAX_SPLITS][ITER];
 #pragma unroll
-            for (int it = 0; it < ITER; ++it) {
-                const int sg = min((int)threadIdx.x + 256 * it, Q * SG - 1) / Q;
-                const int count = (sg + 1) * splits / SG - (sg * splits / SG + s0);
+                for (int it = 0; it < ITER; ++it)
+#pragma unroll
+                    for (int sp = 0; sp < MAX_SPLITS; ++sp)
+                        p[sp][it] = *reinterpret_cast<const float4*>(partial + (size_t)min(s0 + sp, splits - 1) * plane +
+                                                                     (size_t)r0 * LP + off[it]);
+#pragma unroll
+                for (int it = 0; it < ITER; ++it)
+#pragma unroll
+                    for (int sp = 0; sp < MAX_SPLITS; ++sp)
+                        if (s0 + sp < splits) {
+                            v[it].x += p[sp][it].x; v[it].y += p[sp][it].y;
+                            v[it].z += p[sp][it].z; v[it].w += p[sp][it].w;
+                        }
+            }
+        } else {
+            const int sg = threadIdx.x / Q, e = threadIdx.x % Q;
+            const int longest = (splits + SG - 1) / SG, se = (sg + 1) * splits / SG;
+            const float* src = partial + (size_t)min(r0 + e / Q4, re - 1) * LP + (e % Q4) * 4;
+            for (int s0 = 0; s0 < longest; s0 += MAX_SPLITS) {
+                const int sb = sg * splits / SG + s0;
+                float4 p[MAX_SPLITS];
 #pragma unroll
                 for (int sp = 0; sp < MAX_SPLITS; ++sp)
-                    if (sp < count) { v[it].x += p[it][sp].x; v[it].y += p[it][sp].y; v[it].z += p[it][sp].z; v[it].w += p[it][sp].w; }
+                    p[sp] = *reinterpret_cast<const float4*>(src + (size_t)max(0, min(sb + sp, se - 1)) * plane);
+#pragma unroll
+                for (int sp = 0; sp < MAX_SPLITS; ++sp)
+                    if (sb + sp < se) { v[0].x += p[sp].x; v[0].y += p[sp].y; v[0].z += p[sp].z; v[0].w += p[sp].w; }
             }
         }
         if (SG > 1) {
