@@ -1134,6 +1134,17 @@ __global__ __launch_bounds__(256, 2) void resid_mul_t_bf16_kernel(PassJob a, Pas
     else          resid_mul_t_bf16_body<NT, 1, PL, FULL, TINY>(b, q, (id - nb0) % b.nbx, (id - nb0) / b.nbx, red);
 }
 
+// One operand alone (two-chain calls, lrqmm_rsvd) at 48 columns: holding both forms costs the kernel above 176 registers,
+// two waves per SIMD; one form takes 154 to 164, three.  A launch is about 512 workgroups of one wave per SIMD, often
+// more (ceil), and those beyond two per CU ran as a second round: 7168^3 (560 workgroups per pass, 40 columns) 1.172 ->
+// 1.159 ms per call, 5120^3 0.637 -> 0.630, 10240^3 2.37 -> 2.35; 8192^3 (512 workgroups) 1.490 -> 1.499.  At 32
+// columns at least three waves fit in either form, at 64 and 80 two.
+template <int NT, int AXIS, int PL, bool FULL>
+__global__ __launch_bounds__(256, 2) void resid_mul_t_bf16_one_kernel(PassJob a, QuantParams q) {
+    __shared__ __align__(16) float red[64 * NT * 16];
+    resid_mul_t_bf16_body<NT, AXIS, PL, FULL, false>(a, q, (int)blockIdx.x % a.nbx, (int)blockIdx.x / a.nbx, red);
+}
+
 // ---------------------------------------------------------------------------
 // launch plans and dispatch
 // ---------------------------------------------------------------------------
@@ -1233,6 +1244,18 @@ static int dispatch_t(const PassOperand* op, int nop, QuantParams q, hipStream_t
     }
     if constexpr (NT == 1) {        // (fewer than four columns leave room for no wider sketch)
         if (tiny) hipLaunchKernelGGL((resid_mul_t_bf16_kernel<NT, PL, false, true>), LRQ_PAIR_ARGS(p, 256));
+    }
+    if constexpr (NT == 3) {
+        if (nop == 1) {
+            const int axis = op[0].axis;
+            const dim3 grid(p.nb[axis]);
+#define LRQ_T1(AX, FL) hipLaunchKernelGGL((resid_mul_t_bf16_one_kernel<NT, AX, PL, FL>), grid, dim3(256), 0, st, p.job[AX], q)
+            if (axis == 0) { if (full) LRQ_T1(0, true); else LRQ_T1(0, false); }
+            else           { if (full) LRQ_T1(1, true); else LRQ_T1(1, false); }
+#undef LRQ_T1
+            LRQ_CHECK_LAUNCH();
+            return LRQMM_OK;
+        }
     }
     if (!tiny && full) hipLaunchKernelGGL((resid_mul_t_bf16_kernel<NT, PL, true>), LRQ_PAIR_ARGS(p, 256));
     else if (!tiny)    hipLaunchKernelGGL((resid_mul_t_bf16_kernel<NT, PL, false>), LRQ_PAIR_ARGS(p, 256));
