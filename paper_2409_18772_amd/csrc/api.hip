@@ -246,13 +246,13 @@ int planes_values(int p) { return p == LRQMM_PREC_BF16 ? 1 : (p == LRQMM_PREC_BF
 // Whether the two operands' factorizations run as two chains on two streams instead of advancing together, one launch
 // per step for both.  Together they need half the launches, which bound small problems, and no events; as two chains the
 // single-workgroup steps of one fall beside the other's passes, which pays once the passes are as long as those steps.
-// Measured, together / two chains, sketches of 24 and 40 columns: 1024^3 204 / 226 and 302 / 321 us; 2048^3 250 / 264 and
-// 355 / 366; 3072^3 324 / 325 and 453 / 446; 4096^3 392 / 380 and 499 / 485; 12288^3 3.39 / 3.21 and 3.69 / 3.54 ms.
-// Beyond, a pass of one operand fills the chip for so long that the other chain's single-workgroup kernels wait for it
-// (16384^3, 80 columns: 9.48 / 9.69 ms).
+// Measured, together / two chains, us, sketches of 24, 40 and 80 columns (one power iteration): 1024^3 185 / 222,
+// 272 / 292, 593 / 610; 2048^3 247 / 255, 338 / 352, 677 / 690; 3072^3 320 / 325, 433 / 420, 792 / 791; 4096^3 390 / 383,
+// 482 / 467, 846 / 850; 8192^3 1354 / 1342, 1614 / 1501, 1980 / 1904; 12288^3 3443 / 3246, 3853 / 3686, 4285 / 4252;
+// 16384^3 6604 / 6628, 7648 / 7418, 8271 / 8288.
 bool two_chains(int M, int N, int K) {
     const long long elements = (long long)M * K + (long long)K * N;
-    return elements > 13000000 && elements < 400000000;
+    return elements > 13000000;
 }
 
 // int32 accumulation is safe when K * (qmax+1)^2 < 2^31.
