@@ -41,7 +41,7 @@ int gram_blocks(int n, int LP) { return max(1, ceil_div(n, gram_rows_per_block(n
 // float64 matrix cores (v_mfma_f64_16x16x4, layout as at apply_kernel) from a TR-row tile in LDS: the 16 x 16 blocks
 // on and above the diagonal are dealt to the four waves, the rest is their mirror image.  Where a tile has fewer
 // 16-byte groups than the workgroup has threads, SG threads share a group and add SG runs of the splits, combined in
-// order.
+// order.  The sums of a factor do not depend on the other job of the launch.
 template <int NT, int TR>
 __global__ __launch_bounds__(256) void reduce_gram_kernel(GramJob a, GramJob b, int nb0) {
     constexpr int LP = NT * 16;
@@ -85,22 +85,35 @@ __global__ __launch_bounds__(256) void reduce_gram_kernel(GramJob a, GramJob b, 
                 const int e = min((int)threadIdx.x + 256 * it, Q - 1);
                 off[it] = (uint32_t)(min(e / Q4, re - 1 - r0) * LP + (e % Q4) * 4);
             }
-            for (int s0 = 0; s0 < splits; s0 += MAX_SPLITS) {
-                float4 p[MAX_SPLITS][ITER];
+            // (a short factor whose partner forces the 64-row tiles keeps the order of its own 16-row ones)
+            constexpr int RUNS16 = 16 * Q4 >= 256 ? 1 : 256 / (16 * Q4);
+            const int nrun = RUNS16 > 1 && job.rows_per_block == 16 ? RUNS16 : 1;
+            for (int run = 0; run < nrun; ++run) {
+                const int sb = run * splits / nrun, se = (run + 1) * splits / nrun;
+                float4 t[ITER];
 #pragma unroll
-                for (int it = 0; it < ITER; ++it)
+                for (int it = 0; it < ITER; ++it) t[it] = make_float4(0.f, 0.f, 0.f, 0.f);
+                for (int s0 = sb; s0 < se; s0 += MAX_SPLITS) {
+                    float4 p[MAX_SPLITS][ITER];
 #pragma unroll
-                    for (int sp = 0; sp < MAX_SPLITS; ++sp)
-                        p[sp][it] = *reinterpret_cast<const float4*>(partial + (size_t)min(s0 + sp, splits - 1) * plane +
-                                                                     (size_t)r0 * LP + off[it]);
+                    for (int it = 0; it < ITER; ++it)
 #pragma unroll
-                for (int it = 0; it < ITER; ++it)
+                        for (int sp = 0; sp < MAX_SPLITS; ++sp)
+                            p[sp][it] = *reinterpret_cast<const float4*>(partial + (size_t)min(s0 + sp, se - 1) * plane +
+                                                                         (size_t)r0 * LP + off[it]);
 #pragma unroll
-                    for (int sp = 0; sp < MAX_SPLITS; ++sp)
-                        if (s0 + sp < splits) {
-                            v[it].x += p[sp][it].x; v[it].y += p[sp][it].y;
-                            v[it].z += p[sp][it].z; v[it].w += p[sp][it].w;
-                        }
+                    for (int it = 0; it < ITER; ++it)
+#pragma unroll
+                        for (int sp = 0; sp < MAX_SPLITS; ++sp)
+                            if (s0 + sp < se) {
+                                t[it].x += p[sp][it].x; t[it].y += p[sp][it].y;
+                                t[it].z += p[sp][it].z; t[it].w += p[sp][it].w;
+                            }
+                }
+#pragma unroll
+                for (int it = 0; it < ITER; ++it) {
+                    v[it].x += t[it].x; v[it].y += t[it].y; v[it].z += t[it].z; v[it].w += t[it].w;
+                }
             }
         } else {
             const int sg = threadIdx.x / Q, e = threadIdx.x % Q;

@@ -199,6 +199,28 @@ def test_ragged_operands(M, N, K, r, p, q, pad, mode):
     assert np.array_equal(to_np(L.lrqmm_gemm(Aq, amA, BqT, amB, 8, fa, fb)), C)
 
 
+def _separate_calls(L, dA, dB, bits, r, p, q, seed):
+    """The whole call as its parts: each operand quantized and factored by itself, then the product."""
+    Aq, amA = L.lrqmm_quantize(dA, L.AXIS_ROW, bits)
+    BqT, amB = L.lrqmm_quantize(dB, L.AXIS_COL, bits)
+    fa = L.lrqmm_rsvd(dA, amA, L.AXIS_ROW, bits, r, p, q, seed=seed)
+    fb = L.lrqmm_rsvd(dB, amB, L.AXIS_COL, bits, r, p, q, seed=seed)
+    return L.lrqmm_gemm(Aq, amA, BqT, amB, bits, fa, fb)
+
+
+@pytest.mark.parametrize("M,N,K,r,p", [(2200, 600, 300, 20, 8), (300, 600, 2200, 17, 0), (2100, 300, 2500, 24, 8),
+                                       (300, 2300, 700, 20, 0)])
+def test_factors_do_not_depend_on_the_other_operand(M, N, K, r, p):
+    """Sketches of 32 padded columns where one operand's tall factor has more than 2048 rows (the Gram kernel takes it in
+    64-row tiles) and the other's has fewer (16-row tiles, the splits of a pass added in two runs), in one launch: the sums
+    of each keep their own order, so the whole call gives the bits of the separate calls."""
+    import paper_2409_18772_amd as L
+    dA, dB = to_dev(wl.random_matrix("normal", M, K, seed=81)), to_dev(wl.random_matrix("uniform01", K, N, seed=82))
+    say("one long factor", M, N, K, r, p)
+    C = to_np(L.lrqmm_matmul(dA, dB, 8, r, p, 1, seed=9))
+    assert np.array_equal(to_np(_separate_calls(L, dA, dB, 8, r, p, 1, 9)), C)
+
+
 # Extents below one 16-byte load (four values), one operand at a time and together: N < 4 against long rows of A, K < 4
 # against wide rows of B, both, M < 4; the last shape has enough elements for the two-stream schedule.
 TINY_EXTENTS = [(100, 1, 300, 1), (70, 3, 517, 3), (100, 2, 1000, 1), (90, 200, 3, 2), (100, 100, 3, 1), (300, 2, 1, 1),
