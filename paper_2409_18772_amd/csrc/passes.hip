@@ -1163,11 +1163,12 @@ static bool pass_n_wide(int rows, int cols, int LP) {
     return LP >= 64 && (long long)ceil_div(rows, 128) * min(MAX_SPLITS, max(1, cols / 128)) >= 256;
 }
 
+// (an empty reduction has no ranges: splits = 0)
 PassPlan plan_pass_n(int rows, int cols, int LP) {
     const int unit = LP == 16 ? KCHUNK : 64;        // chunk depth of the kernel
     PassPlan p;
     int s = pick_splits(ceil_div(rows, pass_n_wide(rows, cols, LP) ? 128 : 64), cols, 2 * unit, 512, MAX_SPLITS);
-    p.chunk = ceil_div(ceil_div(cols, s), unit) * unit;
+    p.chunk = max(1, ceil_div(ceil_div(cols, s), unit)) * unit;
     p.splits = ceil_div(cols, p.chunk);
     return p;
 }
@@ -1175,7 +1176,7 @@ PassPlan plan_pass_n(int rows, int cols, int LP) {
 PassPlan plan_codes(int rows, int K) {
     PassPlan p;
     int s = pick_splits(ceil_div(rows, 64), K, 4 * KCHUNK, 512, MAX_SPLITS);
-    p.chunk = ceil_div(ceil_div(K, s), KCHUNK) * KCHUNK;
+    p.chunk = max(1, ceil_div(ceil_div(K, s), KCHUNK)) * KCHUNK;
     p.splits = ceil_div(K, p.chunk);
     return p;
 }
@@ -1185,7 +1186,7 @@ PassPlan plan_pass_t(int rows, int cols) {
     const int s = pick_splits(ceil_div(cols, 64), rows, 128, 512, MAX_SPLITS_T);     // few column strips: many row chunks
     // (a multiple of the 128 rows a workgroup takes per step when there are enough rows)
     const int unit = rows >= 512 * s ? 128 : 32;
-    p.chunk = ceil_div(ceil_div(rows, s), unit) * unit;
+    p.chunk = max(1, ceil_div(ceil_div(rows, s), unit)) * unit;
     p.splits = ceil_div(rows, p.chunk);
     return p;
 }

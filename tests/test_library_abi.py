@@ -64,6 +64,25 @@ def test_host_side_validation_without_a_gpu():
     assert lib.lrqmm_matmul_ex(4, 4, 4, 8, 0, 0, 0, 0, 0, 0, 5, None, 4, None, 4, 1.0, 0.0, None, 4, None, 0, None) == -1     # unknown precision
 
 
+@pytest.mark.parametrize("M,N,K", [(0, 96, 80), (64, 0, 80), (64, 96, 0), (0, 0, 0)])
+def test_workspace_of_an_empty_problem(M, N, K):
+    """An extent of zero with rank > 0: the size query returns, an empty product is accepted and a rank above K refused
+    (in a child process: an integer division by zero would end the interpreter)."""
+    import subprocess
+    import sys
+    import paper_2409_18772_amd as L
+    if not os.path.exists(L.lib_path()):
+        pytest.skip("library not built")
+    code = (f"import paper_2409_18772_amd as L; lib = L.load_library();"
+            f"print(L.lrqmm_workspace_bytes({M}, {N}, {K}, 8, 4),"
+            f"lib.lrqmm_gemm_static({M}, {N}, {K}, 8, 8, *([None] * 10), 1.0, 0.0, None, {N}, None, None))")
+    p = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    assert p.returncode == 0, p.stderr
+    nbytes, status = (int(x) for x in p.stdout.split())
+    assert nbytes > 0
+    assert status in ((0,) if M == 0 or N == 0 else (-1, -4))       # (-4: no GPU to look the static scratch up on)
+
+
 def test_missing_library_fails_loudly(monkeypatch, tmp_path):
     import paper_2409_18772_amd.binding as b
     monkeypatch.setattr(b, "_LIB", None)
