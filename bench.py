@@ -89,6 +89,17 @@ def cpu_baseline(w, A, B, budget_rows: int):
     }
 
 
+def small_tile(M, N):
+    """Tile of the integer product's kernel for outputs below 128 tiles of 256 x 256: the largest with 256 tiles or more."""
+    tm, tn = 128, 64 if N <= 64 else 128
+    tiles = lambda: -(-M // tm) * -(-N // tn)
+    if tiles() < 256:
+        tm = 64
+    if tiles() < 256:
+        tn = 64
+    return tm, tn
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -192,18 +203,23 @@ def main():
     }
     # Quantization + factorization of one operand as one streaming job.  Algorithmic bytes: one read for the
     # group maxima, one per residual product (the first of them also writes the codes), 4 B per element each,
-    # plus 1 B per element of codes.  (Shapes off the guard-free kernels read B once more: maxima, codes,
-    # products.)  With rank 0 only the maxima and the codes remain.  Short rows of A (K <= 576, a sketch of at most
-    # 16 columns) are the one case that gets by with fewer reads than this count: maxima, codes and the first
+    # plus 1 B per element of codes.  With rank 0 only the maxima and the codes remain.  Tall A with short rows (at least
+    # 8192 rows, K <= 576, a sketch of at most
+    # 16 columns) is the one case that gets by with fewer reads than this count: maxima, codes and the first
     # product come from a single read there ("reads_performed").
-    one_read_a = (w.rank > 0 and w.K % 16 == 0 and 16 <= w.K <= 576 and w.rank + w.oversample <= 16)
+    # Up to 13 million operand elements (and no such A) both operands advance together, one launch per step for both:
+    # their stages span the same launches, so each reports both operands' time and is priced with both operands' bytes.
+    one_read_a = (w.rank > 0 and w.M >= 8192 and w.K % 16 == 0 and 16 <= w.K <= 576 and w.rank + w.oversample <= 16)
+    joint = w.rank > 0 and not one_read_a and w.M * w.K + w.K * w.N <= 13000000
     for op, elems in (("a", w.M * w.K), ("b", w.K * w.N)):
         n_reads = (1 + passes) if w.rank > 0 else (1 if op == "a" else 2)
         job_ms = stages["quantize_" + op] + stages["rsvd_" + op]
+        if joint:
+            elems = w.M * w.K + w.K * w.N
         gbs = (4.0 * n_reads + 1.0) * elems / (job_ms * 1e-3) / 1e9
         stage_info["rsvd_" + op].update(passes=passes)
         stage_info["quantize_and_factor_" + op] = {
-            "ms": round(job_ms, 4), "operand_reads": n_reads,
+            "ms": round(job_ms, 4), "operand_reads": n_reads, "both_operands": joint,
             "reads_performed": n_reads - 1 if (op == "a" and one_read_a) else n_reads,
             "algorithmic_GBs": round(gbs, 1), "frac_hbm": round(gbs / PEAK_HBM_GBS, 4)}
     stage_info[gemm_key].update(TOPs=round(achieved, 1), frac_int8_mfma=round(achieved / PEAK_INT8_TOPS, 4))
@@ -269,7 +285,7 @@ def main():
                    "inputs": f"{INPUT_TEXT.get(w.kind, w.kind)}, seeds {w.seed_a}/{w.seed_b}"},
         "roofline": {"kernel": ("int8_gemm256_kernel (int8 MFMA GEMM, raw int32 sums; on the library's third "
                                 "stream beside the single-workgroup SVD kernels)") if early else
-                               (("int8_gemm256_kernel" if large_tiles else ("int8_gemm_kernel (128 x 64 tiles)" if w.N <= 64 else "int8_gemm_kernel (128 x 128 tiles)"))
+                               (("int8_gemm256_kernel" if large_tiles else "int8_gemm_kernel (%d x %d tiles)" % small_tile(w.M, w.N))
                                 + " (int8 MFMA GEMM + fused dequant and rank-2r epilogue)"),
                      **roof,
                      # counter bytes of this kernel on this workload, or null when no summary is tracked for it

@@ -62,9 +62,11 @@ extern "C" {
  * cores: as three bfloat16 planes each with the six plane products of weight >= 2^-16 (float32 accuracy),
  * as two planes with three products (relative error of a product 2^-16), or as plain bfloat16 values (2^-8).
  * Quantization, the integer product, the Gram/Cholesky/eigen steps (float64) and the rank-2r update of C
- * (float32) are the same in every mode.  Shapes that take the float32 matrix-core kernels (sketches of up to
- * 16 columns in LRQMM_PREC_FP32 only; reduction lengths that are no multiple of 16 in the code products) are
- * computed at full precision.  `bench.py --precision-modes` measures time and error of every mode. */
+ * (float32) are the same in every mode.  Float32-accurate in every mode are code products over a
+ * reduction that is no multiple of 16, and the first product of an A with short rows (vector scales, K <= 576
+ * and a multiple of 16, 16-byte aligned rows, a sketch of up to 16 columns).  In LRQMM_PREC_FP32 the products of
+ * sketches of up to 16 columns run on the float32 matrix cores, except the first one of lrqmm_matmul, which
+ * also quantizes and takes three planes.  `bench.py --precision-modes` measures time and error of every mode. */
 #define LRQMM_PREC_FP32    0     /* default: float32-equivalent, results match the float64 oracle to 1e-5 */
 #define LRQMM_PREC_BF16X2  1     /* two bfloat16 planes per operand */
 #define LRQMM_PREC_BF16    2     /* one bfloat16 plane per operand: "half precision" */
@@ -293,9 +295,10 @@ LRQMM_API int lrqmm_residual_matmul(int M, int N, int K, int bits, int terms, in
  * synchronisation), writes the per-stage mean duration in milliseconds to
  * stage_ms[LRQMM_PROF_STAGES] (host pointer) and the number of calls averaged to
  * *ncalls (host pointer), then resets the call counter.  Not thread safe.
- *   stage 0 quantize A   stage 1 RSVD of R_A     (stages 0-1 and 2-3 run concurrently: the larger
- *   stage 2 quantize B   stage 3 RSVD of R_B      operand's on the caller's stream, the other's on
- *                                                 the library's second stream)
+ *   stage 0 quantize A   stage 1 RSVD of R_A     (where the operands advance together, stages 0 and 2 span the
+ *   stage 2 quantize B   stage 3 RSVD of R_B      same launches, and so do 1 and 3: each reports both operands'
+ *                                                 time.  Otherwise A's run on the caller's stream and B's
+ *                                                 beside them on the library's second one)
  *   stage 4 compensation panels
  *   stage 5 int8 GEMM kernel with fused epilogue, or -- when the integer product ran early,
  *           see lrqmm_matmul -- the dequantizing rank-2r update kernel alone

@@ -650,7 +650,7 @@ int lrqmm_matmul_ex(int M, int N, int K, int bits, int rank, int oversample, int
     // The two operands' factorizations advance together on the caller's stream, one launch per step for both, or (see
     // two_chains) B's runs on the side stream beside A's.  A tall operand with short rows (an im2col'd convolution:
     // K = 576) keeps its rows in registers -- maxima, codes and Y from a single read -- in a chain of its own.
-    // (in every precision mode: the one-read pass runs in float32, which the reduced modes allow)
+    // (in every precision mode: the one-read pass runs in float32, which the reduced modes allow; see the row limit)
     const bool short_rows = factored && !per_tensor && quant_sketch_rows_usable(A, lda, M, K, LP, w.Aq);
     const bool one_read = short_rows && M >= LRQ_ONE_READ_MIN_ROWS;
     const bool overlap = one_read || (factored && two_chains(M, N, K));
@@ -661,10 +661,12 @@ int lrqmm_matmul_ex(int M, int N, int K, int bits, int rank, int oversample, int
     // stream, leaves raw int32 sums in C, and the epilogue follows the panels as a kernel of
     // its own.  Used for problems on the large-tile kernel.
     // (the raw sums need D's memory: only when its old contents are not an input and it is dense)
-    // Measured on both sides of the rule (4096^3): at l = 24 the SVD takes ~60 us, the product ~85 us -- it outlasts
-    // the window, holds the CUs the panel kernels need, and the fused kernel after the panels is 3-5 % faster; at
-    // l = 40 (SVD ~115 us) the early product wins by 3-5 %; at 16384^3, l = 80 by 10 % (the SVD and the panel
-    // kernels run beside the product, and the update of wide panels has a faster kernel of its own).
+    // Measured, early / fused after the panels, us per call (one power iteration): l = 24: 4096^3 388 / 378, 6144^3
+    // 804 / 830, 8192^3 1428 / 1346, 16384^3 7032 / 6664; l = 32: 409 / 417, 814 / 886, 1460 / 1414, 7184 / 6860; l = 40:
+    // 466 / 479, 888 / 980, 1499 / 1500, 7388 / 7041; l = 56: 615 / 648, 1019 / 1207, 1708 / 1820, 7711 / 7666; l = 80:
+    // 850 / 893, 1267 / 1531, 1919 / 2151, 8254 / 8622.  The early product pays while the SVD hides enough of it (a
+    // narrow sketch's is too short); a long product outlasts it and holds the CUs the panel kernels need, so that at 32
+    // to 40 columns the fused kernel would be the faster one from 8192^3 on.
     const bool early = factored && rank_update_usable(M, N, C) && beta == 0.0f && ldd == N && ell >= 32;
     if (slot >= 0) g_prof.early[slot] = early;
     hipStream_t gst = early ? side->gemm_stream : pst;

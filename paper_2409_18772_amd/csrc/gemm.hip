@@ -1171,7 +1171,8 @@ int launch_int8_gemm(int M, int N, int K, const int8_t* Aq, const int8_t* BqT, c
         LRQ_CHECK_LAUNCH();
         return LRQMM_OK;
     }
-    // The largest tile of which there is one per CU.  Calls with 128 x 128 tiles throughout / with this rule: 4 tiles of
+    // Outputs of fewer than 128 tiles of 256 x 256 (int8_gemm_large_tiles): the largest of the smaller tiles of which there
+    // are at least 256, one per CU.  Calls with 128 x 128 tiles throughout / with this rule: 4 tiles of
     // 128 x 128 (256^3) 87 / 81 us, 104 (1537 x 1021 x 2311) 279 / 258, 128 (512 x 4096 x 4096 layer) 233 / 222;
     // 256 (2000^3) is the same path.
     int mtw = 2, ntw = N <= 64 ? 1 : 2;

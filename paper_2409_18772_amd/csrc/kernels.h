@@ -66,7 +66,7 @@ struct PassOperand {
 // planes: bfloat16 planes per float32 operand in the matrix-core products (3: float32 accuracy, the default;
 // 2: relative error 2^-16 per product; 1: plain bfloat16 operands) -- the reduced-precision compensation of the
 // Methodology (text after Eq. (gemm_r_split)).  With planes == 3 sketches of up to 16 columns use the float32
-// matrix-core kernels.
+// matrix-core kernels, except in the quantizing N pass, which is on bfloat16 planes at every width.
 // N pass: partial[s][rows][LP] = R[:, chunk s] . W[chunk s, :].
 // quantize: the same launch quantizes the operands from their group maxima (amax): it writes the codes (row-major for
 // axis 0, transposed for axis 1) and the step vectors, then read by the later passes.
@@ -82,7 +82,12 @@ int launch_resid_mul_t(const PassOperand* op, int nop, QuantParams q, int LP, hi
 // reduction cut into eight parts that are added in a fixed order.  Otherwise LRQMM_ERR_UNSUPPORTED and nothing is
 // launched.
 #define LRQ_QSR_MAX_BLOCKS 512
-#define LRQ_ONE_READ_MIN_ROWS 8192       // rows from which lrqmm_matmul takes it (see there)
+// Rows from which lrqmm_matmul takes it.  Below, both operands advance together in half the launches and on one stream.
+// Measured, together / one read, us per call (64 columns of B, sketch of 8): K = 576: 2048 rows 91 / 131, 8192 104 / 130,
+// 16384 112 / 132, 32768 152 / 142, 65536 211 / 185, 100352 290 / 238; K = 64: 8192 81 / 140, 65536 126 / 137, 100352
+// 153 / 150 (its two streams cost the host 105 to 140 us a call by themselves, differing between processes).  The calls
+// that gain have about 15 million elements or more; between this limit and those one read is the slower form.
+#define LRQ_ONE_READ_MIN_ROWS 8192
 bool quant_sketch_rows_usable(const float* X, int ldx, int rows, int cols, int LP, const int8_t* codes);
 int quant_sketch_rows_blocks(int rows);
 int launch_quant_sketch_rows(const float* X, int ldx, int rows, int cols, QuantParams q, const float* W, int LP,

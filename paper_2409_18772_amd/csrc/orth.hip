@@ -6,7 +6,8 @@
 // l x l Gram matrix held in LDS by a single workgroup, in float64 (full-rate on
 // this chip).  Orthonormalization is Cholesky-QR with the Gram matrix, the
 // Cholesky factor, its inverse and the application Q = Y T all in float64; the
-// small SVD is a cyclic Jacobi eigen-solve of B B^T.  Accumulating the Gram in
+// small SVD is an eigen-solve of B B^T, by tridiagonalization from 32 columns on (with a
+// check of its result) and by cyclic Jacobi below that or where the check fails.  Accumulating the Gram in
 // float64 keeps the squared condition number harmless (residual sketches have
 // cond ~ 1e2..1e4).  Columns whose pivot vanishes (rank-deficient sketch, e.g. a
 // zero residual) are dropped: the corresponding columns of Q are zero.

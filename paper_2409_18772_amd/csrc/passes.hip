@@ -80,7 +80,7 @@ struct PassJob {
 
 // ---------------------------------------------------------------------------
 // N-type: partial[split][rows][LP] = R[:, k-range] . W[k-range, :]
-// grid (ceil(rows/64), splits); 4 waves x 16 rows.  Per KCHUNK columns: the W chunk goes
+// One workgroup per 64 rows and range of the reduction (rows fastest, job a before job b); 4 waves x 16 rows.  Per KCHUNK columns: the W chunk goes
 // through double-buffered LDS, and both the next chunk of X and of W are already in
 // flight (in registers) while the matrix cores work on the current one.
 // ---------------------------------------------------------------------------
@@ -851,7 +851,7 @@ __global__ __launch_bounds__(512, 4) void codes_mul_rows_kernel(CodesJobBf16 j0,
 
 // ---------------------------------------------------------------------------
 // T-type: partial[split][cols][LP] = R[i-range, :]^T . W[i-range, :]
-// grid (ceil(cols/64), splits); the 4 waves of a block share one 64-column strip,
+// One workgroup per 64-column strip and range of rows (strips fastest, job a before job b); its 4 waves share the strip,
 // interleave rows, and merge their accumulators through LDS.
 // A lane's float4 holds columns c0+4c .. c0+4c+3; component t feeds M-tile t, so
 // M-tile t covers the columns {c0 + 4 c + t}.  Likewise N-tile nt covers the W columns
@@ -1218,7 +1218,8 @@ PassPair make_pair(const PassOperand* op, int nop, bool t_type, int rows_per_wg)
 
 // Sketches of up to 16 columns keep the float32 matrix-core kernels in float32 precision (one tile of W columns: the
 // matrix cores are nowhere near busy and splitting operands into planes only adds work; the
-// conv-shaped workload with l = 8 measures 0.37 ms against 0.39 ms); wider ones use the bf16 kernels.
+// conv-shaped workload with l = 8 measures 0.37 ms against 0.39 ms), except in the quantizing pass, which has no float32
+// form; wider ones use the bf16 kernels.
 template <int NT, int PL, bool QOUT>
 static int dispatch_n(const PassOperand* op, int nop, QuantParams q, hipStream_t st) {
     bool wide = NT >= 4, full = true;

@@ -74,8 +74,7 @@ def test_scaled_configs_full_output(name, M, N, K):
 
 
 SHORT_ROWS = [
-    # M, N, K, rank, oversample, power_iters: K a multiple of 16 up to 576 (A's rows are kept in registers), ragged M,
-    # K / 16 a multiple of 4 and not (the four waves of a row group then take unequal shares)
+    # M, N, K, rank, oversample, power_iters: K a multiple of 16 up to 576, ragged M
     (130, 70, 96, 4, 4, 1),
     (1000, 64, 576, 8, 0, 0),
     (257, 40, 640, 12, 4, 2),
@@ -89,14 +88,28 @@ SHORT_ROWS = [
 ]
 
 
+# From 8192 rows on the maxima, codes and sketch product of such an A come from one read: at that limit and beyond, whole
+# and ragged last tiles, the shortest and longest rows, unequal shares of the reduction, and two shapes that are tall
+# enough but not eligible (longer rows, a wider sketch).
+TALL_SHORT_ROWS = [
+    (8192, 64, 576, 8, 0, 0),
+    (8193, 70, 96, 4, 4, 1),
+    (8207, 33, 16, 4, 0, 0),
+    (9000, 24, 208, 5, 0, 1),
+    (10000, 40, 336, 16, 0, 0),
+    (8300, 20, 544, 8, 8, 2),
+    (8200, 40, 640, 12, 4, 1),
+    (8200, 33, 400, 12, 8, 0),
+]
+
+
 @pytest.mark.parametrize("mode", [o.FLOOR, o.NEAREST])
-@pytest.mark.parametrize("M,N,K,r,p,q", SHORT_ROWS)
+@pytest.mark.parametrize("M,N,K,r,p,q", SHORT_ROWS + TALL_SHORT_ROWS)
 def test_short_rows_of_a_single_read(M, N, K, r, p, q, mode):
-    """A with short rows and a sketch of at most 16 columns: row maxima, codes and the sketch product come from
-    one read of A (the third, fourth and fifth shape have longer rows or wider sketches and take the separate
-    kernels).  Checked against
+    """A with short rows and a sketch of at most 16 columns, below and above the number of rows from which row maxima,
+    codes and the sketch product come from one read of A.  Checked against
     the oracle, and against the same call on a copy of A whose row stride (K + 1) rules that kernel out, so that
-    the separate quantization and sketch kernels run: the two differ only in the order in which the sketch
+    the maxima and the quantizing pass run: the two differ only in the order in which the sketch
     product is summed."""
     import torch
     import paper_2409_18772_amd as L
@@ -115,7 +128,7 @@ def test_short_rows_of_a_single_read(M, N, K, r, p, q, mode):
     D = torch.empty((M, N), dtype=torch.float32, device="cuda")
     L.lrqmm_matmul_ex(wide[:, :K], dB, D, 4, r, p, q, seed=9, round_mode=mode)
     assert rel_fro(C, to_np(D)) < tol_for(ref)
-    # a row stride the one-read kernel accepts (K + 4): the same kernel on a window, the same bits
+    # a row stride the one-read kernel accepts (K + 4): the same kernels on a window, the same bits
     wide4 = torch.zeros((M, K + 4), dtype=torch.float32, device="cuda")
     wide4[:, :K] = dA
     D4 = torch.empty((M, N), dtype=torch.float32, device="cuda")
@@ -219,6 +232,21 @@ def test_factors_do_not_depend_on_the_other_operand(M, N, K, r, p):
     say("one long factor", M, N, K, r, p)
     C = to_np(L.lrqmm_matmul(dA, dB, 8, r, p, 1, seed=9))
     assert np.array_equal(to_np(_separate_calls(L, dA, dB, 8, r, p, 1, 9)), C)
+
+
+@pytest.mark.parametrize("M,N,K,r,p", [(640, 300, 512, 16, 8), (640, 300, 512, 32, 8), (640, 300, 512, 60, 12),
+                                       (300, 640, 500, 16, 8), (300, 640, 500, 32, 8), (300, 640, 512, 32, 8),
+                                       (300, 640, 512, 60, 12), (4096, 300, 1024, 60, 12)])
+def test_guard_free_pass_kernels_equal_the_guarded_ones_bitwise(M, N, K, r, p):
+    """A launch of a residual pass is guard-free when every operand in it has whole chunks and strips.  Beside a partner
+    without them an operand of whole tiles takes the guarded form, by itself the guard-free one (A in the first three
+    shapes, B's R.W in the next two, B's Rt.W in two more; in the last also four waves per workgroup in the pair, eight
+    alone): same arithmetic in the same order, so the whole call gives the bits of the separate calls."""
+    import paper_2409_18772_amd as L
+    dA, dB = to_dev(wl.random_matrix("normal", M, K, seed=83)), to_dev(wl.random_matrix("uniform01", K, N, seed=84))
+    say("guarded vs guard-free", M, N, K, r, p)
+    C = to_np(L.lrqmm_matmul(dA, dB, 4, r, p, 1, seed=9))
+    assert np.array_equal(to_np(_separate_calls(L, dA, dB, 4, r, p, 1, 9)), C)
 
 
 # Extents below one 16-byte load (four values), one operand at a time and together: N < 4 against long rows of A, K < 4
@@ -540,13 +568,15 @@ def test_largest_config_properties():
     assert e_lr * 10.0 < e_dq
 
 
-@pytest.mark.parametrize("shape", [(4096, 2048, 512, 28, 4, 1), (300, 200, 260, 28, 4, 1), (3000, 64, 576, 8, 0, 0)])
+@pytest.mark.parametrize("shape", [(4096, 2048, 512, 28, 4, 1), (300, 200, 260, 28, 4, 1), (3000, 64, 576, 8, 0, 0),
+                                   (8300, 64, 576, 8, 0, 0), (4096, 1024, 3000, 16, 8, 0), (4096, 2100, 3000, 28, 4, 0)])
 def test_call_can_be_captured_in_a_graph(shape):
     """The call only enqueues kernels and event waits (its clears are fill kernels), so it may be recorded
     into a HIP graph, side streams included; every replay must reproduce the eager result, with eager work
-    and synchronizations between the replays.  The first shape takes the three-stream schedule (sketch of 32
-    columns on the large-tile kernel), the third the persistent kernels for short rows of A (their launchers
-    ask the runtime for the device's CU count, which a capture has to tolerate)."""
+    and synchronizations between the replays.  First shape: both factorizations on the caller's stream, the integer product
+    on another (sketch of 32 columns, large-tile kernel); second: one stream; third and fourth: the persistent kernels for
+    short rows of A (their launchers ask the runtime for the device's CU count, which a capture has to tolerate), the
+    fourth with B's chain on the side stream; fifth: two chains; sixth: two chains and the early product."""
     import torch
     import paper_2409_18772_amd as L
     M, N, K, r, p, q = shape

@@ -99,6 +99,63 @@ def test_rsvd_rank_deficient_residual_with_a_wide_sketch(k):
     assert np.linalg.norm((U * S) @ Vt - R) <= 1e-5 * max(np.linalg.norm(R), 1e-30)
 
 
+def _whole_rsvd_of(R, ell):
+    """All ell factors of an operand whose residual is R (|R| < 1/2): rounding to nearest with a last column of 127 in every
+    row makes the step 1, every other code 0 and the last column's residual 0.  Returns float64 U, S, Vt of R."""
+    import paper_2409_18772_amd as L
+    X = np.concatenate([R, np.full((R.shape[0], 1), 127.0)], axis=1).astype(np.float32)
+    amax = o.absmax(X, o.ROWWISE)
+    out = L.lrqmm_rsvd(to_dev(X), to_dev(amax), 0, 8, ell, 0, 1, seed=3, round_mode=o.NEAREST)
+    U, S, Vt = (to_np(t).astype(np.float64) for t in out)
+    assert np.all(Vt[:, -1] == 0)
+    return U, S, Vt[:, :-1]
+
+
+@pytest.mark.parametrize("copies,ell", [(2, 40), (2, 80), (4, 40), (8, 40), (4, 80)])
+def test_rsvd_repeated_singular_values(copies, ell):
+    """Every singular value of R several times (equal diagonal blocks; the float32 products separate the copies by about
+    1e-9 of the largest): the eigenvectors that the tridiagonal solver finds one by one are then 1e-8 off orthogonal in a
+    numpy model of it, inside 1e-11 .. 1e-4, so its results come from the correction step.  No truncation, so R and each
+    group of singular values are determined: tolerances as above (Sigma 2e-5; reconstruction to the rounding of the factors
+    and of the float32 products)."""
+    rng = np.random.default_rng(copies * 100 + ell)
+    k = ell // copies
+    u, _, v = np.linalg.svd(rng.uniform(0, 1, (60, 50)), full_matrices=False)
+    s = np.linspace(3.0, 1.0, k)
+    R = np.kron(np.eye(copies), (u[:, :k] * s) @ v[:k])
+    f = 0.4 / np.abs(R).max()
+    R = (R * f).astype(np.float32)
+    U, S, Vt = _whole_rsvd_of(R, ell)
+    assert np.allclose(S, np.repeat(f * s, copies), rtol=2e-5, atol=0)
+    assert np.max(np.abs(U.T @ U - np.eye(ell))) < 2e-5
+    assert np.max(np.abs(Vt @ Vt.T - np.eye(ell))) < 2e-5
+    assert np.linalg.norm((U * S) @ Vt - R) <= 1e-5 * np.linalg.norm(R)
+
+
+@pytest.mark.parametrize("flat,k,ell", [(1e-3, 3, 40), (1e-3, 7, 80), (1e-4, 3, 80), (5e-5, 3, 80), (3e-5, 3, 80)])
+def test_rsvd_flat_tail_far_below_the_top(flat, k, ell):
+    """k large singular values and a flat tail at `flat` of the largest: the tail's eigenvalues differ by less and less of
+    the matrix norm, and the check of the tridiagonal solver sees 5e-6, 2.5e-5, 1.3e-4, 3e-4, 6e-4 in a numpy model of it:
+    on both sides of the 1e-4 beyond which the result is dropped and the Jacobi solver takes over.  The tail itself is
+    known to the float32 products' noise, about 1e-7 of the largest value per entry, so Sigma there is held to 2e-6 of it."""
+    rng = np.random.default_rng(ell + k)
+    m, n = 260, 300
+    u, _ = np.linalg.qr(rng.standard_normal((m, ell)))
+    v, _ = np.linalg.qr(rng.standard_normal((n, ell)))
+    s = np.full(ell, flat)
+    s[:k] = np.linspace(1.0, 0.5, k)
+    R = (u * s) @ v.T
+    f = 0.4 / np.abs(R).max()
+    R = (R * f).astype(np.float32)
+    U, S, Vt = _whole_rsvd_of(R, ell)
+    say("flat tail", flat, "tail of S / S[0]:", S[k] / S[0], "...", S[-1] / S[0])
+    assert np.all(S[:-1] >= S[1:])
+    assert np.allclose(S[:k], f * s[:k], rtol=2e-5, atol=0)
+    assert np.max(np.abs(S[k:] - f * s[k:])) <= 2e-6 * S[0]
+    assert np.max(np.abs(U.T @ U - np.eye(ell))) < 2e-5
+    assert np.linalg.norm((U * S) @ Vt - R) <= 1e-5 * np.linalg.norm(R)
+
+
 def test_rsvd_truncation_between_nearly_equal_singular_values():
     """A case in which the rank-r truncation is not determined at float32 resolution: the residual of the tall
     conv-shaped operand (100352 x 576, ReLU inputs) with l = 16, one power iteration, truncated to r = 8.  The

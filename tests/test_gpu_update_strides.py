@@ -208,10 +208,9 @@ def test_early_product_equals_fused_store_phase_bitwise(K):
 @pytest.mark.parametrize("ell,round_mode,rows,cols", [(24, 0, 640, 512), (40, 0, 640, 512), (72, 0, 640, 512),
                                                        (40, 1, 640, 512), (40, 0, 4096, 4096)])
 def test_guard_free_pass_kernels_equal_the_guarded_ones_bitwise(axis, ell, round_mode, rows, cols):
-    """A dense operand whose sizes are multiples of 128 takes the guard-free instantiations of the two
-    residual products; the same values inside an array with an odd row stride take the guarded scalar-load
-    kernels.  Same arithmetic in the same order: the factors must agree bit for bit.  (At 640 x 512 only R.W
-    has whole chunks; at 4096 x 4096 the row chunks of Rt.W are multiples of 128 as well.)"""
+    """A dense operand whose sizes are multiples of 128, and the same values inside an array with an odd row stride, whose
+    rows are aligned to single elements only: the guard-free kernels take both, and the factors must agree bit for bit.
+    Guarded against guard-free launches of the same operand: the test of the same name in test_gpu_matmul.py."""
     import torch
     import paper_2409_18772_amd as L
     X = wl.random_matrix("normal", rows, cols, seed=41 + ell)
@@ -220,7 +219,7 @@ def test_guard_free_pass_kernels_equal_the_guarded_ones_bitwise(axis, ell, round
     dense = to_dev(X)
     _, view = window(X, 1)
     rank, p = ell - 8, 8
-    say("guard-free vs guarded", axis, ell, round_mode)
+    say("dense vs odd stride", axis, ell, round_mode)
     a = L.lrqmm_rsvd_ex(dense, amax, axis, 4, rank, p, 1, seed=13, round_mode=round_mode)
     b = L.lrqmm_rsvd_ex(view, amax, axis, 4, rank, p, 1, seed=13, round_mode=round_mode)
     for x, y, name in zip(a, b, ("U", "Sigma", "Vt")):
@@ -230,8 +229,8 @@ def test_guard_free_pass_kernels_equal_the_guarded_ones_bitwise(axis, ell, round
 @pytest.mark.parametrize("M,N,K,r,p,mode,tensor", [(640, 512, 768, 24, 8, 0, False), (512, 640, 1024, 16, 8, 1, False),
                                                    (640, 512, 768, 60, 12, 0, True)])
 def test_fused_quantize_and_sketch_equals_the_separate_calls_bitwise(M, N, K, r, p, mode, tensor):
-    """For shapes on the guard-free pass kernels, lrqmm_matmul takes the group maxima first and lets the first
-    residual product write the codes and the step vectors as well (one read of each operand fewer).  The same
+    """lrqmm_matmul takes the group maxima first and lets the first residual product write the codes and the step vectors
+    as well (one read of each operand fewer).  For sketches wider than 16 columns that is the same
     arithmetic in the same order as quantizing and factoring separately: the chain of lrqmm_quantize_ex,
     lrqmm_rsvd and lrqmm_gemm must give the same C bit for bit (both rounding modes, both scale granularities)."""
     import torch
