@@ -115,7 +115,7 @@ def _whole_rsvd_of(R, ell):
 def test_rsvd_repeated_singular_values(copies, ell):
     """Every singular value of R several times (equal diagonal blocks; the float32 products separate the copies by about
     1e-9 of the largest): the eigenvectors that the tridiagonal solver finds one by one are then 1e-8 off orthogonal in a
-    numpy model of it, inside 1e-11 .. 1e-4, so its results come from the correction step.  No truncation, so R and each
+    numpy model of it, inside 1e-11 .. 1e-4, and its results come from the correction step (seen with its flags printed).  No truncation, so R and each
     group of singular values are determined: tolerances as above (Sigma 2e-5; reconstruction to the rounding of the factors
     and of the float32 products)."""
     rng = np.random.default_rng(copies * 100 + ell)
@@ -134,9 +134,10 @@ def test_rsvd_repeated_singular_values(copies, ell):
 
 @pytest.mark.parametrize("flat,k,ell", [(1e-3, 3, 40), (1e-3, 7, 80), (1e-4, 3, 80), (5e-5, 3, 80), (3e-5, 3, 80)])
 def test_rsvd_flat_tail_far_below_the_top(flat, k, ell):
-    """k large singular values and a flat tail at `flat` of the largest: the tail's eigenvalues differ by less and less of
-    the matrix norm, and the check of the tridiagonal solver sees 5e-6, 2.5e-5, 1.3e-4, 3e-4, 6e-4 in a numpy model of it:
-    on both sides of the 1e-4 beyond which the result is dropped and the Jacobi solver takes over.  The tail itself is
+    """k large singular values and a flat tail at `flat` of the largest: the tail's eigenvalues differ by a few roundings
+    of the matrix norm.  At 1e-3 the tridiagonal solver finds vectors more than 1e-4 off orthogonal (seen with its flags
+    printed), at 1e-4 and below its off-diagonal is about 1e-14 of the norm, the limit for going on: the result is dropped,
+    after the check or before the eigenvectors, and the Jacobi solver takes over.  The tail itself is
     known to the float32 products' noise, about 1e-7 of the largest value per entry, so Sigma there is held to 2e-6 of it."""
     rng = np.random.default_rng(ell + k)
     m, n = 260, 300
