@@ -89,8 +89,8 @@ SHORT_ROWS = [
 
 
 # From 8192 rows on the maxima, codes and sketch product of such an A come from one read: at that limit and beyond, whole
-# and ragged last tiles, the shortest and longest rows, unequal shares of the reduction, and two shapes that are tall
-# enough but not eligible (longer rows, a wider sketch).
+# and ragged last tiles, the shortest and longest rows, unequal shares of the reduction, and three shapes that are tall
+# enough but not eligible (longer rows, also with several splits of B's shorter factor; a wider sketch).
 TALL_SHORT_ROWS = [
     (8192, 64, 576, 8, 0, 0),
     (8193, 70, 96, 4, 4, 1),
@@ -99,6 +99,7 @@ TALL_SHORT_ROWS = [
     (10000, 40, 336, 16, 0, 0),
     (8300, 20, 544, 8, 8, 2),
     (8200, 40, 640, 12, 4, 1),
+    (8300, 600, 610, 12, 4, 1),
     (8200, 33, 400, 12, 8, 0),
 ]
 
