@@ -310,9 +310,11 @@ enum class FirstPass {
 
 // Appends the launches of one factorization, or of two that advance together (one launch per step for both; their
 // operands have different axes), to `ops`.  The sketches are in place.  svd_index: position of the small SVD.
+// basis_suffices: the caller only uses the product U diag(Sigma) Vt, and nothing is truncated (oversample == 0): U = Q,
+// Sigma = 1, Vt = Q^T R carry the same product as the SVD's factors.
 static void factor_launches(LaunchList& ops, const Factor* factors, int n, FirstPass first, QuantParams q, int rank,
                             int oversample, int power_iters, int planes_first, int planes, int planes_last, hipStream_t st,
-                            size_t* svd_index, float* one_read_amax = nullptr) {
+                            size_t* svd_index, float* one_read_amax = nullptr, bool basis_suffices = false) {
     struct Pair { Factor f[2]; PassOperand op[2]; };
     auto p = std::make_shared<Pair>();
     for (int i = 0; i < n; ++i) { p->f[i] = factors[i]; p->op[i] = factors[i].op; }
@@ -364,6 +366,17 @@ static void factor_launches(LaunchList& ops, const Factor* factors, int n, First
     }
     // B^T = R^T Q (cols x l), its Gram B B^T, small SVD, U = Q U', V = B^T U' / sigma
     ops.push_back([=] { return launch_resid_mul_t(p->op, n, q, LP, st, planes_last); });
+    if (basis_suffices) {
+        ops.push_back([=] {
+            BasisJob bj[2];
+            for (int i = 0; i < n; ++i) {
+                const Factor& f = p->f[i];
+                bj[i] = {f.op.partial, f.op.pt.splits, f.op.cols, f.op.Y, f.op.rows, f.U, f.Sigma, f.Vt};
+            }
+            return launch_take_basis(bj, n, LP, rank, st);
+        });
+        return;
+    }
     const Jobs j = jobs_of(true);
     ops.push_back([=] { return launch_reduce_gram(j.g, n, LP, st); });
     ops.push_back([=] { return launch_gram_sum(j.g, n, LP, st); });
@@ -668,6 +681,10 @@ int lrqmm_matmul_ex(int M, int N, int K, int bits, int rank, int oversample, int
     // narrow sketch's is too short); a long product outlasts it and holds the CUs the panel kernels need, so that at 32
     // to 40 columns the fused kernel would be the faster one from 8192^3 on.
     const bool early = factored && rank_update_usable(M, N, C) && beta == 0.0f && ldd == N && ell >= 32;
+    // Nothing to truncate: C needs no more of a factorization than U diag(Sigma) Vt = Q (Q^T R), and the small SVD falls
+    // away.  Up to 16 columns; a call with a wider sketch gives the bits of the separate quantize, rsvd and gemm calls (a
+    // narrow one's first product differs from them anyway).
+    const bool basis_suffices = oversample == 0 && LP == 16;
     if (slot >= 0) g_prof.early[slot] = early;
     hipStream_t gst = early ? side->gemm_stream : pst;
     // Planned first and then issued (see LaunchList): opsA holds the chain of both operands, or A's beside opsB with B's.
@@ -709,13 +726,14 @@ int lrqmm_matmul_ex(int M, int N, int K, int bits, int rank, int oversample, int
                 opsA.push_back([=] { return launch_absmax_pair(A, lda, M, K, amaxA, nullptr, 0, 0, nullptr, qp, per_tensor, pst); });
             mark(opsA, 1, pst);
             factor_launches(opsA, &f[0], 1, one_read ? FirstPass::one_read : quant, qp, rank, oversample, power_iters, pl_first,
-                            pl, pl_last, pst, &svd, amaxA);
+                            pl, pl_last, pst, &svd, amaxA, basis_suffices);
             opsB.push_back([=] {
                 return launch_sketch_and_zero(seed, LRQMM_AXIS_COL, N, ell, LP, WcB, 0, nullptr, amaxB_bits, N, bst);
             });
             opsB.push_back([=] { return launch_absmax_pair(nullptr, 0, 0, K, nullptr, B, ldb, N, amaxB, qp, per_tensor, bst); });
             mark(opsB, 4, bst);
-            factor_launches(opsB, &f[1], 1, quant, qp, rank, oversample, power_iters, pl, pl, pl_last, bst, &svdB);
+            factor_launches(opsB, &f[1], 1, quant, qp, rank, oversample, power_iters, pl, pl, pl_last, bst, &svdB, nullptr,
+                            basis_suffices);
             mark(opsB, 5, bst);
         } else {
             opsA.push_back([=] {
@@ -724,7 +742,8 @@ int lrqmm_matmul_ex(int M, int N, int K, int bits, int rank, int oversample, int
             opsA.push_back([=] { return launch_absmax_pair(A, lda, M, K, amaxA, B, ldb, N, amaxB, qp, per_tensor, pst); });
             mark(opsA, 1, pst);
             mark(opsA, 4, pst);
-            factor_launches(opsA, f, 2, quant, qp, rank, oversample, power_iters, pl_first, pl, pl_last, pst, &svd);
+            factor_launches(opsA, f, 2, quant, qp, rank, oversample, power_iters, pl_first, pl, pl_last, pst, &svd, nullptr,
+                            basis_suffices);
             mark(opsA, 5, pst);
         }
         mark(opsA, 2, pst);

@@ -134,6 +134,16 @@ struct SvdJob {
     double *Ur, *Mv;
 };
 int launch_small_svd(const SvdJob* job, int njob, int ell, int LP, int rank, hipStream_t st);
+// Factors without the small SVD, for sketches padded to 16 columns: U (rows x rank) = the leading columns of Q, Sigma = 1,
+// Vt (rank x cols) = (sum_s partial[s])^T, the T pass's result Q^T R.  U diag(Sigma) Vt is Q Q^T R.
+struct BasisJob {
+    const float* partial;       // [splits][cols][LP]
+    int splits, cols;
+    const float* Q;             // rows x LP
+    int rows;
+    float *U, *Sigma, *Vt;
+};
+int launch_take_basis(const BasisJob* job, int njob, int LP, int rank, hipStream_t st);
 
 // ---- gemm.hip -----------------------------------------------------------
 // X = V^T W is kept as vtw_slices(K) k-slices Xp[ks][t][u] that are summed where X is used.

@@ -1159,6 +1159,59 @@ __global__ __launch_bounds__(SVD_THREADS) void small_svd_kernel(SvdJob j0, SvdJo
     }
 }
 
+// U = Q's leading columns, Sigma = 1, Vt = (sum of the T pass's partials)^T for the jobs (see BasisJob; 16 padded
+// columns).  Workgroups [0, nbV) of a job: 16 columns of R each, four waves with a run of the splits each, eight 16-byte
+// loads in flight, the runs added in order (as reduce_gram_kernel does it) and stored transposed through LDS.  The rest
+// copy Q, four entries of U per thread.  Bound by load latency: one launch in place of the Gram matrix, its sum, the
+// small SVD and the product with its vectors.  Calls, with the SVD / without: 256^3, 8 columns 81 / 57 us; 2000^3, 10
+// columns 204 / 177; 100352 x 64 x 576, 8 columns 242 / 218.
+struct BasisGrid { int nbV, nb; };
+__global__ __launch_bounds__(256) void take_basis_kernel(BasisJob a, BasisJob b, BasisGrid ga, BasisGrid gb, int rank) {
+    __shared__ float4 runs[4][64];
+    __shared__ float tile[16][17];
+    const bool first = (int)blockIdx.x < ga.nb;
+    const BasisJob job = first ? a : b;
+    const int nbV = first ? ga.nbV : gb.nbV, blk = first ? blockIdx.x : blockIdx.x - ga.nb;
+    const int tid = threadIdx.x;
+    if (blk < nbV) {
+        const int k0 = blk * 16, sg = tid >> 6, e = tid & 63;       // group e: row k0 + e / 4, columns 4 (e % 4) ..
+        const int sb = sg * job.splits / 4, se = (sg + 1) * job.splits / 4;
+        const size_t plane = (size_t)job.cols * 16;
+        const float* src = job.partial + (size_t)min(k0 + e / 4, job.cols - 1) * 16 + (e % 4) * 4;
+        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int s0 = sb; s0 < se; s0 += 8) {
+            float4 p[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) p[u] = *reinterpret_cast<const float4*>(src + (size_t)min(s0 + u, se - 1) * plane);
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (s0 + u < se) { v.x += p[u].x; v.y += p[u].y; v.z += p[u].z; v.w += p[u].w; }
+        }
+        runs[sg][e] = v;
+        __syncthreads();
+        if (sg == 0) {
+#pragma unroll
+            for (int g = 1; g < 4; ++g) {
+                const float4 t = runs[g][e];
+                v.x += t.x; v.y += t.y; v.z += t.z; v.w += t.w;
+            }
+            float* t = &tile[e / 4][(e % 4) * 4];
+            t[0] = v.x; t[1] = v.y; t[2] = v.z; t[3] = v.w;
+        }
+        __syncthreads();
+        const int t = tid >> 4, k = tid & 15;
+        if (t < rank && k0 + k < job.cols) job.Vt[(size_t)t * job.cols + k0 + k] = tile[k][t];
+        if (blk == 0 && tid < rank) job.Sigma[tid] = 1.0f;
+        return;
+    }
+    const size_t total = (size_t)job.rows * rank;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const size_t idx = (size_t)(blk - nbV) * 1024 + u * 256 + tid;
+        if (idx < total) job.U[idx] = job.Q[(idx / rank) * 16 + idx % rank];
+    }
+}
+
 #define NT_SWITCH(NTV, CALL)            \
     switch (NTV) {                      \
         case 1: { constexpr int NT_ = 1; CALL; } break; \
@@ -1234,6 +1287,18 @@ int launch_small_svd(const SvdJob* job, int njob, int ell, int LP, int rank, hip
         case 4: hipLaunchKernelGGL(small_svd_kernel<4>, dim3(njob), dim3(SVD_THREADS), 0, st, j0, j1, ell, LP, rank); break;
         default: return LRQMM_ERR_UNSUPPORTED;
     }
+    LRQ_CHECK_LAUNCH();
+    return LRQMM_OK;
+}
+
+int launch_take_basis(const BasisJob* job, int njob, int LP, int rank, hipStream_t st) {
+    if (LP != 16 || rank < 1 || rank > 16) return LRQMM_ERR_UNSUPPORTED;
+    BasisGrid g[2] = {};
+    for (int i = 0; i < njob; ++i) {
+        g[i].nbV = ceil_div(job[i].cols, 16);
+        g[i].nb = g[i].nbV + (int)(((size_t)job[i].rows * rank + 1023) / 1024);
+    }
+    hipLaunchKernelGGL(take_basis_kernel, dim3(g[0].nb + g[1].nb), dim3(256), 0, st, job[0], job[njob - 1], g[0], g[1], rank);
     LRQ_CHECK_LAUNCH();
     return LRQMM_OK;
 }

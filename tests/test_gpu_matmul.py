@@ -283,6 +283,38 @@ def test_extents_below_one_load(M, N, K, r, tensor):
     assert rel_fro(to_np(L.lrqmm_gemm(Aq, amA, BqT, amB, 8, fa, fb)), C) < 2 * tol_for(ref)
 
 
+# M, N, K, rank, power_iters: no oversampling and up to 16 columns.  Column counts around the 16 of a workgroup of the
+# final kernel, splits of the last pass from 1 to 64, the narrowest and widest such sketch, both schedules.
+UNTRUNCATED = [(40, 33, 16, 1, 0), (130, 97, 79, 16, 1), (65, 64, 31, 15, 2), (700, 17, 1030, 7, 1), (9000, 18, 33, 16, 0),
+               (8200, 129, 575, 9, 0), (9000, 40, 1500, 3, 0)]
+
+
+@pytest.mark.parametrize("dist", ["uniform01", "normal", "low_rank"])
+@pytest.mark.parametrize("M,N,K,r,q", UNTRUNCATED)
+def test_untruncated_narrow_sketch(M, N, K, r, q, dist):
+    """rank == sketch width <= 16: the call forms Q (Q^T R) without the small SVD; the oracle and the separate calls form
+    U diag(Sigma) Vt of the same matrix.  low_rank: a residual of rank 1 (A constant: its codes leave one value per row and
+    the maxima's entries zero), so that most columns of Q are dropped.  Frobenius only: the element-wise budget counts the
+    2r + 1 terms of an entry, and at ranks this small the rounding of the length-K panel sums is the larger part (with or
+    without the SVD)."""
+    import paper_2409_18772_amd as L
+    if dist == "low_rank":
+        A = np.full((M, K), 0.3, dtype=np.float32) * (1 + np.arange(M, dtype=np.float32)[:, None] % 3)
+        A[:, 0] = 1.0
+        B = np.full((K, N), 0.7, dtype=np.float32)
+        B[0] = 1.0
+    else:
+        A, B = wl.random_matrix(dist, M, K, seed=91), wl.random_matrix(dist, K, N, seed=92)
+    dA, dB = to_dev(A), to_dev(B)
+    say("untruncated", M, N, K, "rank", r, "q", q, dist)
+    C = to_np(L.lrqmm_matmul(dA, dB, 8, r, 0, q, seed=9))
+    ref = o.lrqmm(A, B, 8, r, 0, q, seed=9)
+    d = rel_fro(ref["C"], C)
+    say("gpu vs oracle", d, "tol", tol_for(ref))
+    assert d < tol_for(ref)
+    assert rel_fro(to_np(_separate_calls(L, dA, dB, 8, r, 0, q, 9)), C) < 2 * tol_for(ref)
+
+
 FULL = ["c2_4096_int8_r16", "c3_4096_int4_r32_outliers"]
 
 
