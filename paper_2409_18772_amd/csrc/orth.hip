@@ -6,12 +6,13 @@
 // l x l Gram matrix held in LDS by a single workgroup, in float64 (full-rate on
 // this chip).  Orthonormalization is Cholesky-QR with the Gram matrix, the
 // Cholesky factor, its inverse and the application Q = Y T all in float64; the
-// small SVD is an eigen-solve of B B^T, by tridiagonalization from 32 columns on (with a
-// check of its result) and by cyclic Jacobi below that or where the check fails.  Accumulating the Gram in
+// small SVD is an eigen-solve of B B^T, by tridiagonalization (with a check of its result) and
+// by cyclic Jacobi below five columns or where the check fails.  Accumulating the Gram in
 // float64 keeps the squared condition number harmless (residual sketches have
 // cond ~ 1e2..1e4).  Columns whose pivot vanishes (rank-deficient sketch, e.g. a
 // zero residual) are dropped: the corresponding columns of Q are zero.
 #include "kernels.h"
+#include <type_traits>
 
 // The kernels of this file are short links of a dependent chain and share the chip with the other operand's
 // streaming passes or with the integer product, whose waves keep every SIMD busy.  Their waves ask for the
@@ -533,7 +534,8 @@ __device__ __forceinline__ bool jacobi_rotation(double gpp, double gqq, double g
 // Eigenvalues are the squared singular values of B, eigenvectors its left singular vectors.
 #define SVD_UPDATE_THREADS 448
 #define SVD_THREADS (64 + SVD_UPDATE_THREADS)
-#define SVD_POOL 19968     // float64 words of LDS: the tridiagonal solver's matrices, or two copies of G and Vt
+// Columns from which the tridiagonal solver is the faster one: l = 4 10.6 against 9.0 us (Jacobi), 5 11.1 / 12.6, 8 13.0 / 18.8
+#define LRQ_TRI_MIN 5
 
 // Loop-invariant addresses of one 2x2 block task of an update thread.
 struct SvdTask {
@@ -547,50 +549,48 @@ struct SvdTask {
 
 // ---------------------------------------------------------------------------
 // The small SVD proper: eigenpairs of the l x l matrix G = B B^T by tridiagonalization.
-//   1. Householder tridiagonalization, G in LDS, eight waves.  A wave's lanes are rows; the waves deal the columns among
-//      themselves, in the product p = G v and in the rank-2 update.  Two barriers per column; every wave forms the
-//      Householder vector for itself (sums over lanes by DPP, no barrier).
-//   2. Eigenvalues by multisection: G lanes per eigenvalue count, each at a point of its own, the eigenvalues below it
-//      (Sturm sequence of the leading minors, rescaled every fourth step: one dependent FMA per row), and a ballot
-//      narrows all intervals by a factor G + 1 per round, down to the resolution of float64.
-//   3. Eigenvectors of the tridiagonal matrix by twisted factorization, one lane per vector: the two LDU sweeps meet at
-//      the index where the residual is smallest.
+//   1. Householder tridiagonalization, G in the registers of one wave (above 40 columns two or four), see tridiagonalize.
+//   2. Eigenvalues by multisection, four waves: every lane counts the eigenvalues below two points of its own (Sturm
+//      sequence of the leading minors, rescaled every eighth row: one dependent FMA per row; the rows of T in registers up
+//      to 40 columns), and ballots narrow all intervals by a factor 2 GL + 1 per round, down to the resolution of float64.
+//   3. Eigenvectors of the tridiagonal matrix by twisted factorization, one lane per vector: the LDU sweep from the top in
+//      one wave, the one from the bottom in another; they meet at the index where the residual is smallest.
 //   4. Back transformation by the Householder vectors, eight lanes per vector, no barrier.
 //   5. S = U^T U on the float64 matrix cores.  Off I by more than 1e-11 (eigenvalues that nearly coincide): one step
-//      U (3 I - S) / 2, which squares the deviation.  By more than 1e-4, or not a number (multiple eigenvalues, zero
-//      rows, a tridiagonal matrix that falls apart): the Jacobi solver below instead.
+//      U (3 I - S) / 2, which squares the deviation.  By more than 1e-4, or not a number (multiple eigenvalues, a
+//      tridiagonal matrix that falls apart): the Jacobi solver below instead; zero rows go there at once.
 // Accuracy: eigenvalues to a few ulps of the largest one; ||G u - s u|| likewise.
-// What bounds it: the dependent chain of a column of step 1, about 2400 cycles (60 float64 operations, five LDS round
-// trips, two barriers) whether four or eight waves share the columns; steps 2 to 4 together about as long as step 1.
+// Alone, Jacobi (below 32 columns) or the earlier form with G in LDS and eight waves / this one, us: l = 16 34 / 17, 24
+// 61 / 27, 40 96 / 54, 64 206 / 102, 80 277 / 147.  What bounds it: step 1's chain of about 1000 cycles per column (two sums
+// over lanes at 130 cycles each, three LDS round trips at 80, about 25 dependent float64 operations) to 1700 at 40 columns,
+// 40 to 50 % of the time; step 2 about 22 %.
 // ---------------------------------------------------------------------------
-template <int CTRL, int ROWS = 0xf>
-__device__ __forceinline__ double dpp_f64(double x) {      // lanes without a source add zero
-    const uint64_t u = __double_as_longlong(x);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, ROWS, 0xf, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, ROWS, 0xf, false);
-    return __longlong_as_double((long long)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo));
-}
 __device__ __forceinline__ double readlane_f64(double x, int lane) {
     const uint64_t u = __double_as_longlong(x);
     const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)u, lane);
     const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
     return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
-// Sum over the wave, the same in every lane.
-__device__ __forceinline__ double wave_sum_f64(double x) {
-    x += dpp_f64<0x111>(x);             // row_shr 1, 2, 4, 8: lane 15 of every row holds the row's sum
-    x += dpp_f64<0x112>(x);
-    x += dpp_f64<0x114>(x);
-    x += dpp_f64<0x118>(x);
-    x += dpp_f64<0x142, 0xa>(x);        // row_bcast 15 into rows 1 and 3
-    x += dpp_f64<0x143, 0xc>(x);        // row_bcast 31 into rows 2 and 3
-    return readlane_f64(x, 63);
+// x of another lane of the same 16-lane row (every lane has a source)
+template <int CTRL>
+__device__ __forceinline__ double dpp_row_f64(double x) {
+    const uint64_t u = __double_as_longlong(x);
+    const uint32_t lo = __builtin_amdgcn_mov_dpp((int)(uint32_t)u, CTRL, 0xf, 0xf, true);
+    const uint32_t hi = __builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+__device__ __forceinline__ double wave_max_f64(double x) {
+    x = fmax(x, dpp_row_f64<0xb1>(x));
+    x = fmax(x, dpp_row_f64<0x4e>(x));
+    x = fmax(x, dpp_row_f64<0x141>(x));
+    x = fmax(x, dpp_row_f64<0x140>(x));
+    return fmax(fmax(readlane_f64(x, 0), readlane_f64(x, 16)), fmax(readlane_f64(x, 32), readlane_f64(x, 48)));
 }
 // Sum over each group of eight lanes, in every lane of the group.
 __device__ __forceinline__ double oct_sum_f64(double x) {
-    x += dpp_f64<0xb1>(x);              // quad_perm 1,0,3,2
-    x += dpp_f64<0x4e>(x);              // quad_perm 2,3,0,1
-    x += dpp_f64<0x141>(x);             // row_half_mirror
+    x += dpp_row_f64<0xb1>(x);              // quad_perm 1,0,3,2
+    x += dpp_row_f64<0x4e>(x);              // quad_perm 2,3,0,1
+    x += dpp_row_f64<0x141>(x);             // row_half_mirror
     return x;
 }
 __device__ __forceinline__ double rcp_f64(double d) {       // hardware estimate and two Newton steps
@@ -599,15 +599,253 @@ __device__ __forceinline__ double rcp_f64(double d) {       // hardware estimate
     return fma(fma(-d, q, 1.0), q, q);
 }
 
-#define TRI_WAVES 8
-// RH: 64-row halves of the matrix (1: l <= 64).  Returns false, before anything is written, when the Jacobi solver has
-// to take over.  pool: vectors (672 words), then A (l rows of l rounded up to 8, plus 1; later S), then Z1 and Z2 (LP x rank rounded up to 16
-// each), at most 19952 words (l = 80, rank above 64).
-template <int RH>
+// Groups of lanes per wave and waves, by register columns.  Measured, us per call of the small SVD, (groups, waves): l = 16
+// (2, 1) 18.3, (4, 1) 17.4; 24 26.7, 28.0; 32 35.8, 36.7; 40 55.1, 54.2, (2, 4) 54.7; 48 85.6, 74.5, (2, 2) 74.1, (2, 4)
+// 72.5; 64 (2, 2) 102, (2, 4) 104; 80 (4, 2) 162, (2, 4) 147.
+constexpr int tri_groups(int LW) { return LW == 16 || LW == 40 ? 4 : 2; }
+constexpr int tri_waves(int LW) { return LW <= 40 ? 1 : (LW == 64 ? 2 : 4); }
+// float64 words of LDS for up to LW columns: the tridiagonal solver's vectors (672), Householder vectors or S, and two
+// matrices of eigenvectors; or the Jacobi solver's two copies of G and Vt
+constexpr int svd_pool(int LW) {
+    const int LP = (LW + 15) / 16 * 16, A = LW * (LW | 1) > LP * LP ? LW * (LW | 1) : LP * LP;
+    int words = 672 + (A + 1) / 2 * 2 + 2 * LP * LP;
+    for (int m = 2; m <= LW; m += 2) {
+        const int need = 2 * m * (m + ((m / 2 - m) & 31)) + m * m;
+        if (need > words && need <= 19968) words = need;
+    }
+    return words;
+}
+// 1/d: hardware estimate e, then q + q (e + e^2), e = 1 - d q
+__device__ __forceinline__ double rcp3_f64(double d) {
+    const double q = __builtin_amdgcn_rcp(d);
+    const double e = fma(-d, q, 1.0);
+    return fma(q, fma(e, e, e), q);
+}
+
+
+// The two results of a swap of 32-lane halves (D = 32) or of odd and even 16-lane rows (D = 16) of x with itself: their sum
+// is x + (x of the lane D away), the same in both.
+template <int D>
+__device__ __forceinline__ double cross_sum_f64(double x) {
+    const uint64_t u = __double_as_longlong(x);
+    const uint32_t l = (uint32_t)u, h = (uint32_t)(u >> 32);
+    typedef uint32_t v2u __attribute__((ext_vector_type(2)));
+    v2u a, b;
+    if (D == 32) {
+        a = __builtin_bit_cast(v2u, __builtin_amdgcn_permlane32_swap(l, l, false, false));
+        b = __builtin_bit_cast(v2u, __builtin_amdgcn_permlane32_swap(h, h, false, false));
+    } else {
+        a = __builtin_bit_cast(v2u, __builtin_amdgcn_permlane16_swap(l, l, false, false));
+        b = __builtin_bit_cast(v2u, __builtin_amdgcn_permlane16_swap(h, h, false, false));
+    }
+    return __longlong_as_double((long long)((uint64_t)b.x << 32 | a.x)) + __longlong_as_double((long long)((uint64_t)b.y << 32 | a.y));
+}
+// Sum over each 16-lane row, in every lane of it.
+__device__ __forceinline__ double row_sum_f64(double x) {
+    x += dpp_row_f64<0xb1>(x);              // quad_perm 1,0,3,2
+    x += dpp_row_f64<0x4e>(x);              // quad_perm 2,3,0,1
+    x += dpp_row_f64<0x141>(x);             // row_half_mirror
+    x += dpp_row_f64<0x140>(x);             // row_mirror
+    return x;
+}
+template <int P>        // over the 64 / P lanes that hold the rows (every group of lanes holds the same values)
+__device__ __forceinline__ double rows_sum_f64(double x) {
+    x = row_sum_f64(x);
+    if (P == 2) x = cross_sum_f64<16>(x);
+    return x;
+}
+template <int P>        // over the P groups
+__device__ __forceinline__ double groups_sum_f64(double x) {
+    if (P == 4) x = cross_sum_f64<16>(x);
+    return cross_sum_f64<32>(x);
+}
+
+// Householder tridiagonalization of the l x l matrix `gram` (leading dimension LP) by NW waves, the matrix in registers.
+// Each wave's P groups of 64 / P lanes share the columns (pairs 2 P NW m + 2 g, + 1 to group g), a lane has R rows.  Step k
+// forms u, beta and w = beta G u - kk u from column k and leaves G - u w^T - w u^T; that update is applied in the next
+// step's sweep over the registers, which also forms the next G x: one pass over the matrix and one LDS round trip of (u, w)
+// and x per step (and, with more than one wave, one barrier, at which the waves exchange their parts of G x).  The norm of
+// x and what follows from it run beside that pass (G u = G x + (u0 - x0) G e).
+// V: row k = u (zeros up to k and from l on); beta into tau, diagonal and off-diagonal into dia, off.
+template <int LW, int P, int NW>
+struct TriShape {
+    static constexpr int G = 64 / P, R = (LW + G - 1) / G;              // lanes per group, rows per lane
+    static constexpr int PT = P * NW, CW = (LW + 2 * PT - 1) / (2 * PT) * 2, LC = CW * PT;      // groups, columns per group, columns
+    static constexpr int ROWS = R * G, VEC = ROWS > LC ? ROWS : LC;     // length of a vector in LDS
+    static constexpr int WORDS = NW * 3 * VEC + (NW > 1 ? 2 * (1 + NW) : 1) * VEC;      // of LDS
+};
+template <int LW, int P, int NW>
+__device__ __forceinline__ void tridiagonalize(const double* __restrict__ gram, int LP, int ell, int wave, int lane,
+                                               double* __restrict__ V, int lda, double* __restrict__ dia,
+                                               double* __restrict__ off, double* __restrict__ tau, double* __restrict__ lds) {
+    using S = TriShape<LW, P, NW>;
+    constexpr int G = S::G, R = S::R, CW = S::CW, PT = S::PT, VEC = S::VEC;
+    const int li = lane & (G - 1), g = wave * P + lane / G;
+    double2* const uw = reinterpret_cast<double2*>(lds) + wave * VEC;       // (u, w) and x, a copy per wave
+    double* const xv = lds + (2 * NW + wave) * VEC;
+    double* const cvs = lds + 3 * NW * VEC;                                 // column k + 1 (two generations where waves share it)
+    double* const yxs = cvs + (NW > 1 ? 2 : 1) * VEC;                       // partial products of the waves
+    double a[R][CW];
+#pragma unroll
+    for (int c = 0; c < CW; ++c) {
+        const int j = min(2 * PT * (c / 2) + 2 * g + (c & 1), LP - 1);
+#pragma unroll
+        for (int r = 0; r < R; ++r) a[r][c] = gram[j * LP + min(li + G * r, LP - 1)];     // (symmetric: row j is column j)
+    }
+    double x[R], u[R], w[R], d[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        x[r] = gram[min(li + G * r, LP - 1)];
+        u[r] = w[r] = d[r] = 0.0;
+    }
+    for (int t = lane; t < VEC; t += 64) {
+        uw[t] = make_double2(0.0, 0.0);
+        xv[t] = 0.0;
+    }
+#pragma unroll
+    for (int c = 0; c < CW; ++c) {
+        const int j = 2 * PT * (c / 2) + 2 * g + (c & 1);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            asm volatile("" : "+v"(a[r][c]));           // (all loads in flight before the first use)
+            if (j >= ell || li + G * r >= ell) a[r][c] = 0.0;
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) x[r] = li + G * r < ell ? x[r] : 0.0;
+    const double2* const uwg = uw + 2 * g;
+    const double* const xvg = xv + 2 * g;
+    // Step k; C0: the first register column with a column beyond k
+    auto step = [&](int k, auto first) {
+        constexpr int C0 = decltype(first)::value;
+        // (values that several lanes hold alike are stored by all of them: no branch)
+        double xm[R], s = 0.0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int i = li + G * r;
+            d[r] = i == k ? x[r] : d[r];
+            xm[r] = i > k ? x[r] : 0.0;
+            xv[i] = xm[r];
+            const double t = i > k + 1 ? xm[r] : 0.0;
+            s = fma(t, t, s);
+        }
+        asm volatile("" ::: "memory");          // (read by other lanes)
+        const double x0 = xv[k + 1];
+        s = rows_sum_f64<P>(s);
+        // G <- G - u w^T - w u^T of the previous step, y = G x
+        double y[R][2];
+#pragma unroll
+        for (int r = 0; r < R; ++r) y[r][0] = y[r][1] = 0.0;
+        constexpr int CH = 4, PAIRS = (CW - C0) / 2, NCH = (PAIRS + CH - 1) / CH;     // column pairs per batch of reads
+        double2 q0[2][CH], q1[2][CH], xx[2][CH];
+        auto fetch = [&](int ch) {
+#pragma unroll
+            for (int p = 0; p < CH; ++p) {
+                if (ch * CH + p >= PAIRS) continue;
+                const int c = C0 + 2 * (ch * CH + p);
+                q0[ch & 1][p] = uwg[PT * c];
+                q1[ch & 1][p] = uwg[PT * c + 1];
+                xx[ch & 1][p] = *reinterpret_cast<const double2*>(xvg + PT * c);
+            }
+        };
+        fetch(0);
+#pragma unroll
+        for (int ch = 0; ch < NCH; ++ch) {
+            if (ch + 1 < NCH) fetch(ch + 1);
+            if (NCH > 3) asm volatile("" ::: "memory");          // (one batch ahead, not all of them)
+#pragma unroll
+            for (int p = 0; p < CH; ++p) {
+                if (ch * CH + p >= PAIRS) continue;
+                const int c = C0 + 2 * (ch * CH + p), f = ch & 1;
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    a[r][c] = fma(-q0[f][p].x, w[r], fma(-q0[f][p].y, u[r], a[r][c]));
+                    a[r][c + 1] = fma(-q1[f][p].x, w[r], fma(-q1[f][p].y, u[r], a[r][c + 1]));
+                    y[r][0] = fma(a[r][c], xx[f][p].x, y[r][0]);
+                    y[r][1] = fma(a[r][c + 1], xx[f][p].y, y[r][1]);
+                }
+            }
+        }
+        double* const cv = cvs + (NW > 1 ? (k & 1) * VEC : 0);
+        double* const yx = yxs + (k & 1) * NW * VEC;
+        // column k + 1 is row k + 1: its lanes publish their registers
+        if (li == ((k + 1) & (G - 1))) {
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (R == 1 || r == (k + 1) / G) {
+#pragma unroll
+                    for (int c = C0; c < CW; c += 2)
+                        *reinterpret_cast<double2*>(cv + PT * c + 2 * g) = make_double2(a[r][c], a[r][c + 1]);
+                }
+        }
+        double ys[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            ys[r] = groups_sum_f64<P>(y[r][0] + y[r][1]);
+            if (NW > 1) yx[wave * VEC + li + G * r] = ys[r];
+        }
+        if (NW > 1) __syncthreads();
+        else asm volatile("" ::: "memory");          // (read by other lanes)
+        const double n2 = fma(x0, x0, s);       // (0: the next off-diagonal is 0 or not a number, and the solver gives up)
+        double rs = __builtin_amdgcn_rsq(n2);
+        rs = rs * fma(-0.5 * n2, rs * rs, 1.5);
+        rs = rs * fma(-0.5 * n2, rs * rs, 1.5);
+        const double mu = n2 * rs;
+        const double beta = rcp3_f64(fma(fabs(x0), mu, n2));
+        const double dl = copysign(mu, x0), u0 = x0 + dl;
+        double gu[R], c1[R], dot = 0.0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int i = li + G * r;
+            c1[r] = i < S::LC ? cv[min(i, S::LC - 1)] : 0.0;
+            if (NW > 1) {
+                ys[r] = yx[i];
+#pragma unroll
+                for (int v = 1; v < NW; ++v) ys[r] += yx[v * VEC + i];
+            }
+            u[r] = i == k + 1 ? u0 : xm[r];
+            gu[r] = fma(dl, c1[r], ys[r]);
+            dot = fma(u[r], gu[r], dot);
+        }
+        dot = rows_sum_f64<P>(dot);
+        const double kk = (0.5 * beta) * (beta * dot);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int i = li + G * r;
+            const double t = fma(beta, gu[r], -(kk * u[r]));
+            w[r] = i > k ? t : 0.0;
+            uw[i] = make_double2(u[r], w[r]);
+            V[k * lda + min(i, lda - 1)] = u[r];
+        }
+        asm volatile("" ::: "memory");          // (read by other lanes)
+        double w1;
+        if constexpr (R == 1) w1 = readlane_f64(w[0], k + 1);
+        else w1 = uw[k + 1].y;
+        tau[k] = beta;
+        off[k] = -dl;
+#pragma unroll
+        for (int r = 0; r < R; ++r) x[r] = fma(-u[r], w1, fma(-w[r], u0, c1[r]));
+    };
+    constexpr int CM = CW / 4 * 2;          // half of the column pairs; they hold columns up to CM PT - 1
+    const int half = min(CM * PT, ell - 1);
+    int k = 0;
+    for (; k < half; ++k) step(k, std::integral_constant<int, 0>());
+    for (; k + 1 < ell; ++k) step(k, std::integral_constant<int, CM>());
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int i = li + G * r;
+        if (i < ell) dia[i] = i == ell - 1 ? x[r] : d[r];
+    }
+    off[ell - 1] = 0.0;
+}
+
+// Returns false, before anything is written, when the Jacobi solver has to take over.  pool: vectors (672 words), then A
+// (l rows of LW columns, odd stride: the Householder vectors; later S), then Z1 and Z2 (LP x rank rounded up to 16 each).
+template <int LW>
 __device__ __forceinline__ bool tridiagonal_svd(const SvdJob& job, int ell, int LP, int rank, double* const pool,
-                                                int* const flags) {
+                                                int* const flags, int* const twist) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int lda = ((ell + 7) & ~7) | 1, ldz = (rank + 15) & ~15;
+    const int lda = LW | 1, ldz = (rank + 15) & ~15;
     double* const dia = pool;               // diagonal, off-diagonal (below row i)
     double* const off = pool + 96;
     double* const tau = pool + 288;
@@ -615,286 +853,264 @@ __device__ __forceinline__ bool tridiagonal_svd(const SvdJob& job, int ell, int 
     double* const A = pool + 672;
     double* const Z1 = A + ((max(ell * lda, ldz * ldz) + 1) & ~1);         // (even: pairs are 16-byte aligned)
     double* const Z2 = Z1 + LP * ldz;
-    double* const part = Z1;                // [TRI_WAVES][RH * 64] while the matrix is reduced (and behind it eight copies of (v, w))
     if (tid < 2) flags[tid] = 0;
-    for (int base = 0; base < ell * ell; base += 4 * SVD_THREADS) {     // four loads in flight
-        double v[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int idx = min(base + u * SVD_THREADS + tid, ell * ell - 1);
-            v[u] = job.gram[(idx / ell) * LP + idx % ell];
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int idx = base + u * SVD_THREADS + tid;
-            if (idx < ell * ell) A[(idx / ell) * lda + idx % ell] = v[u];
-        }
+    {   // zero rows (columns of the sketch that were dropped) split the matrix
+        bool dead = false;
+        for (int i = lane; i < ell; i += 64) dead = dead || !(job.gram[i * LP + i] > 0.0);
+        if (__any(dead)) return false;          // the same in every wave
     }
-    __syncthreads();
-    // ---- 1. tridiagonalization: row / column k, k = 0 .. l - 2 (the last one only leaves its off-diagonal) ----
-    double2* const vw = reinterpret_cast<double2*>(part + TRI_WAVES * 64 * RH) + wave * (64 * RH);     // the wave's own copy of (v, w)
-    constexpr int CH = 64 * RH / TRI_WAVES;
-    for (int k = 0; k + 1 < ell; ++k) {
-        {
-            double x[RH], s = 0.0;
-#pragma unroll
-            for (int h = 0; h < RH; ++h) {
-                const int i = lane + 64 * h;
-                x[h] = (i > k && i < ell) ? A[k * lda + min(i, ell - 1)] : 0.0;
-                s = i > k + 1 ? fma(x[h], x[h], s) : s;
-            }
-            const double x0 = (RH == 1 || k + 1 < 64) ? readlane_f64(x[0], k + 1) : readlane_f64(x[RH - 1], k + 1 - 64);
-            s = wave_sum_f64(s);
-            if (tid == 0) dia[k] = A[k * lda + k];
-            if (s == 0.0 || k + 2 >= ell) {         // already tridiagonal here (the same in all waves)
-                if (tid == 0) { off[k] = x0; tau[k] = 0.0; }        // (row k is then not read again)
-                continue;
-            }
-            const double n2 = fma(x0, x0, s);
-            double rs = __builtin_amdgcn_rsq(n2);
-            rs = rs * fma(-0.5 * n2, rs * rs, 1.5);
-            rs = rs * fma(-0.5 * n2, rs * rs, 1.5);
-            const double mu = n2 * rs;
-            const double v0 = x0 <= 0.0 ? x0 - mu : -s * rcp_f64(x0 + mu);
-            const double iv0 = rcp_f64(v0);
-            const double t = 2.0 * v0 * v0 * rcp_f64(fma(v0, v0, s));
-            double v[RH], p[RH];
-#pragma unroll
-            for (int h = 0; h < RH; ++h) {
-                v[h] = lane + 64 * h == k + 1 ? 1.0 : x[h] * iv0;
-                vw[lane + 64 * h].x = v[h];
-                p[h] = 0.0;
-            }
-            // p = t G v, each wave its own columns
-            // (a wave has at most CH = ceil(64 RH / 8) columns: all their loads first, columns past the end with weight 0)
-            for (int u0 = 0; u0 < CH; u0 += 4) {
-                if (k + 1 + wave + u0 * TRI_WAVES >= ell) break;        // uniform
-                double vc[4], a[4][RH];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int c = k + 1 + wave + (u0 + u) * TRI_WAVES;
-                    const double t0 = vw[min(c, ell - 1)].x;
-                    vc[u] = c < ell ? t0 : 0.0;
-#pragma unroll
-                    for (int h = 0; h < RH; ++h) a[u][h] = A[min(c, ell - 1) * lda + min(lane + 64 * h, ell - 1)];
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-#pragma unroll
-                    for (int h = 0; h < RH; ++h) p[h] = fma(a[u][h], vc[u], p[h]);
-            }
-#pragma unroll
-            for (int h = 0; h < RH; ++h) part[wave * (64 * RH) + lane + 64 * h] = p[h];
-            __syncthreads();
-            double pv = 0.0;
-#pragma unroll
-            for (int h = 0; h < RH; ++h) {
-                const int i = lane + 64 * h;
-                double sum = 0.0;
-#pragma unroll
-                for (int w = 0; w < TRI_WAVES; ++w) sum += part[w * (64 * RH) + i];
-                p[h] = (i > k && i < ell) ? t * sum : 0.0;
-                pv = fma(p[h], v[h], pv);
-            }
-            const double kk = 0.5 * t * wave_sum_f64(pv);
-            double w[RH];
-#pragma unroll
-            for (int h = 0; h < RH; ++h) {
-                w[h] = fma(-kk, v[h], p[h]);
-                vw[lane + 64 * h].y = w[h];
-            }
-            // G <- G - v w^T - w v^T; row k keeps the vector, zeros around it, for the back transformation
-            for (int u0 = 0; u0 < CH; u0 += 4) {
-                if (k + 1 + wave + u0 * TRI_WAVES >= ell) break;        // uniform
-                double2 b[4];
-                double a[4][RH];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int c = min(k + 1 + wave + (u0 + u) * TRI_WAVES, ell - 1);
-                    b[u] = vw[c];
-#pragma unroll
-                    for (int h = 0; h < RH; ++h) a[u][h] = A[c * lda + min(lane + 64 * h, ell - 1)];
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int c = k + 1 + wave + (u0 + u) * TRI_WAVES;
-#pragma unroll
-                    for (int h = 0; h < RH; ++h) {
-                        const int i = lane + 64 * h;
-                        if (c < ell && i < ell) A[c * lda + i] = fma(-b[u].x, w[h], fma(-b[u].y, v[h], a[u][h]));   // (v, w zero up to k)
-                    }
-                }
-            }
-            if (wave == 0) {
-#pragma unroll
-                for (int h = 0; h < RH; ++h) {
-                    const int i = lane + 64 * h;
-                    if (i < lda) A[k * lda + i] = v[h];         // (zero up to k and from l on)
-                }
-                if (lane == 0) { off[k] = mu; tau[k] = t; }
-            }
-        }
-        __syncthreads();
+    // ---- 1. tridiagonalization ----
+    static_assert(672 + LW * (LW | 1) + TriShape<LW, tri_groups(LW), tri_waves(LW)>::WORDS <= svd_pool(LW), "fits the pool");
+    constexpr int P = tri_groups(LW), NW = tri_waves(LW);
+    if (wave < NW) {
+        tridiagonalize<LW, P, NW>(job.gram, LP, ell, wave, lane, A, lda, dia, off, tau, Z1);
+    } else if (NW > 1) {
+        for (int k = 0; k + 1 < ell; ++k) __syncthreads();
     }
-    if (tid == 0) { dia[ell - 1] = A[(ell - 1) * lda + ell - 1]; off[ell - 1] = 0.0; }
     __syncthreads();
     // scale to a Gershgorin radius of 1; a split, empty or non-finite matrix goes to the other solver
-    double radius = 0.0, least = 1e300;
-    for (int i = 0; i < ell; ++i) {
-        const double a = i > 0 ? fabs(off[i - 1]) : 0.0, b = fabs(off[i]);
-        radius = fmax(radius, fabs(dia[i]) + a + b);
-        if (i + 1 < ell) least = fmin(least, b);
+    double radius, least = 1e300;
+    {
+        double r = 0.0;
+#pragma unroll
+        for (int h = 0; h < (LW > 64 ? 2 : 1); ++h) {
+            const int i = lane + 64 * h;
+            if (i < ell) {
+                const double a0 = i > 0 ? fabs(off[i - 1]) : 0.0, b0 = fabs(off[i]);
+                const double t = fabs(dia[i]) + a0 + b0;
+                r = t > r || !(t == t) ? t : r;         // (a NaN stays)
+                if (i + 1 < ell) least = fmin(least, b0);
+                if (!(t == t)) least = -1.0;
+            }
+        }
+        radius = wave_max_f64(r);
+        least = -wave_max_f64(-least);
     }
     if (!(radius > 1e-280 && radius < 1e280) || !(least > 1e-14 * radius)) return false;      // the same in every thread
     const double inv = rcp_f64(radius);
-    __syncthreads();
     double2* const de = reinterpret_cast<double2*>(pool + 480);         // (d_i, e_{i-1}^2), padded with rows that change no sign
-    for (int i = tid; i < 96; i += SVD_THREADS) {
-        const double e = (i > 0 && i < ell) ? off[i - 1] * inv : 0.0;
-        de[i] = make_double2(i < ell ? dia[i] * inv : 2.0, e * e);
+    const double d0 = tid < ell ? dia[min(tid, 95)] * inv : 2.0;
+    const double o0 = tid < ell ? off[min(tid, 95)] * inv : 0.0, om = (tid > 0 && tid < ell) ? off[min(tid, 95) - 1] * inv : 0.0;
+    __syncthreads();
+    if (tid < 96) {
+        de[tid] = make_double2(d0, om * om);
+        dia[tid] = d0;
+        off[tid] = o0;
     }
     __syncthreads();
-    for (int i = tid; i < ell; i += SVD_THREADS) {
-        dia[i] *= inv;
-        off[i] *= inv;
-    }
-    // ---- 2. the largest eigenvalues, ev[t] the t-th largest; GL lanes each, four waves ----
+    // ---- 2. the largest eigenvalues, ev[t] the t-th largest; four waves, GL lanes each, two points per lane ----
     if (wave < 4) {
-        const int GL = rank <= 16 ? 16 : (rank <= 32 ? 8 : (rank <= 40 ? 6 : (rank <= 64 ? 4 : 3)));
-        const int rounds = rank <= 16 ? 14 : (rank <= 32 ? 18 : (rank <= 40 ? 20 : (rank <= 64 ? 24 : 28)));    // (GL + 1)^rounds > 2^55
+        const int GL = rank <= 8 ? 32 : (rank <= 16 ? 16 : (rank <= 32 ? 8 : (rank <= 40 ? 6 : (rank <= 64 ? 4 : 3))));
+        const int rounds = rank <= 8 ? 9 : (rank <= 16 ? 10 : (rank <= 32 ? 12 : (rank <= 40 ? 14 : (rank <= 64 ? 16 : 18))));     // (2 GL + 1)^rounds > 2^49
         const int per = 64 / GL, grp = lane / GL, g = lane - grp * GL;
         const int t = wave * per + grp;
         const int e = ell - 1 - t;              // eigenvalues below it
-        const double step = rcp_f64(GL + 1.0);
-        double lo = -1.0, hi = 1.0;
+        const double step = rcp_f64(2.0 * GL + 1.0);
+        const uint64_t mask = ((1ull << GL) - 1) << (grp * GL);
+        constexpr bool IN_REGS = LW <= 40;      // the rows of T stay in registers, or come from LDS in every round
+        double2 rows[IN_REGS ? LW : 1];
+        if constexpr (IN_REGS) {
+#pragma unroll
+            for (int i = 0; i < LW; ++i) rows[i] = de[1 + i];
+        }
+        double lo = -1e-6, hi = 1.0;
+        if (wave * per < rank)
         for (int r = 0; r < rounds; ++r) {
             const double h = (hi - lo) * step;
-            const double xp = fma(h, g + 1.0, lo);
+            const double xa = fma(h, g + 1.0, lo), xb = fma(h, (double)(g + 1 + GL), lo);
             // leading minors p_i of T - x I, scaled: the number of sign changes is the number of eigenvalues below x
-            double p0 = 1.0, p1 = de[0].x - xp;
-            uint32_t count = (uint32_t)__double2hiint(p1) >> 31;
-            double2 q[4], qn[4];
+            double a0 = 1.0, a1 = de[0].x - xa, b0 = 1.0, b1 = de[0].x - xb;
+            uint32_t sa = (uint32_t)__double2hiint(a1) >> 31, sb = (uint32_t)__double2hiint(b1) >> 31;     // signs, the last one in bit 0
+            int ca = sa, cb = sb;
+            auto row = [&](double2 q) {
+                const double a2 = fma(q.x - xa, a1, -(q.y * a0));
+                const double b2 = fma(q.x - xb, b1, -(q.y * b0));
+                sa = __builtin_amdgcn_alignbit(sa, (uint32_t)__double2hiint(a2), 31);
+                sb = __builtin_amdgcn_alignbit(sb, (uint32_t)__double2hiint(b2), 31);
+                a0 = a1; a1 = a2;
+                b0 = b1; b1 = b2;
+            };
+            auto eight = [&] {          // after eight rows: their sign changes, and a common scale for the minors
+                ca += __builtin_popcount((sa ^ (sa >> 1)) & 0xffu);
+                cb += __builtin_popcount((sb ^ (sb >> 1)) & 0xffu);
+                const int ea = __builtin_amdgcn_frexp_exp(fmax(fabs(a0), fabs(a1)));
+                const int eb = __builtin_amdgcn_frexp_exp(fmax(fabs(b0), fabs(b1)));
+                a0 = __builtin_amdgcn_ldexp(a0, -ea); a1 = __builtin_amdgcn_ldexp(a1, -ea);
+                b0 = __builtin_amdgcn_ldexp(b0, -eb); b1 = __builtin_amdgcn_ldexp(b1, -eb);
+            };
+            if constexpr (IN_REGS) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) q[u] = de[1 + u];
-            for (int i = 1; i < ell; i += 4) {
-#pragma unroll
-                for (int u = 0; u < 4; ++u) qn[u] = de[i + 4 + u];      // (the next rows; inside the padding at the end)
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const double p2 = fma(q[u].x - xp, p1, -(q[u].y * p0));
-                    q[u] = qn[u];
-                    count += (uint32_t)(__double2hiint(p2) ^ __double2hiint(p1)) >> 31;
-                    p0 = p1;
-                    p1 = p2;
+                for (int i = 0; i < LW; ++i) {
+                    row(rows[i]);
+                    if (i % 8 == 7) eight();
                 }
-                const int ex = __builtin_amdgcn_frexp_exp(fmax(fabs(p0), fabs(p1)));
-                p0 = __builtin_amdgcn_ldexp(p0, -ex);
-                p1 = __builtin_amdgcn_ldexp(p1, -ex);
+            } else {
+                for (int i = 1; i < ell; i += 16) {
+                    double2 q[8], p[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) q[u] = de[i + u];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) p[u] = de[i + 8 + u];      // (inside the padding at the end)
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) row(q[u]);
+                    eight();
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) row(p[u]);
+                    eight();
+                }
             }
-            const uint64_t above = __ballot((int)count > e);
-            const int j = __builtin_popcountll(~above & (((1ull << GL) - 1) << (grp * GL)));   // points at or below
+            // points at or below the eigenvalue (the counts rise with the point)
+            const int j = __builtin_popcountll(~__ballot(ca > e) & mask) + __builtin_popcountll(~__ballot(cb > e) & mask);
             const double nlo = fma(h, (double)j, lo);
-            hi = j == GL ? hi : fma(h, j + 1.0, lo);
+            hi = j == 2 * GL ? hi : fma(h, j + 1.0, lo);
             lo = nlo;
         }
         if (g == 0 && grp < per && t < rank) ev[t] = 0.5 * (lo + hi);
     }
     __syncthreads();
-    for (int idx = tid; idx < 2 * LP * ldz; idx += SVD_THREADS) Z1[idx] = 0.0;
-    __syncthreads();
-    // ---- 3. eigenvectors of the tridiagonal matrix; column t belongs to ev[t] ----
-    if (tid < rank) {
-        const double lam = ev[tid];
-        double* const L = Z1 + tid;
-        double* const Uz = Z2 + tid;
-        const double tiny = 1e-30;
+    // ---- 3. eigenvectors of the tridiagonal matrix; column t belongs to ev[t]: the LDU sweep from the top in one wave, the
+    // one from the bottom in another ----
+    const int t3 = (wave >> 1) * 64 + lane;
+    const bool top_sweep = (wave & 1) == 0, on3 = wave < 4 && t3 < rank;
+    if (on3) {
+        const double lam = ev[t3], tiny = 1e-30;
+        double* const L = Z1 + t3;
+        double* const Uz = Z2 + t3;
         // (the operands of step i + 1 are read before step i writes: LDS reads stay off the recurrences)
-        double dp = dia[0] - lam, o = off[0], dn = dia[1];
-        for (int i = 0; i + 1 < ell; ++i) {
-            const double o2 = off[i + 1], dn2 = dia[min(i + 2, ell - 1)];
-            if (fabs(dp) < tiny) dp = copysign(tiny, dp);
-            Uz[i * ldz] = dp;                           // D+ for now
-            const double l = o * rcp_f64(dp);
-            L[i * ldz] = l;
-            dp = fma(-l, o, dn - lam);
-            o = o2;
-            dn = dn2;
-        }
-        double dm = dia[ell - 1] - lam, best = fabs(dp);
-        int r = ell - 1;
-        double dpi = Uz[(ell - 2) * ldz];
-        o = off[ell - 2];
-        dn = dia[ell - 2];
-        for (int i = ell - 2; i >= 0; --i) {
-            const int ip = max(i - 1, 0);
-            const double o2 = off[ip], dn2 = dia[ip], dp2 = Uz[ip * ldz];
-            if (fabs(dm) < tiny) dm = copysign(tiny, dm);
-            const double u = o * rcp_f64(dm);
-            const double c = dn - lam;
-            dm = fma(-u, o, c);
-            const double gam = fabs(dpi + (dm - c));
-            Uz[i * ldz] = u;
-            if (gam < best) { best = gam; r = i; }
-            o = o2;
-            dn = dn2;
-            dpi = dp2;
-        }
-        double z = 1.0, sum = 1.0, m = L[(ell - 2) * ldz];
-        for (int i = ell - 2; i >= 0; --i) {
-            const double m2 = L[max(i - 1, 0) * ldz];
-            if (i < r) {
-                z = -(m * z);
-                L[i * ldz] = z;
-                sum = fma(z, z, sum);
+        if (top_sweep) {
+            double dp = dia[0] - lam, o = off[0], dn = dia[1];
+            for (int i = 0; i + 1 < ell; ++i) {
+                const double o2 = off[i + 1], dn2 = dia[min(i + 2, ell - 1)];
+                if (fabs(dp) < tiny) dp = copysign(tiny, dp);
+                const double l = o * rcp3_f64(dp);
+                L[i * ldz] = l;
+                dp = fma(-l, o, dn - lam);
+                o = o2;
+                dn = dn2;
             }
-            m = m2;
-        }
-        z = 1.0;
-        m = Uz[0];
-        for (int i = 0; i + 1 < ell; ++i) {
-            const double m2 = Uz[(i + 1) * ldz];
-            if (i >= r) {
-                z = -(m * z);
-                L[(i + 1) * ldz] = z;
-                sum = fma(z, z, sum);
+        } else {
+            double dm = dia[ell - 1] - lam, o = off[ell - 2], dn = dia[ell - 2];
+            for (int i = ell - 2; i >= 0; --i) {
+                const int ip = max(i - 1, 0);
+                const double o2 = off[ip], dn2 = dia[ip];
+                if (fabs(dm) < tiny) dm = copysign(tiny, dm);
+                const double u = o * rcp3_f64(dm);
+                Uz[i * ldz] = u;
+                dm = fma(-u, o, dn - lam);
+                o = o2;
+                dn = dn2;
             }
-            m = m2;
         }
-        L[r * ldz] = 1.0;
-        const double sc = 1.0 / sqrt(sum);
-        for (int i = 0; i < ell; ++i) L[i * ldz] *= sc;
     }
     __syncthreads();
-    // ---- 4. back transformation ----
+    // where the two meet: the smallest |gamma_i| = |(d_i - lambda) - l_{i-1} e_{i-1} - u_i e_i|; eight lanes per vector
     for (int b = 8 * wave; b < rank; b += SVD_THREADS / 8) {
-        const int t = b + (lane >> 3), sl = lane & 7;
-        const bool on = t < rank;
-        double* const col = Z1 + min(t, rank - 1);
-        double z[MAXL / 8];
+        const int t = min(b + (lane >> 3), rank - 1), sl = lane & 7;
+        const double lam = ev[t];
+        double best = 1e300;
+        int r = 0;
 #pragma unroll
-        for (int u = 0; u < MAXL / 8; ++u) z[u] = (sl + 8 * u < ell) ? col[(sl + 8 * u) * ldz] : 0.0;
-        for (int k = ell - 3; k >= 0; --k) {
-            const double tk = tau[k];
-            if (tk == 0.0) continue;            // uniform
-            double v[MAXL / 8], d0 = 0.0, d1 = 0.0;
+        for (int u = 0; u < MAXL / 8; ++u) {
+            if (8 * u < ell) {
+                const int i = min(sl + 8 * u, ell - 1);
+                const double lo = i > 0 ? Z1[max(i - 1, 0) * ldz + t] * off[max(i - 1, 0)] : 0.0;
+                const double up = i + 1 < ell ? Z2[min(i, ell - 2) * ldz + t] * off[i] : 0.0;
+                const double gam = fabs((dia[i] - lam) - lo - up);
+                if (gam < best) { best = gam; r = i; }
+            }
+        }
 #pragma unroll
-            for (int u = 0; u < MAXL / 8; ++u) v[u] = 8 * u < ell ? A[k * lda + sl + 8 * u] : 0.0;      // (uniform)
+        for (int o = 1; o < 8; o <<= 1) {
+            const double ob = __shfl_xor(best, o, 64);
+            const int orr = __shfl_xor(r, o, 64);
+            if (ob < best || (ob == best && orr < r)) { best = ob; r = orr; }
+        }
+        if (sl == 0) twist[t] = r;
+    }
+    __syncthreads();
+    if (on3) {
+        double* const L = Z1 + t3;
+        double* const Uz = Z2 + t3;
+        const int r = twist[t3];
+        double z = 1.0;
+        if (top_sweep) {
+            for (int i0 = ell - 2; i0 >= 0; i0 -= 4) {
+                double m[4];
 #pragma unroll
-            for (int u = 0; u < MAXL / 8; u += 2) {
-                if (8 * u < ell) {
-                    d0 = fma(v[u], z[u], d0);
-                    d1 = fma(v[u + 1], z[u + 1], d1);
+                for (int u = 0; u < 4; ++u) m[u] = L[max(i0 - u, 0) * ldz];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int i = i0 - u;
+                    if (i < r && i >= 0) {
+                        z = -(m[u] * z);
+                        L[i * ldz] = z;
+                    }
                 }
+            }
+            L[r * ldz] = 1.0;
+        } else {
+            for (int i0 = 0; i0 + 1 < ell; i0 += 4) {
+                double m[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) m[u] = Uz[min(i0 + u, ell - 2) * ldz];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int i = i0 + u;
+                    if (i >= r && i + 1 < ell) {
+                        z = -(m[u] * z);
+                        L[(i + 1) * ldz] = z;
+                    }
+                }
+            }
+        }
+    }
+    __syncthreads();
+    // ---- 4. normalization and back transformation, eight lanes per vector; unused rows and columns become zeros ----
+    constexpr int NU = LW / 8;
+    for (int b = 8 * wave; b < ldz; b += SVD_THREADS / 8) {
+        const int t = b + (lane >> 3), sl = lane & 7;
+        double* const col = Z1 + t;
+        double z[NU], n2 = 0.0;
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            z[u] = (sl + 8 * u < ell && t < rank) ? col[(sl + 8 * u) * ldz] : 0.0;
+            n2 = fma(z[u], z[u], n2);
+        }
+        n2 = oct_sum_f64(n2);
+        double sc = __builtin_amdgcn_rsq(n2);
+        sc = sc * fma(-0.5 * n2, sc * sc, 1.5);
+        sc = sc * fma(-0.5 * n2, sc * sc, 1.5);
+        sc = t < rank ? sc : 0.0;
+#pragma unroll
+        for (int u = 0; u < NU; ++u) z[u] *= sc;
+        double v[NU], tk = tau[ell - 2];
+#pragma unroll
+        for (int u = 0; u < NU; ++u) v[u] = A[(ell - 2) * lda + sl + 8 * u];
+        for (int k = ell - 2; k >= 0; --k) {
+            const int kn = max(k - 1, 0);
+            double vn[NU];
+            const double tn = tau[kn];
+#pragma unroll
+            for (int u = 0; u < NU; ++u) vn[u] = A[kn * lda + sl + 8 * u];
+            double d0 = 0.0, d1 = 0.0;
+#pragma unroll
+            for (int u = 0; u < NU; ++u) {
+                if (u & 1) d1 = fma(v[u], z[u], d1);
+                else       d0 = fma(v[u], z[u], d0);
             }
             const double d = tk * oct_sum_f64(d0 + d1);
 #pragma unroll
-            for (int u = 0; u < MAXL / 8; ++u)
-                if (8 * u < ell) z[u] = fma(-d, v[u], z[u]);
+            for (int u = 0; u < NU; ++u) {
+                z[u] = fma(-d, v[u], z[u]);
+                v[u] = vn[u];
+            }
+            tk = tn;
         }
-        if (on) {
+        if (t < ldz) {
 #pragma unroll
-            for (int u = 0; u < MAXL / 8; ++u)
-                if (sl + 8 * u < ell) col[(sl + 8 * u) * ldz] = z[u];
+            for (int u = 0; u < NU; ++u)
+                if (sl + 8 * u < LP) col[(sl + 8 * u) * ldz] = z[u];
+            if (LW + sl < LP) col[(LW + sl) * ldz] = 0.0;
         }
     }
     __syncthreads();
@@ -952,29 +1168,28 @@ __device__ __forceinline__ bool tridiagonal_svd(const SvdJob& job, int ell, int 
     return true;
 }
 
-template <int NB>
+template <int NB, int LW>
 __global__ __launch_bounds__(SVD_THREADS) void small_svd_kernel(SvdJob j0, SvdJob j1, int ell, int LP, int rank) {
     const SvdJob job = blockIdx.x == 0 ? j0 : j1;
     const double* __restrict__ const gram = job.gram;
     float* __restrict__ const Sigma = job.Sigma;
     double* __restrict__ const Ur = job.Ur;
     double* __restrict__ const Mv = job.Mv;
-    __shared__ __align__(16) double pool[SVD_POOL];
+    __shared__ __align__(16) double pool[svd_pool(LW)];
     raise_wave_priority();
     __shared__ __align__(16) double2 rot[2][MAXL / 2];      // (c, s) per slot, two generations
     __shared__ int order[MAXL];
     __shared__ int finished;
     __shared__ int flags[2];
     const int tid = threadIdx.x;
-    // (measured, tridiagonal / Jacobi: l = 10 25 / 20 us, 24 56 / 55, 40 97 / 127, 80 290 / 780)
-    if (ell >= 32) {
-        if (tridiagonal_svd<NB <= 2 ? 1 : 2>(job, ell, LP, rank, pool, flags)) return;
+    if (ell >= LRQ_TRI_MIN) {
+        if (tridiagonal_svd<LW>(job, ell, LP, rank, pool, flags, order)) return;
         __syncthreads();
     }
     const int m = (ell + 1) & ~1;   // even number of players; a zero dummy row/column when ell is odd
     const int half = m / 2;
     int ldg = m + ((half - m) & 31);                      // >= m, = half (mod 32)
-    if (2 * m * ldg + m * m > SVD_POOL) ldg = m + 1;       // largest sketches: accept bank conflicts
+    if (2 * m * ldg + m * m > svd_pool(LW)) ldg = m + 1;       // largest sketches: accept bank conflicts
     const int ldv = m;
     double* const G0 = pool;
     double* const G1 = pool + m * ldg;
@@ -1278,15 +1493,17 @@ int launch_apply(const ApplyJob* job, int njob, int LP, hipStream_t st) {
 }
 
 int launch_small_svd(const SvdJob* job, int njob, int ell, int LP, int rank, hipStream_t st) {
-    const int m = (ell + 1) & ~1, blocks = (m / 2) * (m / 2);
     const SvdJob j0 = job[0], j1 = job[njob - 1];
-    switch (ceil_div(blocks, SVD_UPDATE_THREADS)) {      // 2x2 blocks per update thread
-        case 1: hipLaunchKernelGGL(small_svd_kernel<1>, dim3(njob), dim3(SVD_THREADS), 0, st, j0, j1, ell, LP, rank); break;
-        case 2: hipLaunchKernelGGL(small_svd_kernel<2>, dim3(njob), dim3(SVD_THREADS), 0, st, j0, j1, ell, LP, rank); break;
-        case 3: hipLaunchKernelGGL(small_svd_kernel<3>, dim3(njob), dim3(SVD_THREADS), 0, st, j0, j1, ell, LP, rank); break;
-        case 4: hipLaunchKernelGGL(small_svd_kernel<4>, dim3(njob), dim3(SVD_THREADS), 0, st, j0, j1, ell, LP, rank); break;
-        default: return LRQMM_ERR_UNSUPPORTED;
-    }
+    // (NB: 2 x 2 blocks per update thread of the Jacobi solver; LW: register columns of the tridiagonalization)
+#define LRQ_SVD(NB, LW) hipLaunchKernelGGL((small_svd_kernel<NB, LW>), dim3(njob), dim3(SVD_THREADS), 0, st, j0, j1, ell, LP, rank)
+    if (ell <= 16)      LRQ_SVD(1, 16);
+    else if (ell <= 24) LRQ_SVD(1, 24);
+    else if (ell <= 32) LRQ_SVD(1, 32);
+    else if (ell <= 40) LRQ_SVD(1, 40);
+    else if (ell <= 48) LRQ_SVD(2, 48);
+    else if (ell <= 64) LRQ_SVD(3, 64);
+    else                LRQ_SVD(4, 80);
+#undef LRQ_SVD
     LRQ_CHECK_LAUNCH();
     return LRQMM_OK;
 }

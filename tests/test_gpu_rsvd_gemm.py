@@ -72,11 +72,27 @@ def test_rsvd_against_oracle(rows, cols, axis, bits, rank, p, q, kind):
     assert np.array_equal(to_np(S2), S) and np.array_equal(to_np(U2), U) and np.array_equal(to_np(Vt2), Vt)
 
 
-# The small SVD by tridiagonalization (from 32 columns on), at the edges of its lane groups (l = 32, 33, 40, 41, 64, 65), of
-# its 64-row halves and of the padding of its rows; no truncation, so the factors are determined to float32.
+# The small SVD by tridiagonalization (from 5 columns on), at the edges of its register widths (16, 24, 32, 40, 48, 64, 80
+# columns), of its lane groups and of the padding of its rows; no truncation, so the factors are determined to float32.
 @pytest.mark.parametrize("ell", [31, 32, 33, 40, 41, 47, 57, 58, 59, 64, 65, 72, 73, 79, 80])
 def test_rsvd_small_svd_sizes(ell):
     test_rsvd_against_oracle(260, 300, o.ROWWISE, 4, ell, 0, 1, "normal")
+
+
+@pytest.mark.parametrize("ell", [1, 2, 4, 5, 6, 7, 8, 9, 15, 16, 17, 23, 24, 25, 39, 48, 49, 63])
+def test_rsvd_small_svd_narrow_sizes(ell):
+    """Both sides of the limit to the Jacobi solver (5 columns) and of the other register widths."""
+    test_rsvd_against_oracle(260, 300, o.ROWWISE, 4, ell, 0, 1, "normal")
+
+
+@pytest.mark.parametrize("copies,ell", [(2, 6), (2, 16), (4, 24), (8, 24), (2, 48), (2, 64)])
+def test_rsvd_repeated_singular_values_other_widths(copies, ell):
+    test_rsvd_repeated_singular_values(copies, ell)
+
+
+@pytest.mark.parametrize("flat,k,ell", [(1e-3, 3, 8), (1e-3, 3, 24), (1e-4, 3, 16), (3e-5, 3, 32), (1e-3, 5, 64)])
+def test_rsvd_flat_tail_other_widths(flat, k, ell):
+    test_rsvd_flat_tail_far_below_the_top(flat, k, ell)
 
 
 @pytest.mark.parametrize("k", [0, 1, 7, 40])
