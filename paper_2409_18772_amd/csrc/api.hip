@@ -37,7 +37,7 @@ inline int pad_to(int x, int m) { return (x + m - 1) / m * m; }
 
 struct RsvdWs {
     float *lam, *s, *Wc, *Yr, *partial;
-    double *gpart, *gram, *T, *Ur, *Mv;
+    double *gpart, *gram, *Ur, *Mv;
 };
 
 size_t carve_rsvd(Arena& a, int rows, int cols, int axis, int LP, int rank, RsvdWs* w) {
@@ -60,7 +60,6 @@ size_t carve_rsvd(Arena& a, int rows, int cols, int axis, int LP, int rank, Rsvd
     t.partial = a.take<float>(part);
     t.gpart = a.take<double>((size_t)nb * LP * LP);
     t.gram = a.take<double>((size_t)LP * LP);
-    t.T = a.take<double>((size_t)LP * LP);
     t.Ur = a.take<double>((size_t)LP * rank);
     t.Mv = a.take<double>((size_t)LP * rank);
     if (w) *w = t;
@@ -320,23 +319,23 @@ static void factor_launches(LaunchList& ops, const Factor* factors, int n, First
     for (int i = 0; i < n; ++i) { p->f[i] = factors[i]; p->op[i] = factors[i].op; }
     const int ell = rank + oversample, LP = pad_to(ell, 16);
     // Gram jobs of the tall factors: of the N pass's result (rows x LP) or of the T pass's (cols x LP)
-    struct Jobs { GramJob g[2]; ApplyJob a[2]; };
+    struct Jobs { GramJob g[2]; };
     auto jobs_of = [=](bool t_type) {
         Jobs j = {};
         for (int i = 0; i < n; ++i) {
             const Factor& f = p->f[i];
             const PassOperand& o = f.op;
             j.g[i] = {f.w.partial, t_type ? o.pt.splits : o.pn.splits, t_type ? o.cols : o.rows, t_type ? o.W : o.Y,
-                      f.w.gpart, f.w.gram, f.w.T, 0, 0};
-            j.a[i] = {j.g[i].Y, f.w.T, j.g[i].Y, j.g[i].n, LP, LP, LP, 0};
+                      f.w.gpart, f.w.gram, 0, 0};
         }
         return j;
     };
-    // Q = orth(sum of the partials) in place: Gram (float64) -> Cholesky -> Q = Y T
+    // Q = orth(sum of the partials) in place: Gram (float64), Cholesky and Q = Y T
     auto gram_to_basis = [&](const Jobs& j) {
-        ops.push_back([=] { return launch_gram_sum(j.g, n, LP, st); });
-        ops.push_back([=] { return launch_chol_inverse(j.g, n, ell, LP, st); });
-        ops.push_back([=] { return launch_apply(j.a, n, LP, st); });
+        bool sums = true;           // few partials: added where they are used
+        for (int i = 0; i < n; ++i) sums = sums && orth_apply_sums(j.g[i].blocks > 0 ? j.g[i].blocks : gram_blocks(j.g[i].n, LP), LP);
+        if (!sums) ops.push_back([=] { return launch_gram_sum(j.g, n, LP, st); });
+        ops.push_back([=] { return launch_orth_apply(j.g, n, ell, LP, sums, st); });
     };
     auto orth = [&](bool t_type) {
         const Jobs j = jobs_of(t_type);

@@ -108,7 +108,7 @@ struct GramJob {
     int splits, n;
     float* Y;                   // n x LP: sum of the partials
     double* gpart;              // [blocks][LP][LP]
-    double *gram, *T;           // LP x LP: Gram matrix of Y; T upper triangular with (Y T)^T (Y T) = I
+    double* gram;               // LP x LP: Gram matrix of Y
     int blocks;                 // Gram partials; 0: gram_blocks(n, LP)
     int rows_per_block;         // (set by launch_reduce_gram)
 };
@@ -116,8 +116,10 @@ struct GramJob {
 int launch_reduce_gram(const GramJob* job, int njob, int LP, hipStream_t st);
 // gram = sum over the blocks of gpart, in fixed order.
 int launch_gram_sum(const GramJob* job, int njob, int LP, hipStream_t st);
-// T from gram; (Y T)^T (Y T) = I on the live columns.
-int launch_chol_inverse(const GramJob* job, int njob, int ell, int LP, hipStream_t st);
+// Y <- Y T, T upper triangular with (Y T)^T (Y T) = I on the live columns, from gram; sum: from the Gram partials (as many
+// as orth_apply_sums allows) instead.
+bool orth_apply_sums(int blocks, int LP);
+int launch_orth_apply(const GramJob* job, int njob, int ell, int LP, bool sum, hipStream_t st);
 // out = In[n x LP] . Mat[LP x cm]; normal: out[i*ldo + c]; transposed: out[c*ldo + i].  Up to four jobs.
 struct ApplyJob {
     const float* In;

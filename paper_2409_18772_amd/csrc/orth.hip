@@ -23,6 +23,9 @@ __device__ __forceinline__ void raise_wave_priority() { __builtin_amdgcn_s_setpr
 
 #define GRAM_BATCH 64         // Gram partials per batch of loads when there are more than 64 of them
 #define MAXL LRQMM_MAX_SKETCH
+// Workgroups of orth_apply_kernel per job, at most: 100352 rows, 64 220 us per call, 256 210, 512 209; 8192 1878, 1855, 1855
+#define ORTH_BLOCKS 256
+#define ORTH_PER 2            // orth_apply_kernel adds up to 8 ORTH_PER Gram partials itself
 
 // Workgroups of the Gram kernel, at most: 64 for wide sketches (each leaves an LP x LP float64 partial that a later
 // kernel has to add up: ~1 MB in all at LP = 48), more for narrow sketches, whose partials are small -- a tall
@@ -244,165 +247,6 @@ __global__ __launch_bounds__(64) void gram_sum_parts_kernel(GramJob a, GramJob b
     if (part == 0 && (int)blockIdx.x * 8 + e < entries) gram[idx] = sum;
 }
 
-// Cholesky-QR factor T = L^-T (upper triangular, Q = Y T) of the Gram matrix G = L L^T, by
-// symmetric elimination of the augmented matrix [G | I]: step j subtracts
-// (M[i][j] / d_j) * (row j) from every row i > j, d_j the pivot M[j][j].  The left half is then
-// L^T with rows unscaled (row j times sqrt(d_j)), the right half is L^-1 with row j unscaled
-// the same way, so T[a][b] = M[b][LP + a] / sqrt(d_b).
-//
-// The matrix lives in registers as KR x KC tiles with strided ownership: worker (ti, tg)
-// owns rows ti + NTI*ir (ir < KR) and columns tg + NTI*kc (kc < KC = 2 KR; NTI = LP / KR
-// workers each way), so pivot j = tj + NTI*jr sits in register row jr and register column
-// jr: compile-time constants inside the unrolled jr loop.  At most four wavefronts (one per SIMD)
-// do the work for l <= 64.  A step publishes pivot rows and pivot columns in LDS (two generations,
-// so one workgroup barrier per step is enough).  The serial chain per step is LDS write ->
-// barrier -> LDS read -> reciprocal -> FMA; the square roots are taken once at the end.
-// A pivot below 1e-10 of its original diagonal (rank-deficient sketch) is dead: it
-// eliminates nothing and its row and column of T are zero.  The workgroup holds only the
-// workers (rounded up to whole waves) and 4 KB of LDS, and every worker loads its tile
-// straight from global memory: a small footprint lets the workgroup start at once on a chip
-// that another stream keeps full (with 1024 threads and the matrix staged in LDS it waited
-// hundreds of microseconds for a free CU at l = 80).
-template <int NT>
-struct CholShape {
-    static constexpr int LP = 16 * NT;
-    static constexpr int KR = 4, KC = 8;            // register tile per worker
-    static constexpr int NTI = LP / KR;             // workers per row and per column
-    static constexpr int WORKERS = NTI * NTI;
-    static constexpr int THREADS = (WORKERS + 63) / 64 * 64;
-};
-
-// Two pivots per step: pivots j and j+1 share one publication (rows j, j+1
-// and columns j, j+1 as they stand before pivot j), one barrier and one LDS round trip, and every
-// worker derives the effect of pivot j on row j+1 and on column j+1 itself (redundantly) before it
-// applies both rank-1 updates.  Every matrix element receives exactly the operations of plain
-// one-pivot-at-a-time elimination in the same order; the serial chain per pivot
-// (LDS write -> barrier -> LDS read -> reciprocal -> FMA) is paid once per pair.  NTI is even, so
-// a pair never straddles two register rows; an odd l ends with a dead second pivot (zero row).
-// Updates that cannot change a value that is read later are skipped at compile time (rows above the
-// pivots; eliminated columns of G; columns of the identity half that are still exactly zero):
-// 12.5 instead of 32 FMAs per worker and pivot on average, with the same live values.
-template <int NT>
-__global__ __launch_bounds__(CholShape<NT>::THREADS) void chol_inverse_kernel(GramJob a0, GramJob a1, int ell) {
-    using S = CholShape<NT>;
-    const double* __restrict__ const gram = blockIdx.x == 0 ? a0.gram : a1.gram;
-    double* __restrict__ const T = blockIdx.x == 0 ? a0.T : a1.T;
-    raise_wave_priority();
-    constexpr int LP = S::LP, KR = S::KR, KC = S::KC, NTI = S::NTI;
-    static_assert(NTI % 2 == 0, "pairs of pivots stay inside one register row");
-    __shared__ double rowb[2][2][2 * LP];
-    __shared__ double colb[2][2][LP];
-    __shared__ double thrb[2][2];
-    const int tid = threadIdx.x;
-    const bool worker = tid < S::WORKERS;
-    const int ti = worker ? tid / NTI : 0, tg = worker ? tid - ti * NTI : 0;
-    double mreg[KR][KC];
-    double thr[KR];             // 1e-10 * original diagonal of the thread's rows
-#pragma unroll
-    for (int ir = 0; ir < KR; ++ir) {
-        const int i = ti + NTI * ir;        // < LP; rows and columns >= ell enter as zeros
-        const double gd = gram[i * LP + i];
-        thr[ir] = i < ell ? 1e-10 * gd : 0.0;
-#pragma unroll
-        for (int kc = 0; kc < KC; ++kc) {
-            const int c = tg + NTI * kc;        // < 2 LP
-            const double g = gram[i * LP + (c < LP ? c : c - LP)];     // always inside the LP x LP array
-            mreg[ir][kc] = (c < LP) ? ((i < ell && c < ell) ? g : 0.0) : ((c - LP == i && i < ell) ? 1.0 : 0.0);
-        }
-    }
-    double pivot[KR];           // pivots of the thread's rows, 0 when dead
-#pragma unroll
-    for (int ir = 0; ir < KR; ++ir) pivot[ir] = 0.0;
-    int par = 0;
-    // Register columns that can still change in register row jr (pivots NTI jr .. NTI jr + NTI - 1).  In the
-    // left half [G] the columns of earlier register rows are eliminated and never read again; in the right
-    // half [I] the pivot rows are exactly zero beyond their own column, so later register rows see no change.
-    auto live_col = [](int kc, int jr) { return kc < KR ? kc >= jr : kc - KR <= jr; };
-    auto recip = [](double d) {     // 1/d: hardware estimate and two Newton steps
-        double q = __builtin_amdgcn_rcp(d);
-        q = fma(fma(-d, q, 1.0), q, q);
-        return fma(fma(-d, q, 1.0), q, q);
-    };
-#pragma unroll
-    for (int jr = 0; jr < KR; ++jr) {
-        for (int tj = 0; tj < NTI; tj += 2) {
-            const int j = tj + NTI * jr;
-            if (j >= ell) break;
-            if (worker) {
-                if (tg == tj || tg == tj + 1) {
-#pragma unroll
-                    for (int ir = 0; ir < KR; ++ir)
-                        if (ir >= jr) colb[par][tg - tj][ti + NTI * ir] = mreg[ir][jr];
-                }
-                if (ti == tj || ti == tj + 1) {
-#pragma unroll
-                    for (int kc = 0; kc < KC; ++kc)
-                        if (live_col(kc, jr)) rowb[par][ti - tj][tg + NTI * kc] = mreg[jr][kc];
-                    if (tg == ti) thrb[par][ti - tj] = thr[jr];
-                }
-            }
-            __syncthreads();
-            double l[KR], x[KR], r0[KC], r1[KC];
-#pragma unroll
-            for (int ir = 0; ir < KR; ++ir) {
-                l[ir] = ir >= jr ? colb[par][0][ti + NTI * ir] : 0.0;
-                x[ir] = ir >= jr ? colb[par][1][ti + NTI * ir] : 0.0;
-            }
-#pragma unroll
-            for (int kc = 0; kc < KC; ++kc) {
-                r0[kc] = live_col(kc, jr) ? rowb[par][0][tg + NTI * kc] : 0.0;
-                r1[kc] = live_col(kc, jr) ? rowb[par][1][tg + NTI * kc] : 0.0;
-            }
-            const double a = rowb[par][0][j], brow = rowb[par][0][j + 1], c11 = rowb[par][1][j + 1];
-            const double lnext = colb[par][0][j + 1];
-            const double thr0 = thrb[par][0], thr1 = thrb[par][1];
-            // pivot j
-            const bool live0 = a > thr0 && a > 0.0;
-            const double qa = live0 ? recip(a) : 0.0;
-            // its effect on row j+1 (every worker, for its own columns) and on the next pivot
-            const double f = -(lnext * qa);
-            double r1p[KC];
-#pragma unroll
-            for (int kc = 0; kc < KC; ++kc) r1p[kc] = live_col(kc, jr) ? fma(f, r0[kc], r1[kc]) : 0.0;
-            const double d1 = fma(f, brow, c11);
-            const bool live1 = d1 > thr1 && d1 > 0.0;
-            const double qd = live1 ? recip(d1) : 0.0;
-            if (ti == tj) pivot[jr] = live0 ? a : 0.0;
-            if (ti == tj + 1) pivot[jr] = live1 ? d1 : 0.0;
-#pragma unroll
-            for (int ir = 0; ir < KR; ++ir) {
-                if (ir < jr) continue;          // rows above the pivots: nothing to eliminate
-                const int i = ti + NTI * ir;
-                const double lq = (i > j) ? -(l[ir] * qa) : 0.0;
-                const double xi = fma(lq, brow, x[ir]);             // column j+1 after pivot j
-                const double mq = (i > j + 1) ? -(xi * qd) : 0.0;
-#pragma unroll
-                for (int kc = 0; kc < KC; ++kc)
-                    if (live_col(kc, jr)) mreg[ir][kc] = fma(mq, r1p[kc], fma(lq, r0[kc], mreg[ir][kc]));
-            }
-            par ^= 1;
-        }
-    }
-    if (!worker) return;
-#pragma unroll
-    for (int ir = 0; ir < KR; ++ir) {
-        const double pv = pivot[ir];
-        double inv = 0.0;
-        if (pv > 0.0) {      // 1/sqrt by the hardware estimate and three Newton steps
-            inv = __builtin_amdgcn_rsq(pv);
-            inv = inv * fma(-0.5 * pv, inv * inv, 1.5);
-            inv = inv * fma(-0.5 * pv, inv * inv, 1.5);
-            inv = inv * fma(-0.5 * pv, inv * inv, 1.5);
-        }
-        const int i = ti + NTI * ir;
-#pragma unroll
-        for (int kc = 0; kc < KC; ++kc) {
-            const int c = tg + NTI * kc;
-            if (c >= LP) T[(c - LP) * LP + i] = mreg[ir][kc] * inv;
-        }
-    }
-}
-
 // out = In . Mat with float64 accumulation on the float64 matrix cores, one wavefront per 16
 // rows.  v_mfma_f64_16x16x4 operand layout (lane l): A[i = l%16][k = l/16], B[k = l/16][j = l%16],
 // D[i = 4v + l/16][j = l%16] for v = 0..3.  The reduction index may be visited in any order, so
@@ -479,6 +323,188 @@ __global__ __launch_bounds__(64) void apply_kernel(ApplyJobs jobs) {
                 }
             }
         }
+    }
+}
+
+__device__ __forceinline__ double rcp_f64(double d) {       // hardware estimate and two Newton steps
+    double q = __builtin_amdgcn_rcp(d);
+    q = fma(fma(-d, q, 1.0), q, q);
+    return fma(fma(-d, q, 1.0), q, q);
+}
+
+// Orthonormalization Q = Y T in one launch: every workgroup forms T = L^-T of the Gram matrix G = L L^T for itself, by
+// symmetric elimination of the augmented matrix [G | I], and applies it to its rows of Y in place (on the float64 matrix
+// cores, layout as at apply_kernel; the rows are loaded before the elimination starts).  Step j subtracts
+// (M[i][j] / d_j) * (row j) from every row i > j, d_j the pivot M[j][j].  The left half is then L^T with rows unscaled (row j
+// times sqrt(d_j)), the right half is L^-1 with row j unscaled the same way, so T[a][b] = M[b][LP + a] / sqrt(d_b).  A pivot
+// below 1e-10 of its original diagonal (rank-deficient sketch) is dead: it eliminates nothing and its row and column of T
+// are zero.
+//
+// 256 threads in a 16 x 16 grid (ti, tg) own rows ti + 16 ir and columns tg + 16 kc: pivot j = tj + 16 jr sits in register
+// row and column jr, compile-time constants inside the unrolled jr loop.  Two pivots per step: pivots j and j + 1 share one
+// publication in LDS (rows and columns j, j + 1 as they stand before pivot j; two generations) and one barrier, and every
+// thread derives the effect of pivot j on row and column j + 1 itself before it applies both rank-1 updates; an odd l ends
+// with a dead second pivot.  Updates that cannot change a value that is read later are left out at compile time (rows above
+// the pivots, eliminated columns of G, columns of the identity half that are still zero).
+//
+// What bounds it: the chain of a step, LDS write -> barrier -> LDS read -> two reciprocals -> FMA, about 500 cycles.  T formed
+// by one workgroup of l^2 / 16 workers in a launch of its own, and applied in another, took 10.5 + 4.7 us and a gap at 24
+// columns, 15 + 6.4 at 40, 36 + 16 at 80 (those workers shared one to four SIMDs' LDS reads).  Calls with two launches / with
+// one (one power iteration; the small SVD as it is now): 2048^3 l = 24 215 / 197 us, 40 296 / 270, 80 548 / 491; 4096^3 24
+// 361 / 344, 40 444 / 417, 80 726 / 664; 8192^3 80 1902 / 1855; 16384^3 the same.  82 to 173 registers: the waves start
+// beside resident workgroups of the other chain's passes (4096^3, l = 40, at 306 registers 433 us).
+// parts > 0: G is still in that many partials (see gram_sum_parts_kernel, whose order of addition is kept).
+struct OrthGrid { int nb, rows, parts; };       // workgroups of the job, rows per workgroup (a multiple of 64)
+template <int NT>
+__global__ __launch_bounds__(256, NT <= 2 ? 4 : (NT <= 4 ? 3 : 2)) void orth_apply_kernel(GramJob a0, GramJob a1, OrthGrid g0, OrthGrid g1, int ell) {
+    constexpr int LP = 16 * NT, KC = 2 * NT, KQ = LP / 4, LDT = LP + 1;
+    raise_wave_priority();
+    const bool first = (int)blockIdx.x < g0.nb;
+    const double* __restrict__ const gram = first ? a0.gram : a1.gram;
+    const double* __restrict__ const gpart = first ? a0.gpart : a1.gpart;
+    float* __restrict__ const Y = first ? a0.Y : a1.Y;
+    const int n = first ? a0.n : a1.n, rows = first ? g0.rows : g1.rows, parts = first ? g0.parts : g1.parts;
+    const int blk = first ? blockIdx.x : blockIdx.x - g0.nb;
+    __shared__ double rowb[2][2][2 * LP];
+    __shared__ double colb[2][2][LP];
+    __shared__ double thrb[2][2];
+    __shared__ double Ts[LP * LDT];
+    const int tid = threadIdx.x, ti = tid >> 4, tg = tid & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, li = lane & 15, kq = lane >> 4;
+    const int row_end = min(n, (blk + 1) * rows);
+    // the wave's first 16 rows of Y: lane (li, kq) holds a quarter of row li
+    float y[KQ];
+    auto load_rows = [&](int r0) {
+        const float4* ip = reinterpret_cast<const float4*>(Y + (size_t)min(r0 + li, n - 1) * LP + kq * KQ);
+#pragma unroll
+        for (int u = 0; u < KQ / 4; ++u) {
+            const float4 t = ip[u];
+            y[4 * u + 0] = t.x; y[4 * u + 1] = t.y; y[4 * u + 2] = t.z; y[4 * u + 3] = t.w;
+        }
+    };
+    load_rows(blk * rows + wave * 16);
+    double mreg[NT][KC];
+    if (NT == 1 && parts > 0) {         // one entry per thread
+        const int per = (parts + 7) >> 3;
+        double v[8][ORTH_PER], sum = 0.0;
+#pragma unroll
+        for (int p = 0; p < 8; ++p)
+#pragma unroll
+            for (int u = 0; u < ORTH_PER; ++u) v[p][u] = gpart[(size_t)min(p * per + u, parts - 1) * (LP * LP) + tid];
+#pragma unroll
+        for (int p = 0; p < 8; ++p) {
+            double acc = 0.0;
+#pragma unroll
+            for (int u = 0; u < ORTH_PER; ++u) acc += (u < per && p * per + u < parts) ? v[p][u] : 0.0;
+            sum = p == 0 ? acc : sum + acc;
+        }
+        mreg[0][0] = sum;
+    } else {
+#pragma unroll
+        for (int ir = 0; ir < NT; ++ir)
+#pragma unroll
+            for (int kc = 0; kc < NT; ++kc) mreg[ir][kc] = gram[(ti + 16 * ir) * LP + tg + 16 * kc];
+    }
+    double thr[NT], pivot[NT];          // 1e-10 * original diagonal, on the threads that own it; pivots, 0 when dead
+#pragma unroll
+    for (int ir = 0; ir < NT; ++ir) {
+        const int i = ti + 16 * ir;     // < LP; rows and columns >= ell enter as zeros
+        thr[ir] = (i < ell && ti == tg) ? 1e-10 * mreg[ir][ir] : 0.0;
+        pivot[ir] = 0.0;
+#pragma unroll
+        for (int kc = 0; kc < NT; ++kc) {
+            const int c = tg + 16 * kc;
+            if (i >= ell || c >= ell) mreg[ir][kc] = 0.0;
+            mreg[ir][NT + kc] = (c == i && i < ell) ? 1.0 : 0.0;
+        }
+    }
+    int par = 0;
+    auto live_col = [](int kc, int jr) { return kc < NT ? kc >= jr : kc - NT <= jr; };
+#pragma unroll
+    for (int jr = 0; jr < NT; ++jr) {
+        for (int tj = 0; tj < 16; tj += 2) {
+            const int j = tj + 16 * jr;
+            if (j >= ell) break;
+            if (tg == tj || tg == tj + 1) {
+#pragma unroll
+                for (int ir = 0; ir < NT; ++ir)
+                    if (ir >= jr) colb[par][tg - tj][ti + 16 * ir] = mreg[ir][jr];
+            }
+            if (ti == tj || ti == tj + 1) {
+#pragma unroll
+                for (int kc = 0; kc < KC; ++kc)
+                    if (live_col(kc, jr)) rowb[par][ti - tj][tg + 16 * kc] = mreg[jr][kc];
+                if (tg == ti) thrb[par][ti - tj] = thr[jr];
+            }
+            __syncthreads();
+            double l[NT], x[NT], r0[KC], r1[KC];
+            const double a = rowb[par][0][j], brow = rowb[par][0][j + 1], c11 = rowb[par][1][j + 1];
+            const double lnext = colb[par][0][j + 1];
+            const double thr0 = thrb[par][0], thr1 = thrb[par][1];
+#pragma unroll
+            for (int ir = 0; ir < NT; ++ir) {
+                l[ir] = ir >= jr ? colb[par][0][ti + 16 * ir] : 0.0;
+                x[ir] = ir >= jr ? colb[par][1][ti + 16 * ir] : 0.0;
+            }
+#pragma unroll
+            for (int kc = 0; kc < KC; ++kc) {
+                r0[kc] = live_col(kc, jr) ? rowb[par][0][tg + 16 * kc] : 0.0;
+                r1[kc] = live_col(kc, jr) ? rowb[par][1][tg + 16 * kc] : 0.0;
+            }
+            const bool live0 = a > thr0 && a > 0.0;
+            const double qa = live0 ? rcp_f64(a) : 0.0;
+            const double f = -(lnext * qa);
+            const double d1 = fma(f, brow, c11);
+            const bool live1 = d1 > thr1 && d1 > 0.0;
+            const double qd = live1 ? rcp_f64(d1) : 0.0;
+            if (ti == tj) pivot[jr] = live0 ? a : 0.0;
+            if (ti == tj + 1) pivot[jr] = live1 ? d1 : 0.0;
+            double r1p[KC];
+#pragma unroll
+            for (int kc = 0; kc < KC; ++kc) r1p[kc] = live_col(kc, jr) ? fma(f, r0[kc], r1[kc]) : 0.0;
+#pragma unroll
+            for (int ir = 0; ir < NT; ++ir) {
+                if (ir < jr) continue;          // rows above the pivots: nothing to eliminate
+                const int i = ti + 16 * ir;
+                const double lq = (i > j) ? -(l[ir] * qa) : 0.0;
+                const double xi = fma(lq, brow, x[ir]);             // column j+1 after pivot j
+                const double mq = (i > j + 1) ? -(xi * qd) : 0.0;
+#pragma unroll
+                for (int kc = 0; kc < KC; ++kc)
+                    if (live_col(kc, jr)) mreg[ir][kc] = fma(mq, r1p[kc], fma(lq, r0[kc], mreg[ir][kc]));
+            }
+            par ^= 1;
+        }
+    }
+#pragma unroll
+    for (int ir = 0; ir < NT; ++ir) {
+        const double pv = pivot[ir];
+        double inv = 0.0;
+        if (pv > 0.0) {      // 1/sqrt by the hardware estimate and three Newton steps
+            inv = __builtin_amdgcn_rsq(pv);
+            inv = inv * fma(-0.5 * pv, inv * inv, 1.5);
+            inv = inv * fma(-0.5 * pv, inv * inv, 1.5);
+            inv = inv * fma(-0.5 * pv, inv * inv, 1.5);
+        }
+#pragma unroll
+        for (int kc = 0; kc < NT; ++kc) Ts[(tg + 16 * kc) * LDT + ti + 16 * ir] = mreg[ir][NT + kc] * inv;
+    }
+    __syncthreads();
+    typedef double v4d __attribute__((ext_vector_type(4)));
+    for (int r0 = blk * rows + wave * 16; r0 < row_end; r0 += 64) {
+#pragma unroll 1
+        for (int ct = 0; ct < NT; ++ct) {           // (rolled: the elements of T of one column tile in registers at a time)
+            v4d acc = (v4d){0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int s = 0; s < KQ; ++s)
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)y[s], Ts[(kq * KQ + s) * LDT + 16 * ct + li], acc, 0, 0, 0);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int orow = r0 + 4 * v + kq;
+                if (orow < n) Y[(size_t)orow * LP + 16 * ct + li] = (float)acc[v];
+            }
+        }
+        if (r0 + 64 < row_end) load_rows(r0 + 64);
     }
 }
 
@@ -592,11 +618,6 @@ __device__ __forceinline__ double oct_sum_f64(double x) {
     x += dpp_row_f64<0x4e>(x);              // quad_perm 2,3,0,1
     x += dpp_row_f64<0x141>(x);             // row_half_mirror
     return x;
-}
-__device__ __forceinline__ double rcp_f64(double d) {       // hardware estimate and two Newton steps
-    double q = __builtin_amdgcn_rcp(d);
-    q = fma(fma(-d, q, 1.0), q, q);
-    return fma(fma(-d, q, 1.0), q, q);
 }
 
 // Groups of lanes per wave and waves, by register columns.  Measured, us per call of the small SVD, (groups, waves): l = 16
@@ -1471,13 +1492,6 @@ int launch_gram_sum(const GramJob* job, int njob, int LP, hipStream_t st) {
     return LRQMM_OK;
 }
 
-int launch_chol_inverse(const GramJob* job, int njob, int ell, int LP, hipStream_t st) {
-    NT_SWITCH(LP / 16, hipLaunchKernelGGL((chol_inverse_kernel<NT_>), dim3(njob), dim3(CholShape<NT_>::THREADS), 0, st, job[0],
-                                          job[njob - 1], ell));
-    LRQ_CHECK_LAUNCH();
-    return LRQMM_OK;
-}
-
 int launch_apply(const ApplyJob* job, int njob, int LP, hipStream_t st) {
     ApplyJobs a = {};
     int total = 0;
@@ -1488,6 +1502,27 @@ int launch_apply(const ApplyJob* job, int njob, int LP, hipStream_t st) {
     }
     if (total == 0) return LRQMM_OK;
     NT_SWITCH(LP / 16, hipLaunchKernelGGL((apply_kernel<NT_>), dim3(total), dim3(64), 0, st, a));
+    LRQ_CHECK_LAUNCH();
+    return LRQMM_OK;
+}
+
+// Few partials (16 columns, up to 256 rows) are added where they are used, one launch less.  Gram sum as a launch of its own /
+// here: 200^3 l = 10 92.4 / 88.1 us per call, l = 24 139.6 / 140.6; with up to 64 partials 400^3 l = 10 105.3 / 108.3, 1000^3
+// 113.5 / 119.1.
+bool orth_apply_sums(int blocks, int LP) { return blocks <= 8 * ORTH_PER && LP == 16; }
+
+int launch_orth_apply(const GramJob* job, int njob, int ell, int LP, bool sum, hipStream_t st) {
+    OrthGrid g[2] = {};
+    for (int i = 0; i < njob; ++i) {
+        const int blocks = job[i].blocks > 0 ? job[i].blocks : gram_blocks(job[i].n, LP);
+        if (sum && !orth_apply_sums(blocks, LP)) return LRQMM_ERR_UNSUPPORTED;
+        const int units = ceil_div(job[i].n, 64);
+        g[i].rows = 64 * ceil_div(units, ORTH_BLOCKS);
+        g[i].nb = ceil_div(job[i].n, g[i].rows);
+        g[i].parts = sum ? blocks : 0;
+    }
+    const dim3 grid(g[0].nb + g[1].nb);
+    NT_SWITCH(LP / 16, hipLaunchKernelGGL((orth_apply_kernel<NT_>), grid, dim3(256), 0, st, job[0], job[njob - 1], g[0], g[1], ell));
     LRQ_CHECK_LAUNCH();
     return LRQMM_OK;
 }
