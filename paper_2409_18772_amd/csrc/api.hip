@@ -254,6 +254,22 @@ bool two_chains(int M, int N, int K) {
     return elements > 13000000;
 }
 
+// Whether the integer product (`tiles` tiles of 256 x 256, one per CU at a time) runs early, beside the small SVDs and the
+// panel kernels, with the update as a kernel of its own, or with its fused epilogue after the panels.  Early it saves a last
+// round that leaves most CUs idle, and the time of the SVDs where the product is one round and not much longer than they
+// are; it writes and reads C once more, and a long product holds the CUs that the panel kernels need.  Measured, early /
+// fused, us per call (one power iteration): whole rounds, 4096^3 l = 24 374 / 342, 32 386 / 369, 40 423 / 428, 56 530 / 543,
+// 80 665 / 680; 8192 x 4096 x 4096 l = 40 604 / 593, 56 722 / 719,
+// 80 836 / 909; 8192^3 l = 40 1512 / 1463, 56 1684 / 1660, 80 1854 / 1867; 16384^3
+// l = 40 7540 / 7220, 56 7675 / 7230, 80 8232 / 7900.  Rounds filled to 0.56 (3072^3) l = 32 303 / 309; 0.63 (4608^3) l = 24
+// 460 / 458, 32 472 / 487, 40 528 / 565; 0.75 (6144^3) 32 785 / 833; 0.77 (7168^3) 32 1071 / 1117; 0.84 (9216^3) 40 1905 / 1941;
+// 0.88 (7680^3) 40 1341 / 1326; 0.89 (10240^3) 80 2930 / 3050; 0.95 (5632^3) 32 662 / 653.
+bool early_product(long long tiles, int cus, int ell) {
+    const long long rounds = (tiles + cus - 1) / cus;
+    if (ell < 32) return false;
+    return 100 * tiles <= (ell > 64 ? 90 : 85) * rounds * cus || rounds <= (ell > 64 ? 2 : (ell >= 40 ? 1 : 0));
+}
+
 // int32 accumulation is safe when K * (qmax+1)^2 < 2^31.
 bool k_fits_int32(int K, int bits) {
     const long long lim = 1ll << (2 * (bits - 1));
@@ -673,13 +689,8 @@ int lrqmm_matmul_ex(int M, int N, int K, int bits, int rank, int oversample, int
     // stream, leaves raw int32 sums in C, and the epilogue follows the panels as a kernel of
     // its own.  Used for problems on the large-tile kernel.
     // (the raw sums need D's memory: only when its old contents are not an input and it is dense)
-    // Measured, early / fused after the panels, us per call (one power iteration): l = 24: 4096^3 388 / 378, 6144^3
-    // 804 / 830, 8192^3 1428 / 1346, 16384^3 7032 / 6664; l = 32: 409 / 417, 814 / 886, 1460 / 1414, 7184 / 6860; l = 40:
-    // 466 / 479, 888 / 980, 1499 / 1500, 7388 / 7041; l = 56: 615 / 648, 1019 / 1207, 1708 / 1820, 7711 / 7666; l = 80:
-    // 850 / 893, 1267 / 1531, 1919 / 2151, 8254 / 8622.  The early product pays while the SVD hides enough of it (a
-    // narrow sketch's is too short); a long product outlasts it and holds the CUs the panel kernels need, so that at 32
-    // to 40 columns the fused kernel would be the faster one from 8192^3 on.
-    const bool early = factored && rank_update_usable(M, N, C) && beta == 0.0f && ldd == N && ell >= 32;
+    const bool early = factored && rank_update_usable(M, N, C) && beta == 0.0f && ldd == N &&
+                       early_product(int8_gemm_tiles(M, N), side->cus, ell);
     // Nothing to truncate: C needs no more of a factorization than U diag(Sigma) Vt = Q (Q^T R), and the small SVD falls
     // away.  Up to 16 columns; a call with a wider sketch gives the bits of the separate quantize, rsvd and gemm calls (a
     // narrow one's first product differs from them anyway).

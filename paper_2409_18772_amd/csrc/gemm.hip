@@ -21,6 +21,7 @@ static inline bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 #define BK 64
 #define GEMM_MIN_TILES 256
+#define PANEL_LD 40         // row stride of a 32-column chunk of a bfloat16 panel plane (80 bytes: conflict-free 16-byte reads)
 #ifndef LDS_STRIDE
 #define LDS_STRIDE 80
 #endif
@@ -405,16 +406,111 @@ __global__ __launch_bounds__(512, 1) void int8_gemm256_kernel(int M, int N, int 
     // C == nullptr: only the raw int32 sums are wanted (the dequantization and the update then
     // run later, in rank_update_kernel), and the step vectors are not read.
     const bool want_c = C != nullptr;
+    // Wider panels: the float32 matrix cores would take 4 R2P M N flops at 1/16 of the bfloat16 rate, so the tile's panel rows
+    // are split into three bfloat16 planes while they are staged (32 columns at a time, in the LDS that the operand tiles have
+    // left) and the six plane products of weight >= 2^-16 run on v_mfma_f32_32x32x16_bf16, as in rank_update_bf16_kernel.
+    if (COMP && R2P > 64) {
+        uint16_t* const Lq = reinterpret_cast<uint16_t*>(&As[0][0]);
+        uint16_t* const Rq = reinterpret_cast<uint16_t*>(&Bs[0][0]);
+        constexpr int PL = 256 * PANEL_LD;          // one plane
+        static_assert(2 * BTM * BSTRIDE >= 3 * PL * 2, "three planes of a 32-column chunk fit an operand's LDS");
+        v16f f[2][4];
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt) {
+            const int rbase = m0 + wm * 64 + mt * 32;
+            float sa[16];
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int row = rbase + 8 * (v >> 2) + 4 * lh + (v & 3);
+                sa[v] = row < M ? sA[row] : 0.f;
+            }
+#pragma unroll
+            for (int nt = 0; nt < 4; ++nt) {
+                const int col = n0 + wn * 128 + nt * 32 + l32;
+                const float sb = col < N ? sB[col] : 0.f;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int row = rbase + 8 * (v >> 2) + 4 * lh + (v & 3);
+                    if (WCINT && row < M && col < N) Cint[(size_t)row * N + col] = acc[mt][nt][v];
+                    f[mt][nt][v] = ((float)acc[mt][nt][v] * sa[v]) * sb;
+                }
+            }
+        }
+        for (int t0 = 0; t0 < R2P; t0 += 32) {
+            __syncthreads();            // nobody reads the operand tiles, or the previous chunk, any more
+            // 2 panels x 256 rows x 4 groups of 8 columns, four units per thread
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int unit = tid + 512 * i, r = (unit >> 2) & 255, c8 = (unit & 3) * 8;
+                const bool left = i < 2;
+                // rows / columns past the end re-read the last one (rows are never stored, columns enter as zeros)
+                const float* src = left ? Lp + (size_t)min(m0 + r, M - 1) * R2P : Rp + (size_t)min(n0 + r, N - 1) * R2P;
+                float v[8];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int col = t0 + c8 + 4 * h;
+                    const bool in = col < R2P;
+                    const float4 x = *reinterpret_cast<const float4*>(src + min(col, R2P - 4));
+                    v[4 * h + 0] = in ? x.x : 0.f; v[4 * h + 1] = in ? x.y : 0.f;
+                    v[4 * h + 2] = in ? x.z : 0.f; v[4 * h + 3] = in ? x.w : 0.f;
+                }
+                const Planes3 pl = split_planes<3>(v);
+                uint16_t* dst = (left ? Lq : Rq) + r * PANEL_LD + c8;
+                *reinterpret_cast<v8bf16*>(dst) = pl.p1;
+                *reinterpret_cast<v8bf16*>(dst + PL) = pl.p2;
+                *reinterpret_cast<v8bf16*>(dst + 2 * PL) = pl.p3;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                v8bf16 a[2][3];
+#pragma unroll
+                for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+                    for (int q = 0; q < 3; ++q)
+                        a[mt][q] = *reinterpret_cast<const v8bf16*>(Lq + q * PL + (wm * 64 + mt * 32 + l32) * PANEL_LD + 16 * u + 8 * lh);
+#pragma unroll
+                for (int nt = 0; nt < 4; ++nt) {
+                    v8bf16 b[3];
+#pragma unroll
+                    for (int q = 0; q < 3; ++q)
+                        b[q] = *reinterpret_cast<const v8bf16*>(Rq + q * PL + (wn * 128 + nt * 32 + l32) * PANEL_LD + 16 * u + 8 * lh);
+                    // smallest products first; the two row tiles are independent chains
+#define LRQ_PP(QA, QB)                                                                                          \
+    _Pragma("unroll") for (int mt = 0; mt < 2; ++mt) f[mt][nt] =                                                \
+        __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[mt][QA], b[QB], f[mt][nt], 0, 0, 0);
+                    LRQ_PP(0, 2)
+                    LRQ_PP(1, 1)
+                    LRQ_PP(2, 0)
+                    LRQ_PP(0, 1)
+                    LRQ_PP(1, 0)
+                    LRQ_PP(0, 0)
+#undef LRQ_PP
+                }
+            }
+        }
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+            for (int nt = 0; nt < 4; ++nt) {
+                const int col = n0 + wn * 128 + nt * 32 + l32;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int row = m0 + wm * 64 + mt * 32 + 8 * (v >> 2) + 4 * lh + (v & 3);
+                    if (row < M && col < N) store_out(out, row, col, f[mt][nt][v]);
+                }
+            }
+        return;
+    }
     // Panels of up to 64 columns: the tile's 256 rows of Lp and of Rp are staged in the LDS that the operand
     // tiles have left (whole-row loads; rows past the end as zeros; row stride R2P + 4 floats: conflict-free
     // 16-byte reads), instead of 32 cache lines per load instruction from global memory.  Same values, same
     // order of the products.
-    const bool staged = COMP && R2P <= 64;
     const int LDP = R2P + 4;
     float* const Ls = reinterpret_cast<float*>(&As[0][0]);
     float* const Rs = reinterpret_cast<float*>(&Bs[0][0]);
     static_assert(2 * BTM * BSTRIDE >= 256 * 68 * 4, "a 64-column panel tile fits an operand's LDS");
-    if (staged) {
+    if (COMP) {
         __syncthreads();        // every wave has read its last operand fragments
         const int q4 = R2P / 4;
         for (int idx = tid; idx < 256 * q4; idx += 512) {
@@ -430,9 +526,6 @@ __global__ __launch_bounds__(512, 1) void int8_gemm256_kernel(int M, int N, int 
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt) {
         const int rbase = m0 + wm * 64 + mt * 32;
-        const int lrow = rbase + l32;
-        const bool lok = lrow < M;
-        const float* lp = COMP ? Lp + (size_t)(lok ? lrow : 0) * R2P + 4 * lh : nullptr;
         const float* lps = Ls + (wm * 64 + mt * 32 + l32) * LDP + 4 * lh;
         float sa[16];
 #pragma unroll
@@ -455,21 +548,11 @@ __global__ __launch_bounds__(512, 1) void int8_gemm256_kernel(int M, int N, int 
                 }
                 f[v] = ((float)acc[mt][nt][v] * sa[v]) * sb;
             }
-            if (COMP && staged) {
+            if (COMP) {
                 const float* rps = Rs + (wn * 128 + nt * 32 + l32) * LDP + 4 * lh;
                 for (int t0 = 0; t0 < R2P; t0 += 8) {
                     const float4 a4 = *reinterpret_cast<const float4*>(lps + t0);
                     const float4 b4 = *reinterpret_cast<const float4*>(rps + t0);
-                    f = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.x, b4.x, f, 0, 0, 0);
-                    f = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.y, b4.y, f, 0, 0, 0);
-                    f = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.z, b4.z, f, 0, 0, 0);
-                    f = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.w, b4.w, f, 0, 0, 0);
-                }
-            } else if (COMP) {
-                const float* rp = Rp + (size_t)(col_ok ? col : 0) * R2P + 4 * lh;
-                for (int t0 = 0; t0 < R2P; t0 += 8) {
-                    float4 a4 = lok ? *reinterpret_cast<const float4*>(lp + t0) : make_float4(0.f, 0.f, 0.f, 0.f);
-                    float4 b4 = col_ok ? *reinterpret_cast<const float4*>(rp + t0) : make_float4(0.f, 0.f, 0.f, 0.f);
                     f = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.x, b4.x, f, 0, 0, 0);
                     f = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.y, b4.y, f, 0, 0, 0);
                     f = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.z, b4.z, f, 0, 0, 0);
@@ -1115,9 +1198,8 @@ int launch_int8_gemm_sums_finish(int M, int N, int K, const int8_t* Aq, const in
 
 // (Measured on both sides of the limit: at 121 tiles of 256 x 256 the 128-tile kernel is as fast, 59 us at
 // 2816^3; at 144 tiles it needs 103 us against 63 us at 3072^3.)
-bool int8_gemm_large_tiles(int M, int N) {
-    return M >= BTM && N >= BTN && (long long)ceil_div(M, BTM) * ceil_div(N, BTN) >= 128;
-}
+long long int8_gemm_tiles(int M, int N) { return (long long)ceil_div(M, BTM) * ceil_div(N, BTN); }
+bool int8_gemm_large_tiles(int M, int N) { return M >= BTM && N >= BTN && int8_gemm_tiles(M, N) >= 128; }
 
 // The early-GEMM schedule needs the large-tile kernel and 16-byte accesses to the rows of C.
 bool rank_update_usable(int M, int N, const float* C) {

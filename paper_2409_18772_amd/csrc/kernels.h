@@ -193,6 +193,7 @@ int launch_int8_gemm_sums_finish(int M, int N, int K, const int8_t* Aq, const in
 // True when launch_int8_gemm uses the large-tile kernel, which accepts C == null together with
 // Cint != null (raw int32 sums only; sA, sB are then not read).
 bool int8_gemm_large_tiles(int M, int N);
+long long int8_gemm_tiles(int M, int N);       // of 256 x 256, how many cover the output
 // True when the integer product may run early and launch_rank_update finish the job: the
 // large-tile kernel applies, N % 4 == 0 and C is 16-byte aligned.
 bool rank_update_usable(int M, int N, const float* C);

@@ -314,3 +314,43 @@ def test_gemm_extreme_codes_and_limits():
     # missing workspace
     assert lib.lrqmm_gemm(1, 1, 16, 8, 0, z.data_ptr(), z.data_ptr(), z.data_ptr(), z.data_ptr(), None, None, None,
                           None, None, None, z.data_ptr(), None, None, 0, None) == -3
+
+
+# The large-tile kernel with panels of more than 64 columns (bfloat16 planes, 32 columns at a time): one column more than
+# 64, a chunk that is not full, whole chunks, the widest; whole and ragged tiles, the last rows and columns of each.
+@pytest.mark.parametrize("M,N,K,rank", [(2816, 3072, 256, 33), (2817, 2820, 300, 40), (2900, 2819, 143, 48), (3072, 2816, 384, 64),
+                                        (2830, 2840, 200, 80)])
+def test_gemm_wide_panels_on_large_tiles(M, N, K, rank):
+    """Random factors, sampled rows against float64; alpha, beta and a strided destination; the int32 sums beside C.
+    Bound: an entry is a float32 sum of 2r + 1 terms of total magnitude S, which errs by at most (2r + 2) 2^-24 S, plus
+    three roundings of the dequantization; the panel entries are length-K sums of float32 rounding each: a factor 4."""
+    import torch
+    import paper_2409_18772_amd as L
+    rng = np.random.default_rng(M + rank)
+    say("wide panels", M, N, K, rank)
+    Aq = rng.integers(-128, 128, (M, K), dtype=np.int8)
+    Bq = rng.integers(-128, 128, (K, N), dtype=np.int8)
+    amA, amB = rng.uniform(0.5, 2.0, M).astype(np.float32), rng.uniform(0.5, 2.0, N).astype(np.float32)
+    f32 = lambda x: np.ascontiguousarray(x, dtype=np.float32)
+    orth = lambda n: f32(np.linalg.qr(rng.standard_normal((n, rank)))[0])
+    U, Vt, W, Zt = orth(M), f32(orth(K).T), orth(K), f32(orth(N).T)
+    S, G = (f32(np.sort(rng.uniform(0.1, 3.0, rank))[::-1]) for _ in range(2))
+    dev = [to_dev(t) for t in (Aq, amA, np.ascontiguousarray(Bq.T), amB)]
+    fa, fb = tuple(map(to_dev, (U, S, Vt))), tuple(map(to_dev, (W, G, Zt)))
+    C, Cint = L.lrqmm_gemm(*dev, 8, fa, fb, want_cint=True)
+    rows = np.unique(np.concatenate([[0, 255, 256, M - 1, M - 2, M // 256 * 256 - 1], rng.integers(0, M, 12)]))
+    assert np.array_equal(to_np(Cint)[rows].astype(np.int64), Aq[rows].astype(np.int64) @ Bq.astype(np.int64))
+    sa, sb = (amA / np.float32(127)).astype(np.float64), (amB / np.float32(127)).astype(np.float64)
+    At, Bt = Aq[rows] * sa[rows, None], Bq * sb[None, :]
+    us, P, Q = U[rows].astype(np.float64) * S, Vt @ Bt + (Vt.astype(np.float64) @ W) @ (G[:, None] * Zt.astype(np.float64)), G[:, None] * Zt.astype(np.float64)
+    Sw = At @ W.astype(np.float64)
+    ref = At @ Bt + us @ P + Sw @ Q
+    size = np.abs(At @ Bt) + np.abs(us) @ (np.abs(Vt) @ np.abs(Bt)) + np.abs(At) @ np.abs(W) @ np.abs(Q)
+    err = np.abs(to_np(C)[rows] - ref)
+    assert np.all(err <= 4 * (2 * rank + 3) * 2.0 ** -24 * size)
+    assert rel_fro(ref, to_np(C)[rows]) < 3e-6
+    D = torch.full((M, N + 5), 0.5, dtype=torch.float32, device="cuda")
+    L.lrqmm_gemm_ex(dev[0], dev[1], dev[2], dev[3], 8, D[:, :N], 1.5, -0.5, fa, fb)
+    assert torch.all(D[:, N:] == 0.5)
+    want = 1.5 * to_np(C)[rows].astype(np.float64) - 0.25
+    assert np.abs(to_np(D)[rows, :N] - want).max() <= 3 * 2.0 ** -24 * np.abs(want).max() + 2.0 ** -24
