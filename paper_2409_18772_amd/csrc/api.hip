@@ -43,7 +43,7 @@ struct RsvdWs {
 size_t carve_rsvd(Arena& a, int rows, int cols, int axis, int LP, int rank, RsvdWs* w) {
     const int nscale = axis == LRQMM_AXIS_ROW ? rows : cols;
     const int npad = pad_to(nscale, 4);
-    const PassPlan pn = plan_pass_n(rows, cols, LP), pt = plan_pass_t(rows, cols);
+    const PassPlan pn = plan_pass_n(rows, cols, LP), pt = plan_pass_t(rows, cols, LP);
     const size_t part = (size_t)LP * (size_t)((size_t)pn.splits * rows > (size_t)pt.splits * cols
                                                   ? (size_t)pn.splits * rows
                                                   : (size_t)pt.splits * cols);
@@ -311,7 +311,7 @@ static int make_factor(Factor* f, const float* X, int ldx, int rows, int cols, i
     Arena a(workspace);
     if (carve_rsvd(a, rows, cols, axis, LP, rank, &f->w) > workspace_bytes) return LRQMM_ERR_WORKSPACE;
     f->op = {X, ldx, rows, cols, axis, f->w.lam, f->w.s, f->w.Wc, f->w.Yr, f->w.partial, amax, codes,
-             plan_pass_n(rows, cols, LP), plan_pass_t(rows, cols)};
+             plan_pass_n(rows, cols, LP), plan_pass_t(rows, cols, LP)};
     f->U = U; f->Sigma = Sigma; f->Vt = Vt;
     return LRQMM_OK;
 }

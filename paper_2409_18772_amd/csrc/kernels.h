@@ -47,7 +47,7 @@ struct PassPlan {
     int chunk;    // reduction-index range per split (multiple of 64)
 };
 PassPlan plan_pass_n(int rows, int cols, int LP);
-PassPlan plan_pass_t(int rows, int cols);
+PassPlan plan_pass_t(int rows, int cols, int LP);
 PassPlan plan_codes(int rows, int K);       // code products (launch_codes_mul_n2)
 // One operand of a factorization, as the passes see it.  X is rows x cols with row stride ldx (>= cols); axis 0: scales
 // by row, 1: by column (lam, s: the step vectors).

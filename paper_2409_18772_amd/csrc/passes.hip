@@ -1164,10 +1164,13 @@ static bool pass_n_wide(int rows, int cols, int LP) {
 }
 
 // (an empty reduction has no ranges: splits = 0)
+// Up to 1024 rows ranges of one chunk, down to 64 elements: such a pass is the load latency of its chunks, one after the
+// other.  Two chunks and more / this, us per call: 200^3 l = 10 87.7 / 83.5, 256^3 l = 8 50.8 / 48.2, 512^3 l = 24 130.4 /
+// 127.9, 1000^3 l = 10 113.1 / 108.2; beyond 2000^3 l = 10 157.0 / 163.4.
 PassPlan plan_pass_n(int rows, int cols, int LP) {
     const int unit = LP == 16 ? KCHUNK : 64;        // chunk depth of the kernel
     PassPlan p;
-    int s = pick_splits(ceil_div(rows, pass_n_wide(rows, cols, LP) ? 128 : 64), cols, 2 * unit, 512, MAX_SPLITS);
+    int s = pick_splits(ceil_div(rows, pass_n_wide(rows, cols, LP) ? 128 : 64), cols, rows <= 1024 ? 64 : 2 * unit, 512, MAX_SPLITS);
     p.chunk = max(1, ceil_div(ceil_div(cols, s), unit)) * unit;
     p.splits = ceil_div(cols, p.chunk);
     return p;
@@ -1181,9 +1184,12 @@ PassPlan plan_codes(int rows, int K) {
     return p;
 }
 
-PassPlan plan_pass_t(int rows, int cols) {
+// Few column strips: many row chunks, of 32 rows and more with one tile of sketch columns, of 128 with more.  128 / 32, us
+// per call: l = 10 200^3 87.7 / 83.3, 1000^3 113.1 / 111.7, 2000^3 157.0 / 153.5; l = 24 512^3 130.4 / 136.8, 1537 x 1021 x
+// 2311 203.6 / 213.2.
+PassPlan plan_pass_t(int rows, int cols, int LP) {
     PassPlan p;
-    const int s = pick_splits(ceil_div(cols, 64), rows, 128, 512, MAX_SPLITS_T);     // few column strips: many row chunks
+    const int s = pick_splits(ceil_div(cols, 64), rows, LP == 16 ? 32 : 128, 512, MAX_SPLITS_T);
     // (a multiple of the 128 rows a workgroup takes per step when there are enough rows)
     const int unit = rows >= 512 * s ? 128 : 32;
     p.chunk = max(1, ceil_div(ceil_div(rows, s), unit)) * unit;
