@@ -879,6 +879,12 @@ int lrqmm_residual_matmul(int M, int N, int K, int bits, int terms, int round_mo
         LRQ_TRY(launch_pad_copy(nullptr, M, 0, 1, w.amaxA, static_cast<hipStream_t>(stream)));
         LRQ_TRY(launch_pad_copy(nullptr, N, 0, 1, w.amaxB, static_cast<hipStream_t>(stream)));
     }
+    if (terms >= 3 && int8_terms_usable(M, N, K)) {
+        const int8_t *const Acodes[2] = {w.Aq, w.RAq}, *const Bcodes[2] = {w.BqT, w.RBqT};
+        const float *const amA[2] = {w.amaxA, w.amaxRA}, *const amB[2] = {w.amaxB, w.amaxRB};
+        return launch_int8_terms(M, N, K, Acodes, amA, Bcodes, amB, terms, make_quant_params(bits, round_mode).qmaxf,
+                                 GemmOut{D, ldd, alpha, beta}, static_cast<hipStream_t>(stream));
+    }
     // one integer GEMM per term of Eq. (gemm_r_split), each dequantized with the scales of its two
     // operands and accumulated into D through the GEMM's own alpha/beta update
     auto term = [&](const int8_t* Lq, const float* amaxL, const int8_t* RqT, const float* amaxR, float b) {

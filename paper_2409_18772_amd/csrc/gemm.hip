@@ -570,6 +570,180 @@ __global__ __launch_bounds__(512, 1) void int8_gemm256_kernel(int M, int N, int 
     }
 }
 
+// Complete residual compensation (Eq. (gemm_r_split)): the sum of three or four integer products, each with step vectors of
+// its own, in one launch: the K tiles of all products form one sequence (loads run two tiles ahead across the boundaries),
+// and where a product ends its sums are dequantized and added to a float32 total in registers, in the order and with the
+// roundings of one launch per product that reads and writes D.  Waves of 64 x 64 (64 registers of sums and 64 of totals) in a
+// WM x 2 grid: 256 x 128 tiles with eight waves, one workgroup per CU, or 128 x 128 with four, two per CU; otherwise the
+// staging of the 256 x 256 kernel above.  In the loop it runs at that kernel's rate (2.0 POP/s at 4096^3, bound by the matrix
+// cores' sustained rate, LDS traffic and one barrier per K tile in turn); the read-modify-writes of D, step vectors, starts
+// and ends of a launch per product fall away.  Calls with four products, one launch per product / this: 4096^3 int8 540 / 376
+// us, 5000^3 1142 / 896, 3072^3 414 / 234, 2000^3 216 / 99, 2000 x 2000 x 500 142 / 48, 300^3 68 / 40.
+#define TTN 128
+struct TermArgs {
+    const int8_t *A[2], *B[2];              // codes of the operands and of their residuals (B transposed)
+    const float *amaxA[2], *amaxB[2];       // their group maxima
+};
+template <int WM, bool FULL>
+__global__ __launch_bounds__(128 * WM, WM == 4 ? 1 : 2) void int8_terms_kernel(int M, int N, int K, TermArgs t, int terms, float qmaxf, GemmOut out,
+                                                            int tiles_n, int ntiles) {
+    constexpr int TTM = 64 * WM, THREADS = 128 * WM, ROWS = THREADS / BCHUNKS, LB = TTN / ROWS;     // (TTM / ROWS == 4)
+    __shared__ __align__(16) int8_t As[2][TTM * BSTRIDE];
+    __shared__ __align__(16) int8_t Bs[2][TTN * BSTRIDE];
+    __shared__ __align__(16) float sAs[2][TTM], sBs[2][TTN];
+    const int nk = (K + BBK - 1) / BBK, total = nk * terms;
+    const int tile = xcd_tile(blockIdx.x, tiles_n, ntiles);
+    const int m0 = (tile / tiles_n) * TTM, n0 = (tile % tiles_n) * TTN;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int wm = wave >> 1, wn = wave & 1;
+    const int l32 = lane & 31, lh = lane >> 5;
+    {
+        float l;
+        const int ra = tid % TTM, rb = tid % TTN;
+        make_scales(t.amaxA[tid / TTM][min(m0 + ra, M - 1)], qmaxf, l, sAs[tid / TTM][ra]);
+        if (tid < 2 * TTN) make_scales(t.amaxB[tid / TTN][min(n0 + rb, N - 1)], qmaxf, l, sBs[tid / TTN][rb]);
+    }
+    v16i acc[2][2];
+    v16f f[2][2];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) { acc[a][b][v] = 0; f[a][b][v] = 0.f; }
+    const int srow0 = tid / BCHUNKS, skc = (tid % BCHUNKS) * 16;
+    // offset of a staged row in any code matrix of the operand (rows past the end re-read the last one, never stored)
+    size_t ra[FULL ? 1 : 4], rb[FULL ? 1 : LB];
+    if constexpr (FULL) {
+        ra[0] = (size_t)(m0 + srow0) * K + skc;
+        rb[0] = (size_t)(n0 + srow0) * K + skc;
+    } else {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) ra[u] = (size_t)min(m0 + srow0 + ROWS * u, M - 1) * K;
+#pragma unroll
+        for (int u = 0; u < LB; ++u) rb[u] = (size_t)min(n0 + srow0 + ROWS * u, N - 1) * K;
+    }
+    auto ld = [&](const int8_t* base, const size_t* row, int u, int k0) -> uint4 {
+        if constexpr (FULL) return *reinterpret_cast<const uint4*>(base + (size_t)(ROWS * u) * K + k0 + row[0]);
+        else return load16b<true>(base + row[u], K, k0 + skc);
+    };
+    int lt = 0, lk = 0, st = 0;             // product and column of the next tile to load; column of the next tile to store
+    auto next_load = [&] {                  // (past the end: the last tile again, never used)
+        if (lk + BBK < K) lk += BBK;
+        else if (lt + 1 < terms) { ++lt; lk = 0; }
+    };
+#define LRQ_DECL(S) uint4 S##a0, S##a1, S##a2, S##a3, S##b0, S##b1, S##b2, S##b3
+#define LRQ_GLOAD(S)                                                                                     \
+    {                                                                                                    \
+        const int8_t *const pa = t.A[lt >> 1], *const pb = t.B[lt & 1];                                  \
+        S##a0 = ld(pa, ra, 0, lk); S##b0 = ld(pb, rb, 0, lk); S##a1 = ld(pa, ra, 1, lk);                 \
+        S##b1 = ld(pb, rb, 1, lk); S##a2 = ld(pa, ra, 2, lk); S##a3 = ld(pa, ra, 3, lk);                 \
+        if (LB == 4) { S##b2 = ld(pb, rb, LB == 4 ? 2 : 0, lk); S##b3 = ld(pb, rb, LB == 4 ? 3 : 0, lk); } \
+        next_load();                                                                                     \
+    }
+#define LRQ_ST(BUF, U, V) *reinterpret_cast<uint4*>(&BUF[(srow0 + ROWS * U) * BSTRIDE + skc]) = V
+#define LRQ_SSTORE(S, buf)                                                                               \
+    {                                                                                                    \
+        if (!FULL && st + BBK > K) {                                                                     \
+            const int sh = max(0, st + skc - (K - 16));                                                  \
+            S##a0 = tail16(S##a0, sh); S##a1 = tail16(S##a1, sh); S##a2 = tail16(S##a2, sh);             \
+            S##a3 = tail16(S##a3, sh); S##b0 = tail16(S##b0, sh); S##b1 = tail16(S##b1, sh);             \
+            if (LB == 4) { S##b2 = tail16(S##b2, sh); S##b3 = tail16(S##b3, sh); }                       \
+        }                                                                                                \
+        LRQ_ST(As[buf], 0, S##a0); LRQ_ST(Bs[buf], 0, S##b0); LRQ_ST(As[buf], 1, S##a1);                 \
+        LRQ_ST(Bs[buf], 1, S##b1); LRQ_ST(As[buf], 2, S##a2); LRQ_ST(As[buf], 3, S##a3);                 \
+        if (LB == 4) { LRQ_ST(Bs[buf], 2, S##b2); LRQ_ST(Bs[buf], 3, S##b3); }                           \
+        st = st + BBK < K ? st + BBK : 0;                                                                \
+    }
+    auto compute = [&](int buf) {
+#pragma unroll
+        for (int kk = 0; kk < BBK / 32; ++kk) {
+            v4i af[2], bf[2];
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt)
+                af[mt] = *reinterpret_cast<const v4i*>(&As[buf][(wm * 64 + mt * 32 + l32) * BSTRIDE + kk * 32 + lh * 16]);
+#pragma unroll
+            for (int nt = 0; nt < 2; ++nt)
+                bf[nt] = *reinterpret_cast<const v4i*>(&Bs[buf][(wn * 64 + nt * 32 + l32) * BSTRIDE + kk * 32 + lh * 16]);
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+                for (int nt = 0; nt < 2; ++nt)
+                    acc[mt][nt] = __builtin_amdgcn_mfma_i32_32x32x32_i8(af[mt], bf[nt], acc[mt][nt], 0, 0, 0);
+        }
+    };
+    // D <- alpha * product + beta * D, the next products with beta = 1 and the total in D's place
+    auto add_product = [&](int term) {
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const float4 s4 = *reinterpret_cast<const float4*>(&sAs[term >> 1][wm * 64 + mt * 32 + 8 * g + 4 * lh]);
+                const float sa[4] = {s4.x, s4.y, s4.z, s4.w};
+#pragma unroll
+                for (int nt = 0; nt < 2; ++nt) {
+                    const float sb = sBs[term & 1][wn * 64 + nt * 32 + l32];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int v = 4 * g + e;
+                        f[mt][nt][v] = out.alpha * (((float)acc[mt][nt][v] * sa[e]) * sb) + f[mt][nt][v];
+                        acc[mt][nt][v] = 0;
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);      // (eight entries at a time: the steps of all would not fit in registers)
+            }
+    };
+    if (out.beta != 0.f) {
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+            for (int nt = 0; nt < 2; ++nt) {
+                const int col = n0 + wn * 64 + nt * 32 + l32;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int row = m0 + wm * 64 + mt * 32 + 8 * (v >> 2) + 4 * lh + (v & 3);
+                    if (row < M && col < N) f[mt][nt][v] = out.beta * out.C[(size_t)row * out.ldc + col];
+                }
+            }
+    }
+    LRQ_DECL(r0);
+    LRQ_DECL(r1);
+    LRQ_GLOAD(r0);
+    LRQ_GLOAD(r1);
+    LRQ_SSTORE(r0, 0);
+    __syncthreads();
+    int left = nk, term = 0;                // tiles left of the current product
+    // iteration i: the set that held tile i is free -> load tile i + 2; compute tile i; publish tile i + 1
+#define LRQ_TERM_STEP(J, SCUR, SNEXT)                                \
+    if (i0 + J < total) {                                            \
+        LRQ_GLOAD(SCUR);                                             \
+        compute(J);                                                  \
+        if (i0 + J + 1 < total) { LRQ_SSTORE(SNEXT, 1 - J); }        \
+        if (--left == 0) { add_product(term); ++term; left = nk; }   \
+        __syncthreads();                                             \
+    }
+    for (int i0 = 0; i0 < total; i0 += 2) {
+        LRQ_TERM_STEP(0, r0, r1)
+        LRQ_TERM_STEP(1, r1, r0)
+    }
+#undef LRQ_TERM_STEP
+#undef LRQ_DECL
+#undef LRQ_GLOAD
+#undef LRQ_ST
+#undef LRQ_SSTORE
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt) {
+            const int col = n0 + wn * 64 + nt * 32 + l32;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int row = m0 + wm * 64 + mt * 32 + 8 * (v >> 2) + 4 * lh + (v & 3);
+                if (row < M && col < N) out.C[(size_t)row * out.ldc + col] = f[mt][nt][v];
+            }
+        }
+}
+
 // The epilogue of the GEMM as a kernel of its own, for the schedule in which the integer
 // product runs early (next to the small kernels of the factorizations) and leaves its raw
 // int32 sums in C's memory: C <- float(Cint) sA_i sB_j + Lp . Rp^T in place, with the same
@@ -1215,6 +1389,33 @@ int launch_rank_update(int M, int N, float* C, const float* sA, const float* sB,
     else
         hipLaunchKernelGGL(rank_update_kernel, dim3(ceil_div(M, 128) * tiles_n), dim3(256), 0, st, M, N, C, sA, sB, Lp,
                            Rp, R2P, tiles_n, alpha);
+    LRQ_CHECK_LAUNCH();
+    return LRQMM_OK;
+}
+
+// Few tiles with a long reduction stay with one launch per product and its smaller tiles: 256 x 256 x 6000 160 us against 188
+// (4 tiles); 256 x 4096 x 4096 170 against 157 (64 tiles).
+bool int8_terms_usable(int M, int N, int K) {
+    return K >= 16 && (K <= 2048 || (long long)ceil_div(M, 128) * ceil_div(N, TTN) >= 32);
+}
+
+int launch_int8_terms(int M, int N, int K, const int8_t* const A[2], const float* const amaxA[2], const int8_t* const B[2],
+                      const float* const amaxB[2], int terms, float qmaxf, GemmOut out, hipStream_t st) {
+    if (!int8_terms_usable(M, N, K)) return LRQMM_ERR_UNSUPPORTED;
+    TermArgs t = {{A[0], A[1]}, {B[0], B[1]}, {amaxA[0], amaxA[1]}, {amaxB[0], amaxB[1]}};
+    const int tiles_n = ceil_div(N, TTN);
+    // 256-row tiles where they fill their last round to 3/4, 256 / 128 rows, us: 2000^3 (0.50) 113 / 99, 2560^3 (0.78) 132 / 142,
+    // 3072^3 (0.56) 256 / 234, 3500^3 (0.77) 349 / 381, 4096^3 (1) 377 / 401, 5000^3 (0.78) 895 / 903
+    const long long tall_tiles = (long long)ceil_div(M, 256) * tiles_n;
+    const bool tall = 4 * tall_tiles >= 3 * GEMM_MIN_TILES * ((tall_tiles + GEMM_MIN_TILES - 1) / GEMM_MIN_TILES);
+    const int ttm = tall ? 256 : 128, ntiles = ceil_div(M, ttm) * tiles_n;
+    const bool full = aligned16(A[0]) && aligned16(A[1]) && aligned16(B[0]) && aligned16(B[1]) && M % ttm == 0 && N % TTN == 0 && K % BBK == 0;
+#define LRQ_TERMS(WM, FULL)                                                                                                  \
+    hipLaunchKernelGGL((int8_terms_kernel<WM, FULL>), dim3(ntiles), dim3(128 * WM), 0, st, M, N, K, t, terms, qmaxf, out, tiles_n, \
+                       ntiles)
+    if (tall) { if (full) LRQ_TERMS(4, true); else LRQ_TERMS(4, false); }
+    else      { if (full) LRQ_TERMS(2, true); else LRQ_TERMS(2, false); }
+#undef LRQ_TERMS
     LRQ_CHECK_LAUNCH();
     return LRQMM_OK;
 }

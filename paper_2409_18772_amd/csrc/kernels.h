@@ -175,6 +175,11 @@ struct GemmOut {
 int launch_int8_gemm(int M, int N, int K, const int8_t* Aq, const int8_t* BqT, const float* sA,
                      const float* sB, const float* Lp, const float* Rp, int R2P, GemmOut C,
                      int32_t* Cint, hipStream_t st);
+// D <- alpha (A0 B0 + A0 B1 + A1 B0 [+ A1 B1]) + beta D, the products of the operands' codes (0) and of their residuals' (1),
+// each dequantized by the steps of its group maxima: terms = 3 or 4 products in one launch, where int8_terms_usable.
+bool int8_terms_usable(int M, int N, int K);
+int launch_int8_terms(int M, int N, int K, const int8_t* const A[2], const float* const amaxA[2], const int8_t* const B[2],
+                      const float* const amaxB[2], int terms, float qmaxf, GemmOut out, hipStream_t st);
 // The product with an empty reduction (K == 0): D <- alpha * 0 + beta * D (D not read when beta == 0) and,
 // when Cint is given, zeros in Cint.  Reads no operand.
 int launch_empty_product(int M, int N, GemmOut C, int32_t* Cint, hipStream_t st);

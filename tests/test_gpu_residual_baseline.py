@@ -118,3 +118,37 @@ def test_bad_terms_rejected():
     L.lrqmm_residual_matmul(A, A, D, 8, 4)
     torch.cuda.synchronize()
     assert torch.all(D == 0)
+
+
+# One launch for all products: both tile heights (256 rows in the second and the last four shapes), whole tiles, ragged ones, reductions that end
+# at, before and behind a 128-deep tile and at the shortest one it takes, outputs smaller than a tile; the two loop parities of
+# a product (odd and even tile counts).
+@pytest.mark.parametrize("M,N,K,pad,alpha,beta", [(3072, 3072, 256, 0, 1.0, 0.0), (4096, 4096, 384, 0, 0.75, 0.5),
+                                                  (33, 20, 17, 1, 1.0, 0.0), (130, 257, 640, 0, 0.5, 0.5), (256, 128, 128, 0, 1.0, 0.0),
+                                                  (2817, 2820, 143, 3, 1.5, -0.5), (2900, 2819, 16, 1, 1.0, 0.0),
+                                                  (2830, 2840, 129, 0, -1.0, 1.0), (2819, 2900, 513, 5, 1.0, 0.25)])
+@pytest.mark.parametrize("terms", [3, 4])
+def test_residual_products_in_one_launch(M, N, K, pad, alpha, beta, terms):
+    """The same operations in the same order as one call per product that updates D: the same values."""
+    import torch
+    import paper_2409_18772_amd as L
+    A, B = wl.random_matrix("normal", M, K, seed=21), wl.random_matrix("uniform01", K, N, seed=22)
+    D0 = to_dev(wl.random_matrix("normal", M, N, seed=23))
+    _, dA = window(A, pad)
+    _, dB = window(B, pad)
+    say("residual products", M, N, K, terms)
+
+    def dest():
+        big = torch.full((M, N + pad), SENTINEL, dtype=torch.float32, device="cuda")
+        big[:, :N] = D0
+        return big
+    got, want = dest(), dest()
+    L.lrqmm_residual_matmul(dA, dB, got[:, :N], 8, terms, alpha=alpha, beta=beta)
+    Aq, amA = L.lrqmm_quantize_ex(dA, L.AXIS_ROW, 8)
+    BqT, amB = L.lrqmm_quantize_ex(dB, L.AXIS_COL, 8)
+    RAq, amRA = L.lrqmm_quantize_residual(dA, amA, L.AXIS_ROW, 8)
+    RBqT, amRB = L.lrqmm_quantize_residual(dB, amB, L.AXIS_COL, 8)
+    products = [(Aq, amA, BqT, amB), (Aq, amA, RBqT, amRB), (RAq, amRA, BqT, amB), (RAq, amRA, RBqT, amRB)][:terms]
+    for i, p in enumerate(products):
+        L.lrqmm_gemm_ex(*p, 8, want[:, :N], alpha, beta if i == 0 else 1.0)
+    assert torch.equal(got, want)
