@@ -11,7 +11,7 @@
 // Main loop: up to 128x128 workgroup tile, 4 waves in 2x2, each wave up to 64x64 as 2x2
 // v_mfma_i32_32x32x32_i8 tiles; both operands are K-major (A codes M x K, B codes
 // stored transposed N x K), staged through double-buffered LDS with a padded row
-// stride (80 B) that makes the 16-byte operand reads bank-conflict free.
+// stride (144 B) that makes the 16-byte operand reads bank-conflict free.
 // 32x32 accumulator layout (lane l, register v): row 8*(v/4) + 4*(l/32) + v%4,
 // column l%32 -- identical for the i32 and f32 32x32 MFMAs, which lets the
 // epilogue continue on the same registers with v_mfma_f32_32x32x2_f32.
@@ -19,12 +19,12 @@
 
 static inline bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
-#define BK 64
+#ifndef BBK
+#define BBK 128                 // K depth of one staged tile
+#endif
+#define BSTRIDE (BBK + 16)      // padded LDS row stride, conflict-free 16-byte reads
 #define GEMM_MIN_TILES 256
 #define PANEL_LD 40         // row stride of a 32-column chunk of a bfloat16 panel plane (80 bytes: conflict-free 16-byte reads)
-#ifndef LDS_STRIDE
-#define LDS_STRIDE 80
-#endif
 
 // 16 code bytes of one operand row, k .. k+15, zeros past K.  WIDE (K >= 16): one 16-byte load at any byte
 // alignment (codes are packed rows of K bytes, so an odd K leaves none), branch free with a clamped address; the
@@ -94,23 +94,30 @@ __device__ __forceinline__ int xcd_tile(int id, int tiles_n, int ntiles) {
 }
 
 // MTW, NTW: 32 x 32 MFMA tiles per wave along M and N; the four waves form a 2 x 2 grid, so the workgroup tile is
-// 64 MTW x 64 NTW: 128 x 128; 128 x 64 for outputs of at most 64 columns, e.g. a convolution with 64 output channels
-// as a product -- on a 128-wide tile half the matrix-core work and half of B's LDS tile would be zeros; 64 x 128 and
-// 64 x 64 where the larger tiles are too few to fill the chip (see launch_int8_gemm).
+// 64 MTW x 64 NTW: 128 x 128; 64 x 64 for outputs of at most 64 columns, e.g. a convolution with 64 output channels as a
+// product -- on a 128-wide tile half the matrix-core work and half of B's LDS tile would be zeros; 64 x 128 and 64 x 64 where
+// the larger tiles are too few to fill the chip (see launch_int8_gemm).
+//
+// K tiles are 128 deep, global loads two of them ahead of the matrix cores in a ring of two sets of named registers (as arrays
+// they would go to scratch memory).  The epilogue stages the panel rows of the tile through the LDS that the operand tiles
+// have left, 64 columns at a time: as operands straight from global memory every eight columns of each 32 x 32 tile waited
+// for a load.  Measured, us per call, 64-deep tiles and unstaged panels / this: 2000^3 154.3 / 152.3,
+// 3072 x 1536 x 2048 (l = 40) 295 / 288, 2816^3 (l = 24) 197 / 189, 512 x 4096 x 4096 256 / 251, 1537 x 1021 x 2311 202.5 / 201.3,
+// 100352 x 64 x 576 211.4 / 208.8; a reduction of 64 is half a tile: 100352 x 64 x 64 122.4 / 123.5.
 template <bool WIDE, bool COMP, bool WCINT, int MTW, int NTW>
-__global__ __launch_bounds__(256) void int8_gemm_kernel(int M, int N, int K,
-                                                        const int8_t* __restrict__ Aq,
-                                                        const int8_t* __restrict__ BqT,
-                                                        const float* __restrict__ sA,
-                                                        const float* __restrict__ sB,
-                                                        const float* __restrict__ Lp,
-                                                        const float* __restrict__ Rp, int R2P,
-                                                        GemmOut out,
-                                                        int32_t* __restrict__ Cint, int tiles_n,
-                                                        int ntiles) {
+__global__ __launch_bounds__(256, 2) void int8_gemm_kernel(int M, int N, int K,
+                                                           const int8_t* __restrict__ Aq,
+                                                           const int8_t* __restrict__ BqT,
+                                                           const float* __restrict__ sA,
+                                                           const float* __restrict__ sB,
+                                                           const float* __restrict__ Lp,
+                                                           const float* __restrict__ Rp, int R2P,
+                                                           GemmOut out,
+                                                           int32_t* __restrict__ Cint, int tiles_n,
+                                                           int ntiles) {
     constexpr int TMW = 64 * MTW, TNW = 64 * NTW;       // tile height and width
-    __shared__ __align__(16) int8_t As[2][TMW * LDS_STRIDE];
-    __shared__ __align__(16) int8_t Bs[2][TNW * LDS_STRIDE];
+    __shared__ __align__(16) int8_t As[2][TMW * BSTRIDE];
+    __shared__ __align__(16) int8_t Bs[2][TNW * BSTRIDE];
     const int tile = xcd_tile(blockIdx.x, tiles_n, ntiles);
     const int m0 = (tile / tiles_n) * TMW, n0 = (tile % tiles_n) * TNW;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -125,46 +132,46 @@ __global__ __launch_bounds__(256) void int8_gemm_kernel(int M, int N, int K,
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[a][b][v] = 0;
 
-    // staging: one or two 16-byte chunks per operand tile and thread.  Global loads run three K-tiles ahead of the
-    // matrix cores in a ring of three sets of named registers (as arrays they would go to scratch memory): with
-    // one tile of lookahead every iteration waited for a global load, which short reductions (K = 576 for the
-    // conv-shaped workload: nine tiles) never amortize.  Tiles past the end load zeros and are never stored.
-    const int srow0 = tid >> 2, skc = (tid & 3) * 16;
-#define LRQ_DECL(S) uint4 S##a0, S##a1, S##b0, S##b1
-    const int8_t *const pa0 = code_row(Aq, m0 + srow0, M, K), *const pa1 = code_row(Aq, m0 + srow0 + 64, M, K);
-    const int8_t *const pb0 = code_row(BqT, n0 + srow0, N, K), *const pb1 = code_row(BqT, n0 + srow0 + 64, N, K);
-#define LRQ_GLOAD(S, k0)                                                   \
-    S##a0 = load16b<WIDE>(pa0, K, (k0) + skc);                             \
-    S##b0 = load16b<WIDE>(pb0, K, (k0) + skc);                             \
-    if (MTW == 2) S##a1 = load16b<WIDE>(pa1, K, (k0) + skc);               \
-    if (NTW == 2) S##b1 = load16b<WIDE>(pb1, K, (k0) + skc);
+    // staging: two 16-byte chunks per 64 rows of an operand tile and thread; tiles past the end load zeros or the row's last
+    // codes and are never stored
+    const int srow0 = tid >> 3, skc = (tid & 7) * 16;
+#define LRQ_DECL(S) uint4 S##a0, S##a1, S##a2, S##a3, S##b0, S##b1, S##b2, S##b3
+    const int8_t *pa[2 * MTW], *pb[2 * NTW];
+#pragma unroll
+    for (int u = 0; u < 2 * MTW; ++u) pa[u] = code_row(Aq, m0 + srow0 + 32 * u, M, K);
+#pragma unroll
+    for (int u = 0; u < 2 * NTW; ++u) pb[u] = code_row(BqT, n0 + srow0 + 32 * u, N, K);
+#define LRQ_LD(P, k0) load16b<WIDE>(P, K, (k0) + skc)
+#define LRQ_GLOAD(S, k0)                                                                               \
+    S##a0 = LRQ_LD(pa[0], k0); S##b0 = LRQ_LD(pb[0], k0); S##a1 = LRQ_LD(pa[1], k0); S##b1 = LRQ_LD(pb[1], k0); \
+    if constexpr (MTW == 2) { S##a2 = LRQ_LD(pa[2], k0); S##a3 = LRQ_LD(pa[3], k0); }                   \
+    if constexpr (NTW == 2) { S##b2 = LRQ_LD(pb[2], k0); S##b3 = LRQ_LD(pb[3], k0); }
     // (k0: first column of the set's tile; the branch is the same for the whole workgroup)
-#define LRQ_SSTORE(S, buf, k0)                                                              \
-    if (WIDE && (k0) + BK > K) {                                                            \
-        const int sh = max(0, (k0) + skc - (K - 16));                                       \
-        S##a0 = tail16(S##a0, sh); S##b0 = tail16(S##b0, sh);                               \
-        if (MTW == 2) S##a1 = tail16(S##a1, sh);                                            \
-        if (NTW == 2) S##b1 = tail16(S##b1, sh);                                            \
-    }                                                                                       \
-    *reinterpret_cast<uint4*>(&As[buf][srow0 * LDS_STRIDE + skc]) = S##a0;                  \
-    *reinterpret_cast<uint4*>(&Bs[buf][srow0 * LDS_STRIDE + skc]) = S##b0;                  \
-    if (MTW == 2) *reinterpret_cast<uint4*>(&As[buf][(srow0 + 64) * LDS_STRIDE + skc]) = S##a1; \
-    if (NTW == 2) *reinterpret_cast<uint4*>(&Bs[buf][(srow0 + 64) * LDS_STRIDE + skc]) = S##b1;
+#define LRQ_ST(BUF, U, V) *reinterpret_cast<uint4*>(&BUF[(srow0 + 32 * U) * BSTRIDE + skc]) = V
+#define LRQ_SSTORE(S, buf, k0)                                                                         \
+    if (WIDE && (k0) + BBK > K) {                                                                      \
+        const int sh = max(0, (k0) + skc - (K - 16));                                                  \
+        S##a0 = tail16(S##a0, sh); S##a1 = tail16(S##a1, sh); S##b0 = tail16(S##b0, sh); S##b1 = tail16(S##b1, sh); \
+        if constexpr (MTW == 2) { S##a2 = tail16(S##a2, sh); S##a3 = tail16(S##a3, sh); }               \
+        if constexpr (NTW == 2) { S##b2 = tail16(S##b2, sh); S##b3 = tail16(S##b3, sh); }               \
+    }                                                                                                  \
+    LRQ_ST(As[buf], 0, S##a0); LRQ_ST(Bs[buf], 0, S##b0); LRQ_ST(As[buf], 1, S##a1); LRQ_ST(Bs[buf], 1, S##b1); \
+    if constexpr (MTW == 2) { LRQ_ST(As[buf], 2, S##a2); LRQ_ST(As[buf], 3, S##a3); }                   \
+    if constexpr (NTW == 2) { LRQ_ST(Bs[buf], 2, S##b2); LRQ_ST(Bs[buf], 3, S##b3); }
     LRQ_DECL(r0);
     LRQ_DECL(r1);
-    LRQ_DECL(r2);
     auto compute = [&](int buf) {
 #pragma unroll
-        for (int kk = 0; kk < BK / 32; ++kk) {
+        for (int kk = 0; kk < BBK / 32; ++kk) {
             v4i af[MTW], bf[NTW];
 #pragma unroll
             for (int mt = 0; mt < MTW; ++mt)
                 af[mt] = *reinterpret_cast<const v4i*>(
-                    &As[buf][(wm * 32 * MTW + mt * 32 + l32) * LDS_STRIDE + kk * 32 + lh * 16]);
+                    &As[buf][(wm * 32 * MTW + mt * 32 + l32) * BSTRIDE + kk * 32 + lh * 16]);
 #pragma unroll
             for (int nt = 0; nt < NTW; ++nt)
                 bf[nt] = *reinterpret_cast<const v4i*>(
-                    &Bs[buf][(wn * 32 * NTW + nt * 32 + l32) * LDS_STRIDE + kk * 32 + lh * 16]);
+                    &Bs[buf][(wn * 32 * NTW + nt * 32 + l32) * BSTRIDE + kk * 32 + lh * 16]);
 #pragma unroll
             for (int mt = 0; mt < MTW; ++mt)
 #pragma unroll
@@ -172,69 +179,102 @@ __global__ __launch_bounds__(256) void int8_gemm_kernel(int M, int N, int K,
                     acc[mt][nt] = __builtin_amdgcn_mfma_i32_32x32x32_i8(af[mt], bf[nt], acc[mt][nt], 0, 0, 0);
         }
     };
-    const int nk = (K + BK - 1) / BK;
+    const int nk = (K + BBK - 1) / BBK;
     LRQ_GLOAD(r0, 0);
-    LRQ_GLOAD(r1, BK);
-    LRQ_GLOAD(r2, 2 * BK);
+    LRQ_GLOAD(r1, BBK);
     LRQ_SSTORE(r0, 0, 0);
     __syncthreads();
-    // iteration i: the set that held tile i is free -> load tile i + 3; compute tile i; publish tile i + 1
-#define LRQ_GEMM_STEP(J, SCUR, SNEXT)                       \
-    if (kt + J < nk) {                                      \
-        const int i = kt + J;                               \
-        LRQ_GLOAD(SCUR, (i + 3) * BK);                      \
-        compute(i & 1);                                     \
-        if (i + 1 < nk) { LRQ_SSTORE(SNEXT, (i + 1) & 1, (i + 1) * BK); } \
-        __syncthreads();                                    \
+    // iteration i: the set that held tile i is free -> load tile i + 2; compute tile i; publish tile i + 1
+#define LRQ_GEMM_STEP(J, SCUR, SNEXT)                                  \
+    if (kt + J < nk) {                                                 \
+        const int i = kt + J;                                          \
+        LRQ_GLOAD(SCUR, (i + 2) * BBK);                                \
+        compute(J);                                                    \
+        if (i + 1 < nk) { LRQ_SSTORE(SNEXT, 1 - J, (i + 1) * BBK); }   \
+        __syncthreads();                                               \
     }
-    for (int kt = 0; kt < nk; kt += 3) {
+    for (int kt = 0; kt < nk; kt += 2) {
         LRQ_GEMM_STEP(0, r0, r1)
-        LRQ_GEMM_STEP(1, r1, r2)
-        LRQ_GEMM_STEP(2, r2, r0)
+        LRQ_GEMM_STEP(1, r1, r0)
     }
 #undef LRQ_GEMM_STEP
 #undef LRQ_DECL
 #undef LRQ_GLOAD
+#undef LRQ_LD
+#undef LRQ_ST
 #undef LRQ_SSTORE
 
     // ---- epilogue: dequantize, rank-2r update, store ----
+    v16f f[MTW][NTW];
 #pragma unroll
     for (int mt = 0; mt < MTW; ++mt) {
         const int rbase = m0 + wm * 32 * MTW + mt * 32;
+        float sa[16];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int row = rbase + 8 * (v >> 2) + 4 * lh + (v & 3);
+            sa[v] = sA[min(row, M - 1)];
+        }
 #pragma unroll
         for (int nt = 0; nt < NTW; ++nt) {
             const int col = n0 + wn * 32 * NTW + nt * 32 + l32;
-            const bool col_ok = col < N;
-            const float sb = col_ok ? sB[col] : 0.f;
-            v16f f;
+            const float sb = sB[min(col, N - 1)];
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int row = rbase + 8 * (v >> 2) + 4 * lh + (v & 3);
-                const float sa = (row < M) ? sA[row] : 0.f;
-                if (WCINT && row < M && col_ok) Cint[(size_t)row * N + col] = acc[mt][nt][v];
-                f[v] = ((float)acc[mt][nt][v] * sa) * sb;
-            }
-            if (COMP) {
-                const int lrow = rbase + l32;
-                const float* lp = Lp + (size_t)(lrow < M ? lrow : 0) * R2P + 4 * lh;
-                const float* rp = Rp + (size_t)(col_ok ? col : 0) * R2P + 4 * lh;
-                const bool lok = lrow < M;
-                for (int t0 = 0; t0 < R2P; t0 += 8) {
-                    float4 a4 = lok ? *reinterpret_cast<const float4*>(lp + t0) : make_float4(0.f, 0.f, 0.f, 0.f);
-                    float4 b4 = col_ok ? *reinterpret_cast<const float4*>(rp + t0) : make_float4(0.f, 0.f, 0.f, 0.f);
-                    f = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.x, b4.x, f, 0, 0, 0);
-                    f = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.y, b4.y, f, 0, 0, 0);
-                    f = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.z, b4.z, f, 0, 0, 0);
-                    f = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.w, b4.w, f, 0, 0, 0);
-                }
-            }
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int row = rbase + 8 * (v >> 2) + 4 * lh + (v & 3);
-                if (row < M && col_ok) store_out(out, row, col, f[v]);
+                if (WCINT && row < M && col < N) Cint[(size_t)row * N + col] = acc[mt][nt][v];
+                f[mt][nt][v] = ((float)acc[mt][nt][v] * sa[v]) * sb;
             }
         }
     }
+    if constexpr (COMP) {
+        constexpr int LDP = 68;         // 64 columns, padded: conflict-free 16-byte reads
+        static_assert(2 * BSTRIDE >= LDP * 4, "64 panel columns of a tile fit the operand's LDS");
+        float* const Ls = reinterpret_cast<float*>(&As[0][0]);
+        float* const Rs = reinterpret_cast<float*>(&Bs[0][0]);
+        for (int t0 = 0; t0 < R2P; t0 += 64) {      // (the loop's last barrier, or the one below, has released the LDS)
+            if (t0 > 0) __syncthreads();
+            const int q4 = min(R2P - t0, 64) / 4;
+            for (int idx = tid; idx < (TMW + TNW) * q4; idx += 256) {       // rows past the end re-read the last one (never stored)
+                const int rr = idx / q4, c4 = 4 * (idx - rr * q4);
+                if (rr < TMW)
+                    *reinterpret_cast<float4*>(Ls + rr * LDP + c4) =
+                        *reinterpret_cast<const float4*>(Lp + (size_t)min(m0 + rr, M - 1) * R2P + t0 + c4);
+                else
+                    *reinterpret_cast<float4*>(Rs + (rr - TMW) * LDP + c4) =
+                        *reinterpret_cast<const float4*>(Rp + (size_t)min(n0 + rr - TMW, N - 1) * R2P + t0 + c4);
+            }
+            __syncthreads();
+            const float* const lp = Ls + (wm * 32 * MTW + l32) * LDP + 4 * lh;
+            const float* const rp = Rs + (wn * 32 * NTW + l32) * LDP + 4 * lh;
+            for (int t = 0; t < 4 * q4; t += 8) {       // (R2P % 8 == 0)
+                float4 a4[MTW], b4[NTW];
+#pragma unroll
+                for (int mt = 0; mt < MTW; ++mt) a4[mt] = *reinterpret_cast<const float4*>(lp + 32 * mt * LDP + t);
+#pragma unroll
+                for (int nt = 0; nt < NTW; ++nt) b4[nt] = *reinterpret_cast<const float4*>(rp + 32 * nt * LDP + t);
+#define LRQ_FM(E)                                                                                       \
+    _Pragma("unroll") for (int mt = 0; mt < MTW; ++mt) _Pragma("unroll") for (int nt = 0; nt < NTW; ++nt) \
+        f[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x2f32(a4[mt].E, b4[nt].E, f[mt][nt], 0, 0, 0);
+                LRQ_FM(x)
+                LRQ_FM(y)
+                LRQ_FM(z)
+                LRQ_FM(w)
+#undef LRQ_FM
+            }
+        }
+    }
+#pragma unroll
+    for (int mt = 0; mt < MTW; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NTW; ++nt) {
+            const int col = n0 + wn * 32 * NTW + nt * 32 + l32;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int row = m0 + wm * 32 * MTW + mt * 32 + 8 * (v >> 2) + 4 * lh + (v & 3);
+                if (row < M && col < N) store_out(out, row, col, f[mt][nt][v]);
+            }
+        }
 }
 
 // Large-tile variant for big problems: 256x256 workgroup tile, one workgroup of 8 waves per
@@ -244,13 +284,9 @@ __global__ __launch_bounds__(256) void int8_gemm_kernel(int M, int N, int K,
 // tile is 128 deep: 144 KB of LDS for the two buffers of both operands.
 #define BTM 256
 #define BTN 256
-#ifndef BBK
-#define BBK 128                 // K depth of one staged tile of the large-tile kernel
-#endif
 #ifndef LRQ_GRING
 #define LRQ_GRING 2             // register sets of global loads in flight (tiles ahead of the matrix cores)
 #endif
-#define BSTRIDE (BBK + 16)      // padded LDS row stride, conflict-free 16-byte reads
 #define BCHUNKS (BBK / 16)      // 16-byte chunks per staged row
 #define BROWS (512 / BCHUNKS)   // rows covered by one pass of the 512 threads
 #define BLOADS (256 / BROWS)    // staged 16-byte chunks per thread and operand
@@ -1447,7 +1483,9 @@ int launch_int8_gemm(int M, int N, int K, const int8_t* Aq, const int8_t* BqT, c
     const bool comp = Lp != nullptr;
     // big problems: 256x256 tiles, one workgroup per CU
     const int btiles = ceil_div(M, BTM) * ceil_div(N, BTN);
-    if (int8_gemm_large_tiles(M, N) && wide) {
+    // (in one launch; raw sums always.  Large / small tiles, us per call: 128 tiles of 256 x 256, 4096 x 2048 x 4096, l = 24 306 /
+    // 291, rank 0 102 / 83; 144, 3072^3, 284 / 289, 87 / 85; 169, 3328^3, 297 / 305, 93 / 93; 196, 3584^3, 300 / 317, 101 / 109)
+    if (int8_gemm_large_tiles(M, N) && wide && (!C.C || btiles >= 136)) {
         const int btn = ceil_div(N, BTN);
         dim3 bgrid(btiles);
         dispatch_gemm256(comp, Cint != nullptr, bgrid, st, M, N, K, Aq, BqT, sA, sB, Lp, Rp, R2P, C, Cint, btn, btiles);
@@ -1458,7 +1496,8 @@ int launch_int8_gemm(int M, int N, int K, const int8_t* Aq, const int8_t* BqT, c
     // are at least 256, one per CU.  Calls with 128 x 128 tiles throughout / with this rule: 4 tiles of
     // 128 x 128 (256^3) 87 / 81 us, 104 (1537 x 1021 x 2311) 279 / 258, 128 (512 x 4096 x 4096 layer) 233 / 222;
     // 256 (2000^3) is the same path.
-    int mtw = 2, ntw = N <= 64 ? 1 : 2;
+    // At most 64 columns: 64 rows too, four workgroups per CU (128 x 64 / 64 x 64: 100352 x 64 x 576 213.5 / 208.8 us a call).
+    int mtw = N <= 64 ? 1 : 2, ntw = mtw;
     auto tiles = [&] { return (long long)ceil_div(M, 64 * mtw) * ceil_div(N, 64 * ntw); };
     if (tiles() < GEMM_MIN_TILES) mtw = 1;
     if (tiles() < GEMM_MIN_TILES) ntw = 1;
@@ -1468,7 +1507,6 @@ int launch_int8_gemm(int M, int N, int K, const int8_t* Aq, const int8_t* BqT, c
 #define LRQ_DG(W, MT, NT) dispatch_gemm<W, MT, NT>(comp, Cint != nullptr, grid, st, M, N, K, Aq, BqT, sA, sB, Lp, Rp, R2P, C, Cint, tiles_n, ntiles)
     if (!wide)                     LRQ_DG(false, 2, 2);
     else if (mtw == 2 && ntw == 2) LRQ_DG(true, 2, 2);
-    else if (mtw == 2)             LRQ_DG(true, 2, 1);
     else if (ntw == 2)             LRQ_DG(true, 1, 2);
     else                           LRQ_DG(true, 1, 1);
 #undef LRQ_DG
