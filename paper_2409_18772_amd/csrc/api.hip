@@ -564,9 +564,9 @@ static int gemm_impl(int M, int N, int K, int bits, int rank, const int8_t* Aq, 
     int rc;
     int R2P = 0;
     const int RP = pad_to(rank, 16);
-    LRQ_TRY(launch_panel_prep(M, N, K, rank, RP, q.qmaxf, amaxA, amaxB, W, Vt, w.lamA, w.sA, w.lamB, w.sB,
-                              w.Wp3, w.Vp3, w.X, st));
     if (rank > 0) {
+        LRQ_TRY(launch_panel_prep(M, N, K, rank, RP, q.qmaxf, amaxA, amaxB, W, Vt, w.lamA, w.sA, w.lamB, w.sB,
+                                  w.Wp3, w.Vp3, w.X, st));
         R2P = pad_to(2 * rank, 8);
         // A~ W and (V^T B~)^T without their step vectors, split along K; one launch for both
         const PassPlan pa = plan_codes(M, K), pb = plan_codes(N, K);
@@ -584,8 +584,8 @@ static int gemm_impl(int M, int N, int K, int bits, int rank, const int8_t* Aq, 
         return rc;
     }
     prof_mark(prof_slot, 7, st);
-    rc = launch_int8_gemm(M, N, K, Aq, BqT, w.sA, w.sB, rank > 0 ? w.Lp : nullptr, rank > 0 ? w.Rp : nullptr,
-                          R2P, out, Cint_or_null, st);
+    rc = launch_int8_gemm(M, N, K, Aq, BqT, rank > 0 ? w.sA : amaxA, rank > 0 ? w.sB : amaxB, rank > 0 ? w.Lp : nullptr,
+                          rank > 0 ? w.Rp : nullptr, R2P, out, Cint_or_null, q.qmaxf, st);
     prof_mark(prof_slot, 8, st);
     prof_mark(prof_slot, 9, st);
     prof_mark(prof_slot, 10, st);
@@ -709,7 +709,11 @@ int lrqmm_matmul_ex(int M, int N, int K, int bits, int rank, int oversample, int
     mark(opsA, 0, pst);
     mark(overlap ? opsB : opsA, 3, bst);
     if (!factored) {
-        if (K > 0) {
+        if (!per_tensor && quantize_pair_usable(M, N, K)) {
+            opsA.push_back([=] {
+                return launch_quantize_pair(A, lda, B, ldb, M, N, K, qp, QuantPair{w.Aq, w.BqT, w.amaxA, w.amaxB}, pst);
+            });
+        } else if (K > 0) {
             opsA.push_back([=] { return lrqmm_quantize_ex(A, lda, M, K, LRQMM_AXIS_ROW, bits, round_mode, scale_mode, w.Aq, w.amaxA, pst); });
             opsA.push_back([=] { return lrqmm_quantize_ex(B, ldb, K, N, LRQMM_AXIS_COL, bits, round_mode, scale_mode, w.BqT, w.amaxB, pst); });
         } else {
@@ -866,7 +870,12 @@ int lrqmm_residual_matmul(int M, int N, int K, int bits, int terms, int round_mo
     if (carve_residual(a, M, N, K, &w) > workspace_bytes) return LRQMM_ERR_WORKSPACE;
     if (K == 0) terms = 1;
     int rc;
-    if (K > 0) {
+    if (scale_mode == LRQMM_SCALE_VECTOR && quantize_pair_usable(M, N, K)) {
+        QuantPair o = {w.Aq, w.BqT, w.amaxA, w.amaxB};
+        if (terms >= 3) { o.codesRA = w.RAq; o.codesRB = w.RBqT; o.amaxRA = w.amaxRA; o.amaxRB = w.amaxRB; }
+        LRQ_TRY(launch_quantize_pair(A, lda, B, ldb, M, N, K, make_quant_params(bits, round_mode), o,
+                                     static_cast<hipStream_t>(stream)));
+    } else if (K > 0) {
         LRQ_TRY(lrqmm_quantize_ex(A, lda, M, K, LRQMM_AXIS_ROW, bits, round_mode, scale_mode, w.Aq, w.amaxA, stream));
         LRQ_TRY(lrqmm_quantize_ex(B, ldb, K, N, LRQMM_AXIS_COL, bits, round_mode, scale_mode, w.BqT, w.amaxB, stream));
         if (terms >= 3) {

@@ -49,6 +49,13 @@ __device__ __forceinline__ const int8_t* code_row(const int8_t* __restrict__ bas
     return base + (size_t)min(row, nrows - 1) * K;
 }
 
+// Step of a group from its maximum (the quantizer's).
+__device__ __forceinline__ float step_of(float amax, float qmaxf) {
+    float l, s;
+    make_scales(amax, qmaxf, l, s);
+    return s;
+}
+
 // Last step of Algorithm 2 on one element: D <- alpha * value + beta * D (D is not read when
 // beta == 0, so it may then hold anything).
 __device__ __forceinline__ void store_out(const GemmOut& out, int row, int col, float value) {
@@ -114,7 +121,7 @@ __global__ __launch_bounds__(256, 2) void int8_gemm_kernel(int M, int N, int K,
                                                            const float* __restrict__ Rp, int R2P,
                                                            GemmOut out,
                                                            int32_t* __restrict__ Cint, int tiles_n,
-                                                           int ntiles) {
+                                                           int ntiles, float qmaxf) {
     constexpr int TMW = 64 * MTW, TNW = 64 * NTW;       // tile height and width
     __shared__ __align__(16) int8_t As[2][TMW * BSTRIDE];
     __shared__ __align__(16) int8_t Bs[2][TNW * BSTRIDE];
@@ -205,6 +212,14 @@ __global__ __launch_bounds__(256, 2) void int8_gemm_kernel(int M, int N, int K,
 #undef LRQ_SSTORE
 
     // ---- epilogue: dequantize, rank-2r update, store ----
+    // Without panels sA, sB hold the group maxima, and the tile's steps are formed here, one per thread, in LDS.
+    float* const sAl = reinterpret_cast<float*>(&As[0][0]);
+    float* const sBl = reinterpret_cast<float*>(&Bs[0][0]);
+    if (!COMP) {
+        if (tid < TMW) sAl[tid] = step_of(sA[min(m0 + tid, M - 1)], qmaxf);
+        else if (tid - TMW < TNW) sBl[tid - TMW] = step_of(sB[min(n0 + tid - TMW, N - 1)], qmaxf);
+        __syncthreads();
+    }
     v16f f[MTW][NTW];
 #pragma unroll
     for (int mt = 0; mt < MTW; ++mt) {
@@ -213,12 +228,12 @@ __global__ __launch_bounds__(256, 2) void int8_gemm_kernel(int M, int N, int K,
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const int row = rbase + 8 * (v >> 2) + 4 * lh + (v & 3);
-            sa[v] = sA[min(row, M - 1)];
+            sa[v] = COMP ? sA[min(row, M - 1)] : sAl[row - m0];
         }
 #pragma unroll
         for (int nt = 0; nt < NTW; ++nt) {
             const int col = n0 + wn * 32 * NTW + nt * 32 + l32;
-            const float sb = sB[min(col, N - 1)];
+            const float sb = COMP ? sB[min(col, N - 1)] : sBl[col - n0];
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int row = rbase + 8 * (v >> 2) + 4 * lh + (v & 3);
@@ -307,7 +322,7 @@ __global__ __launch_bounds__(512, 1) void int8_gemm256_kernel(int M, int N, int 
                                                               GemmOut out,
                                                               int32_t* __restrict__ Cint, int tiles_n,
                                                               int ntiles, int full_tiles, int slices,
-                                                              int32_t* __restrict__ part) {
+                                                              int32_t* __restrict__ part, float qmaxf) {
     float* __restrict__ C = out.C;
     __shared__ __align__(16) int8_t As[2][BTM * BSTRIDE];
     __shared__ __align__(16) int8_t Bs[2][BTN * BSTRIDE];
@@ -442,6 +457,15 @@ __global__ __launch_bounds__(512, 1) void int8_gemm256_kernel(int M, int N, int 
     // C == nullptr: only the raw int32 sums are wanted (the dequantization and the update then
     // run later, in rank_update_kernel), and the step vectors are not read.
     const bool want_c = C != nullptr;
+    // Without panels sA, sB hold the group maxima, and the tile's steps are formed here, one per thread, in the LDS that the
+    // operand tiles have left: a launch that prepared them took 5 us of a call at 4096^3.
+    float* const sAl = reinterpret_cast<float*>(&As[0][0]);
+    float* const sBl = reinterpret_cast<float*>(&Bs[0][0]);
+    if (!COMP && want_c) {
+        if (tid < BTM) sAl[tid] = step_of(sA[min(m0 + tid, M - 1)], qmaxf);
+        else sBl[tid - BTM] = step_of(sB[min(n0 + tid - BTM, N - 1)], qmaxf);
+        __syncthreads();
+    }
     // Wider panels: the float32 matrix cores would take 4 R2P M N flops at 1/16 of the bfloat16 rate, so the tile's panel rows
     // are split into three bfloat16 planes while they are staged (32 columns at a time, in the LDS that the operand tiles have
     // left) and the six plane products of weight >= 2^-16 run on v_mfma_f32_32x32x16_bf16, as in rank_update_bf16_kernel.
@@ -545,7 +569,7 @@ __global__ __launch_bounds__(512, 1) void int8_gemm256_kernel(int M, int N, int 
     const int LDP = R2P + 4;
     float* const Ls = reinterpret_cast<float*>(&As[0][0]);
     float* const Rs = reinterpret_cast<float*>(&Bs[0][0]);
-    static_assert(2 * BTM * BSTRIDE >= 256 * 68 * 4, "a 64-column panel tile fits an operand's LDS");
+    static_assert(2 * BTM * BSTRIDE >= 256 * 68 * 4 && BTM + BTN == 512, "a 64-column panel tile fits an operand's LDS");
     if (COMP) {
         __syncthreads();        // every wave has read its last operand fragments
         const int q4 = R2P / 4;
@@ -567,13 +591,13 @@ __global__ __launch_bounds__(512, 1) void int8_gemm256_kernel(int M, int N, int 
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const int row = rbase + 8 * (v >> 2) + 4 * lh + (v & 3);
-            sa[v] = (want_c && row < M) ? sA[row] : 0.f;
+            sa[v] = !want_c ? 0.f : (COMP ? sA[min(row, M - 1)] : sAl[row - m0]);
         }
 #pragma unroll
         for (int nt = 0; nt < 4; ++nt) {
             const int col = n0 + wn * 128 + nt * 32 + l32;
             const bool col_ok = col < N;
-            const float sb = (want_c && col_ok) ? sB[col] : 0.f;
+            const float sb = !want_c ? 0.f : (COMP ? sB[min(col, N - 1)] : sBl[col - n0]);
             v16f f;
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
@@ -1306,16 +1330,16 @@ int launch_build_panels(int M, int N, int K, int r, int RP, int R2P, const float
 static void dispatch_gemm256(bool comp, bool wcint, dim3 grid, hipStream_t st, int M, int N, int K,
                              const int8_t* Aq, const int8_t* BqT, const float* sA, const float* sB,
                              const float* Lp, const float* Rp, int R2P, GemmOut C, int32_t* Cint, int tiles_n,
-                             int ntiles) {
+                             int ntiles, float qmaxf) {
     const bool full = aligned16(Aq) && aligned16(BqT) && (M % BTM == 0) && (N % BTN == 0) && (K % BBK == 0);
 #define LRQ_GEMM(COMP, WC)                                                                                   \
     do {                                                                                                     \
         if (full)                                                                                            \
             hipLaunchKernelGGL((int8_gemm256_kernel<COMP, WC, true>), grid, dim3(512), 0, st, M, N, K, Aq, \
-                               BqT, sA, sB, Lp, Rp, R2P, C, Cint, tiles_n, ntiles, ntiles, 1, nullptr);       \
+                               BqT, sA, sB, Lp, Rp, R2P, C, Cint, tiles_n, ntiles, ntiles, 1, nullptr, qmaxf); \
         else                                                                                                 \
             hipLaunchKernelGGL((int8_gemm256_kernel<COMP, WC, false>), grid, dim3(512), 0, st, M, N, K,  \
-                               Aq, BqT, sA, sB, Lp, Rp, R2P, C, Cint, tiles_n, ntiles, ntiles, 1, nullptr);   \
+                               Aq, BqT, sA, sB, Lp, Rp, R2P, C, Cint, tiles_n, ntiles, ntiles, 1, nullptr, qmaxf); \
     } while (0)
     if (comp) {
         if (wcint) LRQ_GEMM(true, true); else LRQ_GEMM(true, false);
@@ -1329,9 +1353,9 @@ template <bool WIDE, int MTW, int NTW>
 static void dispatch_gemm(bool comp, bool wcint, dim3 grid, hipStream_t st, int M, int N, int K,
                           const int8_t* Aq, const int8_t* BqT, const float* sA, const float* sB,
                           const float* Lp, const float* Rp, int R2P, GemmOut C, int32_t* Cint, int tiles_n,
-                          int ntiles) {
+                          int ntiles, float qmaxf) {
 #define LRQ_GEMM(COMP, WC) hipLaunchKernelGGL((int8_gemm_kernel<WIDE, COMP, WC, MTW, NTW>), grid, dim3(256), 0, st, M, N, K, \
-                                              Aq, BqT, sA, sB, Lp, Rp, R2P, C, Cint, tiles_n, ntiles)
+                                              Aq, BqT, sA, sB, Lp, Rp, R2P, C, Cint, tiles_n, ntiles, qmaxf)
     if (comp) {
         if (wcint) LRQ_GEMM(true, true); else LRQ_GEMM(true, false);
     } else {
@@ -1387,11 +1411,11 @@ int launch_int8_gemm_sums(int M, int N, int K, const int8_t* Aq, const int8_t* B
     const SumsPlan p = part ? plan_sums(M, N, K, Aq, BqT, resident) : SumsPlan{0, 0, 0, 1};
     if (p.left == 0)
         return launch_int8_gemm(M, N, K, Aq, BqT, nullptr, nullptr, nullptr, nullptr, 0, GemmOut{nullptr, N, 1.0f, 0.0f},
-                                Cint, st);
+                                Cint, 0.0f, st);
     const int full_tiles = p.ntiles - p.left;
     hipLaunchKernelGGL((int8_gemm256_kernel<false, true, true, true>), dim3(full_tiles + p.left * p.slices),
                        dim3(512), 0, st, M, N, K, Aq, BqT, nullptr, nullptr, nullptr, nullptr, 0,
-                       GemmOut{nullptr, N, 1.0f, 0.0f}, Cint, p.tiles_n, p.ntiles, full_tiles, p.slices, part);
+                       GemmOut{nullptr, N, 1.0f, 0.0f}, Cint, p.tiles_n, p.ntiles, full_tiles, p.slices, part, 0.0f);
     LRQ_CHECK_LAUNCH();
     return LRQMM_OK;
 }
@@ -1475,7 +1499,7 @@ int launch_empty_product(int M, int N, GemmOut C, int32_t* Cint, hipStream_t st)
 
 int launch_int8_gemm(int M, int N, int K, const int8_t* Aq, const int8_t* BqT, const float* sA,
                      const float* sB, const float* Lp, const float* Rp, int R2P, GemmOut C, int32_t* Cint,
-                     hipStream_t st) {
+                     float qmaxf, hipStream_t st) {
     // the GEMM kernels issue their first operand loads unconditionally: an empty reduction never reaches them
     if (K <= 0) return launch_empty_product(M, N, C, Cint, st);
     // (the 16-byte load path clamps its address to K - 16, so it needs at least one whole group)
@@ -1488,7 +1512,7 @@ int launch_int8_gemm(int M, int N, int K, const int8_t* Aq, const int8_t* BqT, c
     if (int8_gemm_large_tiles(M, N) && wide && (!C.C || btiles >= 136)) {
         const int btn = ceil_div(N, BTN);
         dim3 bgrid(btiles);
-        dispatch_gemm256(comp, Cint != nullptr, bgrid, st, M, N, K, Aq, BqT, sA, sB, Lp, Rp, R2P, C, Cint, btn, btiles);
+        dispatch_gemm256(comp, Cint != nullptr, bgrid, st, M, N, K, Aq, BqT, sA, sB, Lp, Rp, R2P, C, Cint, btn, btiles, qmaxf);
         LRQ_CHECK_LAUNCH();
         return LRQMM_OK;
     }
@@ -1504,7 +1528,7 @@ int launch_int8_gemm(int M, int N, int K, const int8_t* Aq, const int8_t* BqT, c
     if (!wide) mtw = ntw = 2;           // (K < 16: one staged tile)
     const int tiles_n = ceil_div(N, 64 * ntw), ntiles = (int)tiles();
     dim3 grid(ntiles);
-#define LRQ_DG(W, MT, NT) dispatch_gemm<W, MT, NT>(comp, Cint != nullptr, grid, st, M, N, K, Aq, BqT, sA, sB, Lp, Rp, R2P, C, Cint, tiles_n, ntiles)
+#define LRQ_DG(W, MT, NT) dispatch_gemm<W, MT, NT>(comp, Cint != nullptr, grid, st, M, N, K, Aq, BqT, sA, sB, Lp, Rp, R2P, C, Cint, tiles_n, ntiles, qmaxf)
     if (!wide)                     LRQ_DG(false, 2, 2);
     else if (mtw == 2 && ntw == 2) LRQ_DG(true, 2, 2);
     else if (ntw == 2)             LRQ_DG(true, 1, 2);

@@ -13,6 +13,17 @@ int launch_quantize_rows(const float* X, int ldx, int rows, int cols, QuantParam
                          const float* amax0, int8_t* codes, float* amax, hipStream_t st);
 int launch_quantize_cols(const float* X, int ldx, int rows, int cols, QuantParams q, bool per_tensor,
                          const float* amax0, int8_t* codesT, float* amax, hipStream_t st);
+// Both operands of a product, one scale per row of A and per column of B: the same codes and maxima in fewer launches and
+// reads than the two calls above (see quant_pair_kernel).  codesRA ... not null: their residuals too, quantized a second time.
+bool quantize_pair_usable(int M, int N, int K);
+struct QuantPair {
+    int8_t *codesA, *codesB;                // M x K; N x K (transposed)
+    float *amaxA, *amaxB;
+    int8_t *codesRA, *codesRB;
+    float *amaxRA, *amaxRB;
+};
+int launch_quantize_pair(const float* A, int lda, const float* B, int ldb, int M, int N, int K, QuantParams q, QuantPair o,
+                         hipStream_t st);
 // The group maxima alone: row maxima of A (M x K) and column maxima of B (K x N; amaxB cleared by the caller on this
 // stream) in one launch, and with per_tensor their maxima in a second.  M or N may be 0: the other operand alone.
 int launch_absmax_pair(const float* A, int lda, int M, int K, float* amaxA, const float* B, int ldb, int N,
@@ -171,10 +182,10 @@ struct GemmOut {
     float alpha, beta;
 };
 // result = diag(sA) (Aq . BqT^T) diag(sB) [+ Lp . Rp^T when Lp != null]; optional raw int32 output
-// (M x N, dense).
+// (M x N, dense).  Without panels (Lp == null) sA, sB are the group maxima, turned into steps with qmaxf.
 int launch_int8_gemm(int M, int N, int K, const int8_t* Aq, const int8_t* BqT, const float* sA,
                      const float* sB, const float* Lp, const float* Rp, int R2P, GemmOut C,
-                     int32_t* Cint, hipStream_t st);
+                     int32_t* Cint, float qmaxf, hipStream_t st);
 // D <- alpha (A0 B0 + A0 B1 + A1 B0 [+ A1 B1]) + beta D, the products of the operands' codes (0) and of their residuals' (1),
 // each dequantized by the steps of its group maxima: terms = 3 or 4 products in one launch, where int8_terms_usable.
 bool int8_terms_usable(int M, int N, int K);

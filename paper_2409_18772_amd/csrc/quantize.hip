@@ -118,9 +118,12 @@ __global__ __launch_bounds__(256) void quant_rows_cached_kernel(const float* __r
     }
 }
 
-__global__ void fill_u32_kernel(uint32_t* p, int n, uint32_t v) {
+__global__ void fill_u32_kernel(uint32_t* p, int n, uint32_t v, uint32_t* p2 = nullptr) {       // p2: a second array, or null
     int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
+    if (i < n) {
+        p[i] = v;
+        if (p2) p2[i] = v;
+    }
 }
 
 // Column absmax of a row-major matrix.  A workgroup takes 256 columns and a slab of rows: a wave reads 1 KB
@@ -216,16 +219,68 @@ __global__ __launch_bounds__(256) void absmax_pair_kernel(const float* __restric
     if (lane == 0) amaxA[row] = m;
 }
 
+// A's rows quantized from one read (as in quant_rows_cached_kernel) beside the column maxima of B (already cleared): workgroups
+// [0, nbA) take 256 / TPR rows of A each, the rest a 256-column slab of B, so that both operands stream at once.  RES: the
+// residual of A's rows is quantized a second time from the same registers, and B's residual maxima come with its codes.  Calls,
+// separate launches / this (and the steps formed in the product's epilogue): rank 0, 4096^3 int4 119 / 106 us, 2000^3 52 / 36.5,
+// 300^3 23.6 / 18.4; four residual products (one launch for the products), 4096^3 376 / 354.
+template <int TPR, int NV, bool RES>
+__global__ __launch_bounds__(256) void quant_pair_kernel(const float* __restrict__ A, int lda, int M, int K, QuantPair o, int nbA,
+                                                         const float* __restrict__ B, int ldb, int N, int rows_per_block,
+                                                         QuantParams q, int col_blocks) {
+    __shared__ float4 red[4][64];
+    __shared__ float wmax[2][4];
+    if ((int)blockIdx.x >= nbA) {
+        const int id = blockIdx.x - nbA;
+        absmax_cols_body<false>(B, ldb, K, N, rows_per_block, reinterpret_cast<uint32_t*>(o.amaxB), q, nullptr, id % col_blocks,
+                                id / col_blocks, red);
+        return;
+    }
+    const int t = threadIdx.x % TPR;
+    const int row = blockIdx.x * (256 / TPR) + threadIdx.x / TPR;
+    const bool row_ok = row < M;
+    const float* xp = A + (size_t)(row_ok ? row : 0) * lda;
+    float4 v[NV];
+#pragma unroll
+    for (int u = 0; u < NV; ++u) v[u] = load_quad<false>(xp, (t + TPR * u) * 4, K);
+#pragma unroll
+    for (int level = 0; level < (RES ? 2 : 1); ++level) {
+        float m = 0.0f;
+#pragma unroll
+        for (int u = 0; u < NV; ++u)
+            m = fmaxf(fmaxf(m, fabsf(v[u].x)), fmaxf(fabsf(v[u].y), fmaxf(fabsf(v[u].z), fabsf(v[u].w))));
+        m = wave_max(m);
+        if (TPR == 256) {
+            if ((threadIdx.x & 63) == 0) wmax[level][threadIdx.x >> 6] = m;
+            __syncthreads();
+            m = fmaxf(fmaxf(wmax[level][0], wmax[level][1]), fmaxf(wmax[level][2], wmax[level][3]));
+        }
+        if (row_ok && t == 0) (level == 0 ? o.amaxA : o.amaxRA)[row] = m;
+        float lam, s;
+        make_scales(m, q.qmaxf, lam, s);
+        int8_t* cp = (level == 0 ? o.codesA : o.codesRA) + (size_t)(row_ok ? row : 0) * K;
+#pragma unroll
+        for (int u = 0; u < NV; ++u) {
+            const int k = (t + TPR * u) * 4;
+            if (row_ok && k < K) store_quad<false>(cp, k, K, pack_codes(v[u], lam, q));
+            if (RES && level == 0) v[u] = first_level_residual(v[u], lam, s, q);
+        }
+    }
+}
+
 // Quantize a 64(k) x 64(n) tile with per-column scales and store it transposed
 // (codesT is cols x rows, contiguous along the original row index k).  Columns at the end as in the row kernels (what
 // then lies before the tile belongs to the neighbour and is dropped); codes leave 16 bytes at a time at any alignment.
-template <bool TINY>
+// RMAX: the column maxima of the residual (already cleared) come from the same read.
+template <bool TINY, bool RMAX = false>
 __global__ __launch_bounds__(256) void quant_cols_kernel(const float* __restrict__ X, int ldx, int rows,
                                                          int cols, const float* __restrict__ amax,
                                                          QuantParams q,
                                                          int8_t* __restrict__ codesT,
-                                                         const float* __restrict__ amax0) {
+                                                         const float* __restrict__ amax0, uint32_t* __restrict__ rmax_bits) {
     __shared__ __align__(16) int8_t tile[64][80];
+    __shared__ float4 red[RMAX ? 16 : 1][16];
+    float4 rm = make_float4(0.f, 0.f, 0.f, 0.f);
     const int n0 = blockIdx.x * 64, k0 = blockIdx.y * 64;
     const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
     const int n = TINY ? n0 + tx * 4 : min(n0 + tx * 4, cols - 4);
@@ -246,11 +301,30 @@ __global__ __launch_bounds__(256) void quant_cols_kernel(const float* __restrict
                             quant_residual(v.z, lam0[2], s0[2], q), quant_residual(v.w, lam0[3], s0[3], q));
         const float c[4] = {quant_code(v.x, lam[0], q), quant_code(v.y, lam[1], q), quant_code(v.z, lam[2], q),
                             quant_code(v.w, lam[3], q)};
+        if (RMAX) {         // (rows clamped to the last one: a maximum does not mind)
+            rm.x = fmaxf(rm.x, fabsf(fmaf(-c[0], stp[0], v.x)));
+            rm.y = fmaxf(rm.y, fabsf(fmaf(-c[1], stp[1], v.y)));
+            rm.z = fmaxf(rm.z, fabsf(fmaf(-c[2], stp[2], v.z)));
+            rm.w = fmaxf(rm.w, fabsf(fmaf(-c[3], stp[3], v.w)));
+        }
 #pragma unroll
         for (int t = 0; t < 4; ++t)
             if (TINY || n - n0 + t >= 0) tile[n - n0 + t][kl] = (int8_t)(int)c[t];
     }
+    if (RMAX) red[ty][tx] = rm;
     __syncthreads();
+    if (RMAX && ty == 0) {
+#pragma unroll
+        for (int g = 1; g < 16; ++g) {
+            const float4 o = red[g][tx];
+            rm.x = fmaxf(rm.x, o.x); rm.y = fmaxf(rm.y, o.y); rm.z = fmaxf(rm.z, o.z); rm.w = fmaxf(rm.w, o.w);
+        }
+        // (columns n .. n + 3 exist unless TINY, which has no residual maxima)
+        atomicMax(rmax_bits + n + 0, __float_as_uint(rm.x));
+        atomicMax(rmax_bits + n + 1, __float_as_uint(rm.y));
+        atomicMax(rmax_bits + n + 2, __float_as_uint(rm.z));
+        atomicMax(rmax_bits + n + 3, __float_as_uint(rm.w));
+    }
     const int nl = threadIdx.x >> 2, chunk = threadIdx.x & 3;
     const int nn = n0 + nl;
     if (nn >= cols) return;
@@ -367,21 +441,56 @@ int launch_absmax_pair(const float* A, int lda, int M, int K, float* amaxA, cons
 int launch_quantize_cols(const float* X, int ldx, int rows, int cols, QuantParams q, bool per_tensor,
                          const float* amax0, int8_t* codesT, float* amax, hipStream_t st) {
     hipLaunchKernelGGL(fill_u32_kernel, dim3(ceil_div(cols, 256)), dim3(256), 0, st, reinterpret_cast<uint32_t*>(amax), cols,
-                       0u);
+                       0u, nullptr);
     const ColSlabs p = plan_slabs(rows, cols);
     dim3 g1(p.col_blocks, p.slabs), g2(ceil_div(cols, 64), ceil_div(rows, 64));
     uint32_t* const bits = reinterpret_cast<uint32_t*>(amax);
     if (cols >= 4) hipLaunchKernelGGL(absmax_cols_kernel<false>, g1, dim3(256), 0, st, X, ldx, rows, cols, p.rows_per_block, bits, q, amax0);
     else           hipLaunchKernelGGL(absmax_cols_kernel<true>, g1, dim3(256), 0, st, X, ldx, rows, cols, p.rows_per_block, bits, q, amax0);
     if (per_tensor) hipLaunchKernelGGL(tensor_max_kernel, dim3(1), dim3(1024), 0, st, amax, cols, nullptr, 0);
-    if (cols >= 4) hipLaunchKernelGGL(quant_cols_kernel<false>, g2, dim3(256), 0, st, X, ldx, rows, cols, amax, q, codesT, amax0);
-    else           hipLaunchKernelGGL(quant_cols_kernel<true>, g2, dim3(256), 0, st, X, ldx, rows, cols, amax, q, codesT, amax0);
+    if (cols >= 4) hipLaunchKernelGGL(quant_cols_kernel<false>, g2, dim3(256), 0, st, X, ldx, rows, cols, amax, q, codesT, amax0, nullptr);
+    else           hipLaunchKernelGGL(quant_cols_kernel<true>, g2, dim3(256), 0, st, X, ldx, rows, cols, amax, q, codesT, amax0, nullptr);
+    LRQ_CHECK_LAUNCH();
+    return LRQMM_OK;
+}
+
+bool quantize_pair_usable(int M, int N, int K) { return M > 0 && N >= 4 && K >= 4 && K <= 16384; }
+
+int launch_quantize_pair(const float* A, int lda, const float* B, int ldb, int M, int N, int K, QuantParams q, QuantPair o,
+                         hipStream_t st) {
+    if (!quantize_pair_usable(M, N, K)) return LRQMM_ERR_UNSUPPORTED;
+    const bool res = o.codesRA != nullptr;
+    uint32_t *const bits = reinterpret_cast<uint32_t*>(o.amaxB), *const rbits = reinterpret_cast<uint32_t*>(o.amaxRB);
+    hipLaunchKernelGGL(fill_u32_kernel, dim3(ceil_div(N, 256)), dim3(256), 0, st, bits, N, 0u, res ? rbits : nullptr);
+    const ColSlabs p = plan_slabs(K, N);
+    const bool wave = K <= 64 * 4 * 16;         // one wave per row, or a workgroup
+    const int need = ceil_div(K, wave ? 256 : 1024), nbA = wave ? ceil_div(M, 4) : M;
+    const dim3 grid(nbA + p.col_blocks * p.slabs), g2(ceil_div(N, 64), ceil_div(K, 64));
+#define LRQ_QP(T, NV)                                                                                                         \
+    do {                                                                                                                      \
+        if (res) hipLaunchKernelGGL((quant_pair_kernel<T, NV, true>), grid, dim3(256), 0, st, A, lda, M, K, o, nbA, B, ldb, N,  \
+                                    p.rows_per_block, q, p.col_blocks);                                                       \
+        else     hipLaunchKernelGGL((quant_pair_kernel<T, NV, false>), grid, dim3(256), 0, st, A, lda, M, K, o, nbA, B, ldb, N, \
+                                    p.rows_per_block, q, p.col_blocks);                                                       \
+    } while (0)
+#define LRQ_QP_NV(T) do { if (need <= 1) LRQ_QP(T, 1); else if (need <= 2) LRQ_QP(T, 2); \
+        else if (need <= 4) LRQ_QP(T, 4); else if (need <= 8) LRQ_QP(T, 8); else LRQ_QP(T, 16); } while (0)
+    if (wave) LRQ_QP_NV(64);
+    else      LRQ_QP_NV(256);
+#undef LRQ_QP_NV
+#undef LRQ_QP
+    if (res) {
+        hipLaunchKernelGGL((quant_cols_kernel<false, true>), g2, dim3(256), 0, st, B, ldb, K, N, o.amaxB, q, o.codesB, nullptr, rbits);
+        hipLaunchKernelGGL((quant_cols_kernel<false>), g2, dim3(256), 0, st, B, ldb, K, N, o.amaxRB, q, o.codesRB, o.amaxB, nullptr);
+    } else {
+        hipLaunchKernelGGL((quant_cols_kernel<false>), g2, dim3(256), 0, st, B, ldb, K, N, o.amaxB, q, o.codesB, nullptr, nullptr);
+    }
     LRQ_CHECK_LAUNCH();
     return LRQMM_OK;
 }
 
 int launch_tick(uint32_t* word, hipStream_t st) {
-    hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(64), 0, st, word, 1, 0u);
+    hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(64), 0, st, word, 1, 0u, nullptr);
     LRQ_CHECK_LAUNCH();
     return LRQMM_OK;
 }

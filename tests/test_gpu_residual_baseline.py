@@ -152,3 +152,39 @@ def test_residual_products_in_one_launch(M, N, K, pad, alpha, beta, terms):
     for i, p in enumerate(products):
         L.lrqmm_gemm_ex(*p, 8, want[:, :N], alpha, beta if i == 0 else 1.0)
     assert torch.equal(got, want)
+
+
+# Both operands quantized in joint launches: rows of A in one wave's registers (up to 4096 columns) or a workgroup's (up to
+# 16384), one to sixteen loads each, the shortest rows it takes, one past the longest; ragged tiles of B.
+@pytest.mark.parametrize("M,N,K,pad", [(5, 4, 4, 0), (70, 65, 257, 1), (33, 130, 515, 3), (130, 67, 1025, 0), (9, 300, 2049, 2),
+                                       (64, 64, 4096, 0), (7, 70, 4097, 1), (6, 33, 8195, 0), (5, 40, 16384, 0), (5, 40, 16385, 0)])
+@pytest.mark.parametrize("terms", [0, 3, 4])
+def test_joint_quantization_equals_the_separate_calls(M, N, K, pad, terms):
+    """terms 0: direct quantization (rank 0).  The same codes, maxima and products as the quantizer calls and one lrqmm_gemm_ex
+    per product, in every round mode: the same values.  A has a zero row and B a zero column."""
+    import torch
+    import paper_2409_18772_amd as L
+    A, B = wl.random_matrix("normal", M, K, seed=31), wl.random_matrix("normal", K, N, seed=32)
+    A[1] = 0
+    B[:, N // 2] = 0
+    _, dA = window(A, pad)
+    _, dB = window(B, pad)
+    bits = 7 if K > 8192 else 8         # (int32 sums)
+    say("joint quantization", M, N, K, terms)
+    for mode in (o.FLOOR, o.NEAREST):
+        got = torch.full((M, N), 0.5, dtype=torch.float32, device="cuda")
+        want = got.clone()
+        if terms:
+            L.lrqmm_residual_matmul(dA, dB, got, bits, terms, round_mode=mode, alpha=0.75, beta=0.5)
+        else:
+            L.lrqmm_matmul_ex(dA, dB, got, bits, 0, round_mode=mode, alpha=0.75, beta=0.5)
+        Aq, amA = L.lrqmm_quantize_ex(dA, L.AXIS_ROW, bits, mode)
+        BqT, amB = L.lrqmm_quantize_ex(dB, L.AXIS_COL, bits, mode)
+        products = [(Aq, amA, BqT, amB)]
+        if terms:
+            RAq, amRA = L.lrqmm_quantize_residual(dA, amA, L.AXIS_ROW, bits, mode)
+            RBqT, amRB = L.lrqmm_quantize_residual(dB, amB, L.AXIS_COL, bits, mode)
+            products += [(Aq, amA, RBqT, amRB), (RAq, amRA, BqT, amB), (RAq, amRA, RBqT, amRB)][:terms - 1]
+        for i, p in enumerate(products):
+            L.lrqmm_gemm_ex(*p, bits, want, 0.75, 0.5 if i == 0 else 1.0)
+        assert torch.equal(got, want)
