@@ -216,8 +216,8 @@ LRQMM_API int lrqmm_gemm_static(int M, int N, int K, int bits, int rank,
  * size, that on B is enqueued on a second stream owned by the library (created on first use, default priority),
  * forked from and joined back into `stream` with events, so the call is still
  * ordered like a single-stream call from the caller's point of view.  For large
- * problems with a sketch of at least 32 columns (a small SVD long enough to hide it)
- * the integer product is enqueued on a third library stream while both
+ * problems with a sketch of at least 32 columns, where by size and width that is the
+ * faster schedule, the integer product is enqueued on a third library stream while both
  * factorizations are in their small SVD (the GPU is nearly idle then); it leaves
  * raw int32 sums in C's memory, and the dequantizing rank-2r update runs after the
  * panels as a kernel of its own with the arithmetic of the fused epilogue (same

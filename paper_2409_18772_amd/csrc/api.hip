@@ -245,10 +245,9 @@ int planes_values(int p) { return p == LRQMM_PREC_BF16 ? 1 : (p == LRQMM_PREC_BF
 // Whether the two operands' factorizations run as two chains on two streams instead of advancing together, one launch
 // per step for both.  Together they need half the launches, which bound small problems, and no events; as two chains the
 // single-workgroup steps of one fall beside the other's passes, which pays once the passes are as long as those steps.
-// Measured, together / two chains, us, sketches of 24, 40 and 80 columns (one power iteration): 1024^3 185 / 222,
-// 272 / 292, 593 / 610; 2048^3 247 / 255, 338 / 352, 677 / 690; 3072^3 320 / 325, 433 / 420, 792 / 791; 4096^3 390 / 383,
-// 482 / 467, 846 / 850; 8192^3 1354 / 1342, 1614 / 1501, 1980 / 1904; 12288^3 3443 / 3246, 3853 / 3686, 4285 / 4252;
-// 16384^3 6604 / 6628, 7648 / 7418, 8271 / 8288.
+// Measured, together / two chains, us, sketches of 24, 40 and 80 columns (one power iteration): 1024^3 143 / 193 (24);
+// 2048^3 196 / 212, 271 / 285, 497 / 508; 3072^3 279 / 283, 368 / 357, 618 / 614; 4096^3 351 / 348, 445 / 434, 688 / 690;
+// 8192^3 1387 / 1366 (24), 2017 / 1958 (80).
 bool two_chains(int M, int N, int K) {
     const long long elements = (long long)M * K + (long long)K * N;
     return elements > 13000000;

@@ -1295,16 +1295,10 @@ int launch_panel_prep(int M, int N, int K, int r, int RP, float qmaxf, const flo
     a.qmaxf = qmaxf;
     a.nbA = ceil_div(a.Mp, 256);
     a.nbB = ceil_div(a.Np, 256);
-    int nbV = 0;
-    a.nbP = 0; a.kslice = 1; a.nslices = 0;
-    if (r > 0) {
-        a.nbP = (int)(((size_t)a.Kp * RP + 255) / 256);
-        a.kslice = ceil_div(K, vtw_slices(K));
-        a.nslices = ceil_div(K, a.kslice);
-        nbV = r * a.nslices;
-    }
-    const int total = a.nbA + a.nbB + a.nbP + nbV;
-    if (total == 0) return LRQMM_OK;
+    a.nbP = (int)(((size_t)a.Kp * RP + 255) / 256);
+    a.kslice = ceil_div(K, vtw_slices(K));
+    a.nslices = ceil_div(K, a.kslice);
+    const int total = a.nbA + a.nbB + a.nbP + r * a.nslices;
     hipLaunchKernelGGL(panel_prep_kernel, dim3(total), dim3(256), 0, st, a);
     LRQ_CHECK_LAUNCH();
     return LRQMM_OK;

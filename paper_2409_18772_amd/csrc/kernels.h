@@ -162,8 +162,7 @@ int launch_take_basis(const BasisJob* job, int njob, int LP, int rank, hipStream
 // X = V^T W is kept as vtw_slices(K) k-slices Xp[ks][t][u] that are summed where X is used.
 #define LRQ_VTW_MAX_SLICES 16
 int vtw_slices(int K);
-// One launch: step vectors lamX/sX (padded to a multiple of 4) of both operands and, when
-// r > 0, Wp3 / Vp3: W and Vt^T as zero-padded bfloat16 planes [3][RP][Kp] (see launch_codes_mul_n2), and the slices
+// One launch (r > 0): step vectors lamX/sX (padded to a multiple of 4) of both operands, Wp3 / Vp3: W and Vt^T as zero-padded bfloat16 planes [3][RP][Kp] (see launch_codes_mul_n2), and the slices
 // Xp of V^T W.
 int launch_panel_prep(int M, int N, int K, int r, int RP, float qmaxf, const float* amaxA, const float* amaxB,
                       const float* W, const float* Vt, float* lamA, float* sA, float* lamB, float* sB,
