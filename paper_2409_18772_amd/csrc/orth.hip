@@ -562,6 +562,13 @@ __device__ __forceinline__ bool jacobi_rotation(double gpp, double gqq, double g
 #define SVD_THREADS (64 + SVD_UPDATE_THREADS)
 // Columns from which the tridiagonal solver is the faster one: l = 4 10.6 against 9.0 us (Jacobi), 5 11.1 / 12.6, 8 13.0 / 18.8
 #define LRQ_TRI_MIN 5
+// Below 32 columns a matrix whose diagonal spans more than this goes to the Jacobi solver at once: it keeps the small
+// eigenvalues of a graded matrix to their own size, the tridiagonalization to roundings of the norm.  Largest entry of
+// |V^T V - I| on 260 x 300 residuals, singular values down to 10^-x of the largest, tridiagonal / Jacobi: x = 4.75 1.9e-8 /
+// 1.8e-8, 5 3.7e-8 / 1.9e-8, 5.5 4.2e-7 / 2.0e-8, 6 2.7e-6 / 1.5e-8; a flat tail at x = 4 1.6e-8 / 2.8e-7.  Time at 24 columns
+// 109 / 123 us per factorization.  From 32 columns on the tridiagonal solver takes them all (5.5 at 64 and 80: 7.7e-7).
+#define LRQ_TRI_GRADED 1e-9
+#define LRQ_TRI_GRADED_BELOW 32
 
 // Loop-invariant addresses of one 2x2 block task of an update thread.
 struct SvdTask {
@@ -578,13 +585,15 @@ struct SvdTask {
 //   1. Householder tridiagonalization, G in the registers of one wave (above 40 columns two or four), see tridiagonalize.
 //   2. Eigenvalues by multisection, four waves: every lane counts the eigenvalues below two points of its own (Sturm
 //      sequence of the leading minors, rescaled every eighth row: one dependent FMA per row; the rows of T in registers up
-//      to 40 columns), and ballots narrow all intervals by a factor 2 GL + 1 per round, down to the resolution of float64.
+//      to 40 columns), and ballots narrow all intervals by a factor 2 GL + 1 per round, to 2^-49 of the norm, and two rounds
+//      further where an eigenvalue is small.
 //   3. Eigenvectors of the tridiagonal matrix by twisted factorization, one lane per vector: the LDU sweep from the top in
 //      one wave, the one from the bottom in another; they meet at the index where the residual is smallest.
 //   4. Back transformation by the Householder vectors, eight lanes per vector, no barrier.
 //   5. S = U^T U on the float64 matrix cores.  Off I by more than 1e-11 (eigenvalues that nearly coincide): one step
 //      U (3 I - S) / 2, which squares the deviation.  By more than 1e-4, or not a number (multiple eigenvalues, a
-//      tridiagonal matrix that falls apart): the Jacobi solver below instead; zero rows go there at once.
+//      tridiagonal matrix that falls apart): the Jacobi solver below instead; zero rows and narrow graded matrices
+//      (LRQ_TRI_GRADED) go there at once.
 // Accuracy: eigenvalues to a few ulps of the largest one; ||G u - s u|| likewise.
 // Alone, Jacobi (below 32 columns) or the earlier form with G in LDS and eight waves / this one, us: l = 16 34 / 17, 24
 // 61 / 27, 40 96 / 54, 64 206 / 102, 80 277 / 147.  What bounds it: step 1's chain of about 1000 cycles per column (two sums
@@ -875,10 +884,16 @@ __device__ __forceinline__ bool tridiagonal_svd(const SvdJob& job, int ell, int 
     double* const Z1 = A + ((max(ell * lda, ldz * ldz) + 1) & ~1);         // (even: pairs are 16-byte aligned)
     double* const Z2 = Z1 + LP * ldz;
     if (tid < 2) flags[tid] = 0;
-    {   // zero rows (columns of the sketch that were dropped) split the matrix
-        bool dead = false;
-        for (int i = lane; i < ell; i += 64) dead = dead || !(job.gram[i * LP + i] > 0.0);
-        if (__any(dead)) return false;          // the same in every wave
+    {   // zero rows (columns of the sketch that were dropped) split the matrix; narrow graded matrices see LRQ_TRI_GRADED
+        double top = 0.0, low = 1e300;
+        for (int i = lane; i < ell; i += 64) {
+            const double d = job.gram[i * LP + i];
+            top = fmax(top, d);
+            low = d > 0.0 ? fmin(low, d) : 0.0;
+        }
+        top = wave_max_f64(top);
+        low = -wave_max_f64(-low);
+        if (!(low > (ell < LRQ_TRI_GRADED_BELOW ? LRQ_TRI_GRADED * top : 0.0))) return false;          // the same in every wave
     }
     // ---- 1. tridiagonalization ----
     static_assert(672 + LW * (LW | 1) + TriShape<LW, tri_groups(LW), tri_waves(LW)>::WORDS <= svd_pool(LW), "fits the pool");
@@ -927,7 +942,7 @@ __device__ __forceinline__ bool tridiagonal_svd(const SvdJob& job, int ell, int 
         const int t = wave * per + grp;
         const int e = ell - 1 - t;              // eigenvalues below it
         const double step = rcp_f64(2.0 * GL + 1.0);
-        const uint64_t mask = ((1ull << GL) - 1) << (grp * GL);
+        const uint64_t mask = ((1ull << GL) - 1) << (grp * GL), live = __ballot(grp < per && t < rank);
         constexpr bool IN_REGS = LW <= 40;      // the rows of T stay in registers, or come from LDS in every round
         double2 rows[IN_REGS ? LW : 1];
         if constexpr (IN_REGS) {
@@ -936,7 +951,9 @@ __device__ __forceinline__ bool tridiagonal_svd(const SvdJob& job, int ell, int 
         }
         double lo = -1e-6, hi = 1.0;
         if (wave * per < rank)
-        for (int r = 0; r < rounds; ++r) {
+        for (int r = 0; r < rounds + 2; ++r) {
+            // two more where an eigenvalue is far below the largest: V = B^T U' / sigma needs it relative to itself
+            if (r >= rounds && !(__ballot(hi - lo > 1e-11 * hi) & live)) break;
             const double h = (hi - lo) * step;
             const double xa = fma(h, g + 1.0, lo), xb = fma(h, (double)(g + 1 + GL), lo);
             // leading minors p_i of T - x I, scaled: the number of sign changes is the number of eigenvalues below x

@@ -173,6 +173,34 @@ def test_rsvd_flat_tail_far_below_the_top(flat, k, ell):
     assert np.linalg.norm((U * S) @ Vt - R) <= 1e-5 * np.linalg.norm(R)
 
 
+@pytest.mark.parametrize("shape", ["dense", "rows"])
+@pytest.mark.parametrize("ell", [5, 8, 16, 17, 24, 31, 32, 40, 48, 64, 80])
+def test_rsvd_steep_spectrum(ell, shape):
+    """Singular values from 1 down to 1e-5 of the largest.  A row of Vt is B^T u / sigma rounded to float32, so with the
+    eigenvalue right relative to itself an entry of V^T V is off by at most 2 u + u^2 (u = 2^-24: each row has norm 1, its
+    rounding error norm u); 2e-7 leaves 0.8e-7 for the solver, 1e-15 of the largest eigenvalue against 1e-10 of it being
+    1e-5.  rows: the rows of R differ in size as the singular values do, which leaves a graded small matrix."""
+    rng = np.random.default_rng(ell)
+    m, n = 260, 300
+    s = 10.0 ** -np.linspace(0, 5, ell)
+    v, _ = np.linalg.qr(rng.standard_normal((n, ell)))
+    if shape == "dense":
+        u, _ = np.linalg.qr(rng.standard_normal((m, ell)))
+    else:
+        u, h = np.zeros((m, ell)), m // ell
+        for i in range(ell):
+            u[i * h:(i + 1) * h, i] = rng.uniform(0.5, 1.0, h)
+    R = (u * s) @ v.T
+    R = (R * (0.4 / np.abs(R).max())).astype(np.float32)
+    U, S, Vt = _whole_rsvd_of(R, ell)
+    kept = S > 0            # (the last columns of a sketch may fall below the pivot limit: dropped, zero)
+    say("steep", ell, shape, "kept", int(kept.sum()), "tail", S[kept][-1] / S[0])
+    assert kept.sum() >= ell - 1 - ell // 16
+    assert np.max(np.abs(U[:, kept].T @ U[:, kept] - np.eye(int(kept.sum())))) < 2e-7
+    assert np.max(np.abs(Vt[kept] @ Vt[kept].T - np.eye(int(kept.sum())))) < 2e-7
+    assert np.linalg.norm((U * S) @ Vt - R) <= 1e-5 * np.linalg.norm(R)
+
+
 def test_rsvd_truncation_between_nearly_equal_singular_values():
     """A case in which the rank-r truncation is not determined at float32 resolution: the residual of the tall
     conv-shaped operand (100352 x 576, ReLU inputs) with l = 16, one power iteration, truncated to r = 8.  The
