@@ -80,7 +80,9 @@ LRQMM_API const char* lrqmm_status_string(int status);
 
 /* Bytes of device workspace that lrqmm_rsvd / lrqmm_gemm / lrqmm_matmul need for
  * a problem of this size (the maximum over the three).  The workspace must be
- * 256-byte aligned.  Returns 0 for invalid arguments. */
+ * 256-byte aligned.  The size does not fall when an argument grows: a workspace for
+ * the largest of several problems serves them all (a batch of varying M, say).
+ * Returns 0 for invalid arguments. */
 LRQMM_API size_t lrqmm_workspace_bytes(int M, int N, int K, int rank, int oversample);
 
 /*

@@ -40,24 +40,20 @@ struct RsvdWs {
     double *gpart, *gram, *Ur, *Mv;
 };
 
+// Every region of carve_rsvd and carve_matmul is at least as large for a larger problem, so that one workspace, sized for the
+// largest, serves them all.
 size_t carve_rsvd(Arena& a, int rows, int cols, int axis, int LP, int rank, RsvdWs* w) {
     const int nscale = axis == LRQMM_AXIS_ROW ? rows : cols;
     const int npad = pad_to(nscale, 4);
-    const PassPlan pn = plan_pass_n(rows, cols, LP), pt = plan_pass_t(rows, cols, LP);
-    const size_t part = (size_t)LP * (size_t)((size_t)pn.splits * rows > (size_t)pt.splits * cols
-                                                  ? (size_t)pn.splits * rows
-                                                  : (size_t)pt.splits * cols);
-    // (the block count is not monotone in the row count -- 4096 rows make 64 blocks of 64, 4100 rows 33 of 128 --
-    // so take the larger of the two uses, Gram of a rows x LP and of a cols x LP factor)
-    // (and the one-read quantization kernel for row-quantized operands leaves one partial per workgroup)
-    int nb = gram_blocks(rows, LP) > gram_blocks(cols, LP) ? gram_blocks(rows, LP) : gram_blocks(cols, LP);
+    // (the one-read quantization kernel for row-quantized operands leaves one Gram partial per workgroup)
+    int nb = gram_blocks_most(rows > cols ? rows : cols, LP);
     if (axis == LRQMM_AXIS_ROW && LP == 16 && quant_sketch_rows_blocks(rows) > nb) nb = quant_sketch_rows_blocks(rows);
     RsvdWs t;
     t.lam = a.take<float>(npad);
     t.s = a.take<float>(npad);
     t.Wc = a.take<float>((size_t)cols * LP);
     t.Yr = a.take<float>((size_t)rows * LP);
-    t.partial = a.take<float>(part);
+    t.partial = a.take<float>(pass_partial_floats(rows, cols, LP));
     t.gpart = a.take<double>((size_t)nb * LP * LP);
     t.gram = a.take<double>((size_t)LP * LP);
     t.Ur = a.take<double>((size_t)LP * rank);
@@ -71,7 +67,9 @@ struct GemmWs {
     uint16_t *Wp3, *Vp3;
 };
 
-size_t carve_gemm(Arena& a, int M, int N, int K, int rank, GemmWs* w) {
+// smaller_too: room for every problem that is no larger in any extent (what lrqmm_workspace_bytes promises), not only for
+// this one (what lrqmm_gemm and lrqmm_gemm_static ask for).
+size_t carve_gemm(Arena& a, int M, int N, int K, int rank, GemmWs* w, bool smaller_too = false) {
     GemmWs t = {};
     const int Mp = pad_to(M, 4), Np = pad_to(N, 4);
     t.lamA = a.take<float>(Mp);
@@ -83,8 +81,8 @@ size_t carve_gemm(Arena& a, int M, int N, int K, int rank, GemmWs* w) {
         const PassPlan pa = plan_codes(M, K), pb = plan_codes(N, K);
         t.Wp3 = a.take<uint16_t>((size_t)3 * RP * pad_to(K, 64));
         t.Vp3 = a.take<uint16_t>((size_t)3 * RP * pad_to(K, 64));
-        t.partialA = a.take<float>((size_t)RP * pa.splits * M);
-        t.partialB = a.take<float>((size_t)RP * pb.splits * N);
+        t.partialA = a.take<float>(RP * (smaller_too ? codes_partial_rows(M, K) : (size_t)pa.splits * M));
+        t.partialB = a.take<float>(RP * (smaller_too ? codes_partial_rows(N, K) : (size_t)pb.splits * N));
         t.X = a.take<float>((size_t)rank * rank * LRQ_VTW_MAX_SLICES);
         t.Lp = a.take<float>((size_t)M * R2P);
         t.Rp = a.take<float>((size_t)N * R2P);
@@ -124,7 +122,7 @@ size_t carve_matmul(Arena& a, int M, int N, int K, int rank, int oversample, Mat
     size_t sub = 0, sa = 0, sb = 0;
     {
         Arena g(nullptr);
-        sub = carve_gemm(g, M, N, K, rank, nullptr);
+        sub = carve_gemm(g, M, N, K, rank, nullptr, true);
     }
     if (rank > 0) {
         // the two residual factorizations run concurrently: each gets its own region

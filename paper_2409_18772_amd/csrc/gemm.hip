@@ -1396,7 +1396,8 @@ SumsPlan plan_sums(int M, int N, int K, const int8_t* Aq, const int8_t* BqT, int
 }  // namespace
 
 size_t int8_gemm_sums_scratch_bytes(int M, int N, int K) {
-    const bool shape = int8_gemm_large_tiles(M, N) && M % BTM == 0 && N % BTN == 0 && K % BBK == 0 && K >= 8 * BBK;
+    // (whole tiles only; counted for ragged problems too, which contain smaller ones of whole tiles)
+    const bool shape = int8_gemm_large_tiles(M / BTM * BTM, N / BTN * BTN) && K >= 8 * BBK;
     return shape ? (size_t)LRQ_SUMS_MAX_PARTS * BTM * BTN * sizeof(int32_t) : 0;
 }
 

@@ -60,6 +60,10 @@ struct PassPlan {
 PassPlan plan_pass_n(int rows, int cols, int LP);
 PassPlan plan_pass_t(int rows, int cols, int LP);
 PassPlan plan_codes(int rows, int K);       // code products (launch_codes_mul_n2)
+// Room for the partial results of both passes, and rows of it for a code product: at least what the plans need, and no less
+// for a larger problem (a plan takes fewer ranges where there are more rows), so that a workspace serves smaller ones.
+size_t pass_partial_floats(int rows, int cols, int LP);
+size_t codes_partial_rows(int rows, int K);
 // One operand of a factorization, as the passes see it.  X is rows x cols with row stride ldx (>= cols); axis 0: scales
 // by row, 1: by column (lam, s: the step vectors).
 struct PassOperand {
@@ -114,6 +118,7 @@ int launch_codes_mul_n2(const int8_t* codesA, int rowsA, const uint16_t* WA3, Pa
 // ---- orth.hip -----------------------------------------------------------
 // Every launch below takes one job or two (the two operands of a product, in one launch).
 int gram_blocks(int n, int LP);
+int gram_blocks_most(int n, int LP);        // of any factor with up to n rows
 struct GramJob {
     const float* partial;       // [splits][n][LP]
     int splits, n;

@@ -41,6 +41,7 @@ static int gram_rows_per_block(int n, int LP) {
 }
 
 int gram_blocks(int n, int LP) { return max(1, ceil_div(n, gram_rows_per_block(n, LP))); }
+int gram_blocks_most(int n, int LP) { return max(1, min(ceil_div(n, 16), gram_max_blocks(LP))); }
 
 // Y = sum of the pass partials (fixed order); gpart[block] = float64 Gram matrix of the block's rows, formed on the
 // float64 matrix cores (v_mfma_f64_16x16x4, layout as at apply_kernel) from a TR-row tile in LDS: the 16 x 16 blocks

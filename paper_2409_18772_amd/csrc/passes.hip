@@ -1197,6 +1197,27 @@ PassPlan plan_pass_t(int rows, int cols, int LP) {
     return p;
 }
 
+// At least the rows of partial results (rows times ranges) of a plan of pick_splits at up to n rows in blocks of `block`:
+// ceil(target / blocks) ranges of at most block rows a block.  Does not fall when an argument grows (the plans themselves do:
+// 512 blocks make one range, 511 two).
+static size_t most_partial_rows(int n, int block, int reduce_len, int depth, int target, int limit) {
+    return min((size_t)n * min(limit, max(1, reduce_len / depth)), (size_t)n + (size_t)block * target);
+}
+
+size_t pass_partial_floats(int rows, int cols, int LP) {
+    const PassPlan pn = plan_pass_n(rows, cols, LP), pt = plan_pass_t(rows, cols, LP);
+    const int unit = LP == 16 ? KCHUNK : 64, block = LP >= 64 ? 128 : 64;
+    size_t part = LP * max(most_partial_rows(rows, block, cols, 2 * unit, 512, MAX_SPLITS),
+                           most_partial_rows(min(rows, 1024), block, cols, 64, 512, MAX_SPLITS));
+    part = max(part, LP * most_partial_rows(cols, 64, rows, 128, 512, MAX_SPLITS_T));
+    part = max(part, 16 * most_partial_rows(cols, 64, rows, 32, 512, MAX_SPLITS_T));
+    return max(part, LP * max((size_t)pn.splits * rows, (size_t)pt.splits * cols));
+}
+
+size_t codes_partial_rows(int rows, int K) {
+    return max((size_t)plan_codes(rows, K).splits * rows, most_partial_rows(rows, 64, K, 4 * KCHUNK, 512, MAX_SPLITS));
+}
+
 // The jobs of one launch: at most one with scales by row and one with scales by column.  Workgroup shape and plan of an
 // operand depend on its own sizes; a launch has one workgroup shape, so a pair takes the wide one only when both do.
 namespace {

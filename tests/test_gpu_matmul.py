@@ -315,6 +315,23 @@ def test_untruncated_narrow_sketch(M, N, K, r, q, dist):
     assert rel_fro(to_np(_separate_calls(L, dA, dB, 8, r, 0, q, 9)), C) < 2 * tol_for(ref)
 
 
+@pytest.mark.parametrize("big,small", [((359, 2053, 1604), (288, 2053, 1604)), ((228, 691, 3550), (224, 691, 3550)),
+                                       ((1030, 700, 2100), (1000, 640, 256))])
+def test_smaller_call_in_a_larger_call_s_workspace(big, small):
+    """One workspace, exactly the size reported for the larger problem, serves both, with the bits of a workspace of their
+    own (rank 16, no oversampling; and the layer form's factorization in it)."""
+    import torch
+    import paper_2409_18772_amd as L
+    ws = L.Workspace(L.lrqmm_workspace_bytes(*big, 16, 0))
+    for M, N, K in (big, small):
+        A, B = to_dev(wl.random_matrix("normal", M, K, seed=61)), to_dev(wl.random_matrix("normal", K, N, seed=62))
+        say("shared workspace", M, N, K)
+        assert torch.equal(L.lrqmm_matmul(A, B, 8, 16, 0, 1, seed=4, workspace=ws), L.lrqmm_matmul(A, B, 8, 16, 0, 1, seed=4))
+        _, amax = L.lrqmm_quantize(A, L.AXIS_ROW, 8)
+        for x, y in zip(L.lrqmm_rsvd(A, amax, 0, 8, 16, 0, 1, seed=4, workspace=ws), L.lrqmm_rsvd(A, amax, 0, 8, 16, 0, 1, seed=4)):
+            assert torch.equal(x, y)
+
+
 FULL = ["c2_4096_int8_r16", "c3_4096_int4_r32_outliers"]
 
 

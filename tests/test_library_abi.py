@@ -83,6 +83,33 @@ def test_workspace_of_an_empty_problem(M, N, K):
     assert status in ((0,) if M == 0 or N == 0 else (-1, -4))       # (-4: no GPU to look the static scratch up on)
 
 
+def test_workspace_of_a_larger_problem_serves_a_smaller_one():
+    """The size does not fall when an extent, the rank or the oversampling grows.  Extents around the limits of the launch
+    plans (512 blocks of 64 rows, 1024 rows, 256 x 256 tiles) and pairs that the plans treat very differently."""
+    import random
+    import paper_2409_18772_amd as L
+    if not os.path.exists(L.lib_path()):
+        pytest.skip("library not built")
+    size = L.lrqmm_workspace_bytes
+    assert size(288, 2053, 1604, 16, 0) <= size(359, 2053, 1604, 16, 0)
+    assert size(224, 691, 3550, 16, 0) <= size(228, 691, 3550, 16, 0)
+    assert size(4096, 4096, 4096, 32, 8) <= size(4100, 4096, 4096, 32, 8)
+    rng = random.Random(5)
+    edges = [64, 255, 256, 511, 512, 1023, 1024, 1025, 2048, 4096, 4097, 8192, 8193, 32704, 32705, 32768, 65536]
+
+    def extent():
+        return rng.choice(edges) if rng.random() < 0.3 else int(2 ** rng.uniform(5, 17))
+    for _ in range(20000):
+        big = [extent() for _ in range(3)] + [rng.randint(1, 64), rng.choice([0, 4, 8, 16])]
+        small = list(big)
+        for i in rng.sample(range(5), rng.choice([1, 1, 2, 5])):
+            low = 1 if i < 4 else 0
+            small[i] = rng.randint(max(low, big[i] - 40), big[i]) if rng.random() < 0.5 else rng.randint(low, big[i])
+        if rng.random() < 0.1 and small[3] > 0:
+            small[3] = 0
+        assert size(*small) <= size(*big), (small, big)
+
+
 def test_missing_library_fails_loudly(monkeypatch, tmp_path):
     import paper_2409_18772_amd.binding as b
     monkeypatch.setattr(b, "_LIB", None)
