@@ -106,11 +106,13 @@ __device__ __forceinline__ int xcd_tile(int id, int tiles_n, int ntiles) {
 // the larger tiles are too few to fill the chip (see launch_int8_gemm).
 //
 // K tiles are 128 deep, global loads two of them ahead of the matrix cores in a ring of two sets of named registers (as arrays
-// they would go to scratch memory).  The epilogue stages the panel rows of the tile through the LDS that the operand tiles
-// have left, 64 columns at a time: as operands straight from global memory every eight columns of each 32 x 32 tile waited
-// for a load.  Measured, us per call, 64-deep tiles and unstaged panels / this: 2000^3 154.3 / 152.3,
-// 3072 x 1536 x 2048 (l = 40) 295 / 288, 2816^3 (l = 24) 197 / 189, 512 x 4096 x 4096 256 / 251, 1537 x 1021 x 2311 202.5 / 201.3,
-// 100352 x 64 x 576 211.4 / 208.8; a reduction of 64 is half a tile: 100352 x 64 x 64 122.4 / 123.5.
+// they would go to scratch memory).  The epilogue's operands travel beside the K loop: the steps are in LDS before it starts,
+// the first 32 panel columns of the tile's rows in registers; each further 32 are loaded while the matrix cores take the ones
+// before, in two buffers of the LDS that the operand tiles have left.  lrqmm_gemm, us, 64-deep tiles with panels straight from
+// global memory / 128-deep with 64 columns at a time loaded behind the K loop / this: 2048^3 rank 48 74.6 / 72.8 / 65.0; 512 x
+// 4096 x 4096 rank 16 50.1 / 45.9 / 43.8; 4096 x 2048 x 2048 rank 80 186 / 134 / 123; short reductions, where the load latency
+// of the epilogue shows most, 128 x 8192 x 576 rank 80 85.3 / 88.8 / 82.1, 1024 x 1024 x 576 rank 48 45.8 / 47.5 / 43.7,
+// 100352 x 64 x 64 rank 8 33.7 / 34.1 / 31.7, 100352 x 16 x 16 31.5 / 32.7 / 30.4.
 template <bool WIDE, bool COMP, bool WCINT, int MTW, int NTW>
 __global__ __launch_bounds__(256, 2) void int8_gemm_kernel(int M, int N, int K,
                                                            const int8_t* __restrict__ Aq,
@@ -125,6 +127,7 @@ __global__ __launch_bounds__(256, 2) void int8_gemm_kernel(int M, int N, int K,
     constexpr int TMW = 64 * MTW, TNW = 64 * NTW;       // tile height and width
     __shared__ __align__(16) int8_t As[2][TMW * BSTRIDE];
     __shared__ __align__(16) int8_t Bs[2][TNW * BSTRIDE];
+    __shared__ __align__(16) float steps[TMW + TNW];    // of the tile's rows, then of its columns
     const int tile = xcd_tile(blockIdx.x, tiles_n, ntiles);
     const int m0 = (tile / tiles_n) * TMW, n0 = (tile % tiles_n) * TNW;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -165,6 +168,19 @@ __global__ __launch_bounds__(256, 2) void int8_gemm_kernel(int M, int N, int K,
     LRQ_ST(As[buf], 0, S##a0); LRQ_ST(Bs[buf], 0, S##b0); LRQ_ST(As[buf], 1, S##a1); LRQ_ST(Bs[buf], 1, S##b1); \
     if constexpr (MTW == 2) { LRQ_ST(As[buf], 2, S##a2); LRQ_ST(As[buf], 3, S##a3); }                   \
     if constexpr (NTW == 2) { LRQ_ST(Bs[buf], 2, S##b2); LRQ_ST(Bs[buf], 3, S##b3); }
+    // panel rows of the tile, 32 columns at a time: rows past the end re-read the last one, columns past it the last four
+    const int prow = tid >> 3, pcol = (tid & 7) * 4;
+    float4 q0, q1, q2, q3, q4, q5, q6, q7;
+#define LRQ_PL(U, c) *reinterpret_cast<const float4*>(32 * U < TMW ? Lp + (size_t)min(m0 + prow + 32 * U, M - 1) * R2P + c \
+                                                                   : Rp + (size_t)min(n0 + prow + 32 * U - TMW, N - 1) * R2P + c)
+#define LRQ_PLOAD(t0)                                                                                  \
+    {                                                                                                  \
+        const int c = min((t0) + pcol, R2P - 4);                                                       \
+        q0 = LRQ_PL(0, c); q1 = LRQ_PL(1, c); q2 = LRQ_PL(2, c); q3 = LRQ_PL(3, c);                    \
+        if constexpr (MTW + NTW > 2) { q4 = LRQ_PL(4, c); q5 = LRQ_PL(5, c); }                         \
+        if constexpr (MTW + NTW > 3) { q6 = LRQ_PL(6, c); q7 = LRQ_PL(7, c); }                         \
+    }
+#define LRQ_PST(U) *reinterpret_cast<float4*>((32 * U < TMW ? Ls + (prow + 32 * U) * LDP : Rs + (prow + 32 * U - TMW) * LDP) + pcol) = q##U
     LRQ_DECL(r0);
     LRQ_DECL(r1);
     auto compute = [&](int buf) {
@@ -187,8 +203,14 @@ __global__ __launch_bounds__(256, 2) void int8_gemm_kernel(int M, int N, int K,
         }
     };
     const int nk = (K + BBK - 1) / BBK;
+    // (without panels sA, sB hold the group maxima, and the tile's steps are formed here)
+    float st = 0.f;
+    if (tid < TMW) st = sA[min(m0 + tid, M - 1)];
+    else if (tid - TMW < TNW) st = sB[min(n0 + tid - TMW, N - 1)];
     LRQ_GLOAD(r0, 0);
     LRQ_GLOAD(r1, BBK);
+    if constexpr (COMP) LRQ_PLOAD(0);
+    if (tid < TMW + TNW) steps[tid] = COMP ? st : step_of(st, qmaxf);
     LRQ_SSTORE(r0, 0, 0);
     __syncthreads();
     // iteration i: the set that held tile i is free -> load tile i + 2; compute tile i; publish tile i + 1
@@ -212,14 +234,6 @@ __global__ __launch_bounds__(256, 2) void int8_gemm_kernel(int M, int N, int K,
 #undef LRQ_SSTORE
 
     // ---- epilogue: dequantize, rank-2r update, store ----
-    // Without panels sA, sB hold the group maxima, and the tile's steps are formed here, one per thread, in LDS.
-    float* const sAl = reinterpret_cast<float*>(&As[0][0]);
-    float* const sBl = reinterpret_cast<float*>(&Bs[0][0]);
-    if (!COMP) {
-        if (tid < TMW) sAl[tid] = step_of(sA[min(m0 + tid, M - 1)], qmaxf);
-        else if (tid - TMW < TNW) sBl[tid - TMW] = step_of(sB[min(n0 + tid - TMW, N - 1)], qmaxf);
-        __syncthreads();
-    }
     v16f f[MTW][NTW];
 #pragma unroll
     for (int mt = 0; mt < MTW; ++mt) {
@@ -228,12 +242,12 @@ __global__ __launch_bounds__(256, 2) void int8_gemm_kernel(int M, int N, int K,
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const int row = rbase + 8 * (v >> 2) + 4 * lh + (v & 3);
-            sa[v] = COMP ? sA[min(row, M - 1)] : sAl[row - m0];
+            sa[v] = steps[row - m0];
         }
 #pragma unroll
         for (int nt = 0; nt < NTW; ++nt) {
             const int col = n0 + wn * 32 * NTW + nt * 32 + l32;
-            const float sb = COMP ? sB[min(col, N - 1)] : sBl[col - n0];
+            const float sb = steps[TMW + col - n0];
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int row = rbase + 8 * (v >> 2) + 4 * lh + (v & 3);
@@ -243,26 +257,21 @@ __global__ __launch_bounds__(256, 2) void int8_gemm_kernel(int M, int N, int K,
         }
     }
     if constexpr (COMP) {
-        constexpr int LDP = 68;         // 64 columns, padded: conflict-free 16-byte reads
-        static_assert(2 * BSTRIDE >= LDP * 4, "64 panel columns of a tile fit the operand's LDS");
-        float* const Ls = reinterpret_cast<float*>(&As[0][0]);
-        float* const Rs = reinterpret_cast<float*>(&Bs[0][0]);
-        for (int t0 = 0; t0 < R2P; t0 += 64) {      // (the loop's last barrier, or the one below, has released the LDS)
-            if (t0 > 0) __syncthreads();
-            const int q4 = min(R2P - t0, 64) / 4;
-            for (int idx = tid; idx < (TMW + TNW) * q4; idx += 256) {       // rows past the end re-read the last one (never stored)
-                const int rr = idx / q4, c4 = 4 * (idx - rr * q4);
-                if (rr < TMW)
-                    *reinterpret_cast<float4*>(Ls + rr * LDP + c4) =
-                        *reinterpret_cast<const float4*>(Lp + (size_t)min(m0 + rr, M - 1) * R2P + t0 + c4);
-                else
-                    *reinterpret_cast<float4*>(Rs + (rr - TMW) * LDP + c4) =
-                        *reinterpret_cast<const float4*>(Rp + (size_t)min(n0 + rr - TMW, N - 1) * R2P + t0 + c4);
-            }
+        // two buffers of 32 columns in the operand tiles' LDS (the K loop's last barrier has released it)
+        constexpr int LDP = 36;         // padded: conflict-free 16-byte reads
+        static_assert(2 * BSTRIDE >= 2 * LDP * 4, "two chunks of the panel rows fit the operand's LDS");
+        for (int t0 = 0, buf = 0; t0 < R2P; t0 += 32, buf ^= 1) {
+            float* const Ls = reinterpret_cast<float*>(&As[0][0]) + buf * (TMW * LDP);
+            float* const Rs = reinterpret_cast<float*>(&Bs[0][0]) + buf * (TNW * LDP);
+            LRQ_PST(0); LRQ_PST(1); LRQ_PST(2); LRQ_PST(3);
+            if constexpr (MTW + NTW > 2) { LRQ_PST(4); LRQ_PST(5); }
+            if constexpr (MTW + NTW > 3) { LRQ_PST(6); LRQ_PST(7); }
+            if (t0 + 32 < R2P) LRQ_PLOAD(t0 + 32);
             __syncthreads();
             const float* const lp = Ls + (wm * 32 * MTW + l32) * LDP + 4 * lh;
             const float* const rp = Rs + (wn * 32 * NTW + l32) * LDP + 4 * lh;
-            for (int t = 0; t < 4 * q4; t += 8) {       // (R2P % 8 == 0)
+            const int width = min(R2P - t0, 32);
+            for (int t = 0; t < width; t += 8) {       // (R2P % 8 == 0)
                 float4 a4[MTW], b4[NTW];
 #pragma unroll
                 for (int mt = 0; mt < MTW; ++mt) a4[mt] = *reinterpret_cast<const float4*>(lp + 32 * mt * LDP + t);
@@ -279,6 +288,9 @@ __global__ __launch_bounds__(256, 2) void int8_gemm_kernel(int M, int N, int K,
             }
         }
     }
+#undef LRQ_PL
+#undef LRQ_PLOAD
+#undef LRQ_PST
 #pragma unroll
     for (int mt = 0; mt < MTW; ++mt)
 #pragma unroll

@@ -367,6 +367,7 @@ def test_gemm_wide_panels_on_large_tiles(M, N, K, rank):
     fa, fb = tuple(map(to_dev, (U, S, Vt))), tuple(map(to_dev, (W, G, Zt)))
     C, Cint = L.lrqmm_gemm(*dev, 8, fa, fb, want_cint=True)
     rows = np.unique(np.concatenate([[0, 255, 256, M - 1, M - 2, M // 256 * 256 - 1], rng.integers(0, M, 12)]))
+    rows = rows[(rows >= 0) & (rows < M)]
     assert np.array_equal(to_np(Cint)[rows].astype(np.int64), Aq[rows].astype(np.int64) @ Bq.astype(np.int64))
     sa, sb = (amA / np.float32(127)).astype(np.float64), (amB / np.float32(127)).astype(np.float64)
     At, Bt = Aq[rows] * sa[rows, None], Bq * sb[None, :]
@@ -382,3 +383,12 @@ def test_gemm_wide_panels_on_large_tiles(M, N, K, rank):
     assert torch.all(D[:, N:] == 0.5)
     want = 1.5 * to_np(C)[rows].astype(np.float64) - 0.25
     assert np.abs(to_np(D)[rows, :N] - want).max() <= 3 * 2.0 ** -24 * np.abs(want).max() + 2.0 ** -24
+
+
+# The smaller tiles: panels of 8 columns to 160 around the chunks of 32 that the epilogue takes at a time, on each tile shape
+# (64 x 64, 64 x 128, 128 x 128), ragged at every edge, reductions of half a staged tile, one, and one byte more.
+@pytest.mark.parametrize("M,N,K,rank", [(130, 70, 90, 1), (65, 129, 128, 4), (130, 70, 129, 12), (130, 70, 90, 16), (64, 64, 64, 17),
+                                        (129, 191, 257, 32), (130, 97, 143, 33), (100, 190, 100, 80), (1030, 2050, 130, 20),
+                                        (1030, 2050, 64, 36), (2050, 2049, 129, 16), (2050, 2049, 100, 49), (9000, 33, 40, 8)])
+def test_gemm_panel_widths_on_small_tiles(M, N, K, rank):
+    test_gemm_wide_panels_on_large_tiles(M, N, K, rank)
