@@ -90,7 +90,7 @@ def cpu_baseline(w, A, B, budget_rows: int):
 
 
 def small_tile(M, N):
-    """Tile of the integer product's kernel for outputs below 136 tiles of 256 x 256: the largest with 256 tiles or more."""
+    """Tile of the integer product's kernel where it is not the large-tile one: the largest with 256 tiles or more."""
     tm = tn = 64 if N <= 64 else 128
     tiles = lambda: -(-M // tm) * -(-N // tn)
     if tiles() < 256:
@@ -226,7 +226,8 @@ def main():
     # which roof bounds the product: its algorithmic bytes (codes read once, 4-byte results written once, panels)
     # against its operations; below peak_ops / peak_bytes operations per byte the kernel is bound by memory
     gemm_bytes = float(w.M * w.K + w.K * w.N + 4 * w.M * w.N + (0 if early else 8 * w.rank * (w.M + w.N)))
-    large_tiles = w.M >= 256 and w.N >= 256 and -(-w.M // 256) * -(-w.N // 256) >= (128 if early else 136)
+    large_tiles = w.M >= 256 and w.N >= 256 and -(-w.M // 256) * -(-w.N // 256) >= 128
+    large_tiles = large_tiles and (early or -(-w.M // 128) * -(-w.N // 128) > 512)
     if ops / gemm_bytes >= PEAK_INT8_TOPS * 1e12 / (PEAK_HBM_GBS * 1e9):
         roof = {"bound": "mfma", "achieved": round(achieved, 2), "peak": PEAK_INT8_TOPS, "unit": "TOP/s",
                 "frac": round(achieved / PEAK_INT8_TOPS, 4)}

@@ -23,7 +23,8 @@ static inline bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 #define BBK 128                 // K depth of one staged tile
 #endif
 #define BSTRIDE (BBK + 16)      // padded LDS row stride, conflict-free 16-byte reads
-#define GEMM_MIN_TILES 256
+#define GEMM_MIN_TILES 256      // of the smaller tiles: fewer, and the next smaller size is taken
+#define GEMM_CUS 256            // compute units that one round of workgroups fills
 #define PANEL_LD 40         // row stride of a 32-column chunk of a bfloat16 panel plane (80 bytes: conflict-free 16-byte reads)
 
 // 16 code bytes of one operand row, k .. k+15, zeros past K.  WIDE (K >= 16): one 16-byte load at any byte
@@ -1437,10 +1438,18 @@ int launch_int8_gemm_sums_finish(int M, int N, int K, const int8_t* Aq, const in
     return LRQMM_OK;
 }
 
-// (Measured on both sides of the limit: at 121 tiles of 256 x 256 the 128-tile kernel is as fast, 59 us at
-// 2816^3; at 144 tiles it needs 103 us against 63 us at 3072^3.)
 long long int8_gemm_tiles(int M, int N) { return (long long)ceil_div(M, BTM) * ceil_div(N, BTN); }
-bool int8_gemm_large_tiles(int M, int N) { return M >= BTM && N >= BTN && int8_gemm_tiles(M, N) >= 128; }
+// The large-tile kernel pays from half a round of its tiles on (raw sums, where it is the only one that is asked for)
+bool int8_gemm_large_tiles(int M, int N) { return M >= BTM && N >= BTN && int8_gemm_tiles(M, N) >= GEMM_CUS / 2; }
+// ... and with the result in C where the 128 x 128 tiles would no longer all be resident, two per CU: up to 512 of them those
+// are the faster kernel, from a third round on they are not.  lrqmm_gemm at K = 4096, large / 128 x 128 tiles, us, ranks 0, 16
+// and 40: 483 (2570 x 2830) 57.5 / 49.1, 91.5 / 73.4, 116 / 101; 512 (4096 x 2048) 54.7 / 47.3, 88.8 / 72.0, 114 / 101; 516
+// (33024 x 256) 54.9 / 68.4, 130 / 138, 206 / 223; 528 (2816 x 3072) 54.9 / 64.9, 89.1 / 93.7, 114 / 125; 576 (3072^2) 55.2 /
+// 64.9, 89.1 / 93.5, 113 / 125.  At K = 256 512 tiles 16.6 / 12.3, 43.2 / 32.1, 56.6 / 48.8, 528 16.1 / 16.0, 43.2 / 38.0, 56.8
+// / 58.5.
+static bool large_tiles_into_c(int M, int N) {
+    return int8_gemm_large_tiles(M, N) && (long long)ceil_div(M, 128) * ceil_div(N, 128) > 2 * GEMM_CUS;
+}
 
 // The early-GEMM schedule needs the large-tile kernel and 16-byte accesses to the rows of C.
 bool rank_update_usable(int M, int N, const float* C) {
@@ -1471,10 +1480,10 @@ int launch_int8_terms(int M, int N, int K, const int8_t* const A[2], const float
     if (!int8_terms_usable(M, N, K)) return LRQMM_ERR_UNSUPPORTED;
     TermArgs t = {{A[0], A[1]}, {B[0], B[1]}, {amaxA[0], amaxA[1]}, {amaxB[0], amaxB[1]}};
     const int tiles_n = ceil_div(N, TTN);
-    // 256-row tiles where they fill their last round to 3/4, 256 / 128 rows, us: 2000^3 (0.50) 113 / 99, 2560^3 (0.78) 132 / 142,
+    // 256-row tiles, one per CU, where they fill their last round to 3/4, 256 / 128 rows, us: 2000^3 (0.50) 113 / 99, 2560^3 (0.78) 132 / 142,
     // 3072^3 (0.56) 256 / 234, 3500^3 (0.77) 349 / 381, 4096^3 (1) 377 / 401, 5000^3 (0.78) 895 / 903
     const long long tall_tiles = (long long)ceil_div(M, 256) * tiles_n;
-    const bool tall = 4 * tall_tiles >= 3 * GEMM_MIN_TILES * ((tall_tiles + GEMM_MIN_TILES - 1) / GEMM_MIN_TILES);
+    const bool tall = 4 * tall_tiles >= 3 * GEMM_CUS * ((tall_tiles + GEMM_CUS - 1) / GEMM_CUS);
     const int ttm = tall ? 256 : 128, ntiles = ceil_div(M, ttm) * tiles_n;
     const bool full = aligned16(A[0]) && aligned16(A[1]) && aligned16(B[0]) && aligned16(B[1]) && M % ttm == 0 && N % TTN == 0 && K % BBK == 0;
 #define LRQ_TERMS(WM, FULL)                                                                                                  \
@@ -1513,18 +1522,15 @@ int launch_int8_gemm(int M, int N, int K, const int8_t* Aq, const int8_t* BqT, c
     const bool wide = K >= 16;
     const bool comp = Lp != nullptr;
     // big problems: 256x256 tiles, one workgroup per CU
-    const int btiles = ceil_div(M, BTM) * ceil_div(N, BTN);
-    // (in one launch; raw sums always.  Large / small tiles, us per call: 128 tiles of 256 x 256, 4096 x 2048 x 4096, l = 24 306 /
-    // 291, rank 0 102 / 83; 144, 3072^3, 284 / 289, 87 / 85; 169, 3328^3, 297 / 305, 93 / 93; 196, 3584^3, 300 / 317, 101 / 109)
-    if (int8_gemm_large_tiles(M, N) && wide && (!C.C || btiles >= 136)) {
+    if ((C.C ? large_tiles_into_c(M, N) : int8_gemm_large_tiles(M, N)) && wide) {
+        const int btiles = (int)int8_gemm_tiles(M, N);
         const int btn = ceil_div(N, BTN);
         dim3 bgrid(btiles);
         dispatch_gemm256(comp, Cint != nullptr, bgrid, st, M, N, K, Aq, BqT, sA, sB, Lp, Rp, R2P, C, Cint, btn, btiles, qmaxf);
         LRQ_CHECK_LAUNCH();
         return LRQMM_OK;
     }
-    // Outputs of fewer than 128 tiles of 256 x 256 (int8_gemm_large_tiles): the largest of the smaller tiles of which there
-    // are at least 256, one per CU.  Calls with 128 x 128 tiles throughout / with this rule: 4 tiles of
+    // Smaller outputs: the largest of the smaller tiles of which there are at least 256, one per CU.  Calls with 128 x 128 tiles throughout / with this rule: 4 tiles of
     // 128 x 128 (256^3) 87 / 81 us, 104 (1537 x 1021 x 2311) 279 / 258, 128 (512 x 4096 x 4096 layer) 233 / 222;
     // 256 (2000^3) is the same path.
     // At most 64 columns: 64 rows too, four workgroups per CU (128 x 64 / 64 x 64: 100352 x 64 x 576 213.5 / 208.8 us a call).

@@ -210,8 +210,8 @@ int launch_int8_gemm_sums(int M, int N, int K, const int8_t* Aq, const int8_t* B
                           int32_t* part, hipStream_t st);
 int launch_int8_gemm_sums_finish(int M, int N, int K, const int8_t* Aq, const int8_t* BqT, int32_t* Cint, int resident,
                                  const int32_t* part, hipStream_t st);
-// True when launch_int8_gemm uses the large-tile kernel, which accepts C == null together with
-// Cint != null (raw int32 sums only; sA, sB are then not read).
+// True when the large-tile kernel may be asked for raw int32 sums: launch_int8_gemm with C == null and Cint != null (sA, sB are
+// then not read).  With C given launch_int8_gemm takes it from a few more tiles on (large_tiles_into_c).
 bool int8_gemm_large_tiles(int M, int N);
 long long int8_gemm_tiles(int M, int N);       // of 256 x 256, how many cover the output
 // True when the integer product may run early and launch_rank_update finish the job: the

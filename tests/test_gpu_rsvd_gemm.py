@@ -385,6 +385,14 @@ def test_gemm_wide_panels_on_large_tiles(M, N, K, rank):
     assert np.abs(to_np(D)[rows, :N] - want).max() <= 3 * 2.0 ** -24 * np.abs(want).max() + 2.0 ** -24
 
 
+# Both sides of the limit between the large-tile kernel and 128 x 128 tiles (512 tiles of 128 x 128, two per compute unit), narrow
+# and wide panels, whole tiles and ragged ones; many more rows than columns (few tiles wide) and the reverse.
+@pytest.mark.parametrize("M,N,rank", [(4096, 2048, 20), (4096, 2048, 40), (4096, 2049, 20), (4096, 2049, 40), (2570, 2830, 33),
+                                      (3072, 3072, 33), (3072, 3072, 64), (4096, 2304, 12), (33024, 256, 16), (300, 17500, 33)])
+def test_gemm_on_both_sides_of_the_large_tile_limit(M, N, rank):
+    test_gemm_wide_panels_on_large_tiles(M, N, 144, rank)
+
+
 # The smaller tiles: panels of 8 columns to 160 around the chunks of 32 that the epilogue takes at a time, on each tile shape
 # (64 x 64, 64 x 128, 128 x 128), ragged at every edge, reductions of half a staged tile, one, and one byte more.
 @pytest.mark.parametrize("M,N,K,rank", [(130, 70, 90, 1), (65, 129, 128, 4), (130, 70, 129, 12), (130, 70, 90, 16), (64, 64, 64, 17),
