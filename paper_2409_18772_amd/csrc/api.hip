@@ -255,16 +255,19 @@ bool two_chains(int M, int N, int K) {
 // panel kernels, with the update as a kernel of its own, or with its fused epilogue after the panels.  Early it saves a last
 // round that leaves most CUs idle, and the time of the SVDs where the product is one round and not much longer than they
 // are; it writes and reads C once more, and a long product holds the CUs that the panel kernels need.  Measured, early /
-// fused, us per call (one power iteration): whole rounds, 4096^3 l = 24 374 / 342, 32 386 / 369, 40 423 / 428, 56 530 / 543,
-// 80 665 / 680; 8192 x 4096 x 4096 l = 40 604 / 593, 56 722 / 719,
-// 80 836 / 909; 8192^3 l = 40 1512 / 1463, 56 1684 / 1660, 80 1854 / 1867; 16384^3
-// l = 40 7540 / 7220, 56 7675 / 7230, 80 8232 / 7900.  Rounds filled to 0.56 (3072^3) l = 32 303 / 309; 0.63 (4608^3) l = 24
-// 460 / 458, 32 472 / 487, 40 528 / 565; 0.75 (6144^3) 32 785 / 833; 0.77 (7168^3) 32 1071 / 1117; 0.84 (9216^3) 40 1905 / 1941;
-// 0.88 (7680^3) 40 1341 / 1326; 0.89 (10240^3) 80 2930 / 3050; 0.95 (5632^3) 32 662 / 653.
+// fused, us per call (one power iteration).  Whole rounds: 4096^3 l = 24 363 / 329, 32 375 / 357, 40 414 / 418, 56 527 / 539, 80
+// 659 / 673; two, 8192 x 4096 x 4096, 40 599 / 588, 56 710 / 712, 64 771 / 786, 80 828 / 887; four, 8192^3, 40 1486 / 1442, 56 1681 /
+// 1639, 64 1729 / 1716, 80 1852 / 1854.  Rounds filled to 0.56 (one, 3072^3) 32 304 / 309; 0.63 (two, 4608^3) 24 455 / 453, 32 468 /
+// 485, 40 522 / 560; 0.75 (three, 6144^3) 32 781 / 825; 0.77 (four, 7168^3) 32 1068 / 1109.  From 0.85 on widths up to 48 part with
+// little on either side: 0.88 (three, 6656^3) 32 933 / 933, 48 1040 / 1068, (four, 7680^3) 40 1329 / 1317, 48 1373 / 1378, 0.94 (four,
+// 7936^3) 48 1456 / 1436; wider ones gain, 0.88 7680^3 56 1485 / 1512, 64 1539 / 1603, 0.94 7936^3 56 1587 / 1595, 64 1640 / 1685, 80
+// 1721 / 1815, 0.90 (five, 8704^3) 56 1963 / 1996, 64 2024 / 2124, 80 2142 / 2266, 0.89 (seven, 10240^3) 56 2648 / 2624, 64 2731 / 2774,
+// 80 2869 / 2986.
 bool early_product(long long tiles, int cus, int ell) {
     const long long rounds = (tiles + cus - 1) / cus;
     if (ell < 32) return false;
-    return 100 * tiles <= (ell > 64 ? 90 : 85) * rounds * cus || rounds <= (ell > 64 ? 2 : (ell >= 40 ? 1 : 0));
+    const int fill = ell >= 64 || (ell > 48 && rounds <= 5) ? 95 : 85;
+    return 100 * tiles <= fill * rounds * cus || rounds <= (ell > 64 ? 2 : (ell >= 40 ? 1 : 0));
 }
 
 // int32 accumulation is safe when K * (qmax+1)^2 < 2^31.

@@ -204,6 +204,39 @@ def test_early_product_equals_fused_store_phase_bitwise(K):
     assert torch.equal(D1, D2)
 
 
+def _ran_early(L, call):
+    """Whether the integer product of one profiled call ran early, beside the factorizations."""
+    L.lrqmm_profile_enable(L.PROF_GEMM_ONLY)        # (records the one of the two products that the call takes)
+    try:
+        call()
+        stages, n = L.lrqmm_profile_read()
+    finally:
+        L.lrqmm_profile_enable(False)
+    assert n == 1 and (stages["gemm"] > 0) != (stages["int_gemm"] > 0)
+    return stages["int_gemm"] > 0
+
+
+# Calls that take the early product (256 tiles on a chip of which the two SVD workgroups leave 254 CUs, at 40 columns and more):
+# 8 K tiles in two ranges, 33 in eight uneven ones, panels of 64 columns and of 128; two rounds filled to 0.63 (32 columns); four
+# rounds filled to 0.94 (64 columns).
+@pytest.mark.parametrize("M,N,K,r,p", [(4096, 4096, 1024, 32, 8), (4096, 4096, 4224, 32, 8), (4096, 4096, 1024, 64, 16),
+                                       (4608, 4608, 256, 24, 8), (7936, 7936, 192, 48, 16)])
+def test_early_product_runs_and_equals_the_fused_store_phase_bitwise(M, N, K, r, p):
+    """The dense call takes the early product, the call into a window of a wider array the fused kernel (the stage timer says
+    which ran): the same bits, also for panels of more than 64 columns, which both form from bfloat16 planes."""
+    import torch
+    import paper_2409_18772_amd as L
+    dA, dB = to_dev(wl.random_matrix("normal", M, K, seed=33)), to_dev(wl.random_matrix("normal", K, N, seed=34))
+    say("early and fused", M, N, K, r, p)
+    D1 = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")
+    D2 = torch.full((M, N + 4), SENTINEL, dtype=torch.float32, device="cuda")
+    L.lrqmm_matmul_ex(dA, dB, D1, 4, r, p, 0, seed=5)
+    assert _ran_early(L, lambda: L.lrqmm_matmul_ex(dA, dB, D1, 4, r, p, 0, seed=5))
+    assert not _ran_early(L, lambda: L.lrqmm_matmul_ex(dA, dB, D2[:, :N], 4, r, p, 0, seed=5))
+    assert torch.equal(D1, D2[:, :N])
+    assert torch.all(D2[:, N:] == SENTINEL)
+
+
 @pytest.mark.parametrize("axis", [0, 1])
 @pytest.mark.parametrize("ell,round_mode,rows,cols", [(24, 0, 640, 512), (40, 0, 640, 512), (72, 0, 640, 512),
                                                        (40, 1, 640, 512), (40, 0, 4096, 4096)])
