@@ -62,7 +62,7 @@ extern "C" {
  * cores: as three bfloat16 planes each with the six plane products of weight >= 2^-16 (float32 accuracy),
  * as two planes with three products (relative error of a product 2^-16), or as plain bfloat16 values (2^-8).
  * Quantization, the integer product, the Gram/Cholesky/eigen steps (float64) and the rank-2r update of C
- * (float32) are the same in every mode.  Float32-accurate in every mode are code products over a
+ * (float32 or float32-equivalent, see lrqmm_gemm) are the same in every mode.  Float32-accurate in every mode are code products over a
  * reduction that is no multiple of 16, and the first product of an A with short rows (vector scales, K <= 576
  * and a multiple of 16, 16-byte aligned rows, a sketch of up to 16 columns).  In LRQMM_PREC_FP32 the products of
  * sketches of up to 16 columns run on the float32 matrix cores, except the first one of lrqmm_matmul, which
@@ -135,6 +135,10 @@ LRQMM_API int lrqmm_fill_sketch(uint64_t seed, int stream_id, int rows, int cols
  *          generator (which uses lrqmm_fill_sketch(seed, axis, cols, l)).
  * Outputs: U rows x rank, Sigma[rank] (descending), Vt rank x cols, row-major.
  * Singular vectors are defined up to sign; only U.diag(Sigma).Vt is unique.
+ * The residual products leave about 1e-7 of the largest singular value in B, and the SVD of B is that of
+ * B B^T in float64: a value down to 1e-5 of the largest comes with rows of Vt orthonormal to float32 (2e-7);
+ * further down its direction is known less and less well, and a column of the sketch whose share falls below
+ * 1e-10 (squared) of its own length is dropped (Sigma, U and Vt zero there).
  */
 LRQMM_API int lrqmm_rsvd(const float* X, const float* amax, int rows, int cols, int axis, int bits,
                int round_mode, int rank, int oversample, int power_iters, uint64_t seed,
@@ -159,6 +163,10 @@ LRQMM_API int lrqmm_rsvd_ex(const float* X, int ldx, const float* amax, int rows
  *   U M x rank, Sig[rank], Vt rank x K     factors of R_A
  *   W K x rank, Gam[rank], Zt rank x N     factors of R_B
  *   rank == 0: factor pointers are ignored; plain direct-quantization product.
+ *   The 2 rank products of an entry's compensation are added in float32 on the float32 matrix cores; with 2 rank > 64
+ *   and more than 512 tiles of 128 x 128 in C their operands enter as three bfloat16 planes each, with the six plane
+ *   products of weight >= 2^-16 accumulated in float32 (another rounding order; measured against float64 the error is
+ *   0.65 to 0.85 of the float32 instructions').
  *   C    M x N float32 row-major (output)
  *   Cint_or_null  optional M x N int32 output of the raw integer accumulators.
  * K must satisfy K * (qmax+1)^2 < 2^31.
@@ -222,9 +230,9 @@ LRQMM_API int lrqmm_gemm_static(int M, int N, int K, int bits, int rank,
  * faster schedule, the integer product is enqueued on a third library stream while both
  * factorizations are in their small SVD (the GPU is nearly idle then); it leaves
  * raw int32 sums in C's memory, and the dequantizing rank-2r update runs after the
- * panels as a kernel of its own with the arithmetic of the fused epilogue (same
- * bits for panels of up to 64 columns, 2 rank <= 64; wider panels are accumulated from
- * bfloat16 planes, float32-equivalent but in another rounding order).  C must therefore not be read between the call and its completion on
+ * panels as a kernel of its own with the arithmetic of the fused epilogue: the same bits, but
+ * for panels of more than 64 columns (2 rank > 64) on outputs of up to 512 tiles of 128 x 128,
+ * which the fused product takes on the float32 matrix cores (see lrqmm_gemm).  C must therefore not be read between the call and its completion on
  * `stream`.  Calls must not be issued concurrently from several host threads.
  * The call enqueues only kernels and event waits (memory is cleared by fill kernels), so it may be
  * recorded into a HIP graph by stream capture on `stream`; the library's own streams join the

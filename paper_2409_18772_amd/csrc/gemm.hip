@@ -19,13 +19,12 @@
 
 static inline bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
-#ifndef BBK
 #define BBK 128                 // K depth of one staged tile
-#endif
 #define BSTRIDE (BBK + 16)      // padded LDS row stride, conflict-free 16-byte reads
 #define GEMM_MIN_TILES 256      // of the smaller tiles: fewer, and the next smaller size is taken
 #define GEMM_CUS 256            // compute units that one round of workgroups fills
-#define PANEL_LD 40         // row stride of a 32-column chunk of a bfloat16 panel plane (80 bytes: conflict-free 16-byte reads)
+#define PANEL_KC 32         // panel columns staged at a time as bfloat16 planes
+#define PANEL_LD 40         // row stride of such a chunk of a plane (80 bytes: conflict-free 16-byte reads)
 
 // 16 code bytes of one operand row, k .. k+15, zeros past K.  WIDE (K >= 16): one 16-byte load at any byte
 // alignment (codes are packed rows of K bytes, so an odd K leaves none), branch free with a clamped address; the
@@ -55,6 +54,23 @@ __device__ __forceinline__ float step_of(float amax, float qmaxf) {
     float l, s;
     make_scales(amax, qmaxf, l, s);
     return s;
+}
+
+// Columns c .. c + 7 of a panel row, zeros from R2P on, as three bfloat16 planes to dst, dst + plane and dst + 2 plane.
+__device__ __forceinline__ void stage_planes(const float* __restrict__ row, int c, int R2P, uint16_t* dst, int plane) {
+    float v[8];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int col = c + 4 * h;
+        const bool in = col < R2P;
+        const float4 x = *reinterpret_cast<const float4*>(row + min(col, R2P - 4));
+        v[4 * h + 0] = in ? x.x : 0.f; v[4 * h + 1] = in ? x.y : 0.f;
+        v[4 * h + 2] = in ? x.z : 0.f; v[4 * h + 3] = in ? x.w : 0.f;
+    }
+    const Planes3 pl = split_planes<3>(v);
+    *reinterpret_cast<v8bf16*>(dst) = pl.p1;
+    *reinterpret_cast<v8bf16*>(dst + plane) = pl.p2;
+    *reinterpret_cast<v8bf16*>(dst + 2 * plane) = pl.p3;
 }
 
 // Last step of Algorithm 2 on one element: D <- alpha * value + beta * D (D is not read when
@@ -312,12 +328,8 @@ __global__ __launch_bounds__(256, 2) void int8_gemm_kernel(int M, int N, int K,
 // tile is 128 deep: 144 KB of LDS for the two buffers of both operands.
 #define BTM 256
 #define BTN 256
-#ifndef LRQ_GRING
-#define LRQ_GRING 2             // register sets of global loads in flight (tiles ahead of the matrix cores)
-#endif
 #define BCHUNKS (BBK / 16)      // 16-byte chunks per staged row
 #define BROWS (512 / BCHUNKS)   // rows covered by one pass of the 512 threads
-#define BLOADS (256 / BROWS)    // staged 16-byte chunks per thread and operand
 // FULL: M, N multiples of 256 and K a multiple of the tile depth -- operand loads carry no guard at all, so
 // nothing consumes a loaded register before it is written to LDS two iterations later.
 // SPLITK (raw sums only, FULL shapes): workgroups [0, full_tiles) compute one tile each as usual;
@@ -374,9 +386,10 @@ __global__ __launch_bounds__(512, 1) void int8_gemm256_kernel(int M, int N, int 
     // The register sets are individually named scalars (not arrays passed by reference):
     // that keeps them in VGPRs; as arrays they were demoted to scratch memory.
     // (FULL: one base per operand and wave-uniform row offsets; otherwise a clamped row pointer per load)
-    const int8_t *pa[BLOADS], *pb[BLOADS];
+    static_assert(BTM == 4 * BROWS && BTN == BTM, "four staged chunks per thread and operand");
+    const int8_t *pa[4], *pb[4];
 #pragma unroll
-    for (int u = 0; u < BLOADS; ++u) {
+    for (int u = 0; u < 4; ++u) {
         pa[u] = FULL ? nullptr : code_row(Aq, m0 + srow0 + BROWS * u, M, K);
         pb[u] = FULL ? nullptr : code_row(BqT, n0 + srow0 + BROWS * u, N, K);
     }
@@ -399,21 +412,18 @@ __global__ __launch_bounds__(512, 1) void int8_gemm256_kernel(int M, int N, int 
 #define LRQ_DECL(S) uint4 S##a0, S##a1, S##a2, S##a3, S##b0, S##b1, S##b2, S##b3
 #define LRQ_GLOAD(S, k0)                                                   \
     S##a0 = ldA(0, k0); S##b0 = ldB(0, k0); S##a1 = ldA(1, k0); S##b1 = ldB(1, k0); \
-    if (BLOADS == 4) { S##a2 = ldA(2, k0); S##b2 = ldB(2, k0); S##a3 = ldA(3, k0); S##b3 = ldB(3, k0); }
+    S##a2 = ldA(2, k0); S##b2 = ldB(2, k0); S##a3 = ldA(3, k0); S##b3 = ldB(3, k0);
 #define LRQ_TAIL(R) R = tail16(R, sh)
 #define LRQ_SSTORE(S, buf, k0)                                                     \
     if (!FULL && (k0) + BBK > K) {                                                 \
         const int sh = max(0, (k0) + skc - (K - 16));                              \
         LRQ_TAIL(S##a0); LRQ_TAIL(S##b0); LRQ_TAIL(S##a1); LRQ_TAIL(S##b1);        \
-        if (BLOADS == 4) { LRQ_TAIL(S##a2); LRQ_TAIL(S##b2); LRQ_TAIL(S##a3); LRQ_TAIL(S##b3); } \
+        LRQ_TAIL(S##a2); LRQ_TAIL(S##b2); LRQ_TAIL(S##a3); LRQ_TAIL(S##b3);        \
     }                                                                              \
     stA(0, buf, S##a0); stB(0, buf, S##b0); stA(1, buf, S##a1); stB(1, buf, S##b1); \
-    if (BLOADS == 4) { stA(2, buf, S##a2); stB(2, buf, S##b2); stA(3, buf, S##a3); stB(3, buf, S##b3); }
+    stA(2, buf, S##a2); stB(2, buf, S##b2); stA(3, buf, S##a3); stB(3, buf, S##b3);
     LRQ_DECL(r0);
     LRQ_DECL(r1);
-#if LRQ_GRING == 3
-    LRQ_DECL(r2);
-#endif
     auto compute = [&](int buf) {
 #pragma unroll
         for (int kk = 0; kk < BBK / 32; ++kk) {
@@ -435,32 +445,21 @@ __global__ __launch_bounds__(512, 1) void int8_gemm256_kernel(int M, int N, int 
     };
     LRQ_GLOAD(r0, kt0 * BBK);
     LRQ_GLOAD(r1, (kt0 + 1) * BBK);
-#if LRQ_GRING == 3
-    LRQ_GLOAD(r2, (kt0 + 2) * BBK);
-#endif
     LRQ_SSTORE(r0, 0, kt0 * BBK);
     __syncthreads();
-    // iteration i: the set that held tile i is free -> load tile i + LRQ_GRING; compute tile i; publish tile i+1
+    // iteration i: the set that held tile i is free -> load tile i + 2; compute tile i; publish tile i+1
 #define LRQ_GEMM_STEP(J, SCUR, SNEXT)                  \
     if (kt + J < nk) {                                 \
         const int i = kt + J;                          \
-        LRQ_GLOAD(SCUR, (kt0 + i + LRQ_GRING) * BBK);       \
+        LRQ_GLOAD(SCUR, (kt0 + i + 2) * BBK);       \
         compute(i & 1);                                \
         if (i + 1 < nk) { LRQ_SSTORE(SNEXT, (i + 1) & 1, (kt0 + i + 1) * BBK); } \
         __syncthreads();                               \
     }
-#if LRQ_GRING == 3
-    for (int kt = 0; kt < nk; kt += 3) {
-        LRQ_GEMM_STEP(0, r0, r1)
-        LRQ_GEMM_STEP(1, r1, r2)
-        LRQ_GEMM_STEP(2, r2, r0)
-    }
-#else
     for (int kt = 0; kt < nk; kt += 2) {
         LRQ_GEMM_STEP(0, r0, r1)
         LRQ_GEMM_STEP(1, r1, r0)
     }
-#endif
 #undef LRQ_GEMM_STEP
 #undef LRQ_DECL
 #undef LRQ_GLOAD
@@ -509,7 +508,7 @@ __global__ __launch_bounds__(512, 1) void int8_gemm256_kernel(int M, int N, int 
                 }
             }
         }
-        for (int t0 = 0; t0 < R2P; t0 += 32) {
+        for (int t0 = 0; t0 < R2P; t0 += PANEL_KC) {
             __syncthreads();            // nobody reads the operand tiles, or the previous chunk, any more
             // 2 panels x 256 rows x 4 groups of 8 columns, four units per thread
 #pragma unroll
@@ -518,20 +517,7 @@ __global__ __launch_bounds__(512, 1) void int8_gemm256_kernel(int M, int N, int 
                 const bool left = i < 2;
                 // rows / columns past the end re-read the last one (rows are never stored, columns enter as zeros)
                 const float* src = left ? Lp + (size_t)min(m0 + r, M - 1) * R2P : Rp + (size_t)min(n0 + r, N - 1) * R2P;
-                float v[8];
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const int col = t0 + c8 + 4 * h;
-                    const bool in = col < R2P;
-                    const float4 x = *reinterpret_cast<const float4*>(src + min(col, R2P - 4));
-                    v[4 * h + 0] = in ? x.x : 0.f; v[4 * h + 1] = in ? x.y : 0.f;
-                    v[4 * h + 2] = in ? x.z : 0.f; v[4 * h + 3] = in ? x.w : 0.f;
-                }
-                const Planes3 pl = split_planes<3>(v);
-                uint16_t* dst = (left ? Lq : Rq) + r * PANEL_LD + c8;
-                *reinterpret_cast<v8bf16*>(dst) = pl.p1;
-                *reinterpret_cast<v8bf16*>(dst + PL) = pl.p2;
-                *reinterpret_cast<v8bf16*>(dst + 2 * PL) = pl.p3;
+                stage_planes(src, t0 + c8, R2P, (left ? Lq : Rq) + r * PANEL_LD + c8, PL);
             }
             __syncthreads();
 #pragma unroll
@@ -937,18 +923,16 @@ __global__ __launch_bounds__(256, 2) void rank_update_kernel(int M, int N, float
 // 0.87 ms of matrix-core time at 16384^2 and r = 64).  The panel rows are split into three bfloat16 planes while
 // they are staged in LDS (exact: a float32 is the sum of its three planes) and the six plane products of weight
 // >= 2^-16 run on v_mfma_f32_32x32x16_bf16 with float32 accumulation: 192 instead of 512 matrix-core cycles per
-// 16 panel columns.  Float32-equivalent, but a different rounding order than the float32 instructions: results
-// are not bit-identical to the fused epilogue.  Operand layout (lane l): A[i = l%32][k = 8(l/32) .. +8],
+// 16 panel columns.  The same products in the same order as the large-tile kernel's epilogue (the same bits); the
+// smaller tiles keep the float32 instructions, another rounding order.  Operand layout (lane l): A[i = l%32][k = 8(l/32) .. +8],
 // B[k = 8(l/32) .. +8][j = l%32]; D as for the 32x32 float32 instruction.
-#define RU_KC 32        // panel columns per LDS chunk
-#define RU_LD 40        // plane row stride in bfloat16 (80 bytes: conflict-free 16-byte reads)
 __global__ __launch_bounds__(256, 2) void rank_update_bf16_kernel(int M, int N, float* __restrict__ C,
                                                                   const float* __restrict__ sA,
                                                                   const float* __restrict__ sB,
                                                                   const float* __restrict__ Lp,
                                                                   const float* __restrict__ Rp, int R2P, int tiles_n,
                                                                   float alpha) {
-    __shared__ __align__(16) uint16_t pp[2][3][128 * RU_LD];     // [Lp | Rp][plane][row][column of the chunk]
+    __shared__ __align__(16) uint16_t pp[2][3][128 * PANEL_LD];     // [Lp | Rp][plane][row][column of the chunk]
     const int m0 = (blockIdx.x / tiles_n) * 128, n0 = (blockIdx.x % tiles_n) * 128;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int wm = wave >> 1, wn = wave & 1;
@@ -997,7 +981,7 @@ __global__ __launch_bounds__(256, 2) void rank_update_bf16_kernel(int M, int N, 
                     f[mt][nt][4 * g + 3] = ((float)raw[mt][nt][g].w * sa[mt]) * sb[nt][g].w;
                 }
     }
-    for (int t0 = 0; t0 < R2P; t0 += RU_KC) {       // R2P % 8 == 0
+    for (int t0 = 0; t0 < R2P; t0 += PANEL_KC) {       // R2P % 8 == 0
         if (t0 > 0) __syncthreads();                // the previous chunk is no longer read
         // 2 panels x 128 rows x 4 groups of 8 columns = 1024 units, four per thread: load, split, store the planes
 #pragma unroll
@@ -1005,28 +989,16 @@ __global__ __launch_bounds__(256, 2) void rank_update_bf16_kernel(int M, int N, 
             const int unit = threadIdx.x + 256 * i;
             const int pnl = unit >> 9, r = (unit >> 2) & 127, c8 = (unit & 3) * 8;
             const float* src = pnl == 0 ? Lp + (size_t)min(m0 + r, M - 1) * R2P : Rp + (size_t)min(n0 + r, N - 1) * R2P;
-            float v[8];
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {           // rows / columns past the end re-read the last one (never stored)
-                const int col = t0 + c8 + 4 * h;
-                const bool in = col < R2P;          // panel columns past R2P enter as zeros
-                const float4 x = *reinterpret_cast<const float4*>(src + min(col, R2P - 4));
-                v[4 * h + 0] = in ? x.x : 0.f; v[4 * h + 1] = in ? x.y : 0.f;
-                v[4 * h + 2] = in ? x.z : 0.f; v[4 * h + 3] = in ? x.w : 0.f;
-            }
-            const Planes3 pl = split_planes<3>(v);
-            *reinterpret_cast<v8bf16*>(&pp[pnl][0][r * RU_LD + c8]) = pl.p1;
-            *reinterpret_cast<v8bf16*>(&pp[pnl][1][r * RU_LD + c8]) = pl.p2;
-            *reinterpret_cast<v8bf16*>(&pp[pnl][2][r * RU_LD + c8]) = pl.p3;
+            stage_planes(src, t0 + c8, R2P, &pp[pnl][0][r * PANEL_LD + c8], 128 * PANEL_LD);     // (rows past the end: the last one again)
         }
         __syncthreads();
 #pragma unroll
-        for (int u = 0; u < RU_KC / 16; ++u) {
+        for (int u = 0; u < PANEL_KC / 16; ++u) {
             Planes3 a[2], b[2];     // a: Lp rows of the two row tiles (B operand), b: Rp rows of the two column tiles (A operand)
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
-                const int oa = (wm * 64 + t * 32 + l32) * RU_LD + 16 * u + 8 * lh;
-                const int ob = (wn * 64 + t * 32 + l32) * RU_LD + 16 * u + 8 * lh;
+                const int oa = (wm * 64 + t * 32 + l32) * PANEL_LD + 16 * u + 8 * lh;
+                const int ob = (wn * 64 + t * 32 + l32) * PANEL_LD + 16 * u + 8 * lh;
                 a[t].p1 = *reinterpret_cast<const v8bf16*>(&pp[0][0][oa]);
                 a[t].p2 = *reinterpret_cast<const v8bf16*>(&pp[0][1][oa]);
                 a[t].p3 = *reinterpret_cast<const v8bf16*>(&pp[0][2][oa]);

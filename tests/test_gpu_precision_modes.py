@@ -96,3 +96,32 @@ def test_reduced_precision_rsvd(axis):
         assert abs(energy - 1) < max(1e-5, EPS[mode])
         assert resid < 1 + max(1e-4, 4 * EPS[mode])
         assert np.abs(u.T @ u - np.eye(r)).max() < 2e-5       # orthonormalization is float64 in every mode
+
+
+# Untruncated sketches of up to 16 columns, whose factors are Q and Q^T R with Sigma = 1 (no small SVD): these are what the
+# reduced modes round.  One and two power iterations and none, both scale granularities and rounding modes, an update of a window.
+@pytest.mark.parametrize("M,N,K,r,q,bits,tensor,nearest,alpha,beta", [(300, 200, 400, 8, 0, 4, False, False, 1.0, 0.0),
+                                                                      (333, 517, 260, 16, 1, 4, True, False, 0.75, 0.5),
+                                                                      (700, 130, 515, 3, 1, 8, False, True, 1.0, 0.0),
+                                                                      (9000, 64, 576, 8, 0, 4, False, False, 1.5, -0.5),
+                                                                      (640, 512, 768, 15, 2, 8, True, False, 1.0, 0.0)])
+def test_reduced_precision_untruncated_narrow_sketch(M, N, K, r, q, bits, tensor, nearest, alpha, beta):
+    """Bound: as above on alpha C_F; the update adds one rounding of |beta D| and one of the sum (2^-23 of each)."""
+    import torch
+    import paper_2409_18772_amd as L
+    A, B = wl.random_matrix("normal", M, K, seed=81), wl.random_matrix("normal", K, N, seed=82)
+    D0 = wl.random_matrix("normal", M, N, seed=83)
+    rm, sm = (L.ROUND_NEAREST if nearest else L.ROUND_FLOOR), (L.SCALE_TENSOR if tensor else L.SCALE_VECTOR)
+    ref = o.lrqmm(A, B, bits, r, 0, q, seed=9, round_mode=o.NEAREST if nearest else o.FLOOR, per_tensor=tensor)
+    kappa = (np.linalg.norm(ref["C0"]) + np.linalg.norm(ref["C"] - ref["C0"])) / np.linalg.norm(ref["C"])
+    want = alpha * ref["C"] + beta * D0
+    dA, dB = to_dev(A), to_dev(B)
+    for mode in (L.PREC_FP32, L.PREC_SUBSPACE_BF16X2, L.PREC_BF16X2, L.PREC_BF16):
+        D = torch.empty((M, N + 3), dtype=torch.float32, device="cuda")[:, :N]
+        D.copy_(to_dev(D0))
+        L.lrqmm_matmul_ex(dA, dB, D, bits, r, 0, q, seed=9, round_mode=rm, scale_mode=sm, alpha=alpha, beta=beta, precision=mode)
+        err = np.linalg.norm(to_np(D).astype(np.float64) - want)
+        bound = (4 * EPS[mode] * kappa / np.sqrt(min(M, N, K)) + tol_for(ref)) * abs(alpha) * np.linalg.norm(ref["C"]) \
+            + 2.0 ** -23 * (np.linalg.norm(beta * D0) + np.linalg.norm(want))
+        say("untruncated", M, N, K, r, "mode", mode, "err", err, "bound", bound)
+        assert err < bound

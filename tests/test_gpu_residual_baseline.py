@@ -120,13 +120,15 @@ def test_bad_terms_rejected():
     assert torch.all(D == 0)
 
 
-# One launch for all products: both tile heights (256 rows in the second and the last four shapes), whole tiles, ragged ones, reductions that end
-# at, before and behind a 128-deep tile and at the shortest one it takes, outputs smaller than a tile; the two loop parities of
-# a product (odd and even tile counts).
+# One launch for all products: both tile heights (256 rows where such tiles fill their last round to three quarters: 4096^2,
+# 3500^2 and 2049 x 2817), whole tiles, ragged ones, reductions that end at, before and behind a 128-deep tile and at the
+# shortest one it takes, outputs smaller than a tile; the two loop parities of a product (odd and even tile counts).
 @pytest.mark.parametrize("M,N,K,pad,alpha,beta", [(3072, 3072, 256, 0, 1.0, 0.0), (4096, 4096, 384, 0, 0.75, 0.5),
                                                   (33, 20, 17, 1, 1.0, 0.0), (130, 257, 640, 0, 0.5, 0.5), (256, 128, 128, 0, 1.0, 0.0),
                                                   (2817, 2820, 143, 3, 1.5, -0.5), (2900, 2819, 16, 1, 1.0, 0.0),
-                                                  (2830, 2840, 129, 0, -1.0, 1.0), (2819, 2900, 513, 5, 1.0, 0.25)])
+                                                  (2830, 2840, 129, 0, -1.0, 1.0), (2819, 2900, 513, 5, 1.0, 0.25),
+                                                  (3500, 3500, 16, 4, 1.0, 0.0), (2049, 2817, 129, 3, 0.75, 0.5), (3500, 3500, 143, 1, 1.0, 0.0),
+                                                  (2049, 2817, 513, 0, -1.0, 0.25)])
 @pytest.mark.parametrize("terms", [3, 4])
 def test_residual_products_in_one_launch(M, N, K, pad, alpha, beta, terms):
     """The same operations in the same order as one call per product that updates D: the same values."""

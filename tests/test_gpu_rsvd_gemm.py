@@ -270,7 +270,7 @@ GEMM_CASES = [
     (64, 640, 576, 4, 8),
     (500, 300, 77, 8, 3),       # K not a multiple of 16: byte-wise operand path
     (384, 512, 2048, 4, 32),
-    (1000, 64, 576, 4, 8),      # at most 64 columns: the 128 x 64 tile
+    (1000, 64, 576, 4, 8),      # at most 64 columns: 64 x 64 tiles
     (300, 40, 100, 8, 4),       # ... ragged, byte-wise operand path
     (257, 65, 128, 4, 0),       # one column more: back to the 128-wide tile
 ]
@@ -312,7 +312,7 @@ def test_gemm_int_exact_and_compensation(M, N, K, bits, rank):
 # tiles of the smaller kernel.
 @pytest.mark.parametrize("M,N,K,rank", [(70, 90, k, min(k, 5)) for k in (1, 3, 15, 16, 17, 31, 63, 65, 127, 129, 271)]
                          + [(600, 33, 641, 7), (2817, 2820, 143, 0), (150, 70, 1301, 20),
-                            # enough tiles for 128 x 128, 64 x 128 and 128 x 64 ones
+                            # enough tiles for 128 x 128, 64 x 128 and (at most 64 columns) 64 x 64 ones
                             (2100, 2050, 65, 4), (1029, 2045, 70, 3), (32800, 40, 37, 2)])
 def test_gemm_reduction_tails(M, N, K, rank):
     test_gemm_int_exact_and_compensation(M, N, K, 8, rank)

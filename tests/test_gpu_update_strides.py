@@ -144,12 +144,12 @@ def test_gemm_ex_with_factors_and_int_output():
     assert np.all(to_np(bigD)[:, N:] == SENTINEL)
 
 
-@pytest.mark.parametrize("alpha,beta,pad_d", [(1.5, 0.0, 0), (1.5, -0.5, 4)])
-def test_large_tile_paths_sampled_rows(alpha, beta, pad_d):
-    """Sizes on the large-tile kernel: beta = 0 on a dense D takes the early-product schedule (alpha is
-    applied by the update kernel), any other case the fused store phase."""
+@pytest.mark.parametrize("alpha,beta,pad_d,N", [(1.5, 0.0, 0, 2048), (1.5, -0.5, 4, 2048), (1.5, 0.0, 0, 2304), (1.5, -0.5, 4, 2304)])
+def test_large_tile_paths_sampled_rows(alpha, beta, pad_d, N):
+    """beta = 0 on a dense D takes the early-product schedule (large tiles; alpha is applied by the update kernel), any other
+    case the fused store phase: of the 128 x 128 tiles at N = 2048 (512 of them), of the large ones at 2304."""
     import paper_2409_18772_amd as L
-    M, N, K, bits, r, p, q = 4096, 2048, 512, 4, 28, 4, 1
+    M, K, bits, r, p, q = 4096, 512, 4, 28, 4, 1
     A = wl.random_matrix("normal", M, K, seed=12)
     B = wl.random_matrix("normal", K, N, seed=13)
     D0 = wl.random_matrix("normal", M, N, seed=14)
@@ -184,9 +184,8 @@ def test_bad_strides_are_rejected():
 
 @pytest.mark.parametrize("K", [512, 2112])
 def test_early_product_equals_fused_store_phase_bitwise(K):
-    """256 tiles on a chip whose two SVD workgroups leave 254 CUs: the early integer product cuts its last
-    tiles along K (evenly at K = 512, unevenly at 33 K-tiles) and sums them with integer atomics.  The dense
-    call takes that schedule, the call into a window of a wider array the fused kernel: same bits."""
+    """A dense call and one into a window of a wider array: the same bits.  (At 32 columns 256 tiles are a whole round, and both
+    calls take the fused kernel; calls that run early are in the next test.)"""
     import torch
     import paper_2409_18772_amd as L
     M = N = 4096
@@ -218,9 +217,9 @@ def _ran_early(L, call):
 
 # Calls that take the early product (256 tiles on a chip of which the two SVD workgroups leave 254 CUs, at 40 columns and more):
 # 8 K tiles in two ranges, 33 in eight uneven ones, panels of 64 columns and of 128; two rounds filled to 0.63 (32 columns); four
-# rounds filled to 0.94 (64 columns).
+# rounds filled to 0.94 (64 columns); half a round, where the fused kernel is that of the 128 x 128 tiles (panels of 48 columns).
 @pytest.mark.parametrize("M,N,K,r,p", [(4096, 4096, 1024, 32, 8), (4096, 4096, 4224, 32, 8), (4096, 4096, 1024, 64, 16),
-                                       (4608, 4608, 256, 24, 8), (7936, 7936, 192, 48, 16)])
+                                       (4608, 4608, 256, 24, 8), (7936, 7936, 192, 48, 16), (4096, 2048, 512, 24, 8)])
 def test_early_product_runs_and_equals_the_fused_store_phase_bitwise(M, N, K, r, p):
     """The dense call takes the early product, the call into a window of a wider array the fused kernel (the stage timer says
     which ran): the same bits, also for panels of more than 64 columns, which both form from bfloat16 planes."""
