@@ -587,7 +587,8 @@ struct SvdTask {
 //   2. Eigenvalues by multisection, four waves: every lane counts the eigenvalues below two points of its own (Sturm
 //      sequence of the leading minors, rescaled every eighth row: one dependent FMA per row; the rows of T in registers up
 //      to 40 columns), and ballots narrow all intervals by a factor 2 GL + 1 per round, to 2^-49 of the norm, and two rounds
-//      further where an eigenvalue is small.
+//      further where an eigenvalue is small or two are close (a flat tail at 1e-2 of the top, whose vectors else failed the
+//      check below: 24 columns 139 / 111 us per factorization, 80 columns 635 / 346).
 //   3. Eigenvectors of the tridiagonal matrix by twisted factorization, one lane per vector: the LDU sweep from the top in
 //      one wave, the one from the bottom in another; they meet at the index where the residual is smallest.
 //   4. Back transformation by the Householder vectors, eight lanes per vector, no barrier.
@@ -953,8 +954,13 @@ __device__ __forceinline__ bool tridiagonal_svd(const SvdJob& job, int ell, int 
         double lo = -1e-6, hi = 1.0;
         if (wave * per < rank)
         for (int r = 0; r < rounds + 2; ++r) {
-            // two more where an eigenvalue is far below the largest: V = B^T U' / sigma needs it relative to itself
-            if (r >= rounds && !(__ballot(hi - lo > 1e-11 * hi) & live)) break;
+            // two more where an eigenvalue is far below the largest (V = B^T U' / sigma needs it relative to itself) or close to
+            // the next one (whose vectors are then only as orthogonal as the two are apart)
+            if (r >= rounds) {
+                const double next = __shfl(hi, min(lane + GL, 63), 64);
+                const bool close = grp + 1 < per && t + 1 < rank && hi - lo > 1e-6 * (lo - next);
+                if (!(__ballot(close || hi - lo > 1e-11 * hi) & live)) break;
+            }
             const double h = (hi - lo) * step;
             const double xa = fma(h, g + 1.0, lo), xb = fma(h, (double)(g + 1 + GL), lo);
             // leading minors p_i of T - x I, scaled: the number of sign changes is the number of eigenvalues below x

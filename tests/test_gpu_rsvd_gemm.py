@@ -173,6 +173,24 @@ def test_rsvd_flat_tail_far_below_the_top(flat, k, ell):
     assert np.linalg.norm((U * S) @ Vt - R) <= 1e-5 * np.linalg.norm(R)
 
 
+@pytest.mark.parametrize("ell", [8, 20, 24, 31, 40, 48, 64, 80])
+def test_rsvd_flat_tail_orthonormal_factors(ell):
+    """Three large singular values and a flat tail at 1e-2 of the largest: the tail's eigenvalues (1e-4 of the norm) differ by
+    the float32 products' noise, about 1e-11 of the norm.  Factors orthonormal to float32 (bound as below)."""
+    rng = np.random.default_rng(ell)
+    u, _ = np.linalg.qr(rng.standard_normal((260, ell)))
+    v, _ = np.linalg.qr(rng.standard_normal((300, ell)))
+    s = np.full(ell, 1e-2)
+    s[:3] = (1.0, 0.8, 0.6)
+    R = (u * s) @ v.T
+    R = (R * (0.4 / np.abs(R).max())).astype(np.float32)
+    U, S, Vt = _whole_rsvd_of(R, ell)
+    say("flat tail", ell, np.max(np.abs(Vt @ Vt.T - np.eye(ell))))
+    assert np.max(np.abs(U.T @ U - np.eye(ell))) < 2e-7
+    assert np.max(np.abs(Vt @ Vt.T - np.eye(ell))) < 2e-7
+    assert np.linalg.norm((U * S) @ Vt - R) <= 1e-5 * np.linalg.norm(R)
+
+
 @pytest.mark.parametrize("shape", ["dense", "rows"])
 @pytest.mark.parametrize("ell", [5, 8, 16, 17, 24, 31, 32, 40, 48, 64, 80])
 def test_rsvd_steep_spectrum(ell, shape):
