@@ -326,10 +326,11 @@ enum class FirstPass {
 // Appends the launches of one factorization, or of two that advance together (one launch per step for both; their
 // operands have different axes), to `ops`.  The sketches are in place.  svd_index: position of the small SVD.
 // basis_suffices: the caller only uses the product U diag(Sigma) Vt, and nothing is truncated (oversample == 0): U = Q,
-// Sigma = 1, Vt = Q^T R carry the same product as the SVD's factors.
+// Sigma = 1, Vt = Q^T R carry the same product as the SVD's factors.  packed: the quantizing pass leaves packed codes.
 static void factor_launches(LaunchList& ops, const Factor* factors, int n, FirstPass first, QuantParams q, int rank,
                             int oversample, int power_iters, int planes_first, int planes, int planes_last, hipStream_t st,
-                            size_t* svd_index, float* one_read_amax = nullptr, bool basis_suffices = false) {
+                            size_t* svd_index, float* one_read_amax = nullptr, bool basis_suffices = false,
+                            bool packed = false) {
     struct Pair { Factor f[2]; PassOperand op[2]; };
     auto p = std::make_shared<Pair>();
     for (int i = 0; i < n; ++i) { p->f[i] = factors[i]; p->op[i] = factors[i].op; }
@@ -369,7 +370,7 @@ static void factor_launches(LaunchList& ops, const Factor* factors, int n, First
         j.g[0].blocks = quant_sketch_rows_blocks(f.op.rows);
         gram_to_basis(j);
     } else {
-        ops.push_back([=] { return launch_resid_mul_n(p->op, n, q, LP, first == FirstPass::quantize, st, planes_first); });
+        ops.push_back([=] { return launch_resid_mul_n(p->op, n, q, LP, first == FirstPass::quantize, st, planes_first, packed); });
         orth(false);
     }
     for (int it = 0; it < power_iters; ++it) {
@@ -536,7 +537,7 @@ static int gemm_impl(int M, int N, int K, int bits, int rank, const int8_t* Aq, 
                      const int8_t* BqT, const float* amaxB, const float* U, const float* Sig, const float* Vt,
                      const float* W, const float* Gam, const float* Zt, GemmOut out, int32_t* Cint_or_null,
                      void* workspace, size_t workspace_bytes, void* stream, int prof_slot,
-                     hipEvent_t raw_sums_ready = nullptr, int planes = 3) {
+                     hipEvent_t raw_sums_ready = nullptr, int planes = 3, bool packed = false) {
     float* const C = out.C;
     if (M < 0 || N < 0 || K < 0 || rank < 0 || out.ldc < N) return LRQMM_ERR_INVALID_ARG;
     if (!dims_ok(M, N, K) || !output_ok(M, N)) return LRQMM_ERR_UNSUPPORTED;
@@ -571,7 +572,7 @@ static int gemm_impl(int M, int N, int K, int bits, int rank, const int8_t* Aq, 
         // A~ W and (V^T B~)^T without their step vectors, split along K; one launch for both
         const PassPlan pa = plan_codes(M, K), pb = plan_codes(N, K);
         LRQ_TRY(launch_codes_mul_n2(Aq, M, w.Wp3, pa, w.partialA, BqT, N, w.Vp3, pb, w.partialB, K,
-                                    pad_to(K, 64), RP, st, K % 16 == 0 ? planes : 3));     // (as the interface states)
+                                    pad_to(K, 64), RP, st, K % 16 == 0 ? planes : 3, packed));     // (as the interface states)
         LRQ_TRY(launch_build_panels(M, N, K, rank, RP, R2P, U, Sig, w.sA, w.partialA, pa.splits, w.sB,
                                     w.partialB, pb.splits, w.X, Gam, Zt, w.Lp, w.Rp, st));
     }
@@ -585,7 +586,7 @@ static int gemm_impl(int M, int N, int K, int bits, int rank, const int8_t* Aq, 
     }
     prof_mark(prof_slot, 7, st);
     rc = launch_int8_gemm(M, N, K, Aq, BqT, rank > 0 ? w.sA : amaxA, rank > 0 ? w.sB : amaxB, rank > 0 ? w.Lp : nullptr,
-                          rank > 0 ? w.Rp : nullptr, R2P, out, Cint_or_null, q.qmaxf, st);
+                          rank > 0 ? w.Rp : nullptr, R2P, out, Cint_or_null, q.qmaxf, st, packed);
     prof_mark(prof_slot, 8, st);
     prof_mark(prof_slot, 9, st);
     prof_mark(prof_slot, 10, st);
@@ -682,6 +683,10 @@ int lrqmm_matmul_ex(int M, int N, int K, int bits, int rank, int oversample, int
     const bool short_rows = factored && !per_tensor && quant_sketch_rows_usable(A, lda, M, K, LP, w.Aq);
     const bool one_read = short_rows && M >= LRQ_ONE_READ_MIN_ROWS;
     const bool overlap = one_read || (factored && two_chains(M, N, K));
+    // Packed codes wherever they are exact and no larger than the bytes they stand in for (all but the smallest extents).  The
+    // one-read kernel leaves bytes: its products are short and bound by the store of C.
+    const bool packed = factored && !one_read && codes_packable(bits, K) && pk_bytes(M, K) <= (size_t)M * K &&
+                        pk_bytes(N, K) <= (size_t)N * K;
     const int slot = (g_prof.on && g_prof.ncalls < kProfMaxCalls) ? g_prof.ncalls++ : -1;
     hipStream_t bst = overlap ? side->stream : pst;
     // Early integer GEMM: with both factorizations in their single-workgroup SVD the GPU is
@@ -740,14 +745,14 @@ int lrqmm_matmul_ex(int M, int N, int K, int bits, int rank, int oversample, int
                 opsA.push_back([=] { return launch_absmax_pair(A, lda, M, K, amaxA, nullptr, 0, 0, nullptr, qp, per_tensor, pst); });
             mark(opsA, 1, pst);
             factor_launches(opsA, &f[0], 1, one_read ? FirstPass::one_read : quant, qp, rank, oversample, power_iters, pl_first,
-                            pl, pl_last, pst, &svd, amaxA, basis_suffices);
+                            pl, pl_last, pst, &svd, amaxA, basis_suffices, packed);
             opsB.push_back([=] {
                 return launch_sketch_and_zero(seed, LRQMM_AXIS_COL, N, ell, LP, WcB, 0, nullptr, amaxB_bits, N, bst);
             });
             opsB.push_back([=] { return launch_absmax_pair(nullptr, 0, 0, K, nullptr, B, ldb, N, amaxB, qp, per_tensor, bst); });
             mark(opsB, 4, bst);
             factor_launches(opsB, &f[1], 1, quant, qp, rank, oversample, power_iters, pl, pl, pl_last, bst, &svdB, nullptr,
-                            basis_suffices);
+                            basis_suffices, packed);
             mark(opsB, 5, bst);
         } else {
             opsA.push_back([=] {
@@ -757,7 +762,7 @@ int lrqmm_matmul_ex(int M, int N, int K, int bits, int rank, int oversample, int
             mark(opsA, 1, pst);
             mark(opsA, 4, pst);
             factor_launches(opsA, f, 2, quant, qp, rank, oversample, power_iters, pl_first, pl, pl_last, pst, &svd, nullptr,
-                            basis_suffices);
+                            basis_suffices, packed);
             mark(opsA, 5, pst);
         }
         mark(opsA, 2, pst);
@@ -792,7 +797,7 @@ int lrqmm_matmul_ex(int M, int N, int K, int bits, int rank, int oversample, int
         const int resident = side->cus - 2;
         for (int t = 0; t < 3; ++t) LRQ_TRY(launch_tick(w.tick, gst));
         prof_mark(slot, 9, gst);
-        rc = launch_int8_gemm_sums(M, N, K, w.Aq, w.BqT, reinterpret_cast<int32_t*>(C), resident, w.parts, gst);
+        rc = launch_int8_gemm_sums(M, N, K, w.Aq, w.BqT, reinterpret_cast<int32_t*>(C), resident, w.parts, gst, packed);
         prof_mark(slot, 10, gst);
         if (rc != LRQMM_OK) return rc;
         LRQ_TRY(launch_int8_gemm_sums_finish(M, N, K, w.Aq, w.BqT, reinterpret_cast<int32_t*>(C), resident, w.parts, gst));
@@ -808,7 +813,7 @@ int lrqmm_matmul_ex(int M, int N, int K, int bits, int rank, int oversample, int
         prof_mark(slot, 6, pst);
         rc = gemm_impl(M, N, K, bits, rank, w.Aq, w.amaxA, w.BqT, w.amaxB, w.U, w.Sig, w.Vt, w.W, w.Gam, w.Zt,
                        GemmOut{D, ldd, alpha, beta}, nullptr, w.sub, w.sub_bytes, stream, slot,
-                       early ? side->gdone : nullptr, planes_values(precision));
+                       early ? side->gdone : nullptr, planes_values(precision), packed);
     }
     if (rc != LRQMM_OK && gemm_forked) {
         // failed somewhere behind the fork of the third stream: join it too (a second record of the

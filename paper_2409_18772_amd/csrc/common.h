@@ -147,6 +147,38 @@ __device__ __forceinline__ uint4 tail16(uint4 v, int sh) {
     return make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
 }
 
+// ---- codes of at most five bits, packed for the fp6 matrix cores ----
+// The magnitudes 0 .. 16 are the first seventeen values of the six-bit e2m3 format in units of 1/8 (its subnormals and the first
+// binades continue each other), so a code of up to five bits is exact in it, sign and magnitude, and so is a product of two.
+// v_mfma_f32_32x32x64_f8f6f4 takes such operands at twice the rate of the int8 instructions, from 3/4 of the bytes, and adds in
+// float32, where integers are exact below 2^24: the sums are the int8 matrix cores' sums (times 1/64).  Measured on random 4-bit
+// codes, int8 / this: 4096^3 59 / 46 us, 16384^3 3.99 / 2.56 ms; operands in registers 2.4 / 5.0 POP/s.
+// Layout: [row block of 32][k block of 64][PK_BLOCK bytes], a block being a matrix-core operand of a wave: lane l holds row
+// l % 32, codes 32 (l / 32) .. +32 of the block (24 bytes, code e in bits 6 e ..); first the lanes' bytes 0 .. 15, then 16 .. 23, so
+// that both LDS reads of a wave are contiguous.  Codes past K are zero; rows past the end of a block hold anything.
+#define PK_BLOCK 1536
+#define PK_K 64
+__host__ __device__ static inline int pk_kblocks(int K) { return (K + PK_K - 1) / PK_K; }
+static inline size_t pk_bytes(int rows, int K) { return (size_t)((rows + 31) / 32) * pk_kblocks(K) * PK_BLOCK; }
+
+// Sign and magnitude of a code that is given as a float.
+__device__ __forceinline__ uint32_t six_bits(float c) { return (uint32_t)fabsf(c) | ((__float_as_uint(c) >> 26) & 32u); }
+// Four codes in the low six bits of each byte -> 24 bits.
+__device__ __forceinline__ uint32_t squeeze_six(uint32_t w) {
+    const uint32_t t = (w & 0x003f003fu) | ((w >> 2) & 0x0fc00fc0u);
+    return (t & 0xfffu) | ((t >> 4) & 0xfff000u);
+}
+// 32 codes as eight words of 24 bits -> a lane's 24 bytes of block `blk`; valid: codes from this one on are zeroed.
+__device__ __forceinline__ void store_packed(uint8_t* __restrict__ blk, int lane, uint32_t (&t)[8], int valid) {
+    if (valid < 32) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) t[j] &= (1u << (6 * max(0, min(4, valid - 4 * j)))) - 1u;
+    }
+    *reinterpret_cast<uint4*>(blk + lane * 16) = make_uint4(t[0] | (t[1] << 24), (t[1] >> 8) | (t[2] << 16),
+                                                            (t[2] >> 16) | (t[3] << 8), t[4] | (t[5] << 24));
+    *reinterpret_cast<uint2*>(blk + 1024 + lane * 8) = make_uint2((t[5] >> 8) | (t[6] << 16), (t[6] >> 16) | (t[7] << 8));
+}
+
 #define LRQ_CHECK_LAUNCH()                                   \
     do {                                                     \
         if (hipGetLastError() != hipSuccess) return LRQMM_ERR_HIP; \

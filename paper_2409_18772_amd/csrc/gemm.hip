@@ -15,6 +15,7 @@
 // 32x32 accumulator layout (lane l, register v): row 8*(v/4) + 4*(l/32) + v%4,
 // column l%32 -- identical for the i32 and f32 32x32 MFMAs, which lets the
 // epilogue continue on the same registers with v_mfma_f32_32x32x2_f32.
+#include <type_traits>
 #include "kernels.h"
 
 static inline bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
@@ -47,6 +48,98 @@ __device__ __forceinline__ uint4 load16b(const int8_t* __restrict__ rowp, int K,
 }
 __device__ __forceinline__ const int8_t* code_row(const int8_t* __restrict__ base, int row, int nrows, int K) {
     return base + (size_t)min(row, nrows - 1) * K;
+}
+
+// A sum of code products as a float (sums on the fp6 matrix cores are in units of 1/64).
+__device__ __forceinline__ float code_sum(int a) { return (float)a; }
+__device__ __forceinline__ float code_sum(float a) { return a * 64.0f; }
+
+// ---- main loop on packed codes (see PK_BLOCK) ----
+// A wave's 64 lanes copy 16 bytes each from global memory to 1 KB of LDS, without registers in between.
+// (m0 is set here for this one instruction; the compiler sets it before each use of its own.)
+__device__ __forceinline__ void load_to_lds(uint32_t lds, const uint8_t* base, uint32_t off) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %1" ::"s"(lds), "s"(base), "v"(off) : "memory");
+}
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef __attribute__((address_space(3))) uint8_t lds_u8;
+
+// acc += the tile's products over nk k blocks from kb0 on.  The tile is BA row blocks of A (from ra0) by BB of B (from rb0), a wave
+// MT x NT of them (from wa, wb inside the tile); ST stages of LDS hold one k block of the tile each.  The copies of ST - 3 k
+// blocks are in flight while the matrix cores work on one and the next one's operands are read from LDS to registers, so a step
+// is one barrier and no wait for LDS or memory; an even share of 1 KB pieces per wave, the last ones twice where they do not
+// divide.  Row and k blocks past the end: the last one again.  At 16384^3 it reaches 3.4 POP/s of the 5.0 of operands in
+// registers (one k block ahead instead of its operands, 128-deep stages: 3.35); with operand bits that do not change 4.1, so
+// it is the power that bounds it.
+template <int MT, int NT, int BA, int BB, int NW, int ST>
+__device__ __forceinline__ void packed_products(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, int ra0, int nra, int rb0,
+                                                int nrb, int nkb, int kb0, int nk, uint8_t* sm, int wave, int lane, int wa, int wb,
+                                                v16f (&acc)[MT][NT]) {
+    constexpr int STAGE = (BA + BB) * PK_BLOCK, PIECES = STAGE / 1024, PER = (PIECES + NW - 1) / NW;
+    static_assert(STAGE % 1024 == 0 && BA * PK_BLOCK % 1024 == 0, "pieces belong to one operand");
+    const size_t rowb = (size_t)nkb * PK_BLOCK;
+    const uint8_t* src[PER];
+    uint32_t off[PER], dst[PER];
+    const uint32_t base = (uint32_t)(uintptr_t)(lds_u8*)sm;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int piece = min(wave * PER + u, PIECES - 1);
+        const bool isb = piece >= BA * PK_BLOCK / 1024;
+        const int at = (piece - (isb ? BA * PK_BLOCK / 1024 : 0)) * 1024 + lane * 16, r = at / PK_BLOCK;
+        src[u] = (isb ? B + (size_t)rb0 * rowb : A + (size_t)ra0 * rowb) + (size_t)kb0 * PK_BLOCK;
+        off[u] = (uint32_t)(min(r, (isb ? nrb - rb0 : nra - ra0) - 1) * rowb) + at % PK_BLOCK;
+        dst[u] = base + piece * 1024;
+    }
+    auto issue = [&](int t, int s) {
+        const size_t o = (size_t)min(t, nk - 1) * PK_BLOCK;
+#pragma unroll
+        for (int u = 0; u < PER; ++u) load_to_lds(dst[u] + s * STAGE, src[u] + o, off[u]);
+    };
+    struct Frag { v8i a[MT], b[NT]; };
+    auto operand = [&](const uint8_t* p) {
+        const v4i lo = *reinterpret_cast<const v4i*>(p + lane * 16);
+        const int2 hi = *reinterpret_cast<const int2*>(p + 1024 + lane * 8);
+        return (v8i){lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, 0, 0};
+    };
+    auto fetch = [&](Frag& f, int s) {
+        const uint8_t* const p = sm + s * STAGE;
+#pragma unroll
+        for (int m = 0; m < MT; ++m) f.a[m] = operand(p + (wa + m) * PK_BLOCK);
+#pragma unroll
+        for (int n = 0; n < NT; ++n) f.b[n] = operand(p + (BA + wb + n) * PK_BLOCK);
+    };
+#pragma unroll
+    for (int t = 0; t < ST - 1; ++t) issue(t, t);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER * (ST - 2)) : "memory");       // this wave's pieces of block 0
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    Frag f0, f1;
+    fetch(f0, 0);
+    int s = 0;
+    // block i is in `cur`; i + 1 has landed, and nobody reads stage i - 1 any more, behind the barrier
+    auto step = [&](Frag& cur, Frag& nxt, int i) {
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER * (ST - 3)) : "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        const int prev = s == 0 ? ST - 1 : s - 1, next = s + 1 == ST ? 0 : s + 1;
+        issue(i + ST - 1, prev);
+        fetch(nxt, next);
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int n = 0; n < NT; ++n)        // (2: e2m3 operands; scales of 1)
+                acc[m][n] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(cur.a[m], cur.b[n], acc[m][n], 2, 2, 0, 0, 0, 0);
+        __builtin_amdgcn_s_setprio(0);
+        __builtin_amdgcn_sched_barrier(0);
+        s = next;
+    };
+    for (int i = 0; i < nk; i += 2) {
+        step(f0, f1, i);
+        if (i + 1 < nk) step(f1, f0, i + 1);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // (copies past the end, too)
+    __syncthreads();
 }
 
 // Step of a group from its maximum (the quantizer's).
@@ -130,7 +223,8 @@ __device__ __forceinline__ int xcd_tile(int id, int tiles_n, int ntiles) {
 // 4096 x 4096 rank 16 50.1 / 45.9 / 43.8; 4096 x 2048 x 2048 rank 80 186 / 134 / 123; short reductions, where the load latency
 // of the epilogue shows most, 128 x 8192 x 576 rank 80 85.3 / 88.8 / 82.1, 1024 x 1024 x 576 rank 48 45.8 / 47.5 / 43.7,
 // 100352 x 64 x 64 rank 8 33.7 / 34.1 / 31.7, 100352 x 16 x 16 31.5 / 32.7 / 30.4.
-template <bool WIDE, bool COMP, bool WCINT, int MTW, int NTW>
+// PACKED: packed codes instead of bytes; the same tiles and epilogue.
+template <bool WIDE, bool COMP, bool WCINT, int MTW, int NTW, bool PACKED>
 __global__ __launch_bounds__(256, 2) void int8_gemm_kernel(int M, int N, int K,
                                                            const int8_t* __restrict__ Aq,
                                                            const int8_t* __restrict__ BqT,
@@ -142,16 +236,20 @@ __global__ __launch_bounds__(256, 2) void int8_gemm_kernel(int M, int N, int K,
                                                            int32_t* __restrict__ Cint, int tiles_n,
                                                            int ntiles, float qmaxf) {
     constexpr int TMW = 64 * MTW, TNW = 64 * NTW;       // tile height and width
-    __shared__ __align__(16) int8_t As[2][TMW * BSTRIDE];
-    __shared__ __align__(16) int8_t Bs[2][TNW * BSTRIDE];
+    constexpr int ST = 6, LDP = 36;     // stages of packed codes; row stride of a panel chunk (conflict-free 16-byte reads)
+    constexpr int TILE_LDS = PACKED ? ST * (2 * MTW + 2 * NTW) * PK_BLOCK : 2 * (TMW + TNW) * BSTRIDE;
+    static_assert(TILE_LDS >= 2 * (TMW + TNW) * LDP * 4, "two chunks of the panel rows fit the operand tiles' LDS");
+    __shared__ __align__(16) int8_t tiles[TILE_LDS];
+    int8_t* const As[2] = {tiles, tiles + TMW * BSTRIDE};
+    int8_t* const Bs[2] = {tiles + 2 * TMW * BSTRIDE, tiles + (2 * TMW + TNW) * BSTRIDE};
     __shared__ __align__(16) float steps[TMW + TNW];    // of the tile's rows, then of its columns
     const int tile = xcd_tile(blockIdx.x, tiles_n, ntiles);
     const int m0 = (tile / tiles_n) * TMW, n0 = (tile % tiles_n) * TNW;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int wm = wave >> 1, wn = wave & 1;
     const int l32 = lane & 31, lh = lane >> 5;
 
-    v16i acc[MTW][NTW];
+    std::conditional_t<PACKED, v16f, v16i> acc[MTW][NTW];
 #pragma unroll
     for (int a = 0; a < MTW; ++a)
 #pragma unroll
@@ -165,9 +263,9 @@ __global__ __launch_bounds__(256, 2) void int8_gemm_kernel(int M, int N, int K,
 #define LRQ_DECL(S) uint4 S##a0, S##a1, S##a2, S##a3, S##b0, S##b1, S##b2, S##b3
     const int8_t *pa[2 * MTW], *pb[2 * NTW];
 #pragma unroll
-    for (int u = 0; u < 2 * MTW; ++u) pa[u] = code_row(Aq, m0 + srow0 + 32 * u, M, K);
+    for (int u = 0; u < 2 * MTW; ++u) pa[u] = PACKED ? nullptr : code_row(Aq, m0 + srow0 + 32 * u, M, K);
 #pragma unroll
-    for (int u = 0; u < 2 * NTW; ++u) pb[u] = code_row(BqT, n0 + srow0 + 32 * u, N, K);
+    for (int u = 0; u < 2 * NTW; ++u) pb[u] = PACKED ? nullptr : code_row(BqT, n0 + srow0 + 32 * u, N, K);
 #define LRQ_LD(P, k0) load16b<WIDE>(P, K, (k0) + skc)
 #define LRQ_GLOAD(S, k0)                                                                               \
     S##a0 = LRQ_LD(pa[0], k0); S##b0 = LRQ_LD(pb[0], k0); S##a1 = LRQ_LD(pa[1], k0); S##b1 = LRQ_LD(pb[1], k0); \
@@ -198,6 +296,18 @@ __global__ __launch_bounds__(256, 2) void int8_gemm_kernel(int M, int N, int K,
         if constexpr (MTW + NTW > 3) { q6 = LRQ_PL(6, c); q7 = LRQ_PL(7, c); }                         \
     }
 #define LRQ_PST(U) *reinterpret_cast<float4*>((32 * U < TMW ? Ls + (prow + 32 * U) * LDP : Rs + (prow + 32 * U - TMW) * LDP) + pcol) = q##U
+    // (without panels sA, sB hold the group maxima, and the tile's steps are formed here)
+    float st = 0.f;
+    if (tid < TMW) st = sA[min(m0 + tid, M - 1)];
+    else if (tid - TMW < TNW) st = sB[min(n0 + tid - TMW, N - 1)];
+    if constexpr (PACKED) {
+        if constexpr (COMP) LRQ_PLOAD(0);
+        if (tid < TMW + TNW) steps[tid] = COMP ? st : step_of(st, qmaxf);
+        packed_products<MTW, NTW, 2 * MTW, 2 * NTW, 4, ST>(reinterpret_cast<const uint8_t*>(Aq), reinterpret_cast<const uint8_t*>(BqT),
+                                                           m0 >> 5, (M + 31) >> 5, n0 >> 5, (N + 31) >> 5, pk_kblocks(K), 0,
+                                                           pk_kblocks(K), reinterpret_cast<uint8_t*>(tiles), wave, lane, wm * MTW,
+                                                           wn * NTW, acc);
+    } else {
     LRQ_DECL(r0);
     LRQ_DECL(r1);
     auto compute = [&](int buf) {
@@ -220,10 +330,6 @@ __global__ __launch_bounds__(256, 2) void int8_gemm_kernel(int M, int N, int K,
         }
     };
     const int nk = (K + BBK - 1) / BBK;
-    // (without panels sA, sB hold the group maxima, and the tile's steps are formed here)
-    float st = 0.f;
-    if (tid < TMW) st = sA[min(m0 + tid, M - 1)];
-    else if (tid - TMW < TNW) st = sB[min(n0 + tid - TMW, N - 1)];
     LRQ_GLOAD(r0, 0);
     LRQ_GLOAD(r1, BBK);
     if constexpr (COMP) LRQ_PLOAD(0);
@@ -242,6 +348,7 @@ __global__ __launch_bounds__(256, 2) void int8_gemm_kernel(int M, int N, int K,
     for (int kt = 0; kt < nk; kt += 2) {
         LRQ_GEMM_STEP(0, r0, r1)
         LRQ_GEMM_STEP(1, r1, r0)
+    }
     }
 #undef LRQ_GEMM_STEP
 #undef LRQ_DECL
@@ -268,18 +375,16 @@ __global__ __launch_bounds__(256, 2) void int8_gemm_kernel(int M, int N, int K,
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int row = rbase + 8 * (v >> 2) + 4 * lh + (v & 3);
-                if (WCINT && row < M && col < N) Cint[(size_t)row * N + col] = acc[mt][nt][v];
-                f[mt][nt][v] = ((float)acc[mt][nt][v] * sa[v]) * sb;
+                if (WCINT && row < M && col < N) Cint[(size_t)row * N + col] = (int32_t)code_sum(acc[mt][nt][v]);
+                f[mt][nt][v] = (code_sum(acc[mt][nt][v]) * sa[v]) * sb;
             }
         }
     }
     if constexpr (COMP) {
         // two buffers of 32 columns in the operand tiles' LDS (the K loop's last barrier has released it)
-        constexpr int LDP = 36;         // padded: conflict-free 16-byte reads
-        static_assert(2 * BSTRIDE >= 2 * LDP * 4, "two chunks of the panel rows fit the operand's LDS");
         for (int t0 = 0, buf = 0; t0 < R2P; t0 += 32, buf ^= 1) {
-            float* const Ls = reinterpret_cast<float*>(&As[0][0]) + buf * (TMW * LDP);
-            float* const Rs = reinterpret_cast<float*>(&Bs[0][0]) + buf * (TNW * LDP);
+            float* const Ls = reinterpret_cast<float*>(tiles) + buf * ((TMW + TNW) * LDP);
+            float* const Rs = Ls + TMW * LDP;
             LRQ_PST(0); LRQ_PST(1); LRQ_PST(2); LRQ_PST(3);
             if constexpr (MTW + NTW > 2) { LRQ_PST(4); LRQ_PST(5); }
             if constexpr (MTW + NTW > 3) { LRQ_PST(6); LRQ_PST(7); }
@@ -330,6 +435,197 @@ __global__ __launch_bounds__(256, 2) void int8_gemm_kernel(int M, int N, int K,
 #define BTN 256
 #define BCHUNKS (BBK / 16)      // 16-byte chunks per staged row
 #define BROWS (512 / BCHUNKS)   // rows covered by one pass of the 512 threads
+#define LARGE_LDS (2 * BTM * BSTRIDE)       // of each operand's tiles, reused by the epilogue
+struct LargeTile {
+    int M, N, m0, n0;
+    const float *sA, *sB, *Lp, *Rp;
+    int R2P;
+    GemmOut out;
+    int32_t *Cint, *part;       // part: of a workgroup that holds one range of K (partial)
+    bool partial;
+    float qmaxf;
+};
+__device__ __forceinline__ int32_t raw_sum(int a) { return a; }
+__device__ __forceinline__ int32_t raw_sum(float a) { return (int32_t)(a * 64.0f); }
+
+// What follows the products of a large tile (v16i sums of bytes, v16f of packed codes).  The tiles' LDS is free.
+template <bool COMP, bool WCINT, bool SPLITK, class ACC>
+__device__ __forceinline__ void finish_large_tile(const LargeTile& T, ACC (&acc)[2][4], int8_t* ldsA, int8_t* ldsB) {
+    const int M = T.M, N = T.N, m0 = T.m0, n0 = T.n0, R2P = T.R2P;
+    const float *__restrict__ const sA = T.sA, *__restrict__ const sB = T.sB;
+    const float *__restrict__ const Lp = T.Lp, *__restrict__ const Rp = T.Rp;
+    const GemmOut& out = T.out;
+    float* __restrict__ const C = out.C;
+    int32_t *__restrict__ const Cint = T.Cint, *__restrict__ const part = T.part;
+    const bool partial = T.partial;
+    const float qmaxf = T.qmaxf;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int wm = wave >> 1, wn = wave & 1;
+    const int l32 = lane & 31, lh = lane >> 5;
+    // ---- epilogue: dequantize, rank-2r update, store ----
+    // C == nullptr: only the raw int32 sums are wanted (the dequantization and the update then
+    // run later, in rank_update_kernel), and the step vectors are not read.
+    const bool want_c = C != nullptr;
+    // Without panels sA, sB hold the group maxima, and the tile's steps are formed here, one per thread, in the LDS that the
+    // operand tiles have left: a launch that prepared them took 5 us of a call at 4096^3.
+    float* const sAl = reinterpret_cast<float*>(ldsA);
+    float* const sBl = reinterpret_cast<float*>(ldsB);
+    if (!COMP && want_c) {
+        if (tid < BTM) sAl[tid] = step_of(sA[min(m0 + tid, M - 1)], qmaxf);
+        else sBl[tid - BTM] = step_of(sB[min(n0 + tid - BTM, N - 1)], qmaxf);
+        __syncthreads();
+    }
+    // Wider panels: the float32 matrix cores would take 4 R2P M N flops at 1/16 of the bfloat16 rate, so the tile's panel rows
+    // are split into three bfloat16 planes while they are staged (32 columns at a time, in the LDS that the operand tiles have
+    // left) and the six plane products of weight >= 2^-16 run on v_mfma_f32_32x32x16_bf16, as in rank_update_bf16_kernel.
+    if (COMP && R2P > 64) {
+        uint16_t* const Lq = reinterpret_cast<uint16_t*>(ldsA);
+        uint16_t* const Rq = reinterpret_cast<uint16_t*>(ldsB);
+        constexpr int PL = 256 * PANEL_LD;          // one plane
+        static_assert(LARGE_LDS >= 3 * PL * 2, "three planes of a 32-column chunk fit an operand's LDS");
+        v16f f[2][4];
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt) {
+            const int rbase = m0 + wm * 64 + mt * 32;
+            float sa[16];
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int row = rbase + 8 * (v >> 2) + 4 * lh + (v & 3);
+                sa[v] = row < M ? sA[row] : 0.f;
+            }
+#pragma unroll
+            for (int nt = 0; nt < 4; ++nt) {
+                const int col = n0 + wn * 128 + nt * 32 + l32;
+                const float sb = col < N ? sB[col] : 0.f;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int row = rbase + 8 * (v >> 2) + 4 * lh + (v & 3);
+                    if (WCINT && row < M && col < N) Cint[(size_t)row * N + col] = raw_sum(acc[mt][nt][v]);
+                    f[mt][nt][v] = (code_sum(acc[mt][nt][v]) * sa[v]) * sb;
+                }
+            }
+        }
+        for (int t0 = 0; t0 < R2P; t0 += PANEL_KC) {
+            __syncthreads();            // nobody reads the operand tiles, or the previous chunk, any more
+            // 2 panels x 256 rows x 4 groups of 8 columns, four units per thread
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int unit = tid + 512 * i, r = (unit >> 2) & 255, c8 = (unit & 3) * 8;
+                const bool left = i < 2;
+                // rows / columns past the end re-read the last one (rows are never stored, columns enter as zeros)
+                const float* src = left ? Lp + (size_t)min(m0 + r, M - 1) * R2P : Rp + (size_t)min(n0 + r, N - 1) * R2P;
+                stage_planes(src, t0 + c8, R2P, (left ? Lq : Rq) + r * PANEL_LD + c8, PL);
+            }
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                v8bf16 a[2][3];
+#pragma unroll
+                for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+                    for (int q = 0; q < 3; ++q)
+                        a[mt][q] = *reinterpret_cast<const v8bf16*>(Lq + q * PL + (wm * 64 + mt * 32 + l32) * PANEL_LD + 16 * u + 8 * lh);
+#pragma unroll
+                for (int nt = 0; nt < 4; ++nt) {
+                    v8bf16 b[3];
+#pragma unroll
+                    for (int q = 0; q < 3; ++q)
+                        b[q] = *reinterpret_cast<const v8bf16*>(Rq + q * PL + (wn * 128 + nt * 32 + l32) * PANEL_LD + 16 * u + 8 * lh);
+                    // smallest products first; the two row tiles are independent chains
+#define LRQ_PP(QA, QB)                                                                                          \
+    _Pragma("unroll") for (int mt = 0; mt < 2; ++mt) f[mt][nt] =                                                \
+        __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[mt][QA], b[QB], f[mt][nt], 0, 0, 0);
+                    LRQ_PP(0, 2)
+                    LRQ_PP(1, 1)
+                    LRQ_PP(2, 0)
+                    LRQ_PP(0, 1)
+                    LRQ_PP(1, 0)
+                    LRQ_PP(0, 0)
+#undef LRQ_PP
+                }
+            }
+        }
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+            for (int nt = 0; nt < 4; ++nt) {
+                const int col = n0 + wn * 128 + nt * 32 + l32;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int row = m0 + wm * 64 + mt * 32 + 8 * (v >> 2) + 4 * lh + (v & 3);
+                    if (row < M && col < N) store_out(out, row, col, f[mt][nt][v]);
+                }
+            }
+        return;
+    }
+    // Panels of up to 64 columns: the tile's 256 rows of Lp and of Rp are staged in the LDS that the operand
+    // tiles have left (whole-row loads; rows past the end as zeros; row stride R2P + 4 floats: conflict-free
+    // 16-byte reads), instead of 32 cache lines per load instruction from global memory.  Same values, same
+    // order of the products.
+    const int LDP = R2P + 4;
+    float* const Ls = reinterpret_cast<float*>(ldsA);
+    float* const Rs = reinterpret_cast<float*>(ldsB);
+    static_assert(LARGE_LDS >= 256 * 68 * 4 && BTM + BTN == 512, "a 64-column panel tile fits an operand's LDS");
+    if (COMP) {
+        __syncthreads();        // every wave has read its last operand fragments
+        const int q4 = R2P / 4;
+        for (int idx = tid; idx < 256 * q4; idx += 512) {
+            const int rr = idx / q4, c4 = idx - rr * q4;
+            const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
+            const float4 lv = m0 + rr < M ? *reinterpret_cast<const float4*>(Lp + (size_t)(m0 + rr) * R2P + 4 * c4) : z;
+            const float4 rv = n0 + rr < N ? *reinterpret_cast<const float4*>(Rp + (size_t)(n0 + rr) * R2P + 4 * c4) : z;
+            *reinterpret_cast<float4*>(Ls + rr * LDP + 4 * c4) = lv;
+            *reinterpret_cast<float4*>(Rs + rr * LDP + 4 * c4) = rv;
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt) {
+        const int rbase = m0 + wm * 64 + mt * 32;
+        const float* lps = Ls + (wm * 64 + mt * 32 + l32) * LDP + 4 * lh;
+        float sa[16];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int row = rbase + 8 * (v >> 2) + 4 * lh + (v & 3);
+            sa[v] = !want_c ? 0.f : (COMP ? sA[min(row, M - 1)] : sAl[row - m0]);
+        }
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt) {
+            const int col = n0 + wn * 128 + nt * 32 + l32;
+            const bool col_ok = col < N;
+            const float sb = !want_c ? 0.f : (COMP ? sB[min(col, N - 1)] : sBl[col - n0]);
+            v16f f;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int row = rbase + 8 * (v >> 2) + 4 * lh + (v & 3);
+                if (WCINT && row < M && col_ok) {
+                    if (SPLITK && partial) part[(row - m0) * BTN + (col - n0)] = raw_sum(acc[mt][nt][v]);
+                    else Cint[(size_t)row * N + col] = raw_sum(acc[mt][nt][v]);
+                }
+                f[v] = (code_sum(acc[mt][nt][v]) * sa[v]) * sb;
+            }
+            if (COMP) {
+                const float* rps = Rs + (wn * 128 + nt * 32 + l32) * LDP + 4 * lh;
+                for (int t0 = 0; t0 < R2P; t0 += 8) {
+                    const float4 a4 = *reinterpret_cast<const float4*>(lps + t0);
+                    const float4 b4 = *reinterpret_cast<const float4*>(rps + t0);
+                    f = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.x, b4.x, f, 0, 0, 0);
+                    f = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.y, b4.y, f, 0, 0, 0);
+                    f = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.z, b4.z, f, 0, 0, 0);
+                    f = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.w, b4.w, f, 0, 0, 0);
+                }
+            }
+            if (want_c) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int row = rbase + 8 * (v >> 2) + 4 * lh + (v & 3);
+                    if (row < M && col_ok) store_out(out, row, col, f[v]);
+                }
+            }
+        }
+    }
+}
+
 // FULL: M, N multiples of 256 and K a multiple of the tile depth -- operand loads carry no guard at all, so
 // nothing consumes a loaded register before it is written to LDS two iterations later.
 // SPLITK (raw sums only, FULL shapes): workgroups [0, full_tiles) compute one tile each as usual;
@@ -348,7 +644,6 @@ __global__ __launch_bounds__(512, 1) void int8_gemm256_kernel(int M, int N, int 
                                                               int32_t* __restrict__ Cint, int tiles_n,
                                                               int ntiles, int full_tiles, int slices,
                                                               int32_t* __restrict__ part, float qmaxf) {
-    float* __restrict__ C = out.C;
     __shared__ __align__(16) int8_t As[2][BTM * BSTRIDE];
     __shared__ __align__(16) int8_t Bs[2][BTN * BSTRIDE];
     int wg = blockIdx.x, kt0 = 0, nk = (K + BBK - 1) / BBK;
@@ -465,168 +760,48 @@ __global__ __launch_bounds__(512, 1) void int8_gemm256_kernel(int M, int N, int 
 #undef LRQ_GLOAD
 #undef LRQ_SSTORE
 
-    // ---- epilogue: dequantize, rank-2r update, store ----
-    // C == nullptr: only the raw int32 sums are wanted (the dequantization and the update then
-    // run later, in rank_update_kernel), and the step vectors are not read.
-    const bool want_c = C != nullptr;
-    // Without panels sA, sB hold the group maxima, and the tile's steps are formed here, one per thread, in the LDS that the
-    // operand tiles have left: a launch that prepared them took 5 us of a call at 4096^3.
-    float* const sAl = reinterpret_cast<float*>(&As[0][0]);
-    float* const sBl = reinterpret_cast<float*>(&Bs[0][0]);
-    if (!COMP && want_c) {
-        if (tid < BTM) sAl[tid] = step_of(sA[min(m0 + tid, M - 1)], qmaxf);
-        else sBl[tid - BTM] = step_of(sB[min(n0 + tid - BTM, N - 1)], qmaxf);
-        __syncthreads();
-    }
-    // Wider panels: the float32 matrix cores would take 4 R2P M N flops at 1/16 of the bfloat16 rate, so the tile's panel rows
-    // are split into three bfloat16 planes while they are staged (32 columns at a time, in the LDS that the operand tiles have
-    // left) and the six plane products of weight >= 2^-16 run on v_mfma_f32_32x32x16_bf16, as in rank_update_bf16_kernel.
-    if (COMP && R2P > 64) {
-        uint16_t* const Lq = reinterpret_cast<uint16_t*>(&As[0][0]);
-        uint16_t* const Rq = reinterpret_cast<uint16_t*>(&Bs[0][0]);
-        constexpr int PL = 256 * PANEL_LD;          // one plane
-        static_assert(2 * BTM * BSTRIDE >= 3 * PL * 2, "three planes of a 32-column chunk fit an operand's LDS");
-        v16f f[2][4];
-#pragma unroll
-        for (int mt = 0; mt < 2; ++mt) {
-            const int rbase = m0 + wm * 64 + mt * 32;
-            float sa[16];
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int row = rbase + 8 * (v >> 2) + 4 * lh + (v & 3);
-                sa[v] = row < M ? sA[row] : 0.f;
-            }
-#pragma unroll
-            for (int nt = 0; nt < 4; ++nt) {
-                const int col = n0 + wn * 128 + nt * 32 + l32;
-                const float sb = col < N ? sB[col] : 0.f;
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int row = rbase + 8 * (v >> 2) + 4 * lh + (v & 3);
-                    if (WCINT && row < M && col < N) Cint[(size_t)row * N + col] = acc[mt][nt][v];
-                    f[mt][nt][v] = ((float)acc[mt][nt][v] * sa[v]) * sb;
-                }
-            }
-        }
-        for (int t0 = 0; t0 < R2P; t0 += PANEL_KC) {
-            __syncthreads();            // nobody reads the operand tiles, or the previous chunk, any more
-            // 2 panels x 256 rows x 4 groups of 8 columns, four units per thread
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int unit = tid + 512 * i, r = (unit >> 2) & 255, c8 = (unit & 3) * 8;
-                const bool left = i < 2;
-                // rows / columns past the end re-read the last one (rows are never stored, columns enter as zeros)
-                const float* src = left ? Lp + (size_t)min(m0 + r, M - 1) * R2P : Rp + (size_t)min(n0 + r, N - 1) * R2P;
-                stage_planes(src, t0 + c8, R2P, (left ? Lq : Rq) + r * PANEL_LD + c8, PL);
-            }
-            __syncthreads();
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                v8bf16 a[2][3];
-#pragma unroll
-                for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-                    for (int q = 0; q < 3; ++q)
-                        a[mt][q] = *reinterpret_cast<const v8bf16*>(Lq + q * PL + (wm * 64 + mt * 32 + l32) * PANEL_LD + 16 * u + 8 * lh);
-#pragma unroll
-                for (int nt = 0; nt < 4; ++nt) {
-                    v8bf16 b[3];
-#pragma unroll
-                    for (int q = 0; q < 3; ++q)
-                        b[q] = *reinterpret_cast<const v8bf16*>(Rq + q * PL + (wn * 128 + nt * 32 + l32) * PANEL_LD + 16 * u + 8 * lh);
-                    // smallest products first; the two row tiles are independent chains
-#define LRQ_PP(QA, QB)                                                                                          \
-    _Pragma("unroll") for (int mt = 0; mt < 2; ++mt) f[mt][nt] =                                                \
-        __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[mt][QA], b[QB], f[mt][nt], 0, 0, 0);
-                    LRQ_PP(0, 2)
-                    LRQ_PP(1, 1)
-                    LRQ_PP(2, 0)
-                    LRQ_PP(0, 1)
-                    LRQ_PP(1, 0)
-                    LRQ_PP(0, 0)
-#undef LRQ_PP
-                }
-            }
-        }
-#pragma unroll
-        for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-            for (int nt = 0; nt < 4; ++nt) {
-                const int col = n0 + wn * 128 + nt * 32 + l32;
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int row = m0 + wm * 64 + mt * 32 + 8 * (v >> 2) + 4 * lh + (v & 3);
-                    if (row < M && col < N) store_out(out, row, col, f[mt][nt][v]);
-                }
-            }
-        return;
-    }
-    // Panels of up to 64 columns: the tile's 256 rows of Lp and of Rp are staged in the LDS that the operand
-    // tiles have left (whole-row loads; rows past the end as zeros; row stride R2P + 4 floats: conflict-free
-    // 16-byte reads), instead of 32 cache lines per load instruction from global memory.  Same values, same
-    // order of the products.
-    const int LDP = R2P + 4;
-    float* const Ls = reinterpret_cast<float*>(&As[0][0]);
-    float* const Rs = reinterpret_cast<float*>(&Bs[0][0]);
-    static_assert(2 * BTM * BSTRIDE >= 256 * 68 * 4 && BTM + BTN == 512, "a 64-column panel tile fits an operand's LDS");
-    if (COMP) {
-        __syncthreads();        // every wave has read its last operand fragments
-        const int q4 = R2P / 4;
-        for (int idx = tid; idx < 256 * q4; idx += 512) {
-            const int rr = idx / q4, c4 = idx - rr * q4;
-            const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
-            const float4 lv = m0 + rr < M ? *reinterpret_cast<const float4*>(Lp + (size_t)(m0 + rr) * R2P + 4 * c4) : z;
-            const float4 rv = n0 + rr < N ? *reinterpret_cast<const float4*>(Rp + (size_t)(n0 + rr) * R2P + 4 * c4) : z;
-            *reinterpret_cast<float4*>(Ls + rr * LDP + 4 * c4) = lv;
-            *reinterpret_cast<float4*>(Rs + rr * LDP + 4 * c4) = rv;
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt) {
-        const int rbase = m0 + wm * 64 + mt * 32;
-        const float* lps = Ls + (wm * 64 + mt * 32 + l32) * LDP + 4 * lh;
-        float sa[16];
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int row = rbase + 8 * (v >> 2) + 4 * lh + (v & 3);
-            sa[v] = !want_c ? 0.f : (COMP ? sA[min(row, M - 1)] : sAl[row - m0]);
-        }
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt) {
-            const int col = n0 + wn * 128 + nt * 32 + l32;
-            const bool col_ok = col < N;
-            const float sb = !want_c ? 0.f : (COMP ? sB[min(col, N - 1)] : sBl[col - n0]);
-            v16f f;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int row = rbase + 8 * (v >> 2) + 4 * lh + (v & 3);
-                if (WCINT && row < M && col_ok) {
-                    if (SPLITK && partial) part[(row - m0) * BTN + (col - n0)] = acc[mt][nt][v];
-                    else Cint[(size_t)row * N + col] = acc[mt][nt][v];
-                }
-                f[v] = ((float)acc[mt][nt][v] * sa[v]) * sb;
-            }
-            if (COMP) {
-                const float* rps = Rs + (wn * 128 + nt * 32 + l32) * LDP + 4 * lh;
-                for (int t0 = 0; t0 < R2P; t0 += 8) {
-                    const float4 a4 = *reinterpret_cast<const float4*>(lps + t0);
-                    const float4 b4 = *reinterpret_cast<const float4*>(rps + t0);
-                    f = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.x, b4.x, f, 0, 0, 0);
-                    f = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.y, b4.y, f, 0, 0, 0);
-                    f = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.z, b4.z, f, 0, 0, 0);
-                    f = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.w, b4.w, f, 0, 0, 0);
-                }
-            }
-            if (want_c) {
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int row = rbase + 8 * (v >> 2) + 4 * lh + (v & 3);
-                    if (row < M && col_ok) store_out(out, row, col, f[v]);
-                }
-            }
+    finish_large_tile<COMP, WCINT, SPLITK>(LargeTile{M, N, m0, n0, sA, sB, Lp, Rp, R2P, out, Cint, part, partial, qmaxf}, acc, &As[0][0],
+                                           &Bs[0][0]);
+}
+
+// The same tiles from packed codes.
+template <bool COMP, bool WCINT, bool SPLITK = false>
+__global__ __launch_bounds__(512, 1) void packed_gemm256_kernel(int M, int N, int K, const uint8_t* __restrict__ A,
+                                                                const uint8_t* __restrict__ B, const float* __restrict__ sA,
+                                                                const float* __restrict__ sB, const float* __restrict__ Lp,
+                                                                const float* __restrict__ Rp, int R2P, GemmOut out,
+                                                                int32_t* __restrict__ Cint, int tiles_n, int ntiles, int full_tiles,
+                                                                int slices, int32_t* __restrict__ part, float qmaxf) {
+    constexpr int ST = 6;
+    __shared__ __align__(16) int8_t tiles[2 * LARGE_LDS];
+    static_assert(ST * 16 * PK_BLOCK <= 2 * LARGE_LDS, "the stages fit");
+    int wg = blockIdx.x, kb0 = 0, nk = pk_kblocks(K);
+    const int nkb = nk;
+    bool partial = false;
+    if constexpr (SPLITK) {
+        if (wg >= full_tiles) {
+            const int e = wg - full_tiles, lt = e / slices, sl = e - lt * slices;
+            wg = full_tiles + lt;
+            part += (size_t)e * (BTM * BTN);
+            kb0 = (int)((long long)sl * nkb / slices);
+            nk = (int)((long long)(sl + 1) * nkb / slices) - kb0;
+            partial = true;
         }
     }
+    const int tile = xcd_tile(wg, tiles_n, ntiles);
+    const int m0 = (tile / tiles_n) * BTM, n0 = (tile % tiles_n) * BTN;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    v16f acc[2][4];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
+    packed_products<2, 4, 8, 8, 8, ST>(A, B, m0 >> 5, (M + 31) >> 5, n0 >> 5, (N + 31) >> 5, nkb, kb0, nk, reinterpret_cast<uint8_t*>(tiles),
+                                       wave, lane, (wave >> 1) * 2, (wave & 1) * 4, acc);
+    finish_large_tile<COMP, WCINT, SPLITK>(LargeTile{M, N, m0, n0, sA, sB, Lp, Rp, R2P, out, Cint, part, partial, qmaxf}, acc, tiles,
+                                           tiles + LARGE_LDS);
 }
 
 // Complete residual compensation (Eq. (gemm_r_split)): the sum of three or four integer products, each with step vectors of
@@ -1309,11 +1484,15 @@ int launch_build_panels(int M, int N, int K, int r, int RP, int R2P, const float
 static void dispatch_gemm256(bool comp, bool wcint, dim3 grid, hipStream_t st, int M, int N, int K,
                              const int8_t* Aq, const int8_t* BqT, const float* sA, const float* sB,
                              const float* Lp, const float* Rp, int R2P, GemmOut C, int32_t* Cint, int tiles_n,
-                             int ntiles, float qmaxf) {
+                             int ntiles, float qmaxf, bool packed) {
     const bool full = aligned16(Aq) && aligned16(BqT) && (M % BTM == 0) && (N % BTN == 0) && (K % BBK == 0);
 #define LRQ_GEMM(COMP, WC)                                                                                   \
     do {                                                                                                     \
-        if (full)                                                                                            \
+        if (packed)                                                                                          \
+            hipLaunchKernelGGL((packed_gemm256_kernel<COMP, WC>), grid, dim3(512), 0, st, M, N, K,           \
+                               reinterpret_cast<const uint8_t*>(Aq), reinterpret_cast<const uint8_t*>(BqT), sA, sB, Lp, Rp, R2P, C, \
+                               Cint, tiles_n, ntiles, ntiles, 1, nullptr, qmaxf);                            \
+        else if (full)                                                                                       \
             hipLaunchKernelGGL((int8_gemm256_kernel<COMP, WC, true>), grid, dim3(512), 0, st, M, N, K, Aq, \
                                BqT, sA, sB, Lp, Rp, R2P, C, Cint, tiles_n, ntiles, ntiles, 1, nullptr, qmaxf); \
         else                                                                                                 \
@@ -1328,12 +1507,12 @@ static void dispatch_gemm256(bool comp, bool wcint, dim3 grid, hipStream_t st, i
 #undef LRQ_GEMM
 }
 
-template <bool WIDE, int MTW, int NTW>
+template <bool WIDE, int MTW, int NTW, bool PACKED>
 static void dispatch_gemm(bool comp, bool wcint, dim3 grid, hipStream_t st, int M, int N, int K,
                           const int8_t* Aq, const int8_t* BqT, const float* sA, const float* sB,
                           const float* Lp, const float* Rp, int R2P, GemmOut C, int32_t* Cint, int tiles_n,
                           int ntiles, float qmaxf) {
-#define LRQ_GEMM(COMP, WC) hipLaunchKernelGGL((int8_gemm_kernel<WIDE, COMP, WC, MTW, NTW>), grid, dim3(256), 0, st, M, N, K, \
+#define LRQ_GEMM(COMP, WC) hipLaunchKernelGGL((int8_gemm_kernel<WIDE, COMP, WC, MTW, NTW, PACKED>), grid, dim3(256), 0, st, M, N, K, \
                                               Aq, BqT, sA, sB, Lp, Rp, R2P, C, Cint, tiles_n, ntiles, qmaxf)
     if (comp) {
         if (wcint) LRQ_GEMM(true, true); else LRQ_GEMM(true, false);
@@ -1387,15 +1566,20 @@ size_t int8_gemm_sums_scratch_bytes(int M, int N, int K) {
 }
 
 int launch_int8_gemm_sums(int M, int N, int K, const int8_t* Aq, const int8_t* BqT, int32_t* Cint, int resident,
-                          int32_t* part, hipStream_t st) {
+                          int32_t* part, hipStream_t st, bool packed) {
     const SumsPlan p = part ? plan_sums(M, N, K, Aq, BqT, resident) : SumsPlan{0, 0, 0, 1};
     if (p.left == 0)
         return launch_int8_gemm(M, N, K, Aq, BqT, nullptr, nullptr, nullptr, nullptr, 0, GemmOut{nullptr, N, 1.0f, 0.0f},
-                                Cint, 0.0f, st);
+                                Cint, 0.0f, st, packed);
     const int full_tiles = p.ntiles - p.left;
-    hipLaunchKernelGGL((int8_gemm256_kernel<false, true, true, true>), dim3(full_tiles + p.left * p.slices),
-                       dim3(512), 0, st, M, N, K, Aq, BqT, nullptr, nullptr, nullptr, nullptr, 0,
-                       GemmOut{nullptr, N, 1.0f, 0.0f}, Cint, p.tiles_n, p.ntiles, full_tiles, p.slices, part, 0.0f);
+    if (packed)
+        hipLaunchKernelGGL((packed_gemm256_kernel<false, true, true>), dim3(full_tiles + p.left * p.slices), dim3(512), 0, st, M, N, K,
+                           reinterpret_cast<const uint8_t*>(Aq), reinterpret_cast<const uint8_t*>(BqT), nullptr, nullptr, nullptr,
+                           nullptr, 0, GemmOut{nullptr, N, 1.0f, 0.0f}, Cint, p.tiles_n, p.ntiles, full_tiles, p.slices, part, 0.0f);
+    else
+        hipLaunchKernelGGL((int8_gemm256_kernel<false, true, true, true>), dim3(full_tiles + p.left * p.slices),
+                           dim3(512), 0, st, M, N, K, Aq, BqT, nullptr, nullptr, nullptr, nullptr, 0,
+                           GemmOut{nullptr, N, 1.0f, 0.0f}, Cint, p.tiles_n, p.ntiles, full_tiles, p.slices, part, 0.0f);
     LRQ_CHECK_LAUNCH();
     return LRQMM_OK;
 }
@@ -1409,6 +1593,9 @@ int launch_int8_gemm_sums_finish(int M, int N, int K, const int8_t* Aq, const in
     LRQ_CHECK_LAUNCH();
     return LRQMM_OK;
 }
+
+// Codes of at most five bits whose sums stay below 2^24.
+bool codes_packable(int bits, int K) { return bits <= 5 && ((long long)K << (2 * (bits - 1))) <= (1ll << 24); }
 
 long long int8_gemm_tiles(int M, int N) { return (long long)ceil_div(M, BTM) * ceil_div(N, BTN); }
 // The large-tile kernel pays from half a round of its tiles on (raw sums, where it is the only one that is asked for)
@@ -1487,7 +1674,7 @@ int launch_empty_product(int M, int N, GemmOut C, int32_t* Cint, hipStream_t st)
 
 int launch_int8_gemm(int M, int N, int K, const int8_t* Aq, const int8_t* BqT, const float* sA,
                      const float* sB, const float* Lp, const float* Rp, int R2P, GemmOut C, int32_t* Cint,
-                     float qmaxf, hipStream_t st) {
+                     float qmaxf, hipStream_t st, bool packed) {
     // the GEMM kernels issue their first operand loads unconditionally: an empty reduction never reaches them
     if (K <= 0) return launch_empty_product(M, N, C, Cint, st);
     // (the 16-byte load path clamps its address to K - 16, so it needs at least one whole group)
@@ -1498,7 +1685,7 @@ int launch_int8_gemm(int M, int N, int K, const int8_t* Aq, const int8_t* BqT, c
         const int btiles = (int)int8_gemm_tiles(M, N);
         const int btn = ceil_div(N, BTN);
         dim3 bgrid(btiles);
-        dispatch_gemm256(comp, Cint != nullptr, bgrid, st, M, N, K, Aq, BqT, sA, sB, Lp, Rp, R2P, C, Cint, btn, btiles, qmaxf);
+        dispatch_gemm256(comp, Cint != nullptr, bgrid, st, M, N, K, Aq, BqT, sA, sB, Lp, Rp, R2P, C, Cint, btn, btiles, qmaxf, packed);
         LRQ_CHECK_LAUNCH();
         return LRQMM_OK;
     }
@@ -1513,11 +1700,16 @@ int launch_int8_gemm(int M, int N, int K, const int8_t* Aq, const int8_t* BqT, c
     if (!wide) mtw = ntw = 2;           // (K < 16: one staged tile)
     const int tiles_n = ceil_div(N, 64 * ntw), ntiles = (int)tiles();
     dim3 grid(ntiles);
-#define LRQ_DG(W, MT, NT) dispatch_gemm<W, MT, NT>(comp, Cint != nullptr, grid, st, M, N, K, Aq, BqT, sA, sB, Lp, Rp, R2P, C, Cint, tiles_n, ntiles, qmaxf)
-    if (!wide)                     LRQ_DG(false, 2, 2);
-    else if (mtw == 2 && ntw == 2) LRQ_DG(true, 2, 2);
-    else if (ntw == 2)             LRQ_DG(true, 1, 2);
-    else                           LRQ_DG(true, 1, 1);
+#define LRQ_DG(W, MT, NT, PK) dispatch_gemm<W, MT, NT, PK>(comp, Cint != nullptr, grid, st, M, N, K, Aq, BqT, sA, sB, Lp, Rp, R2P, C, Cint, tiles_n, ntiles, qmaxf)
+    if (packed) {
+        if (mtw == 2 && ntw == 2)  LRQ_DG(true, 2, 2, true);
+        else if (ntw == 2)         LRQ_DG(true, 1, 2, true);
+        else                       LRQ_DG(true, 1, 1, true);
+    }
+    else if (!wide)                LRQ_DG(false, 2, 2, false);
+    else if (mtw == 2 && ntw == 2) LRQ_DG(true, 2, 2, false);
+    else if (ntw == 2)             LRQ_DG(true, 1, 2, false);
+    else                           LRQ_DG(true, 1, 1, false);
 #undef LRQ_DG
     LRQ_CHECK_LAUNCH();
     return LRQMM_OK;

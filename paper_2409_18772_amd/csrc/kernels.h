@@ -85,8 +85,9 @@ struct PassOperand {
 // N pass: partial[s][rows][LP] = R[:, chunk s] . W[chunk s, :].
 // quantize: the same launch quantizes the operands from their group maxima (amax): it writes the codes (row-major for
 // axis 0, transposed for axis 1) and the step vectors, then read by the later passes.
+// packed: the codes leave packed (see PK_BLOCK; codes is then 16-byte aligned and holds pk_bytes).
 int launch_resid_mul_n(const PassOperand* op, int nop, QuantParams q, int LP, bool quantize, hipStream_t st,
-                       int planes = 3);
+                       int planes = 3, bool packed = false);
 // T pass: partial[s][cols][LP] = R[chunk s, :]^T . Y[chunk s, :].
 int launch_resid_mul_t(const PassOperand* op, int nop, QuantParams q, int LP, hipStream_t st, int planes = 3);
 // Row quantization and the sketch product from one read, for operands quantized by rows whose rows are short
@@ -113,7 +114,8 @@ int launch_quant_sketch_rows(const float* X, int ldx, int rows, int cols, QuantP
 // WX3: the K x LP factor as three bfloat16 planes [3][LP][Kp] (k fastest, Kp = K rounded up to 64, zero padded).
 int launch_codes_mul_n2(const int8_t* codesA, int rowsA, const uint16_t* WA3, PassPlan planA,
                         float* partialA, const int8_t* codesB, int rowsB, const uint16_t* WB3,
-                        PassPlan planB, float* partialB, int K, int Kp, int LP, hipStream_t st, int planes = 3);
+                        PassPlan planB, float* partialB, int K, int Kp, int LP, hipStream_t st, int planes = 3,
+                        bool packed = false);
 
 // ---- orth.hip -----------------------------------------------------------
 // Every launch below takes one job or two (the two operands of a product, in one launch).
@@ -189,7 +191,9 @@ struct GemmOut {
 // (M x N, dense).  Without panels (Lp == null) sA, sB are the group maxima, turned into steps with qmaxf.
 int launch_int8_gemm(int M, int N, int K, const int8_t* Aq, const int8_t* BqT, const float* sA,
                      const float* sB, const float* Lp, const float* Rp, int R2P, GemmOut C,
-                     int32_t* Cint, float qmaxf, hipStream_t st);
+                     int32_t* Cint, float qmaxf, hipStream_t st, bool packed = false);
+// packed (here and below): both code matrices are packed (see PK_BLOCK), where codes_packable(bits, K); same results.
+bool codes_packable(int bits, int K);
 // D <- alpha (A0 B0 + A0 B1 + A1 B0 [+ A1 B1]) + beta D, the products of the operands' codes (0) and of their residuals' (1),
 // each dequantized by the steps of its group maxima: terms = 3 or 4 products in one launch, where int8_terms_usable.
 bool int8_terms_usable(int M, int N, int K);
@@ -207,7 +211,7 @@ int launch_empty_product(int M, int N, GemmOut C, int32_t* Cint, hipStream_t st)
 #define LRQ_SUMS_MAX_PARTS 64       // (tile, range) pairs at most
 size_t int8_gemm_sums_scratch_bytes(int M, int N, int K);
 int launch_int8_gemm_sums(int M, int N, int K, const int8_t* Aq, const int8_t* BqT, int32_t* Cint, int resident,
-                          int32_t* part, hipStream_t st);
+                          int32_t* part, hipStream_t st, bool packed = false);
 int launch_int8_gemm_sums_finish(int M, int N, int K, const int8_t* Aq, const int8_t* BqT, int32_t* Cint, int resident,
                                  const int32_t* part, hipStream_t st);
 // True when the large-tile kernel may be asked for raw int32 sums: launch_int8_gemm with C == null and Cint != null (sA, sB are

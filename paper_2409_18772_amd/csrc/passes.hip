@@ -54,7 +54,8 @@ struct WStage {
 // Quantization fused into the first residual product (the sketch pass): with the group maxima known, one
 // read of the operand yields both its codes and Y = R.Omega.  amax: the group maxima (rows of X for AXIS 0,
 // columns for AXIS 1); lam_out / s_out: the step vectors lambda = qmax/amax, s = amax/qmax that the later
-// passes read; codes: rows x cols row-major (AXIS 0) or transposed, cols x rows (AXIS 1).
+// passes read; codes: rows x cols row-major (AXIS 0) or transposed, cols x rows (AXIS 1), or the same matrix packed.
+enum { QOUT_NONE = 0, QOUT_BYTES = 1, QOUT_PACKED = 2 };
 struct QOut {
     const float* amax;
     float* lam_out;
@@ -435,7 +436,7 @@ struct WStageBf16 {
 // of the reduction, when it is not whole, through clamped loads (the branch is the same for all waves); rows past
 // the end re-read the last row and are not stored.  FULL: every chunk is whole and, with the code output, so are the
 // row blocks -- without the branches a 512 x 4096 operand (24 columns) factors 4 % faster, 4096^3 0.7 %.
-template <int NT, int PL, bool QOUT, int NW, int KC>
+template <int NT, int PL, int QOUT, int NW, int KC>
 struct NSmem {
     static constexpr int RB = 16 * NW;      // rows per workgroup
     static constexpr int LDK = WStageBf16<NT, KC, 64 * NW, PL>::LDK;
@@ -444,7 +445,7 @@ struct NSmem {
     uint16_t wl[2][PL * NT * 16 * LDK];
     float sl[2][2 * KC];                    // per-column lambda | step of the chunk (AXIS 1)
 };
-template <int NT, int AXIS, int PL, bool QOUT, int NW, int KC, bool FULL>
+template <int NT, int AXIS, int PL, int QOUT, int NW, int KC, bool FULL>
 __device__ __forceinline__ void resid_mul_n_bf16_body(const PassJob& job, QuantParams q, int bx, int by,
                                                       NSmem<NT, PL, QOUT, NW, KC>& sm) {
     LRQ_PASS_JOB(job);
@@ -510,11 +511,29 @@ __device__ __forceinline__ void resid_mul_n_bf16_body(const PassJob& job, QuantP
     // QOUT: the RB x KC code tile of a chunk is staged in LDS (two tiles, so the chunk loop keeps its single
     // barrier) and leaves for global memory one chunk later, 16 bytes per thread.  Tile rows are X rows (AXIS 0,
     // codes row-major) or X columns (AXIS 1, codes transposed).  16-byte stores at any alignment; the last group of
-    // a row of codes byte by byte when it is not whole.
+    // a row of codes byte by byte when it is not whole.  Packed: one lane of a block (32 codes) per thread.
     auto flush_codes = [&](int tb, int kprev) {
         constexpr int PIECES = CTW * CTL / 16;
         const int r0 = AXIS == 0 ? bx * RB : kprev, nrow = AXIS == 0 ? rows : cols;
         const int c0 = AXIS == 0 ? kprev : bx * RB, ld = AXIS == 0 ? cols : rows;
+        if constexpr (QOUT == QOUT_PACKED) {        // whole blocks of 32 rows x 64 codes; a wave stores one
+            const int nrb = (nrow + 31) >> 5, nkb = pk_kblocks(ld);
+            for (int e = threadIdx.x; e < CTW * CTL / 32; e += THREADS) {
+                const int l = e & 63, b = e >> 6, rb = b % (CTW / 32), cb = b / (CTW / 32);
+                if ((r0 >> 5) + rb >= nrb || (c0 >> 6) + cb >= nkb) continue;
+                const int seg = 64 * cb + 32 * (l >> 5);
+                const uint4* src = reinterpret_cast<const uint4*>(&ct[tb][(32 * rb + (l & 31)) * CTS + seg]);
+                const uint4 lo = src[0], hi = src[1];
+                uint32_t t[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+                if (AXIS == 1) {
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) t[j] = squeeze_six(t[j]);
+                }
+                store_packed(reinterpret_cast<uint8_t*>(qo.codes) + ((size_t)((r0 >> 5) + rb) * nkb + (c0 >> 6) + cb) * PK_BLOCK, l, t,
+                             ld - c0 - seg);
+            }
+            return;
+        }
         int8_t* const base = qo.codes + (size_t)r0 * ld + c0;
         const bool whole = FULL || (r0 + CTW <= nrow && c0 + CTL <= ld);      // uniform
         for (int e = threadIdx.x; e < PIECES; e += THREADS) {
@@ -569,11 +588,14 @@ __device__ __forceinline__ void resid_mul_n_bf16_body(const PassJob& job, QuantP
                         res[4 * h + 1] = quant_code_residual<RM>(xv.y, l4.y, s4.y, q, c1);
                         res[4 * h + 2] = quant_code_residual<RM>(xv.z, l4.z, s4.z, q, c2);
                         res[4 * h + 3] = quant_code_residual<RM>(xv.w, l4.w, s4.w, q, c3);
-                        const int i0 = (int)c0, i1 = (int)c1, i2 = (int)c2, i3 = (int)c3;
+                        constexpr bool SIX = QOUT == QOUT_PACKED;
+                        const int i0 = SIX ? (int)six_bits(c0) : (int)c0, i1 = SIX ? (int)six_bits(c1) : (int)c1;
+                        const int i2 = SIX ? (int)six_bits(c2) : (int)c2, i3 = SIX ? (int)six_bits(c3) : (int)c3;
                         const int lr = wave * 16 + r;     // row inside the workgroup
-                        if (AXIS == 0) {    // four codes along the row: one packed word
-                            const uint32_t pk = (uint32_t)(i0 & 0xff) | ((uint32_t)(i1 & 0xff) << 8) |
-                                                ((uint32_t)(i2 & 0xff) << 16) | ((uint32_t)(i3 & 0xff) << 24);
+                        if (AXIS == 0) {    // four codes along the row: one word (packed: of 24 bits)
+                            const uint32_t pk = SIX ? (uint32_t)(i0 | (i1 << 6) | (i2 << 12) | (i3 << 18))
+                                                    : (uint32_t)(i0 & 0xff) | ((uint32_t)(i1 & 0xff) << 8) |
+                                                          ((uint32_t)(i2 & 0xff) << 16) | ((uint32_t)(i3 & 0xff) << 24);
                             *reinterpret_cast<uint32_t*>(&ct[buf][lr * CTS + 16 * j + 4 * g]) = pk;
                         } else {            // four columns of the transposed tile
                             int8_t* cp = &ct[buf][(16 * j + 4 * g) * CTS + lr];
@@ -623,7 +645,7 @@ __device__ __forceinline__ void resid_mul_n_bf16_body(const PassJob& job, QuantP
         }
 }
 
-template <int NT, int PL, bool QOUT, int NW, int KC, bool FULL>
+template <int NT, int PL, int QOUT, int NW, int KC, bool FULL>
 __global__ __launch_bounds__(64 * NW, NT <= 2 ? 4 : (NT <= 3 ? 3 : 2)) void resid_mul_n_bf16_kernel(PassJob a, PassJob b, int nb0,
                                                                                               QuantParams q) {
     __shared__ __align__(16) NSmem<NT, PL, QOUT, NW, KC> sm;
@@ -847,6 +869,119 @@ __global__ __launch_bounds__(512, 4) void codes_mul_rows_kernel(CodesJobBf16 j0,
         load_tile(x, tile);
         process(x, tile);
     }
+}
+
+// The same product from packed codes, at every K and width, with the same products in the same order (the same bits).  Lane
+// (li, kq) needs codes 16 kq .. +16 of a row's 64: half of a lane's 24 bytes of the block, which it loads whole; one conversion
+// instruction makes the 32 bfloat16 values of its two 16-row tiles.  A wave owns a block of 32 rows; slabs of four k blocks, the
+// planes staged as above.
+template <int NT, int PL>
+__global__ __launch_bounds__(256, 1) void codes_mul_packed_kernel(CodesJobBf16 j0, CodesJobBf16 j1, int K, int Kp) {
+    using S = CodesShape<NT, PL>;
+    constexpr int RP = S::RP, KB = S::KB, LDK = S::LDK, NC = S::NC;
+    typedef uint32_t v6u __attribute__((ext_vector_type(6)));
+    typedef __bf16 v32bf __attribute__((ext_vector_type(32)));
+    __shared__ __align__(16) uint16_t bs[PL * RP * LDK];
+    const CodesJobBf16 job = blockIdx.z == 0 ? j0 : j1;
+    if ((int)blockIdx.x * 128 >= job.rows || (int)blockIdx.y >= job.splits) return;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int li = lane & 15, kq = lane >> 4;
+    const int nkb = pk_kblocks(K), nrb = (job.rows + 31) >> 5;
+    const int rb = blockIdx.x * 4 + wave;
+    const int kb = blockIdx.y * job.chunk, ke = min(K, kb + job.chunk);
+    // (blocks past the end: the last one again, never stored)
+    const uint8_t* const ap = reinterpret_cast<const uint8_t*>(job.Cq) + (size_t)min(rb, nrb - 1) * nkb * PK_BLOCK;
+    const int unit = 32 * (kq >> 1) + li;
+    v4f acc[2][NT];
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = (v4f){0.f, 0.f, 0.f, 0.f};
+    struct Codes { uint4 w[NC][2]; uint2 x[NC][2]; };
+    auto load = [&](Codes& c, int ks) {
+#pragma unroll
+        for (int i = 0; i < NC; ++i) {
+            const uint8_t* blk = ap + (size_t)min(ks / PK_K + i, nkb - 1) * PK_BLOCK;
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt) {
+                c.w[i][mt] = *reinterpret_cast<const uint4*>(blk + (unit + 16 * mt) * 16);
+                c.x[i][mt] = *reinterpret_cast<const uint2*>(blk + 1024 + (unit + 16 * mt) * 8);
+            }
+        }
+    };
+    for (int ks = kb; ks < ke; ks += KB) {
+        Codes ca;
+        load(ca, ks);
+        if (ks > kb) __syncthreads();       // previous slab no longer read
+        for (int p0 = threadIdx.x; p0 < S::PIECES; p0 += 256 * S::BATCH) {
+            uint4 t[S::BATCH];
+#pragma unroll
+            for (int u = 0; u < S::BATCH; ++u) {
+                const int p = min(p0 + 256 * u, S::PIECES - 1);
+                const int rowp = p / (KB / 8), seg = p - rowp * (KB / 8);
+                const int k = ks + 8 * seg;
+                const uint4 v = *reinterpret_cast<const uint4*>(job.Bp + (size_t)rowp * Kp + min(k, Kp - 8));
+                t[u] = (k < Kp) ? v : make_uint4(0u, 0u, 0u, 0u);
+            }
+#pragma unroll
+            for (int u = 0; u < S::BATCH; ++u) {
+                const int p = p0 + 256 * u;
+                if (p < S::PIECES) {
+                    const int rowp = p / (KB / 8), seg = p - rowp * (KB / 8);
+                    *reinterpret_cast<uint4*>(&bs[rowp * LDK + 8 * seg]) = t[u];
+                }
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            if (ks + 64 * c < ke) {             // uniform
+                uint32_t h[2][3];
+#pragma unroll
+                for (int mt = 0; mt < 2; ++mt) {
+                    const uint4 w = ca.w[c][mt];
+                    const uint2 x = ca.x[c][mt];
+                    h[mt][0] = (kq & 1) ? w.w : w.x;        // (stored order: words 0 1 2 3 | 4 5)
+                    h[mt][1] = (kq & 1) ? x.x : w.y;
+                    h[mt][2] = (kq & 1) ? x.y : w.z;
+                }
+                const v6u six = {h[0][0], h[0][1], h[0][2], h[1][0], h[1][1], h[1][2]};
+                const v32bf val = __builtin_amdgcn_cvt_scalef32_pk32_bf16_fp6(six, 8.0f);
+#pragma unroll
+                for (int sidx = 0; sidx < 2; ++sidx) {
+                    v8bf af[2];
+                    if (sidx == 0) {
+                        af[0] = __builtin_shufflevector(val, val, 0, 1, 2, 3, 4, 5, 6, 7);
+                        af[1] = __builtin_shufflevector(val, val, 16, 17, 18, 19, 20, 21, 22, 23);
+                    } else {
+                        af[0] = __builtin_shufflevector(val, val, 8, 9, 10, 11, 12, 13, 14, 15);
+                        af[1] = __builtin_shufflevector(val, val, 24, 25, 26, 27, 28, 29, 30, 31);
+                    }
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                        for (int pl = 0; pl < PL; ++pl) {
+                            union { uint4 u; v8bf v; } b;
+                            b.u = *reinterpret_cast<const uint4*>(
+                                &bs[(pl * RP + 16 * nt + li) * LDK + 64 * c + 16 * kq + 8 * sidx]);
+#pragma unroll
+                            for (int mt = 0; mt < 2; ++mt)
+                                acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[mt], b.v, acc[mt][nt], 0, 0, 0);
+                        }
+                }
+            }
+        }
+    }
+    float* out = job.partial + (size_t)blockIdx.y * job.rows * RP;
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int row = rb * 32 + 16 * mt + 4 * kq + v;
+                if (row < job.rows) out[(size_t)row * RP + 16 * nt + li] = acc[mt][nt][v];
+            }
 }
 
 // ---------------------------------------------------------------------------
@@ -1247,7 +1382,7 @@ PassPair make_pair(const PassOperand* op, int nop, bool t_type, int rows_per_wg)
 // matrix cores are nowhere near busy and splitting operands into planes only adds work; the
 // conv-shaped workload with l = 8 measures 0.37 ms against 0.39 ms), except in the quantizing pass, which has no float32
 // form; wider ones use the bf16 kernels.
-template <int NT, int PL, bool QOUT>
+template <int NT, int PL, int QOUT>
 static int dispatch_n(const PassOperand* op, int nop, QuantParams q, hipStream_t st) {
     bool wide = NT >= 4, full = true;
     for (int i = 0; i < nop; ++i) wide = wide && pass_n_wide(op[i].rows, op[i].cols, 16 * NT);
@@ -1310,15 +1445,16 @@ static int dispatch_t(const PassOperand* op, int nop, QuantParams q, hipStream_t
         else                  NT_SWITCH(LP / 16, return (F<NT_, 3 __VA_ARGS__))        \
     } while (0)
 
-int launch_resid_mul_n(const PassOperand* op, int nop, QuantParams q, int LP, bool quantize, hipStream_t st, int planes) {
-    if (quantize) LRQ_NT_PL(dispatch_n, , true>(op, nop, q, st));
+int launch_resid_mul_n(const PassOperand* op, int nop, QuantParams q, int LP, bool quantize, hipStream_t st, int planes, bool packed) {
+    if (quantize && packed) LRQ_NT_PL(dispatch_n, , QOUT_PACKED>(op, nop, q, st));
+    if (quantize) LRQ_NT_PL(dispatch_n, , QOUT_BYTES>(op, nop, q, st));
     if (LP == 16 && planes == 3) {
         const PassPair p = make_pair(op, nop, false, 64);
         hipLaunchKernelGGL(resid_mul_n_kernel, LRQ_PAIR_ARGS(p, 256));
         LRQ_CHECK_LAUNCH();
         return LRQMM_OK;
     }
-    LRQ_NT_PL(dispatch_n, , false>(op, nop, q, st));
+    LRQ_NT_PL(dispatch_n, , QOUT_NONE>(op, nop, q, st));
     return LRQMM_ERR_UNSUPPORTED;
 }
 
@@ -1367,9 +1503,17 @@ int launch_resid_mul_t(const PassOperand* op, int nop, QuantParams q, int LP, hi
 
 int launch_codes_mul_n2(const int8_t* codesA, int rowsA, const uint16_t* WA3, PassPlan planA,
                         float* partialA, const int8_t* codesB, int rowsB, const uint16_t* WB3,
-                        PassPlan planB, float* partialB, int K, int Kp, int LP, hipStream_t st, int planes) {
+                        PassPlan planB, float* partialB, int K, int Kp, int LP, hipStream_t st, int planes, bool packed) {
     const CodesJobBf16 j0 = {codesA, WA3, partialA, rowsA, planA.chunk, planA.splits};
     const CodesJobBf16 j1 = {codesB, WB3, partialB, rowsB, planB.chunk, planB.splits};
+    if (packed) {
+        const dim3 grid(ceil_div(max(rowsA, rowsB), 128), max(planA.splits, planB.splits), 2);
+#define LRQ_CMP(PLV) NT_SWITCH(LP / 16, hipLaunchKernelGGL((codes_mul_packed_kernel<NT_, PLV>), grid, dim3(256), 0, st, j0, j1, K, Kp))
+        if (planes == 2) { LRQ_CMP(2); } else if (planes == 1) { LRQ_CMP(1); } else { LRQ_CMP(3); }
+#undef LRQ_CMP
+        LRQ_CHECK_LAUNCH();
+        return LRQMM_OK;
+    }
     if (K < 16) {       // (then the factor has at most 15 columns)
         if (LP != 16) return LRQMM_ERR_UNSUPPORTED;
         dim3 g1(ceil_div(max(rowsA, rowsB), 128), max(planA.splits, planB.splits), 2);

@@ -250,6 +250,25 @@ def test_guard_free_pass_kernels_equal_the_guarded_ones_bitwise(M, N, K, r, p):
     assert np.array_equal(to_np(_separate_calls(L, dA, dB, 4, r, p, 1, 9)), C)
 
 
+# Codes of up to five bits travel packed inside the call.  Edges of the 32-row and 64-code blocks (one short, whole, one over), odd
+# numbers of k blocks and fewer than the stages of the product, 128 x 128 / 64 x 128 / 64 x 64 / 256 x 256 tiles, tiles cut along K
+# beside the SVDs, and the longest reduction that 5-bit sums leave exact (the next one takes bytes).
+PACKED = [(128, 96, 128, 4, 24, 8), (127, 97, 191, 4, 20, 8), (129, 160, 193, 2, 17, 0), (320, 321, 385, 5, 24, 8),
+          (1025, 1000, 449, 3, 40, 8), (2080, 2049, 320, 4, 17, 0), (3100, 2900, 200, 4, 36, 0), (4096, 4096, 1024, 4, 32, 8),
+          (64, 96, 65536, 5, 17, 0), (96, 64, 65540, 5, 17, 0)]
+
+
+@pytest.mark.parametrize("M,N,K,bits,r,p", PACKED)
+def test_packed_codes_give_the_bits_of_the_separate_calls(M, N, K, bits, r, p):
+    """The separate calls quantize to bytes and multiply on the int8 matrix cores: integer sums are the same, and so are all
+    roundings behind them."""
+    import paper_2409_18772_amd as L
+    dA, dB = to_dev(wl.random_matrix("normal", M, K, seed=91)), to_dev(wl.random_matrix("uniform_pm1", K, N, seed=92))
+    say("packed codes", M, N, K, "bits", bits, r, p)
+    C = to_np(L.lrqmm_matmul(dA, dB, bits, r, p, 1, seed=9))
+    assert np.array_equal(to_np(_separate_calls(L, dA, dB, bits, r, p, 1, 9)), C)
+
+
 # Extents below one 16-byte load (four values), one operand at a time and together: N < 4 against long rows of A, K < 4
 # against wide rows of B, both, M < 4; the last shape has enough elements for the two-stream schedule.
 TINY_EXTENTS = [(100, 1, 300, 1), (70, 3, 517, 3), (100, 2, 1000, 1), (90, 200, 3, 2), (100, 100, 3, 1), (300, 2, 1, 1),
