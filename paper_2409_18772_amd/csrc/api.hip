@@ -685,7 +685,8 @@ int lrqmm_matmul_ex(int M, int N, int K, int bits, int rank, int oversample, int
     const bool overlap = one_read || (factored && two_chains(M, N, K));
     // Packed codes wherever they are exact and no larger than the bytes they stand in for (all but the smallest extents).  The
     // one-read kernel leaves bytes: its products are short and bound by the store of C.
-    const bool packed = factored && !one_read && codes_packable(bits, K) && pk_bytes(M, K) <= (size_t)M * K &&
+    const bool pair = !factored && !per_tensor && quantize_pair_usable(M, N, K);
+    const bool packed = (pair || (factored && !one_read)) && codes_packable(bits, K) && pk_bytes(M, K) <= (size_t)M * K &&
                         pk_bytes(N, K) <= (size_t)N * K;
     const int slot = (g_prof.on && g_prof.ncalls < kProfMaxCalls) ? g_prof.ncalls++ : -1;
     hipStream_t bst = overlap ? side->stream : pst;
@@ -714,9 +715,9 @@ int lrqmm_matmul_ex(int M, int N, int K, int bits, int rank, int oversample, int
     mark(opsA, 0, pst);
     mark(overlap ? opsB : opsA, 3, bst);
     if (!factored) {
-        if (!per_tensor && quantize_pair_usable(M, N, K)) {
+        if (pair) {
             opsA.push_back([=] {
-                return launch_quantize_pair(A, lda, B, ldb, M, N, K, qp, QuantPair{w.Aq, w.BqT, w.amaxA, w.amaxB}, pst);
+                return launch_quantize_pair(A, lda, B, ldb, M, N, K, qp, QuantPair{w.Aq, w.BqT, w.amaxA, w.amaxB}, pst, packed);
             });
         } else if (K > 0) {
             opsA.push_back([=] { return lrqmm_quantize_ex(A, lda, M, K, LRQMM_AXIS_ROW, bits, round_mode, scale_mode, w.Aq, w.amaxA, pst); });

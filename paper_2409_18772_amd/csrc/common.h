@@ -178,6 +178,26 @@ __device__ __forceinline__ void store_packed(uint8_t* __restrict__ blk, int lane
                                                             (t[2] >> 16) | (t[3] << 8), t[4] | (t[5] << 24));
     *reinterpret_cast<uint2*>(blk + 1024 + lane * 8) = make_uint2((t[5] >> 8) | (t[6] << 16), (t[6] >> 16) | (t[7] << 8));
 }
+// A tile of codes in LDS (TW rows of TL codes, stride TS bytes; a word of 24 bits per four codes, or BYTES of six) -> its blocks:
+// row block r0 / 32, k block c0 / 64 on; a wave stores one block at a time.
+template <int TW, int TL, int TS, bool BYTES>
+__device__ __forceinline__ void store_packed_tile(const int8_t* tile, uint8_t* __restrict__ codes, int r0, int rows, int c0, int K,
+                                                  int tid, int threads) {
+    const int nrb = (rows + 31) >> 5, nkb = pk_kblocks(K);
+    for (int e = tid; e < TW * TL / 32; e += threads) {
+        const int l = e & 63, b = e >> 6, rb = b % (TW / 32), cb = b / (TW / 32);
+        if ((r0 >> 5) + rb >= nrb || (c0 >> 6) + cb >= nkb) continue;
+        const int seg = 64 * cb + 32 * (l >> 5);
+        const uint4* src = reinterpret_cast<const uint4*>(&tile[(32 * rb + (l & 31)) * TS + seg]);
+        const uint4 lo = src[0], hi = src[1];
+        uint32_t t[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+        if (BYTES) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) t[j] = squeeze_six(t[j]);
+        }
+        store_packed(codes + ((size_t)((r0 >> 5) + rb) * nkb + (c0 >> 6) + cb) * PK_BLOCK, l, t, K - c0 - seg);
+    }
+}
 
 #define LRQ_CHECK_LAUNCH()                                   \
     do {                                                     \

@@ -22,8 +22,9 @@ struct QuantPair {
     int8_t *codesRA, *codesRB;
     float *amaxRA, *amaxRB;
 };
+// packed: packed codes (see PK_BLOCK), first level only.
 int launch_quantize_pair(const float* A, int lda, const float* B, int ldb, int M, int N, int K, QuantParams q, QuantPair o,
-                         hipStream_t st);
+                         hipStream_t st, bool packed = false);
 // The group maxima alone: row maxima of A (M x K) and column maxima of B (K x N; amaxB cleared by the caller on this
 // stream) in one launch, and with per_tensor their maxima in a second.  M or N may be 0: the other operand alone.
 int launch_absmax_pair(const float* A, int lda, int M, int K, float* amaxA, const float* B, int ldb, int N,

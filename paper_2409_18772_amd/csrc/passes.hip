@@ -516,22 +516,8 @@ __device__ __forceinline__ void resid_mul_n_bf16_body(const PassJob& job, QuantP
         constexpr int PIECES = CTW * CTL / 16;
         const int r0 = AXIS == 0 ? bx * RB : kprev, nrow = AXIS == 0 ? rows : cols;
         const int c0 = AXIS == 0 ? kprev : bx * RB, ld = AXIS == 0 ? cols : rows;
-        if constexpr (QOUT == QOUT_PACKED) {        // whole blocks of 32 rows x 64 codes; a wave stores one
-            const int nrb = (nrow + 31) >> 5, nkb = pk_kblocks(ld);
-            for (int e = threadIdx.x; e < CTW * CTL / 32; e += THREADS) {
-                const int l = e & 63, b = e >> 6, rb = b % (CTW / 32), cb = b / (CTW / 32);
-                if ((r0 >> 5) + rb >= nrb || (c0 >> 6) + cb >= nkb) continue;
-                const int seg = 64 * cb + 32 * (l >> 5);
-                const uint4* src = reinterpret_cast<const uint4*>(&ct[tb][(32 * rb + (l & 31)) * CTS + seg]);
-                const uint4 lo = src[0], hi = src[1];
-                uint32_t t[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-                if (AXIS == 1) {
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) t[j] = squeeze_six(t[j]);
-                }
-                store_packed(reinterpret_cast<uint8_t*>(qo.codes) + ((size_t)((r0 >> 5) + rb) * nkb + (c0 >> 6) + cb) * PK_BLOCK, l, t,
-                             ld - c0 - seg);
-            }
+        if constexpr (QOUT == QOUT_PACKED) {
+            store_packed_tile<CTW, CTL, CTS, AXIS == 1>(ct[tb], reinterpret_cast<uint8_t*>(qo.codes), r0, nrow, c0, ld, threadIdx.x, THREADS);
             return;
         }
         int8_t* const base = qo.codes + (size_t)r0 * ld + c0;

@@ -269,6 +269,20 @@ def test_packed_codes_give_the_bits_of_the_separate_calls(M, N, K, bits, r, p):
     assert np.array_equal(to_np(_separate_calls(L, dA, dB, bits, r, p, 1, 9)), C)
 
 
+# The same without a factorization: rows in the registers of a wave or (beyond 4096 codes) of a workgroup, in one to four loads, rows
+# that end inside a load, 16-row groups that end early.
+@pytest.mark.parametrize("M,N,K,bits", [(256, 256, 64, 4), (131, 97, 193, 4), (65, 100, 1030, 5), (300, 130, 4096, 2), (70, 64, 4099, 4),
+                                        (97, 300, 9001, 4), (2100, 2300, 700, 4)])
+def test_packed_codes_without_a_factorization(M, N, K, bits):
+    import paper_2409_18772_amd as L
+    dA, dB = to_dev(wl.random_matrix("normal", M, K, seed=93)), to_dev(wl.random_matrix("uniform_pm1", K, N, seed=94))
+    say("packed codes, rank 0", M, N, K, "bits", bits)
+    C = to_np(L.lrqmm_matmul(dA, dB, bits, 0))
+    Aq, amA = L.lrqmm_quantize(dA, L.AXIS_ROW, bits)
+    BqT, amB = L.lrqmm_quantize(dB, L.AXIS_COL, bits)
+    assert np.array_equal(to_np(L.lrqmm_gemm(Aq, amA, BqT, amB, bits)), C)
+
+
 # Extents below one 16-byte load (four values), one operand at a time and together: N < 4 against long rows of A, K < 4
 # against wide rows of B, both, M < 4; the last shape has enough elements for the two-stream schedule.
 TINY_EXTENTS = [(100, 1, 300, 1), (70, 3, 517, 3), (100, 2, 1000, 1), (90, 200, 3, 2), (100, 100, 3, 1), (300, 2, 1, 1),
