@@ -102,8 +102,8 @@ struct MatmulWs {
 
 size_t carve_matmul(Arena& a, int M, int N, int K, int rank, int oversample, MatmulWs* w) {
     MatmulWs t = {};
-    t.Aq = a.take<int8_t>((size_t)M * K);
-    t.BqT = a.take<int8_t>((size_t)N * K);
+    t.Aq = a.take<int8_t>(pk_bytes(M, K, PK8));         // (the most of any format)
+    t.BqT = a.take<int8_t>(pk_bytes(N, K, PK8));
     t.amaxA = a.take<float>(M);
     t.amaxB = a.take<float>(N);
     t.tick = a.take<uint32_t>(64);
@@ -326,11 +326,11 @@ enum class FirstPass {
 // Appends the launches of one factorization, or of two that advance together (one launch per step for both; their
 // operands have different axes), to `ops`.  The sketches are in place.  svd_index: position of the small SVD.
 // basis_suffices: the caller only uses the product U diag(Sigma) Vt, and nothing is truncated (oversample == 0): U = Q,
-// Sigma = 1, Vt = Q^T R carry the same product as the SVD's factors.  packed: the quantizing pass leaves packed codes.
+// Sigma = 1, Vt = Q^T R carry the same product as the SVD's factors.  packed: the format of the quantizing pass's codes.
 static void factor_launches(LaunchList& ops, const Factor* factors, int n, FirstPass first, QuantParams q, int rank,
                             int oversample, int power_iters, int planes_first, int planes, int planes_last, hipStream_t st,
                             size_t* svd_index, float* one_read_amax = nullptr, bool basis_suffices = false,
-                            bool packed = false) {
+                            int packed = PK_NONE) {
     struct Pair { Factor f[2]; PassOperand op[2]; };
     auto p = std::make_shared<Pair>();
     for (int i = 0; i < n; ++i) { p->f[i] = factors[i]; p->op[i] = factors[i].op; }
@@ -537,7 +537,7 @@ static int gemm_impl(int M, int N, int K, int bits, int rank, const int8_t* Aq, 
                      const int8_t* BqT, const float* amaxB, const float* U, const float* Sig, const float* Vt,
                      const float* W, const float* Gam, const float* Zt, GemmOut out, int32_t* Cint_or_null,
                      void* workspace, size_t workspace_bytes, void* stream, int prof_slot,
-                     hipEvent_t raw_sums_ready = nullptr, int planes = 3, bool packed = false) {
+                     hipEvent_t raw_sums_ready = nullptr, int planes = 3, int packed = PK_NONE) {
     float* const C = out.C;
     if (M < 0 || N < 0 || K < 0 || rank < 0 || out.ldc < N) return LRQMM_ERR_INVALID_ARG;
     if (!dims_ok(M, N, K) || !output_ok(M, N)) return LRQMM_ERR_UNSUPPORTED;
@@ -683,11 +683,9 @@ int lrqmm_matmul_ex(int M, int N, int K, int bits, int rank, int oversample, int
     const bool short_rows = factored && !per_tensor && quant_sketch_rows_usable(A, lda, M, K, LP, w.Aq);
     const bool one_read = short_rows && M >= LRQ_ONE_READ_MIN_ROWS;
     const bool overlap = one_read || (factored && two_chains(M, N, K));
-    // Packed codes wherever they are exact and no larger than the bytes they stand in for (all but the smallest extents).  The
-    // one-read kernel leaves bytes: its products are short and bound by the store of C.
+    // The one-read kernel leaves rows of bytes: its products are short and bound by the store of C.
     const bool pair = !factored && !per_tensor && quantize_pair_usable(M, N, K);
-    const bool packed = (pair || (factored && !one_read)) && codes_packable(bits, K) && pk_bytes(M, K) <= (size_t)M * K &&
-                        pk_bytes(N, K) <= (size_t)N * K;
+    const int packed = pair || (factored && !one_read) ? packed_format(bits, K) : PK_NONE;
     const int slot = (g_prof.on && g_prof.ncalls < kProfMaxCalls) ? g_prof.ncalls++ : -1;
     hipStream_t bst = overlap ? side->stream : pst;
     // Early integer GEMM: with both factorizations in their single-workgroup SVD the GPU is
@@ -834,10 +832,10 @@ struct ResidualWs {
 };
 size_t carve_residual(Arena& a, int M, int N, int K, ResidualWs* w) {
     ResidualWs t = {};
-    t.Aq = a.take<int8_t>((size_t)M * K);
-    t.RAq = a.take<int8_t>((size_t)M * K);
-    t.BqT = a.take<int8_t>((size_t)N * K);
-    t.RBqT = a.take<int8_t>((size_t)N * K);
+    t.Aq = a.take<int8_t>(pk_bytes(M, K, PK8));
+    t.RAq = a.take<int8_t>(pk_bytes(M, K, PK8));
+    t.BqT = a.take<int8_t>(pk_bytes(N, K, PK8));
+    t.RBqT = a.take<int8_t>(pk_bytes(N, K, PK8));
     t.amaxA = a.take<float>(M);
     t.amaxRA = a.take<float>(M);
     t.amaxB = a.take<float>(N);
@@ -875,12 +873,13 @@ int lrqmm_residual_matmul(int M, int N, int K, int bits, int terms, int round_mo
     Arena a(workspace);
     if (carve_residual(a, M, N, K, &w) > workspace_bytes) return LRQMM_ERR_WORKSPACE;
     if (K == 0) terms = 1;
-    int rc;
+    int rc, packed = PK_NONE;
     if (scale_mode == LRQMM_SCALE_VECTOR && quantize_pair_usable(M, N, K)) {
+        if (terms == 4 && int8_terms_usable(M, N, K)) packed = packed_format(bits, K);
         QuantPair o = {w.Aq, w.BqT, w.amaxA, w.amaxB};
         if (terms >= 3) { o.codesRA = w.RAq; o.codesRB = w.RBqT; o.amaxRA = w.amaxRA; o.amaxRB = w.amaxRB; }
         LRQ_TRY(launch_quantize_pair(A, lda, B, ldb, M, N, K, make_quant_params(bits, round_mode), o,
-                                     static_cast<hipStream_t>(stream)));
+                                     static_cast<hipStream_t>(stream), packed));
     } else if (K > 0) {
         LRQ_TRY(lrqmm_quantize_ex(A, lda, M, K, LRQMM_AXIS_ROW, bits, round_mode, scale_mode, w.Aq, w.amaxA, stream));
         LRQ_TRY(lrqmm_quantize_ex(B, ldb, K, N, LRQMM_AXIS_COL, bits, round_mode, scale_mode, w.BqT, w.amaxB, stream));
@@ -898,7 +897,7 @@ int lrqmm_residual_matmul(int M, int N, int K, int bits, int terms, int round_mo
         const int8_t *const Acodes[2] = {w.Aq, w.RAq}, *const Bcodes[2] = {w.BqT, w.RBqT};
         const float *const amA[2] = {w.amaxA, w.amaxRA}, *const amB[2] = {w.amaxB, w.amaxRB};
         return launch_int8_terms(M, N, K, Acodes, amA, Bcodes, amB, terms, make_quant_params(bits, round_mode).qmaxf,
-                                 GemmOut{D, ldd, alpha, beta}, static_cast<hipStream_t>(stream));
+                                 GemmOut{D, ldd, alpha, beta}, static_cast<hipStream_t>(stream), packed);
     }
     // one integer GEMM per term of Eq. (gemm_r_split), each dequantized with the scales of its two
     // operands and accumulated into D through the GEMM's own alpha/beta update

@@ -147,19 +147,24 @@ __device__ __forceinline__ uint4 tail16(uint4 v, int sh) {
     return make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
 }
 
-// ---- codes of at most five bits, packed for the fp6 matrix cores ----
-// The magnitudes 0 .. 16 are the first seventeen values of the six-bit e2m3 format in units of 1/8 (its subnormals and the first
-// binades continue each other), so a code of up to five bits is exact in it, sign and magnitude, and so is a product of two.
-// v_mfma_f32_32x32x64_f8f6f4 takes such operands at twice the rate of the int8 instructions, from 3/4 of the bytes, and adds in
-// float32, where integers are exact below 2^24: the sums are the int8 matrix cores' sums (times 1/64).  Measured on random 4-bit
-// codes, int8 / this: 4096^3 59 / 46 us, 16384^3 3.99 / 2.56 ms; operands in registers 2.4 / 5.0 POP/s.
-// Layout: [row block of 32][k block of 64][PK_BLOCK bytes], a block being a matrix-core operand of a wave: lane l holds row
-// l % 32, codes 32 (l / 32) .. +32 of the block (24 bytes, code e in bits 6 e ..); first the lanes' bytes 0 .. 15, then 16 .. 23, so
-// that both LDS reads of a wave are contiguous.  Codes past K are zero; rows past the end of a block hold anything.
-#define PK_BLOCK 1536
+// ---- packed codes: the order of the matrix cores' operands ----
+// Inside a call codes travel as blocks that a wave loads whole, or copies to LDS as they are: [row block of 32][k block of 64]
+// [pk_block bytes], a block being an operand of 32 rows and 64 k: lane l holds row l % 32, codes 32 (l / 32) .. +32 of the block.
+// Codes past K are zero; rows past the end of a block hold anything.  Two formats:
+//   PK8: bytes, 32 per lane: first the lanes' codes 0 .. 15, then 16 .. 31, two operands of v_mfma_i32_32x32x32_i8 (which takes the
+//   k of a block in another order than the memory's, A and B alike).
+//   PK6: codes of at most five bits.  The magnitudes 0 .. 16 are the first seventeen values of the six-bit e2m3 format in units of
+//   1/8 (its subnormals and the first binades continue each other), so a code is exact in it, sign and magnitude, and so is a
+//   product of two.  v_mfma_f32_32x32x64_f8f6f4 takes such operands at twice the rate of the int8 instructions, from 3/4 of the
+//   bytes, and adds in float32, where integers are exact below 2^24: the sums are the int8 matrix cores' sums (times 1/64).
+//   Measured on random 4-bit codes, int8 from rows of codes / this: 4096^3 59 / 46 us, 16384^3 3.99 / 2.56 ms; operands in registers
+//   2.4 / 5.0 POP/s.  24 bytes per lane (code e in bits 6 e ..): first the lanes' bytes 0 .. 15, then 16 .. 23.
+// Both LDS reads of a wave are contiguous.
+enum { PK_NONE = 0, PK6 = 6, PK8 = 8 };
 #define PK_K 64
+__host__ __device__ static constexpr int pk_block(int fmt) { return fmt == PK6 ? 1536 : 2048; }
 __host__ __device__ static inline int pk_kblocks(int K) { return (K + PK_K - 1) / PK_K; }
-static inline size_t pk_bytes(int rows, int K) { return (size_t)((rows + 31) / 32) * pk_kblocks(K) * PK_BLOCK; }
+static inline size_t pk_bytes(int rows, int K, int fmt) { return (size_t)((rows + 31) / 32) * pk_kblocks(K) * pk_block(fmt); }
 
 // Sign and magnitude of a code that is given as a float.
 __device__ __forceinline__ uint32_t six_bits(float c) { return (uint32_t)fabsf(c) | ((__float_as_uint(c) >> 26) & 32u); }
@@ -168,19 +173,28 @@ __device__ __forceinline__ uint32_t squeeze_six(uint32_t w) {
     const uint32_t t = (w & 0x003f003fu) | ((w >> 2) & 0x0fc00fc0u);
     return (t & 0xfffu) | ((t >> 4) & 0xfff000u);
 }
-// 32 codes as eight words of 24 bits -> a lane's 24 bytes of block `blk`; valid: codes from this one on are zeroed.
+// 32 codes as eight words of four (PK6: 24 bits each) -> a lane's part of block `blk`; valid: codes from this one on are zeroed.
+template <int FMT>
 __device__ __forceinline__ void store_packed(uint8_t* __restrict__ blk, int lane, uint32_t (&t)[8], int valid) {
     if (valid < 32) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) t[j] &= (1u << (6 * max(0, min(4, valid - 4 * j)))) - 1u;
+        for (int j = 0; j < 8; ++j) {
+            const int v = max(0, min(4, valid - 4 * j));
+            t[j] &= v == 4 ? 0xffffffffu : (1u << (FMT * v)) - 1u;
+        }
+    }
+    if (FMT == PK8) {
+        *reinterpret_cast<uint4*>(blk + lane * 16) = make_uint4(t[0], t[1], t[2], t[3]);
+        *reinterpret_cast<uint4*>(blk + 1024 + lane * 16) = make_uint4(t[4], t[5], t[6], t[7]);
+        return;
     }
     *reinterpret_cast<uint4*>(blk + lane * 16) = make_uint4(t[0] | (t[1] << 24), (t[1] >> 8) | (t[2] << 16),
                                                             (t[2] >> 16) | (t[3] << 8), t[4] | (t[5] << 24));
     *reinterpret_cast<uint2*>(blk + 1024 + lane * 8) = make_uint2((t[5] >> 8) | (t[6] << 16), (t[6] >> 16) | (t[7] << 8));
 }
-// A tile of codes in LDS (TW rows of TL codes, stride TS bytes; a word of 24 bits per four codes, or BYTES of six) -> its blocks:
-// row block r0 / 32, k block c0 / 64 on; a wave stores one block at a time.
-template <int TW, int TL, int TS, bool BYTES>
+// A tile of codes in LDS (TW rows of TL codes, stride TS bytes; PK6: a word of 24 bits per four codes, or BYTES of six) -> its
+// blocks: row block r0 / 32, k block c0 / 64 on; a wave stores one block at a time.
+template <int FMT, int TW, int TL, int TS, bool BYTES>
 __device__ __forceinline__ void store_packed_tile(const int8_t* tile, uint8_t* __restrict__ codes, int r0, int rows, int c0, int K,
                                                   int tid, int threads) {
     const int nrb = (rows + 31) >> 5, nkb = pk_kblocks(K);
@@ -191,11 +205,11 @@ __device__ __forceinline__ void store_packed_tile(const int8_t* tile, uint8_t* _
         const uint4* src = reinterpret_cast<const uint4*>(&tile[(32 * rb + (l & 31)) * TS + seg]);
         const uint4 lo = src[0], hi = src[1];
         uint32_t t[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-        if (BYTES) {
+        if (FMT == PK6 && BYTES) {
 #pragma unroll
             for (int j = 0; j < 8; ++j) t[j] = squeeze_six(t[j]);
         }
-        store_packed(codes + ((size_t)((r0 >> 5) + rb) * nkb + (c0 >> 6) + cb) * PK_BLOCK, l, t, K - c0 - seg);
+        store_packed<FMT>(codes + ((size_t)((r0 >> 5) + rb) * nkb + (c0 >> 6) + cb) * pk_block(FMT), l, t, K - c0 - seg);
     }
 }
 

@@ -54,7 +54,7 @@ __device__ __forceinline__ const int8_t* code_row(const int8_t* __restrict__ bas
 __device__ __forceinline__ float code_sum(int a) { return (float)a; }
 __device__ __forceinline__ float code_sum(float a) { return a * 64.0f; }
 
-// ---- main loop on packed codes (see PK_BLOCK) ----
+// ---- main loop on packed codes (see PK8, PK6) ----
 // A wave's 64 lanes copy 16 bytes each from global memory to 1 KB of LDS, without registers in between.
 // (m0 is set here for this one instruction; the compiler sets it before each use of its own.)
 __device__ __forceinline__ void load_to_lds(uint32_t lds, const uint8_t* base, uint32_t off) {
@@ -62,6 +62,11 @@ __device__ __forceinline__ void load_to_lds(uint32_t lds, const uint8_t* base, u
 }
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) uint8_t lds_u8;
+// Sums of a 32 x 32 tile: int32, or float32 in units of 1/64 (exact either way).
+template <int FMT> using PackedSum = std::conditional_t<FMT == PK6, v16f, v16i>;
+
+template <int H>
+__device__ __forceinline__ v4i half(const v8i& v) { return __builtin_shufflevector(v, v, 4 * H, 4 * H + 1, 4 * H + 2, 4 * H + 3); }
 
 // acc += the tile's products over nk k blocks from kb0 on.  The tile is BA row blocks of A (from ra0) by BB of B (from rb0), a wave
 // MT x NT of them (from wa, wb inside the tile); ST stages of LDS hold one k block of the tile each.  The copies of ST - 3 k
@@ -70,10 +75,12 @@ typedef __attribute__((address_space(3))) uint8_t lds_u8;
 // divide.  Row and k blocks past the end: the last one again.  At 16384^3 it reaches 3.4 POP/s of the 5.0 of operands in
 // registers (one k block ahead instead of its operands, 128-deep stages: 3.35); with operand bits that do not change 4.1, so
 // it is the power that bounds it.
-template <int MT, int NT, int BA, int BB, int NW, int ST>
+template <int FMT, int MT, int NT, int BA, int BB, int NW, int ST, bool STACK = false>
 __device__ __forceinline__ void packed_products(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, int ra0, int nra, int rb0,
                                                 int nrb, int nkb, int kb0, int nk, uint8_t* sm, int wave, int lane, int wa, int wb,
-                                                v16f (&acc)[MT][NT]) {
+                                                PackedSum<FMT> (&acc)[MT][NT], const uint8_t* __restrict__ A1 = nullptr,
+                                                const uint8_t* __restrict__ B1 = nullptr) {
+    constexpr int PK_BLOCK = pk_block(FMT);
     constexpr int STAGE = (BA + BB) * PK_BLOCK, PIECES = STAGE / 1024, PER = (PIECES + NW - 1) / NW;
     static_assert(STAGE % 1024 == 0 && BA * PK_BLOCK % 1024 == 0, "pieces belong to one operand");
     const size_t rowb = (size_t)nkb * PK_BLOCK;
@@ -84,8 +91,14 @@ __device__ __forceinline__ void packed_products(const uint8_t* __restrict__ A, c
     for (int u = 0; u < PER; ++u) {
         const int piece = min(wave * PER + u, PIECES - 1);
         const bool isb = piece >= BA * PK_BLOCK / 1024;
-        const int at = (piece - (isb ? BA * PK_BLOCK / 1024 : 0)) * 1024 + lane * 16, r = at / PK_BLOCK;
-        src[u] = (isb ? B + (size_t)rb0 * rowb : A + (size_t)ra0 * rowb) + (size_t)kb0 * PK_BLOCK;
+        int pi = piece - (isb ? BA * PK_BLOCK / 1024 : 0);
+        const uint8_t* operand = isb ? B : A;
+        if constexpr (STACK) {
+            const int h = (isb ? BB : BA) / 2 * PK_BLOCK / 1024;
+            if (pi >= h) { pi -= h; operand = isb ? B1 : A1; }
+        }
+        const int at = pi * 1024 + lane * 16, r = at / PK_BLOCK;
+        src[u] = operand + (size_t)(isb ? rb0 : ra0) * rowb + (size_t)kb0 * PK_BLOCK;
         off[u] = (uint32_t)(min(r, (isb ? nrb - rb0 : nra - ra0) - 1) * rowb) + at % PK_BLOCK;
         dst[u] = base + piece * 1024;
     }
@@ -97,6 +110,10 @@ __device__ __forceinline__ void packed_products(const uint8_t* __restrict__ A, c
     struct Frag { v8i a[MT], b[NT]; };
     auto operand = [&](const uint8_t* p) {
         const v4i lo = *reinterpret_cast<const v4i*>(p + lane * 16);
+        if constexpr (FMT == PK8) {
+            const v4i h4 = *reinterpret_cast<const v4i*>(p + 1024 + lane * 16);
+            return (v8i){lo.x, lo.y, lo.z, lo.w, h4.x, h4.y, h4.z, h4.w};
+        }
         const int2 hi = *reinterpret_cast<const int2*>(p + 1024 + lane * 8);
         return (v8i){lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, 0, 0};
     };
@@ -128,8 +145,19 @@ __device__ __forceinline__ void packed_products(const uint8_t* __restrict__ A, c
 #pragma unroll
         for (int m = 0; m < MT; ++m)
 #pragma unroll
-            for (int n = 0; n < NT; ++n)        // (2: e2m3 operands; scales of 1)
-                acc[m][n] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(cur.a[m], cur.b[n], acc[m][n], 2, 2, 0, 0, 0, 0);
+            for (int n = 0; n < NT; ++n) {
+                if constexpr (FMT == PK6)       // (2: e2m3 operands; scales of 1)
+                    acc[m][n] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(cur.a[m], cur.b[n], acc[m][n], 2, 2, 0, 0, 0, 0);
+                else
+                    acc[m][n] = __builtin_amdgcn_mfma_i32_32x32x32_i8(half<0>(cur.a[m]), half<0>(cur.b[n]), acc[m][n], 0, 0, 0);
+            }
+        if constexpr (FMT == PK8) {
+#pragma unroll
+            for (int m = 0; m < MT; ++m)
+#pragma unroll
+                for (int n = 0; n < NT; ++n)
+                    acc[m][n] = __builtin_amdgcn_mfma_i32_32x32x32_i8(half<1>(cur.a[m]), half<1>(cur.b[n]), acc[m][n], 0, 0, 0);
+        }
         __builtin_amdgcn_s_setprio(0);
         __builtin_amdgcn_sched_barrier(0);
         s = next;
@@ -223,8 +251,8 @@ __device__ __forceinline__ int xcd_tile(int id, int tiles_n, int ntiles) {
 // 4096 x 4096 rank 16 50.1 / 45.9 / 43.8; 4096 x 2048 x 2048 rank 80 186 / 134 / 123; short reductions, where the load latency
 // of the epilogue shows most, 128 x 8192 x 576 rank 80 85.3 / 88.8 / 82.1, 1024 x 1024 x 576 rank 48 45.8 / 47.5 / 43.7,
 // 100352 x 64 x 64 rank 8 33.7 / 34.1 / 31.7, 100352 x 16 x 16 31.5 / 32.7 / 30.4.
-// PACKED: packed codes instead of bytes; the same tiles and epilogue.
-template <bool WIDE, bool COMP, bool WCINT, int MTW, int NTW, bool PACKED>
+// PACKED: the format of packed codes, or PK_NONE for rows of bytes; the same tiles and epilogue.
+template <bool WIDE, bool COMP, bool WCINT, int MTW, int NTW, int PACKED>
 __global__ __launch_bounds__(256, 2) void int8_gemm_kernel(int M, int N, int K,
                                                            const int8_t* __restrict__ Aq,
                                                            const int8_t* __restrict__ BqT,
@@ -236,9 +264,11 @@ __global__ __launch_bounds__(256, 2) void int8_gemm_kernel(int M, int N, int K,
                                                            int32_t* __restrict__ Cint, int tiles_n,
                                                            int ntiles, float qmaxf) {
     constexpr int TMW = 64 * MTW, TNW = 64 * NTW;       // tile height and width
-    constexpr int ST = 6, LDP = 36;     // stages of packed codes; row stride of a panel chunk (conflict-free 16-byte reads)
-    constexpr int TILE_LDS = PACKED ? ST * (2 * MTW + 2 * NTW) * PK_BLOCK : 2 * (TMW + TNW) * BSTRIDE;
-    static_assert(TILE_LDS >= 2 * (TMW + TNW) * LDP * 4, "two chunks of the panel rows fit the operand tiles' LDS");
+    constexpr int ST = PACKED == PK8 && MTW + NTW == 4 ? 4 : 6;     // stages of packed codes (two workgroups share a CU's LDS)
+    constexpr int LDP = 36;             // row stride of a panel chunk (conflict-free 16-byte reads)
+    constexpr int OPERAND_LDS = PACKED ? ST * (2 * MTW + 2 * NTW) * pk_block(PACKED) : 2 * (TMW + TNW) * BSTRIDE;
+    constexpr int PANEL_LDS = 2 * (TMW + TNW) * LDP * 4;            // two chunks of the panel rows, in the operand tiles' LDS
+    constexpr int TILE_LDS = OPERAND_LDS > PANEL_LDS ? OPERAND_LDS : PANEL_LDS;
     __shared__ __align__(16) int8_t tiles[TILE_LDS];
     int8_t* const As[2] = {tiles, tiles + TMW * BSTRIDE};
     int8_t* const Bs[2] = {tiles + 2 * TMW * BSTRIDE, tiles + (2 * TMW + TNW) * BSTRIDE};
@@ -249,7 +279,7 @@ __global__ __launch_bounds__(256, 2) void int8_gemm_kernel(int M, int N, int K,
     const int wm = wave >> 1, wn = wave & 1;
     const int l32 = lane & 31, lh = lane >> 5;
 
-    std::conditional_t<PACKED, v16f, v16i> acc[MTW][NTW];
+    PackedSum<PACKED> acc[MTW][NTW];
 #pragma unroll
     for (int a = 0; a < MTW; ++a)
 #pragma unroll
@@ -300,10 +330,10 @@ __global__ __launch_bounds__(256, 2) void int8_gemm_kernel(int M, int N, int K,
     float st = 0.f;
     if (tid < TMW) st = sA[min(m0 + tid, M - 1)];
     else if (tid - TMW < TNW) st = sB[min(n0 + tid - TMW, N - 1)];
-    if constexpr (PACKED) {
+    if constexpr (PACKED != PK_NONE) {
         if constexpr (COMP) LRQ_PLOAD(0);
         if (tid < TMW + TNW) steps[tid] = COMP ? st : step_of(st, qmaxf);
-        packed_products<MTW, NTW, 2 * MTW, 2 * NTW, 4, ST>(reinterpret_cast<const uint8_t*>(Aq), reinterpret_cast<const uint8_t*>(BqT),
+        packed_products<PACKED, MTW, NTW, 2 * MTW, 2 * NTW, 4, ST>(reinterpret_cast<const uint8_t*>(Aq), reinterpret_cast<const uint8_t*>(BqT),
                                                            m0 >> 5, (M + 31) >> 5, n0 >> 5, (N + 31) >> 5, pk_kblocks(K), 0,
                                                            pk_kblocks(K), reinterpret_cast<uint8_t*>(tiles), wave, lane, wm * MTW,
                                                            wn * NTW, acc);
@@ -765,16 +795,16 @@ __global__ __launch_bounds__(512, 1) void int8_gemm256_kernel(int M, int N, int 
 }
 
 // The same tiles from packed codes.
-template <bool COMP, bool WCINT, bool SPLITK = false>
+template <int FMT, bool COMP, bool WCINT, bool SPLITK = false>
 __global__ __launch_bounds__(512, 1) void packed_gemm256_kernel(int M, int N, int K, const uint8_t* __restrict__ A,
                                                                 const uint8_t* __restrict__ B, const float* __restrict__ sA,
                                                                 const float* __restrict__ sB, const float* __restrict__ Lp,
                                                                 const float* __restrict__ Rp, int R2P, GemmOut out,
                                                                 int32_t* __restrict__ Cint, int tiles_n, int ntiles, int full_tiles,
                                                                 int slices, int32_t* __restrict__ part, float qmaxf) {
-    constexpr int ST = 6;
+    constexpr int ST = FMT == PK8 ? 4 : 6;
     __shared__ __align__(16) int8_t tiles[2 * LARGE_LDS];
-    static_assert(ST * 16 * PK_BLOCK <= 2 * LARGE_LDS, "the stages fit");
+    static_assert(ST * 16 * pk_block(FMT) <= 2 * LARGE_LDS, "the stages fit");
     int wg = blockIdx.x, kb0 = 0, nk = pk_kblocks(K);
     const int nkb = nk;
     bool partial = false;
@@ -791,14 +821,14 @@ __global__ __launch_bounds__(512, 1) void packed_gemm256_kernel(int M, int N, in
     const int tile = xcd_tile(wg, tiles_n, ntiles);
     const int m0 = (tile / tiles_n) * BTM, n0 = (tile % tiles_n) * BTN;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    v16f acc[2][4];
+    PackedSum<FMT> acc[2][4];
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll
         for (int b = 0; b < 4; ++b)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
-    packed_products<2, 4, 8, 8, 8, ST>(A, B, m0 >> 5, (M + 31) >> 5, n0 >> 5, (N + 31) >> 5, nkb, kb0, nk, reinterpret_cast<uint8_t*>(tiles),
+            for (int v = 0; v < 16; ++v) acc[a][b][v] = 0;
+    packed_products<FMT, 2, 4, 8, 8, 8, ST>(A, B, m0 >> 5, (M + 31) >> 5, n0 >> 5, (N + 31) >> 5, nkb, kb0, nk, reinterpret_cast<uint8_t*>(tiles),
                                        wave, lane, (wave >> 1) * 2, (wave & 1) * 4, acc);
     finish_large_tile<COMP, WCINT, SPLITK>(LargeTile{M, N, m0, n0, sA, sB, Lp, Rp, R2P, out, Cint, part, partial, qmaxf}, acc, tiles,
                                            tiles + LARGE_LDS);
@@ -976,6 +1006,98 @@ __global__ __launch_bounds__(128 * WM, WM == 4 ? 1 : 2) void int8_terms_kernel(i
                 if (row < M && col < N) out.C[(size_t)row * out.ldc + col] = f[mt][nt][v];
             }
         }
+}
+
+// Four products of the codes (0) and the residuals' codes (1) of both operands, packed: a 128 x 128 tile of D needs 128 rows of each of
+// the four code matrices, which stacked are the operands of one 256 x 256 tile of the kernel above, a product per quadrant.  So
+// every operand tile is read and staged once for two products, the matrix cores see 64 x 128 tiles per wave, and the quadrants
+// meet in LDS at the end, added in the order (and with the roundings) of one launch per product.  Four products of random codes, us,
+// int8_terms_kernel / this with bytes / with six bits: 300^3 16.5 / 14.7 / 13.5, 1024^3 26.2 / 22.4 / 18.8, 1537 x 1021 x 2311 79.5 /
+// 40.4 / 31.5, 2000^3 62.4 / 41.8 / 32.8, 3000^3 205 / 143 / 106, 4096^3 312 / 274 / 195, 5000^3 736 / 529 / 378, 8192^3 2239 / 1926 /
+// 1314.  (Three products would leave a quadrant idle: int8_terms_kernel.)
+template <int FMT>
+__global__ __launch_bounds__(512, 1) void packed_terms_kernel(int M, int N, int K, TermArgs t, float qmaxf, GemmOut out, int tiles_n,
+                                                              int ntiles) {
+    constexpr int ST = FMT == PK8 ? 4 : 6, T = 128, LD = T + 8;     // (+ 8: the two row groups of a wave's store on different banks)
+    __shared__ __align__(16) uint8_t stages[2 * LARGE_LDS];
+    __shared__ __align__(16) float steps[4 * T];
+    static_assert(ST * 16 * pk_block(FMT) <= 2 * LARGE_LDS && 2 * T * LD * 4 <= 2 * LARGE_LDS, "stages and two quadrants fit");
+    const int tile = xcd_tile(blockIdx.x, tiles_n, ntiles);
+    const int m0 = (tile / tiles_n) * T, n0 = (tile % tiles_n) * T;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int wm = wave >> 1, wn = wave & 1, l32 = lane & 31, lh = lane >> 5;
+    {
+        const int lvl = (tid >> 7) & 1, e = tid & 127;
+        steps[tid] = step_of(tid < 256 ? t.amaxA[lvl][min(m0 + e, M - 1)] : t.amaxB[lvl][min(n0 + e, N - 1)], qmaxf);
+    }
+    PackedSum<FMT> acc[2][4];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[a][b][v] = 0;
+    packed_products<FMT, 2, 4, 8, 8, 8, ST, true>(reinterpret_cast<const uint8_t*>(t.A[0]), reinterpret_cast<const uint8_t*>(t.B[0]), m0 >> 5,
+                                                  (M + 31) >> 5, n0 >> 5, (N + 31) >> 5, pk_kblocks(K), 0, pk_kblocks(K), stages, wave,
+                                                  lane, wm * 2, wn * 4, acc, reinterpret_cast<const uint8_t*>(t.A[1]),
+                                                  reinterpret_cast<const uint8_t*>(t.B[1]));
+    float* const quad = reinterpret_cast<float*>(stages);
+    const int crow = tid >> 5, ccol = (tid & 31) * 4;           // of this thread's sixteenth of the rows: crow + 16 i
+    float4 f[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) f[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    const int cols = min(4, N - n0 - ccol);                     // columns of this thread's groups inside D
+    if (out.beta != 0.f) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const float* p = out.C + (size_t)min(m0 + crow + 16 * i, M - 1) * out.ldc + n0 + ccol;
+            if (cols > 0) f[i].x = out.beta * p[0];
+            if (cols > 1) f[i].y = out.beta * p[1];
+            if (cols > 2) f[i].z = out.beta * p[2];
+            if (cols > 3) f[i].w = out.beta * p[3];
+        }
+    }
+#pragma unroll
+    for (int level = 0; level < 2; ++level) {
+        if (level) __syncthreads();
+        if ((wm >> 1) == level) {
+            const int rbase = (wm & 1) * 64 + 4 * lh;
+            float* const q = quad + wn * (T * LD);
+#pragma unroll
+            for (int nt = 0; nt < 4; ++nt) {
+                const float sb = steps[256 + wn * T + nt * 32 + l32];
+#pragma unroll
+                for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        const int row = rbase + mt * 32 + 8 * (v >> 2) + (v & 3);
+                        q[row * LD + nt * 32 + l32] = out.alpha * ((code_sum(acc[mt][nt][v]) * steps[level * T + row]) * sb);
+                    }
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                const float4 x = *reinterpret_cast<const float4*>(quad + b * (T * LD) + (crow + 16 * i) * LD + ccol);
+                f[i].x = x.x + f[i].x; f[i].y = x.y + f[i].y; f[i].z = x.z + f[i].z; f[i].w = x.w + f[i].w;
+            }
+    }
+    const bool whole = cols == 4 && (out.ldc & 3) == 0 && ((uintptr_t)out.C & 15) == 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int row = m0 + crow + 16 * i;
+        if (row >= M) continue;
+        float* p = out.C + (size_t)row * out.ldc + n0 + ccol;
+        if (whole) *reinterpret_cast<float4*>(p) = f[i];
+        else {
+            if (cols > 0) p[0] = f[i].x;
+            if (cols > 1) p[1] = f[i].y;
+            if (cols > 2) p[2] = f[i].z;
+            if (cols > 3) p[3] = f[i].w;
+        }
+    }
 }
 
 // The epilogue of the GEMM as a kernel of its own, for the schedule in which the integer
@@ -1484,14 +1606,16 @@ int launch_build_panels(int M, int N, int K, int r, int RP, int R2P, const float
 static void dispatch_gemm256(bool comp, bool wcint, dim3 grid, hipStream_t st, int M, int N, int K,
                              const int8_t* Aq, const int8_t* BqT, const float* sA, const float* sB,
                              const float* Lp, const float* Rp, int R2P, GemmOut C, int32_t* Cint, int tiles_n,
-                             int ntiles, float qmaxf, bool packed) {
+                             int ntiles, float qmaxf, int packed) {
     const bool full = aligned16(Aq) && aligned16(BqT) && (M % BTM == 0) && (N % BTN == 0) && (K % BBK == 0);
+#define LRQ_PACKED(FMT, COMP, WC)                                                                            \
+    hipLaunchKernelGGL((packed_gemm256_kernel<FMT, COMP, WC>), grid, dim3(512), 0, st, M, N, K,              \
+                       reinterpret_cast<const uint8_t*>(Aq), reinterpret_cast<const uint8_t*>(BqT), sA, sB, Lp, Rp, R2P, C, Cint, \
+                       tiles_n, ntiles, ntiles, 1, nullptr, qmaxf)
 #define LRQ_GEMM(COMP, WC)                                                                                   \
     do {                                                                                                     \
-        if (packed)                                                                                          \
-            hipLaunchKernelGGL((packed_gemm256_kernel<COMP, WC>), grid, dim3(512), 0, st, M, N, K,           \
-                               reinterpret_cast<const uint8_t*>(Aq), reinterpret_cast<const uint8_t*>(BqT), sA, sB, Lp, Rp, R2P, C, \
-                               Cint, tiles_n, ntiles, ntiles, 1, nullptr, qmaxf);                            \
+        if (packed == PK6) LRQ_PACKED(PK6, COMP, WC);                                                        \
+        else if (packed == PK8) LRQ_PACKED(PK8, COMP, WC);                                                   \
         else if (full)                                                                                       \
             hipLaunchKernelGGL((int8_gemm256_kernel<COMP, WC, true>), grid, dim3(512), 0, st, M, N, K, Aq, \
                                BqT, sA, sB, Lp, Rp, R2P, C, Cint, tiles_n, ntiles, ntiles, 1, nullptr, qmaxf); \
@@ -1505,9 +1629,10 @@ static void dispatch_gemm256(bool comp, bool wcint, dim3 grid, hipStream_t st, i
         if (wcint) LRQ_GEMM(false, true); else LRQ_GEMM(false, false);
     }
 #undef LRQ_GEMM
+#undef LRQ_PACKED
 }
 
-template <bool WIDE, int MTW, int NTW, bool PACKED>
+template <bool WIDE, int MTW, int NTW, int PACKED>
 static void dispatch_gemm(bool comp, bool wcint, dim3 grid, hipStream_t st, int M, int N, int K,
                           const int8_t* Aq, const int8_t* BqT, const float* sA, const float* sB,
                           const float* Lp, const float* Rp, int R2P, GemmOut C, int32_t* Cint, int tiles_n,
@@ -1566,16 +1691,19 @@ size_t int8_gemm_sums_scratch_bytes(int M, int N, int K) {
 }
 
 int launch_int8_gemm_sums(int M, int N, int K, const int8_t* Aq, const int8_t* BqT, int32_t* Cint, int resident,
-                          int32_t* part, hipStream_t st, bool packed) {
+                          int32_t* part, hipStream_t st, int packed) {
     const SumsPlan p = part ? plan_sums(M, N, K, Aq, BqT, resident) : SumsPlan{0, 0, 0, 1};
     if (p.left == 0)
         return launch_int8_gemm(M, N, K, Aq, BqT, nullptr, nullptr, nullptr, nullptr, 0, GemmOut{nullptr, N, 1.0f, 0.0f},
                                 Cint, 0.0f, st, packed);
     const int full_tiles = p.ntiles - p.left;
-    if (packed)
-        hipLaunchKernelGGL((packed_gemm256_kernel<false, true, true>), dim3(full_tiles + p.left * p.slices), dim3(512), 0, st, M, N, K,
-                           reinterpret_cast<const uint8_t*>(Aq), reinterpret_cast<const uint8_t*>(BqT), nullptr, nullptr, nullptr,
-                           nullptr, 0, GemmOut{nullptr, N, 1.0f, 0.0f}, Cint, p.tiles_n, p.ntiles, full_tiles, p.slices, part, 0.0f);
+#define LRQ_SUMS(FMT)                                                                                                                 \
+    hipLaunchKernelGGL((packed_gemm256_kernel<FMT, false, true, true>), dim3(full_tiles + p.left * p.slices), dim3(512), 0, st, M, N, \
+                       K, reinterpret_cast<const uint8_t*>(Aq), reinterpret_cast<const uint8_t*>(BqT), nullptr, nullptr, nullptr,     \
+                       nullptr, 0, GemmOut{nullptr, N, 1.0f, 0.0f}, Cint, p.tiles_n, p.ntiles, full_tiles, p.slices, part, 0.0f)
+    if (packed == PK6)      LRQ_SUMS(PK6);
+    else if (packed == PK8) LRQ_SUMS(PK8);
+#undef LRQ_SUMS
     else
         hipLaunchKernelGGL((int8_gemm256_kernel<false, true, true, true>), dim3(full_tiles + p.left * p.slices),
                            dim3(512), 0, st, M, N, K, Aq, BqT, nullptr, nullptr, nullptr, nullptr, 0,
@@ -1594,8 +1722,14 @@ int launch_int8_gemm_sums_finish(int M, int N, int K, const int8_t* Aq, const in
     return LRQMM_OK;
 }
 
-// Codes of at most five bits whose sums stay below 2^24.
-bool codes_packable(int bits, int K) { return bits <= 5 && ((long long)K << (2 * (bits - 1))) <= (1ll << 24); }
+// Six bits for codes of at most five whose sums stay below 2^24, bytes from six bits on.  Products of random 8-bit codes at rank 0,
+// us, from rows of bytes (staged through registers) / from blocks of bytes (copied to LDS as they are): 300^3 4.3 / 4.0, 1024^3 5.9 /
+// 5.7, 2000^3 20.8 / 16.9, 1537 x 1021 x 2311 19.6 / 11.2 (rows of an odd length), 512 x 4096 x 4096 19.8 / 16.4, 3072 x 1536 x 2048
+// 25.1 / 19.1, 3000^3 53.4 / 44.7, 5000^3 164 / 138, 8192^3 507 / 474; at 4096^3 and beyond the chip's power bounds both (77 to 87).
+int packed_format(int bits, int K) {
+    if (bits > 5) return PK8;
+    return ((long long)K << (2 * (bits - 1))) <= (1ll << 24) ? PK6 : PK_NONE;
+}
 
 long long int8_gemm_tiles(int M, int N) { return (long long)ceil_div(M, BTM) * ceil_div(N, BTN); }
 // The large-tile kernel pays from half a round of its tiles on (raw sums, where it is the only one that is asked for)
@@ -1635,9 +1769,16 @@ bool int8_terms_usable(int M, int N, int K) {
 }
 
 int launch_int8_terms(int M, int N, int K, const int8_t* const A[2], const float* const amaxA[2], const int8_t* const B[2],
-                      const float* const amaxB[2], int terms, float qmaxf, GemmOut out, hipStream_t st) {
-    if (!int8_terms_usable(M, N, K)) return LRQMM_ERR_UNSUPPORTED;
+                      const float* const amaxB[2], int terms, float qmaxf, GemmOut out, hipStream_t st, int packed) {
+    if (!int8_terms_usable(M, N, K) || (packed && terms != 4)) return LRQMM_ERR_UNSUPPORTED;
     TermArgs t = {{A[0], A[1]}, {B[0], B[1]}, {amaxA[0], amaxA[1]}, {amaxB[0], amaxB[1]}};
+    if (packed) {
+        const int tn = ceil_div(N, 128), nt = ceil_div(M, 128) * tn;
+        if (packed == PK6) hipLaunchKernelGGL(packed_terms_kernel<PK6>, dim3(nt), dim3(512), 0, st, M, N, K, t, qmaxf, out, tn, nt);
+        else               hipLaunchKernelGGL(packed_terms_kernel<PK8>, dim3(nt), dim3(512), 0, st, M, N, K, t, qmaxf, out, tn, nt);
+        LRQ_CHECK_LAUNCH();
+        return LRQMM_OK;
+    }
     const int tiles_n = ceil_div(N, TTN);
     // 256-row tiles, one per CU, where they fill their last round to 3/4, 256 / 128 rows, us: 2000^3 (0.50) 113 / 99, 2560^3 (0.78) 132 / 142,
     // 3072^3 (0.56) 256 / 234, 3500^3 (0.77) 349 / 381, 4096^3 (1) 377 / 401, 5000^3 (0.78) 895 / 903
@@ -1674,7 +1815,7 @@ int launch_empty_product(int M, int N, GemmOut C, int32_t* Cint, hipStream_t st)
 
 int launch_int8_gemm(int M, int N, int K, const int8_t* Aq, const int8_t* BqT, const float* sA,
                      const float* sB, const float* Lp, const float* Rp, int R2P, GemmOut C, int32_t* Cint,
-                     float qmaxf, hipStream_t st, bool packed) {
+                     float qmaxf, hipStream_t st, int packed) {
     // the GEMM kernels issue their first operand loads unconditionally: an empty reduction never reaches them
     if (K <= 0) return launch_empty_product(M, N, C, Cint, st);
     // (the 16-byte load path clamps its address to K - 16, so it needs at least one whole group)
@@ -1701,15 +1842,17 @@ int launch_int8_gemm(int M, int N, int K, const int8_t* Aq, const int8_t* BqT, c
     const int tiles_n = ceil_div(N, 64 * ntw), ntiles = (int)tiles();
     dim3 grid(ntiles);
 #define LRQ_DG(W, MT, NT, PK) dispatch_gemm<W, MT, NT, PK>(comp, Cint != nullptr, grid, st, M, N, K, Aq, BqT, sA, sB, Lp, Rp, R2P, C, Cint, tiles_n, ntiles, qmaxf)
-    if (packed) {
-        if (mtw == 2 && ntw == 2)  LRQ_DG(true, 2, 2, true);
-        else if (ntw == 2)         LRQ_DG(true, 1, 2, true);
-        else                       LRQ_DG(true, 1, 1, true);
-    }
-    else if (!wide)                LRQ_DG(false, 2, 2, false);
-    else if (mtw == 2 && ntw == 2) LRQ_DG(true, 2, 2, false);
-    else if (ntw == 2)             LRQ_DG(true, 1, 2, false);
-    else                           LRQ_DG(true, 1, 1, false);
+#define LRQ_DGS(W, PK)                                       \
+    do {                                                    \
+        if (mtw == 2 && ntw == 2) LRQ_DG(W, 2, 2, PK);      \
+        else if (ntw == 2)        LRQ_DG(W, 1, 2, PK);      \
+        else                      LRQ_DG(W, 1, 1, PK);      \
+    } while (0)
+    if (packed == PK6)      LRQ_DGS(true, PK6);
+    else if (packed == PK8) LRQ_DGS(true, PK8);
+    else if (!wide)         LRQ_DG(false, 2, 2, PK_NONE);
+    else                    LRQ_DGS(true, PK_NONE);
+#undef LRQ_DGS
 #undef LRQ_DG
     LRQ_CHECK_LAUNCH();
     return LRQMM_OK;

@@ -22,9 +22,9 @@ struct QuantPair {
     int8_t *codesRA, *codesRB;
     float *amaxRA, *amaxRB;
 };
-// packed: packed codes (see PK_BLOCK), first level only.
+// packed: the format of packed codes (see PK8, PK6), or PK_NONE for rows of bytes.
 int launch_quantize_pair(const float* A, int lda, const float* B, int ldb, int M, int N, int K, QuantParams q, QuantPair o,
-                         hipStream_t st, bool packed = false);
+                         hipStream_t st, int packed = PK_NONE);
 // The group maxima alone: row maxima of A (M x K) and column maxima of B (K x N; amaxB cleared by the caller on this
 // stream) in one launch, and with per_tensor their maxima in a second.  M or N may be 0: the other operand alone.
 int launch_absmax_pair(const float* A, int lda, int M, int K, float* amaxA, const float* B, int ldb, int N,
@@ -86,9 +86,9 @@ struct PassOperand {
 // N pass: partial[s][rows][LP] = R[:, chunk s] . W[chunk s, :].
 // quantize: the same launch quantizes the operands from their group maxima (amax): it writes the codes (row-major for
 // axis 0, transposed for axis 1) and the step vectors, then read by the later passes.
-// packed: the codes leave packed (see PK_BLOCK; codes is then 16-byte aligned and holds pk_bytes).
+// packed: the format in which the codes leave (not PK_NONE: codes is then 16-byte aligned and holds pk_bytes).
 int launch_resid_mul_n(const PassOperand* op, int nop, QuantParams q, int LP, bool quantize, hipStream_t st,
-                       int planes = 3, bool packed = false);
+                       int planes = 3, int packed = PK_NONE);
 // T pass: partial[s][cols][LP] = R[chunk s, :]^T . Y[chunk s, :].
 int launch_resid_mul_t(const PassOperand* op, int nop, QuantParams q, int LP, hipStream_t st, int planes = 3);
 // Row quantization and the sketch product from one read, for operands quantized by rows whose rows are short
@@ -116,7 +116,7 @@ int launch_quant_sketch_rows(const float* X, int ldx, int rows, int cols, QuantP
 int launch_codes_mul_n2(const int8_t* codesA, int rowsA, const uint16_t* WA3, PassPlan planA,
                         float* partialA, const int8_t* codesB, int rowsB, const uint16_t* WB3,
                         PassPlan planB, float* partialB, int K, int Kp, int LP, hipStream_t st, int planes = 3,
-                        bool packed = false);
+                        int packed = PK_NONE);
 
 // ---- orth.hip -----------------------------------------------------------
 // Every launch below takes one job or two (the two operands of a product, in one launch).
@@ -192,14 +192,15 @@ struct GemmOut {
 // (M x N, dense).  Without panels (Lp == null) sA, sB are the group maxima, turned into steps with qmaxf.
 int launch_int8_gemm(int M, int N, int K, const int8_t* Aq, const int8_t* BqT, const float* sA,
                      const float* sB, const float* Lp, const float* Rp, int R2P, GemmOut C,
-                     int32_t* Cint, float qmaxf, hipStream_t st, bool packed = false);
-// packed (here and below): both code matrices are packed (see PK_BLOCK), where codes_packable(bits, K); same results.
-bool codes_packable(int bits, int K);
+                     int32_t* Cint, float qmaxf, hipStream_t st, int packed = PK_NONE);
+// packed (here and below): the format of both code matrices; same results.
+// The format in which codes travel inside a call (PK_NONE: rows of bytes).
+int packed_format(int bits, int K);
 // D <- alpha (A0 B0 + A0 B1 + A1 B0 [+ A1 B1]) + beta D, the products of the operands' codes (0) and of their residuals' (1),
 // each dequantized by the steps of its group maxima: terms = 3 or 4 products in one launch, where int8_terms_usable.
 bool int8_terms_usable(int M, int N, int K);
 int launch_int8_terms(int M, int N, int K, const int8_t* const A[2], const float* const amaxA[2], const int8_t* const B[2],
-                      const float* const amaxB[2], int terms, float qmaxf, GemmOut out, hipStream_t st);
+                      const float* const amaxB[2], int terms, float qmaxf, GemmOut out, hipStream_t st, int packed = PK_NONE);
 // The product with an empty reduction (K == 0): D <- alpha * 0 + beta * D (D not read when beta == 0) and,
 // when Cint is given, zeros in Cint.  Reads no operand.
 int launch_empty_product(int M, int N, GemmOut C, int32_t* Cint, hipStream_t st);
@@ -212,7 +213,7 @@ int launch_empty_product(int M, int N, GemmOut C, int32_t* Cint, hipStream_t st)
 #define LRQ_SUMS_MAX_PARTS 64       // (tile, range) pairs at most
 size_t int8_gemm_sums_scratch_bytes(int M, int N, int K);
 int launch_int8_gemm_sums(int M, int N, int K, const int8_t* Aq, const int8_t* BqT, int32_t* Cint, int resident,
-                          int32_t* part, hipStream_t st, bool packed = false);
+                          int32_t* part, hipStream_t st, int packed = PK_NONE);
 int launch_int8_gemm_sums_finish(int M, int N, int K, const int8_t* Aq, const int8_t* BqT, int32_t* Cint, int resident,
                                  const int32_t* part, hipStream_t st);
 // True when the large-tile kernel may be asked for raw int32 sums: launch_int8_gemm with C == null and Cint != null (sA, sB are

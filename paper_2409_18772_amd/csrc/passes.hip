@@ -54,8 +54,8 @@ struct WStage {
 // Quantization fused into the first residual product (the sketch pass): with the group maxima known, one
 // read of the operand yields both its codes and Y = R.Omega.  amax: the group maxima (rows of X for AXIS 0,
 // columns for AXIS 1); lam_out / s_out: the step vectors lambda = qmax/amax, s = amax/qmax that the later
-// passes read; codes: rows x cols row-major (AXIS 0) or transposed, cols x rows (AXIS 1), or the same matrix packed.
-enum { QOUT_NONE = 0, QOUT_BYTES = 1, QOUT_PACKED = 2 };
+// passes read; codes: rows x cols row-major (AXIS 0) or transposed, cols x rows (AXIS 1), or the same matrix packed (PK6, PK8).
+enum { QOUT_NONE = 0, QOUT_BYTES = 1 };         // or PK6, PK8
 struct QOut {
     const float* amax;
     float* lam_out;
@@ -516,8 +516,8 @@ __device__ __forceinline__ void resid_mul_n_bf16_body(const PassJob& job, QuantP
         constexpr int PIECES = CTW * CTL / 16;
         const int r0 = AXIS == 0 ? bx * RB : kprev, nrow = AXIS == 0 ? rows : cols;
         const int c0 = AXIS == 0 ? kprev : bx * RB, ld = AXIS == 0 ? cols : rows;
-        if constexpr (QOUT == QOUT_PACKED) {
-            store_packed_tile<CTW, CTL, CTS, AXIS == 1>(ct[tb], reinterpret_cast<uint8_t*>(qo.codes), r0, nrow, c0, ld, threadIdx.x, THREADS);
+        if constexpr (QOUT == PK6 || QOUT == PK8) {
+            store_packed_tile<QOUT, CTW, CTL, CTS, AXIS == 1>(ct[tb], reinterpret_cast<uint8_t*>(qo.codes), r0, nrow, c0, ld, threadIdx.x, THREADS);
             return;
         }
         int8_t* const base = qo.codes + (size_t)r0 * ld + c0;
@@ -574,7 +574,7 @@ __device__ __forceinline__ void resid_mul_n_bf16_body(const PassJob& job, QuantP
                         res[4 * h + 1] = quant_code_residual<RM>(xv.y, l4.y, s4.y, q, c1);
                         res[4 * h + 2] = quant_code_residual<RM>(xv.z, l4.z, s4.z, q, c2);
                         res[4 * h + 3] = quant_code_residual<RM>(xv.w, l4.w, s4.w, q, c3);
-                        constexpr bool SIX = QOUT == QOUT_PACKED;
+                        constexpr bool SIX = QOUT == PK6;
                         const int i0 = SIX ? (int)six_bits(c0) : (int)c0, i1 = SIX ? (int)six_bits(c1) : (int)c1;
                         const int i2 = SIX ? (int)six_bits(c2) : (int)c2, i3 = SIX ? (int)six_bits(c3) : (int)c3;
                         const int lr = wave * 16 + r;     // row inside the workgroup
@@ -858,10 +858,10 @@ __global__ __launch_bounds__(512, 4) void codes_mul_rows_kernel(CodesJobBf16 j0,
 }
 
 // The same product from packed codes, at every K and width, with the same products in the same order (the same bits).  Lane
-// (li, kq) needs codes 16 kq .. +16 of a row's 64: half of a lane's 24 bytes of the block, which it loads whole; one conversion
-// instruction makes the 32 bfloat16 values of its two 16-row tiles.  A wave owns a block of 32 rows; slabs of four k blocks, the
+// (li, kq) needs codes 16 kq .. +16 of a row's 64: PK8: 16 bytes of the block; PK6: half of a lane's 24 bytes, which it loads whole,
+// and one conversion instruction makes the 32 bfloat16 values of its two 16-row tiles.  A wave owns a block of 32 rows; slabs of four k blocks, the
 // planes staged as above.
-template <int NT, int PL>
+template <int FMT, int NT, int PL>
 __global__ __launch_bounds__(256, 1) void codes_mul_packed_kernel(CodesJobBf16 j0, CodesJobBf16 j1, int K, int Kp) {
     using S = CodesShape<NT, PL>;
     constexpr int RP = S::RP, KB = S::KB, LDK = S::LDK, NC = S::NC;
@@ -876,20 +876,24 @@ __global__ __launch_bounds__(256, 1) void codes_mul_packed_kernel(CodesJobBf16 j
     const int rb = blockIdx.x * 4 + wave;
     const int kb = blockIdx.y * job.chunk, ke = min(K, kb + job.chunk);
     // (blocks past the end: the last one again, never stored)
-    const uint8_t* const ap = reinterpret_cast<const uint8_t*>(job.Cq) + (size_t)min(rb, nrb - 1) * nkb * PK_BLOCK;
+    const uint8_t* const ap = reinterpret_cast<const uint8_t*>(job.Cq) + (size_t)min(rb, nrb - 1) * nkb * pk_block(FMT);
     const int unit = 32 * (kq >> 1) + li;
     v4f acc[2][NT];
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = (v4f){0.f, 0.f, 0.f, 0.f};
-    struct Codes { uint4 w[NC][2]; uint2 x[NC][2]; };
+    struct Codes { uint4 w[NC][2]; uint2 x[FMT == PK6 ? NC : 1][2]; };
     auto load = [&](Codes& c, int ks) {
 #pragma unroll
         for (int i = 0; i < NC; ++i) {
-            const uint8_t* blk = ap + (size_t)min(ks / PK_K + i, nkb - 1) * PK_BLOCK;
+            const uint8_t* blk = ap + (size_t)min(ks / PK_K + i, nkb - 1) * pk_block(FMT);
 #pragma unroll
             for (int mt = 0; mt < 2; ++mt) {
+                if constexpr (FMT == PK8) {
+                    c.w[i][mt] = *reinterpret_cast<const uint4*>(blk + 1024 * (kq & 1) + (unit + 16 * mt) * 16);
+                    continue;
+                }
                 c.w[i][mt] = *reinterpret_cast<const uint4*>(blk + (unit + 16 * mt) * 16);
                 c.x[i][mt] = *reinterpret_cast<const uint2*>(blk + 1024 + (unit + 16 * mt) * 8);
             }
@@ -922,21 +926,28 @@ __global__ __launch_bounds__(256, 1) void codes_mul_packed_kernel(CodesJobBf16 j
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
             if (ks + 64 * c < ke) {             // uniform
-                uint32_t h[2][3];
+                v32bf val;
+                if constexpr (FMT == PK6) {
+                    uint32_t h[2][3];
 #pragma unroll
-                for (int mt = 0; mt < 2; ++mt) {
-                    const uint4 w = ca.w[c][mt];
-                    const uint2 x = ca.x[c][mt];
-                    h[mt][0] = (kq & 1) ? w.w : w.x;        // (stored order: words 0 1 2 3 | 4 5)
-                    h[mt][1] = (kq & 1) ? x.x : w.y;
-                    h[mt][2] = (kq & 1) ? x.y : w.z;
+                    for (int mt = 0; mt < 2; ++mt) {
+                        const uint4 w = ca.w[c][mt];
+                        const uint2 x = ca.x[c][mt];
+                        h[mt][0] = (kq & 1) ? w.w : w.x;        // (stored order: words 0 1 2 3 | 4 5)
+                        h[mt][1] = (kq & 1) ? x.x : w.y;
+                        h[mt][2] = (kq & 1) ? x.y : w.z;
+                    }
+                    const v6u six = {h[0][0], h[0][1], h[0][2], h[1][0], h[1][1], h[1][2]};
+                    val = __builtin_amdgcn_cvt_scalef32_pk32_bf16_fp6(six, 8.0f);
                 }
-                const v6u six = {h[0][0], h[0][1], h[0][2], h[1][0], h[1][1], h[1][2]};
-                const v32bf val = __builtin_amdgcn_cvt_scalef32_pk32_bf16_fp6(six, 8.0f);
 #pragma unroll
                 for (int sidx = 0; sidx < 2; ++sidx) {
                     v8bf af[2];
-                    if (sidx == 0) {
+                    if constexpr (FMT == PK8) {
+#pragma unroll
+                        for (int mt = 0; mt < 2; ++mt)
+                            af[mt] = sidx == 0 ? codes_to_bf16(ca.w[c][mt].x, ca.w[c][mt].y) : codes_to_bf16(ca.w[c][mt].z, ca.w[c][mt].w);
+                    } else if (sidx == 0) {
                         af[0] = __builtin_shufflevector(val, val, 0, 1, 2, 3, 4, 5, 6, 7);
                         af[1] = __builtin_shufflevector(val, val, 16, 17, 18, 19, 20, 21, 22, 23);
                     } else {
@@ -1431,8 +1442,9 @@ static int dispatch_t(const PassOperand* op, int nop, QuantParams q, hipStream_t
         else                  NT_SWITCH(LP / 16, return (F<NT_, 3 __VA_ARGS__))        \
     } while (0)
 
-int launch_resid_mul_n(const PassOperand* op, int nop, QuantParams q, int LP, bool quantize, hipStream_t st, int planes, bool packed) {
-    if (quantize && packed) LRQ_NT_PL(dispatch_n, , QOUT_PACKED>(op, nop, q, st));
+int launch_resid_mul_n(const PassOperand* op, int nop, QuantParams q, int LP, bool quantize, hipStream_t st, int planes, int packed) {
+    if (quantize && packed == PK6) LRQ_NT_PL(dispatch_n, , PK6>(op, nop, q, st));
+    if (quantize && packed == PK8) LRQ_NT_PL(dispatch_n, , PK8>(op, nop, q, st));
     if (quantize) LRQ_NT_PL(dispatch_n, , QOUT_BYTES>(op, nop, q, st));
     if (LP == 16 && planes == 3) {
         const PassPair p = make_pair(op, nop, false, 64);
@@ -1489,13 +1501,14 @@ int launch_resid_mul_t(const PassOperand* op, int nop, QuantParams q, int LP, hi
 
 int launch_codes_mul_n2(const int8_t* codesA, int rowsA, const uint16_t* WA3, PassPlan planA,
                         float* partialA, const int8_t* codesB, int rowsB, const uint16_t* WB3,
-                        PassPlan planB, float* partialB, int K, int Kp, int LP, hipStream_t st, int planes, bool packed) {
+                        PassPlan planB, float* partialB, int K, int Kp, int LP, hipStream_t st, int planes, int packed) {
     const CodesJobBf16 j0 = {codesA, WA3, partialA, rowsA, planA.chunk, planA.splits};
     const CodesJobBf16 j1 = {codesB, WB3, partialB, rowsB, planB.chunk, planB.splits};
     if (packed) {
         const dim3 grid(ceil_div(max(rowsA, rowsB), 128), max(planA.splits, planB.splits), 2);
-#define LRQ_CMP(PLV) NT_SWITCH(LP / 16, hipLaunchKernelGGL((codes_mul_packed_kernel<NT_, PLV>), grid, dim3(256), 0, st, j0, j1, K, Kp))
-        if (planes == 2) { LRQ_CMP(2); } else if (planes == 1) { LRQ_CMP(1); } else { LRQ_CMP(3); }
+#define LRQ_CMP(FMT, PLV) NT_SWITCH(LP / 16, hipLaunchKernelGGL((codes_mul_packed_kernel<FMT, NT_, PLV>), grid, dim3(256), 0, st, j0, j1, K, Kp))
+        if (packed == PK8) { if (planes == 2) { LRQ_CMP(PK8, 2); } else if (planes == 1) { LRQ_CMP(PK8, 1); } else { LRQ_CMP(PK8, 3); } }
+        else               { if (planes == 2) { LRQ_CMP(PK6, 2); } else if (planes == 1) { LRQ_CMP(PK6, 1); } else { LRQ_CMP(PK6, 3); } }
 #undef LRQ_CMP
         LRQ_CHECK_LAUNCH();
         return LRQMM_OK;

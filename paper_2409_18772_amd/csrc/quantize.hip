@@ -268,11 +268,11 @@ __global__ __launch_bounds__(256) void quant_pair_kernel(const float* __restrict
     }
 }
 
-// The same with packed codes (see PK_BLOCK), without the second level.  A workgroup of WG threads takes WG / TPR rows, so that
+// The same with packed codes (see PK8, PK6).  A workgroup of WG threads takes WG / TPR rows, so that
 // the lanes of a block that it stores are 128 bytes (64 beyond 4096 columns) next to each other; the codes cross the waves through
 // LDS.  On B's side it works as workgroups of 256.  (16 rows a workgroup, 256 bytes: 65 KB of LDS and 16 waves leave one per CU, a call
 // of 4096^3 93.5 us against 89.7.)
-template <int WG, int TPR, int NV>
+template <int FMT, int WG, int TPR, int NV, bool RES>
 __global__ __launch_bounds__(WG) void quant_pair_packed_kernel(const float* __restrict__ A, int lda, int M, int K, QuantPair o, int nbA,
                                                                  const float* __restrict__ B, int ldb, int N, int rows_per_block,
                                                                  QuantParams q, int col_blocks, int col_jobs) {
@@ -290,49 +290,57 @@ __global__ __launch_bounds__(WG) void quant_pair_packed_kernel(const float* __re
     const int row0 = blockIdx.x * ROWS, row = row0 + r;
     const float* xp = A + (size_t)min(row, M - 1) * lda;
     float4 v[NV];
-    float m = 0.0f;
 #pragma unroll
     for (int u = 0; u < NV; ++u) v[u] = load_quad<false>(xp, (t + TPR * u) * 4, K);
-#pragma unroll
-    for (int u = 0; u < NV; ++u)
-        m = fmaxf(fmaxf(m, fabsf(v[u].x)), fmaxf(fabsf(v[u].y), fmaxf(fabsf(v[u].z), fabsf(v[u].w))));
-    m = wave_max(m);
-    if (TPR == 256) {
-        if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = m;
-        __syncthreads();
-        m = fmaxf(fmaxf(wmax[4 * r], wmax[4 * r + 1]), fmaxf(wmax[4 * r + 2], wmax[4 * r + 3]));
-    }
-    if (row < M && t == 0) o.amaxA[row] = m;
-    float lam, s;
-    make_scales(m, q.qmaxf, lam, s);
     const int nkb = pk_kblocks(K);
 #pragma unroll
-    for (int u = 0; u < NV; ++u) {
-        const int k = (t + TPR * u) * 4;
-        if (k >= nkb * PK_K) continue;
-        uint32_t w = six_bits(quant_code(v[u].x, lam, q)) | six_bits(quant_code(v[u].y, lam, q)) << 6 |
-                     six_bits(quant_code(v[u].z, lam, q)) << 12 | six_bits(quant_code(v[u].w, lam, q)) << 18;
-        const int past = k - (K - 4);           // (the row's last four values stand in where the quad crosses its end)
-        if (past > 0) w = past < 4 ? w >> (6 * past) : 0u;
-        words[r * LDW + (k >> 2)] = w;
-    }
-    __syncthreads();
-    for (int e = threadIdx.x; e < ROWS * 2 * nkb; e += WG) {
-        const int rr = e % ROWS, unit = e / ROWS, orow = row0 + rr;
-        if (orow >= M) continue;
-        const uint4* src = reinterpret_cast<const uint4*>(&words[rr * LDW + 8 * unit]);
-        const uint4 lo = src[0], hi = src[1];
-        uint32_t w[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-        store_packed(reinterpret_cast<uint8_t*>(o.codesA) + ((size_t)(orow >> 5) * nkb + (unit >> 1)) * PK_BLOCK,
-                     32 * (unit & 1) + (orow & 31), w, 32);
+    for (int level = 0; level < (RES ? 2 : 1); ++level) {
+        if (level) __syncthreads();         // the first level's codes have left, its maxima are read
+        float m = 0.0f;
+#pragma unroll
+        for (int u = 0; u < NV; ++u)
+            m = fmaxf(fmaxf(m, fabsf(v[u].x)), fmaxf(fabsf(v[u].y), fmaxf(fabsf(v[u].z), fabsf(v[u].w))));
+        m = wave_max(m);
+        if (TPR == 256) {
+            if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = m;
+            __syncthreads();
+            m = fmaxf(fmaxf(wmax[4 * r], wmax[4 * r + 1]), fmaxf(wmax[4 * r + 2], wmax[4 * r + 3]));
+        }
+        if (row < M && t == 0) (level == 0 ? o.amaxA : o.amaxRA)[row] = m;
+        float lam, s;
+        make_scales(m, q.qmaxf, lam, s);
+#pragma unroll
+        for (int u = 0; u < NV; ++u) {
+            const int k = (t + TPR * u) * 4;
+            if (k < nkb * PK_K) {
+                uint32_t w;
+                if constexpr (FMT == PK8) w = pack_codes(v[u], lam, q);
+                else w = six_bits(quant_code(v[u].x, lam, q)) | six_bits(quant_code(v[u].y, lam, q)) << 6 |
+                         six_bits(quant_code(v[u].z, lam, q)) << 12 | six_bits(quant_code(v[u].w, lam, q)) << 18;
+                const int past = k - (K - 4);           // (the row's last four values stand in where the quad crosses its end)
+                if (past > 0) w = past < 4 ? w >> (FMT * past) : 0u;
+                words[r * LDW + (k >> 2)] = w;
+            }
+            if (RES && level == 0) v[u] = first_level_residual(v[u], lam, s, q);
+        }
+        __syncthreads();
+        uint8_t* const codes = reinterpret_cast<uint8_t*>(level == 0 ? o.codesA : o.codesRA);
+        for (int e = threadIdx.x; e < ROWS * 2 * nkb; e += WG) {
+            const int rr = e % ROWS, unit = e / ROWS, orow = row0 + rr;
+            if (orow >= M) continue;
+            const uint4* src = reinterpret_cast<const uint4*>(&words[rr * LDW + 8 * unit]);
+            const uint4 lo = src[0], hi = src[1];
+            uint32_t w[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+            store_packed<FMT>(codes + ((size_t)(orow >> 5) * nkb + (unit >> 1)) * pk_block(FMT), 32 * (unit & 1) + (orow & 31), w, 32);
+        }
     }
 }
 
 // Quantize a 64(k) x 64(n) tile with per-column scales and store it transposed
 // (codesT is cols x rows, contiguous along the original row index k).  Columns at the end as in the row kernels (what
 // then lies before the tile belongs to the neighbour and is dropped); codes leave 16 bytes at a time at any alignment.
-// RMAX: the column maxima of the residual (already cleared) come from the same read.  PACKED: packed codes.
-template <bool TINY, bool RMAX = false, bool PACKED = false>
+// RMAX: the column maxima of the residual (already cleared) come from the same read.  PACKED: packed codes of this format.
+template <bool TINY, bool RMAX = false, int PACKED = PK_NONE>
 __global__ __launch_bounds__(256) void quant_cols_kernel(const float* __restrict__ X, int ldx, int rows,
                                                          int cols, const float* __restrict__ amax,
                                                          QuantParams q,
@@ -369,7 +377,7 @@ __global__ __launch_bounds__(256) void quant_cols_kernel(const float* __restrict
         }
 #pragma unroll
         for (int t = 0; t < 4; ++t)
-            if (TINY || n - n0 + t >= 0) tile[n - n0 + t][kl] = (int8_t)(PACKED ? (int)six_bits(c[t]) : (int)c[t]);
+            if (TINY || n - n0 + t >= 0) tile[n - n0 + t][kl] = (int8_t)(PACKED == PK6 ? (int)six_bits(c[t]) : (int)c[t]);
     }
     if (RMAX) red[ty][tx] = rm;
     __syncthreads();
@@ -385,8 +393,8 @@ __global__ __launch_bounds__(256) void quant_cols_kernel(const float* __restrict
         atomicMax(rmax_bits + n + 2, __float_as_uint(rm.z));
         atomicMax(rmax_bits + n + 3, __float_as_uint(rm.w));
     }
-    if constexpr (PACKED) {
-        store_packed_tile<64, 64, 80, true>(&tile[0][0], reinterpret_cast<uint8_t*>(codesT), n0, cols, k0, rows, threadIdx.x, 256);
+    if constexpr (PACKED != PK_NONE) {
+        store_packed_tile<PACKED, 64, 64, 80, true>(&tile[0][0], reinterpret_cast<uint8_t*>(codesT), n0, cols, k0, rows, threadIdx.x, 256);
         return;
     }
     const int nl = threadIdx.x >> 2, chunk = threadIdx.x & 3;
@@ -521,9 +529,9 @@ int launch_quantize_cols(const float* X, int ldx, int rows, int cols, QuantParam
 bool quantize_pair_usable(int M, int N, int K) { return M > 0 && N >= 4 && K >= 4 && K <= 16384; }
 
 int launch_quantize_pair(const float* A, int lda, const float* B, int ldb, int M, int N, int K, QuantParams q, QuantPair o,
-                         hipStream_t st, bool packed) {
+                         hipStream_t st, int packed) {
     const bool res = o.codesRA != nullptr;
-    if (!quantize_pair_usable(M, N, K) || (packed && res)) return LRQMM_ERR_UNSUPPORTED;
+    if (!quantize_pair_usable(M, N, K)) return LRQMM_ERR_UNSUPPORTED;
     uint32_t *const bits = reinterpret_cast<uint32_t*>(o.amaxB), *const rbits = reinterpret_cast<uint32_t*>(o.amaxRB);
     hipLaunchKernelGGL(fill_u32_kernel, dim3(ceil_div(N, 256)), dim3(256), 0, st, bits, N, 0u, res ? rbits : nullptr);
     const ColSlabs p = plan_slabs(K, N);
@@ -533,16 +541,32 @@ int launch_quantize_pair(const float* A, int lda, const float* B, int ldb, int M
     if (packed) {
         const int rows = wave ? 8 : 4, nbP = ceil_div(M, rows), jobs = p.col_blocks * p.slabs;
         const dim3 gp(nbP + ceil_div(jobs, wave ? 2 : 4));
-#define LRQ_QPP(T, NV)                                                                                              \
-    hipLaunchKernelGGL((quant_pair_packed_kernel<(T == 64 ? 512 : 1024), T, NV>), gp, dim3(T == 64 ? 512 : 1024), 0, st, A, lda, M, K, o, nbP, B, ldb, N,   \
-                       p.rows_per_block, q, p.col_blocks, jobs)
-#define LRQ_QPP_NV(T) do { if (need <= 1) LRQ_QPP(T, 1); else if (need <= 2) LRQ_QPP(T, 2); \
-        else if (need <= 4) LRQ_QPP(T, 4); else if (need <= 8) LRQ_QPP(T, 8); else LRQ_QPP(T, 16); } while (0)
-        if (wave) LRQ_QPP_NV(64);
-        else      LRQ_QPP_NV(256);
+#define LRQ_QPP(F, T, NV, R)                                                                                           \
+    hipLaunchKernelGGL((quant_pair_packed_kernel<F, (T == 64 ? 512 : 1024), T, NV, R>), gp, dim3(T == 64 ? 512 : 1024), 0, st, A, lda, \
+                       M, K, o, nbP, B, ldb, N, p.rows_per_block, q, p.col_blocks, jobs)
+#define LRQ_QPP_NV(F, T, R) do { if (need <= 1) LRQ_QPP(F, T, 1, R); else if (need <= 2) LRQ_QPP(F, T, 2, R); \
+        else if (need <= 4) LRQ_QPP(F, T, 4, R); else if (need <= 8) LRQ_QPP(F, T, 8, R); else LRQ_QPP(F, T, 16, R); } while (0)
+#define LRQ_QPP_T(F, R) do { if (wave) LRQ_QPP_NV(F, 64, R); else LRQ_QPP_NV(F, 256, R); } while (0)
+#define LRQ_QCP(F, R, AMAX, CODES, AMAX0, RBITS) \
+    hipLaunchKernelGGL((quant_cols_kernel<false, R, F>), g2, dim3(256), 0, st, B, ldb, K, N, AMAX, q, CODES, AMAX0, RBITS)
+#define LRQ_PAIR(F)                                                 \
+    do {                                                            \
+        if (res) {                                                  \
+            LRQ_QPP_T(F, true);                                     \
+            LRQ_QCP(F, true, o.amaxB, o.codesB, nullptr, rbits);    \
+            LRQ_QCP(F, false, o.amaxRB, o.codesRB, o.amaxB, nullptr); \
+        } else {                                                    \
+            LRQ_QPP_T(F, false);                                    \
+            LRQ_QCP(F, false, o.amaxB, o.codesB, nullptr, nullptr); \
+        }                                                           \
+    } while (0)
+        if (packed == PK6) LRQ_PAIR(PK6);
+        else               LRQ_PAIR(PK8);
+#undef LRQ_PAIR
+#undef LRQ_QCP
+#undef LRQ_QPP_T
 #undef LRQ_QPP_NV
 #undef LRQ_QPP
-        hipLaunchKernelGGL((quant_cols_kernel<false, false, true>), g2, dim3(256), 0, st, B, ldb, K, N, o.amaxB, q, o.codesB, nullptr, nullptr);
         LRQ_CHECK_LAUNCH();
         return LRQMM_OK;
     }

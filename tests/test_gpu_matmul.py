@@ -250,12 +250,16 @@ def test_guard_free_pass_kernels_equal_the_guarded_ones_bitwise(M, N, K, r, p):
     assert np.array_equal(to_np(_separate_calls(L, dA, dB, 4, r, p, 1, 9)), C)
 
 
-# Codes of up to five bits travel packed inside the call.  Edges of the 32-row and 64-code blocks (one short, whole, one over), odd
+# Codes travel packed inside the call, up to five bits in six.  Edges of the 32-row and 64-code blocks (one short, whole, one over), odd
 # numbers of k blocks and fewer than the stages of the product, 128 x 128 / 64 x 128 / 64 x 64 / 256 x 256 tiles, tiles cut along K
 # beside the SVDs, and the longest reduction that 5-bit sums leave exact (the next one takes bytes).
 PACKED = [(128, 96, 128, 4, 24, 8), (127, 97, 191, 4, 20, 8), (129, 160, 193, 2, 17, 0), (320, 321, 385, 5, 24, 8),
           (1025, 1000, 449, 3, 40, 8), (2080, 2049, 320, 4, 17, 0), (3100, 2900, 200, 4, 36, 0), (4096, 4096, 1024, 4, 32, 8),
           (64, 96, 65536, 5, 17, 0), (96, 64, 65540, 5, 17, 0)]
+# Codes of six bits and more travel as bytes in the same blocks.
+PACKED += [(127, 97, 191, 8, 20, 8), (129, 160, 193, 6, 17, 0), (33, 34, 35, 8, 17, 0), (320, 321, 385, 7, 24, 8), (1025, 1000, 449, 8, 40, 8),
+           (1537, 1021, 1100, 8, 24, 8), (2080, 2049, 320, 8, 17, 0), (3100, 2900, 200, 8, 36, 0), (4096, 4096, 1024, 8, 32, 8),
+           (64, 96, 131071, 8, 17, 0)]
 
 
 @pytest.mark.parametrize("M,N,K,bits,r,p", PACKED)
@@ -272,7 +276,8 @@ def test_packed_codes_give_the_bits_of_the_separate_calls(M, N, K, bits, r, p):
 # The same without a factorization: rows in the registers of a wave or (beyond 4096 codes) of a workgroup, in one to four loads, rows
 # that end inside a load, 16-row groups that end early.
 @pytest.mark.parametrize("M,N,K,bits", [(256, 256, 64, 4), (131, 97, 193, 4), (65, 100, 1030, 5), (300, 130, 4096, 2), (70, 64, 4099, 4),
-                                        (97, 300, 9001, 4), (2100, 2300, 700, 4)])
+                                        (97, 300, 9001, 4), (2100, 2300, 700, 4), (256, 256, 64, 8), (131, 97, 193, 8),
+                                        (5, 4, 4, 8), (65, 100, 1030, 6), (70, 64, 4099, 8), (97, 300, 9001, 8), (2100, 2300, 700, 8)])
 def test_packed_codes_without_a_factorization(M, N, K, bits):
     import paper_2409_18772_amd as L
     dA, dB = to_dev(wl.random_matrix("normal", M, K, seed=93)), to_dev(wl.random_matrix("uniform_pm1", K, N, seed=94))

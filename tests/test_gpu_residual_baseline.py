@@ -190,3 +190,28 @@ def test_joint_quantization_equals_the_separate_calls(M, N, K, pad, terms):
         for i, p in enumerate(products):
             L.lrqmm_gemm_ex(*p, bits, want, 0.75, 0.5 if i == 0 else 1.0)
         assert torch.equal(got, want)
+
+
+# Four products of packed codes as the quadrants of one tile: edges of the 128 x 128 tiles and of the 32-row and 64-code blocks, rows of
+# A in the registers of a wave or of a workgroup, both formats and the first reduction too long for six bits, an update of a window.
+@pytest.mark.parametrize("M,N,K,bits,alpha,beta,pad", [(128, 128, 64, 8, 1.0, 0.0, 0), (127, 129, 63, 8, 0.75, 0.5, 3), (130, 5, 65, 6, 1.0, 0.5, 0),
+                                                       (300, 260, 1030, 8, 1.0, 0.0, 8), (1000, 700, 4099, 8, -0.5, 1.0, 1), (129, 127, 200, 4, 1.0, 0.0, 0),
+                                                       (1, 300, 333, 4, 1.0, 0.25, 5), (1100, 600, 5000, 5, 1.0, 0.0, 0), (2100, 1900, 320, 2, 1.0, 0.0, 0)])
+def test_four_products_in_one_tile_give_the_bits_of_one_launch_each(M, N, K, bits, alpha, beta, pad):
+    """Each product's sums are exact integers, and the steps, alpha and the running total round in the same places."""
+    import torch
+    import paper_2409_18772_amd as L
+    A, B = to_dev(wl.random_matrix("normal", M, K, seed=41)), to_dev(wl.random_matrix("uniform_pm1", K, N, seed=42))
+    D0 = wl.random_matrix("normal", M, N, seed=43)
+    say("four products", M, N, K, bits, alpha, beta, pad)
+    _, D = window(D0, pad)
+    L.lrqmm_residual_matmul(A, B, D, bits, 4, alpha=alpha, beta=beta)
+    codes = {}
+    for name, X, axis in (("A", A, L.AXIS_ROW), ("B", B, L.AXIS_COL)):
+        codes[name, 0] = L.lrqmm_quantize(X, axis, bits)
+        codes[name, 1] = L.lrqmm_quantize_residual(X, codes[name, 0][1], axis, bits)
+    _, W = window(D0, pad)
+    for i, j in ((0, 0), (0, 1), (1, 0), (1, 1)):
+        L.lrqmm_gemm_ex(*codes["A", i], *codes["B", j], bits, D=W, alpha=alpha, beta=beta)
+        beta = 1.0
+    assert np.array_equal(to_np(D), to_np(W))
