@@ -63,13 +63,11 @@ size_t carve_rsvd(Arena& a, int rows, int cols, int axis, int LP, int rank, Rsvd
 }
 
 struct GemmWs {
-    float *lamA, *sA, *lamB, *sB, *partialA, *partialB, *X, *Lp, *Rp;
-    uint16_t *Wp3, *Vp3;
+    float *lamA, *sA, *lamB, *sB, *X, *Lp, *Rp;
+    uint16_t *Wf, *Vf;
 };
 
-// smaller_too: room for every problem that is no larger in any extent (what lrqmm_workspace_bytes promises), not only for
-// this one (what lrqmm_gemm and lrqmm_gemm_static ask for).
-size_t carve_gemm(Arena& a, int M, int N, int K, int rank, GemmWs* w, bool smaller_too = false) {
+size_t carve_gemm(Arena& a, int M, int N, int K, int rank, GemmWs* w) {
     GemmWs t = {};
     const int Mp = pad_to(M, 4), Np = pad_to(N, 4);
     t.lamA = a.take<float>(Mp);
@@ -78,11 +76,8 @@ size_t carve_gemm(Arena& a, int M, int N, int K, int rank, GemmWs* w, bool small
     t.sB = a.take<float>(Np);
     if (rank > 0) {
         const int RP = pad_to(rank, 16), R2P = pad_to(2 * rank, 8);
-        const PassPlan pa = plan_codes(M, K), pb = plan_codes(N, K);
-        t.Wp3 = a.take<uint16_t>((size_t)3 * RP * pad_to(K, 64));
-        t.Vp3 = a.take<uint16_t>((size_t)3 * RP * pad_to(K, 64));
-        t.partialA = a.take<float>(RP * (smaller_too ? codes_partial_rows(M, K) : (size_t)pa.splits * M));
-        t.partialB = a.take<float>(RP * (smaller_too ? codes_partial_rows(N, K) : (size_t)pb.splits * N));
+        t.Wf = a.take<uint16_t>((size_t)3 * RP * pad_to(K, 64));
+        t.Vf = a.take<uint16_t>((size_t)3 * RP * pad_to(K, 64));
         t.X = a.take<float>((size_t)rank * rank * LRQ_VTW_MAX_SLICES);
         t.Lp = a.take<float>((size_t)M * R2P);
         t.Rp = a.take<float>((size_t)N * R2P);
@@ -122,7 +117,7 @@ size_t carve_matmul(Arena& a, int M, int N, int K, int rank, int oversample, Mat
     size_t sub = 0, sa = 0, sb = 0;
     {
         Arena g(nullptr);
-        sub = carve_gemm(g, M, N, K, rank, nullptr, true);
+        sub = carve_gemm(g, M, N, K, rank, nullptr);
     }
     if (rank > 0) {
         // the two residual factorizations run concurrently: each gets its own region
@@ -567,14 +562,11 @@ static int gemm_impl(int M, int N, int K, int bits, int rank, const int8_t* Aq, 
     const int RP = pad_to(rank, 16);
     if (rank > 0) {
         LRQ_TRY(launch_panel_prep(M, N, K, rank, RP, q.qmaxf, amaxA, amaxB, W, Vt, w.lamA, w.sA, w.lamB, w.sB,
-                                  w.Wp3, w.Vp3, w.X, st));
+                                  w.Wf, w.Vf, w.X, st));
         R2P = pad_to(2 * rank, 8);
-        // A~ W and (V^T B~)^T without their step vectors, split along K; one launch for both
-        const PassPlan pa = plan_codes(M, K), pb = plan_codes(N, K);
-        LRQ_TRY(launch_codes_mul_n2(Aq, M, w.Wp3, pa, w.partialA, BqT, N, w.Vp3, pb, w.partialB, K,
-                                    pad_to(K, 64), RP, st, K % 16 == 0 ? planes : 3, packed));     // (as the interface states)
-        LRQ_TRY(launch_build_panels(M, N, K, rank, RP, R2P, U, Sig, w.sA, w.partialA, pa.splits, w.sB,
-                                    w.partialB, pb.splits, w.X, Gam, Zt, w.Lp, w.Rp, st));
+        PanelArgs pa = {Aq, BqT, w.Wf, w.Vf, U, Sig, w.sA, w.sB, w.X, Gam, Zt, w.Lp, w.Rp, M, N, K, rank, R2P};
+        pa.nslices = ceil_div(K, ceil_div(K, vtw_slices(K)));
+        LRQ_TRY(launch_panels(pa, RP, K % 16 == 0 ? planes : 3, packed, st));       // (as the interface states)
     }
     if (raw_sums_ready) {
         // the integer product ran early on another stream and left its int32 sums in C
@@ -618,12 +610,16 @@ int lrqmm_gemm_static(int M, int N, int K, int bits, int rank, const int8_t* Aq,
     if (!dims_ok(M, N, K) || !output_ok(M, N)) return LRQMM_ERR_UNSUPPORTED;
     if (rank > LRQMM_MAX_SKETCH) return LRQMM_ERR_UNSUPPORTED;
     if (M == 0 || N == 0) return LRQMM_OK;
-    // (which problems fit is part of the interface: the limit still counts two K x RP float32 regions that the
-    // kernels no longer need)
+    // (which problems fit is part of the interface: the limit still counts regions that the kernels no longer need, two of K x
+    // RP float32 values and the partial results of the code products)
     Arena a(nullptr);
     const int RP = pad_to(rank, 16);
     a.take<float>((size_t)K * RP);
     a.take<float>((size_t)K * RP);
+    if (rank > 0) {
+        a.take<float>((size_t)codes_splits(M, K) * M * RP);
+        a.take<float>((size_t)codes_splits(N, K) * N * RP);
+    }
     if (carve_gemm(a, M, N, K, rank, nullptr) > (size_t)LRQMM_STATIC_SCRATCH_BYTES) return LRQMM_ERR_STATIC_LIMIT;
     void* ws = nullptr;
     const int rc = static_scratch(&ws);

@@ -1331,11 +1331,8 @@ __global__ __launch_bounds__(256, 2) void rank_update_bf16_kernel(int M, int N, 
 // ---------------------------------------------------------------------------
 // Panels of the rank-2r update (compensation terms of Algorithm 2 regrouped):
 //   C = C0 + [U Sigma | A~ W] . [V^T B~ + (V^T W) Gamma Z^T ; Gamma Z^T]
-// Two small launches surround the two code-matrix products A~ W and (V^T B~)^T:
-//   panel_prep:   step vectors of both operands, zero-padded copies of W and V for the
-//                 matrix-core kernels, and X = V^T W in k-slices;
-//   build_panels: sums the split partials of the code products, applies the steps and
-//                 assembles the left (M x R2P) and right (N x R2P) panels.
+// panel_prep: step vectors of both operands, the planes of W and V as matrix-core operands, and X = V^T W in k-slices; the code
+// products and the panels follow in one launch (passes.hip).
 // ---------------------------------------------------------------------------
 
 // Xp[ks][t][u] = sum over the ks-th slice of k of Vt[t][k] W[k][u] (r x r per slice), float64
@@ -1375,36 +1372,17 @@ __device__ __forceinline__ void vtw_block(const float* __restrict__ Vt, const fl
     }
 }
 
-// x = hi + mid + lo with each term a bfloat16 (the upper 16 bits of a float32): every term is
-// the round-to-nearest-even bfloat16 of what is left and the subtractions are exact, so the
-// remainder is below 2^-27 |x| -- the three planes carry x to better than float32 precision.
-// (Finite inputs; rounding cannot overflow for |x| < 2^127.)
-__device__ __forceinline__ uint32_t bf16_rne_bits(float x) {
-    const uint32_t u = __float_as_uint(x);
-    return (u + 0x7fffu + ((u >> 16) & 1u)) & 0xffff0000u;
-}
-__device__ __forceinline__ void split_bf16x3(float x, uint16_t (&h)[3]) {
-    const uint32_t b0 = bf16_rne_bits(x);
-    const float r1 = x - __uint_as_float(b0);
-    const uint32_t b1 = bf16_rne_bits(r1);
-    const float r2 = r1 - __uint_as_float(b1);
-    const uint32_t b2 = bf16_rne_bits(r2);
-    h[0] = (uint16_t)(b0 >> 16);
-    h[1] = (uint16_t)(b1 >> 16);
-    h[2] = (uint16_t)(b2 >> 16);
-}
-
 struct PrepArgs {
     const float *amaxA, *amaxB, *W, *Vt;
     float *lamA, *sA, *lamB, *sB, *Xp;
-    uint16_t *Wp3, *Vp3;
+    uint16_t *Wf, *Vf;
     int M, Mp, N, Np, K, Kp, r, RP, kslice, nslices;
     float qmaxf;
     int nbA, nbB, nbP;      // workgroups of the first three sections
 };
 
 // Workgroup ranges: [0, nbA) steps of A, [nbA, nbA+nbB) steps of B, then nbP workgroups that
-// write the zero-padded bfloat16 planes of W (K x r) and V = Vt^T, then
+// write the zero-padded bfloat16 planes of W (K x r) and V = Vt^T in operand order (see FACTOR_PIECE), then
 // r * nslices workgroups of V^T W.
 __global__ __launch_bounds__(256) void panel_prep_kernel(PrepArgs a) {
     __shared__ double part[256];
@@ -1422,18 +1400,28 @@ __global__ __launch_bounds__(256) void panel_prep_kernel(PrepArgs a) {
     }
     b -= a.nbA + a.nbB;
     if (b < a.nbP) {
-        const size_t idx = (size_t)b * 256 + threadIdx.x;     // k fastest: coalesced plane writes
-        if (idx >= (size_t)a.Kp * a.RP) return;
-        const int c = (int)(idx / a.Kp), k = (int)(idx % a.Kp);
-        const bool in = c < a.r && k < a.K;
-        const float wv = in ? a.W[(size_t)k * a.r + c] : 0.f;
-        const float vv = in ? a.Vt[(size_t)c * a.K + k] : 0.f;
-        uint16_t h[3];
-        const size_t plane = (size_t)a.RP * a.Kp;
-        split_bf16x3(wv, h);
-        a.Wp3[idx] = h[0]; a.Wp3[plane + idx] = h[1]; a.Wp3[2 * plane + idx] = h[2];
-        split_bf16x3(vv, h);
-        a.Vp3[idx] = h[0]; a.Vp3[plane + idx] = h[1]; a.Vp3[2 * plane + idx] = h[2];
+        // one lane's eight k of an operand, of both factors
+        const int idx = b * 256 + threadIdx.x, NT = a.RP / 16;
+        if (idx >= a.Kp / 64 * NT * 128) return;
+        const int lane = idx & 63, h = (idx >> 6) & 1, blk = idx >> 7;           // blk: k block and column tile
+        const int c = 16 * (blk % NT) + (lane & 15), k0 = 64 * (blk / NT) + 16 * (lane >> 4) + 8 * h;
+        float w[8], v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int k = min(k0 + e, a.K - 1), cc = min(c, a.r - 1);
+            const bool in = c < a.r && k0 + e < a.K;
+            const float wv = a.W[(size_t)k * a.r + cc], vv = a.Vt[(size_t)cc * a.K + k];
+            w[e] = in ? wv : 0.f;
+            v[e] = in ? vv : 0.f;
+        }
+        const Planes3 pw = split_planes<3>(w), pv = split_planes<3>(v);
+        const size_t at = (size_t)(blk * 6 + h) * FACTOR_PIECE + lane * 8;
+        *reinterpret_cast<v8bf16*>(a.Wf + at) = pw.p1;
+        *reinterpret_cast<v8bf16*>(a.Wf + at + 2 * FACTOR_PIECE) = pw.p2;
+        *reinterpret_cast<v8bf16*>(a.Wf + at + 4 * FACTOR_PIECE) = pw.p3;
+        *reinterpret_cast<v8bf16*>(a.Vf + at) = pv.p1;
+        *reinterpret_cast<v8bf16*>(a.Vf + at + 2 * FACTOR_PIECE) = pv.p2;
+        *reinterpret_cast<v8bf16*>(a.Vf + at + 4 * FACTOR_PIECE) = pv.p3;
         return;
     }
     b -= a.nbP;
@@ -1443,162 +1431,24 @@ __global__ __launch_bounds__(256) void panel_prep_kernel(PrepArgs a) {
     else                vtw_block<128>(a.Vt, a.W, a.K, a.r, a.kslice, t, ks, a.Xp, part);
 }
 
-// p[0] + p[stride] + ... (n <= MAXN terms, fixed order).  All loads are issued before the first
-// add, without branches: a clamped index re-reads the last term, whose value is then masked.
-template <int MAXN>
-__device__ __forceinline__ float sum_slices(const float* __restrict__ p, int n, size_t stride) {
-    float v[MAXN];
-#pragma unroll
-    for (int t = 0; t < MAXN; ++t) v[t] = p[(size_t)min(t, n - 1) * stride];
-    float acc = 0.f;
-#pragma unroll
-    for (int t = 0; t < MAXN; ++t) acc += (t < n) ? v[t] : 0.f;
-    return acc;
-}
-
-struct BuildArgs {
-    const float *U, *Sig, *sA, *partialA, *sB, *partialB, *Xp, *Gam, *Zt;
-    float *Lp, *Rp;
-    int M, N, r, RP, R2P, splitsA, splitsB, nslices, nbR;
-};
-
-#define BR_J 16     // columns j of C per workgroup of the right panel: short strips, many workgroups --
-                    // a workgroup is a chain of three load latencies, so the strips run side by side
-// Workgroups [nbR, ...): left panel, one thread per entry:
-//   Lp[i][c] = U[i][c] Sig[c] (c < r),  sA[i] sum_sp partialA[sp][i][c-r] (r <= c < 2r), 0 beyond.
-// Workgroups [0, nbR) (the longer ones, dispatched first): BR_J rows j of the right panel each:
-//   Rp[j][c] = sB[j] sum_sp partialB[sp][j][c] + sum_u X[c][u] Gam[u] Zt[u][j]   (c < r),
-//              Gam[c-r] Zt[c-r][j] (r <= c < 2r), 0 beyond,
-// with X Gamma and the Zt strip staged in LDS so that global reads and writes stay coalesced.
-__global__ __launch_bounds__(256) void build_panels_kernel(BuildArgs a) {
-    extern __shared__ float panel_lds[];        // sized by the launcher from r: xg | zt | pv
-    const int r = a.r, RP = a.RP, R2P = a.R2P;
-    float* const xg = panel_lds;                 // r x (RP + 1): X Gamma
-    float* const zt = xg + r * (RP + 1);         // RP x (BR_J + 1): strip of Zt
-    float* const pv = zt + RP * (BR_J + 1);      // BR_J x RP: strip of (Vt B~)^T
-    if ((int)blockIdx.x >= a.nbR) {
-        const size_t idx = (size_t)(blockIdx.x - a.nbR) * 256 + threadIdx.x;
-        if (idx >= (size_t)a.M * R2P) return;
-        const int i = (int)(idx / R2P), c = (int)(idx % R2P);
-        float v = 0.f;
-        if (c < r) {
-            v = a.U[(size_t)i * r + c] * a.Sig[c];
-        } else if (c < 2 * r) {
-            const size_t plane = (size_t)a.M * RP;
-            v = sum_slices<MAX_SPLITS>(a.partialA + (size_t)i * RP + (c - r), a.splitsA, plane) * a.sA[i];
-        }
-        a.Lp[idx] = v;
-        return;
-    }
-    const int j0 = (int)blockIdx.x * BR_J;
-    for (int e0 = threadIdx.x; e0 < r * r; e0 += 4 * 256) {      // four entries' slice loads in flight
-        float x[4];
-#pragma unroll
-        for (int m = 0; m < 4; ++m)
-            x[m] = sum_slices<LRQ_VTW_MAX_SLICES>(a.Xp + min(e0 + 256 * m, r * r - 1), a.nslices, (size_t)r * r);
-#pragma unroll
-        for (int m = 0; m < 4; ++m) {
-            const int e = e0 + 256 * m;
-            if (e < r * r) {
-                const int c = e / r, u = e - c * r;
-                xg[c * (RP + 1) + u] = x[m] * a.Gam[u];
-            }
-        }
-    }
-    for (int e0 = threadIdx.x; e0 < RP * BR_J; e0 += 4 * 256) {
-        float z[4];
-#pragma unroll
-        for (int m = 0; m < 4; ++m) {
-            const int e = e0 + 256 * m;
-            const int u = min(e / BR_J, r - 1), j = min(j0 + e % BR_J, a.N - 1);
-            z[m] = a.Zt[(size_t)u * a.N + j];
-        }
-#pragma unroll
-        for (int m = 0; m < 4; ++m) {
-            const int e = e0 + 256 * m;
-            const int u = e / BR_J, jl = e % BR_J;
-            if (e < RP * BR_J) zt[u * (BR_J + 1) + jl] = (u < r && j0 + jl < a.N) ? z[m] : 0.f;
-        }
-    }
-    for (int e = threadIdx.x; e < r * (RP - r); e += 256) {     // zero columns u >= r of X Gamma
-        const int c = e / (RP - r), u = r + e - c * (RP - r);
-        xg[c * (RP + 1) + u] = 0.f;
-    }
-    // sB[j] sum_sp partialB[sp][j][c] for the strip, four entries' split loads in flight
-    const size_t plane = (size_t)a.N * RP;
-    const int jn = min(BR_J, a.N - j0);
-    for (int e0 = threadIdx.x; e0 < jn * RP; e0 += 4 * 256) {
-        float x[4];
-#pragma unroll
-        for (int m = 0; m < 4; ++m)
-            x[m] = sum_slices<MAX_SPLITS>(a.partialB + (size_t)j0 * RP + min(e0 + 256 * m, jn * RP - 1), a.splitsB, plane);
-#pragma unroll
-        for (int m = 0; m < 4; ++m) {
-            const int e = e0 + 256 * m;
-            if (e < jn * RP) pv[e] = x[m] * a.sB[j0 + e / RP];
-        }
-    }
-    __syncthreads();
-    for (int e = threadIdx.x; e < BR_J * R2P; e += 256) {
-        const int jl = e / R2P, c = e - jl * R2P;
-        const int j = j0 + jl;
-        if (j >= a.N) break;
-        float v = 0.f;
-        if (c < r) {
-            float acc = pv[jl * RP + c];
-            for (int u0 = 0; u0 < RP; u0 += 8) {       // rows u >= r of zt are zero
-                float xv[8], zv[8];
-#pragma unroll
-                for (int t = 0; t < 8; ++t) {
-                    xv[t] = xg[c * (RP + 1) + u0 + t];
-                    zv[t] = zt[(u0 + t) * (BR_J + 1) + jl];
-                }
-#pragma unroll
-                for (int t = 0; t < 8; ++t) acc = fmaf(xv[t], zv[t], acc);
-            }
-            v = acc;
-        } else if (c < 2 * r) {
-            v = a.Gam[c - r] * zt[(c - r) * (BR_J + 1) + jl];
-        }
-        a.Rp[(size_t)j * R2P + c] = v;
-    }
-}
-
 int vtw_slices(int K) { return max(1, min(LRQ_VTW_MAX_SLICES, K / 256)); }
 
 int launch_panel_prep(int M, int N, int K, int r, int RP, float qmaxf, const float* amaxA, const float* amaxB,
                       const float* W, const float* Vt, float* lamA, float* sA, float* lamB, float* sB,
-                      uint16_t* Wp3, uint16_t* Vp3, float* Xp, hipStream_t st) {
+                      uint16_t* Wf, uint16_t* Vf, float* Xp, hipStream_t st) {
     PrepArgs a;
     a.amaxA = amaxA; a.amaxB = amaxB; a.W = W; a.Vt = Vt;
     a.lamA = lamA; a.sA = sA; a.lamB = lamB; a.sB = sB; a.Xp = Xp;
-    a.Wp3 = Wp3; a.Vp3 = Vp3; a.Kp = (K + 63) / 64 * 64;
+    a.Wf = Wf; a.Vf = Vf; a.Kp = (K + 63) / 64 * 64;
     a.M = M; a.Mp = (M + 3) / 4 * 4; a.N = N; a.Np = (N + 3) / 4 * 4; a.K = K; a.r = r; a.RP = RP;
     a.qmaxf = qmaxf;
     a.nbA = ceil_div(a.Mp, 256);
     a.nbB = ceil_div(a.Np, 256);
-    a.nbP = (int)(((size_t)a.Kp * RP + 255) / 256);
+    a.nbP = ceil_div(a.Kp / 64 * (RP / 16) * 128, 256);
     a.kslice = ceil_div(K, vtw_slices(K));
     a.nslices = ceil_div(K, a.kslice);
     const int total = a.nbA + a.nbB + a.nbP + r * a.nslices;
     hipLaunchKernelGGL(panel_prep_kernel, dim3(total), dim3(256), 0, st, a);
-    LRQ_CHECK_LAUNCH();
-    return LRQMM_OK;
-}
-
-int launch_build_panels(int M, int N, int K, int r, int RP, int R2P, const float* U, const float* Sig,
-                        const float* sA, const float* partialA, int splitsA, const float* sB,
-                        const float* partialB, int splitsB, const float* Xp, const float* Gam, const float* Zt,
-                        float* Lp, float* Rp, hipStream_t st) {
-    BuildArgs a;
-    a.U = U; a.Sig = Sig; a.sA = sA; a.partialA = partialA; a.sB = sB; a.partialB = partialB; a.Xp = Xp;
-    a.Gam = Gam; a.Zt = Zt; a.Lp = Lp; a.Rp = Rp;
-    a.M = M; a.N = N; a.r = r; a.RP = RP; a.R2P = R2P; a.splitsA = splitsA; a.splitsB = splitsB;
-    a.nslices = ceil_div(K, ceil_div(K, vtw_slices(K)));
-    a.nbR = ceil_div(N, BR_J);
-    const int total = a.nbR + (int)(((size_t)M * R2P + 255) / 256);
-    const size_t lds = sizeof(float) * ((size_t)r * (RP + 1) + (size_t)RP * (BR_J + 1) + (size_t)BR_J * RP);
-    hipLaunchKernelGGL(build_panels_kernel, dim3(total), dim3(256), lds, st, a);
     LRQ_CHECK_LAUNCH();
     return LRQMM_OK;
 }

@@ -60,11 +60,10 @@ struct PassPlan {
 };
 PassPlan plan_pass_n(int rows, int cols, int LP);
 PassPlan plan_pass_t(int rows, int cols, int LP);
-PassPlan plan_codes(int rows, int K);       // code products (launch_codes_mul_n2)
-// Room for the partial results of both passes, and rows of it for a code product: at least what the plans need, and no less
+// Room for the partial results of both passes: at least what the plans need, and no less
 // for a larger problem (a plan takes fewer ranges where there are more rows), so that a workspace serves smaller ones.
 size_t pass_partial_floats(int rows, int cols, int LP);
-size_t codes_partial_rows(int rows, int K);
+int codes_splits(int rows, int K);          // (of lrqmm_gemm_static's limit alone)
 // One operand of a factorization, as the passes see it.  X is rows x cols with row stride ldx (>= cols); axis 0: scales
 // by row, 1: by column (lam, s: the step vectors).
 struct PassOperand {
@@ -110,13 +109,19 @@ int quant_sketch_rows_blocks(int rows);
 int launch_quant_sketch_rows(const float* X, int ldx, int rows, int cols, QuantParams q, const float* W, int LP,
                              float* Y, double* gpart, float* amax, float* lam_out, float* s_out, int8_t* codes,
                              hipStream_t st);
-// Two independent products in one launch:
-// partialX[s][rowsX][LP] = scale-free codesX[:, chunk s] . WX[chunk s, :]  (codesX rowsX x K int8)
-// WX3: the K x LP factor as three bfloat16 planes [3][LP][Kp] (k fastest, Kp = K rounded up to 64, zero padded).
-int launch_codes_mul_n2(const int8_t* codesA, int rowsA, const uint16_t* WA3, PassPlan planA,
-                        float* partialA, const int8_t* codesB, int rowsB, const uint16_t* WB3,
-                        PassPlan planB, float* partialB, int K, int Kp, int LP, hipStream_t st, int planes = 3,
-                        int packed = PK_NONE);
+// The panels of the rank-2r update from the codes of both operands, in one launch (RP: r rounded up to 16).  Wf, Vf: the K x r
+// factors W and Vt^T as three bfloat16 planes in operand order, zero padded: [k block of 64][column tile of 16][plane][step][lane][8],
+// a piece (k block, tile, plane, step) being an operand of v_mfma_f32_16x16x32_bf16.  Every codes format gives the same bits.
+#define FACTOR_PIECE 512            // bfloat16 values
+struct PanelArgs {
+    const int8_t *codesA, *codesB;          // of A and of B transposed
+    const uint16_t *Wf, *Vf;
+    const float *U, *Sig, *sA, *sB, *Xp, *Gam, *Zt;
+    float *Lp, *Rp;
+    int M, N, K, r, R2P, nslices;           // nslices: of Xp
+    int nbR;                                // (set by launch_panels)
+};
+int launch_panels(const PanelArgs& a, int RP, int planes, int packed, hipStream_t st);
 
 // ---- orth.hip -----------------------------------------------------------
 // Every launch below takes one job or two (the two operands of a product, in one launch).
@@ -169,19 +174,12 @@ int launch_take_basis(const BasisJob* job, int njob, int LP, int rank, hipStream
 // ---- gemm.hip -----------------------------------------------------------
 // X = V^T W is kept as vtw_slices(K) k-slices Xp[ks][t][u] that are summed where X is used.
 #define LRQ_VTW_MAX_SLICES 16
-int vtw_slices(int K);
-// One launch (r > 0): step vectors lamX/sX (padded to a multiple of 4) of both operands, Wp3 / Vp3: W and Vt^T as zero-padded bfloat16 planes [3][RP][Kp] (see launch_codes_mul_n2), and the slices
+int vtw_slices(int K);      // (at most)
+// One launch (r > 0): step vectors lamX/sX (padded to a multiple of 4) of both operands, Wf / Vf: the planes of W and Vt^T (see PanelArgs), and the slices
 // Xp of V^T W.
 int launch_panel_prep(int M, int N, int K, int r, int RP, float qmaxf, const float* amaxA, const float* amaxB,
                       const float* W, const float* Vt, float* lamA, float* sA, float* lamB, float* sB,
-                      uint16_t* Wp3, uint16_t* Vp3, float* Xp, hipStream_t st);
-// Left panel  Lp[i][0..r) = U[i][t] Sig[t],  Lp[i][r..2r) = sA[i] sum_s partialA[s][i][u]
-// Right panel Rp[j][0..r) = sB[j] sum_s partialB[s][j][t] + sum_u X[t][u] Gam[u] Zt[u][j]
-//             Rp[j][r..2r) = Gam[u] Zt[u][j];   both zero padded to R2P columns.
-int launch_build_panels(int M, int N, int K, int r, int RP, int R2P, const float* U, const float* Sig,
-                        const float* sA, const float* partialA, int splitsA, const float* sB,
-                        const float* partialB, int splitsB, const float* Xp, const float* Gam, const float* Zt,
-                        float* Lp, float* Rp, hipStream_t st);
+                      uint16_t* Wf, uint16_t* Vf, float* Xp, hipStream_t st);
 // Destination of the GEMM: D (row stride ldc) <- alpha * result + beta * D; D is not read when beta == 0.
 struct GemmOut {
     float* C;

@@ -640,28 +640,34 @@ __global__ __launch_bounds__(64 * NW, NT <= 2 ? 4 : (NT <= 3 ? 3 : 2)) void resi
     else          resid_mul_n_bf16_body<NT, 1, PL, QOUT, NW, KC, FULL>(b, q, (id - nb0) % b.nbx, (id - nb0) / b.nbx, sm);
 }
 
-// Product of an int8 code matrix with a float32 factor on the bf16 matrix cores (no scales; blockIdx.z selects one of
-// two independent jobs: A~ W and (V^T B~)^T share one launch).  An int8 code is exact in bfloat16
-// (8 significant bits) and the float32 factor is supplied as three bfloat16 planes
-// hi + mid + lo (exact to 2^-27, see split_bf16x3), so
+// ---------------------------------------------------------------------------
+// Panels of the rank-2r update: the code products A~ W and (V^T B~)^T and what is made of them (see gemm.hip)
+//   Lp[i][c] = U[i][c] Sig[c] (c < r),  sA[i] (Aq W)[i][c - r] (r <= c < 2r),  0 beyond;
+//   Rp[j][c] = sB[j] (BqT V)[j][c] + sum_u X[c][u] Gam[u] Zt[u][j] (c < r),  Gam[c - r] Zt[c - r][j] (r <= c < 2r),  0 beyond.
+//
+// The products run on the bf16 matrix cores: an int8 code is exact in bfloat16 (8 significant bits) and the float32 factor comes as
+// three bfloat16 planes hi + mid + lo (exact to 2^-27, see split_planes), so
 //   code . w = code . hi + code . mid + code . lo
-// holds with every product exact and float32 accumulation in the matrix core: float32
-// accuracy at a fraction of the float32 MFMA cost (3 x 16 cycles instead of 8 x 32 per 32 k).
-// v_mfma_f32_16x16x32_bf16 operand layout (lane l): A[i = l%16][k = 8(l/16) .. +8],
-// B[k = 8(l/16) .. +8][j = l%16], D[i = 4(l/16)+v][j = l%16].  The reduction index may be
-// visited in any order: in a 64-deep chunk lane group kq = l/16 owns k = 16 kq .. 16 kq + 15
-// (one 16-byte load of codes), first half in MFMA step 0, second half in step 1.
-// Bp: [3][RP][Kp] bfloat16 planes of the factor, k fastest, zero padded (Kp % 64 == 0).
-// Codes are read 16 bytes at a time at any alignment (packed rows of K bytes: an odd K leaves none); the group that
-// reaches past K is loaded from K - 16 and moved into place (tail16) where it is used.  Against the byte-by-byte
-// float32 kernel that odd K used to take: 37 -> 11 us at 1537 x 2311 and 1021 x 2311 codes, 16 columns.
-struct CodesJobBf16 {
-    const int8_t* Cq;       // rows x K codes
-    const uint16_t* Bp;     // [3][RP][Kp]
-    float* partial;         // [splits][rows][RP]
-    int rows, chunk, splits;
-};
+// holds with every product exact and float32 accumulation in the matrix core.
+// v_mfma_f32_16x16x32_bf16 operand layout (lane l): A[i = l%16][k = 8(l/16) .. +8], B[k = 8(l/16) .. +8][j = l%16], D[i =
+// 4(l/16)+v][j = l%16].  The reduction index may be visited in any order: in a 64-deep block lane group kq = l/16 owns k = 16 kq
+// .. 16 kq + 15, the first half in step 0, the second in step 1.  The planes lie in that order (FACTOR_PIECE), so that an operand
+// of a wave is 1 KB in a row and goes from memory to its registers without LDS.
+//
+// A workgroup takes 32 RB rows of codes over the whole reduction: its eight waves take a contiguous eighth of the k blocks each, on
+// their own, loads one or more blocks ahead of the matrix cores; at the end their sums meet in LDS, are added in order, and leave
+// as panel rows, so the products themselves never reach memory.  Before (K cut over workgroups, planes staged in LDS, a launch of its own that
+// added the partials and formed the panels), us for both launches / this:
+//   200^3 rank 10 5.3 + 6.5 / 5.1, 2000^3 rank 10 9.4 + 7.5 / 7.8, 1537 x 1021 x 2311 rank 16 13.9 + 8.3 / 8.3, 4096^3 int8 rank 16 12.7 + 9.1 /
+//   12.0, int4 rank 32 14.9 + 12.0 / 18.7, 16384^3 rank 64 433 + 49 / 267, rows kernel below: 100352 x 64 x 576 rank 8 20.2 + 9.1 / 26.3.
+// The planes come through every CU's L1 once per workgroup, at 40 to 45 GB/s a CU, which bounds the larger ones (64 rows a
+// workgroup from 256 of them on: half the reads); touching the planes in the L2 some blocks ahead made them 15 % slower.
+// FMT: PK6, PK8 (see common.h), or PK_NONE: packed rows of K bytes, read 16 bytes at a time at any alignment; the group that reaches
+// past K is loaded from K - 16 and moved into place (tail16) where it is used.  All give the same bits.
+// ---------------------------------------------------------------------------
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef uint32_t v6u __attribute__((ext_vector_type(6)));
+typedef __bf16 v32bf __attribute__((ext_vector_type(32)));
 
 template <bool WIDE>
 __device__ __forceinline__ uint4 load_codes16(const int8_t* __restrict__ rowp, int K, int k) {
@@ -691,294 +697,319 @@ __device__ __forceinline__ v8bf codes_to_bf16(uint32_t lo, uint32_t hi) {
     return r.v;
 }
 
-// Launch shape: grid (ceil(rows / (64 MT)), splits, 2 jobs).  A wave owns 16 MT rows; for each KB-deep slab of
-// its split it issues ALL its code loads at once (KB bytes per row), the four waves copy the slab of Bp into
-// LDS meanwhile, and after one barrier the matrix cores run through the slab without further waits: the HBM
-// latency is paid once per slab with the whole operand in flight.
-template <int NT, int PL = 3>
-struct CodesShape {
-    static constexpr int RP = NT * 16;
-    static constexpr int KB = 256;                      // slab depth: PL RP (KB + 8) bf16 in LDS
-    static constexpr int LDK = KB + 8;
-    static constexpr int NC = KB / 64;                  // 64-deep chunks per slab
-    static constexpr int PIECES = PL * RP * (KB / 8);   // 16-byte pieces of a slab of the first PL planes of Bp
-    static constexpr int BATCH = 8;
-};
-
-// PL: planes of the factor that enter (3: float32 accuracy; 2: relative error 2^-16; 1: plain bfloat16 factor).
-// MT: 16-row tiles per wave (a wave owns 16 MT rows, a workgroup 64 MT).
-// WIDE: K >= 16; below that a row is a single group, read byte by byte.
-template <int NT, int PL = 3, int MT = 4, bool WIDE = true>
-__global__ __launch_bounds__(256, 1) void codes_mul_bf16_kernel(CodesJobBf16 j0, CodesJobBf16 j1, int K, int Kp) {
-    using S = CodesShape<NT, PL>;
-    constexpr int RP = S::RP, KB = S::KB, LDK = S::LDK, NC = S::NC;
-    __shared__ __align__(16) uint16_t bs[PL * RP * LDK];
-    const CodesJobBf16 job = blockIdx.z == 0 ? j0 : j1;
-    if ((int)blockIdx.x * 64 * MT >= job.rows || (int)blockIdx.y >= job.splits) return;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int li = lane & 15, kq = lane >> 4;
-    const int r0 = blockIdx.x * 64 * MT + wave * 16 * MT;
-    const int kb = blockIdx.y * job.chunk, ke = min(K, kb + job.chunk);
-    const int8_t* ap[MT];
+// The sum of X's slices times Gamma, zero columns from r on: r x (RP + 1) in LDS, by `threads` threads.
+__device__ __forceinline__ void stage_x_gamma(const PanelArgs& a, int RP, float* __restrict__ xg, int tid, int threads) {
+    const int r = a.r;
+    for (int e0 = tid; e0 < r * r; e0 += 2 * threads) {      // two entries' slice loads in flight
+        float x[2][LRQ_VTW_MAX_SLICES];
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) ap[mt] = job.Cq + (size_t)min(r0 + 16 * mt + li, job.rows - 1) * K;
-    v4f acc[MT][NT];
+        for (int m = 0; m < 2; ++m)
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
+            for (int t = 0; t < LRQ_VTW_MAX_SLICES; ++t)
+                x[m][t] = a.Xp[min(e0 + threads * m, r * r - 1) + (size_t)min(t, a.nslices - 1) * (r * r)];
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = (v4f){0.f, 0.f, 0.f, 0.f};
-    for (int ks = kb; ks < ke; ks += KB) {
-        // codes of the whole slab; rows past the end re-read the last row (never stored), and
-        // codes past K meet zero planes, so clamped addresses need no mask
-        uint4 ca[MT][NC];
+        for (int m = 0; m < 2; ++m) {
+            const int e = e0 + threads * m;
+            float sum = 0.f;
 #pragma unroll
-        for (int c = 0; c < NC; ++c)            // issued in the order of use: the first chunk's products can start
-#pragma unroll                                  // while the later chunks are still on their way
-            for (int mt = 0; mt < MT; ++mt)
-                ca[mt][c] = load_codes16<WIDE>(ap[mt], K, ks + 64 * c + 16 * kq);
-        if (ks > kb) __syncthreads();       // previous slab no longer read
-        for (int p0 = threadIdx.x; p0 < S::PIECES; p0 += 256 * S::BATCH) {
-            uint4 t[S::BATCH];
-#pragma unroll
-            for (int u = 0; u < S::BATCH; ++u) {
-                const int p = min(p0 + 256 * u, S::PIECES - 1);
-                const int rowp = p / (KB / 8), seg = p - rowp * (KB / 8);
-                const int k = ks + 8 * seg;
-                const uint4 v = *reinterpret_cast<const uint4*>(job.Bp + (size_t)rowp * Kp + min(k, Kp - 8));
-                t[u] = (k < Kp) ? v : make_uint4(0u, 0u, 0u, 0u);
-            }
-#pragma unroll
-            for (int u = 0; u < S::BATCH; ++u) {
-                const int p = p0 + 256 * u;
-                if (p < S::PIECES) {
-                    const int rowp = p / (KB / 8), seg = p - rowp * (KB / 8);
-                    *reinterpret_cast<uint4*>(&bs[rowp * LDK + 8 * seg]) = t[u];
-                }
-            }
+            for (int t = 0; t < LRQ_VTW_MAX_SLICES; ++t) sum += t < a.nslices ? x[m][t] : 0.f;
+            if (e < r * r) xg[e / r * (RP + 1) + e % r] = sum * a.Gam[e % r];
         }
-        __syncthreads();
+    }
+    for (int e = tid; e < r * (RP - r); e += threads) xg[e / (RP - r) * (RP + 1) + r + e % (RP - r)] = 0.f;
+}
+
+// Codes of one k block as a wave's operands: 32 rows as two tiles of 16, lane (li, kq) with codes 16 kq .. +16 of its rows.
+template <int FMT>
+struct CodeBlock {
+    uint4 w[2];
+    uint2 x[FMT == PK6 ? 2 : 1];
+    __device__ __forceinline__ void load(const int8_t* codes, int rb, int rows, int kb, int K, int nkb, int li, int kq) {
+        if constexpr (FMT == PK_NONE) {
 #pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            if (ks + 64 * c < ke) {             // uniform
-                if (WIDE && (K & 15) && ks + 64 * c + 64 > K) {     // uniform: the row ends in this chunk
+            for (int t = 0; t < 2; ++t) {
+                const int8_t* row = codes + (size_t)min(32 * rb + 16 * t + li, rows - 1) * K;
+                w[t] = K >= 16 ? load_codes16<true>(row, K, 64 * kb + 16 * kq) : load_codes16<false>(row, K, 16 * kq);
+            }
+        } else {
+            const uint8_t* blk = reinterpret_cast<const uint8_t*>(codes) + ((size_t)min(rb, (rows - 1) >> 5) * nkb + kb) * pk_block(FMT);
+            const int unit = 32 * (kq >> 1) + li;
 #pragma unroll
-                    for (int mt = 0; mt < MT; ++mt) ca[mt][c] = tail16(ca[mt][c], max(0, ks + 64 * c + 16 * kq - (K - 16)));
-                }
-#pragma unroll
-                for (int sidx = 0; sidx < 2; ++sidx) {
-                    v8bf af[MT];
-#pragma unroll
-                    for (int mt = 0; mt < MT; ++mt)
-                        af[mt] = sidx == 0 ? codes_to_bf16(ca[mt][c].x, ca[mt][c].y)
-                                           : codes_to_bf16(ca[mt][c].z, ca[mt][c].w);
-#pragma unroll
-                    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                        for (int pl = 0; pl < PL; ++pl) {
-                            union { uint4 u; v8bf v; } b;
-                            b.u = *reinterpret_cast<const uint4*>(
-                                &bs[(pl * RP + 16 * nt + li) * LDK + 64 * c + 16 * kq + 8 * sidx]);
-#pragma unroll
-                            for (int mt = 0; mt < MT; ++mt)
-                                acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[mt], b.v, acc[mt][nt], 0, 0, 0);
-                        }
+            for (int t = 0; t < 2; ++t) {
+                if constexpr (FMT == PK8) w[t] = *reinterpret_cast<const uint4*>(blk + 1024 * (kq & 1) + (unit + 16 * t) * 16);
+                else {      // (a lane's 24 bytes whole; the half that is wanted is picked below)
+                    w[t] = *reinterpret_cast<const uint4*>(blk + (unit + 16 * t) * 16);
+                    x[t] = *reinterpret_cast<const uint2*>(blk + 1024 + (unit + 16 * t) * 8);
                 }
             }
         }
     }
-    float* out = job.partial + (size_t)blockIdx.y * job.rows * RP;
+    // -> [step][tile]
+    __device__ __forceinline__ void operands(v8bf (&af)[2][2], int kb, int K, int kq) {
+        if constexpr (FMT == PK6) {
+            uint32_t h[2][3];
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
+            for (int t = 0; t < 2; ++t) {
+                h[t][0] = (kq & 1) ? w[t].w : w[t].x;        // (stored order: words 0 1 2 3 | 4 5)
+                h[t][1] = (kq & 1) ? x[t].x : w[t].y;
+                h[t][2] = (kq & 1) ? x[t].y : w[t].z;
+            }
+            const v6u six = {h[0][0], h[0][1], h[0][2], h[1][0], h[1][1], h[1][2]};
+            const v32bf val = __builtin_amdgcn_cvt_scalef32_pk32_bf16_fp6(six, 8.0f);
+            af[0][0] = __builtin_shufflevector(val, val, 0, 1, 2, 3, 4, 5, 6, 7);
+            af[1][0] = __builtin_shufflevector(val, val, 8, 9, 10, 11, 12, 13, 14, 15);
+            af[0][1] = __builtin_shufflevector(val, val, 16, 17, 18, 19, 20, 21, 22, 23);
+            af[1][1] = __builtin_shufflevector(val, val, 24, 25, 26, 27, 28, 29, 30, 31);
+        } else {
+            // (codes past K meet zero planes, but the group that crosses K has to be moved into place)
+            if (FMT == PK_NONE && (K & 15) && K >= 16 && 64 * kb + 64 > K) {     // uniform
+#pragma unroll
+                for (int t = 0; t < 2; ++t) w[t] = tail16(w[t], max(0, 64 * kb + 16 * kq - (K - 16)));
+            }
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                af[0][t] = codes_to_bf16(w[t].x, w[t].y);
+                af[1][t] = codes_to_bf16(w[t].z, w[t].w);
+            }
+        }
+    }
+};
+
+// The first half (H = 0) or second half of the planes' operands of one k block.
+template <int NT, int PL>
+struct FactorHalf {
+    v8bf b[NT][PL];
+    __device__ __forceinline__ void load(const uint16_t* Wf, int kb, int h, int lane) {
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int row = r0 + 16 * mt + 4 * kq + v;
-                if (row < job.rows) out[(size_t)row * RP + 16 * nt + li] = acc[mt][nt][v];
-            }
+            for (int pl = 0; pl < PL; ++pl)
+                b[nt][pl] = *reinterpret_cast<const v8bf*>(Wf + (size_t)(((kb * NT + nt) * 3 + pl) * 2 + h) * FACTOR_PIECE + lane * 8);
+    }
+};
+template <int NT, int PL>
+__device__ __forceinline__ void panel_products(const v8bf (&af)[2], const FactorHalf<NT, PL>& f, v4f (&acc)[2][NT]) {
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int pl = 0; pl < PL; ++pl)
+#pragma unroll
+            for (int t = 0; t < 2; ++t) acc[t][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[t], f.b[nt][pl], acc[t][nt], 0, 0, 0);
 }
 
-// The same product for short rows (K <= 640) and factors of at most 16 columns: all of Bp fits in LDS (PL planes
-// x 16 rows x (Kp + 8) bfloat16), so workgroups are persistent -- two of eight waves per CU, the planes copied once --
-// and after the one barrier behind that copy the waves are on their own: a wave takes the 16-row tiles w, w + W,
-// w + 2W, ... (W waves in the grid) and loads a tile's codes at once (NC 16-byte loads per lane, the whole row);
-// the sixteen waves of a CU are at different points of that cycle, which keeps loads in flight while others
-// compute.  blockIdx.z selects the job as above.
+#define PANEL_WAVES 8
+#define PANEL_ROWS_MIN 16384    // rows from which panels_rows_kernel takes them
+#define PANEL_TWO_MIN 256       // workgroups of 64 rows from which they are taken in place of 32
+// k blocks of a wave; its sums are added to the others' in the order of the waves, whichever kernel forms them.
+__host__ __device__ static inline int panel_range(int nkb) { return (nkb + PANEL_WAVES - 1) / PANEL_WAVES; }
+
+template <int FMT, int NT, int PL, int RB>
+__global__ __launch_bounds__(512, 2) void panels_kernel(PanelArgs a) {
+    constexpr int RP = NT * 16, AHEAD = NT == 1 ? 3 : 2;
+    __shared__ float red[PANEL_WAVES * 32 * RP];        // [wave][32 rows][RP]
+    __shared__ float xg[RP * (RP + 1)];                 // X Gamma
+    __shared__ float own[RB][RP * 33];                  // right: 32 columns of Zt, [u][row]; left: 32 rows of U Sig
+    __shared__ float step[32 * RB];
+    const bool right = (int)blockIdx.x < a.nbR;         // (the right panel has more to do)
+    const int blk = right ? blockIdx.x : blockIdx.x - a.nbR;
+    const int rows = right ? a.N : a.M, K = a.K, r = a.r, R2P = a.R2P;
+    const int8_t* const codes = right ? a.codesB : a.codesA;
+    const uint16_t* const Wf = right ? a.Vf : a.Wf;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int li = lane & 15, kq = lane >> 4;
+    const int nkb = pk_kblocks(K), kb0 = wave * panel_range(nkb), kb1 = min(nkb, kb0 + panel_range(nkb));
+    v4f acc[RB][2][NT];
+#pragma unroll
+    for (int b = 0; b < RB; ++b)
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) acc[b][t][nt] = (v4f){0.f, 0.f, 0.f, 0.f};
+    // What the panel rows need besides the products: loaded beside the first blocks, so that behind the loop nothing waits for memory
+    // (loaded there, at 4096^3: r = 32 18.6 us, r = 16 12.5).
+    auto stage = [&] {
+        if (right) stage_x_gamma(a, RP, xg, tid, 512);
+#pragma unroll
+        for (int b = 0; b < RB; ++b) {
+            const int r0 = (blk * RB + b) * 32;
+#pragma unroll
+            for (int e0 = 0; e0 < RP * 32; e0 += 512) {
+                const int e = e0 + tid;
+                if (right) {
+                    const int u = e >> 5, j = r0 + (e & 31);
+                    const float z = a.Zt[(size_t)min(u, r - 1) * a.N + min(j, a.N - 1)];
+                    own[b][u * 33 + (e & 31)] = u < r && j < a.N ? z : 0.f;
+                } else if (e < 32 * r) {
+                    own[b][e] = a.U[min((size_t)r0 * r + e, (size_t)a.M * r - 1)] * a.Sig[e % r];
+                }
+            }
+        }
+        if (tid < 32 * RB) step[tid] = (right ? a.sB : a.sA)[min(blk * RB * 32 + tid, rows - 1)];
+    };
+    // blocks ahead: whole blocks of codes, and of the planes as whole blocks, or as halves where they are wide
+    if constexpr (NT <= 2 || NT * RB <= 3) {
+        struct Stage { CodeBlock<FMT> c[RB]; FactorHalf<NT, PL> f[2]; } st[AHEAD];
+        auto load = [&](Stage& s, int kb) {
+            const int k = min(kb, nkb - 1);     // (past the end: the last one again, not used)
+#pragma unroll
+            for (int b = 0; b < RB; ++b) s.c[b].load(codes, blk * RB + b, rows, k, K, nkb, li, kq);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) s.f[h].load(Wf, k, h, lane);
+        };
+        if (kb0 < kb1) {
+#pragma unroll
+            for (int i = 0; i < AHEAD - 1; ++i) load(st[i], kb0 + i);
+        }
+        stage();
+        for (int kb = kb0; kb < kb1; kb += AHEAD) {
+#pragma unroll
+            for (int i = 0; i < AHEAD; ++i) {
+                if (kb + i < kb1) {
+                    load(st[(i + AHEAD - 1) % AHEAD], kb + i + AHEAD - 1);
+                    __builtin_amdgcn_sched_barrier(0);      // (or the loads sink to where they are used, and nothing is ahead)
+#pragma unroll
+                    for (int b = 0; b < RB; ++b) {
+                        v8bf af[2][2];
+                        st[i].c[b].operands(af, kb + i, K, kq);
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) panel_products<NT, PL>(af[h], st[i].f[h], acc[b]);
+                    }
+                }
+            }
+        }
+    } else {
+        CodeBlock<FMT> c[RB];
+        FactorHalf<NT, PL> f[2];
+        auto load_codes = [&](int kb) {
+#pragma unroll
+            for (int b = 0; b < RB; ++b) c[b].load(codes, blk * RB + b, rows, min(kb, nkb - 1), K, nkb, li, kq);
+        };
+        if (kb0 < kb1) { load_codes(kb0); f[0].load(Wf, kb0, 0, lane); }
+        stage();
+        for (int kb = kb0; kb < kb1; ++kb) {
+            v8bf af[RB][2][2];
+#pragma unroll
+            for (int b = 0; b < RB; ++b) c[b].operands(af[b], kb, K, kq);
+            load_codes(kb + 1);
+            f[1].load(Wf, kb, 1, lane);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int b = 0; b < RB; ++b) panel_products<NT, PL>(af[b][0], f[0], acc[b]);
+            __builtin_amdgcn_sched_barrier(0);
+            f[0].load(Wf, min(kb + 1, nkb - 1), 0, lane);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int b = 0; b < RB; ++b) panel_products<NT, PL>(af[b][1], f[1], acc[b]);
+        }
+    }
+#pragma unroll
+    for (int b = 0; b < RB; ++b) {
+        const int r0 = (blk * RB + b) * 32;
+        if (r0 >= rows) break;              // (uniform)
+        if (b > 0) __syncthreads();
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) red[(wave * 32 + 16 * t + 4 * kq + v) * RP + 16 * nt + li] = acc[b][t][nt][v];
+        __syncthreads();
+        const int n = min(32, rows - r0) * R2P;
+        float* const out = (right ? a.Rp : a.Lp) + (size_t)r0 * R2P;
+        for (int e = tid; e < n; e += 512) {
+            const int row = e / R2P, c = e - row * R2P;
+            const int pc = right ? c : c - r;       // column of the product, if any
+            float v = 0.f;
+            if (pc >= 0 && pc < r) {
+#pragma unroll
+                for (int w = 0; w < PANEL_WAVES; ++w) v += red[(w * 32 + row) * RP + pc];
+                v *= step[32 * b + row];
+                if (right) {
+                    for (int u0 = 0; u0 < RP; u0 += 8) {       // rows u >= r of Zt are zero
+#pragma unroll
+                        for (int t = 0; t < 8; ++t) v = fmaf(xg[pc * (RP + 1) + u0 + t], own[b][(u0 + t) * 33 + row], v);
+                    }
+                }
+            } else if (c < 2 * r) {
+                v = right ? a.Gam[c - r] * own[b][(c - r) * 33 + row] : own[b][row * r + c];
+            }
+            out[e] = v;
+        }
+    }
+}
+
+// The same for tall operands with short rows (K <= 640) of bytes and factors of at most 16 columns: all planes fit in LDS (three
+// planes x 16 columns x Kp bfloat16), so workgroups are persistent -- two of eight waves per CU, the planes copied once -- and after
+// the one barrier behind that copy the waves are on their own: a wave takes the 16-row tiles w, w + W, w + 2W, ... (W waves in the
+// grid) and loads a tile's codes at once (NC 16-byte loads per lane, the whole row); the sixteen waves of a CU are at
+// different points of that cycle, which keeps loads in flight while others compute.  blockIdx.z: 0 left panel, 1 right.
 template <int PL, int NC>
-__global__ __launch_bounds__(512, 4) void codes_mul_rows_kernel(CodesJobBf16 j0, CodesJobBf16 j1, int K, int Kp) {
-    extern __shared__ __align__(16) uint16_t bsr[];       // [PL][16][Kp + 8]
-    const CodesJobBf16 job = blockIdx.z == 0 ? j0 : j1;
-    const int ntiles = (job.rows + 15) >> 4;
+__global__ __launch_bounds__(512, 4) void panels_rows_kernel(PanelArgs a) {
+    extern __shared__ __align__(16) uint16_t wf[];        // [k block][plane][step][lane][8]; right: X Gamma behind it
+    __shared__ float xg[16 * 17];
+    const bool right = blockIdx.z == 1;
+    const int rows = right ? a.N : a.M, K = a.K, r = a.r, R2P = a.R2P, nkb = pk_kblocks(K);
+    const int ntiles = (rows + 15) >> 4;
     if ((int)blockIdx.x * 8 >= ntiles) return;            // no tile for any wave of this workgroup
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int li = lane & 15, kq = lane >> 4;
-    const int LDK = Kp + 8, ppr = Kp >> 3;
-    for (int p = threadIdx.x; p < PL * 16 * ppr; p += 512) {
-        const int rowp = p / ppr, seg = p - rowp * ppr;
-        *reinterpret_cast<uint4*>(&bsr[rowp * LDK + 8 * seg]) =
-            *reinterpret_cast<const uint4*>(job.Bp + (size_t)rowp * Kp + 8 * seg);
-    }
+    const uint4* const src = reinterpret_cast<const uint4*>(right ? a.Vf : a.Wf);
+    for (int p = threadIdx.x; p < nkb * 6 * 64; p += 512) reinterpret_cast<uint4*>(wf)[p] = src[p];
+    if (right) stage_x_gamma(a, 16, xg, threadIdx.x, 512);
     __syncthreads();
-    const int nwaves = gridDim.x * 8;
-    // codes past K meet zero planes and rows past the end re-read the last row (never stored): clamped
-    // addresses, no masks
-    auto load_tile = [&](uint4 (&ca)[NC], int tile) {
-        const int8_t* ap = job.Cq + (size_t)min(tile * 16 + li, job.rows - 1) * K;
+    const int8_t* const codes = right ? a.codesB : a.codesA;
+    const int nwaves = gridDim.x * 8, range = panel_range(nkb);
+    const float scale = (right ? a.Gam : a.Sig)[min(li, r - 1)];
+    for (int tile = blockIdx.x * 8 + wave; tile < ntiles; tile += nwaves) {
+        // codes past K meet zero planes and rows past the end re-read the last row (never stored): clamped addresses, no masks
+        uint4 ca[NC];
+        const int8_t* ap = codes + (size_t)min(tile * 16 + li, rows - 1) * K;
 #pragma unroll
         for (int c = 0; c < NC; ++c) ca[c] = load_codes16<true>(ap, K, 64 * c + 16 * kq);
-    };
-    auto process = [&](uint4 (&ca)[NC], int tile) {
-        v4f acc = (v4f){0.f, 0.f, 0.f, 0.f};
+        float step[4], us[4];       // (the epilogue's operands come beside the codes)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int row = min(tile * 16 + 4 * kq + v, rows - 1), col = min(li, r - 1);
+            step[v] = (right ? a.sB : a.sA)[row];
+            us[v] = right ? a.Zt[(size_t)col * rows + row] : a.U[(size_t)row * r + col];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        v4f total = (v4f){0.f, 0.f, 0.f, 0.f}, acc = total;
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
-            if (64 * c >= Kp) continue;             // the planes end at Kp (uniform)
+            if (c >= nkb) continue;             // (uniform)
+            if (c > 0 && c % range == 0) {      // the sums of a range of their own, as in panels_kernel
+                total += acc;
+                acc = (v4f){0.f, 0.f, 0.f, 0.f};
+            }
             if ((K & 15) && 64 * c + 64 > K) ca[c] = tail16(ca[c], max(0, 64 * c + 16 * kq - (K - 16)));     // uniform
 #pragma unroll
-            for (int sidx = 0; sidx < 2; ++sidx) {
-                const v8bf af = sidx == 0 ? codes_to_bf16(ca[c].x, ca[c].y) : codes_to_bf16(ca[c].z, ca[c].w);
+            for (int h = 0; h < 2; ++h) {
+                const v8bf af = h == 0 ? codes_to_bf16(ca[c].x, ca[c].y) : codes_to_bf16(ca[c].z, ca[c].w);
 #pragma unroll
-                for (int pl = 0; pl < PL; ++pl) {
-                    union { uint4 u; v8bf v; } b;
-                    b.u = *reinterpret_cast<const uint4*>(&bsr[(pl * 16 + li) * LDK + 64 * c + 16 * kq + 8 * sidx]);
-                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, b.v, acc, 0, 0, 0);
-                }
+                for (int pl = 0; pl < PL; ++pl)
+                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        af, *reinterpret_cast<const v8bf*>(wf + ((c * 3 + pl) * 2 + h) * FACTOR_PIECE + lane * 8), acc, 0, 0, 0);
             }
         }
+        total += acc;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const int row = tile * 16 + 4 * kq + v;
-            if (row < job.rows) job.partial[(size_t)row * 16 + li] = acc[v];
-        }
-    };
-    uint4 x[NC];
-    for (int tile = blockIdx.x * 8 + wave; tile < ntiles; tile += nwaves) {
-        load_tile(x, tile);
-        process(x, tile);
-    }
-}
-
-// The same product from packed codes, at every K and width, with the same products in the same order (the same bits).  Lane
-// (li, kq) needs codes 16 kq .. +16 of a row's 64: PK8: 16 bytes of the block; PK6: half of a lane's 24 bytes, which it loads whole,
-// and one conversion instruction makes the 32 bfloat16 values of its two 16-row tiles.  A wave owns a block of 32 rows; slabs of four k blocks, the
-// planes staged as above.
-template <int FMT, int NT, int PL>
-__global__ __launch_bounds__(256, 1) void codes_mul_packed_kernel(CodesJobBf16 j0, CodesJobBf16 j1, int K, int Kp) {
-    using S = CodesShape<NT, PL>;
-    constexpr int RP = S::RP, KB = S::KB, LDK = S::LDK, NC = S::NC;
-    typedef uint32_t v6u __attribute__((ext_vector_type(6)));
-    typedef __bf16 v32bf __attribute__((ext_vector_type(32)));
-    __shared__ __align__(16) uint16_t bs[PL * RP * LDK];
-    const CodesJobBf16 job = blockIdx.z == 0 ? j0 : j1;
-    if ((int)blockIdx.x * 128 >= job.rows || (int)blockIdx.y >= job.splits) return;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int li = lane & 15, kq = lane >> 4;
-    const int nkb = pk_kblocks(K), nrb = (job.rows + 31) >> 5;
-    const int rb = blockIdx.x * 4 + wave;
-    const int kb = blockIdx.y * job.chunk, ke = min(K, kb + job.chunk);
-    // (blocks past the end: the last one again, never stored)
-    const uint8_t* const ap = reinterpret_cast<const uint8_t*>(job.Cq) + (size_t)min(rb, nrb - 1) * nkb * pk_block(FMT);
-    const int unit = 32 * (kq >> 1) + li;
-    v4f acc[2][NT];
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = (v4f){0.f, 0.f, 0.f, 0.f};
-    struct Codes { uint4 w[NC][2]; uint2 x[FMT == PK6 ? NC : 1][2]; };
-    auto load = [&](Codes& c, int ks) {
-#pragma unroll
-        for (int i = 0; i < NC; ++i) {
-            const uint8_t* blk = ap + (size_t)min(ks / PK_K + i, nkb - 1) * pk_block(FMT);
-#pragma unroll
-            for (int mt = 0; mt < 2; ++mt) {
-                if constexpr (FMT == PK8) {
-                    c.w[i][mt] = *reinterpret_cast<const uint4*>(blk + 1024 * (kq & 1) + (unit + 16 * mt) * 16);
-                    continue;
+            if (row >= rows) continue;
+            float* const out = (right ? a.Rp : a.Lp) + (size_t)row * R2P;
+            if (li < r) {
+                float p = total[v] * step[v];
+                if (right) {
+#pragma unroll 1
+                    for (int u = 0; u < r; ++u) p = fmaf(xg[li * 17 + u], a.Zt[(size_t)u * rows + row], p);
                 }
-                c.w[i][mt] = *reinterpret_cast<const uint4*>(blk + (unit + 16 * mt) * 16);
-                c.x[i][mt] = *reinterpret_cast<const uint2*>(blk + 1024 + (unit + 16 * mt) * 8);
+                out[right ? li : r + li] = p;
+                out[right ? r + li : li] = us[v] * scale;
             }
-        }
-    };
-    for (int ks = kb; ks < ke; ks += KB) {
-        Codes ca;
-        load(ca, ks);
-        if (ks > kb) __syncthreads();       // previous slab no longer read
-        for (int p0 = threadIdx.x; p0 < S::PIECES; p0 += 256 * S::BATCH) {
-            uint4 t[S::BATCH];
-#pragma unroll
-            for (int u = 0; u < S::BATCH; ++u) {
-                const int p = min(p0 + 256 * u, S::PIECES - 1);
-                const int rowp = p / (KB / 8), seg = p - rowp * (KB / 8);
-                const int k = ks + 8 * seg;
-                const uint4 v = *reinterpret_cast<const uint4*>(job.Bp + (size_t)rowp * Kp + min(k, Kp - 8));
-                t[u] = (k < Kp) ? v : make_uint4(0u, 0u, 0u, 0u);
-            }
-#pragma unroll
-            for (int u = 0; u < S::BATCH; ++u) {
-                const int p = p0 + 256 * u;
-                if (p < S::PIECES) {
-                    const int rowp = p / (KB / 8), seg = p - rowp * (KB / 8);
-                    *reinterpret_cast<uint4*>(&bs[rowp * LDK + 8 * seg]) = t[u];
-                }
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            if (ks + 64 * c < ke) {             // uniform
-                v32bf val;
-                if constexpr (FMT == PK6) {
-                    uint32_t h[2][3];
-#pragma unroll
-                    for (int mt = 0; mt < 2; ++mt) {
-                        const uint4 w = ca.w[c][mt];
-                        const uint2 x = ca.x[c][mt];
-                        h[mt][0] = (kq & 1) ? w.w : w.x;        // (stored order: words 0 1 2 3 | 4 5)
-                        h[mt][1] = (kq & 1) ? x.x : w.y;
-                        h[mt][2] = (kq & 1) ? x.y : w.z;
-                    }
-                    const v6u six = {h[0][0], h[0][1], h[0][2], h[1][0], h[1][1], h[1][2]};
-                    val = __builtin_amdgcn_cvt_scalef32_pk32_bf16_fp6(six, 8.0f);
-                }
-#pragma unroll
-                for (int sidx = 0; sidx < 2; ++sidx) {
-                    v8bf af[2];
-                    if constexpr (FMT == PK8) {
-#pragma unroll
-                        for (int mt = 0; mt < 2; ++mt)
-                            af[mt] = sidx == 0 ? codes_to_bf16(ca.w[c][mt].x, ca.w[c][mt].y) : codes_to_bf16(ca.w[c][mt].z, ca.w[c][mt].w);
-                    } else if (sidx == 0) {
-                        af[0] = __builtin_shufflevector(val, val, 0, 1, 2, 3, 4, 5, 6, 7);
-                        af[1] = __builtin_shufflevector(val, val, 16, 17, 18, 19, 20, 21, 22, 23);
-                    } else {
-                        af[0] = __builtin_shufflevector(val, val, 8, 9, 10, 11, 12, 13, 14, 15);
-                        af[1] = __builtin_shufflevector(val, val, 24, 25, 26, 27, 28, 29, 30, 31);
-                    }
-#pragma unroll
-                    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                        for (int pl = 0; pl < PL; ++pl) {
-                            union { uint4 u; v8bf v; } b;
-                            b.u = *reinterpret_cast<const uint4*>(
-                                &bs[(pl * RP + 16 * nt + li) * LDK + 64 * c + 16 * kq + 8 * sidx]);
-#pragma unroll
-                            for (int mt = 0; mt < 2; ++mt)
-                                acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[mt], b.v, acc[mt][nt], 0, 0, 0);
-                        }
-                }
-            }
+            if (2 * r + li < R2P) out[2 * r + li] = 0.f;
         }
     }
-    float* out = job.partial + (size_t)blockIdx.y * job.rows * RP;
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int row = rb * 32 + 16 * mt + 4 * kq + v;
-                if (row < job.rows) out[(size_t)row * RP + 16 * nt + li] = acc[mt][nt][v];
-            }
 }
 
 // ---------------------------------------------------------------------------
@@ -1308,12 +1339,9 @@ PassPlan plan_pass_n(int rows, int cols, int LP) {
     return p;
 }
 
-PassPlan plan_codes(int rows, int K) {
-    PassPlan p;
-    int s = pick_splits(ceil_div(rows, 64), K, 4 * KCHUNK, 512, MAX_SPLITS);
-    p.chunk = max(1, ceil_div(ceil_div(K, s), KCHUNK)) * KCHUNK;
-    p.splits = ceil_div(K, p.chunk);
-    return p;
+int codes_splits(int rows, int K) {
+    const int s = pick_splits(ceil_div(rows, 64), K, 4 * KCHUNK, 512, MAX_SPLITS);
+    return ceil_div(K, max(1, ceil_div(ceil_div(K, s), KCHUNK)) * KCHUNK);
 }
 
 // Few column strips: many row chunks, of 32 rows and more with one tile of sketch columns, of 128 with more.  128 / 32, us
@@ -1344,10 +1372,6 @@ size_t pass_partial_floats(int rows, int cols, int LP) {
     part = max(part, LP * most_partial_rows(cols, 64, rows, 128, 512, MAX_SPLITS_T));
     part = max(part, 16 * most_partial_rows(cols, 64, rows, 32, 512, MAX_SPLITS_T));
     return max(part, LP * max((size_t)pn.splits * rows, (size_t)pt.splits * cols));
-}
-
-size_t codes_partial_rows(int rows, int K) {
-    return max((size_t)plan_codes(rows, K).splits * rows, most_partial_rows(rows, 64, K, 4 * KCHUNK, 512, MAX_SPLITS));
 }
 
 // The jobs of one launch: at most one with scales by row and one with scales by column.  Workgroup shape and plan of an
@@ -1499,55 +1523,40 @@ int launch_resid_mul_t(const PassOperand* op, int nop, QuantParams q, int LP, hi
     return LRQMM_ERR_UNSUPPORTED;
 }
 
-int launch_codes_mul_n2(const int8_t* codesA, int rowsA, const uint16_t* WA3, PassPlan planA,
-                        float* partialA, const int8_t* codesB, int rowsB, const uint16_t* WB3,
-                        PassPlan planB, float* partialB, int K, int Kp, int LP, hipStream_t st, int planes, int packed) {
-    const CodesJobBf16 j0 = {codesA, WA3, partialA, rowsA, planA.chunk, planA.splits};
-    const CodesJobBf16 j1 = {codesB, WB3, partialB, rowsB, planB.chunk, planB.splits};
-    if (packed) {
-        const dim3 grid(ceil_div(max(rowsA, rowsB), 128), max(planA.splits, planB.splits), 2);
-#define LRQ_CMP(FMT, PLV) NT_SWITCH(LP / 16, hipLaunchKernelGGL((codes_mul_packed_kernel<FMT, NT_, PLV>), grid, dim3(256), 0, st, j0, j1, K, Kp))
-        if (packed == PK8) { if (planes == 2) { LRQ_CMP(PK8, 2); } else if (planes == 1) { LRQ_CMP(PK8, 1); } else { LRQ_CMP(PK8, 3); } }
-        else               { if (planes == 2) { LRQ_CMP(PK6, 2); } else if (planes == 1) { LRQ_CMP(PK6, 1); } else { LRQ_CMP(PK6, 3); } }
-#undef LRQ_CMP
-        LRQ_CHECK_LAUNCH();
-        return LRQMM_OK;
-    }
-    if (K < 16) {       // (then the factor has at most 15 columns)
-        if (LP != 16) return LRQMM_ERR_UNSUPPORTED;
-        dim3 g1(ceil_div(max(rowsA, rowsB), 128), max(planA.splits, planB.splits), 2);
-        if (planes == 2)      hipLaunchKernelGGL((codes_mul_bf16_kernel<1, 2, 2, false>), g1, dim3(256), 0, st, j0, j1, K, Kp);
-        else if (planes == 1) hipLaunchKernelGGL((codes_mul_bf16_kernel<1, 1, 2, false>), g1, dim3(256), 0, st, j0, j1, K, Kp);
-        else                  hipLaunchKernelGGL((codes_mul_bf16_kernel<1, 3, 2, false>), g1, dim3(256), 0, st, j0, j1, K, Kp);
-        LRQ_CHECK_LAUNCH();
-        return LRQMM_OK;
-    }
-    // short rows, one tile of factor columns, no split of the reduction: the persistent kernel
-    const size_t lds_rows = (size_t)planes * 16 * (Kp + 8) * sizeof(uint16_t);
-    if (LP == 16 && K <= 640 && planA.splits == 1 && planB.splits == 1 && lds_rows <= 64 * 1024) {
+int launch_panels(const PanelArgs& in, int RP, int planes, int packed, hipStream_t st) {
+    PanelArgs a = in;
+    const int most = max(a.M, a.N), nkb = pk_kblocks(a.K);
+    if (packed == PK_NONE && RP == 16 && a.K >= 16 && a.K <= 640 && most >= PANEL_ROWS_MIN) {
         int dev = 0, cus = 0;
         if (hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
             return LRQMM_ERR_HIP;
-        dim3 g2(min(ceil_div(ceil_div(max(rowsA, rowsB), 16), 8), 2 * cus), 1, 2);
-        const int nc = ceil_div(K, 64);
-#define LRQ_CMR(PLV, NCV) hipLaunchKernelGGL((codes_mul_rows_kernel<PLV, NCV>), g2, dim3(512), lds_rows, st, j0, j1, K, Kp)
-#define LRQ_CMR_NC(PLV) do { if (nc <= 2) LRQ_CMR(PLV, 2); else if (nc <= 4) LRQ_CMR(PLV, 4); else if (nc <= 6) LRQ_CMR(PLV, 6); \
-        else if (nc <= 8) LRQ_CMR(PLV, 8); else LRQ_CMR(PLV, 10); } while (0)
-        if (planes == 2) LRQ_CMR_NC(2); else if (planes == 1) LRQ_CMR_NC(1); else LRQ_CMR_NC(3);
-#undef LRQ_CMR_NC
-#undef LRQ_CMR
+        const dim3 grid(min(ceil_div(ceil_div(most, 16), 8), 2 * cus), 1, 2);
+        const size_t lds = (size_t)nkb * 6 * FACTOR_PIECE * sizeof(uint16_t);
+#define LRQ_PR(PLV, NCV) hipLaunchKernelGGL((panels_rows_kernel<PLV, NCV>), grid, dim3(512), lds, st, a)
+#define LRQ_PR_NC(PLV) do { if (nkb <= 2) LRQ_PR(PLV, 2); else if (nkb <= 4) LRQ_PR(PLV, 4); else if (nkb <= 6) LRQ_PR(PLV, 6); \
+        else if (nkb <= 8) LRQ_PR(PLV, 8); else LRQ_PR(PLV, 10); } while (0)
+        if (planes == 2) LRQ_PR_NC(2); else if (planes == 1) LRQ_PR_NC(1); else LRQ_PR_NC(3);
+#undef LRQ_PR_NC
+#undef LRQ_PR
         LRQ_CHECK_LAUNCH();
         return LRQMM_OK;
     }
-    // Up to 48 factor columns a workgroup takes 128 rows (two 16-row tiles per wave): with the 256-deep slabs
-    // two or three workgroups share a CU and cover each other's load and staging phases (4096^2 codes, 32
-    // columns: 17.5 -> 16.0 us; 16 columns: 13.8 -> 11.3 us; same bits).  Wider factors keep 256 rows.
-#define LRQ_CM(PLV, MTV) NT_SWITCH(LP / 16, hipLaunchKernelGGL((codes_mul_bf16_kernel<NT_, PLV, MTV>), dim3(ceil_div(max(rowsA, rowsB), 64 * MTV), max(planA.splits, planB.splits), 2), dim3(256), 0, st, j0, j1, K, Kp))
-#define LRQ_CM_PL(MTV) do { if (planes == 2) { LRQ_CM(2, MTV); } else if (planes == 1) { LRQ_CM(1, MTV); } else { LRQ_CM(3, MTV); } } while (0)
-    if (LP <= 48) LRQ_CM_PL(2); else LRQ_CM_PL(4);
-#undef LRQ_CM_PL
-#undef LRQ_CM
+    const bool two = ceil_div(a.M, 64) + ceil_div(a.N, 64) >= PANEL_TWO_MIN;      // 64 rows a workgroup: half the reads of the planes
+    const int block = two ? 64 : 32;
+    a.nbR = ceil_div(a.N, block);
+    const dim3 grid(a.nbR + ceil_div(a.M, block));
+#define LRQ_PK(FMT, PLV)                                                                                                       \
+    do {                                                                                                                       \
+        if (two) { NT_SWITCH(RP / 16, hipLaunchKernelGGL((panels_kernel<FMT, NT_, PLV, 2>), grid, dim3(512), 0, st, a)); }                                                                              \
+        else { NT_SWITCH(RP / 16, hipLaunchKernelGGL((panels_kernel<FMT, NT_, PLV, 1>), grid, dim3(512), 0, st, a)); }     \
+    } while (0)
+#define LRQ_PK_PL(FMT) do { if (planes == 2) { LRQ_PK(FMT, 2); } else if (planes == 1) { LRQ_PK(FMT, 1); } else { LRQ_PK(FMT, 3); } } while (0)
+    if (packed == PK6)      LRQ_PK_PL(PK6);
+    else if (packed == PK8) LRQ_PK_PL(PK8);
+    else                    LRQ_PK_PL(PK_NONE);
+#undef LRQ_PK_PL
+#undef LRQ_PK
     LRQ_CHECK_LAUNCH();
     return LRQMM_OK;
 }

@@ -418,3 +418,36 @@ def test_gemm_on_both_sides_of_the_large_tile_limit(M, N, rank):
                                         (1030, 2050, 64, 36), (2050, 2049, 129, 16), (2050, 2049, 100, 49), (9000, 33, 40, 8)])
 def test_gemm_panel_widths_on_small_tiles(M, N, K, rank):
     test_gemm_wide_panels_on_large_tiles(M, N, K, rank)
+
+
+# Panels: rows of one workgroup short and over (32, 64 rows), k blocks that eight waves do not share evenly or that leave waves idle,
+# every width of the factors; 64 rows a workgroup (16384 rows and more, both sides of the limit); tall operands with short rows in
+# the persistent kernel, on both sides of its limits in rows, columns of the factor and K; each operand as the tall one.
+@pytest.mark.parametrize("M,N,K,bits,rank", [(33, 31, 65, 8, 1), (65, 97, 513, 8, 16), (64, 40, 577, 4, 17), (130, 95, 1100, 8, 33), (100, 129, 700, 4, 50),
+                                             (96, 161, 2000, 8, 80), (16289, 64, 700, 8, 12), (16353, 30, 700, 8, 12), (16390, 70, 130, 4, 40),
+                                             (17000, 90, 513, 4, 80), (16383, 60, 576, 4, 8), (16385, 61, 575, 4, 8), (20000, 33, 640, 8, 16),
+                                             (20001, 20, 641, 8, 3), (50, 16401, 129, 4, 5), (50, 17001, 90, 8, 64)])
+def test_gemm_panels(M, N, K, bits, rank):
+    """Sampled rows against float64.  A term of the products is exact, the planes carry the factors to 2^-27 and a sum of K terms in
+    float32 is off by less than K 2^-24 of the terms' absolute sum, of the order of sqrt(K) 2^-24 in practice: 3e-6, as above."""
+    import paper_2409_18772_amd as L
+    rng = np.random.default_rng(M + N + K)
+    say("panels", M, N, K, bits, rank)
+    q = 2 ** (bits - 1)
+    Aq = rng.integers(-q, q, size=(M, K), dtype=np.int8)
+    Bt = rng.integers(-q, q, size=(N, K), dtype=np.int8)
+    amA, amB = (rng.uniform(0.5, 2.0, n).astype(np.float32) for n in (M, N))
+    f32 = lambda *shape: rng.standard_normal(shape).astype(np.float32)
+    U, S, Vt, W, G, Zt = f32(M, rank), np.abs(f32(rank)), f32(rank, K), f32(K, rank), np.abs(f32(rank)), f32(rank, N)
+    C = to_np(L.lrqmm_gemm(to_dev(Aq), to_dev(amA), to_dev(Bt), to_dev(amB), bits, tuple(map(to_dev, (U, S, Vt))),
+                           tuple(map(to_dev, (W, G, Zt)))))
+    rows = np.unique(np.r_[0:3, 30:34, 62:66, M - 35:M - 30, M - 3:M, rng.integers(0, M, 40)])
+    rows = rows[(rows >= 0) & (rows < M)]
+    s = lambda am: (am / np.float32(q - 1)).astype(np.float64)
+    d = np.float64
+    At, Bd = Aq[rows] * s(amA)[rows, None], Bt.T * s(amB)[None, :]
+    US, GZ = U[rows].astype(d) * S, G[:, None].astype(d) * Zt
+    want = At @ Bd + US @ (Vt.astype(d) @ Bd) + (At @ W.astype(d) + US @ (Vt.astype(d) @ W.astype(d))) @ GZ
+    assert rel_fro(want, C[rows]) < 3e-6
+    # ... and no row or column far from it
+    assert np.abs(C[rows] - want).max() < 1e-4 * np.sqrt((want ** 2).mean())
