@@ -91,7 +91,7 @@ struct MatmulWs {
     float *amaxA, *amaxB, *U, *Sig, *Vt, *W, *Gam, *Zt;
     uint32_t* tick;
     int32_t* parts;                   // partial sums of the early integer product's K ranges
-    void *sub, *subA, *subB;          // gemm scratch aliases the two rsvd regions
+    void *sub, *subA, *subB;          // scratch of the products and of the two factorizations
     size_t sub_bytes, subA_bytes, subB_bytes;
 };
 
@@ -125,14 +125,14 @@ size_t carve_matmul(Arena& a, int M, int N, int K, int rank, int oversample, Mat
         Arena ra(nullptr), rb(nullptr);
         sa = align_up(carve_rsvd(ra, M, K, LRQMM_AXIS_ROW, LP, rank, nullptr), 256);
         sb = align_up(carve_rsvd(rb, K, N, LRQMM_AXIS_COL, LP, rank, nullptr), 256);
-        if (sa + sb > sub) sub = sa + sb;
     }
-    t.sub = a.base ? a.base + a.off : nullptr;
-    t.sub_bytes = sub;
-    t.subA = t.sub;
+    t.subA = a.base ? a.base + a.off : nullptr;
     t.subA_bytes = sa;
     t.subB = a.base ? a.base + a.off + sa : nullptr;
     t.subB_bytes = sb;
+    a.off += sa + sb;
+    t.sub = a.base ? a.base + a.off : nullptr;
+    t.sub_bytes = sub;
     a.off += sub;
     if (w) *w = t;
     return a.off;
@@ -320,12 +320,12 @@ enum class FirstPass {
 
 // Appends the launches of one factorization, or of two that advance together (one launch per step for both; their
 // operands have different axes), to `ops`.  The sketches are in place.  svd_index: position of the small SVD.
-// basis_suffices: the caller only uses the product U diag(Sigma) Vt, and nothing is truncated (oversample == 0): U = Q,
+// stop_at_basis: the list ends with the last product's partials (see launch_basis_panels).  basis_suffices: the caller only uses the product U diag(Sigma) Vt, and nothing is truncated (oversample == 0): U = Q,
 // Sigma = 1, Vt = Q^T R carry the same product as the SVD's factors.  packed: the format of the quantizing pass's codes.
 static void factor_launches(LaunchList& ops, const Factor* factors, int n, FirstPass first, QuantParams q, int rank,
                             int oversample, int power_iters, int planes_first, int planes, int planes_last, hipStream_t st,
                             size_t* svd_index, float* one_read_amax = nullptr, bool basis_suffices = false,
-                            int packed = PK_NONE) {
+                            int packed = PK_NONE, bool stop_at_basis = false) {
     struct Pair { Factor f[2]; PassOperand op[2]; };
     auto p = std::make_shared<Pair>();
     for (int i = 0; i < n; ++i) { p->f[i] = factors[i]; p->op[i] = factors[i].op; }
@@ -377,6 +377,7 @@ static void factor_launches(LaunchList& ops, const Factor* factors, int n, First
     }
     // B^T = R^T Q (cols x l), its Gram B B^T, small SVD, U = Q U', V = B^T U' / sigma
     ops.push_back([=] { return launch_resid_mul_t(p->op, n, q, LP, st, planes_last); });
+    if (stop_at_basis) return;
     if (basis_suffices) {
         ops.push_back([=] {
             BasisJob bj[2];
@@ -532,7 +533,7 @@ static int gemm_impl(int M, int N, int K, int bits, int rank, const int8_t* Aq, 
                      const int8_t* BqT, const float* amaxB, const float* U, const float* Sig, const float* Vt,
                      const float* W, const float* Gam, const float* Zt, GemmOut out, int32_t* Cint_or_null,
                      void* workspace, size_t workspace_bytes, void* stream, int prof_slot,
-                     hipEvent_t raw_sums_ready = nullptr, int planes = 3, int packed = PK_NONE) {
+                     hipEvent_t raw_sums_ready = nullptr, int planes = 3, int packed = PK_NONE, const PanelArgs* ready = nullptr) {
     float* const C = out.C;
     if (M < 0 || N < 0 || K < 0 || rank < 0 || out.ldc < N) return LRQMM_ERR_INVALID_ARG;
     if (!dims_ok(M, N, K) || !output_ok(M, N)) return LRQMM_ERR_UNSUPPORTED;
@@ -561,11 +562,14 @@ static int gemm_impl(int M, int N, int K, int bits, int rank, const int8_t* Aq, 
     int R2P = 0;
     const int RP = pad_to(rank, 16);
     if (rank > 0) {
-        LRQ_TRY(launch_panel_prep(M, N, K, rank, RP, q.qmaxf, amaxA, amaxB, W, Vt, w.lamA, w.sA, w.lamB, w.sB,
-                                  w.Wf, w.Vf, w.X, st));
         R2P = pad_to(2 * rank, 8);
         PanelArgs pa = {Aq, BqT, w.Wf, w.Vf, U, Sig, w.sA, w.sB, w.X, Gam, Zt, w.Lp, w.Rp, M, N, K, rank, R2P};
         pa.nslices = ceil_div(K, ceil_div(K, vtw_slices(K)));
+        pa.ldu = rank;
+        if (ready) pa = *ready;
+        else LRQ_TRY(launch_panel_prep(M, N, K, rank, RP, q.qmaxf, amaxA, amaxB, W, Vt, w.lamA, w.sA, w.lamB, w.sB, w.Wf, w.Vf, w.X, st));
+        w.sA = const_cast<float*>(pa.sA);
+        w.sB = const_cast<float*>(pa.sB);
         LRQ_TRY(launch_panels(pa, RP, K % 16 == 0 ? planes : 3, packed, st));       // (as the interface states)
     }
     if (raw_sums_ready) {
@@ -695,10 +699,12 @@ int lrqmm_matmul_ex(int M, int N, int K, int bits, int rank, int oversample, int
     // away.  Up to 16 columns; a call with a wider sketch gives the bits of the separate quantize, rsvd and gemm calls (a
     // narrow one's first product differs from them anyway).
     const bool basis_suffices = oversample == 0 && LP == 16;
+    const bool basis_panels = factored && basis_suffices && basis_slices(K) > 0;
     if (slot >= 0) g_prof.early[slot] = early;
     hipStream_t gst = early ? side->gemm_stream : pst;
     // Planned first and then issued (see LaunchList): opsA holds the chain of both operands, or A's beside opsB with B's.
     LaunchList opsA, opsB;
+    Factor f[2] = {};
     size_t svd = 0, svdB = 0;       // positions of the small-SVD launches in opsA (and opsB)
     int rc;
     auto mark = [&](LaunchList& ops, int event, hipStream_t st) {
@@ -725,7 +731,6 @@ int lrqmm_matmul_ex(int M, int N, int K, int bits, int rank, int oversample, int
         // The group maxima come first (one read of the operands); the operand's second read yields codes, step vectors and
         // the sketch product Y = R.Omega in one launch.  The sketches are filled by the chain's first launch, which also
         // clears the column maxima (they are formed with atomic maxima).
-        Factor f[2];
         LRQ_TRY(make_factor(&f[0], A, lda, M, K, LRQMM_AXIS_ROW, LP, rank, w.amaxA, w.Aq, w.U, w.Sig, w.Vt, w.subA,
                             w.subA_bytes));
         LRQ_TRY(make_factor(&f[1], B, ldb, K, N, LRQMM_AXIS_COL, LP, rank, w.amaxB, w.BqT, w.W, w.Gam, w.Zt, w.subB,
@@ -740,14 +745,14 @@ int lrqmm_matmul_ex(int M, int N, int K, int bits, int rank, int oversample, int
                 opsA.push_back([=] { return launch_absmax_pair(A, lda, M, K, amaxA, nullptr, 0, 0, nullptr, qp, per_tensor, pst); });
             mark(opsA, 1, pst);
             factor_launches(opsA, &f[0], 1, one_read ? FirstPass::one_read : quant, qp, rank, oversample, power_iters, pl_first,
-                            pl, pl_last, pst, &svd, amaxA, basis_suffices, packed);
+                            pl, pl_last, pst, &svd, amaxA, basis_suffices, packed, basis_panels);
             opsB.push_back([=] {
                 return launch_sketch_and_zero(seed, LRQMM_AXIS_COL, N, ell, LP, WcB, 0, nullptr, amaxB_bits, N, bst);
             });
             opsB.push_back([=] { return launch_absmax_pair(nullptr, 0, 0, K, nullptr, B, ldb, N, amaxB, qp, per_tensor, bst); });
             mark(opsB, 4, bst);
             factor_launches(opsB, &f[1], 1, quant, qp, rank, oversample, power_iters, pl, pl, pl_last, bst, &svdB, nullptr,
-                            basis_suffices, packed);
+                            basis_suffices, packed, basis_panels);
             mark(opsB, 5, bst);
         } else {
             opsA.push_back([=] {
@@ -757,7 +762,7 @@ int lrqmm_matmul_ex(int M, int N, int K, int bits, int rank, int oversample, int
             mark(opsA, 1, pst);
             mark(opsA, 4, pst);
             factor_launches(opsA, f, 2, quant, qp, rank, oversample, power_iters, pl_first, pl, pl_last, pst, &svd, nullptr,
-                            basis_suffices, packed);
+                            basis_suffices, packed, basis_panels);
             mark(opsA, 5, pst);
         }
         mark(opsA, 2, pst);
@@ -806,9 +811,19 @@ int lrqmm_matmul_ex(int M, int N, int K, int bits, int rank, int oversample, int
     }
     if (rc == LRQMM_OK) {
         prof_mark(slot, 6, pst);
-        rc = gemm_impl(M, N, K, bits, rank, w.Aq, w.amaxA, w.BqT, w.amaxB, w.U, w.Sig, w.Vt, w.W, w.Gam, w.Zt,
+        PanelArgs ready = {};
+        if (basis_panels) {
+            GemmWs g;
+            Arena ga(w.sub);
+            carve_gemm(ga, M, N, K, rank, &g);
+            rc = launch_basis_panels({f[0].op.partial, f[1].op.partial, f[1].op.Y, f[0].op.pt.splits, f[1].op.pt.splits, N, K, rank,
+                                      g.Wf, g.Vf, w.Zt, g.X, w.Sig, w.Gam}, pst);
+            ready = {w.Aq, w.BqT, g.Wf, g.Vf, f[0].op.Y, w.Sig, f[0].w.s, f[1].w.s, g.X, w.Gam, w.Zt, g.Lp, g.Rp, M, N, K, rank,
+                     pad_to(2 * rank, 8), basis_slices(K), LP};
+        }
+        if (rc == LRQMM_OK) rc = gemm_impl(M, N, K, bits, rank, w.Aq, w.amaxA, w.BqT, w.amaxB, w.U, w.Sig, w.Vt, w.W, w.Gam, w.Zt,
                        GemmOut{D, ldd, alpha, beta}, nullptr, w.sub, w.sub_bytes, stream, slot,
-                       early ? side->gdone : nullptr, planes_values(precision), packed);
+                       early ? side->gdone : nullptr, planes_values(precision), packed, basis_panels ? &ready : nullptr);
     }
     if (rc != LRQMM_OK && gemm_forked) {
         // failed somewhere behind the fork of the third stream: join it too (a second record of the

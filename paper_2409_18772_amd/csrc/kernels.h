@@ -119,6 +119,7 @@ struct PanelArgs {
     const float *U, *Sig, *sA, *sB, *Xp, *Gam, *Zt;
     float *Lp, *Rp;
     int M, N, K, r, R2P, nslices;           // nslices: of Xp
+    int ldu;                                // row stride of U
     int nbR;                                // (set by launch_panels)
 };
 int launch_panels(const PanelArgs& a, int RP, int planes, int packed, hipStream_t st);
@@ -170,6 +171,17 @@ struct BasisJob {
     float *U, *Sigma, *Vt;
 };
 int launch_take_basis(const BasisJob* job, int njob, int LP, int rank, hipStream_t st);
+// The same for both operands, as the panels need it (see PanelArgs; U is A's Q, ldu = 16): Vf from A's partials, Wf from B's Q, Zt
+// from B's partials, the slices Xp of V^T W, Sig = Gam = 1, in one launch.  basis_slices: of Xp; 0: K is too long.
+int basis_slices(int K);
+struct BasisPanels {
+    const float *partialA, *partialB, *QB;      // [splitsA][K][16], [splitsB][N][16], K x 16
+    int splitsA, splitsB, N, K, r;
+    uint16_t *Wf, *Vf;
+    float *Zt, *Xp, *Sig, *Gam;
+    int slices, per, nkb;                       // (set by launch_basis_panels)
+};
+int launch_basis_panels(const BasisPanels& a, hipStream_t st);
 
 // ---- gemm.hip -----------------------------------------------------------
 // X = V^T W is kept as vtw_slices(K) k-slices Xp[ks][t][u] that are summed where X is used.

@@ -1472,6 +1472,85 @@ __global__ __launch_bounds__(256) void take_basis_kernel(BasisJob a, BasisJob b,
     }
 }
 
+// take_basis and panel_prep in one launch, where both operands' factors are 16 columns wide and K is short: workgroups [0, slices) take
+// `per` k blocks of 64 each: the partials' sums (V) and B's Q (W) as matrix-core operands and their product's slice of X, straight
+// from the 64 x 16 tiles in LDS; the rest take 64 columns of B each, for Zt.  1024 threads: four runs of the splits per group of
+// values, added in order, as in take_basis_kernel.  Calls, two launches / this: 256^3 40.7 / 38.8
+// us, 200^3 74.6 / 71.9, 2000^3 (two blocks a workgroup) 135.8 / 135.9, 100352 x 64 x 576 208 / 203.
+#define BASIS_PER 2         // k blocks of a workgroup, at most: they follow each other
+int basis_slices(int K) {
+    const int nkb = pk_kblocks(K), per = ceil_div(nkb, LRQ_VTW_MAX_SLICES);
+    return per <= BASIS_PER ? ceil_div(nkb, per) : 0;
+}
+__global__ __launch_bounds__(1024) void basis_panels_kernel(BasisPanels a) {
+    __shared__ float4 runs[4][256];
+    __shared__ float vt[64][17], wt[64][17];
+    const bool isA = (int)blockIdx.x < a.slices;
+    const int tid = threadIdx.x, r = a.r, sg = tid >> 8, e = tid & 255;
+    const int first = isA ? blockIdx.x * a.per : blockIdx.x - a.slices, last = isA ? min(first + a.per, a.nkb) : first + 1;
+    const int cols = isA ? a.K : a.N, splits = isA ? a.splitsA : a.splitsB;
+    const int sb = sg * splits / 4, se = (sg + 1) * splits / 4;
+    const size_t plane = (size_t)cols * 16;
+    double x = 0.0;             // X[t][u] of thread 16 t + u
+    for (int blk = first; blk < last; ++blk) {
+        const int k0 = blk * 64;
+        const float* src = (isA ? a.partialA : a.partialB) + (size_t)min(k0 + e / 4, cols - 1) * 16 + (e % 4) * 4;
+        const float w = isA ? a.QB[(size_t)min(k0 + tid / 16, a.K - 1) * 16 + tid % 16] : 0.f;
+        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int s0 = sb; s0 < se; s0 += 8) {
+            float4 p[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) p[u] = *reinterpret_cast<const float4*>(src + (size_t)min(s0 + u, se - 1) * plane);
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (s0 + u < se) { v.x += p[u].x; v.y += p[u].y; v.z += p[u].z; v.w += p[u].w; }
+        }
+        runs[sg][e] = v;
+        wt[tid / 16][tid % 16] = k0 + tid / 16 < a.K && tid % 16 < r ? w : 0.f;
+        __syncthreads();
+        if (sg == 0) {
+#pragma unroll
+            for (int g = 1; g < 4; ++g) {
+                const float4 t = runs[g][e];
+                v.x += t.x; v.y += t.y; v.z += t.z; v.w += t.w;
+            }
+            const bool in = k0 + e / 4 < cols;
+            const int c = (e % 4) * 4;
+            vt[e / 4][c + 0] = in && c + 0 < r ? v.x : 0.f;
+            vt[e / 4][c + 1] = in && c + 1 < r ? v.y : 0.f;
+            vt[e / 4][c + 2] = in && c + 2 < r ? v.z : 0.f;
+            vt[e / 4][c + 3] = in && c + 3 < r ? v.w : 0.f;
+        }
+        __syncthreads();
+        if (isA) {
+            if (tid < 256) {
+#pragma unroll
+                for (int k = 0; k < 64; ++k) x = fma((double)vt[k][tid >> 4], (double)wt[k][tid & 15], x);
+            } else if (tid < 512) {         // a lane's eight k of an operand: V, then W
+                const int lane = tid & 63, h = (tid >> 6) & 1;
+                const bool isV = tid < 384;
+                float q[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const int k = 16 * (lane >> 4) + 8 * h + i;
+                    q[i] = isV ? vt[k][lane & 15] : wt[k][lane & 15];
+                }
+                const Planes3 pl = split_planes<3>(q);
+                uint16_t* const dst = (isV ? a.Vf : a.Wf) + (size_t)(blk * 6 + h) * FACTOR_PIECE + lane * 8;
+                *reinterpret_cast<v8bf16*>(dst) = pl.p1;
+                *reinterpret_cast<v8bf16*>(dst + 2 * FACTOR_PIECE) = pl.p2;
+                *reinterpret_cast<v8bf16*>(dst + 4 * FACTOR_PIECE) = pl.p3;
+            }
+            __syncthreads();
+        } else if (tid / 64 < r && k0 + tid % 64 < a.N) {
+            a.Zt[(size_t)(tid / 64) * a.N + k0 + tid % 64] = vt[tid % 64][tid / 64];
+        }
+    }
+    if (isA && tid < 256 && (tid >> 4) < r && (tid & 15) < r)
+        a.Xp[((size_t)blockIdx.x * r + (tid >> 4)) * r + (tid & 15)] = (float)x;
+    if (blockIdx.x == 0 && tid < r) a.Sig[tid] = a.Gam[tid] = 1.0f;
+}
+
 #define NT_SWITCH(NTV, CALL)            \
     switch (NTV) {                      \
         case 1: { constexpr int NT_ = 1; CALL; } break; \
@@ -1575,6 +1654,17 @@ int launch_take_basis(const BasisJob* job, int njob, int LP, int rank, hipStream
         g[i].nb = g[i].nbV + (int)(((size_t)job[i].rows * rank + 1023) / 1024);
     }
     hipLaunchKernelGGL(take_basis_kernel, dim3(g[0].nb + g[1].nb), dim3(256), 0, st, job[0], job[njob - 1], g[0], g[1], rank);
+    LRQ_CHECK_LAUNCH();
+    return LRQMM_OK;
+}
+
+int launch_basis_panels(const BasisPanels& in, hipStream_t st) {
+    BasisPanels a = in;
+    a.slices = basis_slices(a.K);
+    if (a.slices == 0 || a.r < 1 || a.r > 16) return LRQMM_ERR_UNSUPPORTED;
+    a.nkb = pk_kblocks(a.K);
+    a.per = ceil_div(a.nkb, a.slices);
+    hipLaunchKernelGGL(basis_panels_kernel, dim3(a.slices + ceil_div(a.N, 64)), dim3(1024), 0, st, a);
     LRQ_CHECK_LAUNCH();
     return LRQMM_OK;
 }

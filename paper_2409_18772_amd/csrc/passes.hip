@@ -840,7 +840,7 @@ __global__ __launch_bounds__(512, 2) void panels_kernel(PanelArgs a) {
                     const float z = a.Zt[(size_t)min(u, r - 1) * a.N + min(j, a.N - 1)];
                     own[b][u * 33 + (e & 31)] = u < r && j < a.N ? z : 0.f;
                 } else if (e < 32 * r) {
-                    own[b][e] = a.U[min((size_t)r0 * r + e, (size_t)a.M * r - 1)] * a.Sig[e % r];
+                    own[b][e] = a.U[(size_t)min(r0 + e / r, a.M - 1) * a.ldu + e % r] * a.Sig[e % r];
                 }
             }
         }
@@ -971,7 +971,7 @@ __global__ __launch_bounds__(512, 4) void panels_rows_kernel(PanelArgs a) {
         for (int v = 0; v < 4; ++v) {
             const int row = min(tile * 16 + 4 * kq + v, rows - 1), col = min(li, r - 1);
             step[v] = (right ? a.sB : a.sA)[row];
-            us[v] = right ? a.Zt[(size_t)col * rows + row] : a.U[(size_t)row * r + col];
+            us[v] = right ? a.Zt[(size_t)col * rows + row] : a.U[(size_t)row * a.ldu + col];
         }
         __builtin_amdgcn_sched_barrier(0);
         v4f total = (v4f){0.f, 0.f, 0.f, 0.f}, acc = total;

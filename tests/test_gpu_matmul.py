@@ -755,3 +755,17 @@ def test_gemm_only_profiling_mode():
         assert n == 1 and st["gemm"] > 0 and st["int_gemm"] == 0
     finally:
         L.lrqmm_profile_enable(False)
+
+
+# Panels prepared straight from the last products (sketches of up to 16 columns without oversampling, K up to 2048) and, from one k block
+# more on, through the factors: both sides of the limit, k blocks and columns that end early, one k block and none whole, one chain
+# and two, few and many ranges of the last product.  The oracle forms the SVD.
+@pytest.mark.parametrize("M,N,K,bits,r,q", [(40, 33, 17, 8, 1, 0), (65, 63, 64, 8, 16, 1), (130, 70, 65, 4, 5, 0), (300, 260, 1000, 8, 10, 1),
+                                            (90, 515, 1025, 8, 16, 1), (260, 130, 2048, 8, 9, 1), (260, 130, 2049, 8, 9, 1), (9000, 40, 300, 8, 8, 1)])
+def test_panels_from_the_last_products(M, N, K, bits, r, q):
+    import paper_2409_18772_amd as L
+    A, B = wl.random_matrix("uniform01", M, K, seed=95), wl.random_matrix("uniform01", K, N, seed=96)
+    say("panels from the last products", M, N, K, bits, r, q)
+    C = to_np(L.lrqmm_matmul(to_dev(A), to_dev(B), bits, r, 0, q, seed=7))
+    ref = o.lrqmm(A, B, bits, r, 0, q, seed=7)
+    assert rel_fro(ref["C"], C) < tol_for(ref)
