@@ -53,6 +53,7 @@ int launch_pad_copy(const float* src, int rows, int cols, int ld, float* dst, hi
 
 // ---- passes.hip ---------------------------------------------------------
 #define MAX_SPLITS 8      // upper bound on the splits of plan_pass_n (its partials are summed in one batch)
+#define MAX_SPLITS_FEW 32 // ... up to 1024 rows
 #define MAX_SPLITS_T 64   // upper bound for plan_pass_t (only launch_reduce_gram sums those, in batches)
 struct PassPlan {
     int splits;   // number of partial results

@@ -1329,11 +1329,13 @@ static bool pass_n_wide(int rows, int cols, int LP) {
 // (an empty reduction has no ranges: splits = 0)
 // Up to 1024 rows ranges of one chunk, down to 64 elements: such a pass is the load latency of its chunks, one after the
 // other.  Two chunks and more / this, us per call: 200^3 l = 10 87.7 / 83.5, 256^3 l = 8 50.8 / 48.2, 512^3 l = 24 130.4 /
-// 127.9, 1000^3 l = 10 113.1 / 108.2; beyond 2000^3 l = 10 157.0 / 163.4.
+// 127.9, 1000^3 l = 10 113.1 / 108.2; beyond 2000^3 l = 10 157.0 / 163.4.  Up to MAX_SPLITS_FEW ranges there: with eight a 512 x 4096
+// operand was 64 workgroups of eight chunks each (12.2 us a pass, 24 columns); layer call of 512 x 4096 x 4096, 8 / 32 ranges, 163.4 /
+// 153.3 us.
 PassPlan plan_pass_n(int rows, int cols, int LP) {
     const int unit = LP == 16 ? KCHUNK : 64;        // chunk depth of the kernel
     PassPlan p;
-    int s = pick_splits(ceil_div(rows, pass_n_wide(rows, cols, LP) ? 128 : 64), cols, rows <= 1024 ? 64 : 2 * unit, 512, MAX_SPLITS);
+    int s = pick_splits(ceil_div(rows, pass_n_wide(rows, cols, LP) ? 128 : 64), cols, rows <= 1024 ? 64 : 2 * unit, 512, rows <= 1024 ? MAX_SPLITS_FEW : MAX_SPLITS);
     p.chunk = max(1, ceil_div(ceil_div(cols, s), unit)) * unit;
     p.splits = ceil_div(cols, p.chunk);
     return p;
@@ -1368,7 +1370,7 @@ size_t pass_partial_floats(int rows, int cols, int LP) {
     const PassPlan pn = plan_pass_n(rows, cols, LP), pt = plan_pass_t(rows, cols, LP);
     const int unit = LP == 16 ? KCHUNK : 64, block = LP >= 64 ? 128 : 64;
     size_t part = LP * max(most_partial_rows(rows, block, cols, 2 * unit, 512, MAX_SPLITS),
-                           most_partial_rows(min(rows, 1024), block, cols, 64, 512, MAX_SPLITS));
+                           most_partial_rows(min(rows, 1024), block, cols, 64, 512, MAX_SPLITS_FEW));
     part = max(part, LP * most_partial_rows(cols, 64, rows, 128, 512, MAX_SPLITS_T));
     part = max(part, 16 * most_partial_rows(cols, 64, rows, 32, 512, MAX_SPLITS_T));
     return max(part, LP * max((size_t)pn.splits * rows, (size_t)pt.splits * cols));
