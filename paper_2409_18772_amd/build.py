@@ -16,7 +16,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "liblrqmm.so")
 SOURCES = ["api.hip", "quantize.hip", "sketch.hip", "passes.hip", "orth.hip", "gemm.hip"]
-HEADERS = [os.path.join(CSRC, "common.h"), os.path.join(CSRC, "kernels.h"),
+HEADERS = [os.path.join(CSRC, "common.h"), os.path.join(CSRC, "kernels.h"), os.path.join(CSRC, "sketch.h"),
            os.path.join(HERE, "..", "include", "lrqmm.h")]
 
 FLAGS = [

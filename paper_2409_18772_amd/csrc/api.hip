@@ -729,36 +729,39 @@ int lrqmm_matmul_ex(int M, int N, int K, int bits, int rank, int oversample, int
         for (int e : {1, 4, 2, 5}) mark(opsA, e, pst);
     } else {
         // The group maxima come first (one read of the operands); the operand's second read yields codes, step vectors and
-        // the sketch product Y = R.Omega in one launch.  The sketches are filled by the chain's first launch, which also
-        // clears the column maxima (they are formed with atomic maxima).
+        // the sketch product Y = R.Omega in one launch.  The sketches are filled beside the maxima.
         LRQ_TRY(make_factor(&f[0], A, lda, M, K, LRQMM_AXIS_ROW, LP, rank, w.amaxA, w.Aq, w.U, w.Sig, w.Vt, w.subA,
                             w.subA_bytes));
         LRQ_TRY(make_factor(&f[1], B, ldb, K, N, LRQMM_AXIS_COL, LP, rank, w.amaxB, w.BqT, w.W, w.Gam, w.Zt, w.subB,
                             w.subB_bytes));
         float *const WcA = f[0].w.Wc, *const WcB = f[1].w.Wc;
-        uint32_t* const amaxB_bits = reinterpret_cast<uint32_t*>(w.amaxB);
         float *const amaxA = w.amaxA, *const amaxB = w.amaxB;
         const FirstPass quant = FirstPass::quantize;
         if (overlap) {
-            opsA.push_back([=] { return launch_fill_sketch(seed, LRQMM_AXIS_ROW, K, ell, LP, WcA, pst); });
-            if (!one_read)
-                opsA.push_back([=] { return launch_absmax_pair(A, lda, M, K, amaxA, nullptr, 0, 0, nullptr, qp, per_tensor, pst); });
+            if (one_read) {
+                opsA.push_back([=] { return launch_fill_sketch(seed, LRQMM_AXIS_ROW, K, ell, LP, WcA, pst); });
+            } else {
+                opsA.push_back([=] {
+                    const SketchJob sk = {seed, LRQMM_AXIS_ROW, K, ell, LP, WcA};
+                    return launch_absmax_pair(A, lda, M, K, amaxA, nullptr, 0, 0, nullptr, qp, per_tensor, &sk, 1, pst);
+                });
+            }
             mark(opsA, 1, pst);
             factor_launches(opsA, &f[0], 1, one_read ? FirstPass::one_read : quant, qp, rank, oversample, power_iters, pl_first,
                             pl, pl_last, pst, &svd, amaxA, basis_suffices, packed, basis_panels);
             opsB.push_back([=] {
-                return launch_sketch_and_zero(seed, LRQMM_AXIS_COL, N, ell, LP, WcB, 0, nullptr, amaxB_bits, N, bst);
+                const SketchJob sk = {seed, LRQMM_AXIS_COL, N, ell, LP, WcB};
+                return launch_absmax_pair(nullptr, 0, 0, K, nullptr, B, ldb, N, amaxB, qp, per_tensor, &sk, 1, bst);
             });
-            opsB.push_back([=] { return launch_absmax_pair(nullptr, 0, 0, K, nullptr, B, ldb, N, amaxB, qp, per_tensor, bst); });
             mark(opsB, 4, bst);
             factor_launches(opsB, &f[1], 1, quant, qp, rank, oversample, power_iters, pl, pl, pl_last, bst, &svdB, nullptr,
                             basis_suffices, packed, basis_panels);
             mark(opsB, 5, bst);
         } else {
             opsA.push_back([=] {
-                return launch_sketch_and_zero(seed, LRQMM_AXIS_ROW, K, ell, LP, WcA, N, WcB, amaxB_bits, N, pst);
+                const SketchJob sk[2] = {{seed, LRQMM_AXIS_ROW, K, ell, LP, WcA}, {seed, LRQMM_AXIS_COL, N, ell, LP, WcB}};
+                return launch_absmax_pair(A, lda, M, K, amaxA, B, ldb, N, amaxB, qp, per_tensor, sk, 2, pst);
             });
-            opsA.push_back([=] { return launch_absmax_pair(A, lda, M, K, amaxA, B, ldb, N, amaxB, qp, per_tensor, pst); });
             mark(opsA, 1, pst);
             mark(opsA, 4, pst);
             factor_launches(opsA, f, 2, quant, qp, rank, oversample, power_iters, pl_first, pl, pl_last, pst, &svd, nullptr,

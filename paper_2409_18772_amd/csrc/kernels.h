@@ -25,10 +25,16 @@ struct QuantPair {
 // packed: the format of packed codes (see PK8, PK6), or PK_NONE for rows of bytes.
 int launch_quantize_pair(const float* A, int lda, const float* B, int ldb, int M, int N, int K, QuantParams q, QuantPair o,
                          hipStream_t st, int packed = PK_NONE);
-// The group maxima alone: row maxima of A (M x K) and column maxima of B (K x N; amaxB cleared by the caller on this
-// stream) in one launch, and with per_tensor their maxima in a second.  M or N may be 0: the other operand alone.
+// The group maxima alone, and sketches beside them (what a quantization followed by a factorization starts from): row maxima of A
+// (M x K), column maxima of B (K x N), up to two sketches in one launch (long columns are cleared in one before it), and with
+// per_tensor the matrices' maxima in another.  M or N may be 0: the other operand alone.
+struct SketchJob {
+    uint64_t seed;
+    int stream_id, rows, cols, ld;          // (as for launch_fill_sketch)
+    float* omega;
+};
 int launch_absmax_pair(const float* A, int lda, int M, int K, float* amaxA, const float* B, int ldb, int N,
-                       float* amaxB, QuantParams q, bool per_tensor, hipStream_t st);
+                       float* amaxB, QuantParams q, bool per_tensor, const SketchJob* fill, int nfill, hipStream_t st);
 // lam[n], s[n] from amax[n]; entries n..npad-1 are zero-filled.
 // A minimal kernel (writes one zero word): used as a few microseconds of delay on a stream.
 int launch_tick(uint32_t* word, hipStream_t st);
@@ -44,10 +50,6 @@ int launch_fill_sketch(uint64_t seed, int stream_id, int rows, int cols, int ld,
 int launch_sketch_and_scales(uint64_t seed, int stream_id, int rows, int cols, int ld, float* omega,
                              const float* amax, int n, int npad, float qmaxf, float* lam, float* s,
                              hipStream_t st);
-// The sketch (stream_id 0 or 1), the other stream's sketch for the other operand (omega2, or null), and zero_n words
-// cleared at zero_words, in one launch: the first kernel of a quantization followed by a factorization.
-int launch_sketch_and_zero(uint64_t seed, int stream_id, int rows, int cols, int ld, float* omega, int rows2,
-                           float* omega2, uint32_t* zero_words, int zero_n, hipStream_t st);
 // dst[i*ld + j] = (j < cols) ? src[i*cols + j] : 0
 int launch_pad_copy(const float* src, int rows, int cols, int ld, float* dst, hipStream_t st);
 

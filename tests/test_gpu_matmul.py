@@ -769,3 +769,15 @@ def test_panels_from_the_last_products(M, N, K, bits, r, q):
     C = to_np(L.lrqmm_matmul(to_dev(A), to_dev(B), bits, r, 0, q, seed=7))
     ref = o.lrqmm(A, B, bits, r, 0, q, seed=7)
     assert rel_fro(ref["C"], C) < tol_for(ref)
+
+
+# Column maxima by strips over all rows (up to 512) and by slabs (from 513): columns at the edges of the 64-column strips, of the
+# 256-column slabs and below one load; the separate calls' quantizer has kernels of its own.
+@pytest.mark.parametrize("K", [17, 127, 129, 512, 513])
+@pytest.mark.parametrize("N", [17, 63, 64, 66, 257])
+def test_column_maxima_in_strips_and_slabs(N, K):
+    import paper_2409_18772_amd as L
+    dA, dB = to_dev(wl.random_matrix("normal", 90, K, seed=97)), to_dev(wl.random_matrix("normal", K, N, seed=98))
+    say("column maxima", N, K)
+    C = to_np(L.lrqmm_matmul(dA, dB, 8, 17, 0, 1, seed=9))
+    assert np.array_equal(to_np(_separate_calls(L, dA, dB, 8, 17, 0, 1, 9)), C)
