@@ -21,6 +21,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 PEAK_INT8_TOPS = 5000.0     # MI355X dense int8 MFMA, TOP/s
+PEAK_FP6_TOPS = 10000.0     # MI355X dense fp6 MFMA, TOP/s (codes of up to five bits)
 PEAK_HBM_GBS = 8000.0       # MI355X HBM3E, GB/s
 
 
@@ -228,13 +229,18 @@ def main():
     gemm_bytes = float(w.M * w.K + w.K * w.N + 4 * w.M * w.N + (0 if early else 8 * w.rank * (w.M + w.N)))
     large_tiles = w.M >= 256 and w.N >= 256 and -(-w.M // 256) * -(-w.N // 256) >= 128
     large_tiles = large_tiles and (early or -(-w.M // 128) * -(-w.N // 128) > 512)
-    if ops / gemm_bytes >= PEAK_INT8_TOPS * 1e12 / (PEAK_HBM_GBS * 1e9):
-        roof = {"bound": "mfma", "achieved": round(achieved, 2), "peak": PEAK_INT8_TOPS, "unit": "TOP/s",
-                "frac": round(achieved / PEAK_INT8_TOPS, 4)}
+    # inside lrqmm_matmul codes travel as matrix-core operands, up to five bits (with sums below 2^24) for the fp6 cores
+    packed = w.rank == 0 or not one_read_a
+    six = packed and w.bits <= 5 and w.K << (2 * (w.bits - 1)) <= 1 << 24
+    peak_mfma, cores = (PEAK_FP6_TOPS, "fp6") if six else (PEAK_INT8_TOPS, "int8")
+    if ops / gemm_bytes >= peak_mfma * 1e12 / (PEAK_HBM_GBS * 1e9):
+        roof = {"bound": "mfma", "achieved": round(achieved, 2), "peak": peak_mfma, "unit": "TOP/s",
+                "frac": round(achieved / peak_mfma, 4)}
     else:
         gbs_gemm = gemm_bytes / gemm_s / 1e9 if gemm_s > 0 else 0.0
         roof = {"bound": "hbm", "achieved": round(gbs_gemm, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
                 "frac": round(gbs_gemm / PEAK_HBM_GBS, 4), "algorithmic_bytes_per_launch": gemm_bytes}
+    large_kernel = "packed_gemm256_kernel" if packed else "int8_gemm256_kernel"
     if early:   # the dequantizing rank-2r update alone: reads and rewrites C
         gbs = 8.0 * w.M * w.N / (stages["gemm"] * 1e-3) / 1e9
         stage_info["gemm"].update(kernel="rank_update_kernel", algorithmic_GBs=round(gbs, 1),
@@ -284,13 +290,13 @@ def main():
         "config": {"workload": w.name, "M": w.M, "N": w.N, "K": w.K, "bits": w.bits, "rank": w.rank,
                    "oversample": w.oversample, "power_iters": w.power_iters, "sketch_seed": w.sketch_seed,
                    "inputs": f"{INPUT_TEXT.get(w.kind, w.kind)}, seeds {w.seed_a}/{w.seed_b}"},
-        "roofline": {"kernel": ("int8_gemm256_kernel (int8 MFMA GEMM, raw int32 sums; on the library's third "
-                                "stream beside the single-workgroup SVD kernels)") if early else
-                               (("int8_gemm256_kernel" if large_tiles else "int8_gemm_kernel (%d x %d tiles)" % small_tile(w.M, w.N))
-                                + " (int8 MFMA GEMM + fused dequant and rank-2r epilogue)"),
+        "roofline": {"kernel": ("%s (%s MFMA GEMM, raw int32 sums; on the library's third stream beside the "
+                                "single-workgroup SVD kernels)" % (large_kernel, cores)) if early else
+                               ((large_kernel if large_tiles else "int8_gemm_kernel (%d x %d tiles)" % small_tile(w.M, w.N))
+                                + " (%s MFMA GEMM + fused dequant and rank-2r epilogue)" % cores),
                      **roof,
                      # counter bytes of this kernel on this workload, or null when no summary is tracked for it
-                     "traffic": read_traffic(f"int8_gemm_{SHORT.get(w.name, w.name)}_pmc.txt"),
+                     "traffic": None if packed else read_traffic(f"int8_gemm_{SHORT.get(w.name, w.name)}_pmc.txt"),
                      "launch_ms": round(stages[gemm_key], 4), "ops_per_launch": ops,
                      "alone": {"ms": round(t_gemm_alone * 1e3, 4), "achieved": round(ops / t_gemm_alone / 1e12, 2),
                                "frac": round(ops / t_gemm_alone / 1e12 / PEAK_INT8_TOPS, 4),
