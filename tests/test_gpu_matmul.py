@@ -252,7 +252,7 @@ def test_guard_free_pass_kernels_equal_the_guarded_ones_bitwise(M, N, K, r, p):
 
 # Codes travel packed inside the call, up to five bits in six.  Edges of the 32-row and 64-code blocks (one short, whole, one over), odd
 # numbers of k blocks and fewer than the stages of the product, 128 x 128 / 64 x 128 / 64 x 64 / 256 x 256 tiles, tiles cut along K
-# beside the SVDs, and the longest reduction that 5-bit sums leave exact (the next one takes bytes).
+# beside the SVDs, and both sides of the longest reduction of 5-bit codes in six bits (sums next to the limit: below).
 PACKED = [(128, 96, 128, 4, 24, 8), (127, 97, 191, 4, 20, 8), (129, 160, 193, 2, 17, 0), (320, 321, 385, 5, 24, 8),
           (1025, 1000, 449, 3, 40, 8), (2080, 2049, 320, 4, 17, 0), (3100, 2900, 200, 4, 36, 0), (4096, 4096, 1024, 4, 32, 8),
           (64, 96, 65536, 5, 17, 0), (96, 64, 65540, 5, 17, 0)]
@@ -273,11 +273,56 @@ def test_packed_codes_give_the_bits_of_the_separate_calls(M, N, K, bits, r, p):
     assert np.array_equal(to_np(_separate_calls(L, dA, dB, bits, r, p, 1, 9)), C)
 
 
+def _amax_that_rounds_up(qmax):
+    """A float32 maximum a with fl(a * fl(qmax / a)) > qmax: -a then has the code -(qmax + 1)."""
+    a = np.linspace(1.0, 2.0, 4096, dtype=np.float32)
+    return a[a * (np.float32(qmax) / a) > np.float32(qmax)][0]
+
+
+# bits and the longest reduction that travels in six bits, K 4^(bits - 1) = 2^24.
+@pytest.mark.parametrize("M,N,bits,K", [(64, 96, 5, 65536), (70, 33, 4, 262144), (33, 40, 3, 1048576), (256, 300, 5, 65536)])
+@pytest.mark.parametrize("turn", [False, True])
+def test_six_bit_sums_next_to_their_limit(M, N, bits, K, turn):
+    """Codes -(qmax + 1), one in sixteen a smaller one at irregular places: sums up to 2^24 in units of one product, odd ones among
+    them, where float32 ends to hold every integer.  turn: the second half of the reduction has the other sign, so that the
+    partial sums pass half of it.  Against the int8 product of the separate calls, bit for bit, and its sums against int64 on the
+    CPU in one row."""
+    import torch
+    import paper_2409_18772_amd as L
+    qmax = 2 ** (bits - 1) - 1
+    a = float(_amax_that_rounds_up(qmax))
+
+    def operand(rows, cols, seed, kdim):
+        gen = torch.Generator(device="cuda").manual_seed(seed)
+        u = torch.rand((rows, cols), generator=gen, device="cuda")
+        x = torch.where(u < 1 / 16, torch.full_like(u, -0.97 * a), torch.full_like(u, -a))
+        if turn and kdim is not None:
+            x.narrow(kdim, K // 2, K - K // 2).neg_()
+        return x
+    dA, dB = operand(M, K, 1, 1), operand(K, N, 2, None)
+    say("six-bit sums", M, N, K, bits, "turn", turn)
+    Aq, amA = L.lrqmm_quantize(dA, L.AXIS_ROW, bits)
+    BqT, amB = L.lrqmm_quantize(dB, L.AXIS_COL, bits)
+    ws = L.Workspace.for_problem(M, N, K, 17, 0)
+    fa = L.lrqmm_rsvd(dA, amA, L.AXIS_ROW, bits, 17, 0, 0, seed=9, workspace=ws)
+    fb = L.lrqmm_rsvd(dB, amB, L.AXIS_COL, bits, 17, 0, 0, seed=9, workspace=ws)
+    want, Cint = L.lrqmm_gemm(Aq, amA, BqT, amB, bits, fa, fb, want_cint=True, workspace=ws)
+    assert int(Aq.min()) == -qmax - 1 and int(BqT.min()) == -qmax - 1
+    half = K // 2 if turn else K
+    largest = (Aq[:, :half].float() @ BqT[:, :half].float().T).abs().max()
+    assert float(largest) > (2 ** 22 if turn else 2 ** 23) and bool((Cint % 2 != 0).any())
+    row = np.asarray(to_np(Aq)[0], np.int64) @ np.asarray(to_np(BqT), np.int64).T
+    assert np.array_equal(row, to_np(Cint)[0])
+    assert torch.equal(L.lrqmm_matmul(dA, dB, bits, 17, 0, 0, seed=9, workspace=ws), want)
+
+
 # The same without a factorization: rows in the registers of a wave or (beyond 4096 codes) of a workgroup, in one to four loads, rows
 # that end inside a load, 16-row groups that end early.
 @pytest.mark.parametrize("M,N,K,bits", [(256, 256, 64, 4), (131, 97, 193, 4), (65, 100, 1030, 5), (300, 130, 4096, 2), (70, 64, 4099, 4),
                                         (97, 300, 9001, 4), (2100, 2300, 700, 4), (256, 256, 64, 8), (131, 97, 193, 8),
-                                        (5, 4, 4, 8), (65, 100, 1030, 6), (70, 64, 4099, 8), (97, 300, 9001, 8), (2100, 2300, 700, 8)])
+                                        (5, 4, 4, 8), (65, 100, 1030, 6), (70, 64, 4099, 8), (97, 300, 9001, 8), (2100, 2300, 700, 8)] +
+                         # more than 512 tiles of 128 x 128: the 256 x 256 tiles that store the product themselves, ragged and whole
+                         [(3100, 2901, 200, 4), (4096, 4096, 320, 4), (3100, 2901, 200, 8), (4096, 4096, 320, 8)])
 def test_packed_codes_without_a_factorization(M, N, K, bits):
     import paper_2409_18772_amd as L
     dA, dB = to_dev(wl.random_matrix("normal", M, K, seed=93)), to_dev(wl.random_matrix("uniform_pm1", K, N, seed=94))
@@ -759,9 +804,10 @@ def test_gemm_only_profiling_mode():
 
 # Panels prepared straight from the last products (sketches of up to 16 columns without oversampling, K up to 2048) and, from one k block
 # more on, through the factors: both sides of the limit, k blocks and columns that end early, one k block and none whole, one chain
-# and two, few and many ranges of the last product.  The oracle forms the SVD.
+# and two (the last shape), few and many ranges of the last product.  The oracle forms the SVD.
 @pytest.mark.parametrize("M,N,K,bits,r,q", [(40, 33, 17, 8, 1, 0), (65, 63, 64, 8, 16, 1), (130, 70, 65, 4, 5, 0), (300, 260, 1000, 8, 10, 1),
-                                            (90, 515, 1025, 8, 16, 1), (260, 130, 2048, 8, 9, 1), (260, 130, 2049, 8, 9, 1), (9000, 40, 300, 8, 8, 1)])
+                                            (90, 515, 1025, 8, 16, 1), (260, 130, 2048, 8, 9, 1), (260, 130, 2049, 8, 9, 1), (9000, 40, 300, 8, 8, 1),
+                                            (4000, 2700, 2000, 8, 10, 1)])
 def test_panels_from_the_last_products(M, N, K, bits, r, q):
     import paper_2409_18772_amd as L
     A, B = wl.random_matrix("uniform01", M, K, seed=95), wl.random_matrix("uniform01", K, N, seed=96)

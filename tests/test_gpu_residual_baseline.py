@@ -193,10 +193,12 @@ def test_joint_quantization_equals_the_separate_calls(M, N, K, pad, terms):
 
 
 # Four products of packed codes as the quadrants of one tile: edges of the 128 x 128 tiles and of the 32-row and 64-code blocks, rows of
-# A in the registers of a wave or of a workgroup, both formats and the first reduction too long for six bits, an update of a window.
+# A in the registers of a wave or of a workgroup (up to the longest of the joint quantization), both formats, an update of a window.
 @pytest.mark.parametrize("M,N,K,bits,alpha,beta,pad", [(128, 128, 64, 8, 1.0, 0.0, 0), (127, 129, 63, 8, 0.75, 0.5, 3), (130, 5, 65, 6, 1.0, 0.5, 0),
                                                        (300, 260, 1030, 8, 1.0, 0.0, 8), (1000, 700, 4099, 8, -0.5, 1.0, 1), (129, 127, 200, 4, 1.0, 0.0, 0),
-                                                       (1, 300, 333, 4, 1.0, 0.25, 5), (1100, 600, 5000, 5, 1.0, 0.0, 0), (2100, 1900, 320, 2, 1.0, 0.0, 0)])
+                                                       (1, 300, 333, 4, 1.0, 0.25, 5), (1100, 600, 5000, 5, 1.0, 0.0, 0), (2100, 1900, 320, 2, 1.0, 0.0, 0),
+                                                       (700, 800, 8195, 8, 0.75, 0.5, 1), (800, 700, 16384, 8, 1.0, 0.0, 0),
+                                                       (700, 800, 8195, 4, 0.75, 0.5, 1), (800, 700, 16384, 4, 1.0, 0.0, 0)])
 def test_four_products_in_one_tile_give_the_bits_of_one_launch_each(M, N, K, bits, alpha, beta, pad):
     """Each product's sums are exact integers, and the steps, alpha and the running total round in the same places."""
     import torch
