@@ -889,7 +889,7 @@ int lrqmm_residual_matmul(int M, int N, int K, int bits, int terms, int round_mo
     if (K == 0) terms = 1;
     int rc, packed = PK_NONE;
     if (scale_mode == LRQMM_SCALE_VECTOR && quantize_pair_usable(M, N, K)) {
-        if (terms == 4 && int8_terms_usable(M, N, K)) packed = packed_format(bits, K);
+        if (terms == 4 && int8_terms_usable(M, N, K)) packed = terms_format(M, N, K, bits);
         QuantPair o = {w.Aq, w.BqT, w.amaxA, w.amaxB};
         if (terms >= 3) { o.codesRA = w.RAq; o.codesRB = w.RBqT; o.amaxRA = w.amaxRA; o.amaxRB = w.amaxRB; }
         LRQ_TRY(launch_quantize_pair(A, lda, B, ldb, M, N, K, make_quant_params(bits, round_mode), o,

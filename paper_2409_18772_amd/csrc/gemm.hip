@@ -1618,6 +1618,38 @@ bool int8_terms_usable(int M, int N, int K) {
     return K >= 16 && (K <= 2048 || (long long)ceil_div(M, 128) * ceil_div(N, TTN) >= 32);
 }
 
+// int8_terms_kernel: 256-row tiles, one per CU, where they fill their last round to 3/4, 256 / 128 rows, us: 2000^3 (0.50) 113 / 99, 2560^3
+// (0.78) 132 / 142, 3072^3 (0.56) 256 / 234, 3500^3 (0.77) 349 / 381, 4096^3 (1) 377 / 401, 5000^3 (0.78) 895 / 903
+static bool tall_terms(int M, int N) {
+    const long long tiles = (long long)ceil_div(M, 256) * ceil_div(N, TTN);
+    return 4 * tiles >= 3 * GEMM_CUS * ((tiles + GEMM_CUS - 1) / GEMM_CUS);
+}
+
+// The format of the codes of four products: packed_terms_kernel reads less and multiplies faster, but nothing covers the end of its
+// tiles (one workgroup per CU, the quadrants through LDS), so rows of bytes stay the better form of short reductions.  How short depends
+// on the rounds of 128 x 128 tiles that each of the kernels makes of D (of int8_terms_kernel's a 256-row tile counts for two, and
+// so do two tiles that share a CU).  Whole calls, rows of bytes / packed, us:
+//   one round, up to 256 tiles: 2000^2 8 bits K = 256 31.6 / 34.8, 384 36.4 / 38.6, 512 41.5 / 41.9, 768 51.7 / 49.1; 4 bits 256 31.9 / 33.8, 384
+//     36.2 / 36.5, 512 41.2 / 39.2; 1024^2 the same limits
+//   as many rounds: 4096^2 (4 and 4) 8 bits K = 128 46.0 / 71.7, 512 75.5 / 100, 1024 114.5 / 134, 2048 196 / 200, 3072 278 / 275; 4 bits 512
+//     71.0 / 87.3, 1024 109 / 110, 1536 148 / 133; 2560^2, 4000^2, 8192^2 and 100352 x 64 about the same limits
+//   fewer: 3000^2 (3 and 4) 8 bits K = 512 65.2 / 75.6, 1024 95.8 / 97.7, 1536 132 / 124; 4 bits 512 62.2 / 66.6, 768 77.0 / 74.7; 3072^2,
+//     5000^2 and 6144^2 within 200 of K
+//   half as many (outputs of up to 128 rows, where 256-row tiles are half empty): 64 x 50000 8 bits K = 64 45.7 / 43.0, 512 129 / 114
+int terms_format(int M, int N, int K, int bits) {
+    const int format = packed_format(bits, K);
+    const long long tiles = (long long)ceil_div(M, 128) * ceil_div(N, 128), tall = (long long)ceil_div(M, 256) * ceil_div(N, 128);
+    const long long rounds = (tiles + GEMM_CUS - 1) / GEMM_CUS;
+    const long long byte_rounds = tall_terms(M, N) ? 2 * ((tall + GEMM_CUS - 1) / GEMM_CUS)
+                                                   : tiles <= GEMM_CUS ? 1 : 2 * ((tiles + 2 * GEMM_CUS - 1) / (2 * GEMM_CUS));
+    const bool six = format == PK6;
+    int shortest = six ? 1024 : 2560;
+    if (rounds == 1) shortest = six ? 384 : 512;
+    else if (2 * rounds <= byte_rounds) shortest = 0;
+    else if (rounds < byte_rounds) shortest = six ? 896 : 1408;
+    return K >= shortest ? format : PK_NONE;
+}
+
 int launch_int8_terms(int M, int N, int K, const int8_t* const A[2], const float* const amaxA[2], const int8_t* const B[2],
                       const float* const amaxB[2], int terms, float qmaxf, GemmOut out, hipStream_t st, int packed) {
     if (!int8_terms_usable(M, N, K) || (packed && terms != 4)) return LRQMM_ERR_UNSUPPORTED;
@@ -1630,10 +1662,7 @@ int launch_int8_terms(int M, int N, int K, const int8_t* const A[2], const float
         return LRQMM_OK;
     }
     const int tiles_n = ceil_div(N, TTN);
-    // 256-row tiles, one per CU, where they fill their last round to 3/4, 256 / 128 rows, us: 2000^3 (0.50) 113 / 99, 2560^3 (0.78) 132 / 142,
-    // 3072^3 (0.56) 256 / 234, 3500^3 (0.77) 349 / 381, 4096^3 (1) 377 / 401, 5000^3 (0.78) 895 / 903
-    const long long tall_tiles = (long long)ceil_div(M, 256) * tiles_n;
-    const bool tall = 4 * tall_tiles >= 3 * GEMM_CUS * ((tall_tiles + GEMM_CUS - 1) / GEMM_CUS);
+    const bool tall = tall_terms(M, N);
     const int ttm = tall ? 256 : 128, ntiles = ceil_div(M, ttm) * tiles_n;
     const bool full = aligned16(A[0]) && aligned16(A[1]) && aligned16(B[0]) && aligned16(B[1]) && M % ttm == 0 && N % TTN == 0 && K % BBK == 0;
 #define LRQ_TERMS(WM, FULL)                                                                                                  \

@@ -212,6 +212,7 @@ int packed_format(int bits, int K);
 // D <- alpha (A0 B0 + A0 B1 + A1 B0 [+ A1 B1]) + beta D, the products of the operands' codes (0) and of their residuals' (1),
 // each dequantized by the steps of its group maxima: terms = 3 or 4 products in one launch, where int8_terms_usable.
 bool int8_terms_usable(int M, int N, int K);
+int terms_format(int M, int N, int K, int bits);        // of the codes of four products in one launch
 int launch_int8_terms(int M, int N, int K, const int8_t* const A[2], const float* const amaxA[2], const int8_t* const B[2],
                       const float* const amaxB[2], int terms, float qmaxf, GemmOut out, hipStream_t st, int packed = PK_NONE);
 // The product with an empty reduction (K == 0): D <- alpha * 0 + beta * D (D not read when beta == 0) and,
