@@ -685,7 +685,7 @@ int lrqmm_matmul_ex(int M, int N, int K, int bits, int rank, int oversample, int
     const bool overlap = one_read || (factored && two_chains(M, N, K));
     // The one-read kernel leaves rows of bytes: its products are short and bound by the store of C.
     const bool pair = !factored && !per_tensor && quantize_pair_usable(M, N, K);
-    const int packed = pair || (factored && !one_read) ? packed_format(bits, K) : PK_NONE;
+    const int packed = pair ? direct_format(M, N, K, bits) : (factored && !one_read ? packed_format(bits, K) : PK_NONE);
     const int slot = (g_prof.on && g_prof.ncalls < kProfMaxCalls) ? g_prof.ncalls++ : -1;
     hipStream_t bst = overlap ? side->stream : pst;
     // Early integer GEMM: with both factorizations in their single-workgroup SVD the GPU is

@@ -1581,6 +1581,17 @@ int packed_format(int bits, int K) {
     return ((long long)K << (2 * (bits - 1))) <= (1ll << 24) ? PK6 : PK_NONE;
 }
 
+// Direct quantization: a workgroup of the packing kernel takes eight rows of A through LDS, which costs a tall A with short rows
+// more than a narrow product gains.  Rank 0, 8 bits, rows of bytes / packed, us: 100352 x 64 K = 64 35.7 / 41.0, 256 41.3 / 46.7, 512 61.5 /
+// 65.8, 768 95.5 / 90.7; 100352 x 512 128 81.7 / 86.6, 384 125 / 132, 512 143 / 144; 40000 x 768 384 59.7 / 63.3, 512 65.7 / 67.0; 40000 x 1024 512 84.7
+// / 88.1, 768 112 / 114; 100352 x 1024 256 155 / 156, 512 215 / 213; 100352 x 2048 64 239 / 215.  4 bits: 100352 x 64 K = 384 48.0 / 52.5, 512 60 / 59;
+// 100352 x 512 256 104 / 107, 384 125 / 125.  Up to 8192 rows either takes the same time, which is that of the launches.
+int direct_format(int M, int N, int K, int bits) {
+    const int format = packed_format(bits, K);
+    const bool narrow = format == PK6 ? N <= 512 && K <= 384 : N <= 768 && K <= 512;
+    return M >= 16384 && narrow ? PK_NONE : format;
+}
+
 long long int8_gemm_tiles(int M, int N) { return (long long)ceil_div(M, BTM) * ceil_div(N, BTN); }
 // The large-tile kernel pays from half a round of its tiles on (raw sums, where it is the only one that is asked for)
 bool int8_gemm_large_tiles(int M, int N) { return M >= BTM && N >= BTN && int8_gemm_tiles(M, N) >= GEMM_CUS / 2; }

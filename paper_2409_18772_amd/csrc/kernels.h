@@ -209,6 +209,7 @@ int launch_int8_gemm(int M, int N, int K, const int8_t* Aq, const int8_t* BqT, c
 // packed (here and below): the format of both code matrices; same results.
 // The format in which codes travel inside a call (PK_NONE: rows of bytes).
 int packed_format(int bits, int K);
+int direct_format(int M, int N, int K, int bits);       // ... of a call without a factorization
 // D <- alpha (A0 B0 + A0 B1 + A1 B0 [+ A1 B1]) + beta D, the products of the operands' codes (0) and of their residuals' (1),
 // each dequantized by the steps of its group maxima: terms = 3 or 4 products in one launch, where int8_terms_usable.
 bool int8_terms_usable(int M, int N, int K);

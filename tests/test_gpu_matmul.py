@@ -322,7 +322,10 @@ def test_six_bit_sums_next_to_their_limit(M, N, bits, K, turn):
                                         (97, 300, 9001, 4), (2100, 2300, 700, 4), (256, 256, 64, 8), (131, 97, 193, 8),
                                         (5, 4, 4, 8), (65, 100, 1030, 6), (70, 64, 4099, 8), (97, 300, 9001, 8), (2100, 2300, 700, 8)] +
                          # more than 512 tiles of 128 x 128: the 256 x 256 tiles that store the product themselves, ragged and whole
-                         [(3100, 2901, 200, 4), (4096, 4096, 320, 4), (3100, 2901, 200, 8), (4096, 4096, 320, 8)])
+                         [(3100, 2901, 200, 4), (4096, 4096, 320, 4), (3100, 2901, 200, 8), (4096, 4096, 320, 8)] +
+                         # tall operands on both sides of the limits up to which their rows stay bytes
+                         [(16383, 33, 65, 8), (16385, 33, 65, 8), (16390, 768, 40, 8), (16390, 769, 40, 8), (16391, 20, 512, 8),
+                          (16391, 20, 513, 8), (16390, 512, 40, 4), (16390, 513, 40, 4), (16391, 20, 384, 4), (16391, 20, 385, 4)])
 def test_packed_codes_without_a_factorization(M, N, K, bits):
     import paper_2409_18772_amd as L
     dA, dB = to_dev(wl.random_matrix("normal", M, K, seed=93)), to_dev(wl.random_matrix("uniform_pm1", K, N, seed=94))
