@@ -1012,6 +1012,172 @@ __global__ __launch_bounds__(512, 4) void panels_rows_kernel(PanelArgs a) {
     }
 }
 
+// The same for other tall operands: a wave takes 32 rows over the whole reduction, so its sums never leave its registers and no
+// barrier stands between its codes and its panel rows; a workgroup of eight such waves shares the planes in LDS, two workgroups a CU, all
+// k blocks at once where they fit, and otherwise tall_chunk of them at a time.  The sums of each eighth of the k blocks are added in
+// order, as in panels_kernel: the same bits.  That one holds the registers of a CU with one workgroup, whose loads, sums through
+// LDS and stores stand behind one another for every 64 rows.
+//
+// lrqmm_gemm, 8 bits, two launches as above / panels_kernel / this, us: 100352 x 64 rank 8 K = 700 58.4 / 72.5 / 52.0, 1152 72.0 / 85.2 / 63.7,
+// rank 24 K = 64 51.9 / 65.4 / 35.3, 576 79.2 / 85.9 / 56.2, 2304 177 / 170 / 126, rank 48 K = 576 115 / 114 / 85; 64 x 100352 rank 24 K = 576 122 /
+// 129 / 79, rank 48 191 / 206 / 118 (few reads of Zt per row).  Where a workgroup's 256 rows leave CUs idle, the copies of the planes into
+// LDS, which nothing covers then, make it the slower form (tall_panels): 32768 x 64 rank 8 K = 1152 38.5 / 39.0 / 37.1, rank 24
+// K = 320 34.9 / 34.4 / 31.8, 1152 52.2 / 48.8 / 51.2, rank 48 K = 576 60.2 / 52.5 / 61.3; 50000 x 64 rank 24 K = 1152 63.4 / 66.3 / 58.7, 4096 143 / 135 /
+// 142, rank 48 K = 64 47.9 / 55.2 / 44.3, 320 61.0 / 64.6 / 59.8, 576 69.2 / 70.0 / 69.4, 1152 86.8 / 87.5 / 89.9; 64 x 32768 rank 48 K = 1152 99.9 / 91.9 / 90.1, 4096 200 / 154 / 199.
+constexpr int tall_chunk(int nt, int pl) { return (nt == 3 ? 60 : 72) / (2 * nt * pl); }       // k blocks of planes in LDS
+template <int FMT, int NT, int PL>
+__global__ __launch_bounds__(512, 4) void panels_tall_kernel(PanelArgs a) {
+    constexpr int RP = NT * 16, PIECES = NT * PL * 2, CH = tall_chunk(NT, PL), AHEAD = NT == 1 ? 2 : 1;
+    __shared__ __align__(16) uint16_t wf[CH * PIECES * FACTOR_PIECE];       // [k block][column tile][plane][step][lane][8]
+    __shared__ float xg[RP * (RP + 1)];
+    const bool right = (int)blockIdx.x < a.nbR;
+    const int rows = right ? a.N : a.M, K = a.K, r = a.r, R2P = a.R2P, nkb = pk_kblocks(K);
+    const int8_t* const codes = right ? a.codesB : a.codesA;
+    const uint4* const src = reinterpret_cast<const uint4*>(right ? a.Vf : a.Wf);
+    const float* const steps = right ? a.sB : a.sA;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int li = lane & 15, kq = lane >> 4;
+    const int ngroups = (rows + 255) >> 8, range = panel_range(nkb);
+    const int first = right ? blockIdx.x : blockIdx.x - a.nbR, stride = right ? a.nbR : gridDim.x - a.nbR;
+    const bool once = nkb <= CH;
+    auto stage = [&](int k0) {
+        const int n = min(CH, nkb - k0) * PIECES * 64;
+        for (int p = tid; p < n; p += 512) {
+            const int piece = p >> 6, h = piece & 1, pl = (piece >> 1) % PL, bn = (piece >> 1) / PL;
+            reinterpret_cast<uint4*>(wf)[p] = src[(size_t)(((k0 * NT + bn) * 3 + pl) * 2 + h) * 64 + (p & 63)];
+        }
+    };
+    CodeBlock<FMT> c[AHEAD + 1];
+    float step[2][4], us[2][4];
+    auto begin = [&](int rb) {          // what a block of rows starts from, and (where it fits) what its panel rows need besides the products
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i) c[i].load(codes, rb, rows, min(i, nkb - 1), K, nkb, li, kq);
+        if (NT > 1) return;
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int row = min(32 * rb + 16 * t + 4 * kq + v, rows - 1);
+                step[t][v] = steps[row];
+                if (!right) us[t][v] = a.U[(size_t)row * a.ldu + min(li, r - 1)];
+            }
+    };
+    if (first >= ngroups) return;       // (uniform)
+    begin(first * 8 + wave);
+    if (right) stage_x_gamma(a, RP, xg, tid, 512);
+    if (once) stage(0);
+    __syncthreads();
+    for (int g = first; g < ngroups; g += stride) {
+        const int rb = g * 8 + wave;
+        if (g != first) begin(rb);
+        v4f total[2][NT], acc[2][NT];
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) total[t][nt] = acc[t][nt] = (v4f){0.f, 0.f, 0.f, 0.f};
+        auto add_range = [&] {
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) { total[t][nt] += acc[t][nt]; acc[t][nt] = (v4f){0.f, 0.f, 0.f, 0.f}; }
+        };
+        int left = range;
+        for (int k0 = 0; k0 < nkb; k0 += CH) {
+            if (!once) {
+                __syncthreads();        // nobody reads the k blocks before
+                stage(k0);
+                __syncthreads();
+            }
+            const int k1 = min(nkb, k0 + CH);
+            for (int kb = k0; kb < k1; ++kb) {
+                c[AHEAD].load(codes, rb, rows, min(kb + AHEAD, nkb - 1), K, nkb, li, kq);
+                __builtin_amdgcn_sched_barrier(0);
+                if (left == 0) { add_range(); left = range; }       // (uniform)
+                --left;
+                v8bf af[2][2];
+                c[0].operands(af, kb, K, kq);
+                const uint16_t* const w = wf + (kb - k0) * PIECES * FACTOR_PIECE + lane * 8;
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                        for (int pl = 0; pl < PL; ++pl) {
+                            const v8bf b = *reinterpret_cast<const v8bf*>(w + ((nt * PL + pl) * 2 + h) * FACTOR_PIECE);
+#pragma unroll
+                            for (int t = 0; t < 2; ++t) acc[t][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[h][t], b, acc[t][nt], 0, 0, 0);
+                        }
+#pragma unroll
+                for (int i = 0; i < AHEAD; ++i) c[i] = c[i + 1];
+            }
+        }
+        add_range();
+        if (32 * rb >= rows) continue;          // (the barriers of the next group follow)
+        const bool whole = 32 * rb + 32 <= rows;
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const int row0 = 32 * rb + 16 * t + 4 * kq;
+            float p[NT][4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                if (NT > 1) step[t][v] = steps[min(row0 + v, rows - 1)];
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) p[nt][v] = total[t][nt][v] * step[t][v];
+            }
+            auto z_rows = [&](int u) {
+                const float* const zt = a.Zt + (size_t)u * rows;
+                return whole ? load4u(zt + row0) : load4_tail(zt, row0, rows);
+            };
+            if (right) {
+                constexpr int BATCH = NT == 3 ? 2 : 4;
+                for (int u0 = 0; u0 < r; u0 += BATCH) {
+                    float4 z[BATCH];
+#pragma unroll
+                    for (int j = 0; j < BATCH; ++j) z[j] = z_rows(min(u0 + j, r - 1));
+#pragma unroll
+                    for (int j = 0; j < BATCH; ++j)
+                        if (u0 + j < r) {
+#pragma unroll
+                            for (int nt = 0; nt < NT; ++nt) {
+                                const float x = xg[(16 * nt + li) * (RP + 1) + u0 + j];
+                                p[nt][0] = fmaf(x, z[j].x, p[nt][0]);
+                                p[nt][1] = fmaf(x, z[j].y, p[nt][1]);
+                                p[nt][2] = fmaf(x, z[j].z, p[nt][2]);
+                                p[nt][3] = fmaf(x, z[j].w, p[nt][3]);
+                            }
+                        }
+                }
+            }
+            float* const out = right ? a.Rp : a.Lp;
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                const int col = 16 * nt + li, cc = min(col, r - 1);
+                float own[4];           // the columns that are not a product's
+                if (right) {
+                    const float4 z = z_rows(cc);
+                    const float gam = a.Gam[cc];
+                    own[0] = gam * z.x; own[1] = gam * z.y; own[2] = gam * z.z; own[3] = gam * z.w;
+                } else {
+                    const float sig = a.Sig[cc];
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        own[v] = (NT == 1 ? us[t][v] : a.U[(size_t)min(row0 + v, rows - 1) * a.ldu + cc]) * sig;
+                }
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    if (row0 + v >= rows) continue;
+                    float* const o = out + (size_t)(row0 + v) * R2P;
+                    if (col < r) {
+                        o[right ? col : r + col] = p[nt][v];
+                        o[right ? r + col : col] = own[v];
+                    }
+                    if (nt == 0 && 2 * r + li < R2P) o[2 * r + li] = 0.f;
+                }
+            }
+        }
+    }
+}
+
 // ---------------------------------------------------------------------------
 // T-type: partial[split][cols][LP] = R[i-range, :]^T . W[i-range, :]
 // One workgroup per 64-column strip and range of rows (strips fastest, job a before job b); its 4 waves share the strip,
@@ -1525,6 +1691,15 @@ int launch_resid_mul_t(const PassOperand* op, int nop, QuantParams q, int LP, hi
     return LRQMM_ERR_UNSUPPORTED;
 }
 
+static bool tall_panels(int M, int N, int nkb, int nt, int planes) {
+    if (nt > 3) return false;
+    const int chunks = ceil_div(nkb, tall_chunk(nt, planes));
+    if (N >= 49152 || (N >= 32768 && chunks * nt <= 12)) return true;
+    if (M >= 65536) return true;
+    if (M >= 49152) return chunks * nt <= (nt == 3 ? 6 : 12);
+    return M >= 32768 && (nt == 1 ? chunks <= 4 : nt == 2 && chunks == 1);
+}
+
 int launch_panels(const PanelArgs& in, int RP, int planes, int packed, hipStream_t st) {
     PanelArgs a = in;
     const int most = max(a.M, a.N), nkb = pk_kblocks(a.K);
@@ -1541,6 +1716,28 @@ int launch_panels(const PanelArgs& in, int RP, int planes, int packed, hipStream
         if (planes == 2) LRQ_PR_NC(2); else if (planes == 1) LRQ_PR_NC(1); else LRQ_PR_NC(3);
 #undef LRQ_PR_NC
 #undef LRQ_PR
+        LRQ_CHECK_LAUNCH();
+        return LRQMM_OK;
+    }
+    if (tall_panels(a.M, a.N, nkb, RP / 16, planes)) {
+        int dev = 0, cus = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
+            return LRQMM_ERR_HIP;
+        a.nbR = min(ceil_div(a.N, 256), 2 * cus);
+        const dim3 grid(a.nbR + min(ceil_div(a.M, 256), 2 * cus));
+#define LRQ_PT(FMT, PLV)                                                                                                    \
+    do {                                                                                                                    \
+        if (RP == 16)      hipLaunchKernelGGL((panels_tall_kernel<FMT, 1, PLV>), grid, dim3(512), 0, st, a);                \
+        else if (RP == 32) hipLaunchKernelGGL((panels_tall_kernel<FMT, 2, PLV>), grid, dim3(512), 0, st, a);                \
+        else               hipLaunchKernelGGL((panels_tall_kernel<FMT, 3, PLV>), grid, dim3(512), 0, st, a);                \
+    } while (0)
+#define LRQ_PT_PL(FMT) do { if (planes == 2) LRQ_PT(FMT, 2); else if (planes == 1) LRQ_PT(FMT, 1); else LRQ_PT(FMT, 3); } while (0)
+        if (packed == PK6)      LRQ_PT_PL(PK6);
+        else if (packed == PK8) LRQ_PT_PL(PK8);
+        else                    LRQ_PT_PL(PK_NONE);
+#undef LRQ_PT_PL
+#undef LRQ_PT
         LRQ_CHECK_LAUNCH();
         return LRQMM_OK;
     }

@@ -260,6 +260,9 @@ PACKED = [(128, 96, 128, 4, 24, 8), (127, 97, 191, 4, 20, 8), (129, 160, 193, 2,
 PACKED += [(127, 97, 191, 8, 20, 8), (129, 160, 193, 6, 17, 0), (33, 34, 35, 8, 17, 0), (320, 321, 385, 7, 24, 8), (1025, 1000, 449, 8, 40, 8),
            (1537, 1021, 1100, 8, 24, 8), (2080, 2049, 320, 8, 17, 0), (3100, 2900, 200, 8, 36, 0), (4096, 4096, 1024, 8, 32, 8),
            (64, 96, 131071, 8, 17, 0)]
+# Tall operands, whose panels have a kernel of their own: one to three tiles of factor columns, one chunk of planes and more, both formats.
+PACKED += [(32801, 40, 833, 8, 12, 8), (33000, 45, 321, 4, 20, 8), (65600, 60, 200, 8, 40, 8), (65537, 49, 130, 3, 33, 8),
+           (40, 32802, 833, 4, 12, 8), (70, 49153, 321, 8, 41, 8)]
 
 
 @pytest.mark.parametrize("M,N,K,bits,r,p", PACKED)
@@ -810,7 +813,7 @@ def test_gemm_only_profiling_mode():
 # and two (the last shape), few and many ranges of the last product.  The oracle forms the SVD.
 @pytest.mark.parametrize("M,N,K,bits,r,q", [(40, 33, 17, 8, 1, 0), (65, 63, 64, 8, 16, 1), (130, 70, 65, 4, 5, 0), (300, 260, 1000, 8, 10, 1),
                                             (90, 515, 1025, 8, 16, 1), (260, 130, 2048, 8, 9, 1), (260, 130, 2049, 8, 9, 1), (9000, 40, 300, 8, 8, 1),
-                                            (4000, 2700, 2000, 8, 10, 1)])
+                                            (6700, 40, 2000, 8, 10, 1)])
 def test_panels_from_the_last_products(M, N, K, bits, r, q):
     import paper_2409_18772_amd as L
     A, B = wl.random_matrix("uniform01", M, K, seed=95), wl.random_matrix("uniform01", K, N, seed=96)

@@ -36,6 +36,8 @@ CASES = [
     ("c3_4096_int4_r32_outliers", 640, 512, 768),
     ("c2_4096_int8_r16", 512, 640, 1024),
     ("c3_4096_int4_r32_outliers", 333, 517, 260),     # ragged: guarded kernels
+    ("c2_4096_int8_r16", 33000, 64, 208),             # tall: panels of a kernel of their own
+    ("c3_4096_int4_r32_outliers", 65600, 80, 400),
 ]
 
 
