@@ -1741,13 +1741,15 @@ int launch_panels(const PanelArgs& in, int RP, int planes, int packed, hipStream
         LRQ_CHECK_LAUNCH();
         return LRQMM_OK;
     }
-    const bool two = ceil_div(a.M, 64) + ceil_div(a.N, 64) >= PANEL_TWO_MIN;      // 64 rows a workgroup: half the reads of the planes
+    // 64 rows a workgroup: half the reads of the planes.  From 65 columns on the sums of 64 rows no longer fit in the registers beside
+    // them (lrqmm_gemm, 8 bits, 64 / 32 rows, us: 8192^2 x 1024 rank 72 283.8 / 272.7, 80 288.1 / 277.2, 16384 x 4096 x 2048 rank 72 363.4 / 346.7).
+    const bool two = RP <= 64 && ceil_div(a.M, 64) + ceil_div(a.N, 64) >= PANEL_TWO_MIN;
     const int block = two ? 64 : 32;
     a.nbR = ceil_div(a.N, block);
     const dim3 grid(a.nbR + ceil_div(a.M, block));
 #define LRQ_PK(FMT, PLV)                                                                                                       \
     do {                                                                                                                       \
-        if (two) { NT_SWITCH(RP / 16, hipLaunchKernelGGL((panels_kernel<FMT, NT_, PLV, 2>), grid, dim3(512), 0, st, a)); }                                                                              \
+        if (two) { NT_SWITCH(RP / 16, hipLaunchKernelGGL((panels_kernel<FMT, NT_, PLV, NT_ < 5 ? 2 : 1>), grid, dim3(512), 0, st, a)); } \
         else { NT_SWITCH(RP / 16, hipLaunchKernelGGL((panels_kernel<FMT, NT_, PLV, 1>), grid, dim3(512), 0, st, a)); }     \
     } while (0)
 #define LRQ_PK_PL(FMT) do { if (planes == 2) { LRQ_PK(FMT, 2); } else if (planes == 1) { LRQ_PK(FMT, 1); } else { LRQ_PK(FMT, 3); } } while (0)

@@ -421,13 +421,13 @@ def test_gemm_panel_widths_on_small_tiles(M, N, K, rank):
 
 
 # Panels: rows of one workgroup short and over (32, 64 rows), k blocks that eight waves do not share evenly or that leave waves idle,
-# every width of the factors; 64 rows a workgroup (16384 rows and more, both sides of the limit); tall operands with short rows in
+# every width of the factors; 64 rows a workgroup (16384 rows and more, both sides of the limit; 65 columns and more keep 32); tall operands with short rows in
 # the persistent kernel, on both sides of its limits in rows, columns of the factor and K; each operand as the tall one; the tall
 # kernel (from 32768, 49152 and 65536 rows on, by the width): one chunk of planes, a last one of one k block and a whole one, rows and
 # columns that end early, K below one load, a wave without rows.
 @pytest.mark.parametrize("M,N,K,bits,rank", [(33, 31, 65, 8, 1), (65, 97, 513, 8, 16), (64, 40, 577, 4, 17), (130, 95, 1100, 8, 33), (100, 129, 700, 4, 50),
                                              (96, 161, 2000, 8, 80), (16289, 64, 700, 8, 12), (16353, 30, 700, 8, 12), (16390, 70, 130, 4, 40),
-                                             (17000, 90, 513, 4, 80), (16383, 60, 576, 4, 8), (16385, 61, 575, 4, 8), (20000, 33, 640, 8, 16),
+                                             (17000, 90, 513, 4, 80), (16385, 70, 130, 8, 64), (16385, 70, 130, 8, 65), (16383, 60, 576, 4, 8), (16385, 61, 575, 4, 8), (20000, 33, 640, 8, 16),
                                              (20001, 20, 641, 8, 3), (50, 16401, 129, 4, 5), (70, 17001, 90, 8, 64),
                                              (32768, 40, 769, 8, 3), (32801, 24, 641, 4, 16), (33025, 20, 15, 8, 10), (33000, 50, 380, 8, 20), (49153, 41, 385, 8, 32),
                                              (49500, 60, 193, 4, 33), (49200, 60, 385, 8, 40), (65537, 50, 193, 8, 48), (65600, 48, 577, 4, 40), (66001, 30, 1601, 8, 9),
