@@ -56,9 +56,8 @@ __device__ __forceinline__ float code_sum(float a) { return a * 64.0f; }
 
 // ---- main loop on packed codes (see PK8, PK6) ----
 // A wave's 64 lanes copy 16 bytes each from global memory to 1 KB of LDS, without registers in between.
-// (m0 is set here for this one instruction; the compiler sets it before each use of its own.)
 __device__ __forceinline__ void load_to_lds(uint32_t lds, const uint8_t* base, uint32_t off) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %1" ::"s"(lds), "s"(base), "v"(off) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %1" ::"s"(lds), "s"(base), "v"(off) : "memory", "m0");
 }
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) uint8_t lds_u8;
