@@ -1463,16 +1463,17 @@ static void dispatch_gemm256(bool comp, bool wcint, dim3 grid, hipStream_t st, i
                        tiles_n, ntiles, ntiles, 1, nullptr, qmaxf)
 #define LRQ_GEMM(COMP, WC)                                                                                   \
     do {                                                                                                     \
-        if (packed == PK6) LRQ_PACKED(PK6, COMP, WC);                                                        \
-        else if (packed == PK8) LRQ_PACKED(PK8, COMP, WC);                                                   \
-        else if (full)                                                                                       \
-            hipLaunchKernelGGL((int8_gemm256_kernel<COMP, WC, true>), grid, dim3(512), 0, st, M, N, K, Aq, \
+        if (full)                                                                                            \
+            hipLaunchKernelGGL((int8_gemm256_kernel<COMP, WC, true>), grid, dim3(512), 0, st, M, N, K, Aq,   \
                                BqT, sA, sB, Lp, Rp, R2P, C, Cint, tiles_n, ntiles, ntiles, 1, nullptr, qmaxf); \
         else                                                                                                 \
-            hipLaunchKernelGGL((int8_gemm256_kernel<COMP, WC, false>), grid, dim3(512), 0, st, M, N, K,  \
+            hipLaunchKernelGGL((int8_gemm256_kernel<COMP, WC, false>), grid, dim3(512), 0, st, M, N, K,      \
                                Aq, BqT, sA, sB, Lp, Rp, R2P, C, Cint, tiles_n, ntiles, ntiles, 1, nullptr, qmaxf); \
     } while (0)
-    if (comp) {
+    if (packed) {           // (Cint: raw sums)
+        if (packed == PK6) { if (comp) LRQ_PACKED(PK6, true, false); else if (wcint) LRQ_PACKED(PK6, false, true); else LRQ_PACKED(PK6, false, false); }
+        else               { if (comp) LRQ_PACKED(PK8, true, false); else if (wcint) LRQ_PACKED(PK8, false, true); else LRQ_PACKED(PK8, false, false); }
+    } else if (comp) {
         if (wcint) LRQ_GEMM(true, true); else LRQ_GEMM(true, false);
     } else {
         if (wcint) LRQ_GEMM(false, true); else LRQ_GEMM(false, false);
@@ -1488,7 +1489,9 @@ static void dispatch_gemm(bool comp, bool wcint, dim3 grid, hipStream_t st, int 
                           int ntiles, float qmaxf) {
 #define LRQ_GEMM(COMP, WC) hipLaunchKernelGGL((int8_gemm_kernel<WIDE, COMP, WC, MTW, NTW, PACKED>), grid, dim3(256), 0, st, M, N, K, \
                                               Aq, BqT, sA, sB, Lp, Rp, R2P, C, Cint, tiles_n, ntiles, qmaxf)
-    if (comp) {
+    if constexpr (PACKED != PK_NONE) {      // (without Cint)
+        if (comp) LRQ_GEMM(true, false); else LRQ_GEMM(false, false);
+    } else if (comp) {
         if (wcint) LRQ_GEMM(true, true); else LRQ_GEMM(true, false);
     } else {
         if (wcint) LRQ_GEMM(false, true); else LRQ_GEMM(false, false);
@@ -1711,7 +1714,9 @@ int launch_int8_gemm(int M, int N, int K, const int8_t* Aq, const int8_t* BqT, c
     const bool wide = K >= 16;
     const bool comp = Lp != nullptr;
     // big problems: 256x256 tiles, one workgroup per CU
-    if ((C.C ? large_tiles_into_c(M, N) : int8_gemm_large_tiles(M, N)) && wide) {
+    const bool large = (C.C ? large_tiles_into_c(M, N) : int8_gemm_large_tiles(M, N)) && wide;
+    if (packed && Cint && (C.C || !large)) return LRQMM_ERR_UNSUPPORTED;        // (packed codes: the result or the raw sums)
+    if (large) {
         const int btiles = (int)int8_gemm_tiles(M, N);
         const int btn = ceil_div(N, BTN);
         dim3 bgrid(btiles);

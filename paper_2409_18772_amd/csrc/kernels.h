@@ -206,7 +206,8 @@ struct GemmOut {
 int launch_int8_gemm(int M, int N, int K, const int8_t* Aq, const int8_t* BqT, const float* sA,
                      const float* sB, const float* Lp, const float* Rp, int R2P, GemmOut C,
                      int32_t* Cint, float qmaxf, hipStream_t st, int packed = PK_NONE);
-// packed (here and below): the format of both code matrices; same results.
+// packed (here and below): the format of both code matrices; same results.  Packed codes: no Cint beside a result; Cint without one
+// (out.C == null) holds the raw sums.
 // The format in which codes travel inside a call (PK_NONE: rows of bytes).
 int packed_format(int bits, int K);
 int direct_format(int M, int N, int K, int bits);       // ... of a call without a factorization
