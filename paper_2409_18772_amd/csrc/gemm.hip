@@ -657,11 +657,7 @@ __device__ __forceinline__ void finish_large_tile(const LargeTile& T, ACC (&acc)
 
 // FULL: M, N multiples of 256 and K a multiple of the tile depth -- operand loads carry no guard at all, so
 // nothing consumes a loaded register before it is written to LDS two iterations later.
-// SPLITK (raw sums only, FULL shapes): workgroups [0, full_tiles) compute one tile each as usual;
-// the remaining ntiles - full_tiles tiles are cut into `slices` ranges of K, one workgroup per
-// (tile, range), which leave their int32 partial sums in `part` ([tile][range][256][256]) for
-// sum_tile_slices_kernel (integer addition: exact whatever the cut).
-template <bool COMP, bool WCINT, bool FULL, bool SPLITK = false>
+template <bool COMP, bool WCINT, bool FULL>
 __global__ __launch_bounds__(512, 1) void int8_gemm256_kernel(int M, int N, int K,
                                                               const int8_t* __restrict__ Aq,
                                                               const int8_t* __restrict__ BqT,
@@ -671,23 +667,11 @@ __global__ __launch_bounds__(512, 1) void int8_gemm256_kernel(int M, int N, int 
                                                               const float* __restrict__ Rp, int R2P,
                                                               GemmOut out,
                                                               int32_t* __restrict__ Cint, int tiles_n,
-                                                              int ntiles, int full_tiles, int slices,
-                                                              int32_t* __restrict__ part, float qmaxf) {
+                                                              int ntiles, float qmaxf) {
     __shared__ __align__(16) int8_t As[2][BTM * BSTRIDE];
     __shared__ __align__(16) int8_t Bs[2][BTN * BSTRIDE];
-    int wg = blockIdx.x, kt0 = 0, nk = (K + BBK - 1) / BBK;
-    bool partial = false;
-    if constexpr (SPLITK) {
-        if (wg >= full_tiles) {
-            const int e = wg - full_tiles, lt = e / slices, sl = e - lt * slices;
-            wg = full_tiles + lt;
-            part += (size_t)e * (BTM * BTN);
-            kt0 = (int)((long long)sl * nk / slices);
-            nk = (int)((long long)(sl + 1) * nk / slices) - kt0;
-            partial = true;
-        }
-    }
-    const int tile = xcd_tile(wg, tiles_n, ntiles);
+    const int nk = (K + BBK - 1) / BBK;
+    const int tile = xcd_tile(blockIdx.x, tiles_n, ntiles);
     const int m0 = (tile / tiles_n) * BTM, n0 = (tile % tiles_n) * BTN;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int wm = wave >> 1, wn = wave & 1;
@@ -767,17 +751,17 @@ __global__ __launch_bounds__(512, 1) void int8_gemm256_kernel(int M, int N, int 
                     acc[mt][nt] = __builtin_amdgcn_mfma_i32_32x32x32_i8(af[mt], bf[nt], acc[mt][nt], 0, 0, 0);
         }
     };
-    LRQ_GLOAD(r0, kt0 * BBK);
-    LRQ_GLOAD(r1, (kt0 + 1) * BBK);
-    LRQ_SSTORE(r0, 0, kt0 * BBK);
+    LRQ_GLOAD(r0, 0);
+    LRQ_GLOAD(r1, BBK);
+    LRQ_SSTORE(r0, 0, 0);
     __syncthreads();
     // iteration i: the set that held tile i is free -> load tile i + 2; compute tile i; publish tile i+1
 #define LRQ_GEMM_STEP(J, SCUR, SNEXT)                  \
     if (kt + J < nk) {                                 \
         const int i = kt + J;                          \
-        LRQ_GLOAD(SCUR, (kt0 + i + 2) * BBK);       \
+        LRQ_GLOAD(SCUR, (i + 2) * BBK);                \
         compute(i & 1);                                \
-        if (i + 1 < nk) { LRQ_SSTORE(SNEXT, (i + 1) & 1, (kt0 + i + 1) * BBK); } \
+        if (i + 1 < nk) { LRQ_SSTORE(SNEXT, (i + 1) & 1, (i + 1) * BBK); } \
         __syncthreads();                               \
     }
     for (int kt = 0; kt < nk; kt += 2) {
@@ -789,11 +773,14 @@ __global__ __launch_bounds__(512, 1) void int8_gemm256_kernel(int M, int N, int 
 #undef LRQ_GLOAD
 #undef LRQ_SSTORE
 
-    finish_large_tile<COMP, WCINT, SPLITK>(LargeTile{M, N, m0, n0, sA, sB, Lp, Rp, R2P, out, Cint, part, partial, qmaxf}, acc, &As[0][0],
-                                           &Bs[0][0]);
+    finish_large_tile<COMP, WCINT, false>(LargeTile{M, N, m0, n0, sA, sB, Lp, Rp, R2P, out, Cint, nullptr, false, qmaxf}, acc, &As[0][0],
+                                          &Bs[0][0]);
 }
 
 // The same tiles from packed codes.
+// SPLITK (raw sums only, whole tiles and 128-deep steps): workgroups [0, full_tiles) compute one tile each as usual; the remaining
+// ntiles - full_tiles tiles are cut into `slices` ranges of K, one workgroup per (tile, range), which leave their int32 partial
+// sums in `part` ([tile][range][256][256]) for sum_tile_slices_kernel (integer addition: exact whatever the cut).
 template <int FMT, bool COMP, bool WCINT, bool SPLITK = false>
 __global__ __launch_bounds__(512, 1) void packed_gemm256_kernel(int M, int N, int K, const uint8_t* __restrict__ A,
                                                                 const uint8_t* __restrict__ B, const float* __restrict__ sA,
@@ -1465,10 +1452,10 @@ static void dispatch_gemm256(bool comp, bool wcint, dim3 grid, hipStream_t st, i
     do {                                                                                                     \
         if (full)                                                                                            \
             hipLaunchKernelGGL((int8_gemm256_kernel<COMP, WC, true>), grid, dim3(512), 0, st, M, N, K, Aq,   \
-                               BqT, sA, sB, Lp, Rp, R2P, C, Cint, tiles_n, ntiles, ntiles, 1, nullptr, qmaxf); \
+                               BqT, sA, sB, Lp, Rp, R2P, C, Cint, tiles_n, ntiles, qmaxf);                   \
         else                                                                                                 \
             hipLaunchKernelGGL((int8_gemm256_kernel<COMP, WC, false>), grid, dim3(512), 0, st, M, N, K,      \
-                               Aq, BqT, sA, sB, Lp, Rp, R2P, C, Cint, tiles_n, ntiles, ntiles, 1, nullptr, qmaxf); \
+                               Aq, BqT, sA, sB, Lp, Rp, R2P, C, Cint, tiles_n, ntiles, qmaxf);               \
     } while (0)
     if (packed) {           // (Cint: raw sums)
         if (packed == PK6) { if (comp) LRQ_PACKED(PK6, true, false); else if (wcint) LRQ_PACKED(PK6, false, true); else LRQ_PACKED(PK6, false, false); }
@@ -1544,6 +1531,7 @@ size_t int8_gemm_sums_scratch_bytes(int M, int N, int K) {
 
 int launch_int8_gemm_sums(int M, int N, int K, const int8_t* Aq, const int8_t* BqT, int32_t* Cint, int resident,
                           int32_t* part, hipStream_t st, int packed) {
+    if (packed == PK_NONE) return LRQMM_ERR_UNSUPPORTED;
     const SumsPlan p = part ? plan_sums(M, N, K, Aq, BqT, resident) : SumsPlan{0, 0, 0, 1};
     if (p.left == 0)
         return launch_int8_gemm(M, N, K, Aq, BqT, nullptr, nullptr, nullptr, nullptr, 0, GemmOut{nullptr, N, 1.0f, 0.0f},
@@ -1553,13 +1541,9 @@ int launch_int8_gemm_sums(int M, int N, int K, const int8_t* Aq, const int8_t* B
     hipLaunchKernelGGL((packed_gemm256_kernel<FMT, false, true, true>), dim3(full_tiles + p.left * p.slices), dim3(512), 0, st, M, N, \
                        K, reinterpret_cast<const uint8_t*>(Aq), reinterpret_cast<const uint8_t*>(BqT), nullptr, nullptr, nullptr,     \
                        nullptr, 0, GemmOut{nullptr, N, 1.0f, 0.0f}, Cint, p.tiles_n, p.ntiles, full_tiles, p.slices, part, 0.0f)
-    if (packed == PK6)      LRQ_SUMS(PK6);
-    else if (packed == PK8) LRQ_SUMS(PK8);
+    if (packed == PK6) LRQ_SUMS(PK6);
+    else               LRQ_SUMS(PK8);
 #undef LRQ_SUMS
-    else
-        hipLaunchKernelGGL((int8_gemm256_kernel<false, true, true, true>), dim3(full_tiles + p.left * p.slices),
-                           dim3(512), 0, st, M, N, K, Aq, BqT, nullptr, nullptr, nullptr, nullptr, 0,
-                           GemmOut{nullptr, N, 1.0f, 0.0f}, Cint, p.tiles_n, p.ntiles, full_tiles, p.slices, part, 0.0f);
     LRQ_CHECK_LAUNCH();
     return LRQMM_OK;
 }
@@ -1574,14 +1558,11 @@ int launch_int8_gemm_sums_finish(int M, int N, int K, const int8_t* Aq, const in
     return LRQMM_OK;
 }
 
-// Six bits for codes of at most five whose sums stay below 2^24, bytes from six bits on.  Products of random 8-bit codes at rank 0,
+// Six bits for codes of at most five whose sums stay within 2^24, bytes otherwise.  Products of random 8-bit codes at rank 0,
 // us, from rows of bytes (staged through registers) / from blocks of bytes (copied to LDS as they are): 300^3 4.3 / 4.0, 1024^3 5.9 /
 // 5.7, 2000^3 20.8 / 16.9, 1537 x 1021 x 2311 19.6 / 11.2 (rows of an odd length), 512 x 4096 x 4096 19.8 / 16.4, 3072 x 1536 x 2048
 // 25.1 / 19.1, 3000^3 53.4 / 44.7, 5000^3 164 / 138, 8192^3 507 / 474; at 4096^3 and beyond the chip's power bounds both (77 to 87).
-int packed_format(int bits, int K) {
-    if (bits > 5) return PK8;
-    return ((long long)K << (2 * (bits - 1))) <= (1ll << 24) ? PK6 : PK_NONE;
-}
+int packed_format(int bits, int K) { return bits <= 5 && ((long long)K << (2 * (bits - 1))) <= (1ll << 24) ? PK6 : PK8; }
 
 // Direct quantization: a workgroup of the packing kernel takes eight rows of A through LDS, which costs a tall A with short rows
 // more than a narrow product gains.  Rank 0, 8 bits, rows of bytes / packed, us: 100352 x 64 K = 64 35.7 / 41.0, 256 41.3 / 46.7, 512 61.5 /

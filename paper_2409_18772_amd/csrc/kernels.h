@@ -208,9 +208,9 @@ int launch_int8_gemm(int M, int N, int K, const int8_t* Aq, const int8_t* BqT, c
                      int32_t* Cint, float qmaxf, hipStream_t st, int packed = PK_NONE);
 // packed (here and below): the format of both code matrices; same results.  Packed codes: no Cint beside a result; Cint without one
 // (out.C == null) holds the raw sums.
-// The format in which codes travel inside a call (PK_NONE: rows of bytes).
+// The format in which codes travel inside a call with factorizations, and in one without (there also PK_NONE: rows of bytes).
 int packed_format(int bits, int K);
-int direct_format(int M, int N, int K, int bits);       // ... of a call without a factorization
+int direct_format(int M, int N, int K, int bits);
 // D <- alpha (A0 B0 + A0 B1 + A1 B0 [+ A1 B1]) + beta D, the products of the operands' codes (0) and of their residuals' (1),
 // each dequantized by the steps of its group maxima: terms = 3 or 4 products in one launch, where int8_terms_usable.
 bool int8_terms_usable(int M, int N, int K);
@@ -229,7 +229,7 @@ int launch_empty_product(int M, int N, GemmOut C, int32_t* Cint, hipStream_t st)
 #define LRQ_SUMS_MAX_PARTS 64       // (tile, range) pairs at most
 size_t int8_gemm_sums_scratch_bytes(int M, int N, int K);
 int launch_int8_gemm_sums(int M, int N, int K, const int8_t* Aq, const int8_t* BqT, int32_t* Cint, int resident,
-                          int32_t* part, hipStream_t st, int packed = PK_NONE);
+                          int32_t* part, hipStream_t st, int packed);
 int launch_int8_gemm_sums_finish(int M, int N, int K, const int8_t* Aq, const int8_t* BqT, int32_t* Cint, int resident,
                                  const int32_t* part, hipStream_t st);
 // True when the large-tile kernel may be asked for raw int32 sums: launch_int8_gemm with C == null and Cint != null (sA, sB are

@@ -1637,7 +1637,12 @@ static int dispatch_t(const PassOperand* op, int nop, QuantParams q, hipStream_t
 int launch_resid_mul_n(const PassOperand* op, int nop, QuantParams q, int LP, bool quantize, hipStream_t st, int planes, int packed) {
     if (quantize && packed == PK6) LRQ_NT_PL(dispatch_n, , PK6>(op, nop, q, st));
     if (quantize && packed == PK8) LRQ_NT_PL(dispatch_n, , PK8>(op, nop, q, st));
-    if (quantize) LRQ_NT_PL(dispatch_n, , QOUT_BYTES>(op, nop, q, st));
+    if (quantize) {     // rows of bytes: beside the one-read kernel alone, whose sketches have 16 columns
+        if (LP != 16) return LRQMM_ERR_UNSUPPORTED;
+        if (planes == 1) return dispatch_n<1, 1, QOUT_BYTES>(op, nop, q, st);
+        if (planes == 2) return dispatch_n<1, 2, QOUT_BYTES>(op, nop, q, st);
+        return dispatch_n<1, 3, QOUT_BYTES>(op, nop, q, st);
+    }
     if (LP == 16 && planes == 3) {
         const PassPair p = make_pair(op, nop, false, 64);
         hipLaunchKernelGGL(resid_mul_n_kernel, LRQ_PAIR_ARGS(p, 256));
