@@ -4,8 +4,8 @@
 A step is one pass of the whole hot path (lrqmm_matmul: quantize A and B, factor
 both residuals, integer GEMM with fused compensation) over one batch of synthetic
 input already resident in HBM.  Prints ONE JSON line with the headline metric
-(effective TOPS = 2MNK / t), a roofline object for the dominant kernel (the int8
-MFMA GEMM), the per-stage split, relative errors against
+(effective TOPS = 2MNK / t), a roofline object for the dominant kernel (the
+integer product), the per-stage split, relative errors against
 the exact product, and the CPU oracle timed on the host cores as a baseline.
 """
 from __future__ import annotations
@@ -179,8 +179,8 @@ def main():
 
     # direct-quantization pipeline alone (rank 0) for the overhead figure
     t_dq = timed(lambda: step(0), max(5, args.steps // 2), 2)
-    # the integer product alone on the idle chip (codes resident, fused dequantizing store, no compensation):
-    # context for the in-schedule figure of the roofline object
+    # lrqmm_gemm on the idle chip (rows of byte codes resident, fused dequantizing store, no compensation): the int8 kernel that a
+    # program with codes of its own gets, context for the in-schedule figure of the roofline object
     cA, mA = L.lrqmm_quantize(dA, L.AXIS_ROW, w.bits)
     cB, mB = L.lrqmm_quantize(dB, L.AXIS_COL, w.bits)
     t_gemm_alone = timed(lambda: L.lrqmm_gemm(cA, mA, cB, mB, w.bits, workspace=ws, C=C), max(5, args.steps // 2), 2)
@@ -191,7 +191,7 @@ def main():
 
     ops = 2.0 * w.M * w.N * w.K
     tops = ops / t_step / 1e12
-    # dominant kernel: the int8 MFMA GEMM.  For large problems lrqmm_matmul runs it early on its
+    # dominant kernel: the integer product.  For large problems lrqmm_matmul runs it early on its
     # third stream (stage "int_gemm", raw int32 sums) and the epilogue separately (stage "gemm");
     # otherwise stage "gemm" is the GEMM with its fused epilogue.
     gemm_key = "int_gemm" if early else "gemm"
@@ -223,16 +223,17 @@ def main():
             "ms": round(job_ms, 4), "operand_reads": n_reads, "both_operands": joint,
             "reads_performed": n_reads - 1 if (op == "a" and one_read_a) else n_reads,
             "algorithmic_GBs": round(gbs, 1), "frac_hbm": round(gbs / PEAK_HBM_GBS, 4)}
-    stage_info[gemm_key].update(TOPs=round(achieved, 1), frac_int8_mfma=round(achieved / PEAK_INT8_TOPS, 4))
     # which roof bounds the product: its algorithmic bytes (codes read once, 4-byte results written once, panels)
     # against its operations; below peak_ops / peak_bytes operations per byte the kernel is bound by memory
     gemm_bytes = float(w.M * w.K + w.K * w.N + 4 * w.M * w.N + (0 if early else 8 * w.rank * (w.M + w.N)))
     large_tiles = w.M >= 256 and w.N >= 256 and -(-w.M // 256) * -(-w.N // 256) >= 128
     large_tiles = large_tiles and (early or -(-w.M // 128) * -(-w.N // 128) > 512)
-    # inside lrqmm_matmul codes travel as matrix-core operands, up to five bits (with sums below 2^24) for the fp6 cores
-    packed = w.rank == 0 or not one_read_a
+    # inside lrqmm_matmul codes travel as matrix-core operands, up to five bits (with sums within 2^24) for the fp6 cores; a tall A
+    # with short rows leaves rows of bytes
+    packed = not one_read_a
     six = packed and w.bits <= 5 and w.K << (2 * (w.bits - 1)) <= 1 << 24
     peak_mfma, cores = (PEAK_FP6_TOPS, "fp6") if six else (PEAK_INT8_TOPS, "int8")
+    stage_info[gemm_key].update({"TOPs": round(achieved, 1), f"frac_{cores}_mfma": round(achieved / peak_mfma, 4)})
     if ops / gemm_bytes >= peak_mfma * 1e12 / (PEAK_HBM_GBS * 1e9):
         roof = {"bound": "mfma", "achieved": round(achieved, 2), "peak": peak_mfma, "unit": "TOP/s",
                 "frac": round(achieved / peak_mfma, 4)}
@@ -241,6 +242,7 @@ def main():
         roof = {"bound": "hbm", "achieved": round(gbs_gemm, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
                 "frac": round(gbs_gemm / PEAK_HBM_GBS, 4), "algorithmic_bytes_per_launch": gemm_bytes}
     large_kernel = "packed_gemm256_kernel" if packed else "int8_gemm256_kernel"
+    large_alone = w.M >= 256 and w.N >= 256 and -(-w.M // 128) * -(-w.N // 128) > 512
     if early:   # the dequantizing rank-2r update alone: reads and rewrites C
         gbs = 8.0 * w.M * w.N / (stages["gemm"] * 1e-3) / 1e9
         stage_info["gemm"].update(kernel="rank_update_kernel", algorithmic_GBs=round(gbs, 1),
@@ -296,12 +298,14 @@ def main():
                                 + " (%s MFMA GEMM + fused dequant and rank-2r epilogue)" % cores),
                      **roof,
                      # counter bytes of this kernel on this workload, or null when no summary is tracked for it
-                     "traffic": None if packed else read_traffic(f"int8_gemm_{SHORT.get(w.name, w.name)}_pmc.txt"),
+                     "traffic": read_traffic(f"{'packed' if packed else 'int8'}_gemm_{SHORT.get(w.name, w.name)}_pmc.txt"),
                      "launch_ms": round(stages[gemm_key], 4), "ops_per_launch": ops,
-                     "alone": {"ms": round(t_gemm_alone * 1e3, 4), "achieved": round(ops / t_gemm_alone / 1e12, 2),
-                               "frac": round(ops / t_gemm_alone / 1e12 / PEAK_INT8_TOPS, 4),
-                               "note": "lrqmm_gemm at rank 0 on the idle chip: the same product with its "
-                                       "dequantizing float32 store, wall time per call"}},
+                     "alone": {"kernel": "int8_gemm256_kernel" if large_alone else "int8_gemm_kernel",
+                               "ms": round(t_gemm_alone * 1e3, 4), "achieved": round(ops / t_gemm_alone / 1e12, 2),
+                               "peak": PEAK_INT8_TOPS, "frac": round(ops / t_gemm_alone / 1e12 / PEAK_INT8_TOPS, 4),
+                               "note": "lrqmm_gemm at rank 0 on the idle chip, from rows of bytes on the int8 matrix cores with its "
+                                       "dequantizing float32 store, wall time per call: not the kernel above where that reads "
+                                       "packed codes"}},
         "stages": stage_info,
         "stages_note": "GEMM launch time from HIP events inside the timed region; the other stages from a "
                        "separate fully instrumented pass of the same step",
