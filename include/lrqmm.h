@@ -198,14 +198,14 @@ LRQMM_API int lrqmm_gemm_ex(int M, int N, int K, int bits, int rank,
 /*
  * lrqmm_gemm_ex for callers that cannot allocate device memory or hand over a workspace: code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same
- * kernels and bit-identical results; the scratch memory (step vectors, padded factor copies, partial
- * code products and the two panels of the rank-2r update) is a fixed array of
+ * kernels and bit-identical results; the scratch memory (step vectors, the factors split into planes,
+ * slices of their product and the two panels of the rank-2r update) is a fixed array of
  * LRQMM_STATIC_SCRATCH_BYTES bytes inside the library's device image, one copy per GPU, held until
  * the process ends.  The call allocates and frees nothing.  (Its first call on a device looks the
  * array's address up; make that call outside a capture.)
  * Problems that need more than LRQMM_STATIC_SCRATCH_BYTES return LRQMM_ERR_STATIC_LIMIT and enqueue
- * nothing (the need is what lrqmm_workspace_bytes reports for lrqmm_gemm alone, about
- * 4 (M + N) (3 rank + 4 rank * splits) + 20 K rank bytes; 16 MiB covers M = N = K = 4096 at rank 32).
+ * nothing (counted as about 4 (M + N) (3 rank + 4 rank * splits) + 20 K rank bytes, more than the
+ * kernels take today, so that the same problems fit as ever; 16 MiB covers M = N = K = 4096 at rank 32).
  * All calls on one GPU share that GPU's array: calls that overlap in time on one GPU (two streams,
  * two threads) race on it and must be serialised by the caller; a call does not depend on what an
  * earlier call left there (every word a kernel reads is written earlier in the same call).

@@ -249,15 +249,18 @@ bool two_chains(int M, int N, int K) {
 // Whether the integer product (`tiles` tiles of 256 x 256, one per CU at a time) runs early, beside the small SVDs and the
 // panel kernels, with the update as a kernel of its own, or with its fused epilogue after the panels.  Early it saves a last
 // round that leaves most CUs idle, and the time of the SVDs where the product is one round and not much longer than they
-// are; it writes and reads C once more, and a long product holds the CUs that the panel kernels need.  Measured, early /
-// fused, us per call (one power iteration).  Whole rounds: 4096^3 l = 24 363 / 329, 32 375 / 357, 40 414 / 418, 56 527 / 539, 80
-// 659 / 673; two, 8192 x 4096 x 4096, 40 599 / 588, 56 710 / 712, 64 771 / 786, 80 828 / 887; four, 8192^3, 40 1486 / 1442, 56 1681 /
-// 1639, 64 1729 / 1716, 80 1852 / 1854.  Rounds filled to 0.56 (one, 3072^3) 32 304 / 309; 0.63 (two, 4608^3) 24 455 / 453, 32 468 /
-// 485, 40 522 / 560; 0.75 (three, 6144^3) 32 781 / 825; 0.77 (four, 7168^3) 32 1068 / 1109.  From 0.85 on widths up to 48 part with
-// little on either side: 0.88 (three, 6656^3) 32 933 / 933, 48 1040 / 1068, (four, 7680^3) 40 1329 / 1317, 48 1373 / 1378, 0.94 (four,
-// 7936^3) 48 1456 / 1436; wider ones gain, 0.88 7680^3 56 1485 / 1512, 64 1539 / 1603, 0.94 7936^3 56 1587 / 1595, 64 1640 / 1685, 80
-// 1721 / 1815, 0.90 (five, 8704^3) 56 1963 / 1996, 64 2024 / 2124, 80 2142 / 2266, 0.89 (seven, 10240^3) 56 2648 / 2624, 64 2731 / 2774,
-// 80 2869 / 2986.
+// are; it writes and reads C once more, and a long product holds the CUs that the panel kernels need.  The lines lie alike for both
+// formats of packed codes.  Measured, early / fused, us per call (one power iteration), by the sketch's width, 4 bits; 8 bits.  Whole
+// rounds: one, 4096^3, 24 342 / 302; 356 / 327, 32 344 / 326; 367 / 352, 40 391 / 384; 405 / 407, 56 504 / 501; 507 / 527, 80 684 / 680; 693 / 708;
+// two, 8192 x 4096 x 4096, 40 558 / 538; 591 / 578, 56 653 / 648; 682 / 691, 64 692 / 705; 743 / 752, 80 836 / 864; 851 / 906; four, 8192^3, 56
+// 1436 / 1416; 1652 / 1603, 64 1485 / 1481; 1689 / 1661, 80 1680 / 1733; 1873 / 1906.  Rounds filled to 0.50 (half of one, 4096 x 2048 x 4096) 32
+// 299 / 285; 298 / 293, 80 626 / 626; 626 / 629; 0.56 (one, 3072^3) 32 287 / 284; 286 / 295, 40 341 / 340; 341 / 353; 0.63 (two, 4608^3) 24 411 /
+// 406; 449 / 444, 32 422 / 435; 451 / 477, 40 477 / 514; 506 / 550; 0.75 (three, 6144^3) 32 683 / 719; 779 / 819; 0.77 (four, 7168^3) 32 940 / 958; 1073 /
+// 1107.  From 0.85 on widths up to 48 part with little on either side: 0.88 (three, 6656^3) 32 807 / 812; 916 / 918, 48 914 / 927; 1015 / 1025,
+// (four, 7680^3) 40 1147 / 1139; 1326 / 1297, 48 1197 / 1174; 1346 / 1330, 0.94 (four, 7936^3) 48 1262 / 1230; 1435 / 1402; wider ones gain, 0.88
+// 7680^3 56 1292 / 1309; 1442 / 1459, 64 1339 / 1368; 1490 / 1518, 0.94 7936^3 56 1384 / 1381; 1555 / 1536, 64 1434 / 1447; 1604 / 1594, 80 1608 / 1676; 1781 /
+// 1814, 0.90 (five, 8704^3) 56 1689 / 1714; 1910 / 1931, 64 1756 / 1781; 1967 / 1991, 0.89 (seven, 10240^3) 56 2238 / 2218; 2604 / 2581, 64 2306 / 2301;
+// 2672 / 2660, 80 2583 / 2633; 2975 / 2999.
 bool early_product(long long tiles, int cus, int ell) {
     const long long rounds = (tiles + cus - 1) / cus;
     if (ell < 32) return false;
@@ -320,8 +323,9 @@ enum class FirstPass {
 
 // Appends the launches of one factorization, or of two that advance together (one launch per step for both; their
 // operands have different axes), to `ops`.  The sketches are in place.  svd_index: position of the small SVD.
-// stop_at_basis: the list ends with the last product's partials (see launch_basis_panels).  basis_suffices: the caller only uses the product U diag(Sigma) Vt, and nothing is truncated (oversample == 0): U = Q,
-// Sigma = 1, Vt = Q^T R carry the same product as the SVD's factors.  packed: the format of the quantizing pass's codes.
+// stop_at_basis: the list ends with the last product's partials (see launch_basis_panels).  basis_suffices: the caller only uses the
+// product U diag(Sigma) Vt, and nothing is truncated (oversample == 0): U = Q, Sigma = 1, Vt = Q^T R carry the same product as the
+// SVD's factors.  packed: the format of the quantizing pass's codes.
 static void factor_launches(LaunchList& ops, const Factor* factors, int n, FirstPass first, QuantParams q, int rank,
                             int oversample, int power_iters, int planes_first, int planes, int planes_last, hipStream_t st,
                             size_t* svd_index, float* one_read_amax = nullptr, bool basis_suffices = false,

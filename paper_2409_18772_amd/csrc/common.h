@@ -156,9 +156,9 @@ __device__ __forceinline__ uint4 tail16(uint4 v, int sh) {
 //   PK6: codes of at most five bits.  The magnitudes 0 .. 16 are the first seventeen values of the six-bit e2m3 format in units of
 //   1/8 (its subnormals and the first binades continue each other), so a code is exact in it, sign and magnitude, and so is a
 //   product of two.  v_mfma_f32_32x32x64_f8f6f4 takes such operands at twice the rate of the int8 instructions, from 3/4 of the
-//   bytes, and adds in float32, where integers are exact below 2^24: the sums are the int8 matrix cores' sums (times 1/64).
-//   Measured on random 4-bit codes, int8 from rows of codes / this: 4096^3 59 / 46 us, 16384^3 3.99 / 2.56 ms; operands in registers
-//   2.4 / 5.0 POP/s.  24 bytes per lane (code e in bits 6 e ..): first the lanes' bytes 0 .. 15, then 16 .. 23.
+//   bytes, and adds in float32, where integers are exact up to 2^24: the sums are the int8 matrix cores' sums (times 1/64).
+//   Measured on random 4-bit codes, int8 from rows of codes / this: 4096^3 59 / 46 us, 16384^3 3.99 / 2.56 ms; operands in
+//   registers, one probe of both, 2.4 / 5.0 POP/s (int8 with four waves a SIMD: 2.9).  24 bytes per lane (code e in bits 6 e ..): first the lanes' bytes 0 .. 15, then 16 .. 23.
 // Both LDS reads of a wave are contiguous.
 enum { PK_NONE = 0, PK6 = 6, PK8 = 8 };
 #define PK_K 64

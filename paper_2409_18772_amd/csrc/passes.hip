@@ -1496,8 +1496,9 @@ static bool pass_n_wide(int rows, int cols, int LP) {
 // Up to 1024 rows ranges of one chunk, down to 64 elements: such a pass is the load latency of its chunks, one after the
 // other.  Two chunks and more / this, us per call: 200^3 l = 10 87.7 / 83.5, 256^3 l = 8 50.8 / 48.2, 512^3 l = 24 130.4 /
 // 127.9, 1000^3 l = 10 113.1 / 108.2; beyond 2000^3 l = 10 157.0 / 163.4.  Up to MAX_SPLITS_FEW ranges there: with eight a 512 x 4096
-// operand was 64 workgroups of eight chunks each (12.2 us a pass, 24 columns); layer call of 512 x 4096 x 4096, 8 / 32 ranges, 163.4 /
-// 153.3 us.
+// operand was 64 workgroups of eight chunks each (12.2 us a pass, 24 columns).  Layer calls, 8 bits, one power iteration, 8 / 16 / 32 ranges,
+// us: 512 x 4096 x 4096 l = 24 167 / 158 / 158, 40 231 / 224 / 223, 80 431 / 422 / 423; 128 x 4096 x 4096 l = 80 416 / 406 / 403; 1024 x 4096 x 4096
+// l = 24 186 / 177 / 179, 80 454 / 447 / 451; 256 x 512 x 16384 l = 24 291 / 254 / 238, 80 659 / 611 / 589; 1000^3 equal.
 PassPlan plan_pass_n(int rows, int cols, int LP) {
     const int unit = LP == 16 ? KCHUNK : 64;        // chunk depth of the kernel
     PassPlan p;
