@@ -1564,15 +1564,26 @@ int launch_int8_gemm_sums_finish(int M, int N, int K, const int8_t* Aq, const in
 // 25.1 / 19.1, 3000^3 53.4 / 44.7, 5000^3 164 / 138, 8192^3 507 / 474; at 4096^3 and beyond the chip's power bounds both (77 to 87).
 int packed_format(int bits, int K) { return bits <= 5 && ((long long)K << (2 * (bits - 1))) <= (1ll << 24) ? PK6 : PK8; }
 
-// Direct quantization: a workgroup of the packing kernel takes eight rows of A through LDS, which costs a tall A with short rows
-// more than a narrow product gains.  Rank 0, 8 bits, rows of bytes / packed, us: 100352 x 64 K = 64 35.7 / 41.0, 256 41.3 / 46.7, 512 61.5 /
-// 65.8, 768 95.5 / 90.7; 100352 x 512 128 81.7 / 86.6, 384 125 / 132, 512 143 / 144; 40000 x 768 384 59.7 / 63.3, 512 65.7 / 67.0; 40000 x 1024 512 84.7
-// / 88.1, 768 112 / 114; 100352 x 1024 256 155 / 156, 512 215 / 213; 100352 x 2048 64 239 / 215.  4 bits: 100352 x 64 K = 384 48.0 / 52.5, 512 60 / 59;
-// 100352 x 512 256 104 / 107, 384 125 / 125.  Up to 8192 rows either takes the same time, which is that of the launches.
+// Direct quantization: a workgroup of the packing kernel takes eight rows of A through LDS, four of more than 4096, which costs a tall A
+// with short rows or with such long ones more than a narrow product gains.  Rank 0, 8 bits, rows of bytes / packed, us: 100352 x 64 K = 64
+// 35.7 / 41.0, 256 41.3 / 46.7, 512 61.5 / 65.8, 768 95.5 / 90.7; 100352 x 512 128 81.7 / 86.6, 384 125 / 132, 512 143 / 144; 40000 x 768 384 59.7 / 63.3,
+// 512 65.7 / 67.0; 40000 x 1024 512 84.7 / 88.1, 768 112 / 114; 100352 x 1024 256 155 / 156, 512 215 / 213; 100352 x 2048 64 239 / 215; long rows 16384
+// x 64 4112 82.0 / 106, 8000 170 / 178, 12000 253 / 261; 16384 x 300 4864 132 / 150, 8192 221 / 231, 12000 347 / 328; 5000 x 256 4864 50.4 / 58.0, 12000 121 /
+// 128; 3200 x 64 4112 36.1 / 39.0; 3000 x 64 8000 56.1 / 55.0.  4 bits: 100352 x 64 K = 384 48.0 / 52.5, 512 60 / 59; 100352 x 512 256 104 / 107,
+// 384 125 / 125; 16384 x 256 4112 102 / 120, 8000 202 / 194; 8192 x 256 8192 104 / 112.  Up to 8192 short rows either takes the same time, which is that of the launches.
+// Rows of bytes that are no multiple of four read slower, so that these stay only where nothing but A counts: 100352 x 16 207 40.8 / 44.1, 333
+// 47.8 / 50.7, 461 57.0 / 54.7; 100352 x 64 333 50.8 / 53.3; 100352 x 256 207 64.8 / 65.4; 40000 x 16 207 22.9 / 23.8; 16384 x 64 5001 111 / 120; rows of
+// less than 16, read byte by byte, nowhere: 40000 x 16 K = 11 29.7 / 21.1.
 int direct_format(int M, int N, int K, int bits) {
     const int format = packed_format(bits, K);
-    const bool narrow = format == PK6 ? N <= 512 && K <= 384 : N <= 768 && K <= 512;
-    return M >= 16384 && narrow ? PK_NONE : format;
+    const bool six = format == PK6;
+    if (K < 16) return format;
+    if (K % 4 != 0) return N <= 64 && ((M >= 65536 && K <= 384) || (M >= 16384 && K > 4096)) ? PK_NONE : format;
+    if (K > 4096) {
+        const int widest = K <= 6144 ? 384 : six ? (M < 16384 && K <= 8192 ? 256 : 64) : K <= 8192 ? 384 : 256;
+        return M >= 3072 && N <= widest ? PK_NONE : format;
+    }
+    return M >= 16384 && (six ? N <= 512 && K <= 384 : N <= 768 && K <= 512) ? PK_NONE : format;
 }
 
 long long int8_gemm_tiles(int M, int N) { return (long long)ceil_div(M, BTM) * ceil_div(N, BTN); }
@@ -1630,18 +1641,21 @@ static bool tall_terms(int M, int N) {
 //   fewer: 3000^2 (3 and 4) 8 bits K = 512 65.2 / 75.6, 1024 95.8 / 97.7, 1536 132 / 124; 4 bits 512 62.2 / 66.6, 768 77.0 / 74.7; 3072^2,
 //     5000^2 and 6144^2 within 200 of K
 //   half as many (outputs of up to 128 rows, where 256-row tiles are half empty): 64 x 50000 8 bits K = 64 45.7 / 43.0, 512 129 / 114
+// Rows of bytes that are no multiple of 16, and of an odd number of them even more, read slower, and the limits lie lower:
+//   one round: 2000^2 8 bits K = 200 32.5 / 34.1, 500 42.8 / 41.9, 63 30.7 / 29.8, 461 46.1 / 41.0; 300^2 129 29.9 / 27.5
+//   as many: 4096^2 8 bits K = 700 104 / 114, 1500 173 / 167, 461 94.9 / 99.6, 1001 151 / 134; 4 bits 500 77.2 / 86.5, 700 97.2 / 96.2, 333 75.6 / 80.9, 461
+//     87.5 / 85.8
+//   fewer: 5000^2 8 bits K = 500 141 / 156, 700 180 / 180, 333 138 / 141, 461 166 / 156; 4 bits 500 131 / 135, 700 171 / 152, 207 108 / 117, 333 131 / 126
 int terms_format(int M, int N, int K, int bits) {
+    static const int limits[3][2][3] = {        // [one round, fewer, as many][bytes, six bits][K a multiple of 16, of 4, of neither]
+        {{512, 256, 0}, {384, 192, 0}}, {{1408, 704, 352}, {896, 544, 288}}, {{2560, 1280, 640}, {1024, 704, 448}}};
     const int format = packed_format(bits, K);
     const long long tiles = (long long)ceil_div(M, 128) * ceil_div(N, 128), tall = (long long)ceil_div(M, 256) * ceil_div(N, 128);
     const long long rounds = (tiles + GEMM_CUS - 1) / GEMM_CUS;
     const long long byte_rounds = tall_terms(M, N) ? 2 * ((tall + GEMM_CUS - 1) / GEMM_CUS)
                                                    : tiles <= GEMM_CUS ? 1 : 2 * ((tiles + 2 * GEMM_CUS - 1) / (2 * GEMM_CUS));
-    const bool six = format == PK6;
-    int shortest = six ? 1024 : 2560;
-    if (rounds == 1) shortest = six ? 384 : 512;
-    else if (2 * rounds <= byte_rounds) shortest = 0;
-    else if (rounds < byte_rounds) shortest = six ? 896 : 1408;
-    return K >= shortest ? format : PK_NONE;
+    if (rounds > 1 && 2 * rounds <= byte_rounds) return format;
+    return K >= limits[rounds == 1 ? 0 : rounds < byte_rounds ? 1 : 2][format == PK6][K % 16 == 0 ? 0 : K % 4 == 0 ? 1 : 2] ? format : PK_NONE;
 }
 
 int launch_int8_terms(int M, int N, int K, const int8_t* const A[2], const float* const amaxA[2], const int8_t* const B[2],

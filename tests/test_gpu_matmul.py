@@ -328,7 +328,9 @@ def test_six_bit_sums_next_to_their_limit(M, N, bits, K, turn):
                          [(3100, 2901, 200, 4), (4096, 4096, 320, 4), (3100, 2901, 200, 8), (4096, 4096, 320, 8)] +
                          # tall operands on both sides of the limits up to which their rows stay bytes
                          [(16383, 33, 65, 8), (16385, 33, 65, 8), (16390, 768, 40, 8), (16390, 769, 40, 8), (16391, 20, 512, 8),
-                          (16391, 20, 513, 8), (16390, 512, 40, 4), (16390, 513, 40, 4), (16391, 20, 384, 4), (16391, 20, 385, 4)])
+                          (16391, 20, 513, 8), (16390, 512, 40, 4), (16390, 513, 40, 4), (16391, 20, 384, 4), (16391, 20, 385, 4),
+                          (16391, 20, 516, 8), (16391, 20, 388, 4), (16390, 12, 15, 8), (65536, 17, 383, 8), (65537, 64, 129, 4), (65537, 65, 129, 4),
+                          (3071, 30, 4100, 8), (3073, 64, 4100, 8), (3073, 385, 4100, 4), (3073, 256, 8196, 8), (3073, 257, 8196, 8), (3073, 65, 8196, 4), (16385, 33, 4097, 8)])
 def test_packed_codes_without_a_factorization(M, N, K, bits):
     import paper_2409_18772_amd as L
     dA, dB = to_dev(wl.random_matrix("normal", M, K, seed=93)), to_dev(wl.random_matrix("uniform_pm1", K, N, seed=94))

@@ -199,11 +199,14 @@ def test_joint_quantization_equals_the_separate_calls(M, N, K, pad, terms):
                                                        (1, 300, 333, 4, 1.0, 0.25, 5), (1100, 600, 5000, 5, 1.0, 0.0, 0), (2100, 1900, 320, 2, 1.0, 0.0, 0),
                                                        (700, 800, 8195, 8, 0.75, 0.5, 1), (800, 700, 16384, 8, 1.0, 0.0, 0),
                                                        (700, 800, 8195, 4, 0.75, 0.5, 1), (800, 700, 16384, 4, 1.0, 0.0, 0)] +
-                         # both sides of the shortest reductions that are packed: one round of tiles, fewer rounds, as many, half as many
-                         [(127, 129, 511, 8, 0.75, 0.5, 3), (127, 129, 575, 8, 0.75, 0.5, 3), (130, 5, 513, 6, 1.0, 0.5, 0),
-                          (129, 127, 383, 4, 1.0, 0.0, 0), (129, 127, 385, 4, 1.0, 0.0, 0), (2830, 2840, 1407, 8, 1.0, 0.25, 0),
-                          (2830, 2840, 1409, 8, 1.0, 0.25, 0), (2830, 2840, 897, 4, 1.0, 0.0, 1), (2100, 2200, 1100, 4, -1.0, 0.0, 0),
-                          (2100, 2200, 2600, 8, 1.0, 0.0, 0), (100, 50000, 65, 8, 1.0, 0.0, 0), (100, 50000, 33, 4, 1.0, 0.5, 2)])
+                         # both sides of the shortest reductions that are packed, of 16, 4 and 1: one round of tiles, fewer rounds, as many,
+                         # half as many
+                         [(127, 129, 511, 8, 0.75, 0.5, 3), (127, 129, 512, 8, 0.75, 0.5, 3), (127, 129, 496, 8, 0.75, 0.5, 3), (130, 5, 513, 6, 1.0, 0.5, 0),
+                          (130, 5, 252, 6, 1.0, 0.5, 0), (130, 5, 260, 6, 1.0, 0.5, 0), (129, 127, 383, 4, 1.0, 0.0, 0), (129, 127, 400, 4, 1.0, 0.0, 0),
+                          (129, 127, 188, 4, 1.0, 0.0, 0), (129, 127, 17, 4, 1.0, 0.0, 0), (2830, 2840, 1407, 8, 1.0, 0.25, 0),
+                          (2830, 2840, 1408, 8, 1.0, 0.25, 0), (2830, 2840, 700, 8, 1.0, 0.25, 0), (2830, 2840, 351, 8, 1.0, 0.25, 0),
+                          (2830, 2840, 289, 4, 1.0, 0.0, 1), (2830, 2840, 544, 4, 1.0, 0.0, 0), (2100, 2200, 1024, 4, -1.0, 0.0, 0), (2100, 2200, 700, 4, -1.0, 0.0, 0),
+                          (2100, 2200, 641, 8, 1.0, 0.0, 0), (2100, 2200, 2544, 8, 1.0, 0.0, 0), (100, 50000, 65, 8, 1.0, 0.0, 0), (100, 50000, 33, 4, 1.0, 0.5, 2)])
 def test_four_products_in_one_tile_give_the_bits_of_one_launch_each(M, N, K, bits, alpha, beta, pad):
     """Each product's sums are exact integers, and the steps, alpha and the running total round in the same places."""
     import torch
