@@ -808,7 +808,8 @@ __global__ __launch_bounds__(512, 2) void panels_kernel(PanelArgs a) {
     constexpr int RP = NT * 16, AHEAD = NT == 1 ? 3 : 2;
     __shared__ float red[PANEL_WAVES * 32 * RP];        // [wave][32 rows][RP]
     __shared__ float xg[RP * (RP + 1)];                 // X Gamma
-    __shared__ float own[RB][RP * 33];                  // right: 32 columns of Zt, [u][row]; left: 32 rows of U Sig
+    constexpr int OWN = 36;                             // (aligned groups of four rows)
+    __shared__ __align__(16) float own[RB][RP * OWN];   // right: 32 columns of Zt, [u][row]; left: 32 rows of U Sig
     __shared__ float step[32 * RB];
     const bool right = (int)blockIdx.x < a.nbR;         // (the right panel has more to do)
     const int blk = right ? blockIdx.x : blockIdx.x - a.nbR;
@@ -838,7 +839,7 @@ __global__ __launch_bounds__(512, 2) void panels_kernel(PanelArgs a) {
                 if (right) {
                     const int u = e >> 5, j = r0 + (e & 31);
                     const float z = a.Zt[(size_t)min(u, r - 1) * a.N + min(j, a.N - 1)];
-                    own[b][u * 33 + (e & 31)] = u < r && j < a.N ? z : 0.f;
+                    own[b][u * OWN + (e & 31)] = u < r && j < a.N ? z : 0.f;
                 } else if (e < 32 * r) {
                     own[b][e] = a.U[(size_t)min(r0 + e / r, a.M - 1) * a.ldu + e % r] * a.Sig[e % r];
                 }
@@ -914,27 +915,59 @@ __global__ __launch_bounds__(512, 2) void panels_kernel(PanelArgs a) {
 #pragma unroll
                 for (int v = 0; v < 4; ++v) red[(wave * 32 + 16 * t + 4 * kq + v) * RP + 16 * nt + li] = acc[b][t][nt][v];
         __syncthreads();
-        const int n = min(32, rows - r0) * R2P;
+        const int nrows = min(32, rows - r0);
         float* const out = (right ? a.Rp : a.Lp) + (size_t)r0 * R2P;
-        for (int e = tid; e < n; e += 512) {
-            const int row = e / R2P, c = e - row * R2P;
-            const int pc = right ? c : c - r;       // column of the product, if any
-            float v = 0.f;
-            if (pc >= 0 && pc < r) {
+        // A thread takes GROUP rows of a column, so that an entry of X Gamma read from LDS serves as many products, and both halves of
+        // the panel rows.  A thread per entry of them, with two LDS reads a product (which bound wide panels) and a division for the row /
+        // this, lrqmm_gemm, 8 bits, us: rank 32 2000^3 43.2 / 41.2, 16384 x 100 x 252 27.1 / 23.9, rank 64 300^3 30.8 / 24.4, 4096^3 139 / 132,
+        // 100 x 100352 x 100 245 / 158, 100352 x 100 x 100 127 / 112, rank 80 600 x 41152 x 252 228 / 188.  Four rows at two tiles: no better.
+        constexpr int GROUP = NT <= 2 ? NT : 4;
+        for (int e = tid; e < 32 / GROUP * RP; e += 512) {
+            const int c = e % RP, i0 = e / RP * GROUP;
+            if (c >= r) continue;
+            float v[GROUP], z[GROUP];
 #pragma unroll
-                for (int w = 0; w < PANEL_WAVES; ++w) v += red[(w * 32 + row) * RP + pc];
-                v *= step[32 * b + row];
-                if (right) {
-                    for (int u0 = 0; u0 < RP; u0 += 8) {       // rows u >= r of Zt are zero
+            for (int i = 0; i < GROUP; ++i) {
+                v[i] = 0.f;
 #pragma unroll
-                        for (int t = 0; t < 8; ++t) v = fmaf(xg[pc * (RP + 1) + u0 + t], own[b][(u0 + t) * 33 + row], v);
+                for (int w = 0; w < PANEL_WAVES; ++w) v[i] += red[(w * 32 + i0 + i) * RP + c];
+                v[i] *= step[32 * b + i0 + i];
+            }
+            if (right) {
+                auto z_of = [&](int u) {
+                    const float* const p = &own[b][u * OWN + i0];
+                    if constexpr (GROUP == 1) z[0] = *p;
+                    else if constexpr (GROUP == 2) { const float2 t = *reinterpret_cast<const float2*>(p); z[0] = t.x; z[1] = t.y; }
+                    else { const float4 t = *reinterpret_cast<const float4*>(p); z[0] = t.x; z[1] = t.y; z[2] = t.z; z[3] = t.w; }
+                };
+#pragma unroll 1                        // unrolled, its loads of X Gamma leave the loop over e and spill
+                for (int u0 = 0; u0 < RP; u0 += 8) {       // rows u >= r of Zt are zero
+#pragma unroll
+                    for (int t = 0; t < 8; ++t) {
+                        const float x = xg[c * (RP + 1) + u0 + t];
+                        z_of(u0 + t);
+#pragma unroll
+                        for (int i = 0; i < GROUP; ++i) v[i] = fmaf(x, z[i], v[i]);
                     }
                 }
-            } else if (c < 2 * r) {
-                v = right ? a.Gam[c - r] * own[b][(c - r) * 33 + row] : own[b][row * r + c];
+                z_of(c);
+#pragma unroll
+                for (int i = 0; i < GROUP; ++i) z[i] *= a.Gam[c];
+            } else {
+#pragma unroll
+                for (int i = 0; i < GROUP; ++i) z[i] = own[b][(i0 + i) * r + c];
             }
-            out[e] = v;
+            float* const o = out + i0 * R2P + c;
+            const int product = right ? 0 : r, factor = r - product;
+#pragma unroll
+            for (int i = 0; i < GROUP; ++i)
+                if (i0 + i < nrows) {
+                    o[i * R2P + product] = v[i];
+                    o[i * R2P + factor] = z[i];
+                }
         }
+        const int pad = R2P - 2 * r;
+        for (int e = tid; e < nrows * pad; e += 512) out[e / pad * R2P + 2 * r + e % pad] = 0.f;
     }
 }
 
@@ -1018,12 +1051,8 @@ __global__ __launch_bounds__(512, 4) void panels_rows_kernel(PanelArgs a) {
 // order, as in panels_kernel: the same bits.  That one holds the registers of a CU with one workgroup, whose loads, sums through
 // LDS and stores stand behind one another for every 64 rows.
 //
-// lrqmm_gemm, 8 bits, two launches as above / panels_kernel / this, us: 100352 x 64 rank 8 K = 700 58.4 / 72.5 / 52.0, 1152 72.0 / 85.2 / 63.7,
-// rank 24 K = 64 51.9 / 65.4 / 35.3, 576 79.2 / 85.9 / 56.2, 2304 177 / 170 / 126, rank 48 K = 576 115 / 114 / 85; 64 x 100352 rank 24 K = 576 122 /
-// 129 / 79, rank 48 191 / 206 / 118 (few reads of Zt per row).  Where a workgroup's 256 rows leave CUs idle, the copies of the planes into
-// LDS, which nothing covers then, make it the slower form (tall_panels): 32768 x 64 rank 8 K = 1152 38.5 / 39.0 / 37.1, rank 24
-// K = 320 34.9 / 34.4 / 31.8, 1152 52.2 / 48.8 / 51.2, rank 48 K = 576 60.2 / 52.5 / 61.3; 50000 x 64 rank 24 K = 1152 63.4 / 66.3 / 58.7, 4096 143 / 135 /
-// 142, rank 48 K = 64 47.9 / 55.2 / 44.3, 320 61.0 / 64.6 / 59.8, 576 69.2 / 70.0 / 69.4, 1152 86.8 / 87.5 / 89.9; 64 x 32768 rank 48 K = 1152 99.9 / 91.9 / 90.1, 4096 200 / 154 / 199.
+// lrqmm_gemm, 8 bits, panels_kernel / this, us: 100352 x 64 rank 8 K = 1152 82.5 / 63.3, rank 24 K = 64 58.6 / 35.0, 576 78.9 / 55.8, 2304 162 / 126,
+// rank 48 K = 576 99.8 / 82.9; 64 x 100352 rank 24 K = 576 112 / 79.0, rank 48 152 / 119 (few reads of Zt per row).  tall_panels picks.
 constexpr int tall_chunk(int nt, int pl) { return (nt == 3 ? 60 : 72) / (2 * nt * pl); }       // k blocks of planes in LDS
 template <int FMT, int NT, int PL>
 __global__ __launch_bounds__(512, 4) void panels_tall_kernel(PanelArgs a) {
@@ -1697,13 +1726,25 @@ int launch_resid_mul_t(const PassOperand* op, int nop, QuantParams q, int LP, hi
     return LRQMM_ERR_UNSUPPORTED;
 }
 
+// Where a workgroup's 256 rows leave CUs idle or with one workgroup, the copies of the planes into LDS, which nothing covers then, make
+// panels_tall_kernel the slower form, the more so the more chunks of planes there are.  Of tall left panels it is the slower one up to more
+// rows when the right operand has enough of them for whole workgroups, whose waves then each form 32 right panel rows, the longest
+// part of such a launch.  lrqmm_gemm, 8 bits, panels_kernel / panels_tall_kernel, us, M x N:
+//   rank 8    41152 x 600 K = 1152 97.9 / 99.2, 49152 x 64 48.5 / 41.7, 50000 x 600 133 / 128
+//   rank 24   32768 x 64 K = 252 29.8 / 28.5, 576 36.8 / 38.6, 49152 x 64 46.8 / 42.9, 1152 59.2 / 56.3; 50000 x 300 K = 100 89.3 / 85.4
+//   rank 32   41152 x 600 K = 252 104 / 112, 50000 x 600 141 / 145, 576 160 / 165, 65536 x 600 172 / 172, 131072 x 600 357 / 333
+//   rank 40   57344 x 128 K = 100 59.0 / 54.4; rank 48 57344 x 64 K = 252 54.5 / 56.7, 65536 x 600 137 / 150, 98304 x 200 126 / 123,
+//             98304 x 600 222 / 229, 131072 x 600 296 / 288
+//   right     64 x 32768 rank 24 K = 252 39.6 / 35.9, 1152 56.0 / 56.3, 2304 77.0 / 82.4, rank 48 K = 252 54.8 / 60.1; 64 x 49152 rank 48 K = 576
+//             83.6 / 81.2, 2304 133 / 147, 64 x 65536 159 / 157
 static bool tall_panels(int M, int N, int nkb, int nt, int planes) {
     if (nt > 3) return false;
     const int chunks = ceil_div(nkb, tall_chunk(nt, planes));
-    if (N >= 49152 || (N >= 32768 && chunks * nt <= 12)) return true;
-    if (M >= 65536) return true;
-    if (M >= 49152) return chunks * nt <= (nt == 3 ? 6 : 12);
-    return M >= 32768 && (nt == 1 ? chunks <= 4 : nt == 2 && chunks == 1);
+    if (N >= 49152) return nt < 3 || chunks <= 6 || N >= 65536;
+    if (N >= 32768) return nt < 3 && chunks <= 3;
+    if (nt == 1) return M >= 65536 || (M >= 49152 && chunks <= 12);
+    if (nt == 2) return M >= 65536 || (M >= 49152 && (N <= 128 || nkb <= 2)) || (M >= 32768 && N <= 128 && chunks == 1);
+    return M >= 98304 || (M >= 57344 && N <= 128 && chunks == 1);
 }
 
 int launch_panels(const PanelArgs& in, int RP, int planes, int packed, hipStream_t st) {

@@ -261,7 +261,7 @@ PACKED += [(127, 97, 191, 8, 20, 8), (129, 160, 193, 6, 17, 0), (33, 34, 35, 8, 
            (1537, 1021, 1100, 8, 24, 8), (2080, 2049, 320, 8, 17, 0), (3100, 2900, 200, 8, 36, 0), (4096, 4096, 1024, 8, 32, 8),
            (64, 96, 131071, 8, 17, 0)]
 # Tall operands, whose panels have a kernel of their own: one to three tiles of factor columns, one chunk of planes and more, both formats.
-PACKED += [(32801, 40, 833, 8, 12, 8), (33000, 45, 321, 4, 20, 8), (65600, 60, 200, 8, 40, 8), (65537, 49, 130, 3, 33, 8),
+PACKED += [(49201, 40, 833, 8, 12, 8), (98310, 50, 200, 8, 40, 8), (32801, 40, 833, 8, 12, 8), (33000, 45, 321, 4, 20, 8), (65600, 60, 200, 8, 40, 8), (65537, 49, 130, 3, 33, 8),
            (40, 32802, 833, 4, 12, 8), (70, 49153, 321, 8, 41, 8)]
 
 

@@ -38,6 +38,7 @@ CASES = [
     ("c3_4096_int4_r32_outliers", 333, 517, 260),     # ragged: guarded kernels
     ("c2_4096_int8_r16", 33000, 64, 208),             # tall: panels of a kernel of their own
     ("c3_4096_int4_r32_outliers", 65600, 80, 400),
+    ("c2_4096_int8_r16", 49200, 64, 208),
 ]
 
 

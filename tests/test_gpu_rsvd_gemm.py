@@ -423,15 +423,20 @@ def test_gemm_panel_widths_on_small_tiles(M, N, K, rank):
 # Panels: rows of one workgroup short and over (32, 64 rows), k blocks that eight waves do not share evenly or that leave waves idle,
 # every width of the factors; 64 rows a workgroup (16384 rows and more, both sides of the limit; 65 columns and more keep 32); tall operands with short rows in
 # the persistent kernel, on both sides of its limits in rows, columns of the factor and K; each operand as the tall one; the tall
-# kernel (from 32768, 49152 and 65536 rows on, by the width): one chunk of planes, a last one of one k block and a whole one, rows and
-# columns that end early, K below one load, a wave without rows.
+# kernel (from 32768, 49152, 57344, 65536 and 98304 rows on, by the width and the other operand's rows) and its limits: one chunk of planes, a
+# last one of one k block and a whole one, rows and columns that end early, K below one load, a wave without rows.  Right panels whose
+# groups of rows of a column end early, at every width of a group.
 @pytest.mark.parametrize("M,N,K,bits,rank", [(33, 31, 65, 8, 1), (65, 97, 513, 8, 16), (64, 40, 577, 4, 17), (130, 95, 1100, 8, 33), (100, 129, 700, 4, 50),
                                              (96, 161, 2000, 8, 80), (16289, 64, 700, 8, 12), (16353, 30, 700, 8, 12), (16390, 70, 130, 4, 40),
                                              (17000, 90, 513, 4, 80), (16385, 70, 130, 8, 64), (16385, 70, 130, 8, 65), (16383, 60, 576, 4, 8), (16385, 61, 575, 4, 8), (20000, 33, 640, 8, 16),
                                              (20001, 20, 641, 8, 3), (50, 16401, 129, 4, 5), (70, 17001, 90, 8, 64),
                                              (32768, 40, 769, 8, 3), (32801, 24, 641, 4, 16), (33025, 20, 15, 8, 10), (33000, 50, 380, 8, 20), (49153, 41, 385, 8, 32),
                                              (49500, 60, 193, 4, 33), (49200, 60, 385, 8, 40), (65537, 50, 193, 8, 48), (65600, 48, 577, 4, 40), (66001, 30, 1601, 8, 9),
-                                             (30, 32769, 1089, 8, 13), (40, 32999, 400, 4, 31), (60, 49155, 449, 8, 45)])
+                                             (30, 32769, 1089, 8, 13), (40, 32999, 400, 4, 31), (60, 49155, 449, 8, 45),
+                                             (49153, 41, 769, 8, 3), (49201, 24, 641, 4, 16), (49155, 20, 15, 8, 10), (49160, 129, 128, 8, 20), (40000, 129, 130, 8, 20),
+                                             (98310, 60, 193, 4, 33), (98305, 50, 385, 8, 48), (57345, 128, 192, 8, 40), (57350, 129, 192, 8, 40),
+                                             (37, 16403, 70, 8, 24), (55, 16405, 129, 4, 50), (73, 16407, 80, 8, 72), (31, 1023, 130, 8, 31),
+                                             (66, 1025, 70, 4, 47), (65, 1027, 65, 8, 63), (81, 1026, 90, 8, 79), (40, 32999, 1217, 8, 31), (60, 49155, 1217, 8, 45)])
 def test_gemm_panels(M, N, K, bits, rank):
     """Sampled rows against float64.  A term of the products is exact, the planes carry the factors to 2^-27 and a sum of K terms in
     float32 is off by less than K 2^-24 of the terms' absolute sum, of the order of sqrt(K) 2^-24 in practice: 3e-6, as above."""
