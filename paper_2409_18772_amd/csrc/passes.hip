@@ -827,7 +827,7 @@ __global__ __launch_bounds__(512, 2) void panels_kernel(PanelArgs a) {
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) acc[b][t][nt] = (v4f){0.f, 0.f, 0.f, 0.f};
     // What the panel rows need besides the products: loaded beside the first blocks, so that behind the loop nothing waits for memory
-    // (loaded there, at 4096^3: r = 32 18.6 us, r = 16 12.5).
+    // (loaded there / so, at 4096^3 and with one panel entry a thread behind the sums: r = 32 18.6 / 17.8 us, r = 16 12.5 / 11.5; now 15.4, 10.5).
     auto stage = [&] {
         if (right) stage_x_gamma(a, RP, xg, tid, 512);
 #pragma unroll
