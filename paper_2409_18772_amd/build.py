@@ -15,8 +15,9 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "liblrqmm.so")
-SOURCES = ["api.hip", "quantize.hip", "sketch.hip", "passes.hip", "orth.hip", "gemm.hip"]
+SOURCES = ["api.hip", "quantize.hip", "sketch.hip", "passes.hip", "passes_full_n.hip", "passes_full_t.hip", "orth.hip", "gemm.hip"]
 HEADERS = [os.path.join(CSRC, "common.h"), os.path.join(CSRC, "kernels.h"), os.path.join(CSRC, "sketch.h"),
+           os.path.join(CSRC, "passes_full.h"),
            os.path.join(HERE, "..", "include", "lrqmm.h")]
 
 FLAGS = [
@@ -51,7 +52,7 @@ def build(verbose: bool = True, incremental: bool = False, extra_flags=()) -> st
                  and os.path.getmtime(obj) > max(os.path.getmtime(src), newest_header))
         if not fresh:
             jobs.append([hipcc] + FLAGS + list(extra_flags) + ["-c", src, "-o", obj])
-    with ThreadPoolExecutor(max_workers=min(6, max(1, len(jobs)))) as pool:
+    with ThreadPoolExecutor(max_workers=min(8, max(1, len(jobs)))) as pool:
         list(pool.map(lambda c: _run(c, verbose), jobs))
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC"] + objs + ["-o", LIB], verbose)
     return LIB

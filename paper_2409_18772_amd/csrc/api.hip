@@ -4,6 +4,7 @@
 // caller's buffers and workspace.
 #include "kernels.h"
 #include <cstdio>
+#include <algorithm>
 #include <cstdlib>
 #include <functional>
 #include <memory>
@@ -38,6 +39,7 @@ inline int pad_to(int x, int m) { return (x + m - 1) / m * m; }
 struct RsvdWs {
     float *lam, *s, *Wc, *Yr, *partial;
     double *gpart, *gram, *Ur, *Mv;
+    char* steps;
 };
 
 // Every region of carve_rsvd and carve_matmul is at least as large for a larger problem, so that one workspace, sized for the
@@ -48,6 +50,7 @@ size_t carve_rsvd(Arena& a, int rows, int cols, int axis, int LP, int rank, Rsvd
     // (the one-read quantization kernel for row-quantized operands leaves one Gram partial per workgroup)
     int nb = gram_blocks_most(rows > cols ? rows : cols, LP);
     if (axis == LRQMM_AXIS_ROW && LP == 16 && quant_sketch_rows_blocks(rows) > nb) nb = quant_sketch_rows_blocks(rows);
+    nb = std::max(nb, full_blocks_most(rows > cols ? rows : cols, LP));
     RsvdWs t;
     t.lam = a.take<float>(npad);
     t.s = a.take<float>(npad);
@@ -58,6 +61,7 @@ size_t carve_rsvd(Arena& a, int rows, int cols, int axis, int LP, int rank, Rsvd
     t.gram = a.take<double>((size_t)LP * LP);
     t.Ur = a.take<double>((size_t)LP * rank);
     t.Mv = a.take<double>((size_t)LP * rank);
+    t.steps = a.take<char>(steps_bytes(rows > cols ? rows : cols, LP));
     if (w) *w = t;
     return a.off;
 }
@@ -309,9 +313,17 @@ static int make_factor(Factor* f, const float* X, int ldx, int rows, int cols, i
     Arena a(workspace);
     if (carve_rsvd(a, rows, cols, axis, LP, rank, &f->w) > workspace_bytes) return LRQMM_ERR_WORKSPACE;
     f->op = {X, ldx, rows, cols, axis, f->w.lam, f->w.s, f->w.Wc, f->w.Yr, f->w.partial, amax, codes,
-             plan_pass_n(rows, cols, LP), plan_pass_t(rows, cols, LP)};
+             plan_pass_n(rows, cols, LP), plan_pass_t(rows, cols, LP), f->w.steps, f->w.gpart,
+             pass_full_ranges(false, rows, cols, ldx, LP), pass_full_ranges(true, rows, cols, ldx, LP)};
     f->U = U; f->Sigma = Sigma; f->Vt = Vt;
     return LRQMM_OK;
+}
+
+// The partial results of the last transposed product: a single one where the pass leaves none.
+struct TPartials { const float* p; int splits; };
+static TPartials t_partials(const Factor& f, int planes) {
+    if (planes >= 2 && f.op.ft == 1) return {f.op.W, 1};
+    return {f.op.partial, planes >= 2 && f.op.ft > 1 ? f.op.ft : f.op.pt.splits};
 }
 
 // How the first residual product of a factorization is formed.
@@ -334,30 +346,54 @@ static void factor_launches(LaunchList& ops, const Factor* factors, int n, First
     auto p = std::make_shared<Pair>();
     for (int i = 0; i < n; ++i) { p->f[i] = factors[i]; p->op[i] = factors[i].op; }
     const int ell = rank + oversample, LP = pad_to(ell, 16);
-    // Gram jobs of the tall factors: of the N pass's result (rows x LP) or of the T pass's (cols x LP)
+    // A product and the Gram partials of its result, and then, unless it is the last, Q = orth(result) in place: Gram (float64),
+    // Cholesky and Q = Y T.  An operand whose pass leaves no partial results (launch_pass_full) needs its other factor in the order
+    // of steps, from the orthonormalization before.
     struct Jobs { GramJob g[2]; };
-    auto jobs_of = [=](bool t_type) {
+    auto in_steps = [=](bool t_type, int pl, int i) { return pl >= 2 ? (t_type ? p->op[i].ft : p->op[i].fn) : 0; };
+    auto product = [&](bool t_type, int pl) {
         Jobs j = {};
+        Pair part[2];                       // [1]: the operands whose pass takes the order of steps
+        int np[2] = {0, 0};
         for (int i = 0; i < n; ++i) {
             const Factor& f = p->f[i];
             const PassOperand& o = f.op;
-            j.g[i] = {f.w.partial, t_type ? o.pt.splits : o.pn.splits, t_type ? o.cols : o.rows, t_type ? o.W : o.Y,
-                      f.w.gpart, f.w.gram, 0, 0};
+            const int rows = t_type ? o.cols : o.rows, ranges = in_steps(t_type, pl, i);
+            part[ranges > 0].op[np[ranges > 0]++] = o;
+            j.g[i] = {f.w.partial, ranges > 0 ? ranges : (t_type ? o.pt.splits : o.pn.splits), rows, t_type ? o.W : o.Y, f.w.gpart, f.w.gram,
+                      ranges == 1 ? full_blocks(rows, LP) : 0, 0};
+        }
+        for (int k = 0; k < 2; ++k) {
+            if (np[k] == 0) continue;
+            const Pair a = part[k];
+            const int na = np[k];
+            if (k) ops.push_back([=] { return (t_type ? launch_pass_full_t : launch_pass_full_n)(a.op, na, q, LP, st, pl); });
+            else ops.push_back([=] { return (t_type ? launch_resid_mul_t(a.op, na, q, LP, st, pl)
+                                                    : launch_resid_mul_n(a.op, na, q, LP, false, st, pl)); });
         }
         return j;
     };
-    // Q = orth(sum of the partials) in place: Gram (float64), Cholesky and Q = Y T
-    auto gram_to_basis = [&](const Jobs& j) {
+    auto reduce = [&](const Jobs& j) {      // of the partial results
+        Jobs a = {};
+        int na = 0;
+        for (int i = 0; i < n; ++i) if (j.g[i].blocks == 0) a.g[na++] = j.g[i];
+        if (na > 0) ops.push_back([=] { return launch_reduce_gram(a.g, na, LP, st); });
+    };
+    // next_t, next_pl: the product that takes Q
+    auto gram_to_basis = [&](Jobs j, bool next_t, int next_pl) {
         bool sums = true;           // few partials: added where they are used
-        for (int i = 0; i < n; ++i) sums = sums && orth_apply_sums(j.g[i].blocks > 0 ? j.g[i].blocks : gram_blocks(j.g[i].n, LP), LP);
+        for (int i = 0; i < n; ++i) {
+            sums = sums && orth_apply_sums(j.g[i].blocks > 0 ? j.g[i].blocks : gram_blocks(j.g[i].n, LP), LP);
+            if (in_steps(next_t, next_pl, i)) { j.g[i].steps = p->f[i].w.steps; j.g[i].steps_fmt = steps_format(LP, next_pl); }
+        }
         if (!sums) ops.push_back([=] { return launch_gram_sum(j.g, n, LP, st); });
         ops.push_back([=] { return launch_orth_apply(j.g, n, ell, LP, sums, st); });
     };
-    auto orth = [&](bool t_type) {
-        const Jobs j = jobs_of(t_type);
-        ops.push_back([=] { return launch_reduce_gram(j.g, n, LP, st); });
-        gram_to_basis(j);
+    auto orth = [&](const Jobs& j, bool next_t, int next_pl) {
+        reduce(j);
+        gram_to_basis(j, next_t, next_pl);
     };
+    const int t_first = power_iters > 0 ? planes : planes_last;      // planes of the first transposed product
     // Y = R Omega
     if (first == FirstPass::one_read) {
         const Factor f = p->f[0];
@@ -365,36 +401,41 @@ static void factor_launches(LaunchList& ops, const Factor* factors, int n, First
             return launch_quant_sketch_rows(f.op.X, f.op.ldx, f.op.rows, f.op.cols, q, f.op.W, LP, f.op.Y, f.w.gpart,
                                             one_read_amax, f.w.lam, f.w.s, f.op.codes, st);
         });
-        Jobs j = jobs_of(false);
-        j.g[0].blocks = quant_sketch_rows_blocks(f.op.rows);
-        gram_to_basis(j);
+        Jobs j = {};
+        j.g[0] = {nullptr, 0, f.op.rows, f.op.Y, f.w.gpart, f.w.gram, quant_sketch_rows_blocks(f.op.rows), 0};
+        gram_to_basis(j, true, t_first);
     } else {
-        ops.push_back([=] { return launch_resid_mul_n(p->op, n, q, LP, first == FirstPass::quantize, st, planes_first, packed); });
-        orth(false);
+        const bool quantizing = first == FirstPass::quantize;
+        // (the sketch is not in the order of steps)
+        Jobs j = {};
+        for (int i = 0; i < n; ++i) {
+            const Factor& f = p->f[i];
+            j.g[i] = {f.w.partial, f.op.pn.splits, f.op.rows, f.op.Y, f.w.gpart, f.w.gram, 0, 0};
+        }
+        ops.push_back([=] { return launch_resid_mul_n(p->op, n, q, LP, quantizing, st, planes_first, packed); });
+        orth(j, true, t_first);
     }
     for (int it = 0; it < power_iters; ++it) {
         // Z = orth(R^T Q); Q = orth(R Z)
-        ops.push_back([=] { return launch_resid_mul_t(p->op, n, q, LP, st, planes); });
-        orth(true);
-        ops.push_back([=] { return launch_resid_mul_n(p->op, n, q, LP, false, st, planes); });
-        orth(false);
+        orth(product(true, planes), false, planes);
+        orth(product(false, planes), true, it + 1 < power_iters ? planes : planes_last);
     }
     // B^T = R^T Q (cols x l), its Gram B B^T, small SVD, U = Q U', V = B^T U' / sigma
-    ops.push_back([=] { return launch_resid_mul_t(p->op, n, q, LP, st, planes_last); });
+    const Jobs j = product(true, planes_last);
     if (stop_at_basis) return;
     if (basis_suffices) {
         ops.push_back([=] {
             BasisJob bj[2];
             for (int i = 0; i < n; ++i) {
                 const Factor& f = p->f[i];
-                bj[i] = {f.op.partial, f.op.pt.splits, f.op.cols, f.op.Y, f.op.rows, f.U, f.Sigma, f.Vt};
+                const TPartials t = t_partials(f, planes_last);
+                bj[i] = {t.p, t.splits, f.op.cols, f.op.Y, f.op.rows, f.U, f.Sigma, f.Vt};
             }
             return launch_take_basis(bj, n, LP, rank, st);
         });
         return;
     }
-    const Jobs j = jobs_of(true);
-    ops.push_back([=] { return launch_reduce_gram(j.g, n, LP, st); });
+    reduce(j);
     ops.push_back([=] { return launch_gram_sum(j.g, n, LP, st); });
     if (svd_index) *svd_index = ops.size();         // the GPU is nearly idle from this launch to its end
     ops.push_back([=] {
@@ -823,7 +864,8 @@ int lrqmm_matmul_ex(int M, int N, int K, int bits, int rank, int oversample, int
             GemmWs g;
             Arena ga(w.sub);
             carve_gemm(ga, M, N, K, rank, &g);
-            rc = launch_basis_panels({f[0].op.partial, f[1].op.partial, f[1].op.Y, f[0].op.pt.splits, f[1].op.pt.splits, N, K, rank,
+            const TPartials ta = t_partials(f[0], pl_last), tb = t_partials(f[1], pl_last);
+            rc = launch_basis_panels({ta.p, tb.p, f[1].op.Y, ta.splits, tb.splits, N, K, rank,
                                       g.Wf, g.Vf, w.Zt, g.X, w.Sig, w.Gam}, pst);
             ready = {w.Aq, w.BqT, g.Wf, g.Vf, f[0].op.Y, w.Sig, f[0].w.s, f[1].w.s, g.X, w.Gam, w.Zt, g.Lp, g.Rp, M, N, K, rank,
                      pad_to(2 * rank, 8), basis_slices(K), LP};

@@ -79,7 +79,17 @@ struct PassOperand {
     const float* amax;  // group maxima and codes, used by the quantizing pass
     int8_t* codes;
     PassPlan pn, pt;
+    void* steps;        // for passes_full_*.hip: W (N pass) or Y (T pass) in the order of its steps
+    double* gpart;      // ... Gram partials of the result
+    int fn, ft;         // pass_full_ranges of the N pass, the T pass
 };
+// A tall operand of a residual product in the order of the matrix cores' operands, zero padded, lane 16 g + c holding rows 4 g + (e & 3)
+// + 16 (e >> 2) (e < 8) of column c of a 32-row step: STEPS_PLANES [step][column tile of 16][plane][lane][8], three bfloat16 planes;
+// STEPS_FLOAT [step][lane][8] float32, one column tile (the passes on the float32 matrix cores, see launch_resid_mul_n).
+enum { STEPS_NONE = 0, STEPS_PLANES = 1, STEPS_FLOAT = 2 };
+#define STEP_PIECE 512
+static inline size_t steps_bytes(int n, int LP) { return (size_t)ceil_div(n, 32) * (LP / 16) * 3 * STEP_PIECE * sizeof(uint16_t); }
+static inline int steps_format(int LP, int planes) { return LP == 16 && planes == 3 ? STEPS_FLOAT : STEPS_PLANES; }
 // Both passes take one operand, or two of different axes in one launch.
 // planes: bfloat16 planes per float32 operand in the matrix-core products (3: float32 accuracy, the default;
 // 2: relative error 2^-16 per product; 1: plain bfloat16 operands) -- the reduced-precision compensation of the
@@ -93,6 +103,15 @@ int launch_resid_mul_n(const PassOperand* op, int nop, QuantParams q, int LP, bo
                        int planes = 3, int packed = PK_NONE);
 // T pass: partial[s][cols][LP] = R[chunk s, :]^T . Y[chunk s, :].
 int launch_resid_mul_t(const PassOperand* op, int nop, QuantParams q, int LP, hipStream_t st, int planes = 3);
+// ---- passes_full_n.hip, passes_full_t.hip ----
+// The same products, the other factor in the order of steps, for the operands with fn > 0 (N pass), ft > 0 (T pass): in that many
+// ranges of the reduction, a single one without partial results: Y (rows x LP) = R W, or W (cols x LP) = R^T Y, and
+// full_blocks(results, LP) Gram partials of it.  One operand or two of different axes.
+int pass_full_ranges(bool t_type, int rows, int cols, int ldx, int LP);     // 0: the products above
+int full_blocks(int n, int LP);
+int full_blocks_most(int n, int LP);        // of any result of up to n rows
+int launch_pass_full_n(const PassOperand* op, int nop, QuantParams q, int LP, hipStream_t st, int planes = 3);
+int launch_pass_full_t(const PassOperand* op, int nop, QuantParams q, int LP, hipStream_t st, int planes = 3);
 // Row quantization and the sketch product from one read, for operands quantized by rows whose rows are short
 // (cols <= 576, a multiple of 16) and sketches padded to 16 columns: writes the row maxima amax[rows], the step
 // vectors, the codes (rows x cols), Y = R.W (rows x 16) and gpart[quant_sketch_rows_blocks(rows)][16][16], the
@@ -139,6 +158,8 @@ struct GramJob {
     double* gram;               // LP x LP: Gram matrix of Y
     int blocks;                 // Gram partials; 0: gram_blocks(n, LP)
     int rows_per_block;         // (set by launch_reduce_gram)
+    void* steps;                // launch_orth_apply: Q in the order of steps too
+    int steps_fmt;
 };
 // Y = sum_s partial[s]; gpart[b] = Gram of the b-th block of rows of Y in float64.
 int launch_reduce_gram(const GramJob* job, int njob, int LP, hipStream_t st);

@@ -365,6 +365,8 @@ __global__ __launch_bounds__(256, NT <= 2 ? 4 : (NT <= 4 ? 3 : 2)) void orth_app
     const double* __restrict__ const gpart = first ? a0.gpart : a1.gpart;
     float* __restrict__ const Y = first ? a0.Y : a1.Y;
     const int n = first ? a0.n : a1.n, rows = first ? g0.rows : g1.rows, parts = first ? g0.parts : g1.parts;
+    void* __restrict__ const steps = first ? a0.steps : a1.steps;
+    const int steps_fmt = first ? a0.steps_fmt : a1.steps_fmt;
     const int blk = first ? blockIdx.x : blockIdx.x - g0.nb;
     __shared__ double rowb[2][2][2 * LP];
     __shared__ double colb[2][2][LP];
@@ -372,11 +374,12 @@ __global__ __launch_bounds__(256, NT <= 2 ? 4 : (NT <= 4 ? 3 : 2)) void orth_app
     __shared__ double Ts[LP * LDT];
     const int tid = threadIdx.x, ti = tid >> 4, tg = tid & 15;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, li = lane & 15, kq = lane >> 4;
-    const int row_end = min(n, (blk + 1) * rows);
-    // the wave's first 16 rows of Y: lane (li, kq) holds a quarter of row li
+    const int row_end = min(steps_fmt ? (n + 31) & ~31 : n, (blk + 1) * rows);      // (steps end in zeros)
+    // the wave's first 16 rows of Y: lane (li, kq) holds a quarter of row 4 (li % 4) + li / 4, so that the lane's four results are
+    // adjacent rows
     float y[KQ];
     auto load_rows = [&](int r0) {
-        const float4* ip = reinterpret_cast<const float4*>(Y + (size_t)min(r0 + li, n - 1) * LP + kq * KQ);
+        const float4* ip = reinterpret_cast<const float4*>(Y + (size_t)min(r0 + 4 * (li & 3) + (li >> 2), n - 1) * LP + kq * KQ);
 #pragma unroll
         for (int u = 0; u < KQ / 4; ++u) {
             const float4 t = ip[u];
@@ -499,10 +502,30 @@ __global__ __launch_bounds__(256, NT <= 2 ? 4 : (NT <= 4 ? 3 : 2)) void orth_app
 #pragma unroll
             for (int s = 0; s < KQ; ++s)
                 acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)y[s], Ts[(kq * KQ + s) * LDT + 16 * ct + li], acc, 0, 0, 0);
+            float out[4];
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const int orow = r0 + 4 * v + kq;
-                if (orow < n) Y[(size_t)orow * LP + 16 * ct + li] = (float)acc[v];
+                const int orow = r0 + 4 * kq + v;
+                out[v] = orow < n ? (float)acc[v] : 0.f;
+                if (orow < n) Y[(size_t)orow * LP + 16 * ct + li] = out[v];
+            }
+            const int half = (r0 >> 4) & 1;         // of the step
+            if (NT == 1 && steps_fmt == STEPS_FLOAT) {
+                *reinterpret_cast<float4*>(static_cast<float*>(steps) + (size_t)(r0 >> 5) * 512 + lane * 8 + 4 * half) =
+                    make_float4(out[0], out[1], out[2], out[3]);
+            } else if (steps_fmt == STEPS_PLANES) {
+                uint16_t* dst = static_cast<uint16_t*>(steps) + ((size_t)(r0 >> 5) * NT + ct) * (3 * STEP_PIECE) + lane * 8 + 4 * half;
+                uint32_t w[3][2];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {       // (see split_planes)
+                    const float a = out[2 * h], b = out[2 * h + 1];
+                    w[0][h] = pack_bf16x2(a, b);
+                    const float ra = a - __uint_as_float(w[0][h] << 16), rb = b - __uint_as_float(w[0][h] & 0xffff0000u);
+                    w[1][h] = pack_bf16x2(ra, rb);
+                    w[2][h] = pack_bf16x2(ra - __uint_as_float(w[1][h] << 16), rb - __uint_as_float(w[1][h] & 0xffff0000u));
+                }
+#pragma unroll
+                for (int p = 0; p < 3; ++p) *reinterpret_cast<uint2*>(dst + p * STEP_PIECE) = make_uint2(w[p][0], w[p][1]);
             }
         }
         if (r0 + 64 < row_end) load_rows(r0 + 64);

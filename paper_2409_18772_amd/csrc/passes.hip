@@ -1569,6 +1569,7 @@ size_t pass_partial_floats(int rows, int cols, int LP) {
                            most_partial_rows(min(rows, 1024), block, cols, 64, 512, MAX_SPLITS_FEW));
     part = max(part, LP * most_partial_rows(cols, 64, rows, 128, 512, MAX_SPLITS_T));
     part = max(part, 16 * most_partial_rows(cols, 64, rows, 32, 512, MAX_SPLITS_T));
+    part = max(part, (size_t)LP * 4096);        // (pass_full_ranges: up to 256 workgroups of 16 results)
     return max(part, LP * max((size_t)pn.splits * rows, (size_t)pt.splits * cols));
 }
 

@@ -72,6 +72,32 @@ def test_rsvd_against_oracle(rows, cols, axis, bits, rank, p, q, kind):
     assert np.array_equal(to_np(S2), S) and np.array_equal(to_np(U2), U) and np.array_equal(to_np(Vt2), Vt)
 
 
+# The products over whole reductions, at the edges of their tiles (16 results), steps (32 of the reduction), waves (8 steps) and ranges, on both sides of their
+# limits; nothing is truncated, so the factors are determined to float32.
+@pytest.mark.parametrize("rows,cols,axis,ell", [
+    (63, 64, o.ROWWISE, 8), (64, 64, o.COLWISE, 16), (65, 95, o.ROWWISE, 9), (97, 271, o.COLWISE, 33), (255, 287, o.ROWWISE, 65),
+    (80, 2687, o.ROWWISE, 20), (80, 2688, o.COLWISE, 20), (2719, 66, o.ROWWISE, 48), (130, 4099, o.COLWISE, 7), (4097, 120, o.ROWWISE, 24),
+    (4113, 70, o.COLWISE, 40), (100, 8192, o.ROWWISE, 17), (8193, 70, o.ROWWISE, 12), (8200, 64, o.ROWWISE, 20), (70, 8193, o.COLWISE, 12)])
+def test_rsvd_whole_reductions(rows, cols, axis, ell):
+    test_rsvd_against_oracle(rows, cols, axis, 4, ell, 0, 1, "normal")
+
+
+@pytest.mark.parametrize("M,N,K,rank,lda,ldb", [(100, 4100, 1200, 12, 1203, 4101), (3100, 70, 900, 20, 901, 77), (67, 90, 2700, 40, 2701, 90)])
+def test_rsvd_whole_reductions_of_two_operands(M, N, K, rank, lda, ldb):
+    """Operands that take tiles or ranges of different sizes, with odd row strides, in one launch: the bits of one operand alone."""
+    import torch
+    import paper_2409_18772_amd as L
+    A, B = (torch.empty((r, ld), device="cuda").normal_()[:, :c] for r, ld, c in ((M, lda, K), (K, ldb, N)))
+    D = torch.zeros((M, N), device="cuda")
+    L.lrqmm_matmul_ex(A, B, D, 8, rank, 8, 1, seed=5)
+    Ac, Bc = A.contiguous(), B.contiguous()
+    codes, amax = L.lrqmm_quantize(Ac, L.AXIS_ROW, 8)
+    codesT, amaxT = L.lrqmm_quantize(Bc, L.AXIS_COL, 8)
+    fa = L.lrqmm_rsvd(Ac, amax, L.AXIS_ROW, 8, rank, 8, 1, seed=5)
+    fb = L.lrqmm_rsvd(Bc, amaxT, L.AXIS_COL, 8, rank, 8, 1, seed=5)
+    assert torch.equal(L.lrqmm_gemm(codes, amax, codesT, amaxT, 8, fa, fb), D)
+
+
 # The small SVD by tridiagonalization (from 5 columns on), at the edges of its register widths (16, 24, 32, 40, 48, 64, 80
 # columns), of its lane groups and of the padding of its rows; no truncation, so the factors are determined to float32.
 @pytest.mark.parametrize("ell", [31, 32, 33, 40, 41, 47, 57, 58, 59, 64, 65, 72, 73, 79, 80])
