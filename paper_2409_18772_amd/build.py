@@ -15,7 +15,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "liblrqmm.so")
-SOURCES = ["api.hip", "quantize.hip", "sketch.hip", "passes.hip", "passes_full_n.hip", "passes_full_t.hip", "orth.hip", "gemm.hip"]
+SOURCES = ["api.hip", "quantize.hip", "sketch.hip", "passes.hip", "one_read.hip", "passes_full_n.hip", "passes_full_t.hip", "orth.hip", "gemm.hip"]
 HEADERS = [os.path.join(CSRC, "common.h"), os.path.join(CSRC, "kernels.h"), os.path.join(CSRC, "sketch.h"),
            os.path.join(CSRC, "passes_full.h"),
            os.path.join(HERE, "..", "include", "lrqmm.h")]

@@ -38,8 +38,9 @@ inline int pad_to(int x, int m) { return (x + m - 1) / m * m; }
 
 struct RsvdWs {
     float *lam, *s, *Wc, *Yr, *partial;
-    double *gpart, *gram, *Ur, *Mv;
+    double *gpart, *gram, *Ur, *Mv, *M;
     char* steps;
+    float* mpart;               // one-read kernel: partial R^T Y (may be absent)
 };
 
 // Every region of carve_rsvd and carve_matmul is at least as large for a larger problem, so that one workspace, sized for the
@@ -51,7 +52,7 @@ size_t carve_rsvd(Arena& a, int rows, int cols, int axis, int LP, int rank, Rsvd
     int nb = gram_blocks_most(rows > cols ? rows : cols, LP);
     if (axis == LRQMM_AXIS_ROW && LP == 16 && quant_sketch_rows_blocks(rows) > nb) nb = quant_sketch_rows_blocks(rows);
     nb = std::max(nb, full_blocks_most(rows > cols ? rows : cols, LP));
-    RsvdWs t;
+    RsvdWs t = {};
     t.lam = a.take<float>(npad);
     t.s = a.take<float>(npad);
     t.Wc = a.take<float>((size_t)cols * LP);
@@ -62,6 +63,10 @@ size_t carve_rsvd(Arena& a, int rows, int cols, int axis, int LP, int rank, Rsvd
     t.Ur = a.take<double>((size_t)LP * rank);
     t.Mv = a.take<double>((size_t)LP * rank);
     t.steps = a.take<char>(steps_bytes(rows > cols ? rows : cols, LP));
+    if (axis == LRQMM_AXIS_ROW && LP == 16 && rows > LRQ_ONE_READ_ROWS) {
+        t.M = a.take<double>((size_t)PROJECT_GROUPS * (256 + std::min(cols, LRQ_QSR_MAX_COLS) * 16));       // Gram matrices, then R^T Y
+        t.mpart = a.take<float>((size_t)quant_project_blocks(rows) * std::min(cols, LRQ_QSR_MAX_COLS) * 16);
+    }
     if (w) *w = t;
     return a.off;
 }
@@ -321,10 +326,14 @@ static int make_factor(Factor* f, const float* X, int ldx, int rows, int cols, i
 
 // The partial results of the last transposed product: a single one where the pass leaves none.
 struct TPartials { const float* p; int splits; };
-static TPartials t_partials(const Factor& f, int planes) {
+static TPartials t_partials(const Factor& f, int planes, bool projected = false) {
+    if (projected) return {f.op.W, 1};          // (formed beside the first product)
     if (planes >= 2 && f.op.ft == 1) return {f.op.W, 1};
     return {f.op.partial, planes >= 2 && f.op.ft > 1 ? f.op.ft : f.op.pt.splits};
 }
+
+// Whether the one-read kernel forms R^T Y as well: where R^T Q is the only other product and only its sums are asked for.
+static bool one_read_projects(int power_iters, bool stop_at_basis) { return power_iters == 0 && stop_at_basis; }
 
 // How the first residual product of a factorization is formed.
 enum class FirstPass {
@@ -397,6 +406,20 @@ static void factor_launches(LaunchList& ops, const Factor* factors, int n, First
     // Y = R Omega
     if (first == FirstPass::one_read) {
         const Factor f = p->f[0];
+        if (one_read_projects(power_iters, stop_at_basis)) {
+            // R^T Q = (R^T Y) T: nothing reads the operand again
+            const int blocks = quant_project_blocks(f.op.rows);
+            double *const gsum = f.w.M, *const msum = gsum + PROJECT_GROUPS * 256;
+            GramJob g = {nullptr, 0, f.op.rows, f.op.Y, gsum, f.w.gram, PROJECT_GROUPS, 0};
+            g.M = msum; g.Z = f.op.W; g.m = f.op.cols;
+            ops.push_back([=] {
+                return launch_quant_project_rows(f.op.X, f.op.ldx, f.op.rows, f.op.cols, q, f.op.W, LP, f.op.Y, f.w.gpart, f.w.mpart,
+                                                 one_read_amax, f.w.lam, f.w.s, f.op.codes, st);
+            });
+            ops.push_back([=] { return launch_project_sum(f.w.gpart, f.w.mpart, blocks, f.op.cols, gsum, msum, st); });
+            ops.push_back([=] { return launch_orth_apply(&g, 1, ell, LP, true, st); });
+            return;
+        }
         ops.push_back([=] {
             return launch_quant_sketch_rows(f.op.X, f.op.ldx, f.op.rows, f.op.cols, q, f.op.W, LP, f.op.Y, f.w.gpart,
                                             one_read_amax, f.w.lam, f.w.s, f.op.codes, st);
@@ -726,7 +749,7 @@ int lrqmm_matmul_ex(int M, int N, int K, int bits, int rank, int oversample, int
     // K = 576) keeps its rows in registers -- maxima, codes and Y from a single read -- in a chain of its own.
     // (in every precision mode: the one-read pass runs in float32, which the reduced modes allow; see the row limit)
     const bool short_rows = factored && !per_tensor && quant_sketch_rows_usable(A, lda, M, K, LP, w.Aq);
-    const bool one_read = short_rows && M >= LRQ_ONE_READ_MIN_ROWS;
+    const bool one_read = short_rows && one_read_pays(M, K);
     const bool overlap = one_read || (factored && two_chains(M, N, K));
     // The one-read kernel leaves rows of bytes: its products are short and bound by the store of C.
     const bool pair = !factored && !per_tensor && quantize_pair_usable(M, N, K);
@@ -864,7 +887,7 @@ int lrqmm_matmul_ex(int M, int N, int K, int bits, int rank, int oversample, int
             GemmWs g;
             Arena ga(w.sub);
             carve_gemm(ga, M, N, K, rank, &g);
-            const TPartials ta = t_partials(f[0], pl_last), tb = t_partials(f[1], pl_last);
+            const TPartials ta = t_partials(f[0], pl_last, one_read && one_read_projects(power_iters, basis_panels)), tb = t_partials(f[1], pl_last);
             rc = launch_basis_panels({ta.p, tb.p, f[1].op.Y, ta.splits, tb.splits, N, K, rank,
                                       g.Wf, g.Vf, w.Zt, g.X, w.Sig, w.Gam}, pst);
             ready = {w.Aq, w.BqT, g.Wf, g.Vf, f[0].op.Y, w.Sig, f[0].w.s, f[1].w.s, g.X, w.Gam, w.Zt, g.Lp, g.Rp, M, N, K, rank,

@@ -120,17 +120,26 @@ int launch_pass_full_t(const PassOperand* op, int nop, QuantParams q, int LP, hi
 // reduction cut into eight parts that are added in a fixed order.  Otherwise LRQMM_ERR_UNSUPPORTED and nothing is
 // launched.
 #define LRQ_QSR_MAX_BLOCKS 512
-// Rows from which lrqmm_matmul takes it.  Below, both operands advance together in half the launches and on one stream.
-// Measured, together / one read, us per call (64 columns of B, sketch of 8): K = 576: 2048 rows 91 / 131, 8192 104 / 130,
-// 16384 112 / 132, 32768 152 / 142, 65536 211 / 185, 100352 290 / 238; K = 64: 8192 81 / 140, 65536 126 / 137, 100352
-// 153 / 150 (its two streams cost the host 105 to 140 us a call by themselves, differing between processes).  The calls
-// that gain have about 15 million elements or more; between this limit and those one read is the slower form.
-#define LRQ_ONE_READ_MIN_ROWS 8192
+#define LRQ_QSR_MAX_COLS 576
+// Where lrqmm_matmul takes it, or quant_project_rows_kernel.  Below, both operands advance together in half the launches and on one stream:
+// a call on two streams takes 80 us and more whatever its size.  Together / one read, us per call (4 bits, 64 columns of B, sketch of 8, no
+// power iteration): K = 64 16384 rows 46 / 81, 65536 78 / 83, 100352 98 / 94; 144 32768 71 / 83, 65536 100 / 86; 288 32768 78 / 87, 65536
+// 127 / 101; 576 8192 57 / 95, 16384 65 / 95, 32768 106 / 94, 100352 217 / 164; one power iteration 65536 x 64 140 / 138, 32768 x 576 183 / 177,
+// 16384 x 576 118 / 152.
+#define LRQ_ONE_READ_ROWS 20000
+static inline bool one_read_pays(int rows, int cols) { return (long long)(rows - LRQ_ONE_READ_ROWS) * (cols < 64 ? 64 : cols) >= 4700000; }
 bool quant_sketch_rows_usable(const float* X, int ldx, int rows, int cols, int LP, const int8_t* codes);
 int quant_sketch_rows_blocks(int rows);
 int launch_quant_sketch_rows(const float* X, int ldx, int rows, int cols, QuantParams q, const float* W, int LP,
                              float* Y, double* gpart, float* amax, float* lam_out, float* s_out, int8_t* codes,
                              hipStream_t st);
+// The same (one_read.hip) with R^T Y from that read as well, for the same operands: Y = R.(W H) with a reflection H (see there), and
+// mpart[quant_project_blocks(rows)][cols][16] the workgroups' R^T Y, to be added by launch_project_sum.
+#define LRQ_QPR_MAX_BLOCKS 480      // two on every CU of 256 but one in eight, which the other operand's small
+// launches find half free (496: they waited for the end, the call 180 us in place of 168)
+int quant_project_blocks(int rows);
+int launch_quant_project_rows(const float* X, int ldx, int rows, int cols, QuantParams q, const float* W, int LP, float* Y, double* gpart,
+                              float* mpart, float* amax, float* lam_out, float* s_out, int8_t* codes, hipStream_t st);
 // The panels of the rank-2r update from the codes of both operands, in one launch (RP: r rounded up to 16).  Wf, Vf: the K x r
 // factors W and Vt^T as three bfloat16 planes in operand order, zero padded: [k block of 64][column tile of 16][plane][step][lane][8],
 // a piece (k block, tile, plane, step) being an operand of v_mfma_f32_16x16x32_bf16.  Every codes format gives the same bits.
@@ -160,11 +169,18 @@ struct GramJob {
     int rows_per_block;         // (set by launch_reduce_gram)
     void* steps;                // launch_orth_apply: Q in the order of steps too
     int steps_fmt;
+    const double* M;            // launch_orth_apply (16 columns): Z <- (sum of M's PROJECT_GROUPS parts) T as well, m x LP
+    float* Z;
+    int m;
 };
 // Y = sum_s partial[s]; gpart[b] = Gram of the b-th block of rows of Y in float64.
 int launch_reduce_gram(const GramJob* job, int njob, int LP, hipStream_t st);
 // gram = sum over the blocks of gpart, in fixed order.
 int launch_gram_sum(const GramJob* job, int njob, int LP, hipStream_t st);
+// What `blocks` workgroups of quant_project_rows_kernel have left, added in PROJECT_GROUPS groups: gsum[group][16][16] (Gram partials for
+// launch_orth_apply, with sum) and msum[group][cols][16].
+#define PROJECT_GROUPS 16
+int launch_project_sum(const double* gpart, const float* mpart, int blocks, int cols, double* gsum, double* msum, hipStream_t st);
 // Y <- Y T, T upper triangular with (Y T)^T (Y T) = I on the live columns, from gram; sum: from the Gram partials (as many
 // as orth_apply_sums allows) instead.
 bool orth_apply_sums(int blocks, int LP);

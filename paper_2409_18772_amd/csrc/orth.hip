@@ -248,6 +248,42 @@ __global__ __launch_bounds__(64) void gram_sum_parts_kernel(GramJob a, GramJob b
     if (part == 0 && (int)blockIdx.x * 8 + e < entries) gram[idx] = sum;
 }
 
+// Gram matrices and R^T Y of quant_project_rows_kernel's workgroups, added in float64 in PROJECT_GROUPS contiguous groups (orth_apply_kernel
+// adds the groups): blockIdx.x 0 a group's Gram matrices, an entry a thread, the others 512 values of R^T Y each, two a thread.  496
+// partials of 576 x 16: 5.2 us; a thread per 16 bytes of 16 partials, all groups at once, 24 us (128 bytes at a time of every partial).
+__global__ __launch_bounds__(256) void project_sum_kernel(const double* __restrict__ gpart, const float* __restrict__ mpart, int blocks,
+                                                          int values, double* __restrict__ gsum, double* __restrict__ msum) {
+    constexpr int BATCH = 16;
+    raise_wave_priority();
+    const int b0 = (int)blockIdx.y * blocks / PROJECT_GROUPS, b1 = ((int)blockIdx.y + 1) * blocks / PROJECT_GROUPS;
+    if (blockIdx.x == 0) {
+        double acc = 0.0;
+        for (int b = b0; b < b1; b += BATCH) {
+            double v[BATCH];
+#pragma unroll
+            for (int u = 0; u < BATCH; ++u) v[u] = gpart[(size_t)min(b + u, b1 - 1) * 256 + threadIdx.x];
+#pragma unroll
+            for (int u = 0; u < BATCH; ++u) acc += b + u < b1 ? v[u] : 0.0;
+        }
+        gsum[(size_t)blockIdx.y * 256 + threadIdx.x] = acc;
+        return;
+    }
+    const int at = ((int)blockIdx.x - 1) * 512 + 2 * threadIdx.x;
+    if (at >= values) return;
+    double ax = 0.0, ay = 0.0;
+    for (int b = b0; b < b1; b += BATCH) {
+        float2 v[BATCH];
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) v[u] = *reinterpret_cast<const float2*>(mpart + (size_t)min(b + u, b1 - 1) * values + at);
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {
+            ax += b + u < b1 ? (double)v[u].x : 0.0;
+            ay += b + u < b1 ? (double)v[u].y : 0.0;
+        }
+    }
+    *reinterpret_cast<double2*>(msum + (size_t)blockIdx.y * values + at) = make_double2(ax, ay);
+}
+
 // out = In . Mat with float64 accumulation on the float64 matrix cores, one wavefront per 16
 // rows.  v_mfma_f64_16x16x4 operand layout (lane l): A[i = l%16][k = l/16], B[k = l/16][j = l%16],
 // D[i = 4v + l/16][j = l%16] for v = 0..3.  The reduction index may be visited in any order, so
@@ -355,7 +391,7 @@ __device__ __forceinline__ double rcp_f64(double d) {       // hardware estimate
 // 361 / 344, 40 444 / 417, 80 726 / 664; 8192^3 80 1902 / 1855; 16384^3 the same.  82 to 173 registers: the waves start
 // beside resident workgroups of the other chain's passes (4096^3, l = 40, at 306 registers 433 us).
 // parts > 0: G is still in that many partials (see gram_sum_parts_kernel, whose order of addition is kept).
-struct OrthGrid { int nb, rows, parts; };       // workgroups of the job, rows per workgroup (a multiple of 64)
+struct OrthGrid { int nb, rows, parts, nbY; };  // workgroups of the job, rows per workgroup (a multiple of 64); [nbY, nb): 64 rows of M each
 template <int NT>
 __global__ __launch_bounds__(256, NT <= 2 ? 4 : (NT <= 4 ? 3 : 2)) void orth_apply_kernel(GramJob a0, GramJob a1, OrthGrid g0, OrthGrid g1, int ell) {
     constexpr int LP = 16 * NT, KC = 2 * NT, KQ = LP / 4, LDT = LP + 1;
@@ -367,6 +403,9 @@ __global__ __launch_bounds__(256, NT <= 2 ? 4 : (NT <= 4 ? 3 : 2)) void orth_app
     const int n = first ? a0.n : a1.n, rows = first ? g0.rows : g1.rows, parts = first ? g0.parts : g1.parts;
     void* __restrict__ const steps = first ? a0.steps : a1.steps;
     const int steps_fmt = first ? a0.steps_fmt : a1.steps_fmt;
+    const double* __restrict__ const M = first ? a0.M : a1.M;
+    float* __restrict__ const Z = first ? a0.Z : a1.Z;
+    const int nbY = first ? g0.nbY : g1.nbY, m = first ? a0.m : a1.m;
     const int blk = first ? blockIdx.x : blockIdx.x - g0.nb;
     __shared__ double rowb[2][2][2 * LP];
     __shared__ double colb[2][2][LP];
@@ -495,6 +534,24 @@ __global__ __launch_bounds__(256, NT <= 2 ? 4 : (NT <= 4 ? 3 : 2)) void orth_app
     }
     __syncthreads();
     typedef double v4d __attribute__((ext_vector_type(4)));
+    if (NT == 1 && blk >= nbY) {
+        const int r0 = (blk - nbY) * 64 + wave * 16;
+        const double* mp = M + (size_t)min(r0 + li, m - 1) * LP + kq * KQ;
+        double row[KQ];
+#pragma unroll
+        for (int s = 0; s < KQ; ++s) row[s] = 0.0;
+#pragma unroll 4
+        for (int p = 0; p < PROJECT_GROUPS; ++p)
+#pragma unroll
+            for (int s = 0; s < KQ; ++s) row[s] += mp[(size_t)p * m * LP + s];
+        v4d acc = (v4d){0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int s = 0; s < KQ; ++s) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(row[s], Ts[(kq * KQ + s) * LDT + li], acc, 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            if (r0 + 4 * v + kq < m) Z[(size_t)(r0 + 4 * v + kq) * LP + li] = (float)acc[v];
+        return;
+    }
     for (int r0 = blk * rows + wave * 16; r0 < row_end; r0 += 64) {
 #pragma unroll 1
         for (int ct = 0; ct < NT; ++ct) {           // (rolled: the elements of T of one column tile in registers at a time)
@@ -1618,6 +1675,13 @@ int launch_gram_sum(const GramJob* job, int njob, int LP, hipStream_t st) {
     return LRQMM_OK;
 }
 
+int launch_project_sum(const double* gpart, const float* mpart, int blocks, int cols, double* gsum, double* msum, hipStream_t st) {
+    const dim3 grid(1 + ceil_div(cols * 16, 512), PROJECT_GROUPS);
+    hipLaunchKernelGGL(project_sum_kernel, grid, dim3(256), 0, st, gpart, mpart, blocks, cols * 16, gsum, msum);
+    LRQ_CHECK_LAUNCH();
+    return LRQMM_OK;
+}
+
 int launch_apply(const ApplyJob* job, int njob, int LP, hipStream_t st) {
     ApplyJobs a = {};
     int total = 0;
@@ -1644,7 +1708,8 @@ int launch_orth_apply(const GramJob* job, int njob, int ell, int LP, bool sum, h
         if (sum && !orth_apply_sums(blocks, LP)) return LRQMM_ERR_UNSUPPORTED;
         const int units = ceil_div(job[i].n, 64);
         g[i].rows = 64 * ceil_div(units, ORTH_BLOCKS);
-        g[i].nb = ceil_div(job[i].n, g[i].rows);
+        g[i].nbY = ceil_div(job[i].n, g[i].rows);
+        g[i].nb = g[i].nbY + (LP == 16 && job[i].M ? ceil_div(job[i].m, 64) : 0);
         g[i].parts = sum ? blocks : 0;
     }
     const dim3 grid(g[0].nb + g[1].nb);

@@ -1688,7 +1688,7 @@ static inline bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 bool quant_sketch_rows_usable(const float* X, int ldx, int rows, int cols, int LP, const int8_t* codes) {
     // (rows of up to 576 columns: beyond that the two register sets of a tile no longer fit 128 registers)
-    return rows > 0 && LP == 16 && cols >= 16 && cols % 16 == 0 && cols <= 576 && ldx % 4 == 0 && aligned16(X) &&
+    return rows > 0 && LP == 16 && cols >= 16 && cols % 16 == 0 && cols <= LRQ_QSR_MAX_COLS && ldx % 4 == 0 && aligned16(X) &&
            ((uintptr_t)codes & 3) == 0;
 }
 

@@ -137,6 +137,16 @@ def test_short_rows_of_a_single_read(M, N, K, r, p, q, mode):
     assert np.array_equal(C, to_np(D4))
 
 
+@pytest.mark.parametrize("M,K,r,p,q", [(93438, 16, 2, 0, 0), (93437, 64, 16, 0, 0), (78760, 80, 5, 0, 0), (56720, 128, 8, 0, 0), (44500, 192, 8, 0, 0),
+                                       (42600, 208, 3, 0, 0), (37281, 272, 8, 0, 0), (32240, 384, 16, 0, 0), (31751, 400, 8, 0, 0),
+                                       (29185, 512, 2, 0, 0), (28917, 528, 8, 0, 0), (28161, 576, 16, 0, 0), (28159, 576, 16, 0, 0),
+                                       (28200, 576, 4, 4, 0), (28165, 576, 12, 0, 1), (44487, 192, 4, 4, 1)])
+def test_both_products_of_a_single_read(M, K, r, p, q):
+    """Every block count of the kernel that forms R Omega and R^T (R Omega) from one read of A, rows past its last tile, columns past its last
+    block, both sides of its limit; and the one that forms R Omega alone (truncation or a power iteration)."""
+    test_short_rows_of_a_single_read(M, 48, K, r, p, q, o.FLOOR)
+
+
 def test_rank_zero_is_direct_quant_and_modes():
     import paper_2409_18772_amd as L
     A = wl.random_matrix("normal", 150, 200, seed=1)
