@@ -250,9 +250,16 @@ int planes_values(int p) { return p == LRQMM_PREC_BF16 ? 1 : (p == LRQMM_PREC_BF
 // Measured, together / two chains, us, sketches of 24, 40 and 80 columns (one power iteration): 1024^3 143 / 193 (24);
 // 2048^3 196 / 212, 271 / 285, 497 / 508; 3072^3 279 / 283, 368 / 357, 618 / 614; 4096^3 351 / 348, 445 / 434, 688 / 690;
 // 8192^3 1387 / 1366 (24), 2017 / 1958 (80).
-bool two_chains(int M, int N, int K) {
-    const long long elements = (long long)M * K + (long long)K * N;
-    return elements > 13000000;
+// Those are the passes of passes.hip.  With whole reductions a pass of both operands is short enough on its own up to sides of 4096, us, inputs
+// from memory, two chains / together: 2600^3 l = 10 181 / 166, 24 239 / 229, 40 311 / 301; 3300^3 24 287 / 278, 40 364 / 341, 80 592 / 570; 3700^3 24 328 / 309,
+// 40 400 / 377, 80 636 / 614; 4000^3 24 338 / 332, 40 415 / 413, 80 658 / 649; 4096 x 4096 x 2048 24 269 / 241, 40 359 / 328; 2048 x 2048 x 4096 24 248 / 228; 4096^3
+// 10 280 / 271, 24 333 / 335, 40 400 / 408, 80 633 / 650; not with a short or a longer side: 4096 x 1024 x 4096 10 182 / 191, 1500 x 1500 x 6000 24 259 / 269,
+// 6000 x 3000 x 1600 270 / 278.
+bool two_chains(int M, int N, int K, int LP, int planes) {
+    const long long a = (long long)M * K, b = (long long)K * N;
+    if (a + b <= 13000000) return false;
+    const bool sides = std::max(std::max(M, N), K) <= 4096 && std::min(std::min(M, N), K) >= 2000;
+    return !(planes >= 2 && sides && (LP == 16 || std::max(a, b) <= FULL_ELEMENTS));
 }
 
 // Whether the integer product (`tiles` tiles of 256 x 256, one per CU at a time) runs early, beside the small SVDs and the
@@ -750,7 +757,7 @@ int lrqmm_matmul_ex(int M, int N, int K, int bits, int rank, int oversample, int
     // (in every precision mode: the one-read pass runs in float32, which the reduced modes allow; see the row limit)
     const bool short_rows = factored && !per_tensor && quant_sketch_rows_usable(A, lda, M, K, LP, w.Aq);
     const bool one_read = short_rows && one_read_pays(M, K);
-    const bool overlap = one_read || (factored && two_chains(M, N, K));
+    const bool overlap = one_read || (factored && two_chains(M, N, K, LP, planes_subspace(precision)));
     // The one-read kernel leaves rows of bytes: its products are short and bound by the store of C.
     const bool pair = !factored && !per_tensor && quantize_pair_usable(M, N, K);
     const int packed = pair ? direct_format(M, N, K, bits) : (factored && !one_read ? packed_format(bits, K) : PK_NONE);

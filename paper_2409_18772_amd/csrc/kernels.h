@@ -107,6 +107,7 @@ int launch_resid_mul_t(const PassOperand* op, int nop, QuantParams q, int LP, hi
 // The same products, the other factor in the order of steps, for the operands with fn > 0 (N pass), ft > 0 (T pass): in that many
 // ranges of the reduction, a single one without partial results: Y (rows x LP) = R W, or W (cols x LP) = R^T Y, and
 // full_blocks(results, LP) Gram partials of it.  One operand or two of different axes.
+#define FULL_ELEMENTS 16200000      // of an operand with sides of up to 4096 (see two_chains)
 int pass_full_ranges(bool t_type, int rows, int cols, int ldx, int LP);     // 0: the products above
 int full_blocks(int n, int LP);
 int full_blocks_most(int n, int LP);        // of any result of up to n rows

@@ -10,8 +10,9 @@ int full_blocks_most(int n, int LP) { return max(min(256, ceil_div(n, 16)), full
 // of theirs needs two launches: one operand in each form cost 500 x 500 x 1800, 24 columns 166 us in place of 150.
 // One power iteration, us per call, passes.hip / here: 200^3 l = 10 66.5 / 54.1, 24 126 / 110; 1000^3 10 85 / 75.5, 24 146 / 134, 80 387 /
 // 370; 2000^3 10 130 / 113, 24 198 / 173, 40 266 / 240, 80 463 / 432; two chains: 2800^3 24 242 / 232, 40 319 / 307; 3300^3 10 239 / 220, 24
-// 289 / 278, 40 357 / 357; 4096^3 10 275 / 270, 24 319 / 345, 40 393 / 450, 80 629 / 689: above 13 million elements, where workgroups that
-// take a CU for themselves keep the other chain's kernels out, with one tile of sketch columns alone.
+// 289 / 278, 40 357 / 357; 4096^3 10 275 / 270, 24 319 / 345, 40 393 / 450, 80 629 / 689: workgroups that take a CU for themselves keep the other
+// chain's kernels out.  So the operands of calls with two chains stay, but for one tile of sketch columns; see two_chains for where
+// both advance together, which is better than either.
 // Operands with a side beyond 8192 stay there (500 x 300 x 12000 l = 24 252 / 275; a step of such a call would take two launches), but for the
 // transposed product of a tall one (100352 x 64 x 64 l = 8 111 / 99).
 // Long reductions are cut, into ranges of 512 and more as long as there are CUs without a workgroup, whole / cut: 300 x 5000 x 1200 l = 8
@@ -22,7 +23,7 @@ int pass_full_ranges(bool t_type, int rows, int cols, int ldx, int LP) {
     const int n = t_type ? cols : rows, len = t_type ? rows : cols;
     if (ldx > (1 << 22) || len < 64 || n < 64) return 0;        // (offsets of a workgroup's rows in 32 bits)
     if (cols > FULL_LONG || (rows > FULL_LONG && !(t_type && LP == 16))) return 0;
-    if ((long long)n * len > 13000000) return LP == 16 && len <= 4096;
+    if ((long long)n * len > (max(n, len) <= 4096 ? FULL_ELEMENTS : 13000000)) return LP == 16 && len <= 4096;
     const int tiles = ceil_div(n, 16), steps = len >> 5;
     if (steps < FULL_CUT) return 1;
     const int most = min(max(1, min(FULL_BLOCKS / tiles, steps / 16)), MAX_SPLITS_T);

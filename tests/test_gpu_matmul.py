@@ -232,6 +232,21 @@ def _separate_calls(L, dA, dB, bits, r, p, q, seed):
     return L.lrqmm_gemm(Aq, amA, BqT, amB, bits, fa, fb)
 
 
+@pytest.mark.parametrize("M,N,K,r,p", [(2700, 2600, 2500, 16, 8), (3300, 3300, 3300, 32, 8), (4096, 2001, 3900, 20, 8), (2000, 4096, 3955, 24, 8),
+                                       (2000, 4096, 3956, 24, 8), (1999, 4096, 3900, 24, 8), (4097, 2100, 2000, 24, 8)])
+def test_factorizations_together_and_in_two_chains(M, N, K, r, p):
+    """Both sides of the limits between two chains and factorizations that advance together (sides from 2000 to 4096, 16.2 million elements an
+    operand), with the product fused and early: the bits of the separate calls."""
+    import torch
+    import paper_2409_18772_amd as L
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    dA, dB = (torch.empty(s, device="cuda").normal_(generator=gen) for s in ((M, K), (K, N)))
+    say("together or two chains", M, N, K, r, p)
+    C = to_np(L.lrqmm_matmul(dA, dB, 8, r, p, 1, seed=9))
+    assert np.array_equal(to_np(_separate_calls(L, dA, dB, 8, r, p, 1, 9)), C)
+
+
+
 @pytest.mark.parametrize("M,N,K,r,p", [(2200, 600, 300, 20, 8), (300, 600, 2200, 17, 0), (2100, 300, 2500, 24, 8),
                                        (300, 2300, 700, 20, 0)])
 def test_factors_do_not_depend_on_the_other_operand(M, N, K, r, p):
