@@ -21,7 +21,6 @@
 // l = 80: 10.04 -> 9.97 ms.
 __device__ __forceinline__ void raise_wave_priority() { __builtin_amdgcn_s_setprio(3); }
 
-#define GRAM_BATCH 64         // Gram partials per batch of loads when there are more than 64 of them
 #define MAXL LRQMM_MAX_SKETCH
 // Workgroups of orth_apply_kernel per job, at most: 100352 rows, 64 220 us per call, 256 210, 512 209; 8192 1878, 1855, 1855
 #define ORTH_BLOCKS 256
@@ -220,8 +219,9 @@ __global__ __launch_bounds__(256) void reduce_gram_kernel(GramJob a, GramJob b, 
 // two resident workgroups of the other operand's pass kernels, which leave about 80 registers per lane free on
 // a SIMD -- a kernel with one thread per entry and 64 partials in 128 registers waited for a pass workgroup to
 // drain first (16384^3: 58-121 us on average against 4 us alone; the partials were written by other workgroups on
-// other XCDs, so every load is a long-latency miss and all loads of a batch are issued before the first add).  BATCH = 64 beyond that (tall
-// operands with narrow sketches: several hundred partials).
+// other XCDs, so every load is a long-latency miss and all loads of a batch are issued before the first add).  BATCH = 16, 32 and 64 beyond that,
+// so that up to 512 partials are one batch and no load of it is idle (125 partials with 64 loads a
+// thread, 2000^3 l = 10 116.2 / 112.5 us per call; 1537 x 1021 x 2311 l = 24 172.5 / 168.2).
 template <int BATCH>
 __global__ __launch_bounds__(64) void gram_sum_parts_kernel(GramJob a, GramJob b, int entries) {
     raise_wave_priority();
@@ -1667,10 +1667,12 @@ int launch_gram_sum(const GramJob* job, int njob, int LP, hipStream_t st) {
         most = max(most, j[i].blocks);
     }
     dim3 grid(ceil_div(LP * LP, 8), njob);
-    if (most > GRAM_BATCH)
-        hipLaunchKernelGGL(gram_sum_parts_kernel<GRAM_BATCH>, grid, dim3(64), 0, st, j[0], j[1], LP * LP);
-    else
-        hipLaunchKernelGGL(gram_sum_parts_kernel<8>, grid, dim3(64), 0, st, j[0], j[1], LP * LP);
+#define LRQ_GSUM(B) hipLaunchKernelGGL(gram_sum_parts_kernel<B>, grid, dim3(64), 0, st, j[0], j[1], LP * LP)
+    if (most <= 64)       LRQ_GSUM(8);
+    else if (most <= 128) LRQ_GSUM(16);
+    else if (most <= 256) LRQ_GSUM(32);
+    else                  LRQ_GSUM(64);
+#undef LRQ_GSUM
     LRQ_CHECK_LAUNCH();
     return LRQMM_OK;
 }
