@@ -63,7 +63,7 @@ size_t carve_rsvd(Arena& a, int rows, int cols, int axis, int LP, int rank, Rsvd
     t.Ur = a.take<double>((size_t)LP * rank);
     t.Mv = a.take<double>((size_t)LP * rank);
     t.steps = a.take<char>(steps_bytes(rows > cols ? rows : cols, LP));
-    if (axis == LRQMM_AXIS_ROW && LP == 16 && rows > LRQ_ONE_READ_ROWS) {
+    if (axis == LRQMM_AXIS_ROW && rows > LRQ_ONE_READ_ROWS) {           // (used for sketches of 16 columns alone)
         t.M = a.take<double>((size_t)PROJECT_GROUPS * (256 + std::min(cols, LRQ_QSR_MAX_COLS) * 16));       // Gram matrices, then R^T Y
         t.mpart = a.take<float>((size_t)quant_project_blocks(rows) * std::min(cols, LRQ_QSR_MAX_COLS) * 16);
     }
