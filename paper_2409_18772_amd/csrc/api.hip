@@ -41,6 +41,7 @@ struct RsvdWs {
     double *gpart, *gram, *Ur, *Mv, *M;
     char* steps;
     float* mpart;               // one-read kernel: partial R^T Y (may be absent)
+    int* again;                 // ... and whether a pass for R^T Q follows
 };
 
 // Every region of carve_rsvd and carve_matmul is at least as large for a larger problem, so that one workspace, sized for the
@@ -66,6 +67,7 @@ size_t carve_rsvd(Arena& a, int rows, int cols, int axis, int LP, int rank, Rsvd
     if (axis == LRQMM_AXIS_ROW && rows > LRQ_ONE_READ_ROWS) {           // (used for sketches of 16 columns alone)
         t.M = a.take<double>((size_t)PROJECT_GROUPS * (256 + std::min(cols, LRQ_QSR_MAX_COLS) * 16));       // Gram matrices, then R^T Y
         t.mpart = a.take<float>((size_t)quant_project_blocks(rows) * std::min(cols, LRQ_QSR_MAX_COLS) * 16);
+        t.again = a.take<int>(1);
     }
     if (w) *w = t;
     return a.off;
@@ -331,10 +333,11 @@ static int make_factor(Factor* f, const float* X, int ldx, int rows, int cols, i
     return LRQMM_OK;
 }
 
-// The partial results of the last transposed product: a single one where the pass leaves none.
-struct TPartials { const float* p; int splits; };
+// The partial results of the last transposed product: a single one where the pass leaves none.  projected: formed beside the first
+// product (see one_read_projects); where *again is set, a pass has left `p2` instead.
+struct TPartials { const float* p; int splits; const int* again; const float* p2; int splits2; };
 static TPartials t_partials(const Factor& f, int planes, bool projected = false) {
-    if (projected) return {f.op.W, 1};          // (formed beside the first product)
+    if (projected) return {f.op.W, 1, f.w.again, f.op.partial, f.op.pt.splits};
     if (planes >= 2 && f.op.ft == 1) return {f.op.W, 1};
     return {f.op.partial, planes >= 2 && f.op.ft > 1 ? f.op.ft : f.op.pt.splits};
 }
@@ -414,17 +417,20 @@ static void factor_launches(LaunchList& ops, const Factor* factors, int n, First
     if (first == FirstPass::one_read) {
         const Factor f = p->f[0];
         if (one_read_projects(power_iters, stop_at_basis)) {
-            // R^T Q = (R^T Y) T: nothing reads the operand again
+            // R^T Q = (R^T Y) T: nothing reads the operand again, unless Y shows that this would be less accurate than R^T Q
             const int blocks = quant_project_blocks(f.op.rows);
             double *const gsum = f.w.M, *const msum = gsum + PROJECT_GROUPS * 256;
             GramJob g = {nullptr, 0, f.op.rows, f.op.Y, gsum, f.w.gram, PROJECT_GROUPS, 0};
-            g.M = msum; g.Z = f.op.W; g.m = f.op.cols;
+            g.M = msum; g.Z = f.op.W; g.m = f.op.cols; g.again = f.w.again;
+            PassOperand rtq = f.op;
+            rtq.run = f.w.again;
             ops.push_back([=] {
                 return launch_quant_project_rows(f.op.X, f.op.ldx, f.op.rows, f.op.cols, q, f.op.W, LP, f.op.Y, f.w.gpart, f.w.mpart,
                                                  one_read_amax, f.w.lam, f.w.s, f.op.codes, st);
             });
             ops.push_back([=] { return launch_project_sum(f.w.gpart, f.w.mpart, blocks, f.op.cols, gsum, msum, st); });
             ops.push_back([=] { return launch_orth_apply(&g, 1, ell, LP, true, st); });
+            ops.push_back([=] { return launch_resid_mul_t(&rtq, 1, q, LP, st); });
             return;
         }
         ops.push_back([=] {
@@ -895,7 +901,7 @@ int lrqmm_matmul_ex(int M, int N, int K, int bits, int rank, int oversample, int
             Arena ga(w.sub);
             carve_gemm(ga, M, N, K, rank, &g);
             const TPartials ta = t_partials(f[0], pl_last, one_read && one_read_projects(power_iters, basis_panels)), tb = t_partials(f[1], pl_last);
-            rc = launch_basis_panels({ta.p, tb.p, f[1].op.Y, ta.splits, tb.splits, N, K, rank,
+            rc = launch_basis_panels({ta.p, tb.p, f[1].op.Y, ta.splits, tb.splits, N, K, rank, ta.again, ta.p2, ta.splits2,
                                       g.Wf, g.Vf, w.Zt, g.X, w.Sig, w.Gam}, pst);
             ready = {w.Aq, w.BqT, g.Wf, g.Vf, f[0].op.Y, w.Sig, f[0].w.s, f[1].w.s, g.X, w.Gam, w.Zt, g.Lp, g.Rp, M, N, K, rank,
                      pad_to(2 * rank, 8), basis_slices(K), LP};

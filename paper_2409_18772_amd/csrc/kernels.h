@@ -82,6 +82,7 @@ struct PassOperand {
     void* steps;        // for passes_full_*.hip: W (N pass) or Y (T pass) in the order of its steps
     double* gpart;      // ... Gram partials of the result
     int fn, ft;         // pass_full_ranges of the N pass, the T pass
+    const int* run;     // T pass of 16 columns in float32: does nothing where *run is 0 (null: runs)
 };
 // A tall operand of a residual product in the order of the matrix cores' operands, zero padded, lane 16 g + c holding rows 4 g + (e & 3)
 // + 16 (e >> 2) (e < 8) of column c of a 32-row step: STEPS_PLANES [step][column tile of 16][plane][lane][8], three bfloat16 planes;
@@ -173,6 +174,7 @@ struct GramJob {
     const double* M;            // launch_orth_apply (16 columns): Z <- (sum of M's PROJECT_GROUPS parts) T as well, m x LP
     float* Z;
     int m;
+    int* again;                 // ... and whether R^T Q has to be formed from Q instead (see PROJECT_AMPLIFICATION)
 };
 // Y = sum_s partial[s]; gpart[b] = Gram of the b-th block of rows of Y in float64.
 int launch_reduce_gram(const GramJob* job, int njob, int LP, hipStream_t st);
@@ -181,6 +183,15 @@ int launch_gram_sum(const GramJob* job, int njob, int LP, hipStream_t st);
 // What `blocks` workgroups of quant_project_rows_kernel have left, added in PROJECT_GROUPS groups: gsum[group][16][16] (Gram partials for
 // launch_orth_apply, with sum) and msum[group][cols][16].
 #define PROJECT_GROUPS 16
+// Where Z = (R^T Y) T takes the place of R^T Q.  R^T Y is a float32 sum in the square of the operand's scale, and T multiplies the error of its
+// columns: column j of Z by sum_i |T_ij| |y_i|, next to 1 for columns of Y that are far from dependent, 10^5 at the limit of a live
+// pivot.  Relative distance of Z from float64, 28800 x 576, 8 columns, 4 bits (float32 emulation on the CPU), R^T Q / (R^T Y) T: independent values
+// (1.2 to 1.4) 7e-8 / 3e-8, values about a mean of each column's own (3.9) 7.4e-8 / 7.0e-8, at 8 bits (4.5) 8.1e-8 / 8.1e-8; rank 1 plus 1e-3
+// noise (19) 7e-8 / 3.6e-7, rank 1 times 1 + 1e-4 noise (2500) 8e-8 / 4e-5.  The lengths of live columns keep the squares inside float32's
+// range with as much room as R^T Q has (2^-20 to 2^40; those of 28800 rows of order 1 are 10 to 10^4).
+#define PROJECT_AMPLIFICATION 4.0
+#define PROJECT_LEAST 0x1p-40       // of the squared lengths
+#define PROJECT_MOST 0x1p80
 int launch_project_sum(const double* gpart, const float* mpart, int blocks, int cols, double* gsum, double* msum, hipStream_t st);
 // Y <- Y T, T upper triangular with (Y T)^T (Y T) = I on the live columns, from gram; sum: from the Gram partials (as many
 // as orth_apply_sums allows) instead.
@@ -218,6 +229,9 @@ int basis_slices(int K);
 struct BasisPanels {
     const float *partialA, *partialB, *QB;      // [splitsA][K][16], [splitsB][N][16], K x 16
     int splitsA, splitsB, N, K, r;
+    const int* again;                           // where *again is not 0 (may be null), A's are these
+    const float* partialA2;
+    int splitsA2;
     uint16_t *Wf, *Vf;
     float *Zt, *Xp, *Sig, *Gam;
     int slices, per, nkb;                       // (set by launch_basis_panels)

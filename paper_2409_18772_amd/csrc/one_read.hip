@@ -46,7 +46,8 @@ __device__ __forceinline__ float code_residual(float x, float lam, float s, cons
 //     added in pairs.  For R^T Y a wave has up to three tiles of 16 columns, whose sums stay in its registers for the whole run.
 //   * Y^T Y is added to a float64 matrix in LDS.
 // The sketch is multiplied by a reflection that leaves only its first column with a sum.  Residuals of floor rounding have a mean, so every
-// column of R Omega would be nearly the same vector, and T would have to take that out of R^T Y again; Q Q^T R is the same for both.
+// column of R Omega would be nearly the same vector, and T would have to take that out of R^T Y again; Q Q^T R is the same for both.  Where
+// Y is ill-conditioned all the same, or far from unit scale, a pass for R^T Q follows (PROJECT_AMPLIFICATION).
 // What bounds it: the phases between the barriers, one after the other, of two workgroups a CU that cover each other (what the 64 registers are
 // for).  100352 x 576: 93 us for 289 MB; without the product R^T Y 72, without Y 75, without the loads 86.  quant_sketch_rows_kernel and a pass
 // for R^T Q, which read X twice, 73 + 48 us; the call of 64 columns 203 -> 166 us.  (Eight waves of two rows with 128 registers spilled: 110 us.)

@@ -406,11 +406,13 @@ __global__ __launch_bounds__(256, NT <= 2 ? 4 : (NT <= 4 ? 3 : 2)) void orth_app
     const double* __restrict__ const M = first ? a0.M : a1.M;
     float* __restrict__ const Z = first ? a0.Z : a1.Z;
     const int nbY = first ? g0.nbY : g1.nbY, m = first ? a0.m : a1.m;
+    int* __restrict__ const again = first ? a0.again : a1.again;
     const int blk = first ? blockIdx.x : blockIdx.x - g0.nb;
     __shared__ double rowb[2][2][2 * LP];
     __shared__ double colb[2][2][LP];
     __shared__ double thrb[2][2];
     __shared__ double Ts[LP * LDT];
+    __shared__ double diag[NT == 1 ? LP : 1];           // squared lengths of Y's columns
     const int tid = threadIdx.x, ti = tid >> 4, tg = tid & 15;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, li = lane & 15, kq = lane >> 4;
     const int row_end = min(steps_fmt ? (n + 31) & ~31 : n, (blk + 1) * rows);      // (steps end in zeros)
@@ -454,6 +456,7 @@ __global__ __launch_bounds__(256, NT <= 2 ? 4 : (NT <= 4 ? 3 : 2)) void orth_app
         const int i = ti + 16 * ir;     // < LP; rows and columns >= ell enter as zeros
         thr[ir] = (i < ell && ti == tg) ? 1e-10 * mreg[ir][ir] : 0.0;
         pivot[ir] = 0.0;
+        if (NT == 1 && ti == tg) diag[ti] = i < ell ? mreg[ir][ir] : 0.0;
 #pragma unroll
         for (int kc = 0; kc < NT; ++kc) {
             const int c = tg + 16 * kc;
@@ -534,6 +537,17 @@ __global__ __launch_bounds__(256, NT <= 2 ? 4 : (NT <= 4 ? 3 : 2)) void orth_app
     }
     __syncthreads();
     typedef double v4d __attribute__((ext_vector_type(4)));
+    if (NT == 1 && again && blk == 0 && wave == 0) {
+        double amp = 0.0;
+#pragma unroll
+        for (int s = 0; s < KQ; ++s) amp += fabs(Ts[(kq * KQ + s) * LDT + li]) * sqrt(diag[kq * KQ + s]);
+        amp += __shfl_xor(amp, 16, 64);
+        amp += __shfl_xor(amp, 32, 64);
+        const double d = diag[li];              // (comparisons that fail for a NaN)
+        const bool good = amp <= PROJECT_AMPLIFICATION && (d == 0.0 || (d >= PROJECT_LEAST && d <= PROJECT_MOST));
+        const bool all = __all(good);
+        if (lane == 0) *again = all ? 0 : 1;
+    }
     if (NT == 1 && blk >= nbY) {
         const int r0 = (blk - nbY) * 64 + wave * 16;
         const double* mp = M + (size_t)min(r0 + li, m - 1) * LP + kq * KQ;
@@ -1568,13 +1582,15 @@ __global__ __launch_bounds__(1024) void basis_panels_kernel(BasisPanels a) {
     const bool isA = (int)blockIdx.x < a.slices;
     const int tid = threadIdx.x, r = a.r, sg = tid >> 8, e = tid & 255;
     const int first = isA ? blockIdx.x * a.per : blockIdx.x - a.slices, last = isA ? min(first + a.per, a.nkb) : first + 1;
-    const int cols = isA ? a.K : a.N, splits = isA ? a.splitsA : a.splitsB;
+    const bool second = isA && a.again && *a.again != 0;
+    const float* const partial = isA ? (second ? a.partialA2 : a.partialA) : a.partialB;
+    const int cols = isA ? a.K : a.N, splits = isA ? (second ? a.splitsA2 : a.splitsA) : a.splitsB;
     const int sb = sg * splits / 4, se = (sg + 1) * splits / 4;
     const size_t plane = (size_t)cols * 16;
     double x = 0.0;             // X[t][u] of thread 16 t + u
     for (int blk = first; blk < last; ++blk) {
         const int k0 = blk * 64;
-        const float* src = (isA ? a.partialA : a.partialB) + (size_t)min(k0 + e / 4, cols - 1) * 16 + (e % 4) * 4;
+        const float* src = partial + (size_t)min(k0 + e / 4, cols - 1) * 16 + (e % 4) * 4;
         const float w = isA ? a.QB[(size_t)min(k0 + tid / 16, a.K - 1) * 16 + tid % 16] : 0.f;
         float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
         for (int s0 = sb; s0 < se; s0 += 8) {

@@ -70,6 +70,7 @@ struct PassJob {
     float* partial;
     int ldx, rows, cols, chunk, nbx;        // nbx: workgroups of one range of the reduction
     QOut qo;
+    const int* run;             // (see PassOperand)
 };
 #define LRQ_PASS_JOB(J)                                                                                      \
     const float* __restrict__ const X = (J).X;                                                               \
@@ -1237,6 +1238,7 @@ __device__ __forceinline__ float4 load_cols(const float* __restrict__ rowp, int 
 template <int AXIS, bool TINY>
 __device__ __forceinline__ void resid_mul_t_body(const PassJob& job, QuantParams q, int bx, int by,
                                                  float* __restrict__ const red) {
+    if (job.run && *job.run == 0) return;               // (uniform)
     LRQ_PASS_JOB(job);
     constexpr int LP = 16;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -1590,6 +1592,7 @@ PassPair make_pair(const PassOperand* op, int nop, bool t_type, int rows_per_wg)
         j.ldx = o.ldx; j.rows = o.rows; j.cols = o.cols; j.chunk = plan.chunk;
         j.nbx = t_type ? ceil_div(o.cols, 64) : ceil_div(o.rows, rows_per_wg);
         j.qo = {o.amax, o.lam, o.s, o.codes};
+        j.run = o.run;
         p.nb[o.axis] = j.nbx * plan.splits;
     }
     for (int i = 0; i < 2; ++i) if (p.job[i].nbx == 0) p.job[i].nbx = 1;        // (an absent job: never indexed)

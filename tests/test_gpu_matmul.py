@@ -147,6 +147,54 @@ def test_both_products_of_a_single_read(M, K, r, p, q):
     test_short_rows_of_a_single_read(M, 48, K, r, p, q, o.FLOOR)
 
 
+def _tall_operand(kind, M, K, seed=61):
+    rng = np.random.default_rng(seed)
+    noise = rng.standard_normal((M, K))
+    name, _, size = kind.partition(" ")
+    if name == "scaled":                    # every entry
+        A = np.maximum(noise, 0.0) * float(size)
+    elif name == "factor":                  # rank 1 times 1 + noise
+        A = np.outer(rng.random(M) + 0.5, rng.random(K) + 0.5) * (1.0 + float(size) * noise)
+    elif name == "plus":                    # rank 1 plus noise
+        A = np.outer(rng.random(M) + 0.5, rng.random(K) + 0.5) + float(size) * noise
+    elif name == "graded":                  # columns over `size` powers of ten
+        A = noise * np.logspace(0.0, -float(size), K)
+    elif name == "columns":                 # a scale of its own for every column
+        A = np.maximum(noise, 0.0) * np.exp(float(size) * rng.standard_normal(K))
+    elif name == "means":                   # a mean of its own for every column
+        A = np.maximum(noise + float(size) * rng.standard_normal(K), 0.0)
+    elif name == "rank":                    # fewer dimensions than the sketch has columns, and entries that are codes themselves
+        A = np.rint(7.0 * rng.random((M, int(size))))[:, np.arange(K) % int(size)]
+    return A.astype(np.float32)
+
+
+@pytest.mark.parametrize("mode", [o.FLOOR, o.NEAREST])
+@pytest.mark.parametrize("kind", ["scaled 1e19", "scaled 1e12", "scaled 1e9", "scaled 1e-7", "scaled 1e-10", "scaled 1e-16", "scaled 1e-22", "scaled 1e-25",
+                                  "factor 1e-1", "factor 3e-2", "factor 1e-2", "factor 1e-4", "factor 1e-5", "plus 1e-1", "plus 1e-2",
+                                  "plus 1e-3", "graded 6", "columns 1", "columns 3", "means 1", "means 3", "rank 3", "rank 1"])
+def test_tall_operands_with_structure(kind, mode):
+    """Tall operands read once, q = 0, whose sample matrix is far from orthogonal or far from unit scale: C is as close to float64 as on a copy whose
+    row stride (K + 1) rules the one-read kernel out, where R^T Q is a product of its own.  Each of the two rounds C's two terms to
+    float32 once more than float64 does, 2^-24 kappa."""
+    import torch
+    import paper_2409_18772_amd as L
+    M, N, K, r = 28200, 24, 576, 8
+    A = _tall_operand(kind, M, K)
+    B = wl.random_matrix("normal", K, N, seed=62)
+    say("structured", kind, "mode", mode)
+    dA, dB = to_dev(A), to_dev(B)
+    ref = o.lrqmm(A, B, 4, r, 0, 0, seed=9, round_mode=mode)
+    wide = torch.zeros((M, K + 1), dtype=torch.float32, device="cuda")
+    wide[:, :K] = dA
+    D = torch.empty((M, N), dtype=torch.float32, device="cuda")
+    L.lrqmm_matmul_ex(wide[:, :K], dB, D, 4, r, 0, 0, seed=9, round_mode=mode)
+    d_general = rel_fro(ref["C"], to_np(D))
+    d = rel_fro(ref["C"], to_np(L.lrqmm_matmul(dA, dB, 4, r, 0, 0, seed=9, round_mode=mode)))
+    kappa = (np.linalg.norm(ref["C0"]) + np.linalg.norm(ref["C"] - ref["C0"])) / np.linalg.norm(ref["C"])
+    say("from float64: one read", d, "two", d_general, "kappa", kappa)
+    assert d <= 1.5 * d_general + 2.0 ** -24 * kappa
+
+
 def test_rank_zero_is_direct_quant_and_modes():
     import paper_2409_18772_amd as L
     A = wl.random_matrix("normal", 150, 200, seed=1)
