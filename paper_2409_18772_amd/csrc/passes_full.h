@@ -37,13 +37,18 @@ __device__ __forceinline__ void load_vec(const float* __restrict__ p, float (&v)
 template <>
 __device__ __forceinline__ void load_vec<1>(const float* __restrict__ p, float (&v)[1]) { v[0] = *p; }
 
-// T: the transposed pass.  OUTER: the scales go with the results (else with the reduction).  U steps of a wave are in flight.
+// T: the transposed pass.  OUTER: the scales go with the results (else with the reduction).  Two steps of a wave are in flight.  With four
+// (three for 48 columns and more) these were 126, 186 and 238 registers for 16, 32 and 48 columns, of 512 that a SIMD has for two such waves:
+// beside 48 columns no wave of the other chain's passes fitted a CU (1024 x 4096 x 4096 l = 40 352 us in place of 324, 512 x 4096 x 4096 330
+// / 313).  More steps gain nothing either where a call has the chip to itself, four / two, us: 256 x 512 x 8192 l = 8 147.0 / 141.3, 24
+// 204.5 / 195.7, 2000^3 24 170.7 / 165.8, 40 235.1 / 230.0, 1000 x 700 x 6000 24 220.7 / 209.0, 300 x 5000 x 1200 24 164.4 / 158.6; the exception
+// is 4096 x 512 x 4096 l = 24 in two chains, 224.5 / 231.4.
 // Scales that go with the reduction are loaded one value a lane and handed to the lanes through a few words of LDS of the wave's
 // own: loads return in order, so every load of a step has to be issued as far ahead as its X, and eight lambdas and eight
 // steps a lane would take 16 registers for each step in flight.
-template <int NT, int RT, bool T, bool OUTER, int PL, int U>
+template <int NT, int RT, bool T, bool OUTER, int PL>
 __device__ __forceinline__ void full_body(const FullJob& job, QuantParams q, int blk, int range, float* __restrict__ const lds) {
-    constexpr int LP = 16 * NT, OB = 16 * RT, LD = LP + 4;
+    constexpr int LP = 16 * NT, OB = 16 * RT, LD = LP + 4, U = 2;
     const float* __restrict__ const X = job.X;
     const float* __restrict__ const lam = job.lam;
     const float* __restrict__ const sc = job.sc;
@@ -310,18 +315,16 @@ __device__ __forceinline__ int strip_of(int id, int nb) {
     return x * per + min(x, rest) + i;
 }
 
-constexpr int full_steps(int NT, int RT) { return NT <= 2 || (RT == 1 && NT == 3) ? 4 : 2; }      // in flight, as the registers allow
-
 // Workgroups [0, nb0) work on job a (scales by row), the rest on job b (scales by column).
 template <int NT, bool T, int PL, int RTA, int RTB>
 __global__ __launch_bounds__(512, 2) void full_pair_kernel(FullJob a, FullJob b, int nb0, QuantParams q) {
     __shared__ __align__(16) float lds[full_lds(NT, RTA > RTB ? RTA : RTB)];
     if ((int)blockIdx.x < nb0) {
         const int id = blockIdx.x % a.nb, range = blockIdx.x / a.nb;
-        full_body<NT, RTA, T, !T, PL, full_steps(NT, RTA)>(a, q, T ? strip_of(id, a.nb) : id, range, lds);
+        full_body<NT, RTA, T, !T, PL>(a, q, T ? strip_of(id, a.nb) : id, range, lds);
     } else {
         const int id = (blockIdx.x - nb0) % b.nb, range = (blockIdx.x - nb0) / b.nb;
-        full_body<NT, RTB, T, T, PL, full_steps(NT, RTB)>(b, q, T ? strip_of(id, b.nb) : id, range, lds);
+        full_body<NT, RTB, T, T, PL>(b, q, T ? strip_of(id, b.nb) : id, range, lds);
     }
 }
 
