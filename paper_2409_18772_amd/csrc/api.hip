@@ -257,11 +257,15 @@ int planes_values(int p) { return p == LRQMM_PREC_BF16 ? 1 : (p == LRQMM_PREC_BF
 // 40 400 / 377, 80 636 / 614; 4000^3 24 338 / 332, 40 415 / 413, 80 658 / 649; 4096 x 4096 x 2048 24 269 / 241, 40 359 / 328; 2048 x 2048 x 4096 24 248 / 228; 4096^3
 // 10 280 / 271, 24 333 / 335, 40 400 / 408, 80 633 / 650; not with a short or a longer side: 4096 x 1024 x 4096 10 182 / 191, 1500 x 1500 x 6000 24 259 / 269,
 // 6000 x 3000 x 1600 270 / 278.
+// Few rows of A (a batch through a layer) keep the large operand's chain waiting at every one of its launches, two chains / together: N = K =
+// 4096, 128 rows l = 8 172 / 158, 24 232 / 218, 40 310 / 291, 80 523 / 518; 512 178 / 168, 242 / 233, 313 / 306, 535 / 534; 768 186 / 175, 247 / 241,
+// 320 / 320, 545 / 548; 1024 193 / 183, 255 / 251, 324 / 329, 565 / 563.  A narrow B does not: 4096 x 512 x 4096 163 / 171, 230 / 230, 292 / 300.
 bool two_chains(int M, int N, int K, int LP, int planes) {
     const long long a = (long long)M * K, b = (long long)K * N;
     if (a + b <= 13000000) return false;
-    const bool sides = std::max(std::max(M, N), K) <= 4096 && std::min(std::min(M, N), K) >= 2000;
-    return !(planes >= 2 && sides && (LP == 16 || std::max(a, b) <= FULL_ELEMENTS));
+    if (planes < 2 || std::max(std::max(M, N), K) > 4096) return true;
+    if (M <= 768) return false;
+    return !(std::min(std::min(M, N), K) >= 2000 && (LP == 16 || std::max(a, b) <= FULL_ELEMENTS));
 }
 
 // Whether the integer product (`tiles` tiles of 256 x 256, one per CU at a time) runs early, beside the small SVDs and the

@@ -294,6 +294,12 @@ def test_factorizations_together_and_in_two_chains(M, N, K, r, p):
     assert np.array_equal(to_np(_separate_calls(L, dA, dB, 8, r, p, 1, 9)), C)
 
 
+@pytest.mark.parametrize("M,N,K,r,p", [(768, 4096, 4096, 16, 8), (769, 4096, 4096, 16, 8), (100, 4096, 4096, 32, 8), (65, 3300, 4096, 24, 0),
+                                       (700, 3999, 3301, 64, 16), (768, 4097, 4000, 24, 8)])
+def test_few_rows_beside_a_large_operand(M, N, K, r, p):
+    """Both sides of the limit from which an A of few rows has a chain of its own, with the large operand's passes in either form."""
+    test_factorizations_together_and_in_two_chains(M, N, K, r, p)
+
 
 @pytest.mark.parametrize("M,N,K,r,p", [(2200, 600, 300, 20, 8), (300, 600, 2200, 17, 0), (2100, 300, 2500, 24, 8),
                                        (300, 2300, 700, 20, 0)])
