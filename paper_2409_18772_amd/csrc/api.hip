@@ -346,8 +346,14 @@ static TPartials t_partials(const Factor& f, int planes, bool projected = false)
     return {f.op.partial, planes >= 2 && f.op.ft > 1 ? f.op.ft : f.op.pt.splits};
 }
 
-// Whether the one-read kernel forms R^T Y as well: where R^T Q is the only other product and only its sums are asked for.
-static bool one_read_projects(int power_iters, bool stop_at_basis) { return power_iters == 0 && stop_at_basis; }
+// Whether the one-read kernel forms R^T Y as well: where R^T Q is the only other product and only its sums are asked for, and not
+// where Y is likely to be turned down (PROJECT_AMPLIFICATION): the columns of R Omega are as dependent as those of Omega, whose
+// amplification is above 4 in 5 % of the sketches of 16 columns with 64 rows, in 43 % of 8 with 16, and in none of 3000 with six
+// times as many rows as columns.  Both products / R Omega alone, 100352 rows, 64 columns of B, us: 16 values a row l = 4 98 / 107, 8
+// 124 / 111; 32 l = 8 97 / 111, 16 128 / 115; 64 l = 8 98 / 99; 112 l = 8 99 / 110; 576 l = 8 169 / 204.
+static bool one_read_projects(int power_iters, bool stop_at_basis, int cols, int rank) {
+    return power_iters == 0 && stop_at_basis && cols >= 6 * rank;
+}
 
 // How the first residual product of a factorization is formed.
 enum class FirstPass {
@@ -420,7 +426,7 @@ static void factor_launches(LaunchList& ops, const Factor* factors, int n, First
     // Y = R Omega
     if (first == FirstPass::one_read) {
         const Factor f = p->f[0];
-        if (one_read_projects(power_iters, stop_at_basis)) {
+        if (one_read_projects(power_iters, stop_at_basis, f.op.cols, rank)) {
             // R^T Q = (R^T Y) T: nothing reads the operand again, unless Y shows that this would be less accurate than R^T Q
             const int blocks = quant_project_blocks(f.op.rows);
             double *const gsum = f.w.M, *const msum = gsum + PROJECT_GROUPS * 256;
@@ -767,7 +773,10 @@ int lrqmm_matmul_ex(int M, int N, int K, int bits, int rank, int oversample, int
     // (in every precision mode: the one-read pass runs in float32, which the reduced modes allow; see the row limit)
     const bool short_rows = factored && !per_tensor && quant_sketch_rows_usable(A, lda, M, K, LP, w.Aq);
     const bool one_read = short_rows && one_read_pays(M, K);
-    const bool overlap = one_read || (factored && two_chains(M, N, K, LP, planes_subspace(precision)));
+    // (Such an operand that is not tall enough stays in one stream whatever its size: its passes are short beside the 95 us of two.  Two
+    // chains / together, us, l = 8: 24000 x 64 x 576 104 / 87, 24000 x 4096 x 576 266 / 264, 4000 x 24000 x 576 297 / 278, 300 x 24000 x 576 136 /
+    // 113; one power iteration 24000 x 64 x 576 156 / 155, 24000 x 4096 x 576 336 / 339, 30000 x 1024 x 432 211 / 204, 300 x 24000 x 576 204 / 186.)
+    const bool overlap = one_read || (factored && !short_rows && two_chains(M, N, K, LP, planes_subspace(precision)));
     // The one-read kernel leaves rows of bytes: its products are short and bound by the store of C.
     const bool pair = !factored && !per_tensor && quantize_pair_usable(M, N, K);
     const int packed = pair ? direct_format(M, N, K, bits) : (factored && !one_read ? packed_format(bits, K) : PK_NONE);
@@ -904,7 +913,7 @@ int lrqmm_matmul_ex(int M, int N, int K, int bits, int rank, int oversample, int
             GemmWs g;
             Arena ga(w.sub);
             carve_gemm(ga, M, N, K, rank, &g);
-            const TPartials ta = t_partials(f[0], pl_last, one_read && one_read_projects(power_iters, basis_panels)), tb = t_partials(f[1], pl_last);
+            const TPartials ta = t_partials(f[0], pl_last, one_read && one_read_projects(power_iters, basis_panels, K, rank)), tb = t_partials(f[1], pl_last);
             rc = launch_basis_panels({ta.p, tb.p, f[1].op.Y, ta.splits, tb.splits, N, K, rank, ta.again, ta.p2, ta.splits2,
                                       g.Wf, g.Vf, w.Zt, g.X, w.Sig, w.Gam}, pst);
             ready = {w.Aq, w.BqT, g.Wf, g.Vf, f[0].op.Y, w.Sig, f[0].w.s, f[1].w.s, g.X, w.Gam, w.Zt, g.Lp, g.Rp, M, N, K, rank,

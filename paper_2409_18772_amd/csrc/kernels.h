@@ -123,13 +123,21 @@ int launch_pass_full_t(const PassOperand* op, int nop, QuantParams q, int LP, hi
 // launched.
 #define LRQ_QSR_MAX_BLOCKS 512
 #define LRQ_QSR_MAX_COLS 576
-// Where lrqmm_matmul takes it, or quant_project_rows_kernel.  Below, both operands advance together in half the launches and on one stream:
-// a call on two streams takes 80 us and more whatever its size.  Together / one read, us per call (4 bits, 64 columns of B, sketch of 8, no
-// power iteration): K = 64 16384 rows 46 / 81, 65536 78 / 83, 100352 98 / 94; 144 32768 71 / 83, 65536 100 / 86; 288 32768 78 / 87, 65536
-// 127 / 101; 576 8192 57 / 95, 16384 65 / 95, 32768 106 / 94, 100352 217 / 164; one power iteration 65536 x 64 140 / 138, 32768 x 576 183 / 177,
-// 16384 x 576 118 / 152.
-#define LRQ_ONE_READ_ROWS 20000
-static inline bool one_read_pays(int rows, int cols) { return (long long)(rows - LRQ_ONE_READ_ROWS) * (cols < 64 ? 64 : cols) >= 4700000; }
+// Where lrqmm_matmul takes it, or quant_project_rows_kernel.  Below, both operands advance together in half the launches and on
+// one stream: a call on two streams takes 95 us and more whatever its size.  Together / one read, us per call (64 columns of B
+// unless stated, sketch of 8, no power iteration):
+//   K = 64   80000 rows 88 / 98, 100352 99 / 100 (16 columns of B 111 / 100, 512 172 / 167)
+//   K = 144  52000 88 / 97, 60000 94 / 98 (512 columns 129 / 119), 80000 115 / 99
+//   K = 288  36000 84 / 103, 44000 90 / 103, 52000 110 / 103
+//   K = 432  28000 80 / 104, 34000 103 / 101 (512 columns 141 / 131), 40000 108 / 105
+//   K = 576  24000 88 / 108, 30000 93 / 106, 33000 106 / 109, 40000 115 / 109
+// One power iteration: 80000 x 64 157 / 150, 60000 x 144 169 / 164, 44000 x 288 159 / 158, 34000 x 432 183 / 174, 30000 x 576 172 / 168.
+// Above 13 million elements the joint passes leave partial results, above 32768 rows their Gram workgroups take 128 rows.
+#define LRQ_ONE_READ_ROWS 25000     // more than these in any case
+static inline bool one_read_pays(int rows, int cols) {
+    return (long long)(rows - LRQ_ONE_READ_ROWS) * (cols < 64 ? 64 : cols) >= 4600000 ||
+           (rows > 32768 && (long long)rows * cols > 13000000);
+}
 bool quant_sketch_rows_usable(const float* X, int ldx, int rows, int cols, int LP, const int8_t* codes);
 int quant_sketch_rows_blocks(int rows);
 int launch_quant_sketch_rows(const float* X, int ldx, int rows, int cols, QuantParams q, const float* W, int LP,

@@ -147,6 +147,26 @@ def test_both_products_of_a_single_read(M, K, r, p, q):
     test_short_rows_of_a_single_read(M, 48, K, r, p, q, o.FLOOR)
 
 
+@pytest.mark.parametrize("M,K,r,p,q", [(96875, 16, 2, 0, 0), (96875, 64, 10, 0, 0), (96875, 64, 11, 0, 0), (56945, 144, 8, 0, 0), (40973, 288, 8, 0, 1),
+                                       (33855, 384, 8, 8, 0), (32769, 400, 16, 0, 0), (32769, 432, 8, 0, 0), (32769, 576, 8, 0, 0),
+                                       (32769, 576, 4, 4, 1)])
+def test_limits_of_a_single_read(M, K, r, p, q):
+    """The rows from which A is read once (quantization with one or both products): there C differs in bits from that of a copy whose
+    row stride rules those kernels out; with one row less it does not."""
+    import torch
+    import paper_2409_18772_amd as L
+    gen = torch.Generator(device="cuda").manual_seed(63)
+    wide = torch.empty((M, K + 1), device="cuda").normal_(generator=gen).clamp_(min=0.0)
+    B = torch.empty((K, 40), device="cuda").normal_(generator=gen)
+    for rows in (M - 1, M):
+        say("limit", rows, K, r, p, q)
+        C = L.lrqmm_matmul(wide[:rows, :K].contiguous(), B, 4, r, p, q, seed=9)
+        D = torch.empty_like(C)
+        L.lrqmm_matmul_ex(wide[:rows, :K], B, D, 4, r, p, q, seed=9)
+        assert torch.equal(C, D) == (rows < M)
+        assert rel_fro(to_np(C), to_np(D)) < TOL
+
+
 def _tall_operand(kind, M, K, seed=61):
     rng = np.random.default_rng(seed)
     noise = rng.standard_normal((M, K))
@@ -178,7 +198,7 @@ def test_tall_operands_with_structure(kind, mode):
     float32 once more than float64 does, 2^-24 kappa."""
     import torch
     import paper_2409_18772_amd as L
-    M, N, K, r = 28200, 24, 576, 8
+    M, N, K, r = 32800, 24, 576, 8
     A = _tall_operand(kind, M, K)
     B = wl.random_matrix("normal", K, N, seed=62)
     say("structured", kind, "mode", mode)
