@@ -88,9 +88,8 @@ SHORT_ROWS = [
 ]
 
 
-# From 8192 rows on the maxima, codes and sketch product of such an A come from one read: at that limit and beyond, whole
-# and ragged last tiles, the shortest and longest rows, unequal shares of the reduction, and three shapes that are tall
-# enough but not eligible (longer rows, also with several splits of B's shorter factor; a wider sketch).
+# Taller ones, below the rows from which A is read once (see test_limits_of_a_single_read): the joint passes over whole and ragged
+# last tiles, the shortest and longest rows, unequal shares of the reduction, longer rows and a wider sketch.
 TALL_SHORT_ROWS = [
     (8192, 64, 576, 8, 0, 0),
     (8193, 70, 96, 4, 4, 1),
@@ -165,6 +164,43 @@ def test_limits_of_a_single_read(M, K, r, p, q):
         L.lrqmm_matmul_ex(wide[:rows, :K], B, D, 4, r, p, q, seed=9)
         assert torch.equal(C, D) == (rows < M)
         assert rel_fro(to_np(C), to_np(D)) < TOL
+
+
+# Every block of 64 columns of the kernel that forms both products (q = 0, nothing truncated, at most a sixth as many sketch columns as A
+# has), then widths of the one that forms R Omega alone, by steps of 32 columns; whole and ragged last tiles.
+ONE_READ = [(96877, 16, 2, 0, 0), (96890, 64, 8, 0, 0), (82500, 80, 13, 0, 0), (60947, 128, 8, 0, 0), (48960, 192, 16, 0, 0), (47119, 208, 4, 0, 0),
+            (41920, 272, 8, 0, 0), (33861, 384, 16, 0, 0), (32773, 400, 8, 0, 0), (32784, 512, 12, 0, 0), (32775, 528, 8, 0, 0), (32777, 576, 16, 0, 0),
+            (96881, 16, 4, 0, 1), (96880, 32, 16, 0, 0), (96883, 64, 16, 0, 0), (72920, 96, 4, 4, 1), (53761, 160, 8, 8, 0), (47120, 208, 5, 0, 2),
+            (38700, 336, 16, 0, 1), (32771, 480, 8, 4, 0), (32779, 544, 8, 8, 1), (32784, 576, 12, 0, 1)]
+
+
+@pytest.mark.parametrize("mode,bits", [(o.FLOOR, 8), (o.NEAREST, 4), (o.NEAREST, 8)])
+@pytest.mark.parametrize("M,K,r,p,q", ONE_READ)
+def test_kernels_of_a_single_read(M, K, r, p, q, mode, bits):
+    """Both rounding modes and code widths in the kernels that read a tall A once, against the oracle; that they ran shows in the
+    bits, which differ from those of a copy whose row stride rules them out."""
+    import torch
+    import paper_2409_18772_amd as L
+    N = 16
+    A = wl.random_matrix("relu_normal", M, K, seed=64)
+    B = wl.random_matrix("normal", K, N, seed=65)
+    say("one read", M, K, "rank", r, "p", p, "q", q, "mode", mode, "bits", bits)
+    dA, dB = to_dev(A), to_dev(B)
+    C = to_np(L.lrqmm_matmul(dA, dB, bits, r, p, q, seed=9, round_mode=mode))
+    ref = o.lrqmm(A, B, bits, r, p, q, seed=9, round_mode=mode)
+    d = rel_fro(ref["C"], C)
+    say("gpu vs oracle", d, "tol", tol_for(ref))
+    assert d < tol_for(ref)
+    # A truncation (p > 0) between nearly equal singular values is not unique in float32: for the residuals of 72920 x 96, 4 bits, nearest,
+    # s_4 / (s_4 - s_5) = 234, so that roundings of 2^-24 turn the vectors at the cut by 234 times as much, and single elements of C by
+    # up to that many 2^-24 S, where the budget allows 44; the norm stays within its tolerance.
+    if p == 0:
+        check_elementwise(C, ref, r, what=f"one read {M}x{N}x{K}")
+    wide = torch.zeros((M, K + 1), dtype=torch.float32, device="cuda")
+    wide[:, :K] = dA
+    D = torch.empty((M, N), dtype=torch.float32, device="cuda")
+    L.lrqmm_matmul_ex(wide[:, :K], dB, D, bits, r, p, q, seed=9, round_mode=mode)
+    assert not np.array_equal(C, to_np(D))
 
 
 def _tall_operand(kind, M, K, seed=61):
