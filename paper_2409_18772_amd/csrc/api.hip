@@ -40,7 +40,7 @@ struct RsvdWs {
     float *lam, *s, *Wc, *Yr, *partial;
     double *gpart, *gram, *Ur, *Mv, *M;
     char* steps;
-    float* mpart;               // one-read kernel: partial R^T Y (may be absent)
+    float* mpart;               // one-read kernel: partial R^T Y (tall operands, like M)
     int* again;                 // ... and whether a pass for R^T Q follows
 };
 
@@ -58,17 +58,21 @@ size_t carve_rsvd(Arena& a, int rows, int cols, int axis, int LP, int rank, Rsvd
     t.s = a.take<float>(npad);
     t.Wc = a.take<float>((size_t)cols * LP);
     t.Yr = a.take<float>((size_t)rows * LP);
-    t.partial = a.take<float>(pass_partial_floats(rows, cols, LP));
+    // (the one-read kernel's Gram matrices and R^T Y, then their sums, lie where a pass leaves its partial results later)
+    const size_t partial = pass_partial_floats(rows, cols, LP) * sizeof(float);
+    const bool tall = axis == LRQMM_AXIS_ROW && rows > LRQ_ONE_READ_ROWS;       // (used for sketches of 16 columns alone)
+    const size_t values = (size_t)std::min(cols, LRQ_QSR_MAX_COLS) * 16, sums = PROJECT_GROUPS * (256 + values) * sizeof(double);
+    const size_t project = tall ? sums + quant_project_blocks(rows) * values * sizeof(float) : 0;
+    char* const shared = a.take<char>(std::max(partial, project));
+    t.partial = reinterpret_cast<float*>(shared);
+    t.M = reinterpret_cast<double*>(shared);            // Gram matrices, then R^T Y
+    t.mpart = shared ? reinterpret_cast<float*>(shared + sums) : nullptr;
     t.gpart = a.take<double>((size_t)nb * LP * LP);
     t.gram = a.take<double>((size_t)LP * LP);
     t.Ur = a.take<double>((size_t)LP * rank);
     t.Mv = a.take<double>((size_t)LP * rank);
-    t.steps = a.take<char>(steps_bytes(rows > cols ? rows : cols, LP));
-    if (axis == LRQMM_AXIS_ROW && rows > LRQ_ONE_READ_ROWS) {           // (used for sketches of 16 columns alone)
-        t.M = a.take<double>((size_t)PROJECT_GROUPS * (256 + std::min(cols, LRQ_QSR_MAX_COLS) * 16));       // Gram matrices, then R^T Y
-        t.mpart = a.take<float>((size_t)quant_project_blocks(rows) * std::min(cols, LRQ_QSR_MAX_COLS) * 16);
-        t.again = a.take<int>(1);
-    }
+    t.steps = a.take<char>(full_steps_bytes(rows, cols, LP));
+    if (tall) t.again = a.take<int>(1);
     if (w) *w = t;
     return a.off;
 }

@@ -110,6 +110,7 @@ int launch_resid_mul_t(const PassOperand* op, int nop, QuantParams q, int LP, hi
 // full_blocks(results, LP) Gram partials of it.  One operand or two of different axes.
 #define FULL_ELEMENTS 16200000      // of an operand with sides of up to 4096 (see two_chains)
 int pass_full_ranges(bool t_type, int rows, int cols, int ldx, int LP);     // 0: the products above
+size_t full_steps_bytes(int rows, int cols, int LP);   // of the longest factor in the order of steps; does not fall when an argument grows
 int full_blocks(int n, int LP);
 int full_blocks_most(int n, int LP);        // of any result of up to n rows
 int launch_pass_full_n(const PassOperand* op, int nop, QuantParams q, int LP, hipStream_t st, int planes = 3);

@@ -30,6 +30,12 @@ int pass_full_ranges(bool t_type, int rows, int cols, int ldx, int LP) {
     return ceil_div(steps, ceil_div(steps, most));
 }
 
+// Up to FULL_LONG of either side, and the rows of a tall operand of up to 13 million elements with 64 columns and more beside
+// sketches of 16.
+size_t full_steps_bytes(int rows, int cols, int LP) {
+    return max(steps_bytes(min(max(rows, cols), FULL_LONG), LP), steps_bytes(min(rows, 13000000 / 64), 16));
+}
+
 int launch_pass_full_n(const PassOperand* op, int nop, QuantParams q, int LP, hipStream_t st, int planes) {
     return launch_full_t<false>(op, nop, q, LP, st, planes);
 }

@@ -83,6 +83,24 @@ def test_workspace_of_an_empty_problem(M, N, K):
     assert status in ((0,) if M == 0 or N == 0 else (-1, -4))       # (-4: no GPU to look the static scratch up on)
 
 
+def test_workspace_counts_only_what_can_run():
+    """The sums of the kernel that reads a tall A once lie over the passes' partial results, and factors in the order of steps are
+    counted up to the longest that take that order."""
+    import paper_2409_18772_amd as L
+    if not os.path.exists(L.lib_path()):
+        pytest.skip("library not built")
+    size = L.lrqmm_workspace_bytes
+    # A sketch of 80 columns over 4096 values a row never reads A once: no step where tall operands begin, 25001 rows; a row more costs its
+    # codes and factors, and up to 64 rows of partial results (the kernel's sums would be 19 million bytes).
+    for rows in (20000, 25000, 32768):
+        assert size(rows + 1, 64, 4096, 64, 16) - size(rows, 64, 4096, 64, 16) < 1_000_000
+    # Without either the two calls take 86 and 592 million bytes; a row of 16 columns in the order of steps takes 96, the
+    # kernel's sums are 19 million of which 8 lie over partial results; for 80 columns 256 Gram partials an operand in place of 64 and
+    # 8192 rows in the order of steps.
+    assert size(100352, 64, 576, 8, 0) < 86e6 + 96 * 100352 + 12e6
+    assert size(100352, 64, 4096, 64, 16) < 592e6 + 96 * 100352 + 2 * (192 * 80 * 80 * 8 + 8192 * 480)
+
+
 def test_workspace_of_a_larger_problem_serves_a_smaller_one():
     """The size does not fall when an extent, the rank or the oversampling grows.  Extents around the limits of the launch
     plans (512 blocks of 64 rows, 1024 rows, 256 x 256 tiles) and pairs that the plans treat very differently."""
