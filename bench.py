@@ -204,14 +204,22 @@ def main():
     }
     # Quantization + factorization of one operand as one streaming job.  Algorithmic bytes: one read for the
     # group maxima, one per residual product (the first of them also writes the codes), 4 B per element each,
-    # plus 1 B per element of codes.  With rank 0 only the maxima and the codes remain.  Tall A with short rows (at least
-    # 8192 rows, K <= 576, a sketch of at most
-    # 16 columns) is the one case that gets by with fewer reads than this count: maxima, codes and the first
-    # product come from a single read there ("reads_performed").
-    # Up to 13 million operand elements (and no such A) both operands advance together, one launch per step for both:
-    # their stages span the same launches, so each reports both operands' time and is priced with both operands' bytes.
-    one_read_a = (w.rank > 0 and w.M >= 8192 and w.K % 16 == 0 and 16 <= w.K <= 576 and w.rank + w.oversample <= 16)
-    joint = w.rank > 0 and not one_read_a and w.M * w.K + w.K * w.N <= 13000000
+    # plus 1 B per element of codes.  With rank 0 only the maxima and the codes remain.  Tall A with short rows (K <= 576, a
+    # sketch of at most 16 columns) is the one case that gets by with fewer reads than this count: maxima, codes and the first
+    # product come from a single read there, and with neither power iterations nor truncation the last product as well
+    # ("reads_performed").
+    # Calls of up to 13 million operand elements, with such short rows or with sides of up to 4096 (and no such tall A) advance both
+    # operands together, one launch per step for both: their stages span the same launches, so each reports both operands'
+    # time and is priced with both operands' bytes.
+    ell = w.rank + w.oversample
+    short_rows = w.rank > 0 and w.K % 16 == 0 and 16 <= w.K <= 576 and ell <= 16
+    one_read_a = short_rows and ((w.M - 25000) * max(w.K, 64) >= 4600000 or (w.M > 32768 and w.M * w.K > 13000000))
+    reads_saved = 0 if not one_read_a else (2 if ell == w.rank and w.power_iters == 0 and w.K >= 6 * w.rank else 1)
+    sides = (w.M, w.N, w.K)
+    fits = ell <= 16 or max(w.M * w.K, w.K * w.N) <= 16200000
+    joint = w.rank > 0 and not one_read_a and (
+        short_rows or w.M * w.K + w.K * w.N <= 13000000
+        or (max(sides) <= 4096 and (w.M <= 768 or (min(sides) >= 2000 and fits))))
     for op, elems in (("a", w.M * w.K), ("b", w.K * w.N)):
         n_reads = (1 + passes) if w.rank > 0 else (1 if op == "a" else 2)
         job_ms = stages["quantize_" + op] + stages["rsvd_" + op]
@@ -221,7 +229,7 @@ def main():
         stage_info["rsvd_" + op].update(passes=passes)
         stage_info["quantize_and_factor_" + op] = {
             "ms": round(job_ms, 4), "operand_reads": n_reads, "both_operands": joint,
-            "reads_performed": n_reads - 1 if (op == "a" and one_read_a) else n_reads,
+            "reads_performed": n_reads - reads_saved if op == "a" else n_reads,
             "algorithmic_GBs": round(gbs, 1), "frac_hbm": round(gbs / PEAK_HBM_GBS, 4)}
     # which roof bounds the product: its algorithmic bytes (codes read once, 4-byte results written once, panels)
     # against its operations; below peak_ops / peak_bytes operations per byte the kernel is bound by memory

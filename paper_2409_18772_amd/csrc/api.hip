@@ -256,14 +256,24 @@ int planes_values(int p) { return p == LRQMM_PREC_BF16 ? 1 : (p == LRQMM_PREC_BF
 // Measured, together / two chains, us, sketches of 24, 40 and 80 columns (one power iteration): 1024^3 143 / 193 (24);
 // 2048^3 196 / 212, 271 / 285, 497 / 508; 3072^3 279 / 283, 368 / 357, 618 / 614; 4096^3 351 / 348, 445 / 434, 688 / 690;
 // 8192^3 1387 / 1366 (24), 2017 / 1958 (80).
-// Those are the passes of passes.hip.  With whole reductions a pass of both operands is short enough on its own up to sides of 4096, us, inputs
-// from memory, two chains / together: 2600^3 l = 10 181 / 166, 24 239 / 229, 40 311 / 301; 3300^3 24 287 / 278, 40 364 / 341, 80 592 / 570; 3700^3 24 328 / 309,
-// 40 400 / 377, 80 636 / 614; 4000^3 24 338 / 332, 40 415 / 413, 80 658 / 649; 4096 x 4096 x 2048 24 269 / 241, 40 359 / 328; 2048 x 2048 x 4096 24 248 / 228; 4096^3
-// 10 280 / 271, 24 333 / 335, 40 400 / 408, 80 633 / 650; not with a short or a longer side: 4096 x 1024 x 4096 10 182 / 191, 1500 x 1500 x 6000 24 259 / 269,
-// 6000 x 3000 x 1600 270 / 278.
-// Few rows of A (a batch through a layer) keep the large operand's chain waiting at every one of its launches, two chains / together: N = K =
-// 4096, 128 rows l = 8 172 / 158, 24 232 / 218, 40 310 / 291, 80 523 / 518; 512 178 / 168, 242 / 233, 313 / 306, 535 / 534; 768 186 / 175, 247 / 241,
-// 320 / 320, 545 / 548; 1024 193 / 183, 255 / 251, 324 / 329, 565 / 563.  A narrow B does not: 4096 x 512 x 4096 163 / 171, 230 / 230, 292 / 300.
+// Those are the passes of passes.hip.  With whole reductions a pass of both operands is short enough on its own up to sides of
+// 4096.  Two chains / together, us, inputs from memory, by sketch columns:
+//   2600^3              10 181 / 166    24 239 / 229    40 311 / 301
+//   3300^3                              24 287 / 278    40 364 / 341    80 592 / 570
+//   3700^3                              24 328 / 309    40 400 / 377    80 636 / 614
+//   4000^3                              24 338 / 332    40 415 / 413    80 658 / 649
+//   4096 x 4096 x 2048                  24 269 / 241    40 359 / 328
+//   2048 x 2048 x 4096                  24 248 / 228
+//   4096^3              10 280 / 271    24 333 / 335    40 400 / 408    80 633 / 650
+// and not with a short or a longer side: 4096 x 1024 x 4096 10 182 / 191, 1500 x 1500 x 6000 24 259 / 269, 6000 x 3000 x 1600
+// 24 270 / 278.  Sides between 1500 and 2000: 4096 x 4096 x 1700 40 321 / 316, 3500 x 1700 x 3500 40 318 / 317, 4000 x 1500 x 3500 24
+// 248 / 248.
+// Few rows of A (a batch through a layer) keep the large operand's chain waiting at every one of its launches; N = K = 4096:
+//   128 rows     8 172 / 158    24 232 / 218    40 310 / 291    80 523 / 518
+//   512          8 178 / 168    24 242 / 233    40 313 / 306    80 535 / 534
+//   768          8 186 / 175    24 247 / 241    40 320 / 320    80 545 / 548
+//   1024         8 193 / 183    24 255 / 251    40 324 / 329    80 565 / 563
+// A narrow B does not: 4096 x 512 x 4096 8 163 / 171, 24 230 / 230, 40 292 / 300.
 bool two_chains(int M, int N, int K, int LP, int planes) {
     const long long a = (long long)M * K, b = (long long)K * N;
     if (a + b <= 13000000) return false;

@@ -334,7 +334,9 @@ inline int full_group(int n, int LP) { return LP == 16 || n <= 4096 ? 1 : 2; }
 
 template <int NT, bool T, int PL>
 int dispatch_full(FullJob (&j)[2], QuantParams q, hipStream_t st) {
-    // as few tiles a workgroup as leave every CU one
+    // As few tiles a workgroup as leave every CU one, the operand with more workgroups first.  Both operands at two tiles where either
+    // is, us per call in place of (and half the kernels): 3072 x 1536 x 2048 24 columns 185 / 181, 40 258 / 252, 80 472 / 461, 2311 x 2600 x
+    // 1800 8 130 / 126, 24 193 / 185, 40 262 / 254; squares of 2100 to 2700 1 % faster.  (The order of addition is the same.)
     auto blocks = [&](int i) { return j[i].n ? ceil_div(j[i].n, 16 * j[i].rt) * j[i].ranges : 0; };
     while (blocks(0) + blocks(1) > 256) {
         const int i = blocks(0) >= blocks(1) ? 0 : 1;

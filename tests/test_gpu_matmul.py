@@ -141,8 +141,8 @@ def test_short_rows_of_a_single_read(M, N, K, r, p, q, mode):
                                        (29185, 512, 2, 0, 0), (28917, 528, 8, 0, 0), (28161, 576, 16, 0, 0), (28159, 576, 16, 0, 0),
                                        (28200, 576, 4, 4, 0), (28165, 576, 12, 0, 1), (44487, 192, 4, 4, 1)])
 def test_both_products_of_a_single_read(M, K, r, p, q):
-    """Every block count of the kernel that forms R Omega and R^T (R Omega) from one read of A, rows past its last tile, columns past its last
-    block, both sides of its limit; and the one that forms R Omega alone (truncation or a power iteration)."""
+    """Tall operands with short rows on both sides of the limits of a single read (see test_limits_of_a_single_read), rows past the last
+    tile, columns past the last block of 64, with and without truncation or a power iteration."""
     test_short_rows_of_a_single_read(M, 48, K, r, p, q, o.FLOOR)
 
 
