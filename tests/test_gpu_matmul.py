@@ -850,9 +850,8 @@ def test_call_can_be_captured_in_a_graph(shape):
     """The call only enqueues kernels and event waits (its clears are fill kernels), so it may be recorded
     into a HIP graph, side streams included; every replay must reproduce the eager result, with eager work
     and synchronizations between the replays.  First shape: both factorizations on the caller's stream, the integer product
-    on another (sketch of 32 columns, large-tile kernel); second: one stream; third and fourth: the persistent kernels for
-    short rows of A (their launchers ask the runtime for the device's CU count, which a capture has to tolerate), the
-    fourth with B's chain on the side stream; fifth: two chains; sixth: two chains and the early product."""
+    on another (sketch of 32 columns, large-tile kernel); second: one stream; third and fourth: short rows of A in one stream;
+    fifth: two chains; sixth: one stream and the early product."""
     import torch
     import paper_2409_18772_amd as L
     M, N, K, r, p, q = shape
@@ -886,6 +885,41 @@ def test_call_can_be_captured_in_a_graph(shape):
         step()                       # eager work between replays
         torch.cuda.synchronize()
         assert torch.equal(C, ref), i
+
+
+@pytest.mark.parametrize("shape", [(33000, 64, 576, 8, 0, 0), (33000, 64, 576, 8, 4, 0), (5000, 2100, 3000, 28, 4, 0)])
+def test_calls_on_several_streams_can_be_captured(shape):
+    """The same for the kernels that read a tall A once, B's chain on the side stream, and for two chains with the early product."""
+    test_call_can_be_captured_in_a_graph(shape)
+
+
+def test_captured_call_judges_the_operand_of_each_replay():
+    """Whether R^T Q is formed again is decided on the device: a captured call follows the values that A holds when it is replayed."""
+    import torch
+    import paper_2409_18772_amd as L
+    M, N, K, r = 33000, 40, 576, 8
+    kinds = [torch.from_numpy(_tall_operand(k, M, K)).cuda() for k in ("scaled 1", "factor 1e-4", "scaled 1e19")]
+    B = to_dev(wl.random_matrix("normal", K, N, seed=32))
+    ws = L.Workspace.for_problem(M, N, K, r, 0)
+    A, C = kinds[0].clone(), torch.empty((M, N), dtype=torch.float32, device="cuda")
+    refs = [L.lrqmm_matmul(x, B, 4, r, seed=7, workspace=ws).clone() for x in kinds]
+    torch.cuda.synchronize()
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):
+        L.lrqmm_matmul(A, B, 4, r, seed=7, workspace=ws, C=C)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        L.lrqmm_matmul(A, B, 4, r, seed=7, workspace=ws, C=C)
+    torch.cuda.synchronize()
+    for i in (0, 1, 0, 2, 1, 0):
+        A.copy_(kinds[i])
+        C.fill_(float("nan"))
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(C, refs[i]), i
 
 
 def test_capture_with_profiling_on_is_refused():
