@@ -50,7 +50,7 @@ __device__ __forceinline__ float code_residual(float x, float lam, float s, cons
 // Y is ill-conditioned all the same, or far from unit scale, a pass for R^T Q follows (PROJECT_AMPLIFICATION).
 // What bounds it: the phases between the barriers, one after the other, of two workgroups a CU that cover each other (what the 64 registers are
 // for).  100352 x 576: 93 us for 289 MB; without the product R^T Y 72, without Y 75, without the loads 86.  quant_sketch_rows_kernel and a pass
-// for R^T Q, which read X twice, 73 + 48 us; the call of 64 columns 203 -> 166 us.  (Eight waves of two rows with 128 registers spilled: 110 us.)
+// for R^T Q, which read X twice, 73 + 48 us; the call of 64 columns 203 -> 170 us.  (Eight waves of two rows with 128 registers spilled: 110 us.)
 template <int NB>       // blocks of 64 columns
 __global__ __launch_bounds__(1024, 8) void quant_project_rows_kernel(
     const float* __restrict__ X, int ldx, int rows, int cols, QuantParams q, const float* __restrict__ W,

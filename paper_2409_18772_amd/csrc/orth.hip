@@ -249,8 +249,8 @@ __global__ __launch_bounds__(64) void gram_sum_parts_kernel(GramJob a, GramJob b
 }
 
 // Gram matrices and R^T Y of quant_project_rows_kernel's workgroups, added in float64 in PROJECT_GROUPS contiguous groups (orth_apply_kernel
-// adds the groups): blockIdx.x 0 a group's Gram matrices, an entry a thread, the others 512 values of R^T Y each, two a thread.  496
-// partials of 576 x 16: 5.2 us; a thread per 16 bytes of 16 partials, all groups at once, 24 us (128 bytes at a time of every partial).
+// adds the groups): blockIdx.x 0 a group's Gram matrices, an entry a thread, the others 512 values of R^T Y each, two a thread.  480
+// partials of 576 x 16: 5.3 us; a thread per 16 bytes of 16 partials, all groups at once, 24 us (128 bytes at a time of every partial).
 __global__ __launch_bounds__(256) void project_sum_kernel(const double* __restrict__ gpart, const float* __restrict__ mpart, int blocks,
                                                           int values, double* __restrict__ gsum, double* __restrict__ msum) {
     constexpr int BATCH = 16;
